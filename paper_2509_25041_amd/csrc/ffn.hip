@@ -10,12 +10,15 @@
 // device; there is no host synchronisation).  The bf16 kernel is persistent (one
 // workgroup per compute unit walks the tiles); the fallback kernels size their
 // grid from an upper bound of the tile count and surplus blocks exit at once.
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "bf16.h"
 #include "common.h"
 #include "gemm_bf16_generic.h"
 #include "gemm_bf16_persist.h"
+#include "gemm_bf16_stream.h"
 #include "gemm_common.h"
 #include "gemm_f32.h"
 
@@ -64,9 +67,41 @@ static bool allow_full_lds(const void *kernel, const char *what) {
     return true;
 }
 
+// Weight-streaming kernel for at most strm::MAX_ROWS rows per segment.  At most one workgroup per strip of
+// weight rows and row of the batch finds work; with few of those each gets more than four wavefronts (a finer
+// split of K) until the chip holds about 8 wavefronts per compute unit.  More than that does not pay: 16 per
+// unit took 8.6 instead of 8.2 us on 4 busy segments, 32 took 10.4, and 32.9 instead of 28.8 us on 16; two
+// wavefronts per workgroup at the other end took 29.5 us.
+template <bool FUSED_UP>
+static int launch_stream(const GemmArgs &g, int max_rows, int64_t m_bound, int n_cu, hipStream_t st, const char *what) {
+    const int n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
+    const int n_seg = g.seg_off ? g.S : 1;
+    if ((int64_t)n_strips * n_seg > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
+    const int64_t busy = std::min<int64_t>(n_seg, m_bound) * n_strips;
+    const int mf = max_rows <= 16 ? 1 : max_rows <= 32 ? 2 : 4;
+    int waves = 4;
+    while (waves < strm::MAX_WAVES && busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::KSTEP) waves *= 2;
+    auto launch = [&](auto mf) {
+        constexpr int MF = decltype(mf)::value;
+        strm::gemm_bf16_stream_kernel<FUSED_UP, MF><<<(unsigned)(n_strips * n_seg), waves * 64, strm::lds_bytes(waves, MF), st>>>(g, n_strips);
+    };
+    if (mf == 1) launch(std::integral_constant<int, 1>{});
+    else if (mf == 2) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 4>{});
+    GRACE_LAUNCH_CHECK(what);
+    return GRACE_OK;
+}
+
+// max_rows: bound on the rows of one segment that the callers' routing gives (a token picks an expert once);
+// more rows are still computed correctly.  m_bound: bound on the rows of all segments.
 template <bool FUSED_UP, pers::Who WHO>
-static int launch_gemm(const GemmArgs &g, grace_dtype dt, int64_t m_bound, hipStream_t st, const char *what) {
+static int launch_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t m_bound, hipStream_t st, const char *what) {
     if (m_bound <= 0 || g.N <= 0 || g.K <= 0) return GRACE_OK;
+    if (dt == GRACE_BF16 && max_rows <= strm::MAX_ROWS && (g.kseg_len >= g.K || g.kseg_len % strm::KSTEP == 0)) {
+        const int n_cu = compute_units();
+        if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", what);
+        return launch_stream<FUSED_UP>(g, max_rows, m_bound, n_cu, st, what);
+    }
     const int n_seg = g.seg_off ? g.S : 1;
     const bool k_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK &&
                       n_seg <= pers::MAX_SEGMENTS;
@@ -143,7 +178,7 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     up.out = ws; up.ldo = f;
     up.seg_off = inst_off + g0; up.S = S; up.M_single = 0;
     up.share_state = state;
-    return launch_gemm<true, pers::EXPERTS>(up, dt, (int64_t)T * k, (hipStream_t)stream, who);
+    return launch_gemm<true, pers::EXPERTS>(up, dt, T, (int64_t)T * k, (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_up(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
@@ -181,7 +216,7 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     dn.out = y; dn.ldo = d;
     dn.seg_off = inst_off + g0; dn.S = S; dn.M_single = 0;
     dn.share_state = state; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
-    return launch_gemm<false, pers::EXPERTS>(dn, dt, (int64_t)T * k, (hipStream_t)stream, who);
+    return launch_gemm<false, pers::EXPERTS>(dn, dt, T, (int64_t)T * k, (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
@@ -236,7 +271,7 @@ static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, i
         // the row scatter rides on the persistent bf16 kernel when rows are whole 1 KB pieces; otherwise it
         // is a launch of its own ahead of the projection
         const size_t row_bytes = (size_t)d * (dt == GRACE_F32 ? 4 : 2);
-        const bool persistent = dt == GRACE_BF16 && d % pers::BK == 0 && d >= pers::MIN_K_STEPS * pers::BK;
+        const bool persistent = dt == GRACE_BF16 && T > strm::MAX_ROWS && d % pers::BK == 0 && d >= pers::MIN_K_STEPS * pers::BK;
         if (persistent && row_bytes % 1024 == 0 && (int64_t)T * k < ((int64_t)1 << 29) && row_bytes <= (size_t)INT32_MAX) {
             up.sc_x = x; up.sc_xp = xp; up.sc_pos = perm_pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = (int)row_bytes;
         } else {
@@ -244,7 +279,7 @@ static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, i
             if (rc != GRACE_OK) return rc;
         }
     }
-    return launch_gemm<true, pers::SHARED>(up, dt, T, (hipStream_t)stream, who);
+    return launch_gemm<true, pers::SHARED>(up, dt, T, T, (hipStream_t)stream, who);
 }
 
 extern "C" int grace_shared_ffn_up(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,
@@ -277,7 +312,7 @@ extern "C" int grace_shared_ffn_down(int32_t T, int32_t d, int32_t f, int32_t n_
     dn.N = d; dn.K = F; dn.kseg_len = f; dn.kseg_stride = (int64_t)d * f;  // K segment s lives in w_down[s]
     dn.out = y_shared; dn.ldo = d;
     dn.seg_off = nullptr; dn.S = 1; dn.M_single = T;
-    return launch_gemm<false, pers::SHARED>(dn, dt, T, (hipStream_t)stream, "shared_ffn down projection");
+    return launch_gemm<false, pers::SHARED>(dn, dt, T, T, (hipStream_t)stream, "shared_ffn down projection");
 }
 
 extern "C" int grace_shared_ffn(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,

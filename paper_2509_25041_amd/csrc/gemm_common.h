@@ -49,15 +49,28 @@ __device__ __forceinline__ void share_record(const GemmArgs &g) {
 }
 
 // Down projection: rows of the output that the previous step wrote for this rank and the current
-// segments no longer cover would keep old results; every workgroup zeroes its part of them before
-// it does anything else (they lie outside the rows this launch writes).
-__device__ __forceinline__ void share_clear_stale(const GemmArgs &g) {
+// segments no longer cover would keep old results; every workgroup zeroes its part of them (they lie outside
+// the rows this launch writes).  In two parts, so that a kernel can have the bounds' loads in flight while it works.
+struct StaleRows {
+    int prev_lo, prev_hi, now_lo, now_hi;  // as read
+};
+__device__ __forceinline__ StaleRows stale_rows(const GemmArgs &g) {
+    StaleRows s = {0, 0, 0, 0};
+    if (g.share_state) {
+        s.prev_lo = g.share_state[0];
+        s.prev_hi = g.share_state[1];
+        s.now_lo = g.seg_off[0];
+        s.now_hi = g.seg_off[g.S];
+    }
+    return s;
+}
+__device__ __forceinline__ void clear_stale_rows(const GemmArgs &g, const StaleRows &s) {
     if (!g.share_state) return;
     const int64_t n = g.share_rows;
-    const int64_t pl = max((int64_t)0, min(n, (int64_t)g.share_state[0]));
-    const int64_t ph = max(pl, min(n, (int64_t)g.share_state[1]));
-    const int64_t nl = max((int64_t)0, min(n, (int64_t)g.seg_off[0]));
-    const int64_t nh = max(nl, min(n, (int64_t)g.seg_off[g.S]));
+    const int64_t pl = max((int64_t)0, min(n, (int64_t)s.prev_lo));
+    const int64_t ph = max(pl, min(n, (int64_t)s.prev_hi));
+    const int64_t nl = max((int64_t)0, min(n, (int64_t)s.now_lo));
+    const int64_t nh = max(nl, min(n, (int64_t)s.now_hi));
     // stale rows: [pl, min(ph, nl)) and [max(pl, nh), ph)
     const int64_t a_end = max(pl, min(ph, nl)), b_begin = min(ph, max(pl, nh));
     const int64_t n_a = (a_end - pl) * g.share_row_vec, n_b = (ph - b_begin) * g.share_row_vec;
@@ -68,6 +81,7 @@ __device__ __forceinline__ void share_clear_stale(const GemmArgs &g) {
         y[v] = zero;
     }
 }
+__device__ __forceinline__ void share_clear_stale(const GemmArgs &g) { clear_stale_rows(g, stale_rows(g)); }
 
 // Which (slot, row range) does m-tile `mt` fall into?  Returns false for surplus tiles.
 template <int BM>

@@ -1,0 +1,81 @@
+"""Kernel variants that the launchers choose by size, each at the sizes where it can go wrong, against the
+oracle: edges of its tiles, remainders along every axis, both ends of its range."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2509_25041_amd as grace
+from test_gpu_parity import TOL, host, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def ffn_of_segments(seg_rows, T, k, d, f, dtype=torch.bfloat16, seed=0):
+    """Expert FFN of one rank that hosts every expert, on given row segments of a [T * k, d] buffer, and the
+    oracle's rows."""
+    E = len(seg_rows)
+    rng = np.random.default_rng(seed)
+
+    def normal(scale, *shape):
+        return torch.from_numpy((scale * rng.standard_normal(shape)).astype(np.float32)).cuda().to(dtype)
+
+    table = grace.GraceTable(E, 1, 1, [0], [1], list(range(E + 1)), [0] * E)
+    xp = normal(1.0, T * k, d)
+    wg, wu, wd = normal(0.05, E, f, d), normal(0.05, E, f, d), normal(0.05, E, d, f)
+    off = np.concatenate([[0], np.cumsum(seg_rows)]).astype(np.int32)
+    y = torch.full((T * k, d), 7.0, dtype=dtype, device="cuda")
+    grace.grace_expert_ffn(table, 0, xp, torch.from_numpy(off).cuda(), T, k, wg, wu, wd, y=y)
+    torch.cuda.synchronize()
+    x64, got = oracle.widen(host(xp)), oracle.widen(host(y))
+    want = np.full((T * k, d), 7.0)
+    for e in range(E):
+        lo, hi = int(off[e]), int(off[e + 1])
+        if hi > lo:
+            want[lo:hi] = oracle.ffn_rows(x64[lo:hi], *(oracle.widen(host(w[e])) for w in (wg, wu, wd)), threads=8)
+    return got, want, off
+
+
+def check_segments(got, want, off, tol):
+    for lo, hi in zip(off[:-1], off[1:]):
+        if hi > lo:
+            assert rel_err(got[lo:hi], want[lo:hi]) <= tol, (lo, hi)
+    np.testing.assert_array_equal(got[off[-1]:], want[off[-1]:])   # rows of no segment keep what they held
+
+
+@pytest.mark.parametrize("seg_rows,T,k,d,f", [
+    ([1], 1, 1, 2048, 1024),                        # one row: 16 wavefronts share K
+    ([0, 1, 0, 3], 4, 1, 136, 200),                 # K of 4 whole steps and 8 left over; strips past N in both projections
+    ([16, 15, 0, 1], 16, 4, 256, 96),               # full and nearly full fragment of 16 rows; fewer K steps than the ring is deep
+    ([17, 31, 32], 32, 3, 512, 352),                # two fragments
+    ([33, 48, 49, 64], 64, 4, 1024, 768),           # three and four fragments
+    ([64, 130, 5], 64, 4, 192, 72),                 # more rows in a segment than tokens: walked in pieces
+    ([20, 40], 20, 3, 4096, 40),                    # the same with two fragments; long K up, K of one step and a rest down
+])
+def test_few_rows_per_segment(seg_rows, T, k, d, f):
+    """The weight-streaming kernel of decode batches (at most 64 tokens)."""
+    got, want, off = ffn_of_segments(seg_rows, T, k, d, f)
+    check_segments(got, want, off, TOL["bf16"])
+
+
+@pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2)])
+def test_few_rows_shared_experts(T, d, f, n_shared):
+    """The same kernel on shared experts: the down projection's K runs through n_shared segments (a length that
+    is no multiple of the K step takes the generic kernel); the row scatter is a launch of its own here."""
+    rng = np.random.default_rng(T)
+
+    def normal(scale, *shape):
+        return torch.from_numpy((scale * rng.standard_normal(shape)).astype(np.float32)).cuda().to(torch.bfloat16)
+
+    x, wg, wu, wd = normal(1.0, T, d), normal(0.05, n_shared, f, d), normal(0.05, n_shared, f, d), normal(0.05, n_shared, d, f)
+    got = grace.grace_shared_ffn(x, wg, wu, wd)
+    pos = torch.from_numpy(rng.permutation(T * 2).astype(np.int32)).cuda()
+    ws = torch.zeros(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared), dtype=torch.uint8, device="cuda")
+    xp = torch.zeros((T * 2, d), dtype=torch.bfloat16, device="cuda")
+    grace.grace_shared_ffn_up_scatter(x, wg, wu, ws, pos, 2, xp)
+    two = grace.grace_shared_ffn_down(wd, ws, T)
+    torch.cuda.synchronize()
+    want = oracle.shared_ffn(oracle.widen(host(x)), tuple(oracle.widen(host(w)) for w in (wg, wu, wd)), threads=8)
+    assert rel_err(oracle.widen(host(got)), want) <= TOL["bf16"]
+    assert torch.equal(got, two)
+    np.testing.assert_array_equal(host(xp)[pos.cpu().numpy()], np.repeat(host(x), 2, axis=0))
