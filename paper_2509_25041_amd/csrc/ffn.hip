@@ -18,9 +18,9 @@
 #include "common.h"
 #include "gemm_bf16_generic.h"
 #include "gemm_bf16_persist.h"
-#include "gemm_bf16_stream.h"
 #include "gemm_common.h"
 #include "gemm_f32.h"
+#include "gemm_stream.h"
 
 namespace grace {
 
@@ -67,23 +67,44 @@ static bool allow_full_lds(const void *kernel, const char *what) {
     return true;
 }
 
-// Weight-streaming kernel for at most strm::MAX_ROWS rows per segment.  At most one workgroup per strip of
-// weight rows and row of the batch finds work; with few of those each gets more than four wavefronts (a finer
-// split of K) until the chip holds about 8 wavefronts per compute unit.  More than that does not pay: 16 per
-// unit took 8.6 instead of 8.2 us on 4 busy segments, 32 took 10.4, and 32.9 instead of 28.8 us on 16; two
-// wavefronts per workgroup at the other end took 29.5 us.
-template <bool FUSED_UP>
+// Can the streaming kernel load these operands?  Rows and K segments of whole 16-byte vectors, K segments (where
+// there are several) of whole steps, and offsets that fit its buffer loads.
+template <int EL>
+static bool stream_ok(const GemmArgs &g) {
+    const int n_kseg = (g.K + g.kseg_len - 1) / g.kseg_len;
+    const int64_t k_bytes = ((n_kseg - 1) * g.kseg_stride + g.kseg_len) * EL;
+    return g.K % (16 / EL) == 0 && (n_kseg == 1 || g.kseg_len % strm::kstep<EL>() == 0) &&
+           k_bytes + strm::MAX_ROWS * std::max(g.lda, g.ldb) * EL < (int64_t)strm::NO_DATA;
+}
+
+// Streaming kernel.  With at most strm::MAX_ROWS rows per segment, one workgroup per strip of weight rows and
+// segment.  At most one workgroup per strip and row of the batch finds work; with few of those each gets more
+// than four wavefronts (a finer split of K) until the chip holds about 8 wavefronts per compute unit.  More than
+// that does not pay (bf16): 16 per unit took 8.6 instead of 8.2 us on 4 busy segments, 32 took 10.4, and 32.9
+// instead of 28.8 us on 16; two wavefronts per workgroup at the other end took 29.5 us.
+template <bool FUSED_UP, int EL>
 static int launch_stream(const GemmArgs &g, int max_rows, int64_t m_bound, int n_cu, hipStream_t st, const char *what) {
     const int n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
     const int n_seg = g.seg_off ? g.S : 1;
+    if constexpr (EL == 4) {
+        if (max_rows > strm::MAX_ROWS && n_seg <= 256) {
+            const int64_t grid = ((m_bound / strm::MAX_ROWS + n_seg) * n_strips + 7) / 8 * 8;
+            if (grid > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
+            const int lds = strm::lds_bytes(4, strm::MAX_ROWS / 16);
+            if (n_seg <= 64) strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 1><<<(unsigned)grid, 256, lds, st>>>(g, n_strips);
+            else strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 4><<<(unsigned)grid, 256, lds, st>>>(g, n_strips);
+            GRACE_LAUNCH_CHECK(what);
+            return GRACE_OK;
+        }
+    }
     if ((int64_t)n_strips * n_seg > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
     const int64_t busy = std::min<int64_t>(n_seg, m_bound) * n_strips;
     const int mf = max_rows <= 16 ? 1 : max_rows <= 32 ? 2 : 4;
     int waves = 4;
-    while (waves < strm::MAX_WAVES && busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::KSTEP) waves *= 2;
+    while (waves < strm::MAX_WAVES && busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::kstep<EL>()) waves *= 2;
     auto launch = [&](auto mf) {
         constexpr int MF = decltype(mf)::value;
-        strm::gemm_bf16_stream_kernel<FUSED_UP, MF><<<(unsigned)(n_strips * n_seg), waves * 64, strm::lds_bytes(waves, MF), st>>>(g, n_strips);
+        strm::gemm_stream_kernel<FUSED_UP, EL, MF><<<(unsigned)(n_strips * n_seg), waves * 64, strm::lds_bytes(waves, MF), st>>>(g, n_strips);
     };
     if (mf == 1) launch(std::integral_constant<int, 1>{});
     else if (mf == 2) launch(std::integral_constant<int, 2>{});
@@ -97,10 +118,13 @@ static int launch_stream(const GemmArgs &g, int max_rows, int64_t m_bound, int n
 template <bool FUSED_UP, pers::Who WHO>
 static int launch_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t m_bound, hipStream_t st, const char *what) {
     if (m_bound <= 0 || g.N <= 0 || g.K <= 0) return GRACE_OK;
-    if (dt == GRACE_BF16 && max_rows <= strm::MAX_ROWS && (g.kseg_len >= g.K || g.kseg_len % strm::KSTEP == 0)) {
+    const bool stream16 = dt == GRACE_BF16 && max_rows <= strm::MAX_ROWS && stream_ok<2>(g);
+    const bool stream32 = dt == GRACE_F32 && stream_ok<4>(g);
+    if (stream16 || stream32) {
         const int n_cu = compute_units();
         if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", what);
-        return launch_stream<FUSED_UP>(g, max_rows, m_bound, n_cu, st, what);
+        return stream16 ? launch_stream<FUSED_UP, 2>(g, max_rows, m_bound, n_cu, st, what)
+                        : launch_stream<FUSED_UP, 4>(g, max_rows, m_bound, n_cu, st, what);
     }
     const int n_seg = g.seg_off ? g.S : 1;
     const bool k_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK &&

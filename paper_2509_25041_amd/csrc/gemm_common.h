@@ -114,6 +114,10 @@ struct Tile {
     int slot, m0, m_end;  // segment, first row, end of the tile's rows (the segment's end for its last tile)
 };
 
+struct Segment {
+    int slot, lo, hi, first_tile, tiles;  // its rows, its m-tiles
+};
+
 template <int SPL>
 struct SegTable {
     int lo[SPL], hi[SPL], base[SPL];
@@ -188,6 +192,28 @@ struct SegTable {
         t.slot = __builtin_amdgcn_readlane(slot, src);
         t.m0 = __builtin_amdgcn_readlane(m0, src);
         t.m_end = __builtin_amdgcn_readlane(m_end, src);
+        return t;
+    }
+
+    // the segment that holds m-tile mt < total, as scalars
+    __device__ __forceinline__ Segment segment(int mt, int lane) const {
+        Segment t = {0, 0, 0, 0, 0};
+        bool hit = false;
+#pragma unroll
+        for (int q = 0; q < SPL; ++q) {
+            const int tiles = (hi[q] - lo[q] + bm - 1) / bm;
+            if (mt >= base[q] && mt - base[q] < tiles) {
+                hit = true;
+                t = Segment{lane * SPL + q, lo[q], hi[q], base[q], tiles};
+            }
+        }
+        const unsigned long long owners = __ballot(hit);
+        const int src = owners ? __builtin_ctzll(owners) : 0;
+        t.slot = __builtin_amdgcn_readlane(t.slot, src);
+        t.lo = __builtin_amdgcn_readlane(t.lo, src);
+        t.hi = __builtin_amdgcn_readlane(t.hi, src);
+        t.first_tile = __builtin_amdgcn_readlane(t.first_tile, src);
+        t.tiles = __builtin_amdgcn_readlane(t.tiles, src);
         return t;
     }
 };

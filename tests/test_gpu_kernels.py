@@ -58,24 +58,41 @@ def test_few_rows_per_segment(seg_rows, T, k, d, f):
     check_segments(got, want, off, TOL["bf16"])
 
 
+@pytest.mark.parametrize("seg_rows,T,k,d,f", [
+    ([1, 0, 2], 3, 1, 1024, 256),                   # few rows: one workgroup per strip and segment
+    ([40, 0, 25], 64, 2, 100, 76),                  # K of 6 whole steps and 4 left over; strips past N
+    ([65, 64, 0, 1], 65, 2, 128, 256),              # pieces: 65 rows in two, one full, one row
+    ([0, 130, 17, 300], 300, 2, 548, 1388),         # pieces of one, two and three fragments with ragged ends
+    ([33, 97], 100, 2, 36, 77),                     # odd N up; the down projection's K takes the vector kernel
+    ([1] * 70 + [80] * 3, 160, 2, 64, 32),          # more segments than lanes
+])
+def test_f32_segments(seg_rows, T, k, d, f):
+    """fp32 on the matrix cores: one workgroup per strip (at most 64 tokens) or per strip and piece of a segment."""
+    got, want, off = ffn_of_segments(seg_rows, T, k, d, f, torch.float32)
+    check_segments(got, want, off, TOL["f32"])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2)])
-def test_few_rows_shared_experts(T, d, f, n_shared):
+def test_few_rows_shared_experts(T, d, f, n_shared, dtype):
     """The same kernel on shared experts: the down projection's K runs through n_shared segments (a length that
-    is no multiple of the K step takes the generic kernel); the row scatter is a launch of its own here."""
+    is no multiple of the K step takes the general kernel); the row scatter is a launch of its own here."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     rng = np.random.default_rng(T)
 
     def normal(scale, *shape):
-        return torch.from_numpy((scale * rng.standard_normal(shape)).astype(np.float32)).cuda().to(torch.bfloat16)
+        return torch.from_numpy((scale * rng.standard_normal(shape)).astype(np.float32)).cuda().to(tdt)
 
     x, wg, wu, wd = normal(1.0, T, d), normal(0.05, n_shared, f, d), normal(0.05, n_shared, f, d), normal(0.05, n_shared, d, f)
     got = grace.grace_shared_ffn(x, wg, wu, wd)
     pos = torch.from_numpy(rng.permutation(T * 2).astype(np.int32)).cuda()
-    ws = torch.zeros(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared), dtype=torch.uint8, device="cuda")
-    xp = torch.zeros((T * 2, d), dtype=torch.bfloat16, device="cuda")
+    ws = torch.zeros(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, grace.GRACE_F32 if dtype == "f32" else grace.GRACE_BF16),
+                     dtype=torch.uint8, device="cuda")
+    xp = torch.zeros((T * 2, d), dtype=tdt, device="cuda")
     grace.grace_shared_ffn_up_scatter(x, wg, wu, ws, pos, 2, xp)
     two = grace.grace_shared_ffn_down(wd, ws, T)
     torch.cuda.synchronize()
     want = oracle.shared_ffn(oracle.widen(host(x)), tuple(oracle.widen(host(w)) for w in (wg, wu, wd)), threads=8)
-    assert rel_err(oracle.widen(host(got)), want) <= TOL["bf16"]
+    assert rel_err(oracle.widen(host(got)), want) <= TOL[dtype]
     assert torch.equal(got, two)
     np.testing.assert_array_equal(host(xp)[pos.cpu().numpy()], np.repeat(host(x), 2, axis=0))
