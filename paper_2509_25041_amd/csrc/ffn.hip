@@ -17,6 +17,7 @@
 #include "bf16.h"
 #include "common.h"
 #include "gemm_bf16_generic.h"
+#include "gemm_bf16_mid.h"
 #include "gemm_bf16_persist.h"
 #include "gemm_common.h"
 #include "gemm_f32.h"
@@ -67,14 +68,14 @@ static bool allow_full_lds(const void *kernel, const char *what) {
     return true;
 }
 
-// Can the streaming kernel load these operands?  Rows and K segments of whole 16-byte vectors, K segments (where
-// there are several) of whole steps, and offsets that fit its buffer loads.
+// Can the kernels with buffer loads read these operands?  Rows of whole 16-byte vectors, K segments (where there are
+// several) of a multiple of `kseg_align`, and offsets that fit (at most 128 rows are addressed from one base).
 template <int EL>
-static bool stream_ok(const GemmArgs &g) {
+static bool stream_ok(const GemmArgs &g, int kseg_align = strm::kstep<EL>()) {
     const int n_kseg = (g.K + g.kseg_len - 1) / g.kseg_len;
     const int64_t k_bytes = ((n_kseg - 1) * g.kseg_stride + g.kseg_len) * EL;
-    return g.K % (16 / EL) == 0 && (n_kseg == 1 || g.kseg_len % strm::kstep<EL>() == 0) &&
-           k_bytes + strm::MAX_ROWS * std::max(g.lda, g.ldb) * EL < (int64_t)strm::NO_DATA;
+    return g.K % (16 / EL) == 0 && (n_kseg == 1 || g.kseg_len % kseg_align == 0) &&
+           k_bytes + 128 * std::max(g.lda, g.ldb) * EL < (int64_t)strm::NO_DATA;
 }
 
 // Streaming kernel.  With at most strm::MAX_ROWS rows per segment, one workgroup per strip of weight rows and
@@ -113,25 +114,71 @@ static int launch_stream(const GemmArgs &g, int max_rows, int64_t m_bound, int n
     return GRACE_OK;
 }
 
-// max_rows: bound on the rows of one segment that the callers' routing gives (a token picks an expert once);
-// more rows are still computed correctly.  m_bound: bound on the rows of all segments.
-template <bool FUSED_UP, pers::Who WHO>
-static int launch_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t m_bound, hipStream_t st, const char *what) {
-    if (m_bound <= 0 || g.N <= 0 || g.K <= 0) return GRACE_OK;
-    const bool stream16 = dt == GRACE_BF16 && max_rows <= strm::MAX_ROWS && stream_ok<2>(g);
-    const bool stream32 = dt == GRACE_F32 && stream_ok<4>(g);
-    if (stream16 || stream32) {
-        const int n_cu = compute_units();
-        if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", what);
-        return stream16 ? launch_stream<FUSED_UP, 2>(g, max_rows, m_bound, n_cu, st, what)
-                        : launch_stream<FUSED_UP, 4>(g, max_rows, m_bound, n_cu, st, what);
-    }
+template <bool FUSED_UP>
+static int launch_mid(const GemmArgs &g, int64_t m_bound, hipStream_t st, const char *what) {
+    const int n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
     const int n_seg = g.seg_off ? g.S : 1;
-    const bool k_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK &&
-                      n_seg <= pers::MAX_SEGMENTS;
-    if (dt == GRACE_BF16 && k_ok) {
-        const int n_cu = compute_units();
-        if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", what);
+    const int64_t grid = ((m_bound / mid::BM + n_seg) * n_strips + 63) / 64 * 64;
+    if (grid > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
+    if (g.kseg_len < g.K) mid::gemm_bf16_mid_kernel<FUSED_UP, true, 1><<<(unsigned)grid, mid::THREADS, 0, st>>>(g, n_strips);
+    else if (n_seg <= 64) mid::gemm_bf16_mid_kernel<FUSED_UP, false, 1><<<(unsigned)grid, mid::THREADS, 0, st>>>(g, n_strips);
+    else mid::gemm_bf16_mid_kernel<FUSED_UP, false, 4><<<(unsigned)grid, mid::THREADS, 0, st>>>(g, n_strips);
+    GRACE_LAUNCH_CHECK(what);
+    return GRACE_OK;
+}
+
+// Which kernel takes a launch.
+enum class Route { STREAM, MID, PERSIST, GENERIC, VECTOR_F32, FAILED };
+
+// max_rows: bound on the rows of one segment that the callers' routing gives (a token picks an expert once);
+// more rows are still computed correctly.  m_load: rows that the segments of a busy rank hold together.
+//
+// bf16, the streaming kernel up to 64 rows per segment: with 1 to 16 tokens it is 1.1 to 2 times as fast as the 96-row
+// kernel on every shape, and at 64 tokens on the down projections.  For more than 16 rows a gate+up projection whose
+// 64-column strips fill the compute units goes to the 96-row kernel (d = 2048, f = 1024, 16 segments, 64 tokens:
+// 22.2 -> 20.0 us; d = 4096, f = 14336, 64 tokens 67.8 -> 52.2 us; 12 strips x 16 segments: even).
+//
+// Above that, the 96-row kernel against 256 x 256 tiles: the large tiles take their time by whole rounds over the
+// compute units, 1.0 to 1.4 us per 64 of K and round however few rows a tile holds; the 96-row kernel takes 0.35 to
+// 0.55 us while its tiles fit one round and half the sum of its tiles after that.  It is taken while its tiles are at
+// most 3 (gate+up) or 2 (down, where the large tiles adapt their height) times the large kernel's rounds x
+// compute units.  Measured over 148 projections of five layer shapes at 70 to 4096 tokens: 6.71 ms in all
+// with this rule, 8.71 ms with large tiles only, 6.61 ms with the better one each time; one projection is
+// slower than with large tiles by 8 % (107 -> 118 us), the others by at most 3 %.
+template <bool FUSED_UP>
+static Route route_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t m_load) {
+    if (dt == GRACE_F32) return stream_ok<4>(g) ? Route::STREAM : Route::VECTOR_F32;
+    const int n_cu = compute_units();
+    if (n_cu <= 0) return Route::FAILED;
+    const int n_seg = g.seg_off ? g.S : 1;
+    const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(n_seg, m_load));
+    const int64_t strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+    const bool mid_ok = n_seg <= 256 && stream_ok<2>(g, 8);
+    if (max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && !(FUSED_UP && mid_ok && max_rows > 16 && busy * strips > n_cu * 3 / 4))
+        return Route::STREAM;
+    const bool persist_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK &&
+                            n_seg <= pers::MAX_SEGMENTS;
+    if (!mid_ok) return persist_ok ? Route::PERSIST : Route::GENERIC;
+    if (!persist_ok) return Route::MID;
+    const int64_t large_strips = (g.N + pers::Shape<FUSED_UP>::BN - 1) / pers::Shape<FUSED_UP>::BN;
+    const int64_t tiles = (m_load / mid::BM + busy) * strips, large_tiles = (m_load / pers::BM + busy) * large_strips;
+    const int64_t full = (large_tiles + n_cu - 1) / n_cu * n_cu;
+    return tiles <= full * (FUSED_UP ? 3 : 2) ? Route::MID : Route::PERSIST;
+}
+
+// m_bound: bound on the rows of all segments.
+template <bool FUSED_UP, pers::Who WHO>
+static int launch_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t m_load, int64_t m_bound, hipStream_t st, const char *what) {
+    if (m_bound <= 0 || g.N <= 0 || g.K <= 0) return GRACE_OK;
+    const Route route = route_gemm<FUSED_UP>(g, dt, max_rows, m_load);
+    const int n_cu = compute_units();
+    if (route == Route::FAILED || n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", what);
+    if (route == Route::STREAM)
+        return dt == GRACE_BF16 ? launch_stream<FUSED_UP, 2>(g, max_rows, m_bound, n_cu, st, what)
+                                : launch_stream<FUSED_UP, 4>(g, max_rows, m_bound, n_cu, st, what);
+    if (route == Route::MID) return launch_mid<FUSED_UP>(g, m_bound, st, what);
+    const int n_seg = g.seg_off ? g.S : 1;
+    if (route == Route::PERSIST) {
         // persistent large-tile kernel: one workgroup per compute unit, 160 KB of dynamic LDS
         using SH = pers::Shape<FUSED_UP>;
         const int ntn = (g.N + SH::BN - 1) / SH::BN;
@@ -144,7 +191,7 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t 
             if (!allow_full_lds((const void *)pers::gemm_bf16_persist_kernel<FUSED_UP, 4, WHO>, what)) return GRACE_EHIP;
             pers::gemm_bf16_persist_kernel<FUSED_UP, 4, WHO><<<grid, pers::THREADS, pers::LDS_BYTES, st>>>(g, ntn);
         }
-    } else if (dt == GRACE_BF16) {
+    } else if (route == Route::GENERIC) {
         constexpr int BN = FUSED_UP ? 64 : 128;
         const int64_t mt = m_bound / BM + (g.seg_off ? g.S : 1);
         const int ntn = (g.N + BN - 1) / BN;
@@ -185,6 +232,12 @@ static int expert_ffn_common(const char *who, const grace_table *table, int32_t 
     return GRACE_OK;
 }
 
+// Rows that a busy rank takes of a batch: three times its instances' share (hot experts have replicas, but a
+// rank that holds one of them is still the one the step waits for), at most every token once per instance or choice.
+static int64_t rank_load(const grace_table *table, int S, int32_t T, int32_t k) {
+    return std::min((int64_t)T * std::min(S, k), 3 * (int64_t)T * k * S / table->I);
+}
+
 static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
                          int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_gate, const void *w_up,
                          int32_t *state, void *ws, void *stream) {
@@ -202,7 +255,7 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     up.out = ws; up.ldo = f;
     up.seg_off = inst_off + g0; up.S = S; up.M_single = 0;
     up.share_state = state;
-    return launch_gemm<true, pers::EXPERTS>(up, dt, T, (int64_t)T * k, (hipStream_t)stream, who);
+    return launch_gemm<true, pers::EXPERTS>(up, dt, T, rank_load(table, S, T, k), (int64_t)T * k, (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_up(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
@@ -240,7 +293,7 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     dn.out = y; dn.ldo = d;
     dn.seg_off = inst_off + g0; dn.S = S; dn.M_single = 0;
     dn.share_state = state; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
-    return launch_gemm<false, pers::EXPERTS>(dn, dt, T, (int64_t)T * k, (hipStream_t)stream, who);
+    return launch_gemm<false, pers::EXPERTS>(dn, dt, T, rank_load(table, S, T, k), (int64_t)T * k, (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
@@ -295,7 +348,7 @@ static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, i
         // the row scatter rides on the persistent bf16 kernel when rows are whole 1 KB pieces; otherwise it
         // is a launch of its own ahead of the projection
         const size_t row_bytes = (size_t)d * (dt == GRACE_F32 ? 4 : 2);
-        const bool persistent = dt == GRACE_BF16 && T > strm::MAX_ROWS && d % pers::BK == 0 && d >= pers::MIN_K_STEPS * pers::BK;
+        const bool persistent = route_gemm<true>(up, dt, T, T) == Route::PERSIST;
         if (persistent && row_bytes % 1024 == 0 && (int64_t)T * k < ((int64_t)1 << 29) && row_bytes <= (size_t)INT32_MAX) {
             up.sc_x = x; up.sc_xp = xp; up.sc_pos = perm_pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = (int)row_bytes;
         } else {
@@ -303,7 +356,7 @@ static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, i
             if (rc != GRACE_OK) return rc;
         }
     }
-    return launch_gemm<true, pers::SHARED>(up, dt, T, T, (hipStream_t)stream, who);
+    return launch_gemm<true, pers::SHARED>(up, dt, T, T, T, (hipStream_t)stream, who);
 }
 
 extern "C" int grace_shared_ffn_up(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,
@@ -336,7 +389,7 @@ extern "C" int grace_shared_ffn_down(int32_t T, int32_t d, int32_t f, int32_t n_
     dn.N = d; dn.K = F; dn.kseg_len = f; dn.kseg_stride = (int64_t)d * f;  // K segment s lives in w_down[s]
     dn.out = y_shared; dn.ldo = d;
     dn.seg_off = nullptr; dn.S = 1; dn.M_single = T;
-    return launch_gemm<false, pers::SHARED>(dn, dt, T, T, (hipStream_t)stream, "shared_ffn down projection");
+    return launch_gemm<false, pers::SHARED>(dn, dt, T, T, T, (hipStream_t)stream, "shared_ffn down projection");
 }
 
 extern "C" int grace_shared_ffn(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,

@@ -1,0 +1,246 @@
+// bf16 MFMA grouped GEMM for ordinary batches: 96 rows x 128 weight rows per workgroup, any K that is a multiple of 8.
+//
+// Between decode batches (gemm_stream.h) and prefill (gemm_bf16_persist.h) most row segments hold fewer rows than
+// a tile of the large kernel, so the product is still bound by reading every weight once, while a few hot
+// segments need the matrix cores.  256 x 256 tiles leave compute units without work there (16 segments of an
+// expert width of 1024 make about 150 tiles) and one workgroup per compute unit waits alone for its weights.
+//
+// A workgroup of four wavefronts takes up to 96 rows of a segment and 128 weight rows (gate+up: 64 of each
+// matrix); two fit a compute unit.  The wavefronts split the weight rows, and everything is loaded into registers
+// AHEAD steps of 64 K ahead (weights in flight per compute unit: 128 KB, twice that for up to 32 rows), in whole
+// 128-byte lines: 8 lanes per row.  Loading weights in the MFMA's own layout (row = lane % 16) instead touches a
+// line per lane and makes the address unit the bound (decode batch of 512: 48 / 29 instead of 38 / 23 us for the
+// two projections).  One step ahead of its use a step's data goes to one of two LDS buffers: the activation rows,
+// which all four wavefronts read, and each wavefront's own weights (16-byte chunk c of row r at
+// c ^ ((r >> 1) & 7): no bank conflicts), with one barrier per step.  The order of fragment reads and MFMAs is
+// fixed, so that a read has a pass of MFMAs to arrive.  Loads past K, past the piece's rows or past N are given
+// an offset outside the buffer descriptor's range: they read nothing and give zeros, so every step is the same
+// code whatever K is.
+//
+// Pieces of a segment have one size (a multiple of 16, at most 96).  Workgroups are numbered by segment, strip
+// of weight rows, piece, and dealt to the XCDs in 64 runs of equal length (workgroups go to the XCDs round-robin):
+// pieces that read the same weights run next to each other on one L2, and every XCD gets hot and cold segments
+// (8 runs: 42 instead of 39 us on the batch of 512).
+//
+// Measured, 256 x 256 tiles -> this kernel (up / down projection, us): d = 2048, f = 1024, 16 segments, 70 tokens
+// 33 / 21 -> 21 / 14, 512 tokens 51 / 27 -> 38 / 23 (134 + 67 MB: 3.5 / 2.9 TB/s, of which about 7 us are launch,
+// segment table and first loads); d = 2048, f = 768, 16 segments, 1000 tokens 46 -> 26 (up); d = 4096,
+// f = 14336, one segment, 512 tokens 87 / 229 -> 75 / 120.  K that is no multiple of 64 took a kernel without
+// prefetch before: 3001 rows, N = 2048, K = 2 x 352 58 -> 20 us.
+#pragma once
+#include "bf16.h"
+#include "gemm_common.h"
+
+namespace grace {
+namespace mid {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+
+constexpr int BM = 96, BK = 64, THREADS = 256;
+constexpr int ROW_BYTES = BK * 2, A_BYTES = BM * ROW_BYTES, B_WAVE_BYTES = 32 * ROW_BYTES, LDS_BYTES = 2 * A_BYTES + 8 * B_WAVE_BYTES;
+constexpr uint32_t NO_DATA = 0x80000000u;   // an offset past the descriptor's range
+
+template <bool FUSED_UP>
+struct Shape {
+    static constexpr int BN = FUSED_UP ? 64 : 128;    // output columns per workgroup
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const char *base) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)NO_DATA, 0x00020000);
+}
+__device__ __forceinline__ u32x4_t load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, 0);
+}
+__device__ __forceinline__ int chunk_at(int row, int c) { return row * ROW_BYTES + ((c ^ ((row >> 1) & 7)) * 16); }
+
+// MF: activation fragments of 16 rows.  SEG_K: the weights' K axis is cut in segments (shared experts' down
+// projection), of any length.
+template <bool FUSED_UP, bool SEG_K, int MF>
+__device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, char *smem) {
+    constexpr int AHEAD = MF == 2 ? 8 : MF == 4 ? 6 : 4;   // steps in flight: what 256 registers hold (even)
+    constexpr int AL = MF / 2;   // activation loads per thread and step: 32 rows each
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, q = lane >> 4;
+    const int nk = (g.K + BK - 1) / BK;
+
+    // ---- load sources ----
+    const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 2);
+    uint32_t a_off[AL];
+    const int a_chunk = tid & 7;
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+        const int row = i * 32 + (tid >> 3);
+        a_off[i] = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 2) + (uint32_t)a_chunk * 16u : NO_DATA;
+    }
+    const int wn = n0 + wave * (FUSED_UP ? 16 : 32);   // first output column of the wavefront
+    const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 2;
+    const auto b0_rsrc = rsrc_of((const char *)g.B0 + b_first);
+    const auto b1_rsrc = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
+    // lane: row lane / 8 of every 8, 16-byte chunk lane % 8 (FUSED_UP: rows 0 .. 15 gate, 16 .. 31 up)
+    const int b_row = lane >> 3, b_chunk = lane & 7;
+    uint32_t b_off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = FUSED_UP ? (i & 1) * 8 + b_row : i * 8 + b_row;
+        b_off[i] = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 2) + (uint32_t)b_chunk * 16u : NO_DATA;
+    }
+    char *sb = smem + 2 * A_BYTES + wave * 2 * B_WAVE_BYTES;
+    // K of the next weight loads (scalar), SEG_K: this lane's position in its K segment and the byte
+    // distance that the segments before it add
+    int bk = 0, bseg = b_chunk * 8;
+    uint32_t bjump = 0u;
+
+    u32x4_t ra[AHEAD][AL], rb[AHEAD][4];
+    f32x4_t acc[MF][2];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+    int ak = 0;   // K of the next activation loads (scalar)
+    auto load_a = [&](int set) {
+        const uint32_t none = ak + a_chunk * 8 < g.K ? 0u : NO_DATA;
+#pragma unroll
+        for (int i = 0; i < AL; ++i) ra[set][i] = load16(a_rsrc, a_off[i] | none, (uint32_t)ak * 2u);
+        ak += BK;
+    };
+    auto store_a = [&](int set, int buf) {
+#pragma unroll
+        for (int i = 0; i < AL; ++i)
+            *(u32x4_t *)(smem + buf * A_BYTES + chunk_at(i * 32 + (tid >> 3), a_chunk)) = ra[set][i];
+    };
+    auto load_b = [&](int set) {
+        uint32_t none = bk + b_chunk * 8 < g.K ? 0u : NO_DATA;
+        if (SEG_K) {
+            while (bseg >= g.kseg_len) {
+                bseg -= g.kseg_len;
+                bjump += (uint32_t)((g.kseg_stride - g.kseg_len) * 2);
+            }
+            none += bjump;
+            bseg += BK;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            rb[set][i] = load16(FUSED_UP && i >= 2 ? b1_rsrc : b0_rsrc, SEG_K ? (b_off[i] + none) | (b_off[i] & NO_DATA) | (none & NO_DATA) : b_off[i] | none, (uint32_t)bk * 2u);
+        bk += BK;
+    };
+    auto store_b = [&](int set, int buf) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *(u32x4_t *)(sb + buf * B_WAVE_BYTES + chunk_at(i * 8 + b_row, b_chunk)) = rb[set][i];
+    };
+    // Two groups of 32 K.  The second group's fragments are read while the first is multiplied, each
+    // activation fragment into the registers that its predecessor has just freed.
+    bf16x8_t fa[MF], fb[2][2];
+    auto read_b = [&](int gk, int buf) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fb[gk][j] = *(const bf16x8_t *)(sb + buf * B_WAVE_BYTES + chunk_at(j * 16 + r, gk * 4 + q));
+    };
+    auto read_a = [&](int i, int gk, int buf) { fa[i] = *(const bf16x8_t *)(smem + buf * A_BYTES + chunk_at(i * 16 + r, gk * 4 + q)); };
+    auto mma = [&](int i, int gk) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[gk][j], fa[i], acc[i][j], 0, 0, 0);
+    };
+    auto compute = [&](int buf) {
+        read_b(0, buf);
+#pragma unroll
+        for (int i = 0; i < MF; ++i) read_a(i, 0, buf);
+        read_b(1, buf);
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            mma(i, 0);
+            read_a(i, 1, buf);
+        }
+#pragma unroll
+        for (int i = 0; i < MF; ++i) mma(i, 1);
+        __builtin_amdgcn_sched_group_barrier(0x100, MF + 4, 0);   // LDS reads
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);    // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * MF, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // ---- K loop: step s multiplies LDS buffer s % 2 with weight set s % AHEAD ----
+    // The activation loads go out ahead of the weights': the wait for them at the end of the next step then leaves
+    // that step's and the following one's weights in flight.
+    auto step = [&](int p) {
+        load_a(p % AHEAD);
+        load_b(p);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(p & 1);
+        store_a((p + 1) % AHEAD, (p + 1) & 1);
+        store_b((p + 1) % AHEAD, (p + 1) & 1);
+        __syncthreads();
+    };
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p) {
+        load_a(p);
+        load_b(p);
+    }
+    store_a(0, 0);
+    store_b(0, 0);
+    __syncthreads();
+    int s0 = 0;
+    for (; s0 + AHEAD <= nk; s0 += AHEAD) {
+#pragma unroll
+        for (int p = 0; p < AHEAD; ++p) step(p);
+    }
+#pragma unroll
+    for (int p = 0; p < AHEAD - 1; ++p) {
+        if (s0 + p >= nk) break;
+        step(p);
+    }
+
+    // ---- epilogue: element v of lane l of a block is output column 4 * (l / 16) + v, row l % 16 ----
+    uint16_t *out = (uint16_t *)g.out;
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+        const int row = m0 + i * 16 + r;
+        if (row >= m_end) continue;
+#pragma unroll
+        for (int j = 0; j < (FUSED_UP ? 1 : 2); ++j) {
+            const int col = wn + j * 16 + 4 * q;
+            if (col >= g.N) continue;   // N is a multiple of 8
+            float h[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                h[v] = acc[i][j][v];
+                if (FUSED_UP) h[v] = h[v] * __frcp_rn(1.0f + __expf(-h[v])) * acc[i][1][v];
+            }
+            *(uint2 *)(out + (int64_t)row * g.ldo + col) = make_uint2(pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3]));
+        }
+    }
+}
+
+// SEG_PER_LANE: 1 for up to 64 row segments, 4 for up to 256.  The grid covers the launcher's bound on the pieces;
+// the rest exits.
+template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE>
+__global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArgs g, int n_strips) {
+    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
+    const int lane = (int)threadIdx.x & 63;
+    StaleRows stale;
+    if (!FUSED_UP) stale = stale_rows(g);   // in flight during the work, used at the end
+    SegTable<SEG_PER_LANE> segs;
+    segs.load(g, lane);
+    segs.cut(lane, BM);
+    const int total = segs.total * n_strips, xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
+    const int len = (total + 63) >> 6, chunk = j / max(len, 1), t = (xcd + 8 * chunk) * len + (j - chunk * len);
+    if (chunk < 8 && t < total) {
+        const Segment s = segs.segment(t / n_strips, lane);
+        const int in_seg = t - s.first_tile * n_strips, strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
+        const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
+        const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows), n0 = strip * Shape<FUSED_UP>::BN;
+        if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6>(g, s.slot, m0, m_end, n0, smem);
+        else if (m_end - m0 > 32) tile_body<FUSED_UP, SEG_K, 4>(g, s.slot, m0, m_end, n0, smem);
+        else if (m_end > m0) tile_body<FUSED_UP, SEG_K, 2>(g, s.slot, m0, m_end, n0, smem);
+    }
+    if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
+}
+
+}  // namespace mid
+}  // namespace grace

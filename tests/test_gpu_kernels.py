@@ -59,6 +59,33 @@ def test_few_rows_per_segment(seg_rows, T, k, d, f):
 
 
 @pytest.mark.parametrize("seg_rows,T,k,d,f", [
+    ([1], 70, 1, 2048, 1024),                       # one row, long K
+    ([0, 1, 0, 3, 16, 17, 33], 70, 2, 136, 200),    # K of whole steps and 8 left over; strips past N
+    ([32, 33, 64, 65, 96, 97], 97, 4, 192, 72),     # edges of the pieces of two, four and six fragments
+    ([0, 200, 300], 300, 2, 448, 352),              # several pieces; K of half a step, fewer steps than are loaded ahead
+    ([100, 40], 100, 2, 64, 8),                     # K of one step up, of 8 down
+    ([130, 7], 130, 2, 8, 64),
+    ([2] * 70 + [150, 1], 150, 4, 64, 40),          # more segments than lanes
+])
+def test_ordinary_batches(seg_rows, T, k, d, f):
+    """The kernel between decode batches and large tiles."""
+    got, want, off = ffn_of_segments(seg_rows, T, k, d, f)
+    check_segments(got, want, off, TOL["bf16"])
+
+
+def test_up_projection_of_decode_batches():
+    """More than 16 tokens whose gate+up strips fill the chip: streaming kernel for the down projection only."""
+    got, want, off = ffn_of_segments([17, 0, 40, 9], 40, 2, 256, 16 * 1024 + 24)
+    check_segments(got, want, off, TOL["bf16"])
+
+
+def test_large_tiles():
+    """Large batches keep the 256 x 256 tiles."""
+    got, want, off = ffn_of_segments([4700, 0, 257, 43], 5000, 1, 128, 2048)
+    check_segments(got, want, off, TOL["bf16"])
+
+
+@pytest.mark.parametrize("seg_rows,T,k,d,f", [
     ([1, 0, 2], 3, 1, 1024, 256),                   # few rows: one workgroup per strip and segment
     ([40, 0, 25], 64, 2, 100, 76),                  # K of 6 whole steps and 4 left over; strips past N
     ([65, 64, 0, 1], 65, 2, 128, 256),              # pieces: 65 rows in two, one full, one row
@@ -73,10 +100,10 @@ def test_f32_segments(seg_rows, T, k, d, f):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2)])
-def test_few_rows_shared_experts(T, d, f, n_shared, dtype):
-    """The same kernel on shared experts: the down projection's K runs through n_shared segments (a length that
-    is no multiple of the K step takes the general kernel); the row scatter is a launch of its own here."""
+@pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2), (97, 520, 40, 3)])
+def test_shared_experts_small_batches(T, d, f, n_shared, dtype):
+    """Shared experts: the down projection's K runs through n_shared segments (lengths below, at and off the K step);
+    the row scatter is a launch of its own here."""
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     rng = np.random.default_rng(T)
 
