@@ -6,7 +6,11 @@
 
 namespace grace {
 
-template <bool BF16>
+// Bound by HBM for large batches, by the chain position -> row for small ones: positions and rows of AHEAD
+// choices are loaded before the first is used (k = 8, d = 2048, 1 ahead -> 4: 1 token 5.6 -> 3.2 us, 64 tokens
+// 6.1 -> 3.8 us, 512 tokens 7.5 -> 5.4 us).  With AHEAD > 1 an absent row loads row 0, which is not added: a branch
+// around each load makes the loads wait for one another (4.5 / 5.3 / 6.8 us).
+template <bool BF16, int AHEAD>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ y, const int32_t *__restrict__ perm_pos,
                                                       const float *__restrict__ topk_weight, int k, int row_vec,
                                                       int64_t n_rows, const uint4 *__restrict__ y_shared,
@@ -17,20 +21,36 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ 
         float acc[NV];
 #pragma unroll
         for (int i = 0; i < NV; ++i) acc[i] = 0.0f;
-        for (int j = 0; j < k; ++j) {
-            const int32_t p = perm_pos[t * k + j];
-            if (p < 0 || p >= n_rows) continue;
-            const float w = topk_weight[t * k + j];
-            const uint4 v = nt_load16(&y[(int64_t)p * row_vec + c]);
-            float f[NV];
-            if constexpr (BF16) unpack_bf16x8(v, f); else unpack_f32x4(v, f);
+        uint4 vs = make_uint4(0u, 0u, 0u, 0u);
+        if (y_shared) vs = y_shared[t * row_vec + c];
+        for (int j0 = 0; j0 < k; j0 += AHEAD) {
+            uint4 v[AHEAD];
+            float w[AHEAD];
+            int32_t p[AHEAD];
+            bool row[AHEAD];   // uniform
 #pragma unroll
-            for (int i = 0; i < NV; ++i) acc[i] = fmaf(w, f[i], acc[i]);
+            for (int i = 0; i < AHEAD; ++i) {
+                const int64_t a = t * k + min(j0 + i, k - 1);
+                p[i] = perm_pos[a];
+                w[i] = topk_weight[a];
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                row[i] = j0 + i < k && p[i] >= 0 && p[i] < n_rows;
+                if (AHEAD > 1 || row[i]) v[i] = nt_load16(&y[(int64_t)(row[i] ? p[i] : 0) * row_vec + c]);
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (!row[i]) continue;
+                float f[NV];
+                if constexpr (BF16) unpack_bf16x8(v[i], f); else unpack_f32x4(v[i], f);
+#pragma unroll
+                for (int e = 0; e < NV; ++e) acc[e] = fmaf(w[i], f[e], acc[e]);
+            }
         }
         if (y_shared) {
-            const uint4 v = y_shared[t * row_vec + c];
             float f[NV];
-            if constexpr (BF16) unpack_bf16x8(v, f); else unpack_f32x4(v, f);
+            if constexpr (BF16) unpack_bf16x8(vs, f); else unpack_f32x4(vs, f);
 #pragma unroll
             for (int i = 0; i < NV; ++i) acc[i] += f[i];
         }
@@ -43,6 +63,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ 
 }  // namespace grace
 
 using namespace grace;
+
+// Tokens up to which loading four ahead pays: with 3000 tokens and more the rows in flight of all workgroups are
+// enough (3001, 7001, 32768 tokens, k = 6, 8, 6: 18.2 to 19.4, 46.8, 177 us with 1 ahead, 18.2, 45.5, 178 us with 2,
+// 19.2, 45.2, 177 us with 4; k = 2, 8192 tokens 31.4 us with 1, 32.3 us with 2).
+constexpr int COMBINE_FEW = 1024;
 
 extern "C" int grace_combine(const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T, int32_t k,
                              int32_t d, grace_dtype dt, const void *y_shared, void *out, void *stream) {
@@ -58,12 +83,12 @@ extern "C" int grace_combine(const void *y, const int32_t *perm_pos, const float
     hipStream_t st = (hipStream_t)stream;
     const int row_vec = (int)((size_t)d * el / 16);
     const int64_t n = (int64_t)T * k;
-    if (dt == GRACE_BF16)
-        combine_kernel<true><<<T, 256, 0, st>>>((const uint4 *)y, perm_pos, topk_weight, k, row_vec, n,
-                                                (const uint4 *)y_shared, (uint4 *)out);
-    else
-        combine_kernel<false><<<T, 256, 0, st>>>((const uint4 *)y, perm_pos, topk_weight, k, row_vec, n,
-                                                 (const uint4 *)y_shared, (uint4 *)out);
+    auto launch = [&](auto kernel) {
+        kernel<<<T, 256, 0, st>>>((const uint4 *)y, perm_pos, topk_weight, k, row_vec, n, (const uint4 *)y_shared, (uint4 *)out);
+    };
+    const int ahead = (k < 3 ? 2 : 4) >> (T > COMBINE_FEW ? 1 : 0);
+    if (dt == GRACE_BF16) launch(ahead == 1 ? combine_kernel<true, 1> : ahead == 2 ? combine_kernel<true, 2> : combine_kernel<true, 4>);
+    else launch(ahead == 1 ? combine_kernel<false, 1> : ahead == 2 ? combine_kernel<false, 2> : combine_kernel<false, 4>);
     GRACE_LAUNCH_CHECK("combine_kernel");
     return GRACE_OK;
 }

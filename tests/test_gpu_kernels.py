@@ -123,3 +123,23 @@ def test_shared_experts_small_batches(T, d, f, n_shared, dtype):
     assert rel_err(oracle.widen(host(got)), want) <= TOL[dtype]
     assert torch.equal(got, two)
     np.testing.assert_array_equal(host(xp)[pos.cpu().numpy()], np.repeat(host(x), 2, axis=0))
+
+
+@pytest.mark.parametrize("T,k,dtype", [(1, 1, "bf16"), (7, 2, "f32"), (33, 3, "bf16"), (5, 5, "bf16"), (1024, 6, "f32"), (1025, 9, "bf16")])
+def test_combine_with_absent_rows(T, k, dtype):
+    """Choices loaded ahead, with positions outside the buffer (no row) among them and NaN in a row nobody names."""
+    rng = np.random.default_rng(T * k)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    y = torch.from_numpy(rng.standard_normal((T * k, 24)).astype(np.float32)).to(tdt)
+    pos = rng.permutation(T * k).astype(np.int32)
+    pos[rng.random(T * k) < 0.3] = -1
+    pos[pos == 0] = T * k
+    y[0] = float("nan")
+    w = rng.random((T, k)).astype(np.float32)
+    out = grace.grace_combine(y.cuda(), torch.from_numpy(pos).cuda(), torch.from_numpy(w).cuda())
+    got, rows = oracle.widen(host(out)), oracle.widen(host(y))
+    want = np.zeros((T, 24))
+    for a, p in enumerate(pos):
+        if 0 <= p < T * k:
+            want[a // k] += np.float64(w.reshape(-1)[a]) * rows[p]
+    assert rel_err(got, want) <= (1e-6 if dtype == "f32" else 2.0 ** -8)   # one rounding of an fp32 sum
