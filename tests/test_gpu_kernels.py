@@ -143,3 +143,28 @@ def test_combine_with_absent_rows(T, k, dtype):
         if 0 <= p < T * k:
             want[a // k] += np.float64(w.reshape(-1)[a]) * rows[p]
     assert rel_err(got, want) <= (1e-6 if dtype == "f32" else 2.0 ** -8)   # one rounding of an fp32 sum
+
+
+@pytest.mark.parametrize("nodes,gpus,T,k", [(2, 2, 1, 2), (3, 2, 255, 4), (1, 4, 1025, 3), (4, 2, 513, 2)])
+def test_send_list_block_edges(nodes, gpus, T, k):
+    """Send lists whose assignments end just below, at and past a block of the counting and the expansion kernels."""
+    E, R = 16, nodes * gpus
+    rng = np.random.default_rng(T)
+    ranks = [e % R for e in range(E)]
+    table = grace.GraceTable(E, R, nodes, [r // gpus for r in range(R)], [1] * R, list(range(E + 1)), ranks)
+    experts = np.stack([rng.permutation(E)[:k] for _ in range(T)])
+    order = sorted(range(E), key=lambda e: (ranks[e], e))
+    inst = np.empty(E, np.int32)
+    inst[order] = np.arange(E, dtype=np.int32)
+    topk_inst = torch.from_numpy(inst[experts].astype(np.int32)).cuda()
+    rp, rt, np_, nt, ex, tr = (t.cpu().numpy() for t in grace.grace_send_lists(table, R - 1, topk_inst))
+    dest = np.array(ranks)[experts]
+    for r in range(R):
+        np.testing.assert_array_equal(rt[rp[r]:rp[r + 1]], np.flatnonzero((dest == r).any(axis=1)))
+    for n in range(nodes):
+        np.testing.assert_array_equal(nt[np_[n]:np_[n + 1]], np.flatnonzero((dest // gpus == n).any(axis=1)))
+    for a, d in enumerate(dest.reshape(-1)):
+        assert rt[rp[d] + ex[a]] == a // k
+    other = (R - 1) // gpus
+    assert tr[1] == int((dest // gpus != other).sum())
+    assert tr[3] == int(((dest // gpus == other) & (dest != R - 1)).sum())
