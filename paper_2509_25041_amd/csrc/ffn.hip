@@ -7,8 +7,9 @@
 //   down: y[p, m]  = sum_n h[p,n] Wd[m,n]                                     K = f, N = d
 // Rows are grouped by instance: the rows of one rank are a contiguous range of
 // the dispatch buffer, subdivided per local slot by inst_off (read on the
-// device; there is no host synchronisation).  The bf16 kernel is persistent (one
-// workgroup per compute unit walks the tiles); the fallback kernels size their
+// device; there is no host synchronisation).  route_gemm below chooses the kernel
+// by type, batch and shape.  The large-tile bf16 kernel is persistent (one
+// workgroup per compute unit walks the tiles); the others size their
 // grid from an upper bound of the tile count and surplus blocks exit at once.
 #include <algorithm>
 #include <mutex>
@@ -102,7 +103,8 @@ static int launch_stream(const GemmArgs &g, int max_rows, int64_t m_bound, int n
     const int64_t busy = std::min<int64_t>(n_seg, m_bound) * n_strips;
     const int mf = max_rows <= 16 ? 1 : max_rows <= 32 ? 2 : 4;
     int waves = 4;
-    while (waves < strm::MAX_WAVES && busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::kstep<EL>()) waves *= 2;
+    // (no more than 64 KB of partial sums: a launch may ask for that much LDS without opting in)
+    while (waves < strm::MAX_WAVES && strm::lds_bytes(waves * 2, mf) <= 65536 && busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::kstep<EL>()) waves *= 2;
     auto launch = [&](auto mf) {
         constexpr int MF = decltype(mf)::value;
         strm::gemm_stream_kernel<FUSED_UP, EL, MF><<<(unsigned)(n_strips * n_seg), waves * 64, strm::lds_bytes(waves, MF), st>>>(g, n_strips);

@@ -50,6 +50,7 @@ def check_segments(got, want, off, tol):
     ([17, 31, 32], 32, 3, 512, 352),                # two fragments
     ([33, 48, 49, 64], 64, 4, 1024, 768),           # three and four fragments
     ([64, 130, 5], 64, 4, 192, 72),                 # more rows in a segment than tokens: walked in pieces
+    ([40, 30], 64, 2, 2048, 352),                   # few strips and long K: as many wavefronts as 64 KB of LDS allow
     ([20, 40], 20, 3, 4096, 40),                    # the same with two fragments; long K up, K of one step and a rest down
 ])
 def test_few_rows_per_segment(seg_rows, T, k, d, f):
