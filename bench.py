@@ -303,7 +303,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
                    "rows_per_slot_min_max": [int(seg.min()), int(seg.max())] if len(seg) else [0, 0],
                    "n_shared": cfg.n_shared, "working_set_MB": ws_bytes / 1e6,
                    "row_scatter": "carried by the shared gate+up projection's launch" if fused_scatter else "in the dispatch call"},
-        "roofline": {"kernel": KERNEL_OF_STAGE[dominant] if cfg.dtype == "bf16" else f"{dominant} (fp32 FMA path)",
+        "roofline": {"kernel": KERNEL_OF_STAGE[dominant] if cfg.dtype == "bf16" and cfg.T >= 4096 else f"{dominant} (kernel chosen by type and batch)",
                      "stage": dominant, "bound": work[dominant][0], "achieved": ach, "peak": peak, "unit": unit,
                      "frac": ach / peak, "traffic": traffic, "avg_launch_ms": dom_ms,
                      "algorithmic_per_launch": work[dominant][1], "carries": carried},

@@ -1,6 +1,7 @@
 // Generic bf16 MFMA grouped GEMM: 128x128 block tiles, register-staged loads
-// with zero fill, any K and N that are multiples of 8.  Used when the fast
-// kernel's preconditions do not hold.
+// with zero fill, any K and N that are multiples of 8.  For what the other kernels
+// cannot take: more than 256 row segments with more than 64 tokens, or operands
+// whose offsets from one base pass 2 GB.
 #pragma once
 #include "bf16.h"
 #include "gemm_common.h"

@@ -1,4 +1,5 @@
-// fp32 grouped GEMM on the vector ALUs.
+// fp32 grouped GEMM on the vector ALUs, for rows that are no whole 16-byte vectors (d or f no multiple of 4) and K
+// segments that are no multiple of 16; gemm_stream.h takes the rest at three times the speed.
 #pragma once
 #include "gemm_common.h"
 
