@@ -30,6 +30,7 @@
 #pragma once
 #include "bf16.h"
 #include "gemm_common.h"
+#include "kseg_walk.h"
 
 namespace grace {
 namespace mid {
@@ -40,7 +41,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 constexpr int BM = 96, BK = 64, THREADS = 256;
 constexpr int ROW_BYTES = BK * 2, A_BYTES = BM * ROW_BYTES, B_WAVE_BYTES = 32 * ROW_BYTES, LDS_BYTES = 2 * A_BYTES + 8 * B_WAVE_BYTES;
-constexpr uint32_t NO_DATA = 0x80000000u;   // an offset past the descriptor's range
 
 template <bool FUSED_UP>
 struct Shape {
@@ -88,10 +88,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
         b_off[i] = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 2) + (uint32_t)b_chunk * 16u : NO_DATA;
     }
     char *sb = smem + 2 * A_BYTES + wave * 2 * B_WAVE_BYTES;
-    // K of the next weight loads (scalar), SEG_K: this lane's position in its K segment and the byte
-    // distance that the segments before it add
-    int bk = 0, bseg = b_chunk * 8;
-    uint32_t bjump = 0u;
+    int bk = 0;   // K of the next weight loads (scalar)
+    KSegWalk walk{b_chunk * 8};
 
     u32x4_t ra[AHEAD][AL], rb[AHEAD][4];
     f32x4_t acc[MF][2];
@@ -113,18 +111,11 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
             *(u32x4_t *)(smem + buf * A_BYTES + chunk_at(i * 32 + (tid >> 3), a_chunk)) = ra[set][i];
     };
     auto load_b = [&](int set) {
-        uint32_t none = bk + b_chunk * 8 < g.K ? 0u : NO_DATA;
-        if (SEG_K) {
-            while (bseg >= g.kseg_len) {
-                bseg -= g.kseg_len;
-                bjump += (uint32_t)((g.kseg_stride - g.kseg_len) * 2);
-            }
-            none += bjump;
-            bseg += BK;
-        }
+        const int k = bk + b_chunk * 8;
+        const uint32_t add = SEG_K ? walk.next(k, g.K, g.kseg_len, g.kseg_stride, BK) : k < g.K ? 0u : NO_DATA;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            rb[set][i] = load16(FUSED_UP && i >= 2 ? b1_rsrc : b0_rsrc, SEG_K ? (b_off[i] + none) | (b_off[i] & NO_DATA) | (none & NO_DATA) : b_off[i] | none, (uint32_t)bk * 2u);
+            rb[set][i] = load16(FUSED_UP && i >= 2 ? b1_rsrc : b0_rsrc, SEG_K ? offset_with(b_off[i], add) : b_off[i] | add, (uint32_t)bk * 2u);
         bk += BK;
     };
     auto store_b = [&](int set, int buf) {

@@ -1,0 +1,31 @@
+// Weight offsets of a lane that walks a K axis cut in segments (shared experts' down projection), for buffer loads.
+// Plain C++ (constexpr: host and device), so that the arithmetic can be checked on the host.
+#pragma once
+#include <cstdint>
+
+namespace grace {
+
+constexpr uint32_t NO_DATA = 0x80000000u;   // an offset past the range of the buffer descriptors: reads nothing, gives zeros
+
+// The lane looks at positions k, k + step, ... of K; what the segments before a position add to its byte offset
+// beyond 2 * k is `jump` (elements of 2 bytes).
+struct KSegWalk {
+    int pos;            // position in the K segment
+    uint32_t jump = 0;
+
+    // bytes to add to the offset of position k, then one step on.  Past K there is no data, whatever `jump` has grown to
+    // (in 32 bits it wraps there when the weights hold 2 GiB or more).
+    constexpr uint32_t next(int k, int K, int seg_len, int64_t seg_stride, int step) {
+        while (pos >= seg_len) {
+            pos -= seg_len;
+            jump += (uint32_t)((seg_stride - seg_len) * 2);
+        }
+        pos += step;
+        return k < K ? jump : NO_DATA;
+    }
+};
+
+// offset + add, or no data where either has none
+constexpr uint32_t offset_with(uint32_t offset, uint32_t add) { return (offset + add) | (offset & NO_DATA) | (add & NO_DATA); }
+
+}  // namespace grace
