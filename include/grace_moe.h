@@ -352,6 +352,20 @@ int grace_combine(const void *y, const int32_t *perm_pos, const float *topk_weig
  * must not be called under stream capture.  HOST output: TFLOP/s. */
 int grace_mfma_sustained(int32_t random_operands, int32_t lds_fed, double *tflops_out, void *stream);
 
+/* Which kernel takes a projection of grace_expert_ffn (n_shared == 0: S of the table's I instances on the rank) or
+ * grace_shared_ffn (n_shared > 0; k, S and I unused), and how many work-items the launch has.  The choice depends on
+ * these sizes alone.  up: 1 for the gate+up projection, 0 for the down projection.  n_cu: compute units (0: of the
+ * current device; no device is touched otherwise).  HOST outputs. */
+typedef enum {
+    GRACE_KERNEL_STREAM = 0,     /* weights streamed, few rows per segment; fp32 of any size */
+    GRACE_KERNEL_MID = 1,        /* 96-row pieces x 128 weight rows */
+    GRACE_KERNEL_PERSIST = 2,    /* 256 x 256 tiles, one workgroup per compute unit */
+    GRACE_KERNEL_GENERIC = 3,    /* 128 x 128 tiles: K no multiple of 64 and operands past 2 GB */
+    GRACE_KERNEL_VECTOR_F32 = 4  /* fp32 on the vector ALUs: rows that are no whole 16-byte vectors */
+} grace_kernel;
+int grace_ffn_kernel(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I,
+                     grace_dtype dt, int32_t n_cu, int32_t *kernel, int64_t *work_items);
+
 /* Text of the calling thread's most recent error ("" if none).  The pointer
  * stays valid until the thread's next failing call. */
 const char *grace_last_error(void);

@@ -22,6 +22,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_permute", "grace_permute_rows", "grace_route_permute", "grace_route_permute_static", "grace_send_lists", "grace_expert_ffn", "grace_expert_ffn_up",
            "grace_expert_ffn_down", "grace_expert_ffn_up_share", "grace_expert_ffn_down_share",
            "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_mfma_sustained",
+           "grace_ffn_kernel",
            "grace_last_error")
 
 _lib: Optional[C.CDLL] = None
@@ -78,6 +79,7 @@ def load_library() -> C.CDLL:
     lib.grace_shared_ffn_down.argtypes = [i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_combine.argtypes = [vp, vp, vp, i32, i32, i32, C.c_int, vp, vp, vp]
     lib.grace_mfma_sustained.argtypes = [i32, i32, C.POINTER(C.c_double), vp]
+    lib.grace_ffn_kernel.argtypes = [i32] * 8 + [C.c_int, i32, C.POINTER(i32), C.POINTER(C.c_int64)]
     for name in EXPORTS:
         if name not in ("grace_last_error", "grace_workspace_bytes"):
             getattr(lib, name).restype = C.c_int
@@ -432,3 +434,14 @@ def grace_mfma_sustained(random_operands: bool = True, lds_fed: bool = True) -> 
     out = C.c_double()
     _check(load_library().grace_mfma_sustained(int(random_operands), int(lds_fed), C.byref(out), _stream()))
     return float(out.value)
+
+
+FFN_KERNELS = ("stream", "mid", "persist", "generic", "vector_f32")      # grace_kernel
+
+
+def grace_ffn_kernel(up: bool, T: int, d: int, f: int, dt: int = GRACE_BF16, *, k: int = 1, S: int = 1, I: int = 1,
+                     n_shared: int = 0, n_cu: int = 0) -> Tuple[str, int]:
+    """(kernel, work-items) of a projection's launch (see grace_moe.h); with n_cu no device is needed."""
+    kernel, items = C.c_int32(), C.c_int64()
+    _check(load_library().grace_ffn_kernel(int(up), T, k, d, f, n_shared, S, I, dt, n_cu, C.byref(kernel), C.byref(items)))
+    return FFN_KERNELS[kernel.value], int(items.value)

@@ -79,62 +79,72 @@ static bool stream_ok(const GemmArgs &g, int kseg_align = strm::kstep<EL>()) {
            k_bytes + 128 * std::max(g.lda, g.ldb) * EL < (int64_t)strm::NO_DATA;
 }
 
+// Which kernel takes a launch.
+enum class Route {
+    STREAM = GRACE_KERNEL_STREAM,
+    MID = GRACE_KERNEL_MID,
+    PERSIST = GRACE_KERNEL_PERSIST,
+    GENERIC = GRACE_KERNEL_GENERIC,
+    VECTOR_F32 = GRACE_KERNEL_VECTOR_F32,
+};
+// A rank hosts an expert at most once, so its row segments fit the kernels' segment tables.
+static_assert(GRACE_MAX_EXPERTS <= pers::MAX_SEGMENTS, "more row segments than the kernels' tables hold");
+
+// A launch: bounds that the host knows.  max_rows: rows of one segment that the callers' routing gives at most (a
+// token picks an expert once); more rows are still computed correctly.  m_load: rows that the segments of a busy rank
+// hold together; m_bound: bound on the rows of all segments.
+struct Rows {
+    int max_rows;
+    int64_t m_load, m_bound;
+};
+
+struct Grid {
+    int64_t groups;
+    int threads;   // per workgroup
+};
+// Work-items of a launch along x have to fit 32 bits (HIP refuses more).
+static bool launchable(const Grid &l) { return l.groups * l.threads <= (int64_t)UINT32_MAX; }
+
+// fp32, more rows than one workgroup takes: workgroups per piece of the rows as well
+template <int EL>
+static bool stream_pieces(const Rows &rows) { return EL == 4 && rows.max_rows > strm::MAX_ROWS; }
+
 // Streaming kernel.  With at most strm::MAX_ROWS rows per segment, one workgroup per strip of weight rows and
 // segment.  At most one workgroup per strip and row of the batch finds work; with few of those each gets more
 // than four wavefronts (a finer split of K) until the chip holds about 8 wavefronts per compute unit.  More than
 // that does not pay (bf16): 16 per unit took 8.6 instead of 8.2 us on 4 busy segments, 32 took 10.4, and 32.9
 // instead of 28.8 us on 16; two wavefronts per workgroup at the other end took 29.5 us.
+static int stream_fragments(const Rows &rows) { return rows.max_rows <= 16 ? 1 : rows.max_rows <= 32 ? 2 : 4; }
 template <bool FUSED_UP, int EL>
-static int launch_stream(const GemmArgs &g, int max_rows, int64_t m_bound, int n_cu, hipStream_t st, const char *what) {
-    const int n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
-    const int n_seg = g.seg_off ? g.S : 1;
-    if constexpr (EL == 4) {
-        if (max_rows > strm::MAX_ROWS && n_seg <= 256) {
-            const int64_t grid = ((m_bound / strm::MAX_ROWS + n_seg) * n_strips + 7) / 8 * 8;
-            if (grid > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
-            const int lds = strm::lds_bytes(4, strm::MAX_ROWS / 16);
-            if (n_seg <= 64) strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 1><<<(unsigned)grid, 256, lds, st>>>(g, n_strips);
-            else strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 4><<<(unsigned)grid, 256, lds, st>>>(g, n_strips);
-            GRACE_LAUNCH_CHECK(what);
-            return GRACE_OK;
-        }
-    }
-    if ((int64_t)n_strips * n_seg > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
-    const int64_t busy = std::min<int64_t>(n_seg, m_bound) * n_strips;
-    const int mf = max_rows <= 16 ? 1 : max_rows <= 32 ? 2 : 4;
+static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
+    const int64_t n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
+    if (stream_pieces<EL>(rows)) return {((rows.m_bound / strm::MAX_ROWS + g.S) * n_strips + 7) / 8 * 8, 256};
+    const int64_t busy = std::min<int64_t>(g.S, rows.m_bound) * n_strips;
     int waves = 4;
     // (no more than 64 KB of partial sums: a launch may ask for that much LDS without opting in)
-    while (waves < strm::MAX_WAVES && strm::lds_bytes(waves * 2, mf) <= 65536 && busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::kstep<EL>()) waves *= 2;
-    auto launch = [&](auto mf) {
-        constexpr int MF = decltype(mf)::value;
-        strm::gemm_stream_kernel<FUSED_UP, EL, MF><<<(unsigned)(n_strips * n_seg), waves * 64, strm::lds_bytes(waves, MF), st>>>(g, n_strips);
-    };
-    if (mf == 1) launch(std::integral_constant<int, 1>{});
-    else if (mf == 2) launch(std::integral_constant<int, 2>{});
-    else launch(std::integral_constant<int, 4>{});
-    GRACE_LAUNCH_CHECK(what);
-    return GRACE_OK;
+    while (waves < strm::MAX_WAVES && strm::lds_bytes(waves * 2, stream_fragments(rows)) <= 65536 &&
+           busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::kstep<EL>())
+        waves *= 2;
+    return {n_strips * g.S, waves * 64};
 }
-
 template <bool FUSED_UP>
-static int launch_mid(const GemmArgs &g, int64_t m_bound, hipStream_t st, const char *what) {
-    const int n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
-    const int n_seg = g.seg_off ? g.S : 1;
-    const int64_t grid = ((m_bound / mid::BM + n_seg) * n_strips + 63) / 64 * 64;
-    if (grid > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
-    if (g.kseg_len < g.K) mid::gemm_bf16_mid_kernel<FUSED_UP, true, 1><<<(unsigned)grid, mid::THREADS, 0, st>>>(g, n_strips);
-    else if (n_seg <= 64) mid::gemm_bf16_mid_kernel<FUSED_UP, false, 1><<<(unsigned)grid, mid::THREADS, 0, st>>>(g, n_strips);
-    else mid::gemm_bf16_mid_kernel<FUSED_UP, false, 4><<<(unsigned)grid, mid::THREADS, 0, st>>>(g, n_strips);
-    GRACE_LAUNCH_CHECK(what);
-    return GRACE_OK;
+static Grid mid_grid(const GemmArgs &g, const Rows &rows) {
+    const int64_t n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+    return {((rows.m_bound / mid::BM + g.S) * n_strips + 63) / 64 * 64, mid::THREADS};
+}
+template <bool FUSED_UP>
+static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
+    if (route == Route::STREAM)
+        return dt == GRACE_BF16 ? stream_grid<FUSED_UP, 2>(g, rows, n_cu) : stream_grid<FUSED_UP, 4>(g, rows, n_cu);
+    if (route == Route::MID) return mid_grid<FUSED_UP>(g, rows);
+    if (route == Route::PERSIST) return {pers::grid_blocks(n_cu), pers::THREADS};
+    if (route == Route::GENERIC) {
+        constexpr int BN = FUSED_UP ? 64 : 128;
+        return {(rows.m_bound / BM + g.S) * ((g.N + BN - 1) / BN), 256};
+    }
+    return {(rows.m_bound / FBM + g.S) * ((g.N + FBN - 1) / FBN), 256};
 }
 
-// Which kernel takes a launch.
-enum class Route { STREAM, MID, PERSIST, GENERIC, VECTOR_F32, FAILED };
-
-// max_rows: bound on the rows of one segment that the callers' routing gives (a token picks an expert once);
-// more rows are still computed correctly.  m_load: rows that the segments of a busy rank hold together.
-//
 // bf16, the streaming kernel up to 64 rows per segment: with 1 to 16 tokens it is 1.1 to 2 times as fast as the 96-row
 // kernel on every shape, and at 64 tokens on the down projections.  For more than 16 rows a gate+up projection whose
 // 64-column strips fill the compute units goes to the 96-row kernel (d = 2048, f = 1024, 16 segments, 64 tokens:
@@ -148,66 +158,122 @@ enum class Route { STREAM, MID, PERSIST, GENERIC, VECTOR_F32, FAILED };
 // with this rule, 8.71 ms with large tiles only, 6.61 ms with the better one each time; one projection is
 // slower than with large tiles by 8 % (107 -> 118 us), the others by at most 3 %.
 template <bool FUSED_UP>
-static Route route_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t m_load) {
-    if (dt == GRACE_F32) return stream_ok<4>(g) ? Route::STREAM : Route::VECTOR_F32;
-    const int n_cu = compute_units();
-    if (n_cu <= 0) return Route::FAILED;
-    const int n_seg = g.seg_off ? g.S : 1;
-    const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(n_seg, m_load));
+static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
+    auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };
+    if (dt == GRACE_F32) return stream_ok<4>(g) && fits(Route::STREAM) ? Route::STREAM : Route::VECTOR_F32;
+    const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(g.S, rows.m_load));
     const int64_t strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
-    const bool mid_ok = n_seg <= 256 && stream_ok<2>(g, 8);
-    if (max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && !(FUSED_UP && mid_ok && max_rows > 16 && busy * strips > n_cu * 3 / 4))
+    const bool mid_ok = stream_ok<2>(g, 8) && fits(Route::MID);
+    if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM) &&
+        !(FUSED_UP && mid_ok && rows.max_rows > 16 && busy * strips > n_cu * 3 / 4))
         return Route::STREAM;
-    const bool persist_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK &&
-                            n_seg <= pers::MAX_SEGMENTS;
+    const bool persist_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK;
     if (!mid_ok) return persist_ok ? Route::PERSIST : Route::GENERIC;
     if (!persist_ok) return Route::MID;
     const int64_t large_strips = (g.N + pers::Shape<FUSED_UP>::BN - 1) / pers::Shape<FUSED_UP>::BN;
-    const int64_t tiles = (m_load / mid::BM + busy) * strips, large_tiles = (m_load / pers::BM + busy) * large_strips;
+    const int64_t tiles = (rows.m_load / mid::BM + busy) * strips, large_tiles = (rows.m_load / pers::BM + busy) * large_strips;
     const int64_t full = (large_tiles + n_cu - 1) / n_cu * n_cu;
     return tiles <= full * (FUSED_UP ? 3 : 2) ? Route::MID : Route::PERSIST;
 }
 
-// m_bound: bound on the rows of all segments.
+template <bool FUSED_UP, int EL>
+static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, hipStream_t st) {
+    const int n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
+    if constexpr (EL == 4) {
+        if (stream_pieces<EL>(rows)) {
+            const int lds = strm::lds_bytes(4, strm::MAX_ROWS / 16);
+            if (g.S <= 64) strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 1><<<(unsigned)l.groups, l.threads, lds, st>>>(g, n_strips);
+            else strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 4><<<(unsigned)l.groups, l.threads, lds, st>>>(g, n_strips);
+            return;
+        }
+    }
+    auto launch = [&](auto mf) {
+        constexpr int MF = decltype(mf)::value;
+        strm::gemm_stream_kernel<FUSED_UP, EL, MF><<<(unsigned)l.groups, l.threads, strm::lds_bytes(l.threads / 64, MF), st>>>(g, n_strips);
+    };
+    const int mf = stream_fragments(rows);
+    if (mf == 1) launch(std::integral_constant<int, 1>{});
+    else if (mf == 2) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 4>{});
+}
+
+template <bool FUSED_UP>
+static void launch_mid(const GemmArgs &g, const Grid &l, hipStream_t st) {
+    const int n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+    if (g.kseg_len < g.K) mid::gemm_bf16_mid_kernel<FUSED_UP, true, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
+    else if (g.S <= 64) mid::gemm_bf16_mid_kernel<FUSED_UP, false, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
+    else mid::gemm_bf16_mid_kernel<FUSED_UP, false, 4><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
+}
+
 template <bool FUSED_UP, pers::Who WHO>
-static int launch_gemm(const GemmArgs &g, grace_dtype dt, int max_rows, int64_t m_load, int64_t m_bound, hipStream_t st, const char *what) {
-    if (m_bound <= 0 || g.N <= 0 || g.K <= 0) return GRACE_OK;
-    const Route route = route_gemm<FUSED_UP>(g, dt, max_rows, m_load);
+static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipStream_t st, const char *what) {
+    if (rows.m_bound <= 0 || g.N <= 0 || g.K <= 0) return GRACE_OK;
     const int n_cu = compute_units();
-    if (route == Route::FAILED || n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", what);
-    if (route == Route::STREAM)
-        return dt == GRACE_BF16 ? launch_stream<FUSED_UP, 2>(g, max_rows, m_bound, n_cu, st, what)
-                                : launch_stream<FUSED_UP, 4>(g, max_rows, m_bound, n_cu, st, what);
-    if (route == Route::MID) return launch_mid<FUSED_UP>(g, m_bound, st, what);
-    const int n_seg = g.seg_off ? g.S : 1;
-    if (route == Route::PERSIST) {
+    if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", what);
+    const Route route = route_gemm<FUSED_UP>(g, dt, rows, n_cu);
+    const Grid l = grid_of<FUSED_UP>(route, g, dt, rows, n_cu);
+    if (!launchable(l)) return fail(GRACE_ESHAPE, "%s: grid too large", what);
+    if (route == Route::STREAM) {
+        if (dt == GRACE_BF16) launch_stream<FUSED_UP, 2>(g, rows, l, st);
+        else launch_stream<FUSED_UP, 4>(g, rows, l, st);
+    } else if (route == Route::MID) {
+        launch_mid<FUSED_UP>(g, l, st);
+    } else if (route == Route::PERSIST) {
         // persistent large-tile kernel: one workgroup per compute unit, 160 KB of dynamic LDS
         using SH = pers::Shape<FUSED_UP>;
         const int ntn = (g.N + SH::BN - 1) / SH::BN;
-        const int grid = pers::grid_blocks(n_cu);
-        if ((m_bound / 160 + n_seg) * (int64_t)ntn > INT32_MAX) return fail(GRACE_ESHAPE, "%s: too many tiles", what);   // the lowest m-tile has 160 rows
-        if (n_seg <= 64) {
+        if ((rows.m_bound / 160 + g.S) * (int64_t)ntn > INT32_MAX) return fail(GRACE_ESHAPE, "%s: too many tiles", what);   // the lowest m-tile has 160 rows
+        if (g.S <= 64) {
             if (!allow_full_lds((const void *)pers::gemm_bf16_persist_kernel<FUSED_UP, 1, WHO>, what)) return GRACE_EHIP;
-            pers::gemm_bf16_persist_kernel<FUSED_UP, 1, WHO><<<grid, pers::THREADS, pers::LDS_BYTES, st>>>(g, ntn);
+            pers::gemm_bf16_persist_kernel<FUSED_UP, 1, WHO><<<(unsigned)l.groups, l.threads, pers::LDS_BYTES, st>>>(g, ntn);
         } else if constexpr (WHO == pers::EXPERTS) {  // the shared experts are a single row segment
             if (!allow_full_lds((const void *)pers::gemm_bf16_persist_kernel<FUSED_UP, 4, WHO>, what)) return GRACE_EHIP;
-            pers::gemm_bf16_persist_kernel<FUSED_UP, 4, WHO><<<grid, pers::THREADS, pers::LDS_BYTES, st>>>(g, ntn);
+            pers::gemm_bf16_persist_kernel<FUSED_UP, 4, WHO><<<(unsigned)l.groups, l.threads, pers::LDS_BYTES, st>>>(g, ntn);
         }
     } else if (route == Route::GENERIC) {
         constexpr int BN = FUSED_UP ? 64 : 128;
-        const int64_t mt = m_bound / BM + (g.seg_off ? g.S : 1);
-        const int ntn = (g.N + BN - 1) / BN;
-        if (mt * ntn > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
-        gemm_bf16_kernel<FUSED_UP><<<(unsigned)(mt * ntn), 256, 0, st>>>(g, ntn);
+        gemm_bf16_kernel<FUSED_UP><<<(unsigned)l.groups, l.threads, 0, st>>>(g, (g.N + BN - 1) / BN);
     } else {
-        const int64_t mt = m_bound / FBM + (g.seg_off ? g.S : 1);
-        const int ntn = (g.N + FBN - 1) / FBN;
-        if (mt * ntn > INT32_MAX) return fail(GRACE_ESHAPE, "%s: grid too large", what);
-        gemm_f32_kernel<FUSED_UP><<<(unsigned)(mt * ntn), 256, 0, st>>>(g, ntn);
+        gemm_f32_kernel<FUSED_UP><<<(unsigned)l.groups, l.threads, 0, st>>>(g, (g.N + FBN - 1) / FBN);
     }
     GRACE_LAUNCH_CHECK(what);
     return GRACE_OK;
 }
+
+// Shapes of the two projections (operands are filled in by the entry points).
+//   up:   K = d, N = f, two weight matrices        down: K = f, N = d
+static GemmArgs expert_shape(bool up, int S, int d, int f) {
+    GemmArgs g{};
+    g.K = up ? d : f;
+    g.N = up ? f : d;
+    g.lda = g.ldb = g.kseg_len = g.K;
+    g.ldo = g.N;
+    g.b_slot_stride = (int64_t)d * f;
+    g.S = S;
+    return g;
+}
+
+// The shared experts act as one expert of width F = n_shared * f: gate and up weights [n_shared, f, d]
+// are one [F, d] matrix each; the down weights [n_shared, d, f] are F input features in n_shared
+// K segments of length f that lie d * f elements apart.
+static GemmArgs shared_shape(bool up, int T, int d, int f, int n_shared) {
+    GemmArgs g = expert_shape(up, 1, d, n_shared * f);
+    g.b_slot_stride = 0;
+    g.M_single = T;
+    if (!up) {
+        g.ldb = g.kseg_len = f;
+        g.kseg_stride = (int64_t)d * f;
+    }
+    return g;
+}
+
+// Rows that a busy rank of S out of I instances takes of a batch: three times its instances' share (hot experts have
+// replicas, but a rank that holds one of them is still the one the step waits for), at most every token once per
+// instance or choice.
+static Rows expert_rows(int S, int I, int32_t T, int32_t k) {
+    return {T, std::min((int64_t)T * std::min(S, k), 3 * (int64_t)T * k * S / I), (int64_t)T * k};
+}
+static Rows shared_rows(int32_t T) { return {T, T, T}; }
 
 static int check_ffn_shapes(const char *who, int32_t d, int32_t f, grace_dtype dt) {
     if (dt != GRACE_F32 && dt != GRACE_BF16) return fail(GRACE_EINVAL, "%s: unknown dtype %d", who, (int)dt);
@@ -234,12 +300,6 @@ static int expert_ffn_common(const char *who, const grace_table *table, int32_t 
     return GRACE_OK;
 }
 
-// Rows that a busy rank takes of a batch: three times its instances' share (hot experts have replicas, but a
-// rank that holds one of them is still the one the step waits for), at most every token once per instance or choice.
-static int64_t rank_load(const grace_table *table, int S, int32_t T, int32_t k) {
-    return std::min((int64_t)T * std::min(S, k), 3 * (int64_t)T * k * S / table->I);
-}
-
 static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
                          int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_gate, const void *w_up,
                          int32_t *state, void *ws, void *stream) {
@@ -250,14 +310,11 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     if (!xp || !inst_off || !w_gate || !w_up || !ws) return fail(GRACE_EINVAL, "%s: null device pointer", who);
     if ((((uintptr_t)xp) | ((uintptr_t)w_gate) | ((uintptr_t)w_up) | ((uintptr_t)ws)) & 15)
         return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
-    GemmArgs up{};
-    up.A = xp; up.lda = d;
-    up.B0 = w_gate; up.B1 = w_up; up.b_slot_stride = (int64_t)d * f; up.ldb = d;
-    up.N = f; up.K = d; up.kseg_len = d; up.kseg_stride = 0;
-    up.out = ws; up.ldo = f;
-    up.seg_off = inst_off + g0; up.S = S; up.M_single = 0;
+    GemmArgs up = expert_shape(true, S, d, f);
+    up.A = xp; up.B0 = w_gate; up.B1 = w_up; up.out = ws;
+    up.seg_off = inst_off + g0;
     up.share_state = state;
-    return launch_gemm<true, pers::EXPERTS>(up, dt, T, rank_load(table, S, T, k), (int64_t)T * k, (hipStream_t)stream, who);
+    return launch_gemm<true, pers::EXPERTS>(up, dt, expert_rows(S, table->I, T, k), (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_up(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
@@ -288,14 +345,11 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     const size_t el = dt == GRACE_F32 ? 4 : 2;
     if (state && ((size_t)d * el) % 16 != 0)
         return fail(GRACE_ESHAPE, "%s: row of %zu bytes is not a multiple of 16", who, (size_t)d * el);
-    GemmArgs dn{};
-    dn.A = ws; dn.lda = f;
-    dn.B0 = w_down; dn.B1 = nullptr; dn.b_slot_stride = (int64_t)d * f; dn.ldb = f;
-    dn.N = d; dn.K = f; dn.kseg_len = f; dn.kseg_stride = 0;
-    dn.out = y; dn.ldo = d;
-    dn.seg_off = inst_off + g0; dn.S = S; dn.M_single = 0;
+    GemmArgs dn = expert_shape(false, S, d, f);
+    dn.A = ws; dn.B0 = w_down; dn.out = y;
+    dn.seg_off = inst_off + g0;
     dn.share_state = state; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
-    return launch_gemm<false, pers::EXPERTS>(dn, dt, T, rank_load(table, S, T, k), (int64_t)T * k, (hipStream_t)stream, who);
+    return launch_gemm<false, pers::EXPERTS>(dn, dt, expert_rows(S, table->I, T, k), (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
@@ -327,9 +381,6 @@ static int shared_ffn_common(const char *who, int32_t T, int32_t d, int32_t f, i
     return GRACE_OK;
 }
 
-// The shared experts act as one expert of width F = n_shared * f: gate and up weights [n_shared, f, d]
-// are one [F, d] matrix each; the down weights [n_shared, d, f] are F input features in n_shared
-// K segments of length f that lie d * f elements apart.
 static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,
                          const void *w_gate, const void *w_up, void *ws, const int32_t *perm_pos, int32_t k, void *xp,
                          void *stream) {
@@ -339,18 +390,14 @@ static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, i
     if (!x || !w_gate || !w_up || !ws) return fail(GRACE_EINVAL, "%s: null device pointer", who);
     if ((((uintptr_t)x) | ((uintptr_t)w_gate) | ((uintptr_t)w_up) | ((uintptr_t)ws)) & 15)
         return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
-    const int F = n_shared * f;
-    GemmArgs up{};
-    up.A = x; up.lda = d;
-    up.B0 = w_gate; up.B1 = w_up; up.b_slot_stride = 0; up.ldb = d;
-    up.N = F; up.K = d; up.kseg_len = d; up.kseg_stride = 0;
-    up.out = ws; up.ldo = F;
-    up.seg_off = nullptr; up.S = 1; up.M_single = T;
+    GemmArgs up = shared_shape(true, T, d, f, n_shared);
+    up.A = x; up.B0 = w_gate; up.B1 = w_up; up.out = ws;
     if (perm_pos) {
         // the row scatter rides on the persistent bf16 kernel when rows are whole 1 KB pieces; otherwise it
         // is a launch of its own ahead of the projection
         const size_t row_bytes = (size_t)d * (dt == GRACE_F32 ? 4 : 2);
-        const bool persistent = route_gemm<true>(up, dt, T, T) == Route::PERSIST;
+        const int n_cu = compute_units();
+        const bool persistent = n_cu > 0 && route_gemm<true>(up, dt, shared_rows(T), n_cu) == Route::PERSIST;
         if (persistent && row_bytes % 1024 == 0 && (int64_t)T * k < ((int64_t)1 << 29) && row_bytes <= (size_t)INT32_MAX) {
             up.sc_x = x; up.sc_xp = xp; up.sc_pos = perm_pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = (int)row_bytes;
         } else {
@@ -358,7 +405,7 @@ static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, i
             if (rc != GRACE_OK) return rc;
         }
     }
-    return launch_gemm<true, pers::SHARED>(up, dt, T, T, T, (hipStream_t)stream, who);
+    return launch_gemm<true, pers::SHARED>(up, dt, shared_rows(T), (hipStream_t)stream, who);
 }
 
 extern "C" int grace_shared_ffn_up(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,
@@ -384,14 +431,9 @@ extern "C" int grace_shared_ffn_down(int32_t T, int32_t d, int32_t f, int32_t n_
     if (!w_down || !y_shared || !ws) return fail(GRACE_EINVAL, "shared_ffn_down: null device pointer");
     if ((((uintptr_t)w_down) | ((uintptr_t)y_shared) | ((uintptr_t)ws)) & 15)
         return fail(GRACE_EINVAL, "shared_ffn_down: device pointers must be 16-byte aligned");
-    const int F = n_shared * f;
-    GemmArgs dn{};
-    dn.A = ws; dn.lda = F;
-    dn.B0 = w_down; dn.B1 = nullptr; dn.b_slot_stride = 0; dn.ldb = f;
-    dn.N = d; dn.K = F; dn.kseg_len = f; dn.kseg_stride = (int64_t)d * f;  // K segment s lives in w_down[s]
-    dn.out = y_shared; dn.ldo = d;
-    dn.seg_off = nullptr; dn.S = 1; dn.M_single = T;
-    return launch_gemm<false, pers::SHARED>(dn, dt, T, T, T, (hipStream_t)stream, "shared_ffn down projection");
+    GemmArgs dn = shared_shape(false, T, d, f, n_shared);
+    dn.A = ws; dn.B0 = w_down; dn.out = y_shared;
+    return launch_gemm<false, pers::SHARED>(dn, dt, shared_rows(T), (hipStream_t)stream, "shared_ffn down projection");
 }
 
 extern "C" int grace_shared_ffn(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,
@@ -404,4 +446,23 @@ extern "C" int grace_shared_ffn(const void *x, int32_t T, int32_t d, int32_t f, 
     rc = grace_shared_ffn_up(x, T, d, f, n_shared, dt, w_gate, w_up, ws, stream);
     if (rc != GRACE_OK) return rc;
     return grace_shared_ffn_down(T, d, f, n_shared, dt, w_down, y_shared, ws, stream);
+}
+
+extern "C" int grace_ffn_kernel(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I,
+                                grace_dtype dt, int32_t n_cu, int32_t *kernel, int64_t *work_items) {
+    if (!kernel || !work_items) return fail(GRACE_EINVAL, "ffn_kernel: null output");
+    if (T < 1 || k < 1 || n_shared < 0 || n_cu < 0) return fail(GRACE_EINVAL, "ffn_kernel: T=%d, k=%d, n_shared=%d, n_cu=%d invalid", T, k, n_shared, n_cu);
+    if (n_shared == 0 && (S < 1 || I < S)) return fail(GRACE_EINVAL, "ffn_kernel: S=%d, I=%d invalid", S, I);
+    int rc = n_shared > 0 ? shared_ffn_common("ffn_kernel", T, d, f, n_shared, dt) : check_ffn_shapes("ffn_kernel", d, f, dt);
+    if (rc != GRACE_OK) return rc;
+    if (n_shared == 0 && (int64_t)T * k > INT32_MAX) return fail(GRACE_ESHAPE, "ffn_kernel: T*k exceeds 2^31-1");
+    if (n_cu == 0) n_cu = compute_units();
+    if (n_cu <= 0) return fail(GRACE_EHIP, "ffn_kernel: cannot query the device");
+    const GemmArgs g = n_shared > 0 ? shared_shape(up, T, d, f, n_shared) : expert_shape(up, S, d, f);
+    const Rows rows = n_shared > 0 ? shared_rows(T) : expert_rows(S, I, T, k);
+    const Route r = up ? route_gemm<true>(g, dt, rows, n_cu) : route_gemm<false>(g, dt, rows, n_cu);
+    const Grid l = up ? grid_of<true>(r, g, dt, rows, n_cu) : grid_of<false>(r, g, dt, rows, n_cu);
+    *kernel = (int32_t)r;
+    *work_items = l.groups * l.threads;
+    return GRACE_OK;
 }
