@@ -90,12 +90,17 @@ enum class Route {
 // A rank hosts an expert at most once, so its row segments fit the kernels' segment tables.
 static_assert(GRACE_MAX_EXPERTS <= pers::MAX_SEGMENTS, "more row segments than the kernels' tables hold");
 
-// A launch: bounds that the host knows.  max_rows: rows of one segment that the callers' routing gives at most (a
-// token picks an expert once); more rows are still computed correctly.  m_load: rows that the segments of a busy rank
-// hold together; m_bound: bound on the rows of all segments.
+// What the host knows of a launch's rows.
 struct Rows {
-    int max_rows;
-    int64_t m_load, m_bound;
+    int max_rows;        // of one segment, as the callers' routing gives them (a token picks an expert once); more are still computed correctly
+    int64_t picks;       // rows of all segments if the batch spreads evenly over the instances: picks / instances
+    int instances;
+    bool even_only;      // and that is what they are (all instances here, or one segment)
+    int64_t most;        // bound on the rows of all segments that the routing gives
+    int64_t m_bound;     // and whatever it gives
+
+    // rows of all segments at `quarters` / 4 times the even share
+    int64_t at(int quarters) const { return std::min(most, picks * quarters / (4 * (int64_t)instances)); }
 };
 
 struct Grid {
@@ -145,35 +150,66 @@ static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &
     return {(rows.m_bound / FBM + g.S) * ((g.N + FBN - 1) / FBN), 256};
 }
 
-// bf16, the streaming kernel up to 64 rows per segment: with 1 to 16 tokens it is 1.1 to 2 times as fast as the 96-row
-// kernel on every shape, and at 64 tokens on the down projections.  For more than 16 rows a gate+up projection whose
-// 64-column strips fill the compute units goes to the 96-row kernel (d = 2048, f = 1024, 16 segments, 64 tokens:
-// 22.2 -> 20.0 us; d = 4096, f = 14336, 64 tokens 67.8 -> 52.2 us; 12 strips x 16 segments: even).
+// Row pieces of at most bm rows that `rows` rows of up to n_seg segments make: ragged ends add halves / 2 pieces to every
+// segment that has rows.
+static int64_t pieces_of(int64_t rows, int n_seg, int bm, int halves) {
+    if (n_seg == 1) return (rows + bm - 1) / bm;
+    const int64_t hit = std::max<int64_t>(1, std::min<int64_t>(n_seg, rows));
+    return std::max(hit, (2 * rows + halves * hit * bm) / (2 * bm));
+}
+
+// The 96-row kernel against 256 x 256 tiles.  The large tiles take their time by whole rounds over the compute units,
+// however few rows a tile holds; the 96-row kernel by the number of its tiles.  With the rows of every segment known the line
+// is sharp: gate+up, 2 x n_cu tiles while the large kernel needs one round and 3 x n_cu for every further round, down
+// (where the large tiles adapt their height) 1.6 and 2.6.  The host knows them for the shared experts, and their sum
+// where a rank hosts all instances (2.1 in place of 1.6 there, as whole pieces are counted extra).  Elsewhere ranks hold
+// 0.5 to 3.2 times their instances' even share in the tables of the planner.  At some loads the large tiles just fill
+// their rounds, so the 96-row kernel is taken only if it is the cheaper one, by a little more, at each of 1, 3/2 and
+// 9/4 of the even share.
 //
-// Above that, the 96-row kernel against 256 x 256 tiles: the large tiles take their time by whole rounds over the
-// compute units, 1.0 to 1.4 us per 64 of K and round however few rows a tile holds; the 96-row kernel takes 0.35 to
-// 0.55 us while its tiles fit one round and half the sum of its tiles after that.  It is taken while its tiles are at
-// most 3 (gate+up) or 2 (down, where the large tiles adapt their height) times the large kernel's rounds x
-// compute units.  Measured over 148 projections of five layer shapes at 70 to 4096 tokens: 6.71 ms in all
-// with this rule, 8.71 ms with large tiles only, 6.61 ms with the better one each time; one projection is
-// slower than with large tiles by 8 % (107 -> 118 us), the others by at most 3 %.
+// Measured over 4014 projections (53 ranks of tables for five layer shapes, expert widths whole to a quarter, 1 to 32
+// ranks, 1 to 12000 tokens, three sets of weights in turn): 202.5 ms with large tiles only, 158.6 with this rule and the one
+// below, 155.4 with the best kernel each time.  37 projections are slower than with large tiles by more than 3 % and
+// 1 us, by 22 % at most (a rank with 3.2 times its share, 45.7 -> 55.8 us); taking all projections of a layer step together
+// 7 of 1531 steps are by more than 3 %, by 6 us at most.  With one guess of three times the even share and limits of 3 and 2
+// tiles per round and compute unit (159.0 ms) 164 projections and 63 steps were, by up to 78 us.
+template <bool FUSED_UP>
+static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
+    const int64_t strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+    const int64_t large_strips = (g.N + pers::Shape<FUSED_UP>::BN - 1) / pers::Shape<FUSED_UP>::BN;
+    const bool known = rows.even_only && g.S > 1;
+    for (const int load : {4, 6, 9}) {   // quarters of the even share
+        const int64_t m = rows.at(load);
+        const int64_t tiles = pieces_of(m, g.S, mid::BM, FUSED_UP ? 1 : 2) * strips;
+        const int64_t rounds = (pieces_of(m, g.S, pers::BM, 1) * large_strips + n_cu - 1) / n_cu;
+        // in tenths of n_cu
+        const int64_t limit = FUSED_UP ? 30 * rounds - (known ? 10 : 11) : 26 * rounds - (known ? 5 : 10);
+        if (10 * tiles > n_cu * limit) return false;
+        if (rows.even_only) break;
+    }
+    return true;
+}
+
+// bf16, up to 64 rows per segment: the streaming kernel, which splits the work finest, while the 96-row kernel's tiles
+// would not fill the chip.  A gate+up projection of more than 16 rows leaves it when the other has a tile for three quarters
+// of the compute units (above that line and 32 tokens it takes 0.9 to 1.7 of the 96-row kernel's time, 1.2 in the
+// middle), a down projection when there are one and a half per unit (all 60 qwen-shaped experts on one GPU, 64
+// tokens: large tiles 29.0 us, streaming 29.9 us, 96 rows 26.4 us).  With less than half a tile per unit it takes 0.4 to 0.8 of the
+// 96-row kernel's time; around the lines and with up to 16 tokens the two differ by up to 40 % either way, 0 to 10 % in the middle.
 template <bool FUSED_UP>
 static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };
     if (dt == GRACE_F32) return stream_ok<4>(g) && fits(Route::STREAM) ? Route::STREAM : Route::VECTOR_F32;
-    const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(g.S, rows.m_load));
-    const int64_t strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
     const bool mid_ok = stream_ok<2>(g, 8) && fits(Route::MID);
-    if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM) &&
-        !(FUSED_UP && mid_ok && rows.max_rows > 16 && busy * strips > n_cu * 3 / 4))
-        return Route::STREAM;
+    if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM)) {
+        const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(g.S, rows.at(12)));
+        const int64_t tiles = busy * ((g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN);
+        if (!mid_ok || (FUSED_UP ? rows.max_rows <= 16 || tiles <= n_cu * 3 / 4 : tiles <= n_cu * 3 / 2)) return Route::STREAM;
+        if (!FUSED_UP) return Route::MID;
+    }
     const bool persist_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK;
     if (!mid_ok) return persist_ok ? Route::PERSIST : Route::GENERIC;
-    if (!persist_ok) return Route::MID;
-    const int64_t large_strips = (g.N + pers::Shape<FUSED_UP>::BN - 1) / pers::Shape<FUSED_UP>::BN;
-    const int64_t tiles = (rows.m_load / mid::BM + busy) * strips, large_tiles = (rows.m_load / pers::BM + busy) * large_strips;
-    const int64_t full = (large_tiles + n_cu - 1) / n_cu * n_cu;
-    return tiles <= full * (FUSED_UP ? 3 : 2) ? Route::MID : Route::PERSIST;
+    return !persist_ok || mid_is_cheaper<FUSED_UP>(g, rows, n_cu) ? Route::MID : Route::PERSIST;
 }
 
 template <bool FUSED_UP, int EL>
@@ -267,13 +303,11 @@ static GemmArgs shared_shape(bool up, int T, int d, int f, int n_shared) {
     return g;
 }
 
-// Rows that a busy rank of S out of I instances takes of a batch: three times its instances' share (hot experts have
-// replicas, but a rank that holds one of them is still the one the step waits for), at most every token once per
-// instance or choice.
+// Rows of a rank that hosts S of I instances, at most every token once per instance or choice.
 static Rows expert_rows(int S, int I, int32_t T, int32_t k) {
-    return {T, std::min((int64_t)T * std::min(S, k), 3 * (int64_t)T * k * S / I), (int64_t)T * k};
+    return {T, (int64_t)T * k * S, I, S == I, (int64_t)T * std::min(S, k), (int64_t)T * k};
 }
-static Rows shared_rows(int32_t T) { return {T, T, T}; }
+static Rows shared_rows(int32_t T) { return {T, T, 1, true, T, T}; }
 
 static int check_ffn_shapes(const char *who, int32_t d, int32_t f, grace_dtype dt) {
     if (dt != GRACE_F32 && dt != GRACE_BF16) return fail(GRACE_EINVAL, "%s: unknown dtype %d", who, (int)dt);

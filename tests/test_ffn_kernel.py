@@ -29,3 +29,37 @@ def test_invalid_arguments_are_refused():
         with pytest.raises(grace.GraceError):
             grace.grace_ffn_kernel(True, a["T"], a["d"], a["f"], BF16, k=a["k"], S=a["S"], I=a["I"], n_shared=a["n_shared"], n_cu=a["n_cu"])
     assert grace.load_library().grace_ffn_kernel(1, 4, 1, 64, 64, 0, 1, 1, BF16, N_CU, None, None) == -1
+
+
+# (up, T, k, d, f, S, I): projections of one rank (S of I instances) that the 96-row kernel took, or the streaming one, while
+# 256 x 256 tiles were faster: us before / on large tiles.
+@pytest.mark.parametrize("up,T,k,d,f,S,I,want", [
+    (True, 4556, 4, 2048, 1408, 7, 64, "persist"),      # 87.1 / 57.1: the rank's rows just fill one round of large tiles
+    (True, 2565, 8, 2048, 768, 19, 134, "persist"),     # 81.4 / 58.5
+    (True, 1900, 2, 4096, 7168, 1, 10, "persist"),      # 134.6 / 99.2
+    (True, 1630, 2, 4096, 3584, 8, 8, "persist"),       # 279.9 / 201.9: every instance here
+    (True, 2120, 8, 2048, 256, 64, 64, "persist"),      # 76.8 / 59.2
+    (False, 761, 8, 2048, 1024, 16, 66, "persist"),     # 33.8 / 25.3
+    (False, 64, 4, 2048, 1408, 60, 60, "mid"),          # streaming 29.9 / 29.0; 26.4 on the 96-row kernel
+])
+def test_large_tiles_where_they_are_faster(up, T, k, d, f, S, I, want):
+    assert grace.grace_ffn_kernel(up, T, d, f, BF16, k=k, S=S, I=I, n_cu=N_CU)[0] == want
+
+
+@pytest.mark.parametrize("T,d,f,n_shared", [(2756, 2048, 704, 2), (6055, 2048, 704, 2)])
+def test_shared_projection_keeps_the_row_scatter(T, d, f, n_shared):
+    """Gate+up projections of shared experts that were slower without the large-tile kernel, which carries the row scatter
+    (70.0 / 56.4 and 137.4 / 106.2 us, six rows per token scattered)."""
+    assert grace.grace_ffn_kernel(True, T, d, f, BF16, n_shared=n_shared, n_cu=N_CU)[0] == "persist"
+
+
+@pytest.mark.parametrize("up,T,k,d,f,n_shared,S,I,want", [
+    (True, 1, 8, 2048, 1024, 0, 16, 66, "stream"), (False, 64, 8, 2048, 1024, 0, 16, 66, "stream"),
+    (True, 64, 8, 2048, 1024, 0, 16, 66, "mid"), (True, 200, 8, 2048, 1024, 0, 16, 66, "mid"),
+    (True, 500, 8, 2048, 768, 0, 16, 130, "mid"), (False, 2000, 2, 4096, 3584, 0, 1, 10, "mid"),
+    (True, 200, 8, 2048, 1024, 0, 64, 64, "mid"), (True, 300, 1, 2048, 1408, 2, 1, 1, "mid"),
+    (True, 32768, 1, 2048, 1408, 2, 1, 1, "persist"), (True, 8192, 8, 2048, 768, 0, 16, 130, "persist"),
+    (False, 3001, 6, 2048, 352, 0, 2, 69, "mid"),       # K no multiple of 64
+])
+def test_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
+    assert grace.grace_ffn_kernel(up, T, d, f, BF16, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU)[0] == want
