@@ -6,7 +6,9 @@ import torch
 
 import oracle
 import paper_2509_25041_amd as grace
+import test_gpu_parity as parity
 from test_gpu_parity import TOL, host, rel_err
+from workloads import LayerConfig, make_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -55,6 +57,7 @@ def check_segments(got, want, off, tol):
 ])
 def test_few_rows_per_segment(seg_rows, T, k, d, f):
     """The weight-streaming kernel of decode batches (at most 64 tokens)."""
+    assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows)) == ("stream", "stream")
     got, want, off = ffn_of_segments(seg_rows, T, k, d, f)
     check_segments(got, want, off, TOL["bf16"])
 
@@ -70,18 +73,21 @@ def test_few_rows_per_segment(seg_rows, T, k, d, f):
 ])
 def test_ordinary_batches(seg_rows, T, k, d, f):
     """The kernel between decode batches and large tiles."""
+    assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows)) == ("mid", "mid")
     got, want, off = ffn_of_segments(seg_rows, T, k, d, f)
     check_segments(got, want, off, TOL["bf16"])
 
 
 def test_up_projection_of_decode_batches():
     """More than 16 tokens whose gate+up strips fill the chip: streaming kernel for the down projection only."""
+    assert kernels_of(40, 2, 256, 16 * 1024 + 24, 4, 4) == ("mid", "stream")
     got, want, off = ffn_of_segments([17, 0, 40, 9], 40, 2, 256, 16 * 1024 + 24)
     check_segments(got, want, off, TOL["bf16"])
 
 
 def test_large_tiles():
-    """Large batches keep the 256 x 256 tiles."""
+    """Large batches keep the 256 x 256 tiles (the gate+up projection here)."""
+    assert kernels_of(5000, 1, 128, 2048, 4, 4) == ("persist", "mid")
     got, want, off = ffn_of_segments([4700, 0, 257, 43], 5000, 1, 128, 2048)
     check_segments(got, want, off, TOL["bf16"])
 
@@ -93,6 +99,7 @@ def test_large_tiles():
     ([0, 130, 17, 300], 300, 2, 548, 1388),         # pieces of one, two and three fragments with ragged ends
     ([33, 97], 100, 2, 36, 77),                     # odd N up; the down projection's K takes the vector kernel
     ([1] * 70 + [80] * 3, 160, 2, 64, 32),          # more segments than lanes
+    ([1, 0] * 40, 40, 1, 64, 48),                   # the same with one workgroup per strip and segment
 ])
 def test_f32_segments(seg_rows, T, k, d, f):
     """fp32 on the matrix cores: one workgroup per strip (at most 64 tokens) or per strip and piece of a segment."""
@@ -101,7 +108,8 @@ def test_f32_segments(seg_rows, T, k, d, f):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2), (97, 520, 40, 3)])
+@pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2), (97, 520, 40, 3),
+                                            (1100, 1024, 200, 3)])   # 12 pieces x 8 strips: more than one tile per run of an XCD
 def test_shared_experts_small_batches(T, d, f, n_shared, dtype):
     """Shared experts: the down projection's K runs through n_shared segments (lengths below, at and off the K step);
     the row scatter is a launch of its own here."""
@@ -169,3 +177,71 @@ def test_send_list_block_edges(nodes, gpus, T, k):
     other = (R - 1) // gpus
     assert tr[1] == int((dest // gpus != other).sum())
     assert tr[3] == int(((dest // gpus == other) & (dest != R - 1)).sum())
+
+
+# ------------------------------------------- kernels that a test must reach, with the choice asserted --
+def kernels_of(T, k, d, f, S, I, n_shared=0, dtype="bf16"):
+    """Kernels of the gate+up and the down projection on the current device."""
+    dt = grace.GRACE_F32 if dtype == "f32" else grace.GRACE_BF16
+    return tuple(grace.grace_ffn_kernel(up, T, d, f, dt, k=k, S=S, I=I, n_shared=n_shared)[0] for up in (True, False))
+
+
+@pytest.mark.parametrize("seg_rows,k,d,f,want", [
+    ([300], 1, 128, 14336, ("persist", "mid")),       # 2 m-tiles x 112 n-tiles: pairs cut flat over the XCDs, the shortest K
+    ([300], 1, 13312, 128, ("mid", "persist")),       # the same for the down projection, 2 x 52
+    ([700], 1, 6656, 4096, ("persist", "persist")),   # fewer tiles than compute units, 104 and 64 K steps
+    ([0, 1, 3] * 20 + [7] * 9 + [7857], 1, 512, 384, ("persist", "persist")),   # more segments than lanes, most of them a few rows
+])
+def test_large_tiles_of_few_and_of_many_segments(seg_rows, k, d, f, want):
+    T, S = sum(seg_rows), len(seg_rows)
+    assert kernels_of(T, k, d, f, S, S) == want
+    got, ref, off = ffn_of_segments(seg_rows, T, k, d, f)
+    check_segments(got, ref, off, TOL["bf16"])
+    if S == 1:   # the shared experts' launches of the same shape
+        rng = np.random.default_rng(T)
+        x, wg, wu, wd = (torch.from_numpy((a * rng.standard_normal(n)).astype(np.float32)).cuda().to(torch.bfloat16)
+                         for a, n in ((1.0, (T, d)), (0.05, (1, f, d)), (0.05, (1, f, d)), (0.05, (1, d, f))))
+        assert kernels_of(T, 1, d, f, 1, 1, n_shared=1) == want
+        y = grace.grace_shared_ffn(x, wg, wu, wd)
+        ref = oracle.shared_ffn(oracle.widen(host(x)), tuple(oracle.widen(host(w)) for w in (wg, wu, wd)), threads=8)
+        assert rel_err(oracle.widen(host(y)), ref) <= TOL["bf16"]
+
+
+def test_operands_past_two_gigabytes():
+    """K off 64 in rows so long that 128 of them pass 2 GB: no buffer loads, the 128 x 128 kernel."""
+    T, d, f = 3, 8388616, 8
+    assert kernels_of(T, 1, d, f, 1, 1)[0] == "generic"
+    got, want, off = ffn_of_segments([T], T, 1, d, f)
+    check_segments(got, want, off, TOL["bf16"])
+
+
+@pytest.mark.parametrize("T,d,f,n_shared,k", [
+    (3000, 512, 512, 2, 6),      # 1 KB rows, 12 row tiles x 8 column tiles of 8 K steps
+    (1500, 512, 1024, 2, 64),    # the largest top-k: nearly all rows are moved after the tile loop
+    (700, 2048, 1344, 3, 64),    # 4 KB rows, 3 x 32 tiles
+    (1500, 4096, 2048, 1, 3),    # 8 KB rows, 6 x 16 tiles
+])
+def test_row_scatter_carried_by_the_large_tiles(T, d, f, n_shared, k):
+    """grace_shared_ffn_up_scatter where the projection's launch moves the rows (k > 1, dropped positions)."""
+    assert kernels_of(T, k, d, f, 1, 1, n_shared=n_shared)[0] == "persist"
+    parity.test_shared_up_with_row_scatter_equals_the_two_calls(T, d, f, n_shared, k, "bf16")
+
+
+@pytest.mark.parametrize("T,E,k,d,f,dtype,want", [
+    (16, 8, 2, 256, 192, "bf16", ("stream", "stream")),
+    (48, 32, 4, 256, 1024, "bf16", ("mid", "stream")),     # the record is written by one kernel, read by another
+    (48, 80, 4, 1280, 320, "bf16", ("mid", "mid")),
+    (200, 8, 2, 256, 192, "bf16", ("mid", "mid")),
+    (20000, 8, 2, 128, 256, "bf16", ("persist", "mid")),
+    (40000, 8, 2, 128, 128, "bf16", ("persist", "persist")),
+    (40, 8, 2, 132, 100, "f32", ("stream", "stream")),     # fp32, one workgroup per strip
+    (90, 8, 2, 100, 50, "f32", ("stream", "vector_f32")),
+])
+def test_rank_share_after_routing_changes_by_kernel(monkeypatch, T, E, k, d, f, dtype, want):
+    """Rows of y that an earlier step wrote are zero after the rank's range has moved, whichever kernels run."""
+    cfg = LayerConfig(f"{dtype}_share_{T}", T=T, E=E, k=k, d=d, f=f, dtype=dtype, zipf_s=0.5, nodes=1, gpus_per_node=2, n_hot=2,
+                      replica_mode="all", seed=T)
+    table = grace.GraceTable.from_placement(make_workload(cfg).placement)
+    assert kernels_of(T, k, d, f, len(table.local_experts(1)), table.I, dtype=dtype) == want
+    monkeypatch.setitem(parity.SMALL, cfg.name, cfg)
+    parity.test_layer_rank_share_after_routing_changes(cfg.name)

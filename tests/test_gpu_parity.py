@@ -446,6 +446,7 @@ def test_many_tiles_per_workgroup_element_by_element():
     lo, hi = int(ref.perm.rank_off[lr]), int(ref.perm.rank_off[lr + 1])
     seg = np.diff(ref.perm.inst_off[ref.order.rank_ptr[lr]:ref.order.rank_ptr[lr + 1] + 1])
     assert sum(-(-int(m) // 256) for m in seg) * (cfg.f // 128) > 2 * 256      # > 2 tiles per workgroup
+    assert grace.grace_ffn_kernel(True, cfg.T, cfg.d, cfg.f, k=cfg.k, S=len(seg), I=table.I)[0] == "persist"
     wg, wu, wd = _stack_dev(wl, table.local_experts(lr))
     y = grace.grace_expert_ffn(table, lr, g.xp, g.ioff, cfg.T, cfg.k, wg, wu, wd)
     torch.cuda.synchronize()
@@ -455,9 +456,8 @@ def test_many_tiles_per_workgroup_element_by_element():
 
 
 def test_few_row_tiles_many_column_tiles_element_by_element():
-    """Two m-tiles with 36 (up) and 33 (down) n-tiles: dealing whole m-tiles to the XCDs would take
-    two rounds of tiles, so the GEMM cuts the (m-tile, n-tile) pairs flat into eight ranges with the
-    m index running fastest."""
+    """Two row tiles with 36 (up) and 33 (down) column tiles of 256 x 256: pieces of 96 rows at this batch (the large
+    tiles on such a shape: test_large_tiles_of_few_and_of_many_segments)."""
     cfg = LayerConfig("bf16_wide", T=300, E=2, k=1, d=8448, f=4608, dtype="bf16", zipf_s=0.5, nodes=1,
                       gpus_per_node=1, n_hot=1, replica_mode="all", seed=23)
     wl = make_workload(cfg)
@@ -476,8 +476,8 @@ def test_few_row_tiles_many_column_tiles_element_by_element():
 
 
 def test_few_tiles_long_k_element_by_element():
-    """Two m-tiles, 32 (up) and 16 (down) n-tiles, 64 K steps each: fewer tiles than compute units and
-    a long K (the shape of mixtral's projections at a small batch), expert and shared FFN."""
+    """Two row tiles, 32 (up) and 16 (down) column tiles, 64 K steps each: fewer tiles than compute units and
+    a long K (the shape of mixtral's projections at a small batch), expert and shared FFN; pieces of 96 rows."""
     cfg = LayerConfig("bf16_long_k", T=300, E=2, k=1, d=4096, f=4096, dtype="bf16", zipf_s=0.5, nodes=1,
                       gpus_per_node=1, n_hot=1, replica_mode="all", n_shared=1, seed=24)
     wl = make_workload(cfg)
@@ -504,7 +504,7 @@ def test_few_tiles_long_k_element_by_element():
 
 def test_more_than_64_local_slots_element_by_element():
     """A rank hosting more than 64 expert instances (four row segments per lane in the GEMM's
-    segment table), many of them empty or a few rows long."""
+    segment table), many of them empty or a few rows long; pieces of 96 rows."""
     cfg = LayerConfig("bf16_many_slots", T=1500, E=180, k=4, d=128, f=192, dtype="bf16", zipf_s=1.0, nodes=1,
                       gpus_per_node=2, n_hot=4, replica_mode="all", seed=22)
     wl = make_workload(cfg)
@@ -553,6 +553,7 @@ def test_expert_down_projection_every_tile_height(want_hf, seg_rows):
     rows = int(sum(seg_rows))
     rng = np.random.default_rng(100 + want_hf)
     table = grace.GraceTable(E, 1, 1, [0], [1], list(range(E + 1)), [0] * E)      # every expert once, on the one rank
+    assert grace.grace_ffn_kernel(False, rows, d, f, k=k, S=E, I=E)[0] == "persist"
     xp = torch.from_numpy(rng.standard_normal((rows, d)).astype(np.float32)).cuda().to(torch.bfloat16)
     wg = torch.from_numpy((0.05 * rng.standard_normal((E, f, d))).astype(np.float32)).cuda().to(torch.bfloat16)
     wu = torch.from_numpy((0.05 * rng.standard_normal((E, f, d))).astype(np.float32)).cuda().to(torch.bfloat16)
@@ -571,15 +572,16 @@ def test_expert_down_projection_every_tile_height(want_hf, seg_rows):
 
 
 @pytest.mark.parametrize("T,d,f,n_shared,k,dtype", [
-    (3000, 512, 384, 2, 6, "bf16"),     # 1 KB rows, 12 row tiles x 6 column tiles: every workgroup has K steps to copy in
-    (300, 4096, 128, 1, 3, "bf16"),     # 8 KB rows, 2 tiles for 256 workgroups: nearly all rows moved after the tile loop
-    (5000, 1024, 1024, 1, 1, "bf16"),   # k = 1
-    (700, 2048, 256, 3, 64, "bf16"),    # k = 64: the largest top-k
+    (3000, 512, 384, 2, 6, "bf16"),     # 1 KB rows; a launch of its own, as at the next size
+    (300, 4096, 128, 1, 3, "bf16"),     # 8 KB rows
+    (5000, 1024, 1024, 1, 1, "bf16"),   # k = 1; the projection's launch carries the rows
+    (700, 2048, 256, 3, 64, "bf16"),    # k = 64: the largest top-k; a launch of its own
     (333, 136, 200, 1, 2, "bf16"),      # 272-byte rows: the scatter runs as a launch of its own
     (150, 128, 76, 3, 3, "f32"),        # fp32: likewise
 ])
 def test_shared_up_with_row_scatter_equals_the_two_calls(T, d, f, n_shared, k, dtype):
-    """grace_shared_ffn_up_scatter (the shared gate+up projection carrying the row scatter) against
+    """grace_shared_ffn_up_scatter (rows carried by the gate+up projection where the large tiles take it: more sizes in
+    test_row_scatter_carried_by_the_large_tiles; a launch of their own elsewhere) against
     grace_shared_ffn_up + grace_permute_rows, bit for bit, and the rows against the oracle's gather;
     positions outside the buffer (-1: expert outside the table) are skipped."""
     rng = np.random.default_rng(T + d)
@@ -641,8 +643,8 @@ def test_layer_object_rank_share_matches_oracle():
 
 @pytest.mark.parametrize("name", ["tiny", "bf16_ragged", "f32_ragged"])
 def test_layer_rank_share_after_routing_changes(name):
-    """A layer object stepped with changing gate logits (fp32 kernel and the generic bf16 kernel; the
-    persistent kernel is covered by the graph replay test): after every step `y` is the oracle's rank
+    """A layer object stepped with changing gate logits (other kernels and batches:
+    test_rank_share_after_routing_changes_by_kernel): after every step `y` is the oracle's rank
     share for that step's inputs, rows of other ranks zero although earlier steps wrote there."""
     cfg = SMALL[name]
     wl = make_workload(cfg)
