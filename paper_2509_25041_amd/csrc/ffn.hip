@@ -76,7 +76,7 @@ static bool stream_ok(const GemmArgs &g, int kseg_align = strm::kstep<EL>()) {
     const int n_kseg = (g.K + g.kseg_len - 1) / g.kseg_len;
     const int64_t k_bytes = ((n_kseg - 1) * g.kseg_stride + g.kseg_len) * EL;
     return g.K % (16 / EL) == 0 && (n_kseg == 1 || g.kseg_len % kseg_align == 0) &&
-           k_bytes + 128 * std::max(g.lda, g.ldb) * EL < (int64_t)strm::NO_DATA;
+           k_bytes + 128 * std::max(g.lda, g.ldb) * EL < (int64_t)NO_DATA;
 }
 
 // Which kernel takes a launch.
@@ -236,8 +236,13 @@ static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, hi
 template <bool FUSED_UP>
 static void launch_mid(const GemmArgs &g, const Grid &l, hipStream_t st) {
     const int n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
-    if (g.kseg_len < g.K) mid::gemm_bf16_mid_kernel<FUSED_UP, true, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
-    else if (g.S <= 64) mid::gemm_bf16_mid_kernel<FUSED_UP, false, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
+    if constexpr (!FUSED_UP) {   // K segments: the shared experts' down projection alone
+        if (g.kseg_len < g.K) {
+            mid::gemm_bf16_mid_kernel<false, true, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
+            return;
+        }
+    }
+    if (g.S <= 64) mid::gemm_bf16_mid_kernel<FUSED_UP, false, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
     else mid::gemm_bf16_mid_kernel<FUSED_UP, false, 4><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
 }
 

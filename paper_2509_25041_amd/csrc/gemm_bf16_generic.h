@@ -9,7 +9,6 @@
 namespace grace {
 
 // ------------------------------------------------------------------ bf16 MFMA --
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 constexpr int BM = 128, BK = 64;

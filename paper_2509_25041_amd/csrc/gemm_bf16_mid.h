@@ -30,14 +30,9 @@
 #pragma once
 #include "bf16.h"
 #include "gemm_common.h"
-#include "kseg_walk.h"
 
 namespace grace {
 namespace mid {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 constexpr int BM = 96, BK = 64, THREADS = 256;
 constexpr int ROW_BYTES = BK * 2, A_BYTES = BM * ROW_BYTES, B_WAVE_BYTES = 32 * ROW_BYTES, LDS_BYTES = 2 * A_BYTES + 8 * B_WAVE_BYTES;
@@ -47,12 +42,6 @@ struct Shape {
     static constexpr int BN = FUSED_UP ? 64 : 128;    // output columns per workgroup
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const char *base) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)NO_DATA, 0x00020000);
-}
-__device__ __forceinline__ u32x4_t load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, 0);
-}
 __device__ __forceinline__ int chunk_at(int row, int c) { return row * ROW_BYTES + ((c ^ ((row >> 1) & 7)) * 16); }
 
 // MF: activation fragments of 16 rows.  SEG_K: the weights' K axis is cut in segments (shared experts' down

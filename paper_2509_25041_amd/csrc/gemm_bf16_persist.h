@@ -62,9 +62,6 @@
 namespace grace {
 namespace pers {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
 constexpr int BM = 256, BROWS = 256, THREADS = 512, N_XCD = 8;
 constexpr int BK = 64;
 constexpr int NBUF_A = 2, NBUF_B = 3;          // LDS buffers per operand

@@ -4,7 +4,22 @@
 
 #include <cstdint>
 
+#include "kseg_walk.h"
+
 namespace grace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+
+// 16-byte loads at base + lane offset + scalar offset.  A lane offset of NO_DATA is past the descriptor's range
+// and gives zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const char *base) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)NO_DATA, 0x00020000);
+}
+__device__ __forceinline__ u32x4_t load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, 0);
+}
 
 struct GemmArgs {
     const void *A;          // activations, row p at A + p * lda

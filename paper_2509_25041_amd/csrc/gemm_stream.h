@@ -34,10 +34,6 @@
 namespace grace {
 namespace strm {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
-
 constexpr int MAX_ROWS = 64;      // rows a workgroup handles at a time; bf16: rows per segment up to which this kernel is used
 constexpr int STEP_BYTES = 64;    // of K, per row
 constexpr int MAX_WAVES = 16;     // per workgroup; also keeps the kernel at 128 registers = 16 wavefronts per compute unit
@@ -53,16 +49,6 @@ struct Shape {
 
 // LDS bytes of `waves` wavefronts' partial sums (2 weight fragments x mf activation fragments x 1 KB)
 inline int lds_bytes(int waves, int mf) { return waves * mf * 2 * 1024; }
-
-// 16-byte loads at base + lane offset + scalar offset.  A lane offset of NO_DATA is past the descriptor's range
-// and gives zeros.
-constexpr uint32_t NO_DATA = 0x80000000u;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const char *base) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)NO_DATA, 0x00020000);
-}
-__device__ __forceinline__ u32x4_t load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, 0);
-}
 
 // MF: activation fragments of 16 rows the workgroup handles at a time
 template <bool FUSED_UP, int EL, int MF>
