@@ -117,8 +117,8 @@ static bool stream_pieces(const Rows &rows) { return EL == 4 && rows.max_rows > 
 // Streaming kernel.  With at most strm::MAX_ROWS rows per segment, one workgroup per strip of weight rows and
 // segment.  At most one workgroup per strip and row of the batch finds work; with few of those each gets more
 // than four wavefronts (a finer split of K) until the chip holds about 8 wavefronts per compute unit.  More than
-// that does not pay (bf16): 16 per unit took 8.6 instead of 8.2 us on 4 busy segments, 32 took 10.4, and 32.9
-// instead of 28.8 us on 16; two wavefronts per workgroup at the other end took 29.5 us.
+// that does not pay (bf16, weights partly in the last-level cache): 16 per unit took 8.6 instead of 8.2 us on 4 busy
+// segments, 32 took 10.4, and 32.9 instead of 28.8 us on 16; two wavefronts per workgroup at the other end took 29.5 us.
 static int stream_fragments(const Rows &rows) { return rows.max_rows <= 16 ? 1 : rows.max_rows <= 32 ? 2 : 4; }
 template <bool FUSED_UP, int EL>
 static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
@@ -150,40 +150,42 @@ static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &
     return {(rows.m_bound / FBM + g.S) * ((g.N + FBN - 1) / FBN), 256};
 }
 
-// Row pieces of at most bm rows that `rows` rows of up to n_seg segments make: ragged ends add halves / 2 pieces to every
+// Row pieces of at most bm rows that `rows` rows of up to n_seg segments make: ragged ends add quarters / 4 pieces to every
 // segment that has rows.
-static int64_t pieces_of(int64_t rows, int n_seg, int bm, int halves) {
+static int64_t pieces_of(int64_t rows, int n_seg, int bm, int quarters) {
     if (n_seg == 1) return (rows + bm - 1) / bm;
     const int64_t hit = std::max<int64_t>(1, std::min<int64_t>(n_seg, rows));
-    return std::max(hit, (2 * rows + halves * hit * bm) / (2 * bm));
+    return std::max(hit, (4 * rows + quarters * hit * bm) / (4 * bm));
 }
 
 // The 96-row kernel against 256 x 256 tiles.  The large tiles take their time by whole rounds over the compute units,
 // however few rows a tile holds; the 96-row kernel by the number of its tiles.  With the rows of every segment known the line
 // is sharp: gate+up, 2 x n_cu tiles while the large kernel needs one round and 3 x n_cu for every further round, down
-// (where the large tiles adapt their height) 1.6 and 2.6.  The host knows them for the shared experts, and their sum
-// where a rank hosts all instances (2.1 in place of 1.6 there, as whole pieces are counted extra).  Elsewhere ranks hold
-// 0.5 to 3.2 times their instances' even share in the tables of the planner.  At some loads the large tiles just fill
-// their rounds, so the 96-row kernel is taken only if it is the cheaper one, by a little more, at each of 1, 3/2 and
-// 9/4 of the even share.
+// (where the large tiles adapt their height) about 2 and 2.6.  The host knows the rows for the shared experts, and their sum
+// where a rank hosts all instances.  Elsewhere ranks hold 0.5 to 3.2 times their instances' even share in the tables of
+// the planner.  At some loads the large tiles just fill their rounds, so the 96-row kernel is taken only if it is the
+// cheaper one at the even share and at 7/4 (gate+up) or 3 times (down, where a wrong choice costs more) of it.  Higher
+// loads in the check lose more where ranks hold less than they save where one holds it (gate+up at 512 tokens, d = 2048,
+// f = 1024: 50.7 instead of 37.5 us with 9/4).
 //
-// Measured over 4014 projections (53 ranks of tables for five layer shapes, expert widths whole to a quarter, 1 to 32
-// ranks, 1 to 12000 tokens, three sets of weights in turn): 202.5 ms with large tiles only, 158.6 with this rule and the one
-// below, 155.4 with the best kernel each time.  37 projections are slower than with large tiles by more than 3 % and
-// 1 us, by 22 % at most (a rank with 3.2 times its share, 45.7 -> 55.8 us); taking all projections of a layer step together
-// 7 of 1531 steps are by more than 3 %, by 6 us at most.  With one guess of three times the even share and limits of 3 and 2
-// tiles per round and compute unit (159.0 ms) 164 projections and 63 steps were, by up to 78 us.
+// Measured over 3182 projections inside layer steps (53 ranks of tables for five layer shapes, expert widths whole to a
+// quarter, 1 to 32 ranks, 17 to 12000 tokens, three sets of weights in turn, the row scatter included where the large tiles
+// carry it): 189.1 ms with large tiles only, 152.5 with this rule and the one below, 149.9 with the best kernel each
+// time.  50 projections are slower than with large tiles by more than 3 % and 1 us, by 40 % at most (a rank with 3.1
+// times its share, 84.5 -> 118.5 us); of the 1220 steps, taking their projections together, 2 are slower by 1.5 % or more of a
+// whole step, by 3 us.  With one guess of three times the even share and limits of 3 and 2 tiles per round and compute
+// unit (153.7 ms) 169 projections and 59 steps were, by up to 79 us.
 template <bool FUSED_UP>
 static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
     const int64_t strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
     const int64_t large_strips = (g.N + pers::Shape<FUSED_UP>::BN - 1) / pers::Shape<FUSED_UP>::BN;
     const bool known = rows.even_only && g.S > 1;
-    for (const int load : {4, 6, 9}) {   // quarters of the even share
+    for (const int load : {4, FUSED_UP ? 7 : 12}) {   // quarters of the even share
         const int64_t m = rows.at(load);
-        const int64_t tiles = pieces_of(m, g.S, mid::BM, FUSED_UP ? 1 : 2) * strips;
-        const int64_t rounds = (pieces_of(m, g.S, pers::BM, 1) * large_strips + n_cu - 1) / n_cu;
+        const int64_t tiles = pieces_of(m, g.S, mid::BM, FUSED_UP ? 2 : 3) * strips;
+        const int64_t rounds = (pieces_of(m, g.S, pers::BM, 2) * large_strips + n_cu - 1) / n_cu;
         // in tenths of n_cu
-        const int64_t limit = FUSED_UP ? 30 * rounds - (known ? 10 : 11) : 26 * rounds - (known ? 5 : 10);
+        const int64_t limit = FUSED_UP ? 30 * rounds - (known ? 10 : 11) : 26 * rounds - 5;
         if (10 * tiles > n_cu * limit) return false;
         if (rows.even_only) break;
     }
@@ -192,10 +194,10 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
 
 // bf16, up to 64 rows per segment: the streaming kernel, which splits the work finest, while the 96-row kernel's tiles
 // would not fill the chip.  A gate+up projection of more than 16 rows leaves it when the other has a tile for three quarters
-// of the compute units (above that line and 32 tokens it takes 0.9 to 1.7 of the 96-row kernel's time, 1.2 in the
-// middle), a down projection when there are one and a half per unit (all 60 qwen-shaped experts on one GPU, 64
-// tokens: large tiles 29.0 us, streaming 29.9 us, 96 rows 26.4 us).  With less than half a tile per unit it takes 0.4 to 0.8 of the
-// 96-row kernel's time; around the lines and with up to 16 tokens the two differ by up to 40 % either way, 0 to 10 % in the middle.
+// of the compute units (above that line it takes 0.9 to 1.8 of the 96-row kernel's time, 1.0 to 1.3 in the middle), a down
+// projection when there are one and a half per unit (1.0 to 1.6, 1.2 to 1.5 in the middle; all 60 qwen-shaped experts on one GPU,
+// 64 tokens: large tiles 32.2 us, streaming 41.5 us, 96 rows 28.5 us).  With less than half a tile per unit it takes
+// 0.5 to 0.9 of the 96-row kernel's time, between the two 0.7 to 1.5, 1.0 in the middle.
 template <bool FUSED_UP>
 static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };

@@ -34,22 +34,23 @@ def test_invalid_arguments_are_refused():
 # (up, T, k, d, f, S, I): projections of one rank (S of I instances) that the 96-row kernel took, or the streaming one, while
 # 256 x 256 tiles were faster: us before / on large tiles.
 @pytest.mark.parametrize("up,T,k,d,f,S,I,want", [
-    (True, 4556, 4, 2048, 1408, 7, 64, "persist"),      # 87.1 / 57.1: the rank's rows just fill one round of large tiles
-    (True, 2565, 8, 2048, 768, 19, 134, "persist"),     # 81.4 / 58.5
-    (True, 1900, 2, 4096, 7168, 1, 10, "persist"),      # 134.6 / 99.2
-    (True, 1630, 2, 4096, 3584, 8, 8, "persist"),       # 279.9 / 201.9: every instance here
-    (True, 2120, 8, 2048, 256, 64, 64, "persist"),      # 76.8 / 59.2
-    (False, 761, 8, 2048, 1024, 16, 66, "persist"),     # 33.8 / 25.3
-    (False, 64, 4, 2048, 1408, 60, 60, "mid"),          # streaming 29.9 / 29.0; 26.4 on the 96-row kernel
+    (True, 3583, 4, 2048, 1408, 7, 64, "persist"),      # 87.7 / 55.9: the rank's rows just fill one round of large tiles
+    (True, 2756, 8, 2048, 768, 19, 134, "persist"),     # 86.5 / 55.8
+    (True, 1630, 2, 4096, 1792, 8, 8, "persist"),       # 152.0 / 101.6: every instance here
+    (True, 1630, 2, 4096, 3584, 8, 8, "persist"),       # 273.9 / 194.5
+    (True, 2120, 8, 2048, 256, 64, 64, "persist"),      # 74.2 / 57.1
+    (False, 1254, 8, 2048, 768, 19, 134, "persist"),    # 30.3 / 23.5
+    (False, 64, 4, 2048, 1408, 60, 60, "mid"),          # streaming 41.5 / 32.2; 28.5 on the 96-row kernel
+    (False, 48, 6, 2048, 1408, 64, 64, "mid"),          # streaming 51.8 / 38.5; 35.2
 ])
 def test_large_tiles_where_they_are_faster(up, T, k, d, f, S, I, want):
     assert grace.grace_ffn_kernel(up, T, d, f, BF16, k=k, S=S, I=I, n_cu=N_CU)[0] == want
 
 
-@pytest.mark.parametrize("T,d,f,n_shared", [(2756, 2048, 704, 2), (6055, 2048, 704, 2)])
+@pytest.mark.parametrize("T,d,f,n_shared", [(2756, 2048, 704, 2), (6055, 2048, 704, 2), (1254, 2048, 1408, 2), (571, 2048, 1408, 4)])
 def test_shared_projection_keeps_the_row_scatter(T, d, f, n_shared):
     """Gate+up projections of shared experts that were slower without the large-tile kernel, which carries the row scatter
-    (70.0 / 56.4 and 137.4 / 106.2 us, six rows per token scattered)."""
+    (67.1 / 58.1, 135.1 / 113.9, 65.5 / 54.8 and 58.7 / 49.4 us, the scatter of six or four rows per token included)."""
     assert grace.grace_ffn_kernel(True, T, d, f, BF16, n_shared=n_shared, n_cu=N_CU)[0] == "persist"
 
 

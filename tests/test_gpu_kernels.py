@@ -188,8 +188,8 @@ def kernels_of(T, k, d, f, S, I, n_shared=0, dtype="bf16"):
 
 @pytest.mark.parametrize("seg_rows,k,d,f,want", [
     ([300], 1, 128, 14336, ("persist", "mid")),       # 2 m-tiles x 112 n-tiles: pairs cut flat over the XCDs, the shortest K
-    ([300], 1, 13312, 128, ("mid", "persist")),       # the same for the down projection, 2 x 52
-    ([700], 1, 6656, 4096, ("persist", "persist")),   # fewer tiles than compute units, 104 and 64 K steps
+    ([300], 1, 17408, 128, ("mid", "persist")),       # the same for the down projection, 2 x 68
+    ([700], 1, 8704, 4096, ("persist", "persist")),   # fewer tiles than compute units, 136 and 64 K steps
     ([0, 1, 3] * 20 + [7] * 9 + [7857], 1, 512, 384, ("persist", "persist")),   # more segments than lanes, most of them a few rows
 ])
 def test_large_tiles_of_few_and_of_many_segments(seg_rows, k, d, f, want):
@@ -233,7 +233,7 @@ def test_row_scatter_carried_by_the_large_tiles(T, d, f, n_shared, k):
     (48, 80, 4, 1280, 320, "bf16", ("mid", "mid")),
     (200, 8, 2, 256, 192, "bf16", ("mid", "mid")),
     (20000, 8, 2, 128, 256, "bf16", ("persist", "mid")),
-    (40000, 8, 2, 128, 128, "bf16", ("persist", "persist")),
+    (25000, 8, 2, 256, 128, "bf16", ("persist", "persist")),
     (40, 8, 2, 132, 100, "f32", ("stream", "stream")),     # fp32, one workgroup per strip
     (90, 8, 2, 100, 50, "f32", ("stream", "vector_f32")),
 ])
