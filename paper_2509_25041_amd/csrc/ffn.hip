@@ -151,45 +151,52 @@ static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &
 }
 
 // Row pieces of at most bm rows that `rows` rows of up to n_seg segments make: ragged ends add quarters / 4 pieces to every
-// segment that has rows.
-static int64_t pieces_of(int64_t rows, int n_seg, int bm, int quarters) {
+// segment that has rows.  Where most segments hold less than a piece the few hot ones still make hot / 4 of what all rows
+// together would: a piece per segment may just fill the large kernel's rounds.
+static int64_t pieces_of(int64_t rows, int n_seg, int bm, int quarters, int hot) {
     if (n_seg == 1) return (rows + bm - 1) / bm;
     const int64_t hit = std::max<int64_t>(1, std::min<int64_t>(n_seg, rows));
-    return std::max(hit, (4 * rows + quarters * hit * bm) / (4 * bm));
+    return std::max(4 * hit * bm + hot * rows, 4 * rows + quarters * hit * bm) / (4 * bm);
 }
 
 // The 96-row kernel against 256 x 256 tiles.  The large tiles take their time by whole rounds over the compute units,
 // however few rows a tile holds; the 96-row kernel by the number of its tiles.  With the rows of every segment known the line
 // is sharp: gate+up, 2 x n_cu tiles while the large kernel needs one round and 3 x n_cu for every further round, down
 // (where the large tiles adapt their height) about 2 and 2.6.  The host knows the rows for the shared experts, and their sum
-// where a rank hosts all instances.  Elsewhere ranks hold 0.5 to 3.2 times their instances' even share in the tables of
+// where a rank hosts all instances.  Elsewhere ranks hold 0.5 to 4.9 times their instances' even share in the tables of
 // the planner.  At some loads the large tiles just fill their rounds, so the 96-row kernel is taken only if it is the
-// cheaper one at the even share and at 7/4 (gate+up) or 3 times (down, where a wrong choice costs more) of it.  Higher
-// loads in the check lose more where ranks hold less than they save where one holds it (gate+up at 512 tokens, d = 2048,
-// f = 1024: 50.7 instead of 37.5 us with 9/4).
+// cheaper one at the even share and at 7/4 (gate+up) or 3 times (down, where a wrong choice costs more) of it, and
+// has at most 3 (gate+up) or 2 tiles per round and compute unit for a rank with three times its share.  Higher loads in the
+// check lose more where ranks hold less than they save where one holds it (gate+up at 512 tokens, d = 2048, f = 1024: 50.7
+// instead of 37.5 us with 9/4).
 //
 // Measured over 3182 projections inside layer steps (53 ranks of tables for five layer shapes, expert widths whole to a
 // quarter, 1 to 32 ranks, 17 to 12000 tokens, three sets of weights in turn, the row scatter included where the large tiles
 // carry it): 189.1 ms with large tiles only, 152.5 with this rule and the one below, 149.9 with the best kernel each
-// time.  50 projections are slower than with large tiles by more than 3 % and 1 us, by 40 % at most (a rank with 3.1
-// times its share, 84.5 -> 118.5 us); of the 1220 steps, taking their projections together, 2 are slower by 1.5 % or more of a
-// whole step, by 3 us.  With one guess of three times the even share and limits of 3 and 2 tiles per round and compute
-// unit (153.7 ms) 169 projections and 59 steps were, by up to 79 us.
+// time.  49 projections are slower than with large tiles by more than 3 % and 1 us, by 40 % at most (a rank with 3.1
+// times its share, 84.5 -> 118.5 us); of the 1220 steps, taking their projections together, one is slower by 1.5 % or more of a
+// whole step, by 3 us.  With the condition at three times the share alone (153.7 ms) 169 projections and 59 steps were, by up
+// to 79 us.
 template <bool FUSED_UP>
 static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
     const int64_t strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
     const int64_t large_strips = (g.N + pers::Shape<FUSED_UP>::BN - 1) / pers::Shape<FUSED_UP>::BN;
+    constexpr int HOT = FUSED_UP ? 1 : 0;   // (the down projection's large tiles get lower instead)
     const bool known = rows.even_only && g.S > 1;
     for (const int load : {4, FUSED_UP ? 7 : 12}) {   // quarters of the even share
         const int64_t m = rows.at(load);
-        const int64_t tiles = pieces_of(m, g.S, mid::BM, FUSED_UP ? 2 : 3) * strips;
-        const int64_t rounds = (pieces_of(m, g.S, pers::BM, 2) * large_strips + n_cu - 1) / n_cu;
+        const int64_t tiles = pieces_of(m, g.S, mid::BM, FUSED_UP ? 2 : 3, HOT) * strips;
+        const int64_t rounds = (pieces_of(m, g.S, pers::BM, 2, HOT) * large_strips + n_cu - 1) / n_cu;
         // in tenths of n_cu
         const int64_t limit = FUSED_UP ? 30 * rounds - (known ? 10 : 11) : 26 * rounds - 5;
         if (10 * tiles > n_cu * limit) return false;
         if (rows.even_only) break;
     }
-    return true;
+    if (known) return true;
+    // a rank that holds three times its share, with a whole piece extra for every segment
+    const int64_t m = rows.at(12), hit = std::max<int64_t>(1, std::min<int64_t>(g.S, m));
+    const int64_t rounds = ((m / pers::BM + hit) * large_strips + n_cu - 1) / n_cu;
+    return (m / mid::BM + hit) * strips <= n_cu * rounds * (FUSED_UP ? 3 : 2);
 }
 
 // bf16, up to 64 rows per segment: the streaming kernel, which splits the work finest, while the 96-row kernel's tiles
@@ -198,6 +205,8 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
 // projection when there are one and a half per unit (1.0 to 1.6, 1.2 to 1.5 in the middle; all 60 qwen-shaped experts on one GPU,
 // 64 tokens: large tiles 32.2 us, streaming 41.5 us, 96 rows 28.5 us).  With less than half a tile per unit it takes
 // 0.5 to 0.9 of the 96-row kernel's time, between the two 0.7 to 1.5, 1.0 in the middle.
+// Down projections of few steps along K stay with it up to 32 tokens: the 96-row kernel's start-up is then most of its
+// time (21 tokens, d = 2048, f = 384, 128 segments: a call takes 64.2 us with the streaming kernel, 72.0 with the other).
 template <bool FUSED_UP>
 static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };
@@ -206,8 +215,8 @@ static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int
     if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM)) {
         const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(g.S, rows.at(12)));
         const int64_t tiles = busy * ((g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN);
-        if (!mid_ok || (FUSED_UP ? rows.max_rows <= 16 || tiles <= n_cu * 3 / 4 : tiles <= n_cu * 3 / 2)) return Route::STREAM;
-        if (!FUSED_UP) return Route::MID;
+        if (!mid_ok || rows.max_rows <= 16 || tiles <= (FUSED_UP ? n_cu * 3 / 4 : n_cu * 3 / 2)) return Route::STREAM;
+        if (!FUSED_UP) return rows.max_rows > 32 || g.K >= 1024 ? Route::MID : Route::STREAM;
     }
     const bool persist_ok = g.K % pers::BK == 0 && g.kseg_len % pers::BK == 0 && g.K >= pers::MIN_K_STEPS * pers::BK;
     if (!mid_ok) return persist_ok ? Route::PERSIST : Route::GENERIC;

@@ -61,6 +61,8 @@ def test_shared_projection_keeps_the_row_scatter(T, d, f, n_shared):
     (True, 200, 8, 2048, 1024, 0, 64, 64, "mid"), (True, 300, 1, 2048, 1408, 2, 1, 1, "mid"),
     (True, 32768, 1, 2048, 1408, 2, 1, 1, "persist"), (True, 8192, 8, 2048, 768, 0, 16, 130, "persist"),
     (False, 3001, 6, 2048, 352, 0, 2, 69, "mid"),       # K no multiple of 64
+    (False, 21, 8, 2048, 384, 0, 128, 128, "stream"),   # a whole call 64.2 us, 72.0 with the 96-row kernel
+    (False, 33, 8, 2048, 384, 0, 128, 128, "mid"), (False, 16, 8, 2048, 1408, 0, 64, 64, "stream"),
 ])
 def test_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
     assert grace.grace_ffn_kernel(up, T, d, f, BF16, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU)[0] == want
