@@ -21,7 +21,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3     # fp32 vector
+PEAK_F32_TFLOPS = 157.3     # fp32 vector and matrix
 PEAK_HBM_GBS = 8000.0
 HEADLINE = "dsv2lite"
 OTHERS = ("olmoe", "mixtral", "qwen", "qwen3moe", "olmoe_decode64", "olmoe_decode512", "tiny")
@@ -35,6 +35,9 @@ KERNEL_OF_STAGE = {
     "combine": "combine_kernel (weighted gather to token order)",
     "route_permute": "topk + pick + positions + scatter_rows_kernel (one call; the row scatter moves the bytes)",
 }
+# the projections where the library chooses another kernel than the large tiles for the batch
+OTHER_KERNEL = {"stream": "gemm_stream kernel", "mid": "gemm_bf16_mid_kernel", "generic": "gemm_bf16_kernel",
+                "vector_f32": "gemm_f32_kernel"}
 
 
 def host_info():
@@ -164,9 +167,14 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
     bytes_route = T * (4 * cfg.E + 12 * k)
     bytes_permute = T * d * el + T * k * d * el + 12 * T * k
     bytes_combine = T * k * d * el + T * d * el * (2 if sh is not None else 1) + 8 * T * k
-    # with shared experts the row scatter rides on the shared gate+up projection's launch: the dispatch call
-    # then builds only the index arrays
+    # with shared experts the dispatch call builds only the index arrays; the row scatter rides on the shared gate+up
+    # projection's launch where the large tiles take that, else it is a launch of its own
     fused_scatter = bool(getattr(layer, "fuse_scatter", False)) and sh is not None
+    kernels = {}
+    for stage, up, n_sh in (("ffn_up", True, 0), ("ffn_down", False, 0), ("shared_up", True, cfg.n_shared), ("shared_down", False, cfg.n_shared)):
+        if not stage.startswith("shared") or n_sh:
+            kernels[stage] = grace.grace_ffn_kernel(up, T, d, f, layer.dt, k=k, S=max(1, len(experts)), I=table.I, n_shared=n_sh)[0]
+    carries_rows = fused_scatter and kernels["shared_up"] == "persist" and d * el % 1024 == 0
     bytes_dispatch = bytes_route + (12 * T * k if fused_scatter else bytes_permute)
     # algorithmic work per launch of the kernel behind each call: (bound, amount, unit scale, peak)
     work = {
@@ -259,7 +267,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
     # the shared gate+up projection carries the row scatter: also time the projection by itself (outside the
     # timed region), so that the line shows what the scatter costs it
     carried = None
-    if fused_scatter and dominant == "shared_up":
+    if carries_rows and dominant == "shared_up":
         import ctypes as C
         lib = grace.load_library()
         sg, su, _ = shd
@@ -302,8 +310,10 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
                    "local_rows": m_loc, "local_slots": int(len(experts)),
                    "rows_per_slot_min_max": [int(seg.min()), int(seg.max())] if len(seg) else [0, 0],
                    "n_shared": cfg.n_shared, "working_set_MB": ws_bytes / 1e6,
-                   "row_scatter": "carried by the shared gate+up projection's launch" if fused_scatter else "in the dispatch call"},
-        "roofline": {"kernel": KERNEL_OF_STAGE[dominant] if cfg.dtype == "bf16" and cfg.T >= 4096 else f"{dominant} (kernel chosen by type and batch)",
+                   "row_scatter": "carried by the shared gate+up projection's launch" if carries_rows else
+                   "a launch of its own ahead of the shared gate+up projection" if fused_scatter else "in the dispatch call"},
+        "roofline": {"kernel": KERNEL_OF_STAGE[dominant] if kernels.get(dominant, "persist") == "persist"
+                     else f"{OTHER_KERNEL[kernels[dominant]]} ({dominant})",
                      "stage": dominant, "bound": work[dominant][0], "achieved": ach, "peak": peak, "unit": unit,
                      "frac": ach / peak, "traffic": traffic, "avg_launch_ms": dom_ms,
                      "algorithmic_per_launch": work[dominant][1], "carries": carried},

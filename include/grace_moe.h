@@ -321,10 +321,11 @@ int grace_shared_ffn_down(int32_t T, int32_t d, int32_t f, int32_t n_shared, gra
 
 /* grace_shared_ffn_up and grace_permute_rows (the row movement of Section 5's dispatch order) as one
  * call: both read only x (and perm_pos), the projection is bound by the matrix cores and the row
- * movement by HBM, so for bf16 rows that are multiples of 1024 bytes the persistent kernel of the
- * projection carries the rows along (every wavefront moves a 1 KB piece of a token row every few K
- * steps) instead of a launch of its own; other shapes run the two launches.  Outputs are those of the
- * two calls, bit for bit: the hidden activation in ws and xp[perm_pos[t*k+j]] = x[t].
+ * movement by HBM, so where the large-tile kernel takes the projection (GRACE_KERNEL_PERSIST of
+ * grace_ffn_kernel: large batches, d a multiple of 64) and rows are multiples of 1024 bytes it carries
+ * them along (every wavefront moves a 1 KB piece of a token row every few K steps) instead of a launch
+ * of its own; other shapes and batches run the two launches.  Outputs are those of the two calls, bit
+ * for bit: the hidden activation in ws and xp[perm_pos[t*k+j]] = x[t].
  * DEVICE: perm_pos [T*k] from grace_permute / grace_route_permute called with x == NULL; xp [T*k,d];
  * the rest as for grace_shared_ffn_up.  xp must not overlap x or ws. */
 int grace_shared_ffn_up_scatter(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,
@@ -360,7 +361,7 @@ typedef enum {
     GRACE_KERNEL_STREAM = 0,     /* weights streamed, few rows per segment; fp32 of any size */
     GRACE_KERNEL_MID = 1,        /* 96-row pieces x 128 weight rows */
     GRACE_KERNEL_PERSIST = 2,    /* 256 x 256 tiles, one workgroup per compute unit */
-    GRACE_KERNEL_GENERIC = 3,    /* 128 x 128 tiles: K no multiple of 64 and operands past 2 GB */
+    GRACE_KERNEL_GENERIC = 3,    /* 128 x 128 tiles: K no multiple of 64 and operands past 2 GB, or too many work-items */
     GRACE_KERNEL_VECTOR_F32 = 4  /* fp32 on the vector ALUs: rows that are no whole 16-byte vectors */
 } grace_kernel;
 int grace_ffn_kernel(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I,

@@ -7,9 +7,10 @@
 namespace grace {
 
 // Bound by HBM for large batches, by the chain position -> row for small ones: positions and rows of AHEAD
-// choices are loaded before the first is used (k = 8, d = 2048, 1 ahead -> 4: 1 token 5.6 -> 3.2 us, 64 tokens
-// 6.1 -> 3.8 us, 512 tokens 7.5 -> 5.4 us).  With AHEAD > 1 an absent row loads row 0, which is not added: a branch
-// around each load makes the loads wait for one another (4.5 / 5.3 / 6.8 us).
+// choices are loaded before the first is used (k = 8, d = 2048, the kernel repeated over six inputs, 1 ahead -> 4: 1 token
+// 2.9 -> 2.2 us, 64 tokens 3.9 -> 3.4 us, 512 tokens 7.8 -> 5.3 us; inside a layer step, behind another kernel: 5.6 -> 3.8,
+// 6.1 -> 4.6, 7.5 -> 5.4 us).  With AHEAD > 1 an absent row loads row 0, which is not added: a branch around each load
+// makes the loads wait for one another (1.3 to 1.5 us more).
 template <bool BF16, int AHEAD>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ y, const int32_t *__restrict__ perm_pos,
                                                       const float *__restrict__ topk_weight, int k, int row_vec,

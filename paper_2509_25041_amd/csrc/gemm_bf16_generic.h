@@ -1,7 +1,7 @@
 // Generic bf16 MFMA grouped GEMM: 128x128 block tiles, register-staged loads
 // with zero fill, any K and N that are multiples of 8.  For what the other kernels
-// cannot take: more than 256 row segments with more than 64 tokens, or operands
-// whose offsets from one base pass 2 GB.
+// cannot take: K no multiple of 64 and operands whose offsets from one base pass
+// 2 GB, or launches whose work-items would not fit 32 bits.
 #pragma once
 #include "bf16.h"
 #include "gemm_common.h"

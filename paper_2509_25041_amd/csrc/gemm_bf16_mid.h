@@ -9,8 +9,8 @@
 // matrix); two fit a compute unit.  The wavefronts split the weight rows, and everything is loaded into registers
 // AHEAD steps of 64 K ahead (weights in flight per compute unit: 128 KB, twice that for up to 32 rows), in whole
 // 128-byte lines: 8 lanes per row.  Loading weights in the MFMA's own layout (row = lane % 16) instead touches a
-// line per lane and makes the address unit the bound (decode batch of 512: 48 / 29 instead of 38 / 23 us for the
-// two projections).  One step ahead of its use a step's data goes to one of two LDS buffers: the activation rows,
+// line per lane and makes the address unit the bound (decode batch of 512: 48 instead of 38 us for the gate+up
+// projection).  One step ahead of its use a step's data goes to one of two LDS buffers: the activation rows,
 // which all four wavefronts read, and each wavefront's own weights (16-byte chunk c of row r at
 // c ^ ((r >> 1) & 7): no bank conflicts), with one barrier per step.  The order of fragment reads and MFMAs is
 // fixed, so that a read has a pass of MFMAs to arrive.  Loads past K, past the piece's rows or past N are given
@@ -22,11 +22,13 @@
 // pieces that read the same weights run next to each other on one L2, and every XCD gets hot and cold segments
 // (8 runs: 42 instead of 39 us on the batch of 512).
 //
-// Measured, 256 x 256 tiles -> this kernel (up / down projection, us): d = 2048, f = 1024, 16 segments, 70 tokens
-// 33 / 21 -> 21 / 14, 512 tokens 51 / 27 -> 38 / 23 (134 + 67 MB: 3.5 / 2.9 TB/s, of which about 7 us are launch,
-// segment table and first loads); d = 2048, f = 768, 16 segments, 1000 tokens 46 -> 26 (up); d = 4096,
-// f = 14336, one segment, 512 tokens 87 / 229 -> 75 / 120.  K that is no multiple of 64 took a kernel without
-// prefetch before: 3001 rows, N = 2048, K = 2 x 352 58 -> 20 us.
+// Measured with cold weights, all segments in use (more than 1 GB of others between two uses; up / down projection, 256 x 256
+// tiles -> this kernel, us): 16 segments of d = 2048, f = 1024, 2236 rows with Zipf-shaped shares 49.3 / 27.3 -> 43.3 /
+// 27.0, 300 rows 42.5 / 24.7 -> 44.0 / 22.8; f = 768, 985 rows 44.2 / 22.8 -> 29.5 / 20.4; d = 4096, f = 14336, one
+// segment of 64 rows 72.4 / 199.6 -> 56.2 / 111.9, of 512 rows 96.8 / 195.1 -> 176.5 / 120.3 (the choice takes large tiles
+// for the first of the two).  A rank of an OLMoE-shaped layer whose routing leaves segments empty, three sets of weights
+// in turn: 70 tokens, 11 of 16 segments in use 34.0 / 16.4 -> 21.5 / 13.3, 230 tokens, 13 of 16 44.3 / 19.3 -> 27.7 / 17.7.
+// K that is no multiple of 64 took a kernel without prefetch before: 3001 rows, N = 2048, K = 2 x 352 58 -> 20 us.
 #pragma once
 #include "bf16.h"
 #include "gemm_common.h"

@@ -13,12 +13,15 @@
 // bf16, few rows: bound by HBM (the weights).  The activation rows come from L2 (every workgroup of a segment
 // reads the same few), at most twice the bytes of the weights at 64 rows.  The large-tile kernel
 // (gemm_bf16_persist.h) is the wrong shape there: 256 weight rows per workgroup leave most compute units without
-// a tile, and a 256-row activation tile is mostly clamped duplicates.  Measured (up / down projection, large-tile
-// kernel before -> this one): 16 segments of d = 2048, f = 1024 and 122 rows in all 38.1 / 22.0 -> 28.8 / 16.8 us
-// (134 + 67 MB: 4.7 / 4.0 TB/s; a large copy moves 5.1 TB/s); 4 rows in 4 segments 26.4 / 15.3 -> 8.2 / 5.1 us;
-// 22 rows in 16 segments of f = 768 27.4 / 13.3 -> 12.0 / 8.2 us.  Register depths of 4 to 8 steps make no
-// difference; with about 160 registers (12 wavefronts per compute unit, so that 1024 workgroups no longer run at
-// once) the first case took 30.4 us, with nt loads 3 us more.
+// a tile, and a 256-row activation tile is mostly clamped duplicates.  Measured with cold weights (more than 1 GB of
+// others between two uses; up / down projection, large tiles -> this kernel, us): 16 segments of d = 2048, f = 1024, 122
+// rows in all of them 39.9 / 22.2 -> 29.8 / 16.1 (134 + 67 MB: 4.5 / 4.2 TB/s; a large copy moves 5.1 TB/s); a row in
+// each of 4 of them 32.0 / 19.2 -> 13.9 / 8.6; 22 rows in all 16 segments of f = 768 36.1 / 19.6 -> 21.4 / 12.0.  The
+// 96-row kernel takes 35.4 / 16.2, 17.0 / 10.9 and 25.9 / 12.9 there; with a third of the segments empty, as skewed routing
+// leaves them, it is even or ahead, and it is far ahead where a few rows meet many strips (d = 4096, f = 14336, one segment of 64
+// rows, up: 56 instead of 106 us), so gate+up projections of more than 16 tokens go there when its tiles fill the
+// chip.  Register depths of 4 to 8 steps make no difference; with about 160 registers (12 wavefronts per compute unit, so
+// that 1024 workgroups no longer run at once) the first case took 1.6 us more, with nt loads 3 us more.
 //
 // fp32, any number of rows: d = 1024, f = 2816, 8 segments and 977 rows in all, up / down projection 351 / 492 us on the
 // vector ALUs -> 175 / 108 us (64 / 52 TFLOP/s; the matrix cores are busy 45 % of the time).  What bounds it is the

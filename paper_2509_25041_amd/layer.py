@@ -65,9 +65,9 @@ class GraceMoELayer:
         # routing and permutation as one call (fewer launches than grace_route + grace_permute);
         # False: the two separate calls
         self.single_call_dispatch = True
-        # with shared experts: the dispatch call builds only the index arrays and the row scatter rides
-        # on the shared experts' gate+up projection (grace_shared_ffn_up_scatter), which then runs
-        # ahead of the expert FFN; False: the scatter is part of the dispatch call
+        # with shared experts: the dispatch call builds only the index arrays and the row scatter is part of the shared
+        # experts' gate+up projection (grace_shared_ffn_up_scatter: carried by its launch for large batches, a launch
+        # ahead of it otherwise), which then runs ahead of the expert FFN; False: the scatter is part of the dispatch call
         self.fuse_scatter = self.n_shared > 0
         self.ws_shared = None
         self._key = None
