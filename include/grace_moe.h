@@ -342,6 +342,14 @@ int grace_shared_ffn_up_scatter(const void *x, int32_t T, int32_t d, int32_t f, 
 int grace_combine(const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T, int32_t k, int32_t d,
                   grace_dtype dt, const void *y_shared, void *out, void *stream);
 
+/* grace_combine of a rank share: y as grace_expert_ffn_up_share / _down_share with the same `state` have just left it on
+ * the same stream, so that rows outside the rank's range of the step are zero and need not be read.  Same result as
+ * grace_combine of that y; y must hold nothing else in those rows (a caller that has put other ranks' rows there
+ * uses grace_combine).  DEVICE: state [GRACE_SHARE_STATE_INTS] of the step; the rest as for grace_combine. */
+int grace_combine_share(const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T, int32_t k,
+                        int32_t d, grace_dtype dt, const void *y_shared, const int32_t *state, void *out,
+                        void *stream);
+
 /* ---- diagnostics ---------------------------------------------------------------
  * Measures the bf16 MFMA rate the current device sustains with the grouped GEMM's
  * inner instruction mix (v_mfma_f32_16x16x32_bf16, 12 fragment reads per 32 of them)

@@ -15,6 +15,7 @@ from .binding import (  # noqa: F401
     GraceError,
     GraceTable,
     grace_combine,
+    grace_combine_share,
     grace_expert_ffn,
     grace_expert_ffn_down,
     grace_expert_ffn_down_share,

@@ -21,7 +21,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_route",
            "grace_permute", "grace_permute_rows", "grace_route_permute", "grace_route_permute_static", "grace_send_lists", "grace_expert_ffn", "grace_expert_ffn_up",
            "grace_expert_ffn_down", "grace_expert_ffn_up_share", "grace_expert_ffn_down_share",
-           "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_mfma_sustained",
+           "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_combine_share", "grace_mfma_sustained",
            "grace_ffn_kernel",
            "grace_last_error")
 
@@ -78,6 +78,7 @@ def load_library() -> C.CDLL:
     lib.grace_shared_ffn_up_scatter.argtypes = [vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, i32, vp, vp]
     lib.grace_shared_ffn_down.argtypes = [i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_combine.argtypes = [vp, vp, vp, i32, i32, i32, C.c_int, vp, vp, vp]
+    lib.grace_combine_share.argtypes = [vp, vp, vp, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_mfma_sustained.argtypes = [i32, i32, C.POINTER(C.c_double), vp]
     lib.grace_ffn_kernel.argtypes = [i32] * 8 + [C.c_int, i32, C.POINTER(i32), C.POINTER(C.c_int64)]
     for name in EXPORTS:
@@ -426,6 +427,21 @@ def grace_combine(y: torch.Tensor, perm_pos: torch.Tensor, topk_weight: torch.Te
         out = torch.empty((T, d), dtype=y.dtype, device=y.device)
     _check(load_library().grace_combine(_dp(y), _dp(perm_pos), _dp(topk_weight), T, k, d, _dtype_code(y), _dp(y_shared),
                                         _dp(out), _stream()))
+    return out
+
+
+def grace_combine_share(y: torch.Tensor, perm_pos: torch.Tensor, topk_weight: torch.Tensor, state: torch.Tensor,
+                        y_shared: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """grace_combine of the rank share that grace_expert_ffn_up_share / _down_share with `state` have just left in y:
+    rows outside the rank's range are zero and are not read; see grace_moe.h."""
+    T, k = topk_weight.shape
+    d = y.shape[1]
+    if state.dtype != torch.int32 or state.numel() < SHARE_STATE_INTS:
+        raise ValueError(f"state must hold {SHARE_STATE_INTS} int32")
+    if out is None:
+        out = torch.empty((T, d), dtype=y.dtype, device=y.device)
+    _check(load_library().grace_combine_share(_dp(y), _dp(perm_pos), _dp(topk_weight), T, k, d, _dtype_code(y), _dp(y_shared),
+                                              _dp(state), _dp(out), _stream()))
     return out
 
 

@@ -1,8 +1,11 @@
 // grace_combine: weighted gather of the k expert outputs of every token back to
 // token order (the aggregation step after the expert computation, Section 1),
 // fp32 accumulation in ascending j, one rounding.
+#include <algorithm>
+
 #include "bf16.h"
 #include "common.h"
+#include "gemm_common.h"
 
 namespace grace {
 
@@ -61,6 +64,90 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ 
     }
 }
 
+// A rank share: rows of y outside [state[4], state[5]) are zero (grace_expert_ffn_up_share / _down_share keep them so)
+// and are not read.  A zero row adds w * 0, which is zero or, where the gate weight is not finite, NaN: the sum starts with
+// that.  Every wavefront has its tokens' k positions in its lanes, so a ballot gives the choices to load, taken in ascending
+// order, BATCH at a time; a batch's surplus loads have a descriptor without records and read nothing.  A workgroup takes TOK
+// tokens, whose positions and shared rows it loads at once: bound by HBM (shared rows in, result out) at 6.5 TB/s.
+// d = 2048, bf16, all rows read -> those of the rank: 32768 tokens, k = 6, 1/22 of the rows, shared experts 180 -> 47.5 us;
+// 7001, k = 8, an eighth 45.4 -> 10.8 us; 3001, k = 6, a seventh, shared experts 18.4 -> 6.9 us; d = 4096, 8192 tokens, k = 2, an
+// eighth 32.5 -> 17.7 us.
+template <bool BF16, int TOK, int BATCH>
+__global__ __launch_bounds__(256) void combine_share_kernel(const char *__restrict__ y, const int32_t *__restrict__ perm_pos,
+                                                            const float *__restrict__ topk_weight, int T, int k, int row_vec,
+                                                            int64_t n_rows, const uint4 *__restrict__ y_shared,
+                                                            const int32_t *__restrict__ state, uint4 *__restrict__ out) {
+    constexpr int NV = BF16 ? 8 : 4;
+    const int lane = (int)threadIdx.x & 63, t0 = (int)blockIdx.x * TOK, n_tok = min(TOK, T - t0);
+    const int64_t lo = max(0, state[4]), hi = min(n_rows, (int64_t)state[5]), a0 = (int64_t)t0 * k;
+    const int64_t row_bytes = (int64_t)row_vec * 16;
+    for (int c = (int)threadIdx.x; c - lane < row_vec; c += (int)blockDim.x) {
+        const int cc = min(c, row_vec - 1);   // whole wavefronts stay for the ballots
+        uint4 vs[TOK];
+        float acc[TOK][NV];
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) {
+            vs[i] = y_shared ? y_shared[(int64_t)(t0 + min(i, n_tok - 1)) * row_vec + cc] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int e = 0; e < NV; ++e) acc[i][e] = 0.0f;
+        }
+        for (int j0 = 0; j0 < n_tok * k; j0 += 64) {   // one round when TOK > 1
+            const bool in = j0 + lane < n_tok * k;
+            const int32_t p_lane = in ? perm_pos[a0 + j0 + lane] : -1;
+            const float w_lane = in ? topk_weight[a0 + j0 + lane] : 0.0f;
+            const uint64_t here = __ballot(p_lane >= lo && p_lane < hi);
+            const uint64_t nan = __ballot(p_lane >= 0 && p_lane < n_rows && !(p_lane >= lo && p_lane < hi) && !(w_lane * 0.0f == 0.0f));
+#pragma unroll
+            for (int i = 0; i < TOK; ++i) {
+                const uint64_t mine = TOK == 1 ? ~0ull : ((1ull << k) - 1ull) << (i * k);
+                uint64_t todo = here & mine;
+                if (nan & mine) {
+#pragma unroll
+                    for (int e = 0; e < NV; ++e) acc[i][e] = __builtin_nanf("");
+                }
+                while (todo) {
+                    u32x4_t v[BATCH];
+                    float w[BATCH];
+                    bool more[BATCH];   // uniform
+#pragma unroll
+                    for (int b = 0; b < BATCH; ++b) {
+                        const int src = todo ? __builtin_ctzll(todo) : 0;
+                        more[b] = todo != 0;
+                        todo &= todo - 1;
+                        const int32_t p = __builtin_amdgcn_readlane(p_lane, src);
+                        w[b] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_lane), src));
+                        const auto row = __builtin_amdgcn_make_buffer_rsrc((void *)(y + (more[b] ? p : 0) * row_bytes), 0,
+                                                                          more[b] ? (int)row_bytes : 0, 0x00020000);
+                        v[b] = __builtin_amdgcn_raw_buffer_load_b128(row, cc * 16, 0, 2 /* nt */);
+                    }
+#pragma unroll
+                    for (int b = 0; b < BATCH; ++b) {
+                        if (!more[b]) break;
+                        const uint4 q = make_uint4(v[b][0], v[b][1], v[b][2], v[b][3]);
+                        float f[NV];
+                        if constexpr (BF16) unpack_bf16x8(q, f); else unpack_f32x4(q, f);
+#pragma unroll
+                        for (int e = 0; e < NV; ++e) acc[i][e] = fmaf(w[b], f[e], acc[i][e]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) {
+            if (i >= n_tok || c >= row_vec) break;
+            if (y_shared) {
+                float f[NV];
+                if constexpr (BF16) unpack_bf16x8(vs[i], f); else unpack_f32x4(vs[i], f);
+#pragma unroll
+                for (int e = 0; e < NV; ++e) acc[i][e] += f[e];
+            }
+            uint4 o;
+            if constexpr (BF16) o = pack_bf16x8(acc[i]); else o = pack_f32x4(acc[i]);
+            out[(int64_t)(t0 + i) * row_vec + c] = o;
+        }
+    }
+}
+
 }  // namespace grace
 
 using namespace grace;
@@ -69,20 +156,30 @@ using namespace grace;
 // enough (3001, 7001, 32768 tokens, k = 6, 8, 6: 18.2 to 19.4, 46.8, 177 us with 1 ahead, 18.2, 45.5, 178 us with 2,
 // 19.2, 45.2, 177 us with 4; k = 2, 8192 tokens 31.4 us with 1, 32.3 us with 2).
 constexpr int COMBINE_FEW = 1024;
+// Tokens up to which a rank share is combined like any other y: 64 tokens, k = 8 on a rank with a fifth of the rows 3.8
+// against 4.6 us, 256 fp32 tokens of 128 2.6 against 2.8 us; 512 tokens 5.4 against 4.8 us.
+constexpr int COMBINE_SHARE_ALL = 256;
+
+static int check_combine_args(const char *who, const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T,
+                              int32_t k, int32_t d, grace_dtype dt, const void *y_shared, const void *out) {
+    if (T < 0 || k < 1 || d < 1) return fail(GRACE_EINVAL, "%s: T=%d, k=%d, d=%d invalid", who, T, k, d);
+    if (dt != GRACE_F32 && dt != GRACE_BF16) return fail(GRACE_EINVAL, "%s: unknown dtype %d", who, (int)dt);
+    const size_t el = dt == GRACE_F32 ? 4 : 2;
+    if (((size_t)d * el) % 16 != 0) return fail(GRACE_ESHAPE, "%s: row of %zu bytes is not a multiple of 16", who, (size_t)d * el);
+    if ((int64_t)T * k > INT32_MAX) return fail(GRACE_ESHAPE, "%s: T*k exceeds 2^31-1", who);
+    if (T == 0) return GRACE_OK;
+    if (!y || !perm_pos || !topk_weight || !out) return fail(GRACE_EINVAL, "%s: null device pointer", who);
+    if ((((uintptr_t)y) | ((uintptr_t)out) | ((uintptr_t)y_shared)) & 15)
+        return fail(GRACE_EINVAL, "%s: y, y_shared and out must be 16-byte aligned", who);
+    return GRACE_OK;
+}
 
 extern "C" int grace_combine(const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T, int32_t k,
                              int32_t d, grace_dtype dt, const void *y_shared, void *out, void *stream) {
-    if (T < 0 || k < 1 || d < 1) return fail(GRACE_EINVAL, "combine: T=%d, k=%d, d=%d invalid", T, k, d);
-    if (dt != GRACE_F32 && dt != GRACE_BF16) return fail(GRACE_EINVAL, "combine: unknown dtype %d", (int)dt);
-    const size_t el = dt == GRACE_F32 ? 4 : 2;
-    if (((size_t)d * el) % 16 != 0) return fail(GRACE_ESHAPE, "combine: row of %zu bytes is not a multiple of 16", (size_t)d * el);
-    if ((int64_t)T * k > INT32_MAX) return fail(GRACE_ESHAPE, "combine: T*k exceeds 2^31-1");
-    if (T == 0) return GRACE_OK;
-    if (!y || !perm_pos || !topk_weight || !out) return fail(GRACE_EINVAL, "combine: null device pointer");
-    if ((((uintptr_t)y) | ((uintptr_t)out) | ((uintptr_t)y_shared)) & 15)
-        return fail(GRACE_EINVAL, "combine: y, y_shared and out must be 16-byte aligned");
+    const int rc = check_combine_args("combine", y, perm_pos, topk_weight, T, k, d, dt, y_shared, out);
+    if (rc != GRACE_OK || T == 0) return rc;
     hipStream_t st = (hipStream_t)stream;
-    const int row_vec = (int)((size_t)d * el / 16);
+    const int row_vec = (int)((int64_t)d * (dt == GRACE_F32 ? 4 : 2) / 16);
     const int64_t n = (int64_t)T * k;
     auto launch = [&](auto kernel) {
         kernel<<<T, 256, 0, st>>>((const uint4 *)y, perm_pos, topk_weight, k, row_vec, n, (const uint4 *)y_shared, (uint4 *)out);
@@ -91,5 +188,29 @@ extern "C" int grace_combine(const void *y, const int32_t *perm_pos, const float
     if (dt == GRACE_BF16) launch(ahead == 1 ? combine_kernel<true, 1> : ahead == 2 ? combine_kernel<true, 2> : combine_kernel<true, 4>);
     else launch(ahead == 1 ? combine_kernel<false, 1> : ahead == 2 ? combine_kernel<false, 2> : combine_kernel<false, 4>);
     GRACE_LAUNCH_CHECK("combine_kernel");
+    return GRACE_OK;
+}
+
+extern "C" int grace_combine_share(const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T, int32_t k,
+                                   int32_t d, grace_dtype dt, const void *y_shared, const int32_t *state, void *out,
+                                   void *stream) {
+    const int rc = check_combine_args("combine_share", y, perm_pos, topk_weight, T, k, d, dt, y_shared, out);
+    if (rc != GRACE_OK || T == 0) return rc;
+    if (!state) return fail(GRACE_EINVAL, "combine_share: state is null");
+    const int64_t row_bytes = (int64_t)d * (dt == GRACE_F32 ? 4 : 2), n = (int64_t)T * k;
+    // few tokens: the rows are read sooner than their positions are sorted out (a row past what a descriptor spans: so too)
+    if (T <= COMBINE_SHARE_ALL || row_bytes > INT32_MAX)
+        return grace_combine(y, perm_pos, topk_weight, T, k, d, dt, y_shared, out, stream);
+    const int row_vec = (int)(row_bytes / 16);
+    auto launch = [&](auto kernel, int tok) {
+        kernel<<<(T + tok - 1) / tok, 256, 0, (hipStream_t)stream>>>((const char *)y, perm_pos, topk_weight, T, k, row_vec, n,
+                                                                        (const uint4 *)y_shared, state, (uint4 *)out);
+    };
+    if (T > COMBINE_FEW && k <= 16) {
+        if (dt == GRACE_BF16) launch(combine_share_kernel<true, 4, 2>, 4); else launch(combine_share_kernel<false, 4, 2>, 4);
+    } else {
+        if (dt == GRACE_BF16) launch(combine_share_kernel<true, 1, 4>, 1); else launch(combine_share_kernel<false, 1, 4>, 1);
+    }
+    GRACE_LAUNCH_CHECK("combine_share_kernel");
     return GRACE_OK;
 }

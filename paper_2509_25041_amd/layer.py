@@ -22,7 +22,8 @@ class GraceMoELayer:
     moves with the routing, so each step clears what an earlier step wrote outside
     the current range (grace_expert_ffn_up_share / _down_share do it inside the
     two projections' launches: no extra launch, no memset, the step stays capturable
-    in a HIP graph).
+    in a HIP graph).  The combine relies on it and does not read them
+    (grace_combine_share).
 
     All buffers are allocated once; a step is four to six C calls whose argument lists
     are marshalled once per (logits, x, rr_in, rr_out, stream) and reused, so the
@@ -124,8 +125,8 @@ class GraceMoELayer:
                 calls.append(("shared_up", lib.grace_shared_ffn_up, (p(x), T, d, f, self.n_shared, dt, p(sg), p(su), ws, st)))
             calls.append(("shared_down", lib.grace_shared_ffn_down, (T, d, f, self.n_shared, dt, p(sd), p(self.y_shared),
                                                                      p(self.ws_shared) if fuse else ws, st)))
-        calls.append(("combine", lib.grace_combine, (p(self.y), p(pos), p(tw), T, k, d, dt, p(self.y_shared),
-                                                     p(self.out), st)))
+        calls.append(("combine", lib.grace_combine_share, (p(self.y), p(pos), p(tw), T, k, d, dt, p(self.y_shared),
+                                                           p(self.y_state), p(self.out), st)))
         return calls
 
     def forward(self, logits: torch.Tensor, x: torch.Tensor, rr_in: Optional[torch.Tensor] = None,

@@ -88,6 +88,8 @@ def test_null_and_range_checks_without_device():
     assert lib.grace_combine(None, None, None, 1, 1, 3, 1, None, None, None) == -2               # 6-byte rows
     assert lib.grace_combine(None, None, None, 1, 1, 8, 1, None, None, None) == -1               # null pointers
     assert lib.grace_combine(None, None, None, 0, 1, 8, 1, None, None, None) == 0                # nothing to do
+    assert lib.grace_combine_share(None, None, None, 1, 1, 3, 1, None, None, None, None) == -2
+    assert lib.grace_combine_share(1 << 20, 1 << 20, 1 << 20, 1, 1, 8, 1, None, None, 1 << 20, None) == -1     # no state
     assert lib.grace_mfma_sustained(1, 1, None, None) == -1
     assert lib.grace_table_set_fold_limits(None, -1, -1) == -1
     assert lib.grace_permute_rows(None, None, 1, 1, 8, 1, None, None) == -1

@@ -154,6 +154,33 @@ def test_combine_with_absent_rows(T, k, dtype):
     assert rel_err(got, want) <= (1e-6 if dtype == "f32" else 2.0 ** -8)   # one rounding of an fp32 sum
 
 
+@pytest.mark.parametrize("T,k,d,dtype,lo,hi,shared", [
+    (1, 1, 24, "bf16", 0, 1, False), (1, 8, 2056, "bf16", 2, 3, True), (5, 70, 24, "f32", 60, 300, False), (300, 70, 24, "f32", 6000, 15000, False),
+    (256, 4, 24, "bf16", 3, 700, True), (257, 4, 24, "bf16", 3, 700, True), (1024, 6, 24, "f32", 0, 0, True), (1025, 9, 24, "bf16", 1000, 4000, True), (1027, 16, 2056, "bf16", 0, 16432, False),
+    (1025, 17, 24, "f32", 9000, 17425, False), (2051, 2, 1028, "f32", 4101, 4102, True)])
+def test_combine_share_is_combine_of_zero_rows(T, k, d, dtype, lo, hi, shared):
+    """Rows outside the share are zero and not read: the same bits as grace_combine, which reads them, with positions
+    outside the buffer and gate weights that are not finite (0 * inf) among the absent rows."""
+    rng = np.random.default_rng(T + k)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    y = torch.zeros((T * k, d), dtype=tdt, device="cuda")
+    y[lo:hi] = torch.from_numpy(rng.standard_normal((hi - lo, d)).astype(np.float32)).cuda().to(tdt)
+    pos = rng.permutation(T * k).astype(np.int32)
+    pos[rng.random(T * k) < 0.1] = -1
+    pos[rng.random(T * k) < 0.1] = T * k
+    w = rng.random((T, k)).astype(np.float32)
+    w[rng.random((T, k)) < 0.02] = np.inf
+    ys = torch.from_numpy(rng.standard_normal((T, d)).astype(np.float32)).cuda().to(tdt) if shared else None
+    state = torch.tensor([5, 9, 0, 0, lo, hi, 0, 0], dtype=torch.int32, device="cuda")
+    pos, w = torch.from_numpy(pos).cuda(), torch.from_numpy(w).cuda()
+    want = grace.grace_combine(y, pos, w, ys)
+    if T > 256:
+        y[:lo] = 3.0   # not read
+        y[hi:] = 3.0
+    got = grace.grace_combine_share(y, pos, w, state, ys)
+    torch.testing.assert_close(got, want, rtol=0, atol=0, equal_nan=True)
+
+
 @pytest.mark.parametrize("nodes,gpus,T,k", [(2, 2, 1, 2), (3, 2, 255, 4), (1, 4, 1025, 3), (4, 2, 513, 2)])
 def test_send_list_block_edges(nodes, gpus, T, k):
     """Send lists whose assignments end just below, at and past a block of the counting and the expansion kernels."""
