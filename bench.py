@@ -166,8 +166,8 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
     peak_mm = PEAK_F32_TFLOPS if cfg.dtype == "f32" else PEAK_BF16_TFLOPS
     bytes_route = T * (4 * cfg.E + 12 * k)
     bytes_permute = T * d * el + T * k * d * el + 12 * T * k
-    # (the layer's combine reads the rank's rows only, the others are zero; up to 256 tokens it reads all)
-    bytes_combine = (m_loc if T > 256 else T * k) * d * el + T * d * el * (2 if sh is not None else 1) + 8 * T * k
+    # (the layer's combine reads the rank's rows only, the others are zero)
+    bytes_combine = m_loc * d * el + T * d * el * (2 if sh is not None else 1) + 8 * T * k
     # with shared experts the dispatch call builds only the index arrays; the row scatter rides on the shared gate+up
     # projection's launch where the large tiles take that, else it is a launch of its own
     fused_scatter = bool(getattr(layer, "fuse_scatter", False)) and sh is not None

@@ -1,8 +1,6 @@
 // grace_combine: weighted gather of the k expert outputs of every token back to
 // token order (the aggregation step after the expert computation, Section 1),
 // fp32 accumulation in ascending j, one rounding.
-#include <algorithm>
-
 #include "bf16.h"
 #include "common.h"
 #include "gemm_common.h"
@@ -66,85 +64,77 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ 
 
 // A rank share: rows of y outside [state[4], state[5]) are zero (grace_expert_ffn_up_share / _down_share keep them so)
 // and are not read.  A zero row adds w * 0, which is zero or, where the gate weight is not finite, NaN: the sum starts with
-// that.  Every wavefront has its tokens' k positions in its lanes, so a ballot gives the choices to load, taken in ascending
-// order, BATCH at a time; a batch's surplus loads have a descriptor without records and read nothing.  A workgroup takes TOK
-// tokens, whose positions and shared rows it loads at once: bound by HBM (shared rows in, result out) at 6.5 TB/s.
-// d = 2048, bf16, all rows read -> those of the rank: 32768 tokens, k = 6, 1/22 of the rows, shared experts 180 -> 47.5 us;
-// 7001, k = 8, an eighth 45.4 -> 10.8 us; 3001, k = 6, a seventh, shared experts 18.4 -> 6.9 us; d = 4096, 8192 tokens, k = 2, an
-// eighth 32.5 -> 17.7 us.
-template <bool BF16, int TOK, int BATCH>
+// that.  Every wavefront has its token's k positions in its lanes, so a ballot gives the choices to load, taken in ascending
+// order, BATCH at a time; a batch's surplus loads have a descriptor without records, read nothing and give zeros, so that
+// no branch makes the loads wait for one another.  Bound by HBM (shared rows in, result out) for large batches, by the chain
+// position -> row for small ones.  Layer steps in d = 2048, bf16, all rows read -> those of the rank: 32768 tokens, k = 6, 1/22 of the
+// rows, shared experts 178 -> 47 us; 7001, k = 8, an eighth 45.4 -> 13.0 us; 3001, k = 6, a seventh, shared experts 18.8 ->
+// 6.6 us; d = 4096, 8192 tokens, k = 2, an eighth 31.9 -> 20.4 us.  On a rank that holds every row it takes 0.98 to 1.07 of
+// combine_kernel's time (64 to 32768 tokens).  Batches of 1, 2 and 4: 2048 tokens, k = 8, a quarter of the rows 8.8, 7.3, 7.1 us; k =
+// 2, 4096 tokens of 4096 13.6, 12.6, 13.8 us.  Two or four tokens per workgroup gain up to 2.5 us on prefill with few rows and lose
+// up to a half for fewer tokens or many rows.
+template <bool BF16, int BATCH>
 __global__ __launch_bounds__(256) void combine_share_kernel(const char *__restrict__ y, const int32_t *__restrict__ perm_pos,
-                                                            const float *__restrict__ topk_weight, int T, int k, int row_vec,
+                                                            const float *__restrict__ topk_weight, int k, int row_vec,
                                                             int64_t n_rows, const uint4 *__restrict__ y_shared,
                                                             const int32_t *__restrict__ state, uint4 *__restrict__ out) {
     constexpr int NV = BF16 ? 8 : 4;
-    const int lane = (int)threadIdx.x & 63, t0 = (int)blockIdx.x * TOK, n_tok = min(TOK, T - t0);
-    const int64_t lo = max(0, state[4]), hi = min(n_rows, (int64_t)state[5]), a0 = (int64_t)t0 * k;
-    const int64_t row_bytes = (int64_t)row_vec * 16;
-    for (int c = (int)threadIdx.x; c - lane < row_vec; c += (int)blockDim.x) {
+    const int lane = (int)threadIdx.x & 63;
+    const int64_t t = blockIdx.x, a0 = t * k, row_bytes = (int64_t)row_vec * 16;
+    const int64_t lo = max(0, state[4]), hi = min(n_rows, (int64_t)state[5]);
+    for (int c = (int)threadIdx.x; c - lane < row_vec; c += 256) {
         const int cc = min(c, row_vec - 1);   // whole wavefronts stay for the ballots
-        uint4 vs[TOK];
-        float acc[TOK][NV];
+        int32_t p_lane = perm_pos[a0 + min(lane, k - 1)];
+        float w_lane = topk_weight[a0 + min(lane, k - 1)];
+        uint4 vs = make_uint4(0u, 0u, 0u, 0u);
+        if (y_shared) vs = y_shared[t * row_vec + cc];
+        float acc[NV];
 #pragma unroll
-        for (int i = 0; i < TOK; ++i) {
-            vs[i] = y_shared ? y_shared[(int64_t)(t0 + min(i, n_tok - 1)) * row_vec + cc] : make_uint4(0u, 0u, 0u, 0u);
+        for (int e = 0; e < NV; ++e) acc[e] = 0.0f;
+        for (int j0 = 0;;) {   // 64 choices at a time
+            const bool row = j0 + lane < k && p_lane >= 0 && p_lane < n_rows, here = row && p_lane >= lo && p_lane < hi;
+            uint64_t todo = __ballot(here);
+            if (__ballot(row && !here && !(w_lane * 0.0f == 0.0f))) {
 #pragma unroll
-            for (int e = 0; e < NV; ++e) acc[i][e] = 0.0f;
-        }
-        for (int j0 = 0; j0 < n_tok * k; j0 += 64) {   // one round when TOK > 1
-            const bool in = j0 + lane < n_tok * k;
-            const int32_t p_lane = in ? perm_pos[a0 + j0 + lane] : -1;
-            const float w_lane = in ? topk_weight[a0 + j0 + lane] : 0.0f;
-            const uint64_t here = __ballot(p_lane >= lo && p_lane < hi);
-            const uint64_t nan = __ballot(p_lane >= 0 && p_lane < n_rows && !(p_lane >= lo && p_lane < hi) && !(w_lane * 0.0f == 0.0f));
+                for (int e = 0; e < NV; ++e) acc[e] = __builtin_nanf("");
+            }
+            while (todo) {
+                u32x4_t v[BATCH];
+                float w[BATCH];
 #pragma unroll
-            for (int i = 0; i < TOK; ++i) {
-                const uint64_t mine = TOK == 1 ? ~0ull : ((1ull << k) - 1ull) << (i * k);
-                uint64_t todo = here & mine;
-                if (nan & mine) {
-#pragma unroll
-                    for (int e = 0; e < NV; ++e) acc[i][e] = __builtin_nanf("");
+                for (int b = 0; b < BATCH; ++b) {
+                    const int src = todo ? __builtin_ctzll(todo) : 0;
+                    const int32_t p = __builtin_amdgcn_readlane(p_lane, src);
+                    w[b] = todo ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_lane), src)) : 0.0f;
+                    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(y + (int64_t)p * row_bytes), 0,
+                                                                       todo ? (int)row_bytes : 0, 0x00020000);
+                    v[b] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, cc * 16, 0, 2 /* nt */);
+                    todo &= todo - 1;
                 }
-                while (todo) {
-                    u32x4_t v[BATCH];
-                    float w[BATCH];
-                    bool more[BATCH];   // uniform
 #pragma unroll
-                    for (int b = 0; b < BATCH; ++b) {
-                        const int src = todo ? __builtin_ctzll(todo) : 0;
-                        more[b] = todo != 0;
-                        todo &= todo - 1;
-                        const int32_t p = __builtin_amdgcn_readlane(p_lane, src);
-                        w[b] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_lane), src));
-                        const auto row = __builtin_amdgcn_make_buffer_rsrc((void *)(y + (more[b] ? p : 0) * row_bytes), 0,
-                                                                          more[b] ? (int)row_bytes : 0, 0x00020000);
-                        v[b] = __builtin_amdgcn_raw_buffer_load_b128(row, cc * 16, 0, 2 /* nt */);
-                    }
+                for (int b = 0; b < BATCH; ++b) {
+                    const uint4 q = make_uint4(v[b][0], v[b][1], v[b][2], v[b][3]);
+                    float f[NV];
+                    if constexpr (BF16) unpack_bf16x8(q, f); else unpack_f32x4(q, f);
 #pragma unroll
-                    for (int b = 0; b < BATCH; ++b) {
-                        if (!more[b]) break;
-                        const uint4 q = make_uint4(v[b][0], v[b][1], v[b][2], v[b][3]);
-                        float f[NV];
-                        if constexpr (BF16) unpack_bf16x8(q, f); else unpack_f32x4(q, f);
-#pragma unroll
-                        for (int e = 0; e < NV; ++e) acc[i][e] = fmaf(w[b], f[e], acc[i][e]);
-                    }
+                    for (int e = 0; e < NV; ++e) acc[e] = fmaf(w[b], f[e], acc[e]);
                 }
             }
+            j0 += 64;
+            if (j0 >= k) break;
+            p_lane = perm_pos[a0 + min(j0 + lane, k - 1)];
+            w_lane = topk_weight[a0 + min(j0 + lane, k - 1)];
         }
+        if (c >= row_vec) break;
+        if (y_shared) {
+            float f[NV];
+            if constexpr (BF16) unpack_bf16x8(vs, f); else unpack_f32x4(vs, f);
 #pragma unroll
-        for (int i = 0; i < TOK; ++i) {
-            if (i >= n_tok || c >= row_vec) break;
-            if (y_shared) {
-                float f[NV];
-                if constexpr (BF16) unpack_bf16x8(vs[i], f); else unpack_f32x4(vs[i], f);
-#pragma unroll
-                for (int e = 0; e < NV; ++e) acc[i][e] += f[e];
-            }
-            uint4 o;
-            if constexpr (BF16) o = pack_bf16x8(acc[i]); else o = pack_f32x4(acc[i]);
-            out[(int64_t)(t0 + i) * row_vec + c] = o;
+            for (int e = 0; e < NV; ++e) acc[e] += f[e];
         }
+        uint4 o;
+        if constexpr (BF16) o = pack_bf16x8(acc); else o = pack_f32x4(acc);
+        out[t * row_vec + c] = o;
     }
 }
 
@@ -156,10 +146,6 @@ using namespace grace;
 // enough (3001, 7001, 32768 tokens, k = 6, 8, 6: 18.2 to 19.4, 46.8, 177 us with 1 ahead, 18.2, 45.5, 178 us with 2,
 // 19.2, 45.2, 177 us with 4; k = 2, 8192 tokens 31.4 us with 1, 32.3 us with 2).
 constexpr int COMBINE_FEW = 1024;
-// Tokens up to which a rank share is combined like any other y: 64 tokens, k = 8 on a rank with a fifth of the rows 3.8
-// against 4.6 us, 256 fp32 tokens of 128 2.6 against 2.8 us; 512 tokens 5.4 against 4.8 us.
-constexpr int COMBINE_SHARE_ALL = 256;
-
 static int check_combine_args(const char *who, const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T,
                               int32_t k, int32_t d, grace_dtype dt, const void *y_shared, const void *out) {
     if (T < 0 || k < 1 || d < 1) return fail(GRACE_EINVAL, "%s: T=%d, k=%d, d=%d invalid", who, T, k, d);
@@ -198,19 +184,14 @@ extern "C" int grace_combine_share(const void *y, const int32_t *perm_pos, const
     if (rc != GRACE_OK || T == 0) return rc;
     if (!state) return fail(GRACE_EINVAL, "combine_share: state is null");
     const int64_t row_bytes = (int64_t)d * (dt == GRACE_F32 ? 4 : 2), n = (int64_t)T * k;
-    // few tokens: the rows are read sooner than their positions are sorted out (a row past what a descriptor spans: so too)
-    if (T <= COMBINE_SHARE_ALL || row_bytes > INT32_MAX)
+    if (row_bytes > INT32_MAX)   // past what a buffer descriptor spans: all rows are read
         return grace_combine(y, perm_pos, topk_weight, T, k, d, dt, y_shared, out, stream);
-    const int row_vec = (int)(row_bytes / 16);
-    auto launch = [&](auto kernel, int tok) {
-        kernel<<<(T + tok - 1) / tok, 256, 0, (hipStream_t)stream>>>((const char *)y, perm_pos, topk_weight, T, k, row_vec, n,
-                                                                        (const uint4 *)y_shared, state, (uint4 *)out);
+    auto launch = [&](auto kernel) {
+        kernel<<<T, 256, 0, (hipStream_t)stream>>>((const char *)y, perm_pos, topk_weight, k, (int)(row_bytes / 16), n,
+                                                   (const uint4 *)y_shared, state, (uint4 *)out);
     };
-    if (T > COMBINE_FEW && k <= 16) {
-        if (dt == GRACE_BF16) launch(combine_share_kernel<true, 4, 2>, 4); else launch(combine_share_kernel<false, 4, 2>, 4);
-    } else {
-        if (dt == GRACE_BF16) launch(combine_share_kernel<true, 1, 4>, 1); else launch(combine_share_kernel<false, 1, 4>, 1);
-    }
+    if (dt == GRACE_BF16) launch(k < 3 ? combine_share_kernel<true, 2> : combine_share_kernel<true, 4>);
+    else launch(k < 3 ? combine_share_kernel<false, 2> : combine_share_kernel<false, 4>);
     GRACE_LAUNCH_CHECK("combine_share_kernel");
     return GRACE_OK;
 }

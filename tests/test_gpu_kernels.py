@@ -156,7 +156,7 @@ def test_combine_with_absent_rows(T, k, dtype):
 
 @pytest.mark.parametrize("T,k,d,dtype,lo,hi,shared", [
     (1, 1, 24, "bf16", 0, 1, False), (1, 8, 2056, "bf16", 2, 3, True), (5, 70, 24, "f32", 60, 300, False), (300, 70, 24, "f32", 6000, 15000, False),
-    (256, 4, 24, "bf16", 3, 700, True), (257, 4, 24, "bf16", 3, 700, True), (1024, 6, 24, "f32", 0, 0, True), (1025, 9, 24, "bf16", 1000, 4000, True), (1027, 16, 2056, "bf16", 0, 16432, False),
+    (33, 64, 24, "bf16", 3, 700, True), (1024, 6, 24, "f32", 0, 0, True), (1025, 9, 24, "bf16", 1000, 4000, True), (1027, 16, 2056, "bf16", 0, 16432, False),
     (1025, 17, 24, "f32", 9000, 17425, False), (2051, 2, 1028, "f32", 4101, 4102, True)])
 def test_combine_share_is_combine_of_zero_rows(T, k, d, dtype, lo, hi, shared):
     """Rows outside the share are zero and not read: the same bits as grace_combine, which reads them, with positions
@@ -174,9 +174,8 @@ def test_combine_share_is_combine_of_zero_rows(T, k, d, dtype, lo, hi, shared):
     state = torch.tensor([5, 9, 0, 0, lo, hi, 0, 0], dtype=torch.int32, device="cuda")
     pos, w = torch.from_numpy(pos).cuda(), torch.from_numpy(w).cuda()
     want = grace.grace_combine(y, pos, w, ys)
-    if T > 256:
-        y[:lo] = 3.0   # not read
-        y[hi:] = 3.0
+    y[:lo] = 3.0   # not read
+    y[hi:] = 3.0
     got = grace.grace_combine_share(y, pos, w, state, ys)
     torch.testing.assert_close(got, want, rtol=0, atol=0, equal_nan=True)
 
