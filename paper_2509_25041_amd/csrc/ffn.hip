@@ -133,15 +133,15 @@ static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
     return {n_strips * g.S, waves * 64};
 }
 template <bool FUSED_UP>
-static Grid mid_grid(const GemmArgs &g, const Rows &rows) {
+static Grid mid_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
     const int64_t n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
-    return {((rows.m_bound / mid::BM + g.S) * n_strips + 63) / 64 * 64, mid::THREADS};
+    return {mid::grid_blocks((rows.m_bound / mid::BM + g.S) * n_strips, n_cu), mid::THREADS};
 }
 template <bool FUSED_UP>
 static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     if (route == Route::STREAM)
         return dt == GRACE_BF16 ? stream_grid<FUSED_UP, 2>(g, rows, n_cu) : stream_grid<FUSED_UP, 4>(g, rows, n_cu);
-    if (route == Route::MID) return mid_grid<FUSED_UP>(g, rows);
+    if (route == Route::MID) return mid_grid<FUSED_UP>(g, rows, n_cu);
     if (route == Route::PERSIST) return {pers::grid_blocks(n_cu), pers::THREADS};
     if (route == Route::GENERIC) {
         constexpr int BN = FUSED_UP ? 64 : 128;
@@ -245,16 +245,16 @@ static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, hi
 }
 
 template <bool FUSED_UP>
-static void launch_mid(const GemmArgs &g, const Grid &l, hipStream_t st) {
+static void launch_mid(const GemmArgs &g, const Grid &l, int n_cu, hipStream_t st) {
     const int n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
     if constexpr (!FUSED_UP) {   // K segments: the shared experts' down projection alone
         if (g.kseg_len < g.K) {
-            mid::gemm_bf16_mid_kernel<false, true, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
+            mid::gemm_bf16_mid_kernel<false, true, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
             return;
         }
     }
-    if (g.S <= 64) mid::gemm_bf16_mid_kernel<FUSED_UP, false, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
-    else mid::gemm_bf16_mid_kernel<FUSED_UP, false, 4><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips);
+    if (g.S <= 64) mid::gemm_bf16_mid_kernel<FUSED_UP, false, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
+    else mid::gemm_bf16_mid_kernel<FUSED_UP, false, 4><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
 }
 
 template <bool FUSED_UP, pers::Who WHO>
@@ -269,7 +269,7 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipS
         if (dt == GRACE_BF16) launch_stream<FUSED_UP, 2>(g, rows, l, st);
         else launch_stream<FUSED_UP, 4>(g, rows, l, st);
     } else if (route == Route::MID) {
-        launch_mid<FUSED_UP>(g, l, st);
+        launch_mid<FUSED_UP>(g, l, n_cu, st);
     } else if (route == Route::PERSIST) {
         // persistent large-tile kernel: one workgroup per compute unit, 160 KB of dynamic LDS
         using SH = pers::Shape<FUSED_UP>;

@@ -17,6 +17,13 @@
 // an offset outside the buffer descriptor's range: they read nothing and give zeros, so every step is the same
 // code whatever K is.
 //
+// Groups of four neighbouring strips walk K from different steps on, round and round: with all tiles at the same K, the
+// rows' lines of that moment lie a row apart, and where a row is a multiple of 2 or 4 KB they fall on a few of the memory's
+// channels (16 segments, d = 2048, f = 1024, cold weights, gate+up: 19 rows each 36.5 -> 28.1 us, 96 each 37.0 -> 29.5 us, 1024 rows with
+// Zipf-shaped shares 43.5 -> 39.9 us; d = 4096, f = 3584, 8 segments of 19 rows 91.6 -> 82.0 us; rows of 2 KB and less are even).
+// Single strips at different steps lose what they share of the activation rows in L2 (96 rows each 31 to 38 us).  A strip's
+// step depends on its weights alone, so a row's result does not depend on the batch around it.
+//
 // Pieces of a segment have one size (a multiple of 16, at most 96).  Workgroups are numbered by segment, strip
 // of weight rows, piece, and dealt to the XCDs in 64 runs of equal length (workgroups go to the XCDs round-robin):
 // pieces that read the same weights run next to each other on one L2, and every XCD gets hot and cold segments
@@ -30,6 +37,9 @@
 // in turn: 70 tokens, 11 of 16 segments in use 34.0 / 16.4 -> 21.5 / 13.3, 230 tokens, 13 of 16 44.3 / 19.3 -> 27.7 / 17.7.
 // K that is no multiple of 64 took a kernel without prefetch before: 3001 rows, N = 2048, K = 2 x 352 58 -> 20 us.
 #pragma once
+#include <algorithm>
+#include <type_traits>
+
 #include "bf16.h"
 #include "gemm_common.h"
 
@@ -46,10 +56,12 @@ struct Shape {
 
 __device__ __forceinline__ int chunk_at(int row, int c) { return row * ROW_BYTES + ((c ^ ((row >> 1) & 7)) * 16); }
 
-// MF: activation fragments of 16 rows.  SEG_K: the weights' K axis is cut in segments (shared experts' down
-// projection), of any length.
-template <bool FUSED_UP, bool SEG_K, int MF>
-__device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, char *smem) {
+// MF: activation fragments of 16 rows.  NJ: weight fragments per wavefront, 2 or, for half a tile's weight rows, 1 (gate+up:
+// then 8 rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K
+// axis is cut in segments (shared experts' down projection), of any length.
+template <bool FUSED_UP, bool SEG_K, int MF, int NJ>
+__device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int first_step,
+                                          char *smem) {
     constexpr int AHEAD = MF == 2 ? 8 : MF == 4 ? 6 : 4;   // steps in flight: what 256 registers hold (even)
     constexpr int AL = MF / 2;   // activation loads per thread and step: 32 rows each
     const int tid = (int)threadIdx.x, lane = tid & 63;
@@ -66,35 +78,37 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
         const int row = i * 32 + (tid >> 3);
         a_off[i] = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 2) + (uint32_t)a_chunk * 16u : NO_DATA;
     }
-    const int wn = n0 + wave * (FUSED_UP ? 16 : 32);   // first output column of the wavefront
+    const int wn = n0 + wave * (FUSED_UP ? 8 : 16) * NJ;   // first output column of the wavefront
     const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 2;
     const auto b0_rsrc = rsrc_of((const char *)g.B0 + b_first);
     const auto b1_rsrc = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
-    // lane: row lane / 8 of every 8, 16-byte chunk lane % 8 (FUSED_UP: rows 0 .. 15 gate, 16 .. 31 up)
+    // lane: row lane / 8 of every 8, 16-byte chunk lane % 8 (FUSED_UP: the first half of the rows gate, the second up)
     const int b_row = lane >> 3, b_chunk = lane & 7;
-    uint32_t b_off[4];
+    uint32_t b_off[2 * NJ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int n = FUSED_UP ? (i & 1) * 8 + b_row : i * 8 + b_row;
+    for (int i = 0; i < 2 * NJ; ++i) {
+        const int n = FUSED_UP ? (i % NJ) * 8 + b_row : i * 8 + b_row;
         b_off[i] = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 2) + (uint32_t)b_chunk * 16u : NO_DATA;
     }
     char *sb = smem + 2 * A_BYTES + wave * 2 * B_WAVE_BYTES;
-    int bk = 0;   // K of the next weight loads (scalar)
+    const int k_end = nk * BK;
+    int bk = first_step * BK, b_left = nk;   // K of the next weight loads and how many there are (scalar)
     KSegWalk walk{b_chunk * 8};
 
-    u32x4_t ra[AHEAD][AL], rb[AHEAD][4];
-    f32x4_t acc[MF][2];
+    u32x4_t ra[AHEAD][AL], rb[AHEAD][2 * NJ];
+    f32x4_t acc[MF][NJ];
 #pragma unroll
     for (int i = 0; i < MF; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-    int ak = 0;   // K of the next activation loads (scalar)
+    int ak = first_step * BK, a_left = nk;   // the same for the activation loads
     auto load_a = [&](int set) {
-        const uint32_t none = ak + a_chunk * 8 < g.K ? 0u : NO_DATA;
+        const uint32_t none = a_left > 0 && ak + a_chunk * 8 < g.K ? 0u : NO_DATA;
 #pragma unroll
         for (int i = 0; i < AL; ++i) ra[set][i] = load16(a_rsrc, a_off[i] | none, (uint32_t)ak * 2u);
-        ak += BK;
+        --a_left;
+        ak = ak + BK == k_end ? 0 : ak + BK;
     };
     auto store_a = [&](int set, int buf) {
 #pragma unroll
@@ -103,27 +117,28 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
     };
     auto load_b = [&](int set) {
         const int k = bk + b_chunk * 8;
-        const uint32_t add = SEG_K ? walk.next(k, g.K, g.kseg_len, g.kseg_stride, BK) : k < g.K ? 0u : NO_DATA;
+        const uint32_t add = SEG_K ? walk.next(k, g.K, g.kseg_len, g.kseg_stride, BK) : b_left > 0 && k < g.K ? 0u : NO_DATA;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            rb[set][i] = load16(FUSED_UP && i >= 2 ? b1_rsrc : b0_rsrc, SEG_K ? offset_with(b_off[i], add) : b_off[i] | add, (uint32_t)bk * 2u);
-        bk += BK;
+        for (int i = 0; i < 2 * NJ; ++i)
+            rb[set][i] = load16(FUSED_UP && i >= NJ ? b1_rsrc : b0_rsrc, SEG_K ? offset_with(b_off[i], add) : b_off[i] | add, (uint32_t)bk * 2u);
+        --b_left;
+        bk = SEG_K || bk + BK != k_end ? bk + BK : 0;
     };
     auto store_b = [&](int set, int buf) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *(u32x4_t *)(sb + buf * B_WAVE_BYTES + chunk_at(i * 8 + b_row, b_chunk)) = rb[set][i];
+        for (int i = 0; i < 2 * NJ; ++i) *(u32x4_t *)(sb + buf * B_WAVE_BYTES + chunk_at(i * 8 + b_row, b_chunk)) = rb[set][i];
     };
     // Two groups of 32 K.  The second group's fragments are read while the first is multiplied, each
     // activation fragment into the registers that its predecessor has just freed.
-    bf16x8_t fa[MF], fb[2][2];
+    bf16x8_t fa[MF], fb[2][NJ];
     auto read_b = [&](int gk, int buf) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) fb[gk][j] = *(const bf16x8_t *)(sb + buf * B_WAVE_BYTES + chunk_at(j * 16 + r, gk * 4 + q));
+        for (int j = 0; j < NJ; ++j) fb[gk][j] = *(const bf16x8_t *)(sb + buf * B_WAVE_BYTES + chunk_at(j * 16 + r, gk * 4 + q));
     };
     auto read_a = [&](int i, int gk, int buf) { fa[i] = *(const bf16x8_t *)(smem + buf * A_BYTES + chunk_at(i * 16 + r, gk * 4 + q)); };
     auto mma = [&](int i, int gk) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[gk][j], fa[i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[gk][j], fa[i], acc[i][j], 0, 0, 0);
     };
     auto compute = [&](int buf) {
         read_b(0, buf);
@@ -137,13 +152,13 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
         }
 #pragma unroll
         for (int i = 0; i < MF; ++i) mma(i, 1);
-        __builtin_amdgcn_sched_group_barrier(0x100, MF + 4, 0);   // LDS reads
+        __builtin_amdgcn_sched_group_barrier(0x100, MF + 2 * NJ, 0);   // LDS reads
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);    // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x008, NJ, 0);    // MFMA
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * MF, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, NJ * MF, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
 
@@ -183,26 +198,50 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
 #pragma unroll
     for (int i = 0; i < MF; ++i) {
         const int row = m0 + i * 16 + r;
+        float up[4];
+        if constexpr (FUSED_UP) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) up[v] = NJ == 2 ? acc[i][NJ - 1][v] : __shfl_xor(acc[i][0][v], 32, 64);
+        }
         if (row >= m_end) continue;
 #pragma unroll
-        for (int j = 0; j < (FUSED_UP ? 1 : 2); ++j) {
+        for (int j = 0; j < (FUSED_UP ? 1 : NJ); ++j) {
             const int col = wn + j * 16 + 4 * q;
-            if (col >= g.N) continue;   // N is a multiple of 8
+            if (col >= g.N || (FUSED_UP && NJ == 1 && q >= 2)) continue;   // N is a multiple of 8
             float h[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 h[v] = acc[i][j][v];
-                if (FUSED_UP) h[v] = h[v] * __frcp_rn(1.0f + __expf(-h[v])) * acc[i][1][v];
+                if (FUSED_UP) h[v] = h[v] * __frcp_rn(1.0f + __expf(-h[v])) * up[v];
             }
             *(uint2 *)(out + (int64_t)row * g.ldo + col) = make_uint2(pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3]));
         }
     }
 }
 
+// Which of `count` numbers workgroup b works on, or -1: 64 runs of equal length, dealt to the XCDs in turn.
+__device__ __forceinline__ int of_runs(int b, int count) {
+    const int xcd = b & 7, j = b >> 3, len = (count + 63) >> 6, chunk = j / max(len, 1), t = (xcd + 8 * chunk) * len + (j - chunk * len);
+    return chunk < 8 && t < count ? t : -1;
+}
+
+// Workgroups of the largest launch that `tiles` or fewer tiles make: the tiles, or one per compute unit and the others halved.
+inline int64_t grid_blocks(int64_t tiles, int n_cu) {
+    const int64_t whole = std::min<int64_t>(tiles, n_cu), halves = 2 * std::min<int64_t>(tiles - whole, n_cu);
+    return std::max((tiles + 63) / 64 * 64, (whole + 63) / 64 * 64 + (halves + 63) / 64 * 64);
+}
+
 // SEG_PER_LANE: 1 for up to 64 row segments, 4 for up to 256.  The grid covers the launcher's bound on the pieces;
 // the rest exits.
+//
+// A compute unit has about 33 KB of loads in flight however many wavefronts ask, so one with two tiles takes twice as long as one
+// with one, and with between one and two tiles per unit the launch lasts as long as two (alone 20 to 25 us, in pairs 32 to
+// 38 us).  The tiles past one per unit are then cut in halves of 64 weight rows, a workgroup each.  Segments as a decode
+// batch of 512 has them (16 segments, d = 2048, f = 1024, 1026 rows, 368 tiles), gate+up 36.7 -> 32.1 us, down 22.9 -> 20.2 us; 264
+// tiles of f = 768 41.6 -> 32.3 us; shared experts' gate+up of 3001 rows, 352 tiles 36.0 -> 29.0 us.  Half tiles for all (672
+// instead of 336) read the rows twice as often: 39.7 -> 39.9 us.
 template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE>
-__global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArgs g, int n_strips) {
+__global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArgs g, int n_strips, int n_cu) {
     __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
     const int lane = (int)threadIdx.x & 63;
     StaleRows stale;
@@ -210,16 +249,24 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArg
     SegTable<SEG_PER_LANE> segs;
     segs.load(g, lane);
     segs.cut(lane, BM);
-    const int total = segs.total * n_strips, xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
-    const int len = (total + 63) >> 6, chunk = j / max(len, 1), t = (xcd + 8 * chunk) * len + (j - chunk * len);
-    if (chunk < 8 && t < total) {
+    const int total = segs.total * n_strips, whole = total > n_cu && total < 2 * n_cu ? n_cu : total;
+    const int whole_blocks = (whole + 63) & ~63, b = (int)blockIdx.x - whole_blocks;
+    const int half = b < 0 ? -1 : of_runs(b, 2 * (total - whole)), t = b < 0 ? of_runs((int)blockIdx.x, whole) : half < 0 ? -1 : whole + half / 2;
+    if (t >= 0) {
         const Segment s = segs.segment(t / n_strips, lane);
         const int in_seg = t - s.first_tile * n_strips, strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
         const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
-        const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows), n0 = strip * Shape<FUSED_UP>::BN;
-        if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6>(g, s.slot, m0, m_end, n0, smem);
-        else if (m_end - m0 > 32) tile_body<FUSED_UP, SEG_K, 4>(g, s.slot, m0, m_end, n0, smem);
-        else if (m_end > m0) tile_body<FUSED_UP, SEG_K, 2>(g, s.slot, m0, m_end, n0, smem);
+        const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows);
+        const int n0 = strip * Shape<FUSED_UP>::BN + (half < 0 ? 0 : (half & 1) * (Shape<FUSED_UP>::BN / 2));
+        const int first_step = SEG_K ? 0 : (s.slot * n_strips + strip) / 4 % ((g.K + BK - 1) / BK);
+        auto tile = [&](auto nj) {
+            constexpr int NJ = decltype(nj)::value;
+            if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6, NJ>(g, s.slot, m0, m_end, n0, first_step, smem);
+            else if (m_end - m0 > 32) tile_body<FUSED_UP, SEG_K, 4, NJ>(g, s.slot, m0, m_end, n0, first_step, smem);
+            else if (m_end > m0) tile_body<FUSED_UP, SEG_K, 2, NJ>(g, s.slot, m0, m_end, n0, first_step, smem);
+        };
+        if (half < 0) tile(std::integral_constant<int, 2>{});
+        else if (n0 < g.N) tile(std::integral_constant<int, 1>{});
     }
     if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
 }

@@ -78,6 +78,21 @@ def test_ordinary_batches(seg_rows, T, k, d, f):
     check_segments(got, want, off, TOL["bf16"])
 
 
+@pytest.mark.parametrize("seg_rows,T,k,d,f", [
+    ([96 * 256], 24576, 1, 72, 64),                 # a tile per compute unit: none is cut
+    ([96 * 256 + 1], 24577, 1, 72, 64),             # one tile of one row in halves; the down projection's second half past N
+    ([96 * 511 - 40], 49016, 1, 72, 40),            # all but one of the second ones; gate+up halves of 32 and 8 columns
+    ([96 * 512], 49152, 1, 72, 64),                 # two tiles each: none is cut
+    ([1, 96, 97, 0, 50, 33, 32, 16] * 2 + [70, 64, 17, 200], 200, 20, 2056, 968),   # ragged last strips, 340 and 357 tiles
+    ([3, 0, 40, 90, 17] * 26, 90, 44, 264, 136),    # more segments than lanes
+])
+def test_tiles_in_halves(seg_rows, T, k, d, f):
+    """Between one and two tiles per compute unit of a 256-unit GPU: those past the first per unit are halved."""
+    assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows)) == ("mid", "mid")
+    got, want, off = ffn_of_segments(seg_rows, T, k, d, f)
+    check_segments(got, want, off, TOL["bf16"])
+
+
 def test_up_projection_of_decode_batches():
     """More than 16 tokens whose gate+up strips fill the chip: streaming kernel for the down projection only."""
     assert kernels_of(40, 2, 256, 16 * 1024 + 24, 4, 4) == ("mid", "stream")
@@ -109,7 +124,8 @@ def test_f32_segments(seg_rows, T, k, d, f):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2), (97, 520, 40, 3),
-                                            (1100, 1024, 200, 3)])   # 12 pieces x 8 strips: more than one tile per run of an XCD
+                                            (1100, 1024, 200, 3),    # 12 pieces x 8 strips: more than one tile per run of an XCD
+                                            (1900, 2056, 104, 2)])   # 20 x 17 tiles: the second ones in halves
 def test_shared_experts_small_batches(T, d, f, n_shared, dtype):
     """Shared experts: the down projection's K runs through n_shared segments (lengths below, at and off the K step);
     the row scatter is a launch of its own here."""
