@@ -135,7 +135,16 @@ static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
 template <bool FUSED_UP>
 static Grid mid_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
     const int64_t n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
-    return {mid::grid_blocks((rows.m_bound / mid::BM + g.S) * n_strips, n_cu), mid::THREADS};
+    // ranks hold at most 4.9 times their instances' even share in the tables of the planner; the kernel walks in rounds what is more
+    const int64_t expected = rows.even_only ? rows.m_bound : rows.at(20);
+    const bool exact = g.M_single > 0;   // the shared experts
+    return {mid::grid_blocks((exact ? (expected + mid::BM - 1) / mid::BM : expected / mid::BM + g.S) * n_strips, n_cu, exact), mid::THREADS};
+}
+// All tiles of the rows that a rank could hold are numbered in 32 bits.
+template <bool FUSED_UP>
+static bool mid_tiles_fit(const GemmArgs &g, const Rows &rows) {
+    const int64_t n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+    return launchable({(rows.m_bound / mid::BM + g.S) * n_strips, mid::THREADS});
 }
 template <bool FUSED_UP>
 static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
@@ -211,7 +220,7 @@ template <bool FUSED_UP>
 static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };
     if (dt == GRACE_F32) return stream_ok<4>(g) && fits(Route::STREAM) ? Route::STREAM : Route::VECTOR_F32;
-    const bool mid_ok = stream_ok<2>(g, 8) && fits(Route::MID);
+    const bool mid_ok = stream_ok<2>(g, 8) && mid_tiles_fit<FUSED_UP>(g, rows);
     if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM)) {
         const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(g.S, rows.at(12)));
         const int64_t tiles = busy * ((g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN);

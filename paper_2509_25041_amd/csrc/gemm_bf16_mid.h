@@ -64,7 +64,9 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
                                           char *smem) {
     constexpr int AHEAD = MF == 2 ? 8 : MF == 4 ? 6 : 4;   // steps in flight: what 256 registers hold (even)
     constexpr int AL = MF / 2;   // activation loads per thread and step: 32 rows each
-    const int tid = (int)threadIdx.x, lane = tid & 63;
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));   // what follows from it stays out of the kernel's loop over tiles
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
     const int nk = (g.K + BK - 1) / BK;
@@ -225,14 +227,18 @@ __device__ __forceinline__ int of_runs(int b, int count) {
     return chunk < 8 && t < count ? t : -1;
 }
 
-// Workgroups of the largest launch that `tiles` or fewer tiles make: the tiles, or one per compute unit and the others halved.
-inline int64_t grid_blocks(int64_t tiles, int n_cu) {
-    const int64_t whole = std::min<int64_t>(tiles, n_cu), halves = 2 * std::min<int64_t>(tiles - whole, n_cu);
-    return std::max((tiles + 63) / 64 * 64, (whole + 63) / 64 * 64 + (halves + 63) / 64 * 64);
+// Workgroups of the largest launch that `tiles` or fewer tiles make: the tiles, or one per compute unit and the others halved;
+// few tiles are cut until there is about one per compute unit.  exact: there are that many.
+inline int64_t grid_blocks(int64_t tiles, int n_cu, bool exact) {
+    if (exact && tiles >= 2 * (int64_t)n_cu) return (tiles + 63) / 64 * 64;
+    const int64_t halves = 2 * std::min<int64_t>(std::max<int64_t>(tiles - n_cu, 0), n_cu);
+    return std::max((tiles + 63) / 64 * 64, (n_cu + 63) / 64 * 64 + (halves + 63) / 64 * 64);
 }
 
-// SEG_PER_LANE: 1 for up to 64 row segments, 4 for up to 256.  The grid covers the launcher's bound on the pieces;
-// the rest exits.
+// SEG_PER_LANE: 1 for up to 64 row segments, 4 for up to 256.  The grid covers the pieces of a rank with five times its share
+// of the rows; what is more is walked in rounds, and what is less exits.  (A workgroup without work takes 1 to 1.5 us of a place for
+// the segments' bounds: with one for every row of the batch, 3072 where 224 work, they took longer than the work, down
+// projection of 591 rows in two segments, f = 352 15.9 us.)
 //
 // A compute unit has about 33 KB of loads in flight however many wavefronts ask, so one with two tiles takes twice as long as one
 // with one, and with between one and two tiles per unit the launch lasts as long as two (alone 20 to 25 us, in pairs 32 to
@@ -240,25 +246,42 @@ inline int64_t grid_blocks(int64_t tiles, int n_cu) {
 // batch of 512 has them (16 segments, d = 2048, f = 1024, 1026 rows, 368 tiles), gate+up 36.7 -> 32.1 us, down 22.9 -> 20.2 us; 264
 // tiles of f = 768 41.6 -> 32.3 us; shared experts' gate+up of 3001 rows, 352 tiles 36.0 -> 29.0 us.  Half tiles for all (672
 // instead of 336) read the rows twice as often: 39.7 -> 39.9 us.
+//
+// Few tiles leave units without work, and a step's time falls with the bytes that its workgroup loads: up to one tile for every
+// other unit all are halved (110 tiles, d = 2048, f = 1408, gate+up 22.5 -> 17.4 us, 80 tiles down 16.7 -> 12.3 us), and pieces are
+// cut to 32 or 48 rows while there is a unit for each half (591 rows in two segments, f = 352, gate+up 22.5 -> 12.7 us; 64 rows
+// of d = 4096, f = 14336, down 114 -> 60 us).  More halves than units are slower again (308 of 32 rows 16.0 us, 220 of 48 rows 15.0 us).
 template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE>
 __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArgs g, int n_strips, int n_cu) {
     __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
-    const int lane = (int)threadIdx.x & 63;
     StaleRows stale;
     if (!FUSED_UP) stale = stale_rows(g);   // in flight during the work, used at the end
-    SegTable<SEG_PER_LANE> segs;
-    segs.load(g, lane);
-    segs.cut(lane, BM);
-    const int total = segs.total * n_strips, whole = total > n_cu && total < 2 * n_cu ? n_cu : total;
-    const int whole_blocks = (whole + 63) & ~63, b = (int)blockIdx.x - whole_blocks;
-    const int half = b < 0 ? -1 : of_runs(b, 2 * (total - whole)), t = b < 0 ? of_runs((int)blockIdx.x, whole) : half < 0 ? -1 : whole + half / 2;
-    if (t >= 0) {
+    for (int b = (int)blockIdx.x;;) {       // once, unless the rank has far more rows than its share
+        int lane = (int)threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));      // the table is read again each time: kept, it would cost the tile its registers
+        SegTable<SEG_PER_LANE> segs;
+        segs.load(g, lane);
+        segs.cut(lane, BM);
+        const bool few = 2 * segs.total * n_strips <= n_cu;
+        if (few) {
+            if (2 * segs.count(32) * n_strips <= n_cu) segs.cut(lane, 32);
+            else if (2 * segs.count(48) * n_strips <= n_cu) segs.cut(lane, 48);
+        }
+        const int total = segs.total * n_strips, whole = few ? 0 : total > n_cu && total < 2 * n_cu ? n_cu : total;
+        const int whole_blocks = (whole + 63) & ~63;
+        if (b >= whole_blocks + ((2 * (total - whole) + 63) & ~63)) break;
+        const int half = b < whole_blocks ? -1 : of_runs(b - whole_blocks, 2 * (total - whole));
+        const int t = b < whole_blocks ? of_runs(b, whole) : half < 0 ? -1 : whole + half / 2;
+        const bool again = b >= (int)gridDim.x;
+        b += (int)gridDim.x;
+        if (t < 0) continue;
         const Segment s = segs.segment(t / n_strips, lane);
         const int in_seg = t - s.first_tile * n_strips, strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
         const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
         const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows);
         const int n0 = strip * Shape<FUSED_UP>::BN + (half < 0 ? 0 : (half & 1) * (Shape<FUSED_UP>::BN / 2));
         const int first_step = SEG_K ? 0 : (s.slot * n_strips + strip) / 4 % ((g.K + BK - 1) / BK);
+        if (again) __syncthreads();   // the tile before has been read
         auto tile = [&](auto nj) {
             constexpr int NJ = decltype(nj)::value;
             if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6, NJ>(g, s.slot, m0, m_end, n0, first_step, smem);

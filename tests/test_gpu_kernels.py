@@ -85,12 +85,39 @@ def test_ordinary_batches(seg_rows, T, k, d, f):
     ([96 * 512], 49152, 1, 72, 64),                 # two tiles each: none is cut
     ([1, 96, 97, 0, 50, 33, 32, 16] * 2 + [70, 64, 17, 200], 200, 20, 2056, 968),   # ragged last strips, 340 and 357 tiles
     ([3, 0, 40, 90, 17] * 26, 90, 44, 264, 136),    # more segments than lanes
+    ([96 * 128], 12288, 1, 72, 64),                 # a half per compute unit, pieces of 96 rows
+    ([48 * 128, 0], 6144, 1, 72, 64),               # of 48
+    ([48 * 128 - 31, 1], 6144, 1, 72, 40),          # one too many for that in both projections: of 96; ragged halves
+    ([32 * 128], 4096, 1, 72, 64),                  # of 32
+    ([33, 0, 31, 65, 1], 66, 2, 1032, 328),         # of 32; half strips past N in both projections
 ])
 def test_tiles_in_halves(seg_rows, T, k, d, f):
-    """Between one and two tiles per compute unit of a 256-unit GPU: those past the first per unit are halved."""
+    """Between one and two tiles per compute unit of a 256-unit GPU: those past the first per unit are halved.  Few tiles: all
+    are, in pieces of 32, 48 or 96 rows."""
     assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows)) == ("mid", "mid")
     got, want, off = ffn_of_segments(seg_rows, T, k, d, f)
     check_segments(got, want, off, TOL["bf16"])
+
+
+def test_more_rows_than_a_rank_is_expected_to_hold():
+    """The 96-row kernel's grid covers five times an instance's even share; here one of 64 instances holds every row."""
+    T, k, d, f, E = 3000, 8, 200, 1032, 64
+    rng = np.random.default_rng(1)
+
+    def normal(scale, *shape):
+        return torch.from_numpy((scale * rng.standard_normal(shape)).astype(np.float32)).cuda().bfloat16()
+
+    table = grace.GraceTable(E, E, 1, [0] * E, [1] * E, list(range(E + 1)), list(range(E)))
+    assert kernels_of(T, k, d, f, 1, E) == ("mid", "mid")
+    assert grace.grace_ffn_kernel(True, T, d, f, k=k, S=1, I=E)[1] < (T // 96) * 17 * 256     # fewer workgroups than tiles
+    w = normal(0.05, 1, f, d), normal(0.05, 1, f, d), normal(0.05, 1, d, f)
+    x = normal(1.0, T * k, d)
+    off = np.full(E + 1, T * k, dtype=np.int32)
+    off[:6] = 0
+    y = grace.grace_expert_ffn(table, 5, x, torch.from_numpy(off).cuda(), T, k, *w)
+    rows = rng.permutation(T * k)[:600]
+    want = oracle.ffn_rows(oracle.widen(host(x[rows])), *(oracle.widen(host(m[0])) for m in w), threads=8)
+    assert rel_err(oracle.widen(host(y[rows])), want) <= TOL["bf16"]
 
 
 def test_up_projection_of_decode_batches():
