@@ -54,11 +54,11 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
 //  * rank by broadcast: each lane's key is broadcast through a scalar register (v_readlane) and
 //    compared against the local keys, so after E broadcasts rank = number of larger keys.  Keys are
 //    distinct (they include the expert id), so ranks are a permutation.
-// Out: rank[v] of every local expert (any value >= k when it is not chosen) and, for ranks < k,
-// its gate weight (softmax over all E logits, divided by the sum over the k chosen when renorm != 0).
-template <int VPL>
-__device__ __forceinline__ void token_topk(const float (&raw)[VPL], int lane, int E, int k, int renorm, int (&rank)[VPL],
-                                           float (&weight)[VPL]) {
+// ALONE: the wavefront waits for its own instructions rather than for other wavefronts', and the second way, whose broadcasts
+// do not depend on one another, is the faster one for up to 64 experts whatever k is.
+// Out: rank[v] of every local expert (any value >= k when it is not chosen).
+template <int VPL, bool ALONE = false>
+__device__ __forceinline__ void token_ranks(const float (&raw)[VPL], int lane, int E, int k, int (&rank)[VPL]) {
     float val[VPL];
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
@@ -66,7 +66,7 @@ __device__ __forceinline__ void token_topk(const float (&raw)[VPL], int lane, in
         if (x == 0.0f) x = 0.0f;  // -0.0 and +0.0 compare equal: make them the same bits
         val[v] = x;
     }
-    if (k * (18 + 8 * VPL) < 64 * VPL * (2 + 5 * VPL)) {  // uniform
+    if (!(ALONE && VPL == 1) && k * (18 + 8 * VPL) < 64 * VPL * (2 + 5 * VPL)) {  // uniform
         // finite logits map to integers >= 0x007FFFFF; 0 marks "no expert here" and "already chosen"
         uint32_t pool[VPL];
 #pragma unroll
@@ -115,6 +115,16 @@ __device__ __forceinline__ void token_topk(const float (&raw)[VPL], int lane, in
             }
         }
     }
+}
+
+// Gate weights of the experts of ranks < k (softmax over all E logits, divided by the sum over the k chosen when
+// renorm != 0).
+template <int VPL>
+__device__ __forceinline__ void token_weights(const float (&raw)[VPL], int lane, int E, int k, int renorm, const int (&rank)[VPL],
+                                              float (&weight)[VPL]) {
+    float val[VPL];
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) val[v] = raw[v] == 0.0f ? 0.0f : raw[v];
     // the maximum logit belongs to the expert of rank 0
     float mx = 0.0f;
 #pragma unroll
@@ -132,6 +142,92 @@ __device__ __forceinline__ void token_topk(const float (&raw)[VPL], int lane, in
     const float norm = renorm ? wave_sum_f32(sel) : wave_sum_f32(den);
 #pragma unroll
     for (int v = 0; v < VPL; ++v) weight[v] = ex[v] / norm;
+}
+
+template <int VPL>
+__device__ __forceinline__ void token_topk(const float (&raw)[VPL], int lane, int E, int k, int renorm, int (&rank)[VPL],
+                                           float (&weight)[VPL]) {
+    token_ranks<VPL>(raw, lane, E, k, rank);
+    token_weights<VPL>(raw, lane, E, k, renorm, rank, weight);
+}
+
+// The same gate for four tokens by one wavefront: 16 lanes (a DPP row) per token, lane r of a row holds experts
+// r + 16 u, u < 4 * VPL, as a list in descending order (equal logits: ascending id).  In each of k rounds the row's largest
+// head is choice j and leaves its list: one chain of four DPP steps per round, where a search through all experts of a
+// lane and of the row has more than thirty steps (small batches wait for the chain; 64 experts, k = 8: 4.0 -> 1.5 us).
+// chosen(j, e) is called in the lane of the row that holds choice j, expert e (e >= E if there is none).
+template <int DPP_CTRL>
+__device__ __forceinline__ uint32_t dpp_min_step(uint32_t v) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_CTRL, 0xF, 0xF, false);
+    return min(v, o);
+}
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
+    return dpp_max_step<0x140>(dpp_max_step<0x141>(dpp_max_step<0x4E>(dpp_max_step<0xB1>(v))));
+}
+__device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {
+    return dpp_min_step<0x140>(dpp_min_step<0x141>(dpp_min_step<0x4E>(dpp_min_step<0xB1>(v))));
+}
+__device__ __forceinline__ float row_sum_f32(float v) {
+    return dpp_add_step<0x140>(dpp_add_step<0x141>(dpp_add_step<0x4E>(dpp_add_step<0xB1>(v))));
+}
+template <int VPL, typename F>
+__device__ __forceinline__ void row_topk(const float (&raw)[4 * VPL], int r, int E, int k, F chosen) {
+    constexpr int NU = 4 * VPL;
+    uint32_t key[NU], id[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {   // insertion in front of the first entry that it beats; all comparisons at once
+        const uint32_t kx = r + 16 * u < E ? ordered_bits(raw[u] == 0.0f ? 0.0f : raw[u]) : 0u, ix = (uint32_t)(r + 16 * u);
+        key[u] = kx;
+        id[u] = ix;
+#pragma unroll
+        for (int i = u; i >= 1; --i) {
+            const bool beats = kx > key[i - 1];
+            key[i] = beats ? key[i - 1] : key[i];
+            id[i] = beats ? id[i - 1] : id[i];
+            key[i - 1] = beats ? kx : key[i - 1];
+            id[i - 1] = beats ? ix : id[i - 1];
+        }
+    }
+    for (int j = 0; j < k; ++j) {
+        bool hit = key[0] == row_max_u32(key[0]);
+        if (__popcll(__ballot(hit)) > 4) {   // equal logits in a row
+            const uint32_t lowest = row_min_u32(hit ? id[0] : 0xFFFFFFFFu);
+            hit = hit && id[0] == lowest;
+        }
+        if (hit) chosen(j, (int)id[0]);
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+            key[i] = hit ? (i + 1 < NU ? key[i + 1] : 0u) : key[i];
+            id[i] = hit ? (i + 1 < NU ? id[i + 1] : 0xFFFFu) : id[i];
+        }
+    }
+}
+// Gate weights of the same experts, rank[u] of each given: the sums in token_topk's order (per lane of 64 over its experts, per
+// row of 16, then the rows in pairs), so the same bits.
+template <int VPL>
+__device__ __forceinline__ void row_weights(const float (&raw)[4 * VPL], int r, int E, int k, int renorm, const int (&rank)[4 * VPL],
+                                            float (&weight)[4 * VPL]) {
+    constexpr int NU = 4 * VPL;
+    uint32_t first = 0u;   // the largest logit, by the bits that the choice went by
+#pragma unroll
+    for (int u = 0; u < NU; ++u) first = rank[u] == 0 ? ordered_bits(raw[u] == 0.0f ? 0.0f : raw[u]) : first;
+    first = row_max_u32(first);
+    const float mx = __uint_as_float((first & 0x80000000u) ? first & 0x7FFFFFFFu : ~first);
+    float part[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        float s = 0.0f;
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) {
+            const int w = u + 4 * v;
+            weight[w] = r + 16 * w < E ? expf((raw[w] == 0.0f ? 0.0f : raw[w]) - mx) : 0.0f;
+            s += renorm && rank[w] >= k ? 0.0f : weight[w];
+        }
+        part[u] = row_sum_f32(s);
+    }
+    const float norm = (part[0] + part[1]) + (part[2] + part[3]);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) weight[u] = weight[u] / norm;
 }
 
 // W of Section 4.3's round-robin for expert e: the weight sum of its candidate tier.

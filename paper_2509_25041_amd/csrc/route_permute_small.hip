@@ -16,7 +16,9 @@
 // and by the row scatter: three launches.
 // Outputs are identical either way (all integer work is exact and order-independent).
 #include <mutex>
+#include <type_traits>
 
+#include "bf16.h"
 #include "common.h"
 #include "route_device.h"
 #include "stable_sort.h"
@@ -162,6 +164,218 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
     }
 }
 
+// The smallest batches: top-k, index work and row movement in one launch.  Three launches of 2 to 7 us each wait for one
+// another's first loads there, while all the index work of 64 tokens is a few microseconds for one workgroup.  So every
+// workgroup (one per token) does all of it from the logits, in LDS, and moves and writes what belongs to its token; workgroup 0 also
+// writes the counts and offsets.  A wavefront takes up to four tokens in the gate and at most 64 assignments afterwards (so each
+// lane keeps its assignment in registers); the experts' candidates and the token's row are loaded ahead, under the gate.
+// Layer steps, the three launches -> this one: 1 token, k = 8 10.2 -> TINY1 us; 16 tokens, 128 experts 17.6 -> TINY16 us; 64 tokens
+// 14.5 -> TINY64 us.  From here on the gate alone would take each workgroup longer than a launch of its own (four tokens per
+// wavefront are 2.5 us).
+constexpr int TINY_MAX_PASSES = 2, TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16, TINY_MAX_T = 4 * TINY_MAX_WAVES * TINY_MAX_PASSES;
+inline bool tiny_batch(int T, int k, int E, int I) {
+    return T >= 1 && T <= TINY_MAX_T && (int64_t)T * k <= TINY_MAX_ASG && E <= SMALL_MAX_KEYS && I <= SMALL_MAX_KEYS;
+}
+
+// PASSES: 0, a wavefront per token; else four tokens per wavefront, that many times.
+template <int VPL, int PASSES>
+__global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel(
+    const float *__restrict__ logits, int T, int E, int k, int renorm, const uint32_t *__restrict__ rr_in,
+    uint32_t *__restrict__ rr_out, const int32_t *__restrict__ cand_ptr, const int32_t *__restrict__ cand_g,
+    const uint32_t *__restrict__ cand_cum, int I, int R, int N, const int32_t *__restrict__ rank_ptr,
+    const int32_t *__restrict__ node_first_inst, int32_t *__restrict__ topk_expert, float *__restrict__ topk_weight,
+    int32_t *__restrict__ topk_inst, int32_t *__restrict__ expert_count, int32_t *__restrict__ perm_pos,
+    int32_t *__restrict__ perm_src, int32_t *__restrict__ inst_off, int32_t *__restrict__ rank_off,
+    int32_t *__restrict__ node_off, const uint4 *__restrict__ x, int row_vec, uint4 *__restrict__ xp) {
+    __shared__ int32_t ecnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // requests per expert of a wavefront, then before it
+    __shared__ int32_t icnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // rows per instance of a wavefront, then before it
+    __shared__ int32_t asg[TINY_MAX_ASG];                      // expert of every assignment, then its position
+    __shared__ int32_t first[SMALL_MAX_KEYS], count[SMALL_MAX_KEYS], only[SMALL_MAX_KEYS];   // candidates of an expert; the first one
+    __shared__ uint32_t weight_sum[SMALL_MAX_KEYS], rr[SMALL_MAX_KEYS];
+    __shared__ int32_t ioff[SMALL_MAX_KEYS + 1];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, threads = (int)blockDim.x, waves = threads >> 6;
+    const int n = T * k, groups = (n + 63) >> 6, me = (int)blockIdx.x;   // groups <= waves
+    const bool per_token = x != nullptr;   // a workgroup per token, or one for all
+    // ---- loads ahead: this wavefront's logits, the experts' candidates, the row to move
+    constexpr int NU = PASSES ? 4 * VPL : VPL;   // experts per lane
+    const int r = PASSES ? lane & 15 : lane;
+    float raw[PASSES ? PASSES : 1][NU];
+    auto token = [&](int i) { return PASSES ? (i * waves + wave) * 4 + (lane >> 4) : wave; };   // T <= waves * max(1, 4 * PASSES)
+#pragma unroll
+    for (int i = 0; i < (PASSES ? PASSES : 1); ++i)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int t = token(i), e = r + (PASSES ? 16 : 64) * u;
+            raw[i][u] = (t < T && e < E) ? logits[(size_t)t * E + e] : -INFINITY;
+        }
+    const int e_own = min(tid, E - 1);
+    const int cb = cand_ptr[e_own], ce = cand_ptr[e_own + 1];
+    const uint32_t rr_own = rr_in ? rr_in[e_own] : 0u;
+    const int copies = max(1, threads / row_vec), part = tid / row_vec, vec = tid - part * row_vec;   // `copies` groups of threads share the k rows
+    uint4 row = make_uint4(0u, 0u, 0u, 0u);
+    if (x && part < copies) row = x[(int64_t)me * row_vec + vec];
+    for (int i = tid; i < n; i += threads) asg[i] = -1;
+    for (int i = lane; i < SMALL_MAX_KEYS; i += 64) {
+        ecnt[wave][i] = 0;
+        icnt[wave][i] = 0;
+    }
+    __syncthreads();
+    // ---- gate; the weights, which nothing here needs, by the workgroup that owns the token
+    auto weights_out = [&](int t, const int (&rank)[NU], const float (&weight)[NU]) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int e = r + (PASSES ? 16 : 64) * u;
+            if (e < E && rank[u] < k) {
+                topk_expert[(size_t)t * k + rank[u]] = e;
+                topk_weight[(size_t)t * k + rank[u]] = weight[u];
+            }
+        }
+    };
+    if constexpr (PASSES == 0) {
+        const int t = wave;
+        if (t < T) {   // uniform per wavefront
+            int rank[NU];
+            token_ranks<VPL, true>(raw[0], lane, E, k, rank);
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+                if (r + 64 * u < E && rank[u] < k) asg[t * k + rank[u]] = r + 64 * u;
+            if (!per_token || t == me) {
+                float weight[NU];
+                token_weights<VPL>(raw[0], lane, E, k, renorm, rank, weight);
+                weights_out(t, rank, weight);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            if ((i * waves + wave) * 4 >= T) break;   // uniform per wavefront
+            const int t = token(i);
+            row_topk<VPL>(raw[i], r, E, k, [&](int j, int e) {
+                if (t < T && e < E) asg[t * k + j] = e;
+            });
+            const bool mine = t < T && (!per_token || t == me);
+            if (__ballot(mine)) {
+                int rank[NU];
+                float weight[NU];
+#pragma unroll
+                for (int u = 0; u < NU; ++u) rank[u] = k;
+                wave_ctr_fence();   // (this wavefront's own writes)
+                for (int j = 0; j < k; ++j) {
+                    const int e = t < T ? wave_ctr_load(&asg[t * k + j]) : -1;
+#pragma unroll
+                    for (int u = 0; u < NU; ++u) rank[u] = e == r + 16 * u ? j : rank[u];
+                }
+                row_weights<VPL>(raw[i], r, E, k, renorm, rank, weight);
+                if (mine) weights_out(t, rank, weight);
+            }
+        }
+    }
+    if (tid < E) {
+        first[tid] = cb;
+        count[tid] = ce - cb;
+        only[tid] = cand_g[cb];
+        weight_sum[tid] = cand_cum[ce - 1];
+        rr[tid] = rr_own;
+    }
+    __syncthreads();
+    // ---- requests of each expert: in the group, before it, in all
+    const uint64_t lt = lanemask_lt();
+    const int a = wave * 64 + lane;
+    int e = a < n ? asg[a] : -1;
+    const bool valid = e >= 0;
+    if (!valid) e = 0;
+    uint64_t same = 0;
+    if (wave < groups) {
+        same = wave_match((uint32_t)e, valid, bits_for(E));
+        if (valid && is_last_of(same)) ecnt[wave][e] = (int32_t)__popcll(same);
+    }
+    __syncthreads();
+    if (tid < E) {
+        int32_t run = 0;
+        for (int w = 0; w < groups; ++w) {
+            const int32_t c = ecnt[w][tid];
+            ecnt[w][tid] = run;
+            run += c;
+        }
+        if (me == 0) {
+            expert_count[tid] = run;
+            const uint64_t c = (uint64_t)rr[tid] + (uint64_t)(uint32_t)run;
+            const uint32_t W = weight_sum[tid];
+            if (rr_out) rr_out[tid] = (c >> 32) ? (uint32_t)(c % W) : (uint32_t)c % W;
+        }
+    }
+    __syncthreads();
+    // ---- replica pick; rows of each instance: in the group, before it, in all
+    int g = 0;
+    if (valid) {
+        if (count[e] == 1) {
+            g = only[e];
+        } else {
+            const uint64_t c = (uint64_t)(uint32_t)ecnt[wave][e] + (uint32_t)__popcll(same & lt) + (uint64_t)rr[e];
+            g = pick_candidate(c, e, cand_ptr, cand_g, cand_cum);
+        }
+    }
+    if (wave < groups) {
+        same = wave_match((uint32_t)g, valid, bits_for(I));
+        if (valid && is_last_of(same)) icnt[wave][g] = (int32_t)__popcll(same);
+    }
+    __syncthreads();
+    if (tid < SMALL_MAX_KEYS) {
+        int32_t total = 0;
+        for (int w = 0; w < groups; ++w) {
+            const int32_t c = icnt[w][tid];
+            icnt[w][tid] = total;
+            total += c;
+        }
+        ioff[tid] = total;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        int32_t c[4], s = 0;   // exclusive scan over the ids, four per lane
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c[q] = ioff[lane * 4 + q];
+            s += c[q];
+        }
+        const int32_t incl = wave_scan_add(s);
+        int32_t run = incl - s;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            ioff[lane * 4 + q] = run;
+            run += c[q];
+        }
+        if (lane == 63) ioff[SMALL_MAX_KEYS] = incl;
+    }
+    __syncthreads();
+    // ---- positions, offsets, rows
+    if (a < n) {
+        const int pos = valid ? ioff[g] + icnt[wave][g] + (int32_t)__popcll(same & lt) : -1;
+        asg[a] = pos;
+        if (!per_token || (a >= me * k && a < (me + 1) * k)) {
+            perm_pos[a] = pos;
+            if (valid) {
+                topk_inst[a] = g;
+                perm_src[pos] = a;
+            }
+        }
+    }
+    if (me == 0) {
+        for (int i = tid; i <= I; i += threads) inst_off[i] = ioff[i];
+        for (int r = tid; r <= R; r += threads) rank_off[r] = ioff[rank_ptr[r]];
+        for (int m = tid; m <= N; m += threads) node_off[m] = ioff[node_first_inst[m]];
+    }
+    if (!x) return;
+    __syncthreads();
+    if (part >= copies) return;
+    for (int v = vec; v < row_vec; v += threads) {   // more than once only if a row has more vectors than the workgroup threads
+        if (v != vec) row = x[(int64_t)me * row_vec + v];
+        for (int j = part; j < k; j += copies) {
+            const int32_t p = asg[me * k + j];
+            if (p >= 0) nt_store16(row, &xp[(int64_t)p * row_vec + v]);
+        }
+    }
+}
+
 }  // namespace grace
 
 using namespace grace;
@@ -199,6 +413,27 @@ static int route_permute_impl(const grace_table *table, int32_t local_rank, grac
         return GRACE_OK;
     }
     const int32_t *cand_ptr = table->d_cand_ptr + (size_t)(policy == GRACE_POLICY_WRR ? table->R : local_rank) * E;
+    if (tiny_batch(T, k, E, table->I)) {
+        const int row_vec = x ? (int)((int64_t)d * (dt == GRACE_F32 ? 4 : 2) / 16) : 1;
+        int waves = 4;   // a thread per expert and instance, a wavefront per 64 assignments and, up to the most, for four tokens
+        while (waves < TINY_MAX_WAVES && waves * (T <= TINY_MAX_WAVES ? 1 : 4) < T) waves *= 2;
+        while (waves * 64 < T * k) waves *= 2;
+        auto launch = [&](auto vpl) {
+            constexpr int VPL = decltype(vpl)::value;
+            auto *kern = T <= waves ? route_permute_tiny_kernel<VPL, 0> : T <= waves * 4 ? route_permute_tiny_kernel<VPL, 1>
+                                                                                        : route_permute_tiny_kernel<VPL, TINY_MAX_PASSES>;
+            kern<<<x ? T : 1, waves * 64, 0, st>>>(
+                logits, T, E, k, renorm, rr_in, rr_out, cand_ptr, table->d_cand_g, table->d_cand_cum, table->I, table->R, table->N,
+                table->d_rank_ptr, table->d_node_first_inst, topk_expert, topk_weight, topk_inst, expert_count, perm_pos, perm_src,
+                inst_off, rank_off, node_off, (const uint4 *)x, row_vec, (uint4 *)xp);
+        };
+        if (E <= 64) launch(std::integral_constant<int, 1>{});
+        else if (E <= 128) launch(std::integral_constant<int, 2>{});
+        else if (E <= 192) launch(std::integral_constant<int, 3>{});
+        else launch(std::integral_constant<int, 4>{});
+        GRACE_LAUNCH_CHECK("route_permute_tiny_kernel");
+        return GRACE_OK;
+    }
     rc = launch_topk(logits, T, E, k, renorm, topk_expert, topk_weight, (int32_t *)ws, nullptr, 0, st);
     if (rc != GRACE_OK) return rc;
     dispatch_small_kernel<<<1, SMALL_THREADS, 0, st>>>(T, E, k, rr_in, rr_out, cand_ptr, table->d_cand_g, table->d_cand_cum,

@@ -65,6 +65,18 @@ __device__ __forceinline__ void wave_ctr_add(T *p, T v) {
 }
 __device__ __forceinline__ void wave_ctr_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
+// Inclusive sum over the 64 lanes (all active): inside rows of 16 lanes, then row 0 into row 1 and 2 into 3, then the lower half
+// into the upper one.
+__device__ __forceinline__ int32_t wave_scan_add(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 __device__ __forceinline__ int bits_for(int nkeys) {
     int b = 0;
     while ((1 << b) < nkeys) ++b;

@@ -223,6 +223,36 @@ def test_combine_share_is_combine_of_zero_rows(T, k, d, dtype, lo, hi, shared):
     torch.testing.assert_close(got, want, rtol=0, atol=0, equal_nan=True)
 
 
+@pytest.mark.parametrize("T,E,k,d,dtype,rows,policy", [
+    (1, 1, 1, 8, "bf16", True, 0), (1, 256, 64, 2048, "f32", True, 1), (2, 64, 8, 2048, "bf16", True, 0),
+    (4, 65, 3, 4, "f32", True, 0), (5, 128, 8, 24, "bf16", True, 1), (16, 129, 8, 4096, "bf16", True, 0),
+    (17, 200, 60, 8, "bf16", False, 0), (33, 60, 4, 2056, "bf16", False, 1), (63, 193, 16, 40, "f32", True, 0),
+    (64, 64, 16, 9000, "bf16", True, 0),    # rows of more vectors than a workgroup has threads
+    (65, 64, 8, 8, "bf16", True, 0), (128, 128, 8, 2048, "bf16", True, 0), (127, 256, 8, 40, "f32", True, 1),
+    (64, 64, 17, 8, "bf16", True, 0), (129, 64, 3, 8, "bf16", True, 0)])   # past the one-launch kernel, in assignments and in tokens
+def test_one_launch_dispatch_of_few_tokens(T, E, k, d, dtype, rows, policy):
+    """Routing, index work and rows of up to 128 tokens in one launch against the separate calls: ties, masked experts, counters
+    near 2^32, experts with several candidates."""
+    rng = np.random.default_rng(T * E + k)
+    R = 4
+    hosts = [sorted(rng.choice(R, size=1 if E > 200 else rng.integers(1, 4 if E < 80 else 2), replace=False).tolist()) for _ in range(E)]
+    ptr = np.concatenate([[0], np.cumsum([len(h) for h in hosts])])
+    assert ptr[-1] <= 256
+    table = grace.GraceTable(E, R, 2, [0, 0, 1, 1], rng.integers(1, 9, size=R).tolist(), ptr.tolist(), np.concatenate(hosts).tolist())
+    logits = np.round(rng.standard_normal((T, E)) * 2).astype(np.float32) / 2
+    logits[0, ::2] = -0.0
+    logits[T // 2, 1:] = -np.inf
+    logits = torch.from_numpy(logits).cuda()
+    x = torch.from_numpy(rng.standard_normal((T, d)).astype(np.float32)).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    rr = torch.from_numpy(rng.integers(2 ** 32 - 9, 2 ** 32, size=E, dtype=np.uint64).astype(np.uint32).view(np.int32)).cuda()
+    out_a, out_b = torch.zeros_like(rr), torch.zeros_like(rr)
+    route = grace.grace_route(table, 2, logits, k, 0, rr, out_a, policy=policy)
+    perm = grace.grace_permute(table, route[2], x if rows else None)
+    one = grace.grace_route_permute(table, 2, logits, k, x if rows else None, 0, rr, out_b, policy=policy)
+    for a, b in zip((*route, *perm, out_a), (*one[0], *one[1], out_b)):
+        assert (a is None and b is None) or torch.equal(a, b)
+
+
 @pytest.mark.parametrize("nodes,gpus,T,k", [(2, 2, 1, 2), (3, 2, 255, 4), (1, 4, 1025, 3), (4, 2, 513, 2)])
 def test_send_list_block_edges(nodes, gpus, T, k):
     """Send lists whose assignments end just below, at and past a block of the counting and the expansion kernels."""
