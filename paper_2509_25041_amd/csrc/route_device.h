@@ -151,10 +151,11 @@ __device__ __forceinline__ void token_topk(const float (&raw)[VPL], int lane, in
     token_weights<VPL>(raw, lane, E, k, renorm, rank, weight);
 }
 
-// The same gate for four tokens by one wavefront: 16 lanes (a DPP row) per token, lane r of a row holds experts
-// r + 16 u, u < 4 * VPL, as a list in descending order (equal logits: ascending id).  In each of k rounds the row's largest
+// The same choice for four tokens by one wavefront, up to 64 experts: 16 lanes (a DPP row) per token, lane r of a row holds
+// experts r + 16 u as a list in descending order (equal logits: ascending id).  In each of k rounds the row's largest
 // head is choice j and leaves its list: one chain of four DPP steps per round, where a search through all experts of a
-// lane and of the row has more than thirty steps (small batches wait for the chain; 64 experts, k = 8: 4.0 -> 1.5 us).
+// lane and of the row has more than twenty (a small batch waits for the chain; gate of 64 tokens, k = 8, inside
+// the one-launch dispatch 4.5 -> 3 us).
 // chosen(j, e) is called in the lane of the row that holds choice j, expert e (e >= E if there is none).
 template <int DPP_CTRL>
 __device__ __forceinline__ uint32_t dpp_min_step(uint32_t v) {
@@ -167,12 +168,9 @@ __device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
 __device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {
     return dpp_min_step<0x140>(dpp_min_step<0x141>(dpp_min_step<0x4E>(dpp_min_step<0xB1>(v))));
 }
-__device__ __forceinline__ float row_sum_f32(float v) {
-    return dpp_add_step<0x140>(dpp_add_step<0x141>(dpp_add_step<0x4E>(dpp_add_step<0xB1>(v))));
-}
-template <int VPL, typename F>
-__device__ __forceinline__ void row_topk(const float (&raw)[4 * VPL], int r, int E, int k, F chosen) {
-    constexpr int NU = 4 * VPL;
+template <typename F>
+__device__ __forceinline__ void row_topk(const float (&raw)[4], int r, int E, int k, F chosen) {
+    constexpr int NU = 4;
     uint32_t key[NU], id[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {   // insertion in front of the first entry that it beats; all comparisons at once
@@ -202,34 +200,6 @@ __device__ __forceinline__ void row_topk(const float (&raw)[4 * VPL], int r, int
         }
     }
 }
-// Gate weights of the same experts, rank[u] of each given: the sums in token_topk's order (per lane of 64 over its experts, per
-// row of 16, then the rows in pairs), so the same bits.
-template <int VPL>
-__device__ __forceinline__ void row_weights(const float (&raw)[4 * VPL], int r, int E, int k, int renorm, const int (&rank)[4 * VPL],
-                                            float (&weight)[4 * VPL]) {
-    constexpr int NU = 4 * VPL;
-    uint32_t first = 0u;   // the largest logit, by the bits that the choice went by
-#pragma unroll
-    for (int u = 0; u < NU; ++u) first = rank[u] == 0 ? ordered_bits(raw[u] == 0.0f ? 0.0f : raw[u]) : first;
-    first = row_max_u32(first);
-    const float mx = __uint_as_float((first & 0x80000000u) ? first & 0x7FFFFFFFu : ~first);
-    float part[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        float s = 0.0f;
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-            const int w = u + 4 * v;
-            weight[w] = r + 16 * w < E ? expf((raw[w] == 0.0f ? 0.0f : raw[w]) - mx) : 0.0f;
-            s += renorm && rank[w] >= k ? 0.0f : weight[w];
-        }
-        part[u] = row_sum_f32(s);
-    }
-    const float norm = (part[0] + part[1]) + (part[2] + part[3]);
-#pragma unroll
-    for (int u = 0; u < NU; ++u) weight[u] = weight[u] / norm;
-}
-
 // W of Section 4.3's round-robin for expert e: the weight sum of its candidate tier.
 __device__ __forceinline__ uint32_t next_rr(const uint32_t *rr_in, int e, int32_t n, const int32_t *cand_ptr,
                                             const uint32_t *cand_cum) {

@@ -167,18 +167,22 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
 // The smallest batches: top-k, index work and row movement in one launch.  Three launches of 2 to 7 us each wait for one
 // another's first loads there, while all the index work of 64 tokens is a few microseconds for one workgroup.  So every
 // workgroup (one per token) does all of it from the logits, in LDS, and moves and writes what belongs to its token; workgroup 0 also
-// writes the counts and offsets.  A wavefront takes up to four tokens in the gate and at most 64 assignments afterwards (so each
-// lane keeps its assignment in registers); the experts' candidates and the token's row are loaded ahead, under the gate.
-// Layer steps, the three launches -> this one: 1 token, k = 8 10.2 -> TINY1 us; 16 tokens, 128 experts 17.6 -> TINY16 us; 64 tokens
-// 14.5 -> TINY64 us.  From here on the gate alone would take each workgroup longer than a launch of its own (four tokens per
-// wavefront are 2.5 us).
-constexpr int TINY_MAX_PASSES = 2, TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16, TINY_MAX_T = 4 * TINY_MAX_WAVES * TINY_MAX_PASSES;
+// writes the counts and offsets.  Bound by latency, so: a wavefront takes a token in the gate, or four (row_topk) past 16 tokens,
+// and at most 64 assignments afterwards (each lane keeps its own in registers); candidates, the token's row and its logits
+// are loaded ahead; the gate weights, which only the caller needs, come last, under the row's stores.
+// Layer steps, the three launches -> this one (1, 16, 64 tokens): 64 experts, k = 8 24.3 -> 20.8, 30.6 -> 25.0, 38.0 -> 33.9 us; 8 experts, k = 2
+// 22.8 -> 17.8, 30.8 -> 27.2, 34.9 -> 30.5 us; 128 experts, k = 8 22.8 -> 18.8, 31.1 -> 24.0 us.  Where the line lies: every workgroup
+// repeats the gate of all tokens; 64 experts, k = 8 100 tokens 39.2 -> 37.6, 128 tokens 39.1 -> 38.3, k = 6 56.1 -> 55.8, 56.7 -> 57.6 us; 128
+// experts, two tokens per wavefront past 16 (four by rows: 33 tokens 32.1 -> 32.2, 64 tokens 34.9 -> 36.1 us).
+constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
+constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;   // up to 64 experts, more
 inline bool tiny_batch(int T, int k, int E, int I) {
-    return T >= 1 && T <= TINY_MAX_T && (int64_t)T * k <= TINY_MAX_ASG && E <= SMALL_MAX_KEYS && I <= SMALL_MAX_KEYS;
+    return T >= 1 && T <= (E <= 64 ? TINY_MAX_T : TINY_MAX_T_WIDE) && (int64_t)T * k <= TINY_MAX_ASG && E <= SMALL_MAX_KEYS &&
+           I <= SMALL_MAX_KEYS;
 }
 
-// PASSES: 0, a wavefront per token; else four tokens per wavefront, that many times.
-template <int VPL, int PASSES>
+// VPL: experts per lane where a wavefront takes a token; ROWS: a wavefront takes four tokens at a time.  PASSES: how often.
+template <int VPL, bool ROWS, int PASSES>
 __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel(
     const float *__restrict__ logits, int T, int E, int k, int renorm, const uint32_t *__restrict__ rr_in,
     uint32_t *__restrict__ rr_out, const int32_t *__restrict__ cand_ptr, const int32_t *__restrict__ cand_g,
@@ -189,23 +193,23 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
     int32_t *__restrict__ node_off, const uint4 *__restrict__ x, int row_vec, uint4 *__restrict__ xp) {
     __shared__ int32_t ecnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // requests per expert of a wavefront, then before it
     __shared__ int32_t icnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // rows per instance of a wavefront, then before it
-    __shared__ int32_t asg[TINY_MAX_ASG];                      // expert of every assignment, then its position
+    __shared__ int32_t asg[TINY_MAX_ASG], where[TINY_MAX_ASG]; // expert of every assignment; its position
     __shared__ int32_t first[SMALL_MAX_KEYS], count[SMALL_MAX_KEYS], only[SMALL_MAX_KEYS];   // candidates of an expert; the first one
     __shared__ uint32_t weight_sum[SMALL_MAX_KEYS], rr[SMALL_MAX_KEYS];
     __shared__ int32_t ioff[SMALL_MAX_KEYS + 1];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, threads = (int)blockDim.x, waves = threads >> 6;
-    const int n = T * k, groups = (n + 63) >> 6, me = (int)blockIdx.x;   // groups <= waves
-    const bool per_token = x != nullptr;   // a workgroup per token, or one for all
+    const int n = T * k, groups = (n + 63) >> 6, me = (int)blockIdx.x;   // groups <= waves; a workgroup per token
     // ---- loads ahead: this wavefront's logits, the experts' candidates, the row to move
-    constexpr int NU = PASSES ? 4 * VPL : VPL;   // experts per lane
-    const int r = PASSES ? lane & 15 : lane;
-    float raw[PASSES ? PASSES : 1][NU];
-    auto token = [&](int i) { return PASSES ? (i * waves + wave) * 4 + (lane >> 4) : wave; };   // T <= waves * max(1, 4 * PASSES)
+    static_assert(!ROWS || VPL == 1, "row_topk takes up to 64 experts");
+    constexpr int NU = ROWS ? 4 : VPL;   // experts per lane
+    const int r = ROWS ? lane & 15 : lane;
+    float raw[PASSES][NU];
+    auto token = [&](int i) { return ROWS ? (i * waves + wave) * 4 + (lane >> 4) : i * waves + wave; };
 #pragma unroll
-    for (int i = 0; i < (PASSES ? PASSES : 1); ++i)
+    for (int i = 0; i < PASSES; ++i)
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
-            const int t = token(i), e = r + (PASSES ? 16 : 64) * u;
+            const int t = token(i), e = r + (ROWS ? 16 : 64) * u;
             raw[i][u] = (t < T && e < E) ? logits[(size_t)t * E + e] : -INFINITY;
         }
     const int e_own = min(tid, E - 1);
@@ -214,60 +218,33 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
     const int copies = max(1, threads / row_vec), part = tid / row_vec, vec = tid - part * row_vec;   // `copies` groups of threads share the k rows
     uint4 row = make_uint4(0u, 0u, 0u, 0u);
     if (x && part < copies) row = x[(int64_t)me * row_vec + vec];
+    float own[VPL];   // the last wavefront's: the token's logits, for its weights
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) {
+        const int e = lane + 64 * v;
+        own[v] = (wave == waves - 1 && e < E) ? logits[(size_t)me * E + e] : -INFINITY;
+    }
     for (int i = tid; i < n; i += threads) asg[i] = -1;
     for (int i = lane; i < SMALL_MAX_KEYS; i += 64) {
         ecnt[wave][i] = 0;
         icnt[wave][i] = 0;
     }
     __syncthreads();
-    // ---- gate; the weights, which nothing here needs, by the workgroup that owns the token
-    auto weights_out = [&](int t, const int (&rank)[NU], const float (&weight)[NU]) {
+    // ---- gate (the weights, which nothing here needs, at the end)
 #pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int e = r + (PASSES ? 16 : 64) * u;
-            if (e < E && rank[u] < k) {
-                topk_expert[(size_t)t * k + rank[u]] = e;
-                topk_weight[(size_t)t * k + rank[u]] = weight[u];
-            }
-        }
-    };
-    if constexpr (PASSES == 0) {
-        const int t = wave;
-        if (t < T) {   // uniform per wavefront
-            int rank[NU];
-            token_ranks<VPL, true>(raw[0], lane, E, k, rank);
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-                if (r + 64 * u < E && rank[u] < k) asg[t * k + rank[u]] = r + 64 * u;
-            if (!per_token || t == me) {
-                float weight[NU];
-                token_weights<VPL>(raw[0], lane, E, k, renorm, rank, weight);
-                weights_out(t, rank, weight);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < PASSES; ++i) {
-            if ((i * waves + wave) * 4 >= T) break;   // uniform per wavefront
-            const int t = token(i);
-            row_topk<VPL>(raw[i], r, E, k, [&](int j, int e) {
+    for (int i = 0; i < PASSES; ++i) {
+        const int t = token(i);
+        if ((ROWS ? (i * waves + wave) * 4 : t) >= T) break;   // uniform per wavefront
+        if constexpr (ROWS) {
+            row_topk(raw[i], r, E, k, [&](int j, int e) {
                 if (t < T && e < E) asg[t * k + j] = e;
             });
-            const bool mine = t < T && (!per_token || t == me);
-            if (__ballot(mine)) {
-                int rank[NU];
-                float weight[NU];
+        } else {
+            int rank[NU];
+            token_ranks<VPL, true>(raw[i], lane, E, k, rank);
 #pragma unroll
-                for (int u = 0; u < NU; ++u) rank[u] = k;
-                wave_ctr_fence();   // (this wavefront's own writes)
-                for (int j = 0; j < k; ++j) {
-                    const int e = t < T ? wave_ctr_load(&asg[t * k + j]) : -1;
-#pragma unroll
-                    for (int u = 0; u < NU; ++u) rank[u] = e == r + 16 * u ? j : rank[u];
-                }
-                row_weights<VPL>(raw[i], r, E, k, renorm, rank, weight);
-                if (mine) weights_out(t, rank, weight);
-            }
+            for (int u = 0; u < NU; ++u)
+                if (lane + 64 * u < E && rank[u] < k) asg[t * k + rank[u]] = lane + 64 * u;
         }
     }
     if (tid < E) {
@@ -350,8 +327,8 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
     // ---- positions, offsets, rows
     if (a < n) {
         const int pos = valid ? ioff[g] + icnt[wave][g] + (int32_t)__popcll(same & lt) : -1;
-        asg[a] = pos;
-        if (!per_token || (a >= me * k && a < (me + 1) * k)) {
+        where[a] = pos;
+        if (a >= me * k && a < (me + 1) * k) {
             perm_pos[a] = pos;
             if (valid) {
                 topk_inst[a] = g;
@@ -364,15 +341,34 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
         for (int r = tid; r <= R; r += threads) rank_off[r] = ioff[rank_ptr[r]];
         for (int m = tid; m <= N; m += threads) node_off[m] = ioff[node_first_inst[m]];
     }
-    if (!x) return;
     __syncthreads();
-    if (part >= copies) return;
-    for (int v = vec; v < row_vec; v += threads) {   // more than once only if a row has more vectors than the workgroup threads
-        if (v != vec) row = x[(int64_t)me * row_vec + v];
-        for (int j = part; j < k; j += copies) {
-            const int32_t p = asg[me * k + j];
-            if (p >= 0) nt_store16(row, &xp[(int64_t)p * row_vec + v]);
+    if (x && part < copies) {
+        for (int v = vec; v < row_vec; v += threads) {   // more than once only if a row has more vectors than the workgroup threads
+            if (v != vec) row = x[(int64_t)me * row_vec + v];
+            for (int j = part; j < k; j += copies) {
+                const int32_t p = where[me * k + j];
+                if (p >= 0) nt_store16(row, &xp[(int64_t)p * row_vec + v]);
+            }
         }
+    }
+    // ---- what the call returns of the token's gate
+    if (wave == waves - 1) {
+        int rank[VPL];
+        float weight[VPL];
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) rank[v] = k;
+        for (int j = 0; j < k; ++j) {
+            const int e_j = asg[me * k + j];
+#pragma unroll
+            for (int v = 0; v < VPL; ++v) rank[v] = e_j == lane + 64 * v ? j : rank[v];
+        }
+        token_weights<VPL>(own, lane, E, k, renorm, rank, weight);
+#pragma unroll
+        for (int v = 0; v < VPL; ++v)
+            if (rank[v] < k) {
+                topk_expert[(size_t)me * k + rank[v]] = lane + 64 * v;
+                topk_weight[(size_t)me * k + rank[v]] = weight[v];
+            }
     }
 }
 
@@ -415,14 +411,19 @@ static int route_permute_impl(const grace_table *table, int32_t local_rank, grac
     const int32_t *cand_ptr = table->d_cand_ptr + (size_t)(policy == GRACE_POLICY_WRR ? table->R : local_rank) * E;
     if (tiny_batch(T, k, E, table->I)) {
         const int row_vec = x ? (int)((int64_t)d * (dt == GRACE_F32 ? 4 : 2) / 16) : 1;
-        int waves = 4;   // a thread per expert and instance, a wavefront per 64 assignments and, up to the most, for four tokens
-        while (waves < TINY_MAX_WAVES && waves * (T <= TINY_MAX_WAVES ? 1 : 4) < T) waves *= 2;
+        int waves = 4;   // a thread per expert and instance, a wavefront per 64 assignments and, up to the most, per token or four
+        const bool rows = E <= 64 && T > TINY_MAX_WAVES;
+        while (waves < TINY_MAX_WAVES && waves * (rows ? 4 : 1) < T) waves *= 2;
         while (waves * 64 < T * k) waves *= 2;
         auto launch = [&](auto vpl) {
             constexpr int VPL = decltype(vpl)::value;
-            auto *kern = T <= waves ? route_permute_tiny_kernel<VPL, 0> : T <= waves * 4 ? route_permute_tiny_kernel<VPL, 1>
-                                                                                        : route_permute_tiny_kernel<VPL, TINY_MAX_PASSES>;
-            kern<<<x ? T : 1, waves * 64, 0, st>>>(
+            auto *kern = route_permute_tiny_kernel<VPL, false, 1>;
+            if constexpr (VPL == 1) {
+                if (rows) kern = T <= 4 * waves ? route_permute_tiny_kernel<1, true, 1> : route_permute_tiny_kernel<1, true, 2>;
+            } else if (T > waves) {
+                kern = route_permute_tiny_kernel<VPL, false, 2>;
+            }
+            kern<<<T, waves * 64, 0, st>>>(
                 logits, T, E, k, renorm, rr_in, rr_out, cand_ptr, table->d_cand_g, table->d_cand_cum, table->I, table->R, table->N,
                 table->d_rank_ptr, table->d_node_first_inst, topk_expert, topk_weight, topk_inst, expert_count, perm_pos, perm_src,
                 inst_off, rank_off, node_off, (const uint4 *)x, row_vec, (uint4 *)xp);
