@@ -22,6 +22,7 @@
 #include "gemm_bf16_persist.h"
 #include "gemm_common.h"
 #include "gemm_f32.h"
+#include "gemm_f32_mid.h"
 #include "gemm_stream.h"
 
 namespace grace {
@@ -140,17 +141,23 @@ static Grid mid_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
     const bool exact = g.M_single > 0;   // the shared experts
     return {mid::grid_blocks((exact ? (expected + mid::BM - 1) / mid::BM : expected / mid::BM + g.S) * n_strips, n_cu, exact), mid::THREADS};
 }
-// All tiles of the rows that a rank could hold are numbered in 32 bits.
 template <bool FUSED_UP>
+static Grid mid_f32_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
+    const int64_t n_strips = (g.N + midf::Shape<FUSED_UP>::BN - 1) / midf::Shape<FUSED_UP>::BN;
+    const int64_t expected = rows.even_only ? rows.m_bound : rows.at(20);
+    return {(std::max<int64_t>((expected / midf::BM + g.S) * n_strips, n_cu) + 63) / 64 * 64, midf::THREADS};
+}
+// All tiles of the rows that a rank could hold are numbered in 32 bits.
+template <bool FUSED_UP, typename SHAPE>
 static bool mid_tiles_fit(const GemmArgs &g, const Rows &rows) {
-    const int64_t n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+    const int64_t n_strips = (g.N + SHAPE::BN - 1) / SHAPE::BN;
     return launchable({(rows.m_bound / mid::BM + g.S) * n_strips, mid::THREADS});
 }
 template <bool FUSED_UP>
 static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     if (route == Route::STREAM)
         return dt == GRACE_BF16 ? stream_grid<FUSED_UP, 2>(g, rows, n_cu) : stream_grid<FUSED_UP, 4>(g, rows, n_cu);
-    if (route == Route::MID) return mid_grid<FUSED_UP>(g, rows, n_cu);
+    if (route == Route::MID) return dt == GRACE_BF16 ? mid_grid<FUSED_UP>(g, rows, n_cu) : mid_f32_grid<FUSED_UP>(g, rows, n_cu);
     if (route == Route::PERSIST) return {pers::grid_blocks(n_cu), pers::THREADS};
     if (route == Route::GENERIC) {
         constexpr int BN = FUSED_UP ? 64 : 128;
@@ -219,8 +226,13 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
 template <bool FUSED_UP>
 static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };
-    if (dt == GRACE_F32) return stream_ok<4>(g) && fits(Route::STREAM) ? Route::STREAM : Route::VECTOR_F32;
-    const bool mid_ok = stream_ok<2>(g, 8) && mid_tiles_fit<FUSED_UP>(g, rows);
+    if (dt == GRACE_F32) {
+        // more rows per segment than one workgroup of the streaming kernel takes at a time; output rows of 16-byte vectors
+        if (rows.max_rows > strm::MAX_ROWS && g.N % 4 == 0 && stream_ok<4>(g, 4) && mid_tiles_fit<FUSED_UP, midf::Shape<FUSED_UP>>(g, rows))
+            return Route::MID;
+        return stream_ok<4>(g) && fits(Route::STREAM) ? Route::STREAM : Route::VECTOR_F32;
+    }
+    const bool mid_ok = stream_ok<2>(g, 8) && mid_tiles_fit<FUSED_UP, mid::Shape<FUSED_UP>>(g, rows);
     if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM)) {
         const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(g.S, rows.at(12)));
         const int64_t tiles = busy * ((g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN);
@@ -254,6 +266,19 @@ static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, hi
 }
 
 template <bool FUSED_UP>
+static void launch_mid_f32(const GemmArgs &g, const Grid &l, int n_cu, hipStream_t st) {
+    const int n_strips = (g.N + midf::Shape<FUSED_UP>::BN - 1) / midf::Shape<FUSED_UP>::BN;
+    if constexpr (!FUSED_UP) {
+        if (g.kseg_len < g.K) {
+            midf::gemm_f32_mid_kernel<false, true, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
+            return;
+        }
+    }
+    if (g.S <= 64) midf::gemm_f32_mid_kernel<FUSED_UP, false, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
+    else midf::gemm_f32_mid_kernel<FUSED_UP, false, 4><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
+}
+
+template <bool FUSED_UP>
 static void launch_mid(const GemmArgs &g, const Grid &l, int n_cu, hipStream_t st) {
     const int n_strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
     if constexpr (!FUSED_UP) {   // K segments: the shared experts' down projection alone
@@ -278,7 +303,8 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipS
         if (dt == GRACE_BF16) launch_stream<FUSED_UP, 2>(g, rows, l, st);
         else launch_stream<FUSED_UP, 4>(g, rows, l, st);
     } else if (route == Route::MID) {
-        launch_mid<FUSED_UP>(g, l, n_cu, st);
+        if (dt == GRACE_BF16) launch_mid<FUSED_UP>(g, l, n_cu, st);
+        else launch_mid_f32<FUSED_UP>(g, l, n_cu, st);
     } else if (route == Route::PERSIST) {
         // persistent large-tile kernel: one workgroup per compute unit, 160 KB of dynamic LDS
         using SH = pers::Shape<FUSED_UP>;

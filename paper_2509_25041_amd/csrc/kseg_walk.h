@@ -8,17 +8,17 @@ namespace grace {
 constexpr uint32_t NO_DATA = 0x80000000u;   // an offset past the range of the buffer descriptors: reads nothing, gives zeros
 
 // The lane looks at positions k, k + step, ... of K; what the segments before a position add to its byte offset
-// beyond 2 * k is `jump` (elements of 2 bytes).
+// beyond el * k is `jump` (elements of el bytes).
 struct KSegWalk {
     int pos;            // position in the K segment
     uint32_t jump = 0;
 
     // bytes to add to the offset of position k, then one step on.  Past K there is no data, whatever `jump` has grown to
     // (in 32 bits it wraps there when the weights hold 2 GiB or more).
-    constexpr uint32_t next(int k, int K, int seg_len, int64_t seg_stride, int step) {
+    constexpr uint32_t next(int k, int K, int seg_len, int64_t seg_stride, int step, int el = 2) {
         while (pos >= seg_len) {
             pos -= seg_len;
-            jump += (uint32_t)((seg_stride - seg_len) * 2);
+            jump += (uint32_t)((seg_stride - seg_len) * el);
         }
         pos += step;
         return k < K ? jump : NO_DATA;

@@ -175,9 +175,9 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
 // repeats the gate of all tokens; 64 experts, k = 8 100 tokens 39.2 -> 37.6, 128 tokens 39.1 -> 38.3, k = 6 56.1 -> 55.8, 56.7 -> 57.6 us; 128
 // experts, two tokens per wavefront past 16 (four by rows: 33 tokens 32.1 -> 32.2, 64 tokens 34.9 -> 36.1 us).
 constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
-constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;   // up to 64 experts, more
+constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_TOP2 = 16 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;
 inline bool tiny_batch(int T, int k, int E, int I) {
-    return T >= 1 && T <= (E <= 64 ? TINY_MAX_T : TINY_MAX_T_WIDE) && (int64_t)T * k <= TINY_MAX_ASG && E <= SMALL_MAX_KEYS &&
+    return T >= 1 && T <= (E > 64 ? TINY_MAX_T_WIDE : k > 2 ? TINY_MAX_T : TINY_MAX_T_TOP2) && (int64_t)T * k <= TINY_MAX_ASG && E <= SMALL_MAX_KEYS &&
            I <= SMALL_MAX_KEYS;
 }
 
@@ -419,7 +419,8 @@ static int route_permute_impl(const grace_table *table, int32_t local_rank, grac
             constexpr int VPL = decltype(vpl)::value;
             auto *kern = route_permute_tiny_kernel<VPL, false, 1>;
             if constexpr (VPL == 1) {
-                if (rows) kern = T <= 4 * waves ? route_permute_tiny_kernel<1, true, 1> : route_permute_tiny_kernel<1, true, 2>;
+                if (rows) kern = T <= 4 * waves ? route_permute_tiny_kernel<1, true, 1> : T <= 8 * waves ? route_permute_tiny_kernel<1, true, 2>
+                                                                                                : route_permute_tiny_kernel<1, true, 4>;
             } else if (T > waves) {
                 kern = route_permute_tiny_kernel<VPL, false, 2>;
             }

@@ -228,10 +228,10 @@ def test_combine_share_is_combine_of_zero_rows(T, k, d, dtype, lo, hi, shared):
     (4, 65, 3, 4, "f32", True, 0), (5, 128, 8, 24, "bf16", True, 1), (16, 129, 8, 4096, "bf16", True, 0),
     (17, 200, 60, 8, "bf16", False, 0), (33, 60, 4, 2056, "bf16", False, 1), (63, 193, 16, 40, "f32", True, 0),
     (64, 64, 16, 9000, "bf16", True, 0),    # rows of more vectors than a workgroup has threads
-    (65, 64, 8, 8, "bf16", True, 0), (32, 128, 8, 2048, "bf16", True, 0), (31, 256, 8, 40, "f32", True, 1), (96, 8, 4, 128, "f32", True, 1),
-    (64, 64, 17, 8, "bf16", True, 0), (97, 64, 3, 8, "bf16", True, 0), (33, 65, 3, 8, "bf16", True, 0)])   # past it, in assignments and in tokens
+    (65, 64, 8, 8, "bf16", True, 0), (32, 128, 8, 2048, "bf16", True, 0), (31, 256, 8, 40, "f32", True, 1), (96, 8, 4, 128, "f32", True, 1), (256, 8, 2, 128, "f32", True, 0),
+    (64, 64, 17, 8, "bf16", True, 0), (97, 64, 3, 8, "bf16", True, 0), (257, 64, 2, 8, "bf16", True, 0), (33, 65, 3, 8, "bf16", True, 0)])   # past it, in assignments and in tokens
 def test_one_launch_dispatch_of_few_tokens(T, E, k, d, dtype, rows, policy):
-    """Routing, index work and rows of up to 96 tokens in one launch against the separate calls: ties, masked experts, counters
+    """Routing, index work and rows of up to 96 (k = 2: 256) tokens in one launch against the separate calls: ties, masked experts, counters
     near 2^32, experts with several candidates."""
     rng = np.random.default_rng(T * E + k)
     R = 4
