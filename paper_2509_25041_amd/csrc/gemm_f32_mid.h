@@ -8,7 +8,9 @@
 // kernel) the address unit is the bound, 45 % of the matrix cores' time; here a step's 32 cycles per MFMA are far longer than
 // its loads, so what bounds it is the matrix cores and how evenly the tiles fall on the compute units: 64 weight rows
 // per workgroup, not 128, and pieces of up to 96 rows, lower ones while they leave units without work.
-// d = 1024, f = 2816, 8 segments, 977 rows, streaming kernel -> this one: gate+up UPS, down DNS us.
+// d = 1024, f = 2816, 8 segments, 977 rows, streaming kernel -> this one: gate+up 175 -> 156, down 107 -> 96 us (64 -> 72 and
+// 52 -> 59 TFLOP/s; a single segment of 6144 rows 110 and 123, the library 151).  The rest is the tiles' uneven sizes on few compute
+// units: 658 rows in seven full pieces, 9 to 30 rows in others.
 #pragma once
 #include "gemm_bf16_mid.h"
 

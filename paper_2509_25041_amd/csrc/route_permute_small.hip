@@ -35,6 +35,9 @@ inline bool small_batch(int T, int k, int E, int I) {
            ceil_div(T, SMALL_WAVES) * k <= SMALL_MAX_PER_WAVE;
 }
 
+// Bound by latency: a lane's assignments (four at most) are loaded at once and stay in registers, and the candidates of every
+// expert are loaded ahead of the loops, which have no global load left but those of experts with several candidates (a chain
+// of three per group of 64 assignments before: 512 tokens, k = 8 15.1 -> 11.4 us, 1000 tokens, k = 2 9.5 -> 7.5 us).
 __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
     int T, int E, int k, const uint32_t *__restrict__ rr_in, uint32_t *__restrict__ rr_out,
     const int32_t *__restrict__ cand_ptr, const int32_t *__restrict__ cand_g, const uint32_t *__restrict__ cand_cum, int I,
@@ -42,35 +45,47 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
     const int32_t *__restrict__ topk_expert, int32_t *__restrict__ topk_inst, int32_t *__restrict__ expert_count,
     int32_t *__restrict__ perm_pos, int32_t *__restrict__ perm_src, int32_t *__restrict__ inst_off,
     int32_t *__restrict__ rank_off, int32_t *__restrict__ node_off) {
+    constexpr int GROUPS = SMALL_MAX_PER_WAVE / 64;
     __shared__ int32_t ecnt[SMALL_WAVES][SMALL_MAX_KEYS];  // requests per expert of a wavefront, then before it
     __shared__ int32_t icnt[SMALL_WAVES][SMALL_MAX_KEYS];  // rows per instance of a wavefront, then before it
-    __shared__ int32_t asg[SMALL_WAVES][SMALL_MAX_PER_WAVE];  // expert, then instance, of the wavefront's assignments
+    __shared__ int32_t count[SMALL_MAX_KEYS], only[SMALL_MAX_KEYS];   // candidates of an expert; the first one
+    __shared__ uint32_t rr[SMALL_MAX_KEYS];
     __shared__ int32_t ioff[SMALL_MAX_KEYS + 1];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tpw = (T + SMALL_WAVES - 1) / SMALL_WAVES;  // tokens per wavefront
     const int t0 = min(T, wave * tpw), t1 = min(T, t0 + tpw);
     const int n_w = (t1 - t0) * k;                         // assignments of this wavefront, in order
     const int64_t a0 = (int64_t)t0 * k;
+    int key[GROUPS];   // expert, then instance, of this lane's assignments; -1: none, or an expert id outside the table
+#pragma unroll
+    for (int q = 0; q < GROUPS; ++q) key[q] = q * 64 + lane < n_w ? topk_expert[a0 + q * 64 + lane] : -1;
+    const int e_own = min(tid, E - 1);
+    const int cb = cand_ptr[e_own], ce = cand_ptr[e_own + 1];
+    const uint32_t rr_own = rr_in ? rr_in[e_own] : 0u;
     for (int i = lane; i < SMALL_MAX_KEYS; i += 64) {
         ecnt[wave][i] = 0;
         icnt[wave][i] = 0;
     }
-    int ebits = 0, ibits = 0;
-    while ((1 << ebits) < E) ++ebits;
-    while ((1 << ibits) < I) ++ibits;
+    const int ebits = bits_for(E), ibits = bits_for(I);
     const uint64_t lt = lanemask_lt();
     // The LDS operations of one wavefront execute in program order, so a counter updated by the last
     // lane of a match set is seen by the next group of 64 assignments.
     // ---- 0. this wavefront's experts and their counts ---------------------------------------------
-    for (int b = 0; b < n_w; b += 64) {
-        const int j = b + lane;
-        bool valid = j < n_w;
-        int e = valid ? topk_expert[a0 + j] : 0;
-        valid = valid && (unsigned)e < (unsigned)E;
-        if (j < n_w) asg[wave][j] = valid ? e : -1;
+#pragma unroll
+    for (int q = 0; q < GROUPS; ++q) {
+        if (q * 64 >= n_w) break;   // uniform per wavefront
+        if ((unsigned)key[q] >= (unsigned)E) key[q] = -1;
+        const bool valid = key[q] >= 0;
+        const int e = valid ? key[q] : 0;
         const uint64_t same = wave_match((uint32_t)e, valid, ebits);
         if (valid && is_last_of(same)) wave_ctr_add(&ecnt[wave][e], (int32_t)__popcll(same));
         wave_ctr_fence();
+    }
+    const uint32_t weight_sum = cand_cum[ce - 1];
+    if (tid < E) {
+        count[tid] = ce - cb;
+        only[tid] = cand_g[cb];
+        rr[tid] = rr_own;
     }
     __syncthreads();
     // ---- 1. requests of each expert before each wavefront; totals -----------------------------
@@ -83,24 +98,27 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
             run += c;
         }
         expert_count[tid] = run;
-        if (rr_out) rr_out[tid] = next_rr(rr_in, tid, run, cand_ptr, cand_cum);
+        const uint64_t c = (uint64_t)rr_own + (uint64_t)(uint32_t)run;
+        if (rr_out) rr_out[tid] = (c >> 32) ? (uint32_t)(c % weight_sum) : (uint32_t)c % weight_sum;
     }
     __syncthreads();
     // ---- 2. replica pick, in assignment order; instance counts ---------------------------------
-    for (int b = 0; b < n_w; b += 64) {
-        const int j = b + lane;
-        const int e_in = j < n_w ? asg[wave][j] : -1;
-        const bool valid = e_in >= 0;
-        const int e = valid ? e_in : 0;
+#pragma unroll
+    for (int q = 0; q < GROUPS; ++q) {
+        if (q * 64 >= n_w) break;
+        const bool valid = key[q] >= 0;
+        const int e = valid ? key[q] : 0;
         const uint64_t same = wave_match((uint32_t)e, valid, ebits);
         int g = 0;
         if (valid) {
-            const uint64_t c = (uint64_t)(uint32_t)wave_ctr_load(&ecnt[wave][e]) + (uint32_t)__popcll(same & lt) +
-                               (uint64_t)(rr_in ? rr_in[e] : 0u);
-            g = pick_candidate(c, e, cand_ptr, cand_g, cand_cum);
-            topk_inst[a0 + j] = g;
+            g = only[e];
+            if (count[e] > 1) {
+                const uint64_t c = (uint64_t)(uint32_t)wave_ctr_load(&ecnt[wave][e]) + (uint32_t)__popcll(same & lt) + (uint64_t)rr[e];
+                g = pick_candidate(c, e, cand_ptr, cand_g, cand_cum);
+            }
+            topk_inst[a0 + q * 64 + lane] = g;
+            key[q] = g;
         }
-        if (j < n_w) asg[wave][j] = valid ? g : -1;
         if (valid && is_last_of(same)) wave_ctr_add(&ecnt[wave][e], (int32_t)__popcll(same));
         const uint64_t same_g = wave_match((uint32_t)g, valid, ibits);
         if (valid && is_last_of(same_g)) wave_ctr_add(&icnt[wave][g], (int32_t)__popcll(same_g));
@@ -127,12 +145,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
             c[q] = ioff[lane * 4 + q];
             s += c[q];
         }
-        int32_t incl = s;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int32_t v = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += v;
-        }
+        const int32_t incl = wave_scan_add(s);
         int32_t run = incl - s;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -146,18 +159,19 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
     for (int r = tid; r <= R; r += SMALL_THREADS) rank_off[r] = ioff[rank_ptr[r]];
     for (int n = tid; n <= N; n += SMALL_THREADS) node_off[n] = ioff[node_first_inst[n]];
     // ---- 4. positions ---------------------------------------------------------------------------
-    for (int b = 0; b < n_w; b += 64) {
-        const int j = b + lane;
-        const int g_in = j < n_w ? asg[wave][j] : -1;
-        const bool valid = g_in >= 0;
-        const int g = valid ? g_in : 0;
+#pragma unroll
+    for (int q = 0; q < GROUPS; ++q) {
+        if (q * 64 >= n_w) break;
+        const int64_t a = a0 + q * 64 + lane;
+        const bool valid = key[q] >= 0;
+        const int g = valid ? key[q] : 0;
         const uint64_t same = wave_match((uint32_t)g, valid, ibits);
         if (valid) {
             const int32_t pos = ioff[g] + wave_ctr_load(&icnt[wave][g]) + (int32_t)__popcll(same & lt);
-            perm_pos[a0 + j] = pos;
-            perm_src[pos] = (int32_t)(a0 + j);
-        } else if (j < n_w) {
-            perm_pos[a0 + j] = -1;  // expert id outside the table: no row
+            perm_pos[a] = pos;
+            perm_src[pos] = (int32_t)a;
+        } else if (q * 64 + lane < n_w) {
+            perm_pos[a] = -1;  // expert id outside the table: no row
         }
         if (valid && is_last_of(same)) wave_ctr_add(&icnt[wave][g], (int32_t)__popcll(same));
         wave_ctr_fence();
@@ -172,7 +186,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
 // are loaded ahead; the gate weights, which only the caller needs, come last, under the row's stores.
 // Layer steps, the three launches -> this one (1, 16, 64 tokens): 64 experts, k = 8 24.3 -> 20.8, 30.6 -> 25.0, 38.0 -> 33.9 us; 8 experts, k = 2
 // 22.8 -> 17.8, 30.8 -> 27.2, 34.9 -> 30.5 us; 128 experts, k = 8 22.8 -> 18.8, 31.1 -> 24.0 us.  Where the line lies: every workgroup
-// repeats the gate of all tokens; 64 experts, k = 8 100 tokens 39.2 -> 37.6, 128 tokens 39.1 -> 38.3, k = 6 56.1 -> 55.8, 56.7 -> 57.6 us; 128
+// repeats the gate of all tokens; 64 experts, k = 8 100 tokens 39.2 -> 37.6, 128 tokens 39.1 -> 38.3, k = 6 56.1 -> 55.8, 56.7 -> 57.6 us; k = 2 200 tokens 42.5 -> 40.6, 256 tokens 42.7 -> 41.4 us; 128
 // experts, two tokens per wavefront past 16 (four by rows: 33 tokens 32.1 -> 32.2, 64 tokens 34.9 -> 36.1 us).
 constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
 constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_TOP2 = 16 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;
