@@ -7,7 +7,7 @@ from typing import List, Optional, Tuple
 
 import torch
 
-from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, grace_workspace_bytes, load_library
+from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_workspace_bytes, load_library
 
 STAGES = ("route", "permute", "route_permute", "ffn_up", "ffn_down", "shared_up", "shared_down", "combine")
 
@@ -138,7 +138,7 @@ class GraceMoELayer:
         append to), a pair of HIP events is recorded around every library call,
         or only around the calls named in `timed_stages`; `event_pool` supplies
         pre-created timing events (popped two per timed call)."""
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _stream()
         key = (logits.data_ptr(), x.data_ptr(), None if rr_in is None else rr_in.data_ptr(),
                None if rr_out is None else rr_out.data_ptr(), stream)
         if key != self._key:
