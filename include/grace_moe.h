@@ -283,6 +283,13 @@ int grace_expert_ffn_up(const grace_table *table, int32_t rank, const void *xp, 
 int grace_expert_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k,
                           int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, void *ws, void *stream);
 
+/* grace_expert_ffn_down that also writes the rows of other ranks, as zeros, inside its own launch: for a y that holds
+ * nothing yet.  d * sizeof(dt) must be a multiple of 16; when `rank` hosts no instance nothing is launched and y is not
+ * written. */
+int grace_expert_ffn_down_fresh(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k,
+                                int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, void *ws,
+                                void *stream);
+
 /* grace_expert_ffn_up / _down that also keep y a rank share from step to step.  On one GPU only
  * the rows of `rank` are computed; the rows of other ranks, which the second all-to-all of
  * Section 1 would deliver, are defined as zero.  The rank's row range [inst_off[first instance of

@@ -18,6 +18,7 @@ from .binding import (  # noqa: F401
     grace_combine_share,
     grace_expert_ffn,
     grace_expert_ffn_down,
+    grace_expert_ffn_down_fresh,
     grace_expert_ffn_down_share,
     grace_expert_ffn_up,
     grace_expert_ffn_up_share,

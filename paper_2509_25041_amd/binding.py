@@ -20,7 +20,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_table_instances", "grace_table_local_experts", "grace_table_set_fold_limits", "grace_workspace_bytes",
            "grace_route",
            "grace_permute", "grace_permute_rows", "grace_route_permute", "grace_route_permute_static", "grace_send_lists", "grace_expert_ffn", "grace_expert_ffn_up",
-           "grace_expert_ffn_down", "grace_expert_ffn_up_share", "grace_expert_ffn_down_share",
+           "grace_expert_ffn_down", "grace_expert_ffn_down_fresh", "grace_expert_ffn_up_share", "grace_expert_ffn_down_share",
            "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_combine_share", "grace_mfma_sustained",
            "grace_ffn_kernel",
            "grace_last_error")
@@ -71,6 +71,7 @@ def load_library() -> C.CDLL:
     lib.grace_expert_ffn.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp]
     lib.grace_expert_ffn_up.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_expert_ffn_down.argtypes = [vp, i32, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
+    lib.grace_expert_ffn_down_fresh.argtypes = lib.grace_expert_ffn_down.argtypes
     lib.grace_expert_ffn_up_share.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp]
     lib.grace_expert_ffn_down_share.argtypes = [vp, i32, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp]
     lib.grace_shared_ffn.argtypes = [vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp]
@@ -320,9 +321,19 @@ def grace_expert_ffn(table: GraceTable, rank: int, xp: torch.Tensor, inst_off: t
     for w in (w_gate, w_up, w_down):
         if w.dtype != xp.dtype:
             raise ValueError("weights and activations must share one dtype")
+    ws = _ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, dt), xp.device)
+    if y is None and S > 0 and d * xp.element_size() % 16 == 0:
+        # the down projection's launch zeroes the rows of other ranks (8000 rows of 4 KB, none of them another rank's:
+        # 9 us for a fill of all of them)
+        y = torch.empty((T * k, d), dtype=xp.dtype, device=xp.device)
+        lib = load_library()
+        _check(lib.grace_expert_ffn_up(table.handle, rank, _dp(xp), _dp(inst_off), T, k, d, f, dt, _dp(w_gate), _dp(w_up), _dp(ws),
+                                       _stream()))
+        _check(lib.grace_expert_ffn_down_fresh(table.handle, rank, _dp(inst_off), T, k, d, f, dt, _dp(w_down), _dp(y), _dp(ws),
+                                               _stream()))
+        return y
     if y is None:
         y = torch.zeros((T * k, d), dtype=xp.dtype, device=xp.device)
-    ws = _ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, dt), xp.device)
     _check(load_library().grace_expert_ffn(table.handle, rank, _dp(xp), _dp(inst_off), T, k, d, f, dt,
                                            _dp(w_gate) if S else None, _dp(w_up) if S else None,
                                            _dp(w_down) if S else None, _dp(y), _dp(ws), _stream()))
@@ -341,6 +352,14 @@ def grace_expert_ffn_down(table: GraceTable, rank: int, inst_off: torch.Tensor, 
     S, d, f = w_down.shape
     _check(load_library().grace_expert_ffn_down(table.handle, rank, _dp(inst_off), T, k, d, f, _dtype_code(y),
                                                 _dp(w_down) if S else None, _dp(y), _dp(ws), _stream()))
+
+
+def grace_expert_ffn_down_fresh(table: GraceTable, rank: int, inst_off: torch.Tensor, T: int, k: int, w_down: torch.Tensor,
+                                y: torch.Tensor, ws: torch.Tensor) -> None:
+    """grace_expert_ffn_down that also zeroes the rows of other ranks; see grace_moe.h."""
+    S, d, f = w_down.shape
+    _check(load_library().grace_expert_ffn_down_fresh(table.handle, rank, _dp(inst_off), T, k, d, f, _dtype_code(y),
+                                                      _dp(w_down) if S else None, _dp(y), _dp(ws), _stream()))
 
 
 def grace_expert_ffn_up_share(table: GraceTable, rank: int, xp: torch.Tensor, inst_off: torch.Tensor, T: int, k: int,

@@ -419,7 +419,7 @@ static_assert(SHARE_STATE_INTS == GRACE_SHARE_STATE_INTS, "header and kernels mu
 
 static int expert_ffn_down(const char *who, const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
                            int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state,
-                           void *ws, void *stream) {
+                           bool clear_others, void *ws, void *stream) {
     int g0, S;
     int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
     if (rc != GRACE_OK) return rc;
@@ -428,26 +428,32 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     if ((((uintptr_t)w_down) | ((uintptr_t)y) | ((uintptr_t)ws)) & 15)
         return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
     const size_t el = dt == GRACE_F32 ? 4 : 2;
-    if (state && ((size_t)d * el) % 16 != 0)
+    if ((state || clear_others) && ((size_t)d * el) % 16 != 0)
         return fail(GRACE_ESHAPE, "%s: row of %zu bytes is not a multiple of 16", who, (size_t)d * el);
     GemmArgs dn = expert_shape(false, S, d, f);
     dn.A = ws; dn.B0 = w_down; dn.out = y;
     dn.seg_off = inst_off + g0;
-    dn.share_state = state; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
+    dn.share_state = state; dn.clear_others = clear_others; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
     return launch_gemm<false, pers::EXPERTS>(dn, dt, expert_rows(S, table->I, T, k), (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
                                      int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y,
                                      void *ws, void *stream) {
-    return expert_ffn_down("expert_ffn_down", table, rank, inst_off, T, k, d, f, dt, w_down, y, nullptr, ws, stream);
+    return expert_ffn_down("expert_ffn_down", table, rank, inst_off, T, k, d, f, dt, w_down, y, nullptr, false, ws, stream);
+}
+
+extern "C" int grace_expert_ffn_down_fresh(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
+                                           int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y,
+                                           void *ws, void *stream) {
+    return expert_ffn_down("expert_ffn_down_fresh", table, rank, inst_off, T, k, d, f, dt, w_down, y, nullptr, true, ws, stream);
 }
 
 extern "C" int grace_expert_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
                                            int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y,
                                            int32_t *state, void *ws, void *stream) {
     if (!state) return fail(GRACE_EINVAL, "expert_ffn_down_share: state is null");
-    return expert_ffn_down("expert_ffn_down_share", table, rank, inst_off, T, k, d, f, dt, w_down, y, state, ws, stream);
+    return expert_ffn_down("expert_ffn_down_share", table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream);
 }
 
 extern "C" int grace_expert_ffn(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,

@@ -41,6 +41,7 @@ struct GemmArgs {
     // projection's launch keeps the record, the down projection's launch (a later kernel on the same
     // stream) only reads it: no kernel reads what another workgroup of the same launch writes.
     int32_t *share_state;
+    bool clear_others;      // no record: all rows outside the current range are stale (a buffer never written before)
     int64_t share_rows;     // rows of the whole output buffer
     int share_row_vec;      // 16-byte vectors per output row
     // Row scatter carried along by the launch (null: none): xp[pos[t*k+j]] = x[t], rows of sc_row_bytes
@@ -76,11 +77,15 @@ __device__ __forceinline__ StaleRows stale_rows(const GemmArgs &g) {
         s.prev_hi = g.share_state[1];
         s.now_lo = g.seg_off[0];
         s.now_hi = g.seg_off[g.S];
+    } else if (g.clear_others) {
+        s.prev_hi = (int)g.share_rows;   // T * k, at most 2^31 - 1
+        s.now_lo = g.seg_off[0];
+        s.now_hi = g.seg_off[g.S];
     }
     return s;
 }
 __device__ __forceinline__ void clear_stale_rows(const GemmArgs &g, const StaleRows &s) {
-    if (!g.share_state) return;
+    if (!g.share_state && !g.clear_others) return;
     const int64_t n = g.share_rows;
     const int64_t pl = max((int64_t)0, min(n, (int64_t)s.prev_lo));
     const int64_t ph = max(pl, min(n, (int64_t)s.prev_hi));

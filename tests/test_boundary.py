@@ -99,6 +99,7 @@ def test_null_and_range_checks_without_device():
                                           None, None, None, None, None, None) == -1
     assert lib.grace_expert_ffn_up_share(None, 0, None, None, 1, 1, 8, 8, 1, None, None, None, None, None) == -1
     assert lib.grace_expert_ffn_down_share(None, 0, None, 1, 1, 8, 8, 1, None, None, None, None, None) == -1
+    assert lib.grace_expert_ffn_down_fresh(None, 0, None, 1, 1, 8, 8, 1, None, None, None, None) == -1
     assert lib.grace_send_lists(None, 0, None, 1, 1, None, None, None, None, None, None, None, None) == -1
 
 

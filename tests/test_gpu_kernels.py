@@ -99,6 +99,28 @@ def test_tiles_in_halves(seg_rows, T, k, d, f):
     check_segments(got, want, off, TOL["bf16"])
 
 
+@pytest.mark.parametrize("T,k,d,f,dtype", [(3, 2, 64, 32, "bf16"), (40, 4, 256, 128, "f32"), (130, 4, 200, 72, "bf16"),
+                                           (90, 4, 40, 24, "f32"), (90, 4, 100, 50, "f32"), (3000, 8, 256, 512, "bf16")])
+def test_fresh_output_is_zero_outside_the_rank(T, k, d, f, dtype):
+    """Every kernel's down projection zeroes what it does not compute of a y that holds NaN: rows before, behind and, for an empty
+    rank, all; the rank's rows are those of the call on zeros."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    table = grace.GraceTable(8, 4, 1, [0] * 4, [1] * 4, list(range(9)), [e // 2 for e in range(8)])
+    w = [(torch.randn(s, generator=gen, device="cuda") * 0.1).to(tdt) for s in ((2, f, d), (2, f, d), (2, d, f))]
+    x = torch.randn((T * k, d), generator=gen, device="cuda").to(tdt)
+    cuts = [0, 0, T * k // 5, T * k // 3, T * k // 2, T * k // 2, T * k // 2, T * k - 1, T * k]
+    off = torch.tensor(cuts, dtype=torch.int32, device="cuda")
+    ws = torch.empty(grace.grace_workspace_bytes(T, 8, k, 8, d, f, 0, int(dtype == "bf16")), dtype=torch.uint8, device="cuda")
+    for rank in range(4):
+        want = torch.zeros_like(x)
+        grace.grace_expert_ffn(table, rank, x, off, T, k, *w, y=want)
+        y = torch.full_like(x, float("nan"))
+        grace.grace_expert_ffn_up(table, rank, x, off, T, k, w[0], w[1], ws)
+        grace.grace_expert_ffn_down_fresh(table, rank, off, T, k, w[2], y, ws)
+        assert torch.equal(y, want) and torch.equal(grace.grace_expert_ffn(table, rank, x, off, T, k, *w), want)
+
+
 def test_more_rows_than_a_rank_is_expected_to_hold():
     """The 96-row kernel's grid covers five times an instance's even share; here one of 64 instances holds every row."""
     T, k, d, f, E = 3000, 8, 200, 1032, 64
