@@ -32,11 +32,11 @@ KERNEL_OF_STAGE = {
     "ffn_down": "gemm_bf16_persist_kernel<false, *, EXPERTS> (grouped down projection)",
     "shared_up": "gemm_bf16_persist_kernel<true, 1, SHARED> (shared experts' gate+up projection, fused SwiGLU; carries the row scatter)",
     "shared_down": "gemm_bf16_persist_kernel<false, 1, SHARED> (shared experts' down projection)",
-    "combine": "combine_kernel (weighted gather to token order)",
-    "route_permute": "topk + pick + positions + scatter_rows_kernel (one call; the row scatter moves the bytes)",
+    "combine": "combine_share_kernel (weighted gather of the rank's rows to token order)",
+    "route_permute": "topk + pick + positions + scatter_rows_kernel (one call; the row scatter moves the bytes), one kernel for the smallest batches",
 }
 # the projections where the library chooses another kernel than the large tiles for the batch
-OTHER_KERNEL = {"stream": "gemm_stream kernel", "mid": "gemm_bf16_mid_kernel", "generic": "gemm_bf16_kernel",
+OTHER_KERNEL = {"stream": "gemm_stream kernel", "mid": "gemm_bf16_mid_kernel / gemm_f32_mid_kernel", "generic": "gemm_bf16_kernel",
                 "vector_f32": "gemm_f32_kernel"}
 
 

@@ -189,9 +189,10 @@ int grace_permute_rows(const void *x, const int32_t *perm_pos, int32_t T, int32_
  * Same arguments, outputs (bit for bit) and errors as grace_route (Section 3,
  * Section 4.3, Algorithms 3 and 4) followed by grace_permute (Section 5) on its
  * topk_inst, with fewer kernel launches.  Decode-sized batches, which are bound
- * by launch latency, are handled by the top-k kernel, one single-workgroup
- * kernel and the row scatter instead of five launches: that path is taken when
- * ceil(T / 16) * k <= 256, E <= 256 and the table has at most 256 instances.
+ * by launch latency, take one launch (T <= 96, 256 with k <= 2, 32 with more than
+ * 64 experts; T * k <= 1024), or the top-k kernel, one single-workgroup kernel
+ * and the row scatter instead of five launches (ceil(T / 16) * k <= 256); both
+ * with E <= 256 and at most 256 instances in the table.
  * For every other size the replica pick also produces the histograms the
  * permutation starts from, which saves one launch.  The workspace holds the
  * routing and the permutation histograms side by side during this call
@@ -373,8 +374,8 @@ int grace_mfma_sustained(int32_t random_operands, int32_t lds_fed, double *tflop
  * these sizes alone.  up: 1 for the gate+up projection, 0 for the down projection.  n_cu: compute units (0: of the
  * current device; no device is touched otherwise).  HOST outputs. */
 typedef enum {
-    GRACE_KERNEL_STREAM = 0,     /* weights streamed, few rows per segment; fp32 of any size */
-    GRACE_KERNEL_MID = 1,        /* 96-row pieces x 128 weight rows */
+    GRACE_KERNEL_STREAM = 0,     /* weights streamed, few rows per segment; fp32 of any size if N % 4 != 0 */
+    GRACE_KERNEL_MID = 1,        /* pieces of up to 96 rows x 128 (fp32: 64) weight rows */
     GRACE_KERNEL_PERSIST = 2,    /* 256 x 256 tiles, one workgroup per compute unit */
     GRACE_KERNEL_GENERIC = 3,    /* 128 x 128 tiles: K no multiple of 64 and operands past 2 GB, or too many work-items */
     GRACE_KERNEL_VECTOR_F32 = 4  /* fp32 on the vector ALUs: rows that are no whole 16-byte vectors */

@@ -13,7 +13,7 @@
 //   2. replica pick        Algorithm 4 tier + weighted round-robin, per wavefront in order
 //   3. offsets             per instance / rank / node, scan of the per-wavefront instance counts
 //   4. positions           stable rank of every assignment in (node, rank, slot) order (Section 5)
-// and by the row scatter: three launches.
+// and by the row scatter: three launches.  Still smaller ones take a single launch (route_permute_tiny_kernel).
 // Outputs are identical either way (all integer work is exact and order-independent).
 #include <mutex>
 #include <type_traits>
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
     __shared__ int32_t ecnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // requests per expert of a wavefront, then before it
     __shared__ int32_t icnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // rows per instance of a wavefront, then before it
     __shared__ int32_t asg[TINY_MAX_ASG], where[TINY_MAX_ASG]; // expert of every assignment; its position
-    __shared__ int32_t first[SMALL_MAX_KEYS], count[SMALL_MAX_KEYS], only[SMALL_MAX_KEYS];   // candidates of an expert; the first one
+    __shared__ int32_t count[SMALL_MAX_KEYS], only[SMALL_MAX_KEYS];   // candidates of an expert; the first one
     __shared__ uint32_t weight_sum[SMALL_MAX_KEYS], rr[SMALL_MAX_KEYS];
     __shared__ int32_t ioff[SMALL_MAX_KEYS + 1];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, threads = (int)blockDim.x, waves = threads >> 6;
@@ -262,7 +262,6 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
         }
     }
     if (tid < E) {
-        first[tid] = cb;
         count[tid] = ce - cb;
         only[tid] = cand_g[cb];
         weight_sum[tid] = cand_cum[ce - 1];
