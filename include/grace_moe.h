@@ -285,8 +285,8 @@ int grace_expert_ffn_down(const grace_table *table, int32_t rank, const int32_t 
                           int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, void *ws, void *stream);
 
 /* grace_expert_ffn_down that also writes the rows of other ranks, as zeros, inside its own launch: for a y that holds
- * nothing yet.  d * sizeof(dt) must be a multiple of 16; when `rank` hosts no instance nothing is launched and y is not
- * written. */
+ * nothing yet.  d * sizeof(dt) must be a multiple of 16.  When `rank` hosts no instance all of y is zeroed and inst_off,
+ * w_down and ws are not read. */
 int grace_expert_ffn_down_fresh(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k,
                                 int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, void *ws,
                                 void *stream);

@@ -27,6 +27,11 @@
 
 namespace grace {
 
+// Zeroes n 16-byte vectors (a kernel, not a memset: the call may be captured into a graph).
+__global__ __launch_bounds__(256) void zero_fill_kernel(uint4 *__restrict__ out, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // Compute units of the current device (cached per device).
 static int compute_units() {
     static int cached[64] = {0};
@@ -423,13 +428,19 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     int g0, S;
     int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
     if (rc != GRACE_OK) return rc;
-    if (S == 0 || T == 0) return GRACE_OK;
-    if (!inst_off || !w_down || !y || !ws) return fail(GRACE_EINVAL, "%s: null device pointer", who);
+    if (T == 0 || (S == 0 && !clear_others)) return GRACE_OK;
+    if (!y || (S > 0 && (!inst_off || !w_down || !ws))) return fail(GRACE_EINVAL, "%s: null device pointer", who);
     if ((((uintptr_t)w_down) | ((uintptr_t)y) | ((uintptr_t)ws)) & 15)
         return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
     const size_t el = dt == GRACE_F32 ? 4 : 2;
     if ((state || clear_others) && ((size_t)d * el) % 16 != 0)
         return fail(GRACE_ESHAPE, "%s: row of %zu bytes is not a multiple of 16", who, (size_t)d * el);
+    if (S == 0) {   // every row is another rank's
+        const int64_t n = (int64_t)T * k * (int64_t)((size_t)d * el / 16);
+        zero_fill_kernel<<<(unsigned)std::min<int64_t>((n + 255) / 256, 4096), 256, 0, (hipStream_t)stream>>>((uint4 *)y, n);
+        GRACE_LAUNCH_CHECK(who);
+        return GRACE_OK;
+    }
     GemmArgs dn = expert_shape(false, S, d, f);
     dn.A = ws; dn.B0 = w_down; dn.out = y;
     dn.seg_off = inst_off + g0;

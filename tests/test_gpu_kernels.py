@@ -121,6 +121,27 @@ def test_fresh_output_is_zero_outside_the_rank(T, k, d, f, dtype):
         assert torch.equal(y, want) and torch.equal(grace.grace_expert_ffn(table, rank, x, off, T, k, *w), want)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,k,d,f", [(1, 1, 8, 8), (37, 3, 136, 64), (3000, 8, 2048, 64)])
+def test_rank_without_instances_gives_zeros(T, k, d, f, dtype):
+    """A table may leave a rank without instances; its call then has nothing to read of the weights, which need not be empty, and
+    all rows are other ranks'.  The buffer that torch hands out here held NaN."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    table = grace.GraceTable(2, 3, 1, [0] * 3, [1] * 3, [0, 1, 2], [0, 2])
+    assert len(table.local_experts(1)) == 0
+    off = torch.tensor([0, T * k // 2, T * k], dtype=torch.int32, device="cuda")
+    x = torch.ones((T * k, d), dtype=tdt, device="cuda")
+    w = [torch.ones(s, dtype=tdt, device="cuda") for s in ((1, f, d), (1, f, d), (1, d, f))]
+    ws = torch.empty(grace.grace_workspace_bytes(T, 2, k, 2, d, f, 0, int(dtype == "bf16")), dtype=torch.uint8, device="cuda")
+    y = torch.full_like(x, float("nan"))
+    grace.grace_expert_ffn_down_fresh(table, 1, off, T, k, w[2], y, ws)
+    assert torch.equal(y, torch.zeros_like(y))
+    torch.cuda.empty_cache()
+    held = torch.full_like(x, float("nan"))
+    del held
+    assert torch.equal(grace.grace_expert_ffn(table, 1, x, off, T, k, *w, ws=ws), torch.zeros_like(x))
+
+
 def test_more_rows_than_a_rank_is_expected_to_hold():
     """The 96-row kernel's grid covers five times an instance's even share; here one of 64 instances holds every row."""
     T, k, d, f, E = 3000, 8, 200, 1032, 64
