@@ -152,11 +152,12 @@ static Grid mid_f32_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
     const int64_t expected = rows.even_only ? rows.m_bound : rows.at(20);
     return {(std::max<int64_t>((expected / midf::BM + g.S) * n_strips, n_cu) + 63) / 64 * 64, midf::THREADS};
 }
-// All tiles of the rows that a rank could hold are numbered in 32 bits.
+// All tiles of the rows that a rank could hold, in whole runs of the XCDs, are one launch at most: their numbers fit 32 bits and so
+// does every grid above (a hot rank's are walked by fewer workgroups).
 template <bool FUSED_UP, typename SHAPE>
 static bool mid_tiles_fit(const GemmArgs &g, const Rows &rows) {
     const int64_t n_strips = (g.N + SHAPE::BN - 1) / SHAPE::BN;
-    return launchable({(rows.m_bound / mid::BM + g.S) * n_strips, mid::THREADS});
+    return launchable({((rows.m_bound / mid::BM + g.S) * n_strips + 63) / 64 * 64, mid::THREADS});
 }
 template <bool FUSED_UP>
 static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {

@@ -16,6 +16,10 @@ F32, BF16 = grace.GRACE_F32, grace.GRACE_BF16
     (True, 32768, 6, 2048, 1408, 2, 1, 1, BF16),          # ordinary ones
     (False, 1, 8, 2048, 1024, 0, 18, 72, BF16),
     (True, 1000, 2, 1024, 2816, 0, 8, 16, F32),
+    (True, 96 * 5592403, 1, 72, 192, 1, 1, 1, BF16),      # 2^24 - 7 tiles: 2^32 work-items once they are rounded up to whole runs
+    (True, 96 * 5592403, 1, 72, 192, 0, 1, 1, BF16),
+    (True, 96 * 5592403, 1, 64, 96, 1, 1, 1, F32),
+    (False, 96 * 5592403, 1, 384, 72, 0, 1, 1, BF16),
 ])
 def test_launch_fits_32_bits_of_work_items(up, T, k, d, f, n_shared, S, I, dt):
     """HIP refuses a launch of 2^32 work-items or more along one axis."""
