@@ -221,6 +221,23 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
     return (m / mid::BM + hit) * strips <= n_cu * rounds * (FUSED_UP ? 3 : 2);
 }
 
+// fp32, batches of more than 64 tokens: the 96-row kernel against the streaming kernel, whose pieces of 64 rows and 32 weight rows
+// are a third of its tiles.  Long launches are faster on the 96-row kernel; with few tiles per compute unit that depends on
+// how the rank's rows fall into them, which the host does not know.  Measured over 1332 expert FFNs, each kernel alone (8 to 128
+// experts on 1 to 4 ranks, Zipf-shaped shares, 65 to 5000 tokens, k = 2 and 8, d x f from 128 x 256 to 2048 x 2048, also 548 and
+// 1388, whose rows are no whole lines), and 234 of shared experts:
+//  * five tiles per compute unit at the even share and K of 20 steps or more: streaming 66.3 ms, 96 rows 57.1 ms, in 170 expert
+//    projections and 23 of shared experts none slower by more than 1 %;
+//  * gate+up of fewer tiles, but with 8 or more segments, N >= 2048 and K >= 1024: 21.0 -> 16.5 ms in 129, five slower by 3
+//    to 11 %; with fewer segments 4.6 -> 4.4 ms in 60, ten slower by up to 14 %;
+//  * the other 2365: 0.47 to 1.69 times as fast, 832 faster and 1125 slower by more than 3 %.
+template <bool FUSED_UP>
+static bool mid_f32_is_faster(const GemmArgs &g, const Rows &rows, int n_cu) {
+    const int64_t strips = (g.N + midf::Shape<FUSED_UP>::BN - 1) / midf::Shape<FUSED_UP>::BN;
+    if (g.K < 20 * midf::BK) return false;
+    return rows.at(4) * strips >= (int64_t)5 * n_cu * midf::BM || (FUSED_UP && g.S >= 8 && g.N >= 2048 && g.K >= 1024);
+}
+
 // bf16, up to 64 rows per segment: the streaming kernel, which splits the work finest, while the 96-row kernel's tiles
 // would not fill the chip.  A gate+up projection of more than 16 rows leaves it when the other has a tile for three quarters
 // of the compute units (above that line it takes 0.9 to 1.8 of the 96-row kernel's time, 1.0 to 1.3 in the middle), a down
@@ -233,10 +250,12 @@ template <bool FUSED_UP>
 static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };
     if (dt == GRACE_F32) {
-        // more rows per segment than one workgroup of the streaming kernel takes at a time; output rows of 16-byte vectors
-        if (rows.max_rows > strm::MAX_ROWS && g.N % 4 == 0 && stream_ok<4>(g, 4) && mid_tiles_fit<FUSED_UP, midf::Shape<FUSED_UP>>(g, rows))
-            return Route::MID;
-        return stream_ok<4>(g) && fits(Route::STREAM) ? Route::STREAM : Route::VECTOR_F32;
+        const bool stream = stream_ok<4>(g) && fits(Route::STREAM);
+        // output rows of whole 16-byte vectors; K segments of any length (shared experts' down projection, f = 1388, two of them, d =
+        // 1024, 65 to 5000 tokens: vector ALUs 329 to 577 us, 96 rows 38 to 289 us)
+        const bool mid = rows.max_rows > strm::MAX_ROWS && g.N % 4 == 0 && stream_ok<4>(g, 4) && mid_tiles_fit<FUSED_UP, midf::Shape<FUSED_UP>>(g, rows);
+        if (mid && (!stream || mid_f32_is_faster<FUSED_UP>(g, rows, n_cu))) return Route::MID;
+        return stream ? Route::STREAM : Route::VECTOR_F32;
     }
     const bool mid_ok = stream_ok<2>(g, 8) && mid_tiles_fit<FUSED_UP, mid::Shape<FUSED_UP>>(g, rows);
     if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM)) {

@@ -1,5 +1,6 @@
-// fp32 grouped GEMM on the matrix cores (v_mfma_f32_16x16x4_f32: full fp32 products and sums) for more than 64 rows per segment:
-// 96 rows x 64 weight rows per workgroup, K a multiple of 4.
+// fp32 grouped GEMM on the matrix cores (v_mfma_f32_16x16x4_f32: full fp32 products and sums) for long launches of batches of
+// more than 64 tokens: 96 rows x 64 weight rows per workgroup, K a multiple of 4.  Short ones, whose few tiles leave units idle
+// or waiting for the last, are faster on the streaming kernel (mid_f32_is_faster in ffn.hip).
 //
 // The same staging as gemm_bf16_mid.h: whole 128-byte lines into registers AHEAD steps ahead, then one of two LDS
 // buffers, one barrier per step of 32 K.  A lane reads 16 bytes, four consecutive K, of a row and four MFMAs take one of them each (K

@@ -1,5 +1,5 @@
 // MFMA grouped GEMM that reads both operands straight into registers: few rows per segment (decode batches, bf16 and
-// fp32), and larger fp32 batches whose output rows are no whole 16-byte vectors (gemm_f32_mid.h takes the others).
+// fp32), and fp32 of any size whose launch is not long enough for gemm_f32_mid.h or whose output rows are no whole 16-byte vectors.
 //
 // A workgroup owns 32 weight rows of one segment (gate+up: 16 of each matrix, i.e. 16 output columns; down: 32
 // columns) and up to 64 of the segment's rows, and its wavefronts split K, so that the 32 weight rows, which lie

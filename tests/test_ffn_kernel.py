@@ -70,3 +70,21 @@ def test_shared_projection_keeps_the_row_scatter(T, d, f, n_shared):
 ])
 def test_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
     assert grace.grace_ffn_kernel(up, T, d, f, BF16, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU)[0] == want
+
+
+@pytest.mark.parametrize("up,T,k,d,f,n_shared,S,I,want", [
+    # streaming kernel / 96-row kernel, us
+    (True, 2000, 8, 2048, 768, 0, 4, 8, "mid"),          # 524 / 428: more than five tiles per compute unit
+    (False, 2000, 8, 2048, 768, 0, 4, 8, "mid"),         # 279 / 231
+    (False, 5000, 1, 2048, 768, 1, 1, 1, "mid"),         # 180 / 150
+    (True, 500, 8, 1024, 2816, 0, 16, 64, "mid"),        # 191 / 152: gate+up of many segments, wide and long
+    (False, 500, 8, 1024, 2816, 0, 16, 64, "stream"),    # 92.5 / 135
+    (True, 200, 8, 2048, 768, 0, 4, 8, "stream"),        # 68.5 / 93.9
+    (True, 500, 2, 548, 1388, 0, 16, 16, "stream"),      # 58.8 / 62.6
+    (True, 1000, 1, 2048, 768, 1, 1, 1, "stream"),       # 69.8 / 106
+    (False, 1000, 1, 2048, 2048, 2, 1, 1, "stream"),     # 177 / 211
+    (False, 65, 1, 1024, 1388, 2, 1, 1, "mid"),          # vector ALUs 329 / 37.5: K segments of 1388 are not for the streaming kernel
+    (False, 64, 1, 1024, 1388, 2, 1, 1, "vector_f32"),
+])
+def test_f32_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
+    assert grace.grace_ffn_kernel(up, T, d, f, F32, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU)[0] == want

@@ -142,25 +142,21 @@ def test_rank_without_instances_gives_zeros(T, k, d, f, dtype):
     assert torch.equal(grace.grace_expert_ffn(table, 1, x, off, T, k, *w, ws=ws), torch.zeros_like(x))
 
 
-def test_more_rows_than_a_rank_is_expected_to_hold():
-    """The 96-row kernel's grid covers five times an instance's even share; here one of 64 instances holds every row."""
-    T, k, d, f, E = 3000, 8, 200, 1032, 64
-    rng = np.random.default_rng(1)
-
-    def normal(scale, *shape):
-        return torch.from_numpy((scale * rng.standard_normal(shape)).astype(np.float32)).cuda().bfloat16()
-
-    table = grace.GraceTable(E, E, 1, [0] * E, [1] * E, list(range(E + 1)), list(range(E)))
-    assert kernels_of(T, k, d, f, 1, E) == ("mid", "mid")
-    assert grace.grace_ffn_kernel(True, T, d, f, k=k, S=1, I=E)[1] < (T // 96) * 17 * 256     # fewer workgroups than tiles
-    w = normal(0.05, 1, f, d), normal(0.05, 1, f, d), normal(0.05, 1, d, f)
-    x = normal(1.0, T * k, d)
-    off = np.full(E + 1, T * k, dtype=np.int32)
-    off[:6] = 0
-    y = grace.grace_expert_ffn(table, 5, x, torch.from_numpy(off).cuda(), T, k, *w)
-    rows = rng.permutation(T * k)[:600]
-    want = oracle.ffn_rows(oracle.widen(host(x[rows])), *(oracle.widen(host(m[0])) for m in w), threads=8)
-    assert rel_err(oracle.widen(host(y[rows])), want) <= TOL["bf16"]
+@pytest.mark.parametrize("T,k,d,f,S,dtype,up,bn", [
+    (3000, 8, 200, 1032, 1, "bf16", True, 64),
+    (3000, 8, 200, 1032, 1, "bf16", False, 128),
+    (200, 8, 1024, 2048, 8, "f32", True, 32),
+    (1000, 8, 8192, 640, 8, "f32", False, 64),
+])
+def test_more_rows_than_a_rank_is_expected_to_hold(T, k, d, f, S, dtype, up, bn):
+    """The 96-row kernels' grids cover five times a rank's even share; here one rank of many holds every row, so that workgroups
+    take several tiles."""
+    dt = grace.GRACE_F32 if dtype == "f32" else grace.GRACE_BF16
+    seg_rows = [T * k // S] * S
+    kernel, items = grace.grace_ffn_kernel(up, T, d, f, dt, k=k, S=S, I=64)
+    strips = -(-(f if up else d) // bn)
+    assert kernel == "mid" and items < S * -(-seg_rows[0] // 96) * strips * 256     # fewer workgroups than tiles
+    ffn_rows_of_segments(seg_rows, T, k, d, f, dtype, first=8, I=64, S=S)
 
 
 def test_up_projection_of_decode_batches():
@@ -177,19 +173,66 @@ def test_large_tiles():
     check_segments(got, want, off, TOL["bf16"])
 
 
-@pytest.mark.parametrize("seg_rows,T,k,d,f", [
-    ([1, 0, 2], 3, 1, 1024, 256),                   # few rows: one workgroup per strip and segment
-    ([40, 0, 25], 64, 2, 100, 76),                  # K of 6 whole steps and 4 left over; strips past N
-    ([65, 64, 0, 1], 65, 2, 128, 256),              # pieces: 65 rows in two, one full, one row
-    ([0, 130, 17, 300], 300, 2, 548, 1388),         # pieces of one, two and three fragments with ragged ends
-    ([33, 97], 100, 2, 36, 77),                     # odd N up; the down projection's K takes the vector kernel
-    ([1] * 70 + [80] * 3, 160, 2, 64, 32),          # more segments than lanes
-    ([1, 0] * 40, 40, 1, 64, 48),                   # the same with one workgroup per strip and segment
+@pytest.mark.parametrize("seg_rows,T,k,d,f,want", [
+    ([1, 0, 2], 3, 1, 1024, 256, ("stream", "stream")),          # few rows: one workgroup per strip and segment
+    ([40, 0, 25], 64, 2, 100, 76, ("stream", "stream")),         # K of 6 whole steps and 4 left over; strips past N
+    ([65, 64, 0, 1], 65, 2, 128, 256, ("stream", "stream")),     # pieces: 65 rows in two, one full, one row
+    ([0, 130, 17, 300], 300, 2, 548, 1388, ("stream", "stream")),   # pieces of one, two and three fragments with ragged ends
+    ([33, 97], 100, 2, 36, 77, ("stream", "vector_f32")),        # odd N up; the down projection's K takes the vector kernel
+    ([33, 97], 100, 2, 34, 64, ("vector_f32", "stream")),        # odd N down
+    ([1] * 70 + [80] * 3, 160, 2, 64, 32, ("stream", "stream")),    # more segments than lanes
+    ([1] * 70 + [80] * 3, 160, 2, 36, 77, ("stream", "vector_f32")),
+    ([1, 0] * 40, 40, 1, 64, 48, ("stream", "stream")),          # the same with one workgroup per strip and segment
 ])
-def test_f32_segments(seg_rows, T, k, d, f):
-    """fp32 on the matrix cores: one workgroup per strip (at most 64 tokens) or per strip and piece of a segment."""
-    got, want, off = ffn_of_segments(seg_rows, T, k, d, f, torch.float32)
-    check_segments(got, want, off, TOL["f32"])
+def test_f32_segments(seg_rows, T, k, d, f, want):
+    """fp32 streaming kernel: one workgroup per strip (at most 64 tokens) or per strip and piece of a segment."""
+    assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows), dtype="f32") == want
+    got, ref, off = ffn_of_segments(seg_rows, T, k, d, f, torch.float32)
+    check_segments(got, ref, off, TOL["f32"])
+
+
+def ffn_rows_of_segments(seg_rows, T, k, d, f, dt, first=0, I=None, S=None):
+    """Expert FFN of the rank that hosts instances `first` .. `first + S - 1` of I, all segments of that rank, and the oracle's
+    result for some rows of each segment: both ends, the first pieces' edges and a few more."""
+    S, I = S or len(seg_rows), I or len(seg_rows)
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(sum(seg_rows))
+    rng = np.random.default_rng(sum(seg_rows))
+
+    def normal(scale, *shape):
+        return (scale * torch.randn(shape, generator=gen, device="cuda")).to(tdt)
+
+    R = I // S
+    table = grace.GraceTable(I, R, 1, [0] * R, [1] * R, list(range(I + 1)), [e // S for e in range(I)])
+    w = normal(0.05, S, f, d), normal(0.05, S, f, d), normal(0.05, S, d, f)
+    x = normal(1.0, T * k, d)
+    off = np.zeros(I + 1, dtype=np.int32)
+    off[first + 1:first + S + 1] = np.cumsum(seg_rows)
+    off[first + S + 1:] = off[first + S]
+    y = grace.grace_expert_ffn(table, first // S, x, torch.from_numpy(off).cuda(), T, k, *w)
+    assert not y[int(off[first + S]):].any()
+    for s in range(S):
+        lo, hi = int(off[first + s]), int(off[first + s + 1])
+        if hi == lo:
+            continue
+        rows = np.unique(np.clip([lo, hi - 1, lo + 15, lo + 16, lo + 95, lo + 96, *(lo + rng.integers(0, hi - lo, 10))], lo, hi - 1))
+        ref = oracle.ffn_rows(oracle.widen(host(x[rows])), *(oracle.widen(host(m[s])) for m in w), threads=8)
+        assert rel_err(oracle.widen(host(y[rows])), ref) <= TOL[dt], (s, lo, hi)
+
+
+@pytest.mark.parametrize("seg_rows,T,k,d,f,want", [
+    ([1, 0, 17, 33, 49, 65, 81, 96], 96, 8, 1024, 2048, ("mid", "stream")),    # pieces of one to six fragments
+    ([1, 0, 0, 0, 0, 0, 0, 2], 65, 2, 1028, 2052, ("mid", "stream")),          # few tiles: pieces of 16; K and N off the steps
+    ([40, 0, 0, 0, 0, 0, 0, 24], 65, 2, 1024, 2048, ("mid", "stream")),        # of 32
+    ([130, 0, 0, 0, 0, 0, 0, 0], 130, 2, 1024, 2048, ("mid", "stream")),       # of 64
+    ([300, 0, 0, 0, 0, 0, 50, 0], 300, 2, 1024, 2048, ("mid", "stream")),      # more tiles than compute units: of 96
+    ([0, 3000, 1, 97, 1500, 95, 700, 807], 3100, 2, 1284, 644, ("mid", "mid")),    # long launches; K and N off the steps and strips
+    ([0, 1, 95, 96, 97] * 14 + [2154], 6200, 1, 1280, 640, ("mid", "mid")),    # more segments than lanes
+])
+def test_f32_long_launches(seg_rows, T, k, d, f, want):
+    """fp32 in tiles of 96 rows and 64 weight rows."""
+    assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows), dtype="f32") == want
+    ffn_rows_of_segments(seg_rows, T, k, d, f, "f32")
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
