@@ -230,8 +230,8 @@ __device__ __forceinline__ int of_runs(int b, int count) {
 // Workgroups of the largest launch that `tiles` or fewer tiles make: the tiles, or one per compute unit and the others halved;
 // few tiles are cut until there is about one per compute unit.  exact: there are that many.
 inline int64_t grid_blocks(int64_t tiles, int n_cu, bool exact) {
-    if (exact && tiles >= 2 * (int64_t)n_cu) return (tiles + 63) / 64 * 64;
-    const int64_t halves = 2 * std::min<int64_t>(std::max<int64_t>(tiles - n_cu, 0), n_cu);
+    if (exact && 2 * tiles > 3 * (int64_t)n_cu) return (tiles + 63) / 64 * 64;
+    const int64_t halves = std::min<int64_t>(2 * std::max<int64_t>(tiles - n_cu, 0), n_cu);
     return std::max((tiles + 63) / 64 * 64, (n_cu + 63) / 64 * 64 + (halves + 63) / 64 * 64);
 }
 
@@ -245,7 +245,9 @@ inline int64_t grid_blocks(int64_t tiles, int n_cu, bool exact) {
 // 38 us).  The tiles past one per unit are then cut in halves of 64 weight rows, a workgroup each.  Segments as a decode
 // batch of 512 has them (16 segments, d = 2048, f = 1024, 1026 rows, 368 tiles), gate+up 36.7 -> 32.1 us, down 22.9 -> 20.2 us; 264
 // tiles of f = 768 41.6 -> 32.3 us; shared experts' gate+up of 3001 rows, 352 tiles 36.0 -> 29.0 us.  Half tiles for all (672
-// instead of 336) read the rows twice as often: 39.7 -> 39.9 us.
+// instead of 336) read the rows twice as often: 39.7 -> 39.9 us.  Up to one and a half tiles per unit, where tiles and halves still run
+// all at once, two workgroups to a unit: shared experts' gate+up, whole -> halved, 384 tiles of d = 2048 34.5 -> 29.0 us, 396 33.6 ->
+// 40.0 us, 432 34.0 -> 47.4 us, 448 of d = 4096 60.9 -> 82.7 us.
 //
 // Few tiles leave units without work, and a step's time falls with the bytes that its workgroup loads: up to one tile for every
 // other unit all are halved (110 tiles, d = 2048, f = 1408, gate+up 22.5 -> 17.4 us, 80 tiles down 16.7 -> 12.3 us), and pieces are
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArg
             if (2 * segs.count(32) * n_strips <= n_cu) segs.cut(lane, 32);
             else if (2 * segs.count(48) * n_strips <= n_cu) segs.cut(lane, 48);
         }
-        const int total = segs.total * n_strips, whole = few ? 0 : total > n_cu && total < 2 * n_cu ? n_cu : total;
+        const int total = segs.total * n_strips, whole = few ? 0 : total > n_cu && 2 * total <= 3 * n_cu ? n_cu : total;
         const int whole_blocks = (whole + 63) & ~63;
         if (b >= whole_blocks + ((2 * (total - whole) + 63) & ~63)) break;
         const int half = b < whole_blocks ? -1 : of_runs(b - whole_blocks, 2 * (total - whole));

@@ -27,6 +27,13 @@ def test_launch_fits_32_bits_of_work_items(up, T, k, d, f, n_shared, S, I, dt):
     assert 0 < items < 2 ** 32, (kernel, items)
 
 
+@pytest.mark.parametrize("tiles", [1, 64, 192, 256, 257, 352, 384, 385, 396, 432, 448, 511, 512])
+def test_tiles_of_the_shared_experts_run_all_at_once(tiles):
+    """Up to two 96-row tiles per compute unit: whole or in part halved, not more workgroups than the units take at a time."""
+    kernel, items = grace.grace_ffn_kernel(True, 96 * tiles - 5, 72, 64, BF16, n_shared=1, n_cu=N_CU)
+    assert kernel == "mid" and tiles * 256 <= items <= 2 * N_CU * 256
+
+
 def test_invalid_arguments_are_refused():
     for bad in (dict(T=0), dict(k=0), dict(S=0), dict(S=3, I=2), dict(d=12), dict(n_shared=-1), dict(n_cu=-1)):
         a = {**dict(T=4, d=64, f=64, k=1, S=1, I=1, n_shared=0, n_cu=N_CU), **bad}

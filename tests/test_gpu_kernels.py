@@ -81,7 +81,9 @@ def test_ordinary_batches(seg_rows, T, k, d, f):
 @pytest.mark.parametrize("seg_rows,T,k,d,f", [
     ([96 * 256], 24576, 1, 72, 64),                 # a tile per compute unit: none is cut
     ([96 * 256 + 1], 24577, 1, 72, 64),             # one tile of one row in halves; the down projection's second half past N
-    ([96 * 511 - 40], 49016, 1, 72, 40),            # all but one of the second ones; gate+up halves of 32 and 8 columns
+    ([96 * 384 - 40], 36824, 1, 72, 40),            # the second ones of half the units; gate+up halves of 32 and 8 columns
+    ([96 * 384 + 1], 36865, 1, 72, 64),             # one more: none is cut
+    ([96 * 511 - 40], 49016, 1, 72, 40),            # nor with all but one of the second ones
     ([96 * 512], 49152, 1, 72, 64),                 # two tiles each: none is cut
     ([1, 96, 97, 0, 50, 33, 32, 16] * 2 + [70, 64, 17, 200], 200, 20, 2056, 968),   # ragged last strips, 340 and 357 tiles
     ([3, 0, 40, 90, 17] * 26, 90, 44, 264, 136),    # more segments than lanes
@@ -92,8 +94,8 @@ def test_ordinary_batches(seg_rows, T, k, d, f):
     ([33, 0, 31, 65, 1], 66, 2, 1032, 328),         # of 32; half strips past N in both projections
 ])
 def test_tiles_in_halves(seg_rows, T, k, d, f):
-    """Between one and two tiles per compute unit of a 256-unit GPU: those past the first per unit are halved.  Few tiles: all
-    are, in pieces of 32, 48 or 96 rows."""
+    """Between one tile and one and a half per compute unit of a 256-unit GPU: those past the first per unit are halved.  Few
+    tiles: all are, in pieces of 32, 48 or 96 rows."""
     assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows)) == ("mid", "mid")
     got, want, off = ffn_of_segments(seg_rows, T, k, d, f)
     check_segments(got, want, off, TOL["bf16"])
