@@ -177,11 +177,16 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_f32_mid_kernel(const GemmArgs
             else if (segs.count(64) * n_strips <= n_cu) segs.cut(lane, 64);
         }
         const int total = segs.total * n_strips;
-        if (b >= ((total + 63) & ~63)) break;
+        const int blocks = (total + 63) & ~63;
+        if (b >= blocks) break;
         const int t = mid::of_runs(b, total);
         const bool again = b >= (int)gridDim.x;
         b += (int)gridDim.x;
-        if (t < 0) continue;
+        const bool more = b < blocks;
+        if (t < 0) {
+            if (more) continue;
+            break;
+        }
         const Segment s = segs.segment(t / n_strips, lane);
         const int in_seg = t - s.first_tile * n_strips, strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
         const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
@@ -197,6 +202,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_f32_mid_kernel(const GemmArgs
             case 6: tile_body<FUSED_UP, SEG_K, 6>(g, s.slot, m0, m_end, n0, first_step, smem); break;
             default: break;   // no rows
         }
+        if (!more) break;
     }
     if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
 }
