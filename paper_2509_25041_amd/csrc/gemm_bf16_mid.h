@@ -253,6 +253,8 @@ inline int64_t grid_blocks(int64_t tiles, int n_cu, bool exact) {
 // other unit all are halved (110 tiles, d = 2048, f = 1408, gate+up 22.5 -> 17.4 us, 80 tiles down 16.7 -> 12.3 us), and pieces are
 // cut to 32 or 48 rows while there is a unit for each half (591 rows in two segments, f = 352, gate+up 22.5 -> 12.7 us; 64 rows
 // of d = 4096, f = 14336, down 114 -> 60 us).  More halves than units are slower again (308 of 32 rows 16.0 us, 220 of 48 rows 15.0 us).
+// With fewer than four steps along K there is too little to cut: K = 128, 64 tiles of 4 to 16 segments whole 5.5, halved 6.7 us (K = 256, 48
+// tiles 7.0 -> 5.9 us).
 template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE>
 __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArgs g, int n_strips, int n_cu) {
     __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
@@ -264,7 +266,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArg
         SegTable<SEG_PER_LANE> segs;
         segs.load(g, lane);
         segs.cut(lane, BM);
-        const bool few = 2 * segs.total * n_strips <= n_cu;
+        const bool few = g.K >= 4 * BK && 2 * segs.total * n_strips <= n_cu;
         if (few) {
             if (2 * segs.count(32) * n_strips <= n_cu) segs.cut(lane, 32);
             else if (2 * segs.count(48) * n_strips <= n_cu) segs.cut(lane, 48);
