@@ -311,6 +311,21 @@ def test_combine_share_is_combine_of_zero_rows(T, k, d, dtype, lo, hi, shared):
     torch.testing.assert_close(got, want, rtol=0, atol=0, equal_nan=True)
 
 
+@pytest.mark.parametrize("R", [1, 2])
+def test_combine_of_a_layer_that_hosts_every_instance(R):
+    """Nothing to leave out: grace_combine, with the bits of grace_combine_share."""
+    T, E, k, d, f = 33, 8, 2, 72, 40
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    table = grace.GraceTable(E, R, 1, [0] * R, [1] * R, list(range(E + 1)), [e * R // E for e in range(E)])
+    S = E // R
+    w = [(torch.randn(s, generator=gen, device="cuda") * 0.1).bfloat16() for s in ((S, f, d), (S, f, d), (S, d, f))]
+    layer = grace.GraceMoELayer(table, 0, T, k, d, f, torch.bfloat16, *w)
+    out = layer.forward(torch.randn((T, E), generator=gen, device="cuda"), torch.randn((T, d), generator=gen, device="cuda").bfloat16())
+    lib = grace.load_library()
+    assert layer._calls[-1][1] is (lib.grace_combine if R == 1 else lib.grace_combine_share)
+    assert torch.equal(out, grace.grace_combine_share(layer.y, layer.perm_out[0], layer.route_out[1], layer.y_state))
+
+
 @pytest.mark.parametrize("T,E,k,d,dtype,rows,policy", [
     (1, 1, 1, 8, "bf16", True, 0), (1, 256, 64, 2048, "f32", True, 1), (2, 64, 8, 2048, "bf16", True, 0),
     (4, 65, 3, 4, "f32", True, 0), (5, 128, 8, 24, "bf16", True, 1), (16, 129, 8, 4096, "bf16", True, 0),
