@@ -72,9 +72,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ 
 // 6.6 us; d = 4096, 8192 tokens, k = 2, an eighth 31.9 -> 20.4 us.  On a rank that holds every row it takes 0.98 to 1.07 of
 // combine_kernel's time (64 to 32768 tokens).  Batches of 1, 2 and 4: 2048 tokens, k = 8, a quarter of the rows 8.8, 7.3, 7.1 us; k =
 // 2, 4096 tokens of 4096 13.6, 12.6, 13.8 us.  Two or four tokens per workgroup gain up to 2.5 us on prefill with few rows and lose
-// up to a half for fewer tokens or many rows.
-template <bool BF16, int BATCH>
-__global__ __launch_bounds__(256) void combine_share_kernel(const char *__restrict__ y, const int32_t *__restrict__ perm_pos,
+// up to a half for fewer tokens or many rows.  A second pass over the ballots would cost wide rows what they save (a token of d = 4096,
+// k = 2, combine_kernel 2.27 us, 256 threads 2.67, 512 threads 2.13): rows of more than 256 vectors take 512 threads.
+template <bool BF16, int BATCH, int THREADS>
+__global__ __launch_bounds__(THREADS) void combine_share_kernel(const char *__restrict__ y, const int32_t *__restrict__ perm_pos,
                                                             const float *__restrict__ topk_weight, int k, int row_vec,
                                                             int64_t n_rows, const uint4 *__restrict__ y_shared,
                                                             const int32_t *__restrict__ state, uint4 *__restrict__ out) {
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(256) void combine_share_kernel(const char *__restri
     const int lane = (int)threadIdx.x & 63;
     const int64_t t = blockIdx.x, a0 = t * k, row_bytes = (int64_t)row_vec * 16;
     const int64_t lo = max(0, state[4]), hi = min(n_rows, (int64_t)state[5]);
-    for (int c = (int)threadIdx.x; c - lane < row_vec; c += 256) {
+    for (int c = (int)threadIdx.x; c - lane < row_vec; c += THREADS) {
         const int cc = min(c, row_vec - 1);   // whole wavefronts stay for the ballots
         int32_t p_lane = perm_pos[a0 + min(lane, k - 1)];
         float w_lane = topk_weight[a0 + min(lane, k - 1)];
@@ -186,12 +187,18 @@ extern "C" int grace_combine_share(const void *y, const int32_t *perm_pos, const
     const int64_t row_bytes = (int64_t)d * (dt == GRACE_F32 ? 4 : 2), n = (int64_t)T * k;
     if (row_bytes > INT32_MAX)   // past what a buffer descriptor spans: all rows are read
         return grace_combine(y, perm_pos, topk_weight, T, k, d, dt, y_shared, out, stream);
-    auto launch = [&](auto kernel) {
-        kernel<<<T, 256, 0, (hipStream_t)stream>>>((const char *)y, perm_pos, topk_weight, k, (int)(row_bytes / 16), n,
-                                                   (const uint4 *)y_shared, state, (uint4 *)out);
+    auto launch = [&](auto kernel, int threads) {
+        kernel<<<T, threads, 0, (hipStream_t)stream>>>((const char *)y, perm_pos, topk_weight, k, (int)(row_bytes / 16), n,
+                                                       (const uint4 *)y_shared, state, (uint4 *)out);
     };
-    if (dt == GRACE_BF16) launch(k < 3 ? combine_share_kernel<true, 2> : combine_share_kernel<true, 4>);
-    else launch(k < 3 ? combine_share_kernel<false, 2> : combine_share_kernel<false, 4>);
+    auto by_row = [&](auto narrow, auto wide) { row_bytes <= 256 * 16 ? launch(narrow, 256) : launch(wide, 512); };
+    if (dt == GRACE_BF16) {
+        if (k < 3) by_row(combine_share_kernel<true, 2, 256>, combine_share_kernel<true, 2, 512>);
+        else by_row(combine_share_kernel<true, 4, 256>, combine_share_kernel<true, 4, 512>);
+    } else {
+        if (k < 3) by_row(combine_share_kernel<false, 2, 256>, combine_share_kernel<false, 2, 512>);
+        else by_row(combine_share_kernel<false, 4, 256>, combine_share_kernel<false, 4, 512>);
+    }
     GRACE_LAUNCH_CHECK("combine_share_kernel");
     return GRACE_OK;
 }
