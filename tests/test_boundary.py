@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2509_25041_amd as grace
 from paper_2509_25041_amd import binding
@@ -27,6 +28,20 @@ def test_library_exports_every_declared_symbol():
     for n in names:
         assert getattr(lib, n) is not None
     assert os.path.dirname(grace.library_path()).endswith("paper_2509_25041_amd")
+
+
+def test_asking_for_the_stream_initialises_the_device(monkeypatch):
+    """GraceTable may be the first GPU call of a process: torch's own initialisation, and its messages where it is not
+    possible, come before the library's."""
+    if torch.cuda.is_initialized():
+        pytest.skip("the device is in use already")
+
+    def lazy_init():
+        raise RuntimeError("initialised here")
+
+    monkeypatch.setattr(torch.cuda, "_lazy_init", lazy_init)
+    with pytest.raises(RuntimeError, match="initialised here"):
+        grace.GraceTable(1, 1, 1, [0], [1], [0, 1], [0])
 
 
 def test_binding_has_the_entry_points_under_their_own_names():

@@ -1,5 +1,7 @@
 """Kernel variants that the launchers choose by size, each at the sizes where it can go wrong, against the
 oracle: edges of its tiles, remainders along every axis, both ends of its range."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -101,11 +103,14 @@ def test_tiles_in_halves(seg_rows, T, k, d, f):
     check_segments(got, want, off, TOL["bf16"])
 
 
-@pytest.mark.parametrize("T,k,d,f,dtype", [(3, 2, 64, 32, "bf16"), (40, 4, 256, 128, "f32"), (130, 4, 200, 72, "bf16"),
-                                           (90, 4, 40, 24, "f32"), (90, 4, 100, 50, "f32"), (3000, 8, 256, 512, "bf16")])
-def test_fresh_output_is_zero_outside_the_rank(T, k, d, f, dtype):
-    """Every kernel's down projection zeroes what it does not compute of a y that holds NaN: rows before, behind and, for an empty
-    rank, all; the rank's rows are those of the call on zeros."""
+@pytest.mark.parametrize("T,k,d,f,dtype,down", [
+    (3, 2, 64, 32, "bf16", "stream"), (40, 4, 256, 128, "f32", "stream"), (130, 4, 200, 72, "bf16", "mid"), (90, 4, 40, 24, "f32", "stream"),
+    (90, 4, 100, 50, "f32", "vector_f32"), (3000, 8, 256, 512, "bf16", "mid"), (25000, 2, 256, 128, "bf16", "persist"),
+    (6000, 8, 1280, 640, "f32", "mid"), (3, 2, 8, 8388616, "bf16", "generic")])
+def test_fresh_output_is_zero_outside_the_rank(T, k, d, f, dtype, down):
+    """Every kernel's down projection zeroes what it does not compute of a y that holds NaN: rows before and behind the rank's, for
+    a rank without rows all; the rank's rows are those of the call on zeros."""
+    assert kernels_of(T, k, d, f, 2, 8, dtype=dtype)[1] == down
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     gen = torch.Generator(device="cuda").manual_seed(T)
     table = grace.GraceTable(8, 4, 1, [0] * 4, [1] * 4, list(range(9)), [e // 2 for e in range(8)])
@@ -335,17 +340,20 @@ def test_combine_of_a_layer_that_hosts_every_instance(R):
     (65, 64, 8, 8, "bf16", True, 0), (32, 128, 8, 2048, "bf16", True, 0), (31, 256, 8, 40, "f32", True, 1), (96, 8, 4, 128, "f32", True, 1), (256, 8, 2, 128, "f32", True, 0),
     (64, 64, 17, 8, "bf16", True, 0), (97, 64, 3, 8, "bf16", True, 0), (257, 64, 2, 8, "bf16", True, 0), (33, 65, 3, 8, "bf16", True, 0)])   # past it, in assignments and in tokens
 def test_one_launch_dispatch_of_few_tokens(T, E, k, d, dtype, rows, policy):
-    """Routing, index work and rows of up to 96 (k = 2: 256) tokens in one launch against the separate calls: ties, masked experts, counters
-    near 2^32, experts with several candidates."""
+    """Routing, index work and rows of up to 96 (k = 2: 256) tokens in one launch against the oracle and, bit for bit, the separate
+    calls: ties, masked experts, counters near 2^32, experts with several candidates."""
     rng = np.random.default_rng(T * E + k)
     R = 4
     hosts = [sorted(rng.choice(R, size=1 if E > 200 else rng.integers(1, 4 if E < 80 else 2), replace=False).tolist()) for _ in range(E)]
     ptr = np.concatenate([[0], np.cumsum([len(h) for h in hosts])])
     assert ptr[-1] <= 256
-    table = grace.GraceTable(E, R, 2, [0, 0, 1, 1], rng.integers(1, 9, size=R).tolist(), ptr.tolist(), np.concatenate(hosts).tolist())
+    pl = SimpleNamespace(E=E, R=R, N=2, rank_node=np.array([0, 0, 1, 1], np.int32), poll_weight=rng.integers(1, 9, size=R).astype(np.uint32),
+                         inst_ptr=ptr.astype(np.int32), inst_rank=np.concatenate(hosts).astype(np.int32))
+    table = grace.GraceTable.from_placement(pl)
     logits = np.round(rng.standard_normal((T, E)) * 2).astype(np.float32) / 2
     logits[0, ::2] = -0.0
     logits[T // 2, 1:] = -np.inf
+    logits_host = logits
     logits = torch.from_numpy(logits).cuda()
     x = torch.from_numpy(rng.standard_normal((T, d)).astype(np.float32)).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
     rr = torch.from_numpy(rng.integers(2 ** 32 - 9, 2 ** 32, size=E, dtype=np.uint64).astype(np.uint32).view(np.int32)).cuda()
@@ -355,6 +363,10 @@ def test_one_launch_dispatch_of_few_tokens(T, E, k, d, dtype, rows, policy):
     one = grace.grace_route_permute(table, 2, logits, k, x if rows else None, 0, rr, out_b, policy=policy)
     for a, b in zip((*route, *perm, out_a), (*one[0], *one[1], out_b)):
         assert (a is None and b is None) or torch.equal(a, b)
+    ref = oracle.route_permute(logits_host, pl, k, 2, renorm=0, rr_in=rr.cpu().numpy().view(np.uint32), policy=policy)
+    (te, tw, ti, cnt), (pos, src, ioff, roff, noff, xp) = one
+    parity.check_route_permute(SimpleNamespace(te=te, tw=tw, ti=ti, cnt=cnt, rout=out_b, pos=pos, src=src, ioff=ioff, roff=roff, noff=noff, xp=xp),
+                               ref, SimpleNamespace(x=host(x)), k)
 
 
 @pytest.mark.parametrize("nodes,gpus,T,k", [(2, 2, 1, 2), (3, 2, 255, 4), (1, 4, 1025, 3), (4, 2, 513, 2)])
