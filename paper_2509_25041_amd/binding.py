@@ -118,6 +118,7 @@ def _dp(t: Optional[torch.Tensor]):
 
 
 def _stream() -> int:
+    # (_cuda_getDevice initialises the device on first use, as current_stream() does)
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
@@ -470,7 +471,6 @@ def grace_combine_share(y: torch.Tensor, perm_pos: torch.Tensor, topk_weight: to
 def grace_mfma_sustained(random_operands: bool = True, lds_fed: bool = True) -> float:
     """Sustained bf16 MFMA TFLOP/s of the current device (see grace_moe.h)."""
     out = C.c_double()
-    torch.cuda.init()   # no tensor has done it
     _check(load_library().grace_mfma_sustained(int(random_operands), int(lds_fed), C.byref(out), _stream()))
     return float(out.value)
 

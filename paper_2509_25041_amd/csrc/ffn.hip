@@ -9,8 +9,9 @@
 // the dispatch buffer, subdivided per local slot by inst_off (read on the
 // device; there is no host synchronisation).  route_gemm below chooses the kernel
 // by type, batch and shape.  The large-tile bf16 kernel is persistent (one
-// workgroup per compute unit walks the tiles); the others size their
-// grid from an upper bound of the tile count and surplus blocks exit at once.
+// workgroup per compute unit walks the tiles); the 96-row kernels launch for five times
+// the rank's even share of the rows and walk what is more in rounds; the others size their
+// grid from an upper bound of the tile count.  Surplus blocks exit at once.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -192,13 +193,13 @@ static int64_t pieces_of(int64_t rows, int n_seg, int bm, int quarters, int hot)
 // check lose more where ranks hold less than they save where one holds it (gate+up at 512 tokens, d = 2048, f = 1024: 50.7
 // instead of 37.5 us with 9/4).
 //
-// Measured over 3182 projections inside layer steps (53 ranks of tables for five layer shapes, expert widths whole to a
+// Measured over 51204 projections inside 18287 layer steps (ranks of tables for five layer shapes, expert widths whole to a
 // quarter, 1 to 32 ranks, 17 to 12000 tokens, three sets of weights in turn, the row scatter included where the large tiles
-// carry it): 189.1 ms with large tiles only, 152.5 with this rule and the one below, 149.9 with the best kernel each
-// time.  49 projections are slower than with large tiles by more than 3 % and 1 us, by 40 % at most (a rank with 3.1
-// times its share, 84.5 -> 118.5 us); of the 1220 steps, taking their projections together, one is slower by 1.5 % or more of a
-// whole step, by 3 us.  With the condition at three times the share alone (153.7 ms) 169 projections and 59 steps were, by up
-// to 79 us.
+// carry it): 3008 ms with large tiles wherever they can run, 2178 with this rule and the one below, 2122 with the best kernel
+// each time.  481 projections are slower than with large tiles by more than 3 % and 1 us, by 85 % at most (a rank with four times
+// its share, 44.7 -> 82.8 us); of the steps, taking their projections together, 52 by more than 3 %, by 22 % at most.  The other way round the
+// rule leaves 1556 projections on large tiles where 96 rows would be faster by as much, by 2.5 times at most: ranks with a tenth of
+// their share (158 rows of 8963 tokens, 46.7 and 18.8 us), which the host cannot know.
 template <bool FUSED_UP>
 static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
     const int64_t strips = (g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
@@ -228,24 +229,31 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
 // 1388, whose rows are no whole lines), and 234 of shared experts:
 //  * five tiles per compute unit at the even share and K of 20 steps or more: streaming 66.3 ms, 96 rows 57.1 ms, in 170 expert
 //    projections and 23 of shared experts none slower by more than 1 %;
-//  * gate+up of fewer tiles, but with 8 or more segments, N >= 2048 and K >= 1024: 21.0 -> 16.5 ms in 129, five slower by 3
-//    to 11 %; with fewer segments 4.6 -> 4.4 ms in 60, ten slower by up to 14 %;
-//  * the other 2365: 0.47 to 1.69 times as fast, 832 faster and 1125 slower by more than 3 %.
+//  * many segments even out what their ragged ends take.  Gate+up, 8 segments or more, N >= 2048, K >= 512 38.2 -> 31.9 ms in 242, 20
+//    slower by 3 to 15 % (with fewer segments ten of 60); 16 segments, N >= 1024, a tile for every other unit 4.9 -> 4.0 ms in 34
+//    more, none slower; down, 8 segments, N >= 2048, two tiles per unit 4.6 -> 4.0 ms in 28, none slower by more than 3 %;
+//  * the other 2190: 0.47 to 1.69 times as fast, 697 faster and 1110 slower by more than 3 %.
+// In all 226.3 ms with the streaming kernel, 206.4 with 96 rows, 209.3 with this rule.
 template <bool FUSED_UP>
 static bool mid_f32_is_faster(const GemmArgs &g, const Rows &rows, int n_cu) {
     const int64_t strips = (g.N + midf::Shape<FUSED_UP>::BN - 1) / midf::Shape<FUSED_UP>::BN;
-    if (g.K < 20 * midf::BK) return false;
-    return rows.at(4) * strips >= (int64_t)5 * n_cu * midf::BM || (FUSED_UP && g.S >= 8 && g.N >= 2048 && g.K >= 1024);
+    const int64_t work = rows.at(4) * strips, round = (int64_t)n_cu * midf::BM;   // of one tile per compute unit
+    const bool long_k = g.K >= 20 * midf::BK;
+    if (long_k && work >= 5 * round) return true;
+    if (FUSED_UP) return (g.S >= 8 && g.N >= 2048 && g.K >= 512) || (g.S >= 16 && g.N >= 1024 && long_k && 2 * work >= round);
+    return g.S >= 8 && g.N >= 2048 && long_k && work >= 2 * round;
 }
 
 // bf16, up to 64 rows per segment: the streaming kernel, which splits the work finest, while the 96-row kernel's tiles
 // would not fill the chip.  A gate+up projection of more than 16 rows leaves it when the other has a tile for three quarters
-// of the compute units (above that line it takes 0.9 to 1.8 of the 96-row kernel's time, 1.0 to 1.3 in the middle), a down
-// projection when there are one and a half per unit (1.0 to 1.6, 1.2 to 1.5 in the middle; all 60 qwen-shaped experts on one GPU,
-// 64 tokens: large tiles 32.2 us, streaming 41.5 us, 96 rows 28.5 us).  With less than half a tile per unit it takes
-// 0.5 to 0.9 of the 96-row kernel's time, between the two 0.7 to 1.5, 1.0 in the middle.
-// Down projections of few steps along K stay with it up to 32 tokens: the 96-row kernel's start-up is then most of its
-// time (21 tokens, d = 2048, f = 384, 128 segments: a call takes 64.2 us with the streaming kernel, 72.0 with the other).
+// of the compute units, a down projection when there are one and a half per unit, and with few steps along K only past 32
+// tokens (21 tokens, d = 2048, f = 384, 128 segments 11.4 us, 14.2 with the other).  Time of the streaming kernel over that of the 96-row
+// kernel in the steps above with 17 to 64 tokens (median, and what 96 of 100 lie between), by tiles per compute unit at three times the even share:
+//   gate+up: up to 1/4 0.86 (0.71 to 1.17), to 3/4 1.12 (0.74 to 1.59), to 1 1.29 (0.97 to 1.73), to 3/2 1.44 (1.21 to 1.97), more 1.21 (1.02 to 1.48)
+//   down, K >= 1024: up to 1/4 0.91 (0.71 to 1.28), to 1 1.09 (0.78 to 1.36), to 3/2 1.16 (1.02 to 1.34), more 1.30 (1.05 to 1.63)
+//   down, K < 1024: up to 1 0.89 (0.74 to 1.09), to 3/2 0.96 (0.83 to 1.31), more 1.15 (0.99 to 1.38)
+// All 8257 such gate+up projections take 281.6 ms with the streaming kernel, 235.0 with 96 rows, 237.4 with this rule and 229.7
+// with the best kernel each time; the down projections 188.1, 177.9, 179.7 and 169.0.
 template <bool FUSED_UP>
 static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };

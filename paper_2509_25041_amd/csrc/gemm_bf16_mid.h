@@ -30,11 +30,11 @@
 // (8 runs: 42 instead of 39 us on the batch of 512).
 //
 // Measured with cold weights, all segments in use (more than 1 GB of others between two uses; up / down projection, 256 x 256
-// tiles -> this kernel, us): 16 segments of d = 2048, f = 1024, 2236 rows with Zipf-shaped shares 49.3 / 27.3 -> 43.3 /
-// 27.0, 300 rows 42.5 / 24.7 -> 44.0 / 22.8; f = 768, 985 rows 44.2 / 22.8 -> 29.5 / 20.4; d = 4096, f = 14336, one
-// segment of 64 rows 72.4 / 199.6 -> 56.2 / 111.9, of 512 rows 96.8 / 195.1 -> 176.5 / 120.3 (the choice takes large tiles
-// for the first of the two).  A rank of an OLMoE-shaped layer whose routing leaves segments empty, three sets of weights
-// in turn: 70 tokens, 11 of 16 segments in use 34.0 / 16.4 -> 21.5 / 13.3, 230 tokens, 13 of 16 44.3 / 19.3 -> 27.7 / 17.7.
+// tiles and this kernel, us): 16 segments of d = 2048, f = 1024, 2236 rows with Zipf-shaped shares 50.1 / 26.2 and 41.7 /
+// 25.9, 300 rows 41.6 / 24.5 and 32.3 / 19.5; f = 768, 985 rows 44.4 / 22.0 and 28.0 / 19.4; d = 4096, f = 14336, one
+// segment of 64 rows 70.5 / 199.8 and 43.9 / 60.4, of 512 rows 99.5 / 193.8 and 188.5 / 125.1 (the choice takes large tiles
+// for the first of the two).  Segments as a batch of 70 tokens has them, 11 of 16 in use 36.2 / 21.1 and 23.0 / 14.8, of 230
+// tokens, 13 of 16 45.8 / 23.4 and 27.1 / 17.1.
 // K that is no multiple of 64 took a kernel without prefetch before: 3001 rows, N = 2048, K = 2 x 352 58 -> 20 us.
 #pragma once
 #include <algorithm>

@@ -15,11 +15,11 @@
 // (gemm_bf16_persist.h) is the wrong shape there: 256 weight rows per workgroup leave most compute units without
 // a tile, and a 256-row activation tile is mostly clamped duplicates.  Measured with cold weights (more than 1 GB of
 // others between two uses; up / down projection, large tiles -> this kernel, us): 16 segments of d = 2048, f = 1024, 122
-// rows in all of them 39.9 / 22.2 -> 29.8 / 16.1 (134 + 67 MB: 4.5 / 4.2 TB/s; a large copy moves 5.1 TB/s); a row in
-// each of 4 of them 32.0 / 19.2 -> 13.9 / 8.6; 22 rows in all 16 segments of f = 768 36.1 / 19.6 -> 21.4 / 12.0.  The
-// 96-row kernel takes 35.4 / 16.2, 17.0 / 10.9 and 25.9 / 12.9 there; with a third of the segments empty, as skewed routing
-// leaves them, it is even or ahead, and it is far ahead where a few rows meet many strips (d = 4096, f = 14336, one segment of 64
-// rows, up: 56 instead of 106 us), so gate+up projections of more than 16 tokens go there when its tiles fill the
+// rows in all of them 37.7 / 21.4 -> 29.7 / 16.4 (134 + 67 MB: 4.5 / 4.1 TB/s; a large copy moves 5.1 TB/s); a row in
+// each of 4 of them 26.5 / 14.8 -> 19.3 / 10.7; 22 rows in all 16 segments of f = 768 36.1 / 19.0 -> 21.4 / 12.0.  The
+// 96-row kernel takes 27.5 / 17.2, 11.7 / 8.1 and 21.7 / 13.5 there; with a third of the segments
+// empty, as skewed routing leaves them, it is ahead (20.4 / 13.4 and 28.7 / 16.3), and far ahead where a few rows meet many strips (d =
+// 4096, f = 14336, one segment of 64 rows 43.9 / 60.4 and 105.9 / 97.6), so gate+up projections of more than 16 tokens go there when its tiles fill the
 // chip.  Register depths of 4 to 8 steps make no difference; with about 160 registers (12 wavefronts per compute unit, so
 // that 1024 workgroups no longer run at once) the first case took 1.6 us more, with nt loads 3 us more.
 //

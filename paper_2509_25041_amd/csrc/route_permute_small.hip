@@ -186,8 +186,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
 // are loaded ahead; the gate weights, which only the caller needs, come last, under the row's stores.
 // Layer steps, the three launches -> this one (1, 16, 64 tokens): 64 experts, k = 8 24.3 -> 20.8, 30.6 -> 25.0, 38.0 -> 33.9 us; 8 experts, k = 2
 // 22.8 -> 17.8, 30.8 -> 27.2, 34.9 -> 30.5 us; 128 experts, k = 8 22.8 -> 18.8, 31.1 -> 24.0 us.  Where the line lies: every workgroup
-// repeats the gate of all tokens; 64 experts, k = 8 100 tokens 39.2 -> 37.6, 128 tokens 39.1 -> 38.3, k = 6 56.1 -> 55.8, 56.7 -> 57.6 us; k = 2 200 tokens 42.5 -> 40.6, 256 tokens 42.7 -> 41.4 us; 128
-// experts, two tokens per wavefront past 16 (four by rows: 33 tokens 32.1 -> 32.2, 64 tokens 34.9 -> 36.1 us).
+// repeats the gate of all tokens, so the call (replayed from a graph) gains less with each.  96 tokens, 64 experts, k = 3, 4, 5, 6, 8: three
+// launches as the next larger batch takes them 10.4, 10.4, 11.0, 11.2, 11.8, this one 7.5, 8.2, 8.6, 9.4, 10.5 us; 85 tokens, k = 12 is the most
+// assignments.  Past 96 tokens k = 6 and 8 are about even in a step (128 tokens 56.7 -> 57.6, 39.1 -> 38.3 us).  256 tokens with k = 1, 2, where four
+// passes of the wavefronts end: 9.1, 10.0 to 10.6 against 10.9, 10.4 to 11.0 us.  128 and 256 experts, 32 tokens, k = 8, two passes: 9.5 and 11.4
+// against 12.3 and 14.0 us (33 tokens); four tokens by rows there 33 tokens 32.1 -> 32.2, 64 tokens 34.9 -> 36.1 us a step.
 constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
 constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_TOP2 = 16 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;
 inline bool tiny_batch(int T, int k, int E, int I) {

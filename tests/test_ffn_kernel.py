@@ -86,6 +86,11 @@ def test_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
     (False, 5000, 1, 2048, 768, 1, 1, 1, "mid"),         # 180 / 150
     (True, 500, 8, 1024, 2816, 0, 16, 64, "mid"),        # 191 / 152: gate+up of many segments, wide and long
     (False, 500, 8, 1024, 2816, 0, 16, 64, "stream"),    # 92.5 / 135
+    (True, 500, 2, 548, 2816, 0, 8, 16, "mid"),          # 63.6 / 60.9
+    (True, 300, 8, 1024, 1388, 0, 16, 16, "mid"),        # 183 / 151
+    (True, 65, 2, 1024, 1388, 0, 16, 64, "stream"),      # 22.3 / 18.6: less than a tile for every other unit
+    (False, 1000, 8, 2048, 768, 0, 16, 16, "mid"),       # 287 / 244: two tiles per unit of many segments
+    (False, 128, 8, 2048, 768, 0, 16, 16, "stream"),     # 51.2 / 59.4
     (True, 200, 8, 2048, 768, 0, 4, 8, "stream"),        # 68.5 / 93.9
     (True, 500, 2, 548, 1388, 0, 16, 16, "stream"),      # 58.8 / 62.6
     (True, 1000, 1, 2048, 768, 1, 1, 1, "stream"),       # 69.8 / 106
