@@ -472,7 +472,7 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     GemmArgs dn = expert_shape(false, S, d, f);
     dn.A = ws; dn.B0 = w_down; dn.out = y;
     dn.seg_off = inst_off + g0;
-    dn.share_state = state; dn.clear_others = clear_others; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
+    dn.share_state = state; dn.stale = state ? 1 : clear_others ? 2 : 0; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
     return launch_gemm<false, pers::EXPERTS>(dn, dt, expert_rows(S, table->I, T, k), (hipStream_t)stream, who);
 }
 
