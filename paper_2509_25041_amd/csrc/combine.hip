@@ -69,11 +69,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4 *__restrict__ 
 // no branch makes the loads wait for one another.  Bound by HBM (shared rows in, result out) for large batches, by the chain
 // position -> row for small ones.  Layer steps in d = 2048, bf16, all rows read -> those of the rank: 32768 tokens, k = 6, 1/22 of the
 // rows, shared experts 178 -> 47 us; 7001, k = 8, an eighth 45.4 -> 13.0 us; 3001, k = 6, a seventh, shared experts 18.8 ->
-// 6.6 us; d = 4096, 8192 tokens, k = 2, an eighth 31.9 -> 20.4 us.  On a rank that holds every row it takes 0.98 to 1.07 of
-// combine_kernel's time (64 to 32768 tokens).  Batches of 1, 2 and 4: 2048 tokens, k = 8, a quarter of the rows 8.8, 7.3, 7.1 us; k =
+// 6.6 us; d = 4096, 8192 tokens, k = 2, an eighth 31.9 -> 20.4 us.  On a rank that holds every row it takes 0.85 (k = 16) to
+// 1.25 (k = 1) of combine_kernel's time; the layer calls that one there.  Batches of 1, 2 and 4: 2048 tokens, k = 8, a quarter of the rows 8.8, 7.3, 7.1 us; k =
 // 2, 4096 tokens of 4096 13.6, 12.6, 13.8 us.  Two or four tokens per workgroup gain up to 2.5 us on prefill with few rows and lose
 // up to a half for fewer tokens or many rows.  A second pass over the ballots would cost wide rows what they save (a token of d = 4096,
-// k = 2, combine_kernel 2.27 us, 256 threads 2.67, 512 threads 2.13): rows of more than 256 vectors take 512 threads.
+// k = 2, combine_kernel 2.27 us, 256 threads 2.67, 512 threads 2.13; 1000 tokens in fp32 8.4, 9.2, 7.9): rows of more than 256 vectors take
+// 512 threads.  Large batches hide the passes behind other tokens, and fewer of them fit a compute unit then (d = 4096, an eighth of the
+// rows, 2048 tokens, k = 4 8.3 -> 7.6, 4096 tokens 13.4 -> 14.1, 16384 tokens 37.6 -> 43.8 us).
 template <bool BF16, int BATCH, int THREADS>
 __global__ __launch_bounds__(THREADS) void combine_share_kernel(const char *__restrict__ y, const int32_t *__restrict__ perm_pos,
                                                             const float *__restrict__ topk_weight, int k, int row_vec,
@@ -147,6 +149,9 @@ using namespace grace;
 // enough (3001, 7001, 32768 tokens, k = 6, 8, 6: 18.2 to 19.4, 46.8, 177 us with 1 ahead, 18.2, 45.5, 178 us with 2,
 // 19.2, 45.2, 177 us with 4; k = 2, 8192 tokens 31.4 us with 1, 32.3 us with 2).
 constexpr int COMBINE_FEW = 1024;
+// Tokens up to which combine_share_kernel takes wide rows in one pass.
+constexpr int COMBINE_WIDE_MAX = 2048;
+
 static int check_combine_args(const char *who, const void *y, const int32_t *perm_pos, const float *topk_weight, int32_t T,
                               int32_t k, int32_t d, grace_dtype dt, const void *y_shared, const void *out) {
     if (T < 0 || k < 1 || d < 1) return fail(GRACE_EINVAL, "%s: T=%d, k=%d, d=%d invalid", who, T, k, d);
@@ -191,7 +196,7 @@ extern "C" int grace_combine_share(const void *y, const int32_t *perm_pos, const
         kernel<<<T, threads, 0, (hipStream_t)stream>>>((const char *)y, perm_pos, topk_weight, k, (int)(row_bytes / 16), n,
                                                        (const uint4 *)y_shared, state, (uint4 *)out);
     };
-    auto by_row = [&](auto narrow, auto wide) { row_bytes <= 256 * 16 ? launch(narrow, 256) : launch(wide, 512); };
+    auto by_row = [&](auto narrow, auto wide) { row_bytes <= 256 * 16 || T > COMBINE_WIDE_MAX ? launch(narrow, 256) : launch(wide, 512); };
     if (dt == GRACE_BF16) {
         if (k < 3) by_row(combine_share_kernel<true, 2, 256>, combine_share_kernel<true, 2, 512>);
         else by_row(combine_share_kernel<true, 4, 256>, combine_share_kernel<true, 4, 512>);

@@ -294,7 +294,7 @@ def test_combine_with_absent_rows(T, k, dtype):
     (1, 1, 24, "bf16", 0, 1, False), (1, 8, 2056, "bf16", 2, 3, True), (5, 70, 24, "f32", 60, 300, False), (300, 70, 24, "f32", 6000, 15000, False),
     (33, 64, 24, "bf16", 3, 700, True), (1024, 6, 24, "f32", 0, 0, True), (1025, 9, 24, "bf16", 1000, 4000, True), (1027, 16, 2056, "bf16", 0, 16432, False),
     (1025, 17, 24, "f32", 9000, 17425, False), (2051, 2, 1028, "f32", 4101, 4102, True),
-    (3, 2, 2048, "bf16", 1, 4, True), (40, 3, 4096, "bf16", 30, 90, False), (40, 2, 4104, "bf16", 0, 60, True), (5, 70, 2052, "f32", 60, 300, True)])   # one or more passes of a workgroup over a row
+    (3, 2, 2048, "bf16", 1, 4, True), (40, 3, 4096, "bf16", 30, 90, False), (40, 2, 4104, "bf16", 0, 60, True), (5, 70, 2052, "f32", 60, 300, True), (2049, 3, 2056, "bf16", 900, 2100, True)])   # one or more passes of a workgroup over a row
 def test_combine_share_is_combine_of_zero_rows(T, k, d, dtype, lo, hi, shared):
     """Rows outside the share are zero and not read: the same bits as grace_combine, which reads them, with positions
     outside the buffer and gate weights that are not finite (0 * inf) among the absent rows."""
