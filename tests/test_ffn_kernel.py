@@ -60,8 +60,8 @@ def test_large_tiles_where_they_are_faster(up, T, k, d, f, S, I, want):
 
 @pytest.mark.parametrize("T,d,f,n_shared", [(2756, 2048, 704, 2), (6055, 2048, 704, 2), (1254, 2048, 1408, 2), (571, 2048, 1408, 4)])
 def test_shared_projection_keeps_the_row_scatter(T, d, f, n_shared):
-    """Gate+up projections of shared experts that were slower without the large-tile kernel, which carries the row scatter
-    (67.1 / 58.1, 135.1 / 113.9, 65.5 / 54.8 and 58.7 / 49.4 us, the scatter of six or four rows per token included)."""
+    """Gate+up projections of shared experts that are slower without the large-tile kernel, which carries the row scatter
+    (65.8 / 58.4, 128.7 / 113.4, 56.3 / 53.2 and 54.6 / 45.5 us, the scatter of six or four rows per token included)."""
     assert grace.grace_ffn_kernel(True, T, d, f, BF16, n_shared=n_shared, n_cu=N_CU)[0] == "persist"
 
 
@@ -72,7 +72,7 @@ def test_shared_projection_keeps_the_row_scatter(T, d, f, n_shared):
     (True, 200, 8, 2048, 1024, 0, 64, 64, "mid"), (True, 300, 1, 2048, 1408, 2, 1, 1, "mid"),
     (True, 32768, 1, 2048, 1408, 2, 1, 1, "persist"), (True, 8192, 8, 2048, 768, 0, 16, 130, "persist"),
     (False, 3001, 6, 2048, 352, 0, 2, 69, "mid"),       # K no multiple of 64
-    (False, 21, 8, 2048, 384, 0, 128, 128, "stream"),   # a whole call 64.2 us, 72.0 with the 96-row kernel
+    (False, 21, 8, 2048, 384, 0, 128, 128, "stream"),   # 11.4 us, 14.2 with the 96-row kernel
     (False, 33, 8, 2048, 384, 0, 128, 128, "mid"), (False, 16, 8, 2048, 1408, 0, 64, 64, "stream"),
 ])
 def test_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
