@@ -249,6 +249,11 @@ int grace_route_permute_static(const grace_table *table, int32_t local_rank, gra
 int grace_send_lists(const grace_table *table, int32_t local_rank, const int32_t *topk_inst, int32_t T, int32_t k,
                      int32_t *rank_send_ptr, int32_t *rank_send_tok, int32_t *node_send_ptr, int32_t *node_send_tok,
                      int32_t *expand, int64_t *traffic, void *ws, void *stream);
+/* The same, and the entries of the two token arrays past the ends of their lists, up to T*k, become -1 (for
+ * buffers that held nothing before: no fill ahead of the call). */
+int grace_send_lists_fresh(const grace_table *table, int32_t local_rank, const int32_t *topk_inst, int32_t T, int32_t k,
+                           int32_t *rank_send_ptr, int32_t *rank_send_tok, int32_t *node_send_ptr, int32_t *node_send_tok,
+                           int32_t *expand, int64_t *traffic, void *ws, void *stream);
 
 /* ---- grace_expert_ffn: grouped SwiGLU FFN over one rank's rows ---------------
  * The expert computation between dispatch and aggregation (Section 1).  For

@@ -19,7 +19,7 @@ _STATUS = {0: "GRACE_OK", -1: "GRACE_EINVAL", -2: "GRACE_ESHAPE", -3: "GRACE_ETA
 EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", "grace_table_info",
            "grace_table_instances", "grace_table_local_experts", "grace_table_set_fold_limits", "grace_workspace_bytes",
            "grace_route",
-           "grace_permute", "grace_permute_rows", "grace_route_permute", "grace_route_permute_static", "grace_send_lists", "grace_expert_ffn", "grace_expert_ffn_up",
+           "grace_permute", "grace_permute_rows", "grace_route_permute", "grace_route_permute_static", "grace_send_lists", "grace_send_lists_fresh", "grace_expert_ffn", "grace_expert_ffn_up",
            "grace_expert_ffn_down", "grace_expert_ffn_down_fresh", "grace_expert_ffn_up_share", "grace_expert_ffn_down_share",
            "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_combine_share", "grace_mfma_sustained",
            "grace_ffn_kernel",
@@ -68,6 +68,7 @@ def load_library() -> C.CDLL:
     lib.grace_route_permute_static.argtypes = [vp, i32, C.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp,
                                                vp, i32, C.c_int, vp, vp, vp, vp, vp, vp, vp]
     lib.grace_send_lists.argtypes = [vp, i32, vp, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.grace_send_lists_fresh.argtypes = lib.grace_send_lists.argtypes
     lib.grace_expert_ffn.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp]
     lib.grace_expert_ffn_up.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_expert_ffn_down.argtypes = [vp, i32, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
@@ -299,13 +300,13 @@ def grace_send_lists(table: GraceTable, local_rank: int, topk_inst: torch.Tensor
     T, k = topk_inst.shape
     dev = topk_inst.device
     i32 = dict(dtype=torch.int32, device=dev)
-    rp, rt = torch.empty(table.R + 1, **i32), torch.full((T * k,), -1, **i32)
-    np_, nt = torch.empty(table.N + 1, **i32), torch.full((T * k,), -1, **i32)
+    rp, rt = torch.empty(table.R + 1, **i32), torch.empty(T * k, **i32)
+    np_, nt = torch.empty(table.N + 1, **i32), torch.empty(T * k, **i32)
     ex = torch.empty(T * k, **i32)
     tr = torch.empty(4, dtype=torch.int64, device=dev)
     ws = _ws(ws, grace_workspace_bytes(T, table.E, k, table.I), dev)
-    _check(load_library().grace_send_lists(table.handle, local_rank, _dp(topk_inst), T, k, _dp(rp), _dp(rt), _dp(np_),
-                                           _dp(nt), _dp(ex), _dp(tr), _dp(ws), _stream()))
+    _check(load_library().grace_send_lists_fresh(table.handle, local_rank, _dp(topk_inst), T, k, _dp(rp), _dp(rt), _dp(np_),
+                                                 _dp(nt), _dp(ex), _dp(tr), _dp(ws), _stream()))
     return rp, rt, np_, nt, ex, tr
 
 

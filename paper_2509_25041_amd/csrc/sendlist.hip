@@ -10,8 +10,13 @@
 //   1. dedup_keys_kernel  one lane per assignment: its destination rank / node; the
 //                         token's first assignment per destination keeps the
 //                         destination as its sort key, the others get -1
-//   2. stable counting sort by rank key and by node key (stable_sort.h)
+//   2. stable counting sorts by rank key and by node key (stable_sort.h), one launch for both where each is one
 //   3. expand_traffic_kernel  expansion map + traffic sums
+// At most PERM_CHUNK assignments: send_lists_small_kernel does all of it in one workgroup.
+//
+// The lists are used by planning code that makes several short calls per batch, so launches count: with grace_route ahead and
+// grace_permute behind, 16384 tokens of k = 4 take 74.4 -> 61.9 us with
+// seven launches instead of ten (one for both sorts, no fills of the lists ahead of them), 9001 of k = 6 68.9 -> 57.7 us.
 #include "common.h"
 #include "stable_sort.h"
 
@@ -71,12 +76,47 @@ __global__ __launch_bounds__(PERM_CHUNK) void dedup_keys_kernel(const int32_t *_
     for (int i = (int)threadIdx.x; i < N; i += PERM_CHUNK) node_hist[(size_t)blockIdx.x * N + i] = hist[R + i];
 }
 
+// traffic[] (below) from the list lengths and the rows of every destination rank, by a whole workgroup; acc: LDS.
+template <typename ROWS>
+__device__ __forceinline__ void traffic_sums(int R, int N, int local_rank, const int32_t *__restrict__ rank_node,
+                                             const int32_t *rank_send_ptr, const int32_t *node_send_ptr, ROWS rows_of,
+                                             unsigned long long *acc, int64_t *__restrict__ traffic) {
+    if (threadIdx.x < 4) acc[threadIdx.x] = 0ull;
+    __syncthreads();
+    const int my_node = rank_node[local_rank];
+    int my_first = 0;  // first rank of the own node (ranks are node-major)
+    while (my_first < R && rank_node[my_first] != my_node) ++my_first;
+    const int local_idx = local_rank - my_first;
+    for (int r = (int)threadIdx.x; r < R; r += (int)blockDim.x) {
+        const int nd = rank_node[r];
+        const unsigned long long uniq = (unsigned long long)(rank_send_ptr[r + 1] - rank_send_ptr[r]);
+        const unsigned long long rows = (unsigned long long)rows_of(r);
+        if (nd != my_node) {
+            atomicAdd(&acc[1], rows);
+            // the peer of local_rank in node nd: same index inside the node (modulo the node's size)
+            int first = r, size = 0;
+            while (first > 0 && rank_node[first - 1] == nd) --first;
+            while (first + size < R && rank_node[first + size] == nd) ++size;
+            const int peer = first + local_idx % size;
+            if (r != peer) atomicAdd(&acc[2], uniq);
+        } else if (r != local_rank) {
+            atomicAdd(&acc[2], uniq);
+            atomicAdd(&acc[3], rows);
+        }
+    }
+    for (int n = (int)threadIdx.x; n < N; n += (int)blockDim.x)
+        if (n != my_node) atomicAdd(&acc[0], (unsigned long long)(node_send_ptr[n + 1] - node_send_ptr[n]));
+    __syncthreads();
+    if (threadIdx.x < 4) traffic[threadIdx.x] = (int64_t)acc[threadIdx.x];
+}
+
 // expand[a] = index of a's token in the send list of a's destination rank.
 // traffic[0] cross-node tokens with de-duplication: sum over other nodes of their distinct tokens
 // traffic[1] cross-node rows without (one per assignment)
 // traffic[2] intra-node tokens with de-duplication: distinct tokens for the other ranks of the own
 //            node plus, in every other node, for the ranks other than the peer that received stage 1
 // traffic[3] intra-node rows of a flat dispatch: assignments to the other ranks of the own node
+// rank_tail, node_tail (both or none): the lists, whose entries past their ends become -1.
 // counters: [0, R) rows per destination rank (all blocks add their share: integer sums, exact in any
 // order), [R] number of blocks that have added; the block that finishes last turns them into traffic[].
 // EXPAND_CHUNK assignments per block: the blocks' sums meet on the same few addresses (65536 assignments, 8 ranks:
@@ -91,7 +131,8 @@ __global__ __launch_bounds__(256) void expand_traffic_kernel(const int32_t *__re
                                                              const int32_t *__restrict__ rank_send_ptr,
                                                              const int32_t *__restrict__ node_send_ptr,
                                                              int32_t *__restrict__ expand, int64_t *__restrict__ traffic,
-                                                             int32_t *__restrict__ counters) {
+                                                             int32_t *__restrict__ counters, int32_t *__restrict__ rank_tail,
+                                                             int32_t *__restrict__ node_tail) {
     __shared__ int32_t naive_rank[GRACE_MAX_RANKS];
     __shared__ unsigned long long acc[4];
     __shared__ int last_block;
@@ -111,6 +152,10 @@ __global__ __launch_bounds__(256) void expand_traffic_kernel(const int32_t *__re
             if (traffic) atomicAdd(&naive_rank[r], 1);
         }
         expand[a] = e;
+        if (rank_tail) {
+            if (a >= rank_send_ptr[R]) rank_tail[a] = -1;
+            if (a >= node_send_ptr[N]) node_tail[a] = -1;
+        }
     }
     if (!traffic) return;
     __syncthreads();
@@ -128,33 +173,88 @@ __global__ __launch_bounds__(256) void expand_traffic_kernel(const int32_t *__re
     if (threadIdx.x == 0) last_block = atomicAdd(&counters[R], 1) == (int)gridDim.x - 1;
     __syncthreads();
     if (!last_block) return;
-    if (threadIdx.x < 4) acc[threadIdx.x] = 0ull;
+    traffic_sums(R, N, local_rank, rank_node, rank_send_ptr, node_send_ptr,
+                 [&](int r) { return atomicAdd(&counters[r], 0); },   // read at the L2, past this CU's cache
+                 acc, traffic);
+}
+
+// At most one chunk of assignments, and as many ranks: a workgroup does everything in LDS, one launch instead of three
+//
+// (the same calls for 1 and 60 tokens of k = 8: 68 -> 49 us, half of it from the fills and the permutation's histogram).
+constexpr int SMALL_LIST_RANKS = PERM_CHUNK;
+__global__ __launch_bounds__(PERM_CHUNK) void send_lists_small_kernel(
+    const int32_t *__restrict__ topk_inst, int n, int k, int I, int R, int N, int local_rank, const int32_t *__restrict__ inst_rank,
+    const int32_t *__restrict__ rank_node, int32_t *__restrict__ rank_send_ptr, int32_t *__restrict__ rank_send_tok,
+    int32_t *__restrict__ node_send_ptr, int32_t *__restrict__ node_send_tok, int32_t *__restrict__ expand,
+    int64_t *__restrict__ traffic, int fill) {
+    constexpr int WAVES = PERM_CHUNK / 64;
+    __shared__ int32_t wcnt[WAVES][SMALL_LIST_RANKS];                        // keys of a wavefront, then those before it
+    __shared__ int32_t roff[SMALL_LIST_RANKS + 1], noff[SMALL_LIST_RANKS + 1];   // list starts
+    __shared__ int32_t dest_r[PERM_CHUNK], dest_n[PERM_CHUNK], where[PERM_CHUNK];
+    __shared__ int32_t rows[SMALL_LIST_RANKS];
+    __shared__ unsigned long long acc[4];
+    const int a = (int)threadIdx.x, lane = a & 63, wave = a >> 6;
+    const int g = a < n ? topk_inst[a] : -1;
+    const bool to = (unsigned)g < (unsigned)I;
+    const int r = to ? inst_rank[g] : -1, nd = to ? rank_node[r] : -1;
+    dest_r[a] = r;
+    dest_n[a] = nd;
+    rows[a] = 0;
     __syncthreads();
-    const int my_node = rank_node[local_rank];
-    int my_first = 0;  // first rank of the own node (ranks are node-major)
-    while (my_first < R && rank_node[my_first] != my_node) ++my_first;
-    const int local_idx = local_rank - my_first;
-    for (int r = (int)threadIdx.x; r < R; r += 256) {
-        const int nd = rank_node[r];
-        const unsigned long long uniq = (unsigned long long)(rank_send_ptr[r + 1] - rank_send_ptr[r]);
-        const unsigned long long rows = (unsigned long long)atomicAdd(&counters[r], 0);  // read at the L2, past this CU's cache
-        if (nd != my_node) {
-            atomicAdd(&acc[1], rows);
-            // the peer of local_rank in node nd: same index inside the node (modulo the node's size)
-            int first = r, size = 0;
-            while (first > 0 && rank_node[first - 1] == nd) --first;
-            while (first + size < R && rank_node[first + size] == nd) ++size;
-            const int peer = first + local_idx % size;
-            if (r != peer) atomicAdd(&acc[2], uniq);
-        } else if (r != local_rank) {
-            atomicAdd(&acc[2], uniq);
-            atomicAdd(&acc[3], rows);
-        }
+    int first = a;
+    bool first_n = true;
+    for (int b = a - a % k; b < a; ++b) {
+        if (dest_r[b] == r && first == a) first = b;
+        if (dest_n[b] == nd) first_n = false;
     }
-    for (int n = (int)threadIdx.x; n < N; n += 256)
-        if (n != my_node) atomicAdd(&acc[0], (unsigned long long)(node_send_ptr[n + 1] - node_send_ptr[n]));
-    __syncthreads();
-    if (threadIdx.x < 4) traffic[threadIdx.x] = (int64_t)acc[threadIdx.x];
+    if (to && traffic) atomicAdd(&rows[r], 1);
+    auto sort = [&](int key, int nkeys, int32_t *off, int32_t *ptr, int32_t *tok) {   // position of this thread's key
+        for (int i = lane; i < nkeys; i += 64) wcnt[wave][i] = 0;   // its own wavefront's row: in program order
+        const bool valid = key >= 0;
+        const uint64_t same = wave_match((uint32_t)max(key, 0), valid, bits_for(nkeys));
+        if (valid && is_last_of(same)) wcnt[wave][key] = (int32_t)__popcll(same);
+        __syncthreads();
+        if (a < nkeys) {
+            int32_t run = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const int32_t c = wcnt[w][a];
+                wcnt[w][a] = run;
+                run += c;
+            }
+            off[a] = run;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            int32_t carry = 0;
+            for (int k0 = 0; k0 < nkeys; k0 += 64) {
+                const int32_t c = k0 + lane < nkeys ? off[k0 + lane] : 0, incl = wave_scan_add(c);
+                if (k0 + lane < nkeys) off[k0 + lane] = carry + incl - c;
+                carry += __builtin_amdgcn_readlane(incl, 63);
+            }
+            if (lane == 0) off[nkeys] = carry;
+        }
+        __syncthreads();
+        for (int i = a; i <= nkeys; i += PERM_CHUNK) ptr[i] = off[i];
+        int32_t pos = -1;
+        if (valid) {
+            pos = off[key] + wcnt[wave][key] + (int32_t)__popcll(same & lanemask_lt());
+            tok[pos] = a / k;
+        }
+        if (fill && a < n && a >= off[nkeys]) tok[a] = -1;
+        return pos;
+    };
+    where[a] = sort(to && first == a ? r : -1, R, roff, rank_send_ptr, rank_send_tok);
+    __syncthreads();   // before the next sort's counts, too
+    if (a < n) expand[a] = to ? where[first] - roff[r] : -1;
+    sort(to && first_n ? nd : -1, N, noff, node_send_ptr, node_send_tok);
+    if (traffic) traffic_sums(R, N, local_rank, rank_node, roff, noff, [&](int r) { return rows[r]; }, acc, traffic);
+}
+
+static int bits(int nkeys) {
+    int b = 0;
+    while ((1 << b) < nkeys) ++b;
+    return b;
 }
 
 static int sort_by_key(const grace_table *table, const int32_t *keys, int64_t n, int k, int nkeys, int32_t *hist, int32_t *base, int32_t *off,
@@ -169,9 +269,9 @@ static int sort_by_key(const grace_table *table, const int32_t *keys, int64_t n,
 
 using namespace grace;
 
-extern "C" int grace_send_lists(const grace_table *table, int32_t local_rank, const int32_t *topk_inst, int32_t T,
-                                int32_t k, int32_t *rank_send_ptr, int32_t *rank_send_tok, int32_t *node_send_ptr,
-                                int32_t *node_send_tok, int32_t *expand, int64_t *traffic, void *ws, void *stream) {
+static int send_lists(const grace_table *table, int32_t local_rank, const int32_t *topk_inst, int32_t T, int32_t k,
+                      int32_t *rank_send_ptr, int32_t *rank_send_tok, int32_t *node_send_ptr, int32_t *node_send_tok, int32_t *expand,
+                      int64_t *traffic, bool fill, void *ws, void *stream) {
     if (!table) return fail(GRACE_EINVAL, "send_lists: table is null");
     if (local_rank < 0 || local_rank >= table->R)
         return fail(GRACE_EINVAL, "send_lists: local_rank=%d outside [0,%d)", local_rank, table->R);
@@ -183,6 +283,13 @@ extern "C" int grace_send_lists(const grace_table *table, int32_t local_rank, co
     hipStream_t st = (hipStream_t)stream;
     const int64_t n = (int64_t)T * k;
     const int R = table->R, N = table->N, I = table->I;
+    if (n > 0 && n <= PERM_CHUNK && std::max(R, N) <= SMALL_LIST_RANKS && fold_mode(table, 1, R) == 1) {
+        send_lists_small_kernel<<<1, PERM_CHUNK, 0, st>>>(topk_inst, (int)n, k, I, R, N, local_rank, table->d_inst_rank, table->d_rank_node,
+                                                          rank_send_ptr, rank_send_tok, node_send_ptr, node_send_tok, expand, traffic,
+                                                          fill);
+        GRACE_LAUNCH_CHECK("send_lists_small_kernel");
+        return GRACE_OK;
+    }
     const size_t seg = align_up((size_t)n * 4, 256);
     char *w = (char *)ws;
     int32_t *rank_key = (int32_t *)w, *node_key = (int32_t *)(w + seg), *first_idx = (int32_t *)(w + 2 * seg);
@@ -203,15 +310,37 @@ extern "C" int grace_send_lists(const grace_table *table, int32_t local_rank, co
             node_hist);
         GRACE_LAUNCH_CHECK("dedup_keys_kernel");
     }
-    int rc = sort_by_key(table, rank_key, n, k, R, hist, base, rank_send_ptr, pos_r, rank_send_tok, st, true);
-    if (rc != GRACE_OK) return rc;
-    rc = sort_by_key(table, node_key, n, k, N, node_hist ? node_hist : hist, base, node_send_ptr, pos_n, node_send_tok, st, node_hist != nullptr);
-    if (rc != GRACE_OK) return rc;
+    if (node_hist && fold_mode(table, (int)nchunks, R) == 1 && fold_mode(table, (int)nchunks, N) == 1) {
+        const KeySort ranks = {rank_key, R, bits(R), hist, nullptr, rank_send_ptr, pos_r, rank_send_tok};
+        const KeySort nodes = {node_key, N, bits(N), node_hist, nullptr, node_send_ptr, pos_n, node_send_tok};
+        key_pos_fold_pair_kernel<<<dim3((unsigned)nchunks, 2), POS_FOLD_THREADS, 0, st>>>(ranks, nodes, n, (int)nchunks, k);
+        GRACE_LAUNCH_CHECK("key_pos_fold_pair_kernel");
+    } else {
+        int rc = sort_by_key(table, rank_key, n, k, R, hist, base, rank_send_ptr, pos_r, rank_send_tok, st, true);
+        if (rc != GRACE_OK) return rc;
+        rc = sort_by_key(table, node_key, n, k, N, node_hist ? node_hist : hist, base, node_send_ptr, pos_n, node_send_tok, st,
+                         node_hist != nullptr);
+        if (rc != GRACE_OK) return rc;
+    }
     if (n > 0 || traffic) {
         expand_traffic_kernel<<<(unsigned)std::max<int64_t>(1, ceil_div(n, EXPAND_CHUNK)), 256, 0, st>>>(
             topk_inst, n, I, R, N, local_rank, table->d_inst_rank, table->d_rank_node, first_idx, pos_r, rank_send_ptr,
-            node_send_ptr, expand, traffic, counters);
+            node_send_ptr, expand, traffic, counters, fill ? rank_send_tok : nullptr, node_send_tok);
         GRACE_LAUNCH_CHECK("expand_traffic_kernel");
     }
     return GRACE_OK;
+}
+
+extern "C" int grace_send_lists(const grace_table *table, int32_t local_rank, const int32_t *topk_inst, int32_t T,
+                                int32_t k, int32_t *rank_send_ptr, int32_t *rank_send_tok, int32_t *node_send_ptr,
+                                int32_t *node_send_tok, int32_t *expand, int64_t *traffic, void *ws, void *stream) {
+    return send_lists(table, local_rank, topk_inst, T, k, rank_send_ptr, rank_send_tok, node_send_ptr, node_send_tok, expand, traffic,
+                      false, ws, stream);
+}
+
+extern "C" int grace_send_lists_fresh(const grace_table *table, int32_t local_rank, const int32_t *topk_inst, int32_t T,
+                                      int32_t k, int32_t *rank_send_ptr, int32_t *rank_send_tok, int32_t *node_send_ptr,
+                                      int32_t *node_send_tok, int32_t *expand, int64_t *traffic, void *ws, void *stream) {
+    return send_lists(table, local_rank, topk_inst, T, k, rank_send_ptr, rank_send_tok, node_send_ptr, node_send_tok, expand, traffic,
+                      true, ws, stream);
 }

@@ -4,7 +4,8 @@
 //   key_scan_kernel   per-key exclusive scan over chunks, exclusive scan over keys
 //   key_pos_kernel    one wavefront per chunk: stable rank of each item among equal
 //                     keys (ballot matching) -> position of every item and its inverse
-//   key_pos_fold_kernel  the last two in one launch when there are few chunks
+//   key_pos_fold_kernel  the last two in one launch when there are few chunks, the first as well when there is one;
+//                     key_pos_fold_pair_kernel: the same for two sorts of the same items
 // Keys outside [0, nkeys) are skipped (position -1).  No atomics that affect order.
 #pragma once
 #include "common.h"
@@ -139,16 +140,25 @@ static __global__ __launch_bounds__(64) void key_pos_kernel(const int32_t *__res
 // Ranking: with at most POS_PAR_KEYS keys every wavefront ranks 64 of the chunk's items at once
 // (match sets by ballot, their sizes in the wavefront's row of wcnt, an exclusive scan over the
 // eight rows on top of the chunk's start positions); with more keys wavefront 0 walks the chunk.
+// Without chunk_hist there is one chunk and the block counts its own keys.
 constexpr int POS_FOLD_THREADS = 512, POS_WAVES = POS_FOLD_THREADS / 64;
 constexpr int POS_PAR_KEYS = 512;
 static_assert(PERM_CHUNK == POS_FOLD_THREADS, "one item per thread when all wavefronts rank");
 
-static __global__ __launch_bounds__(POS_FOLD_THREADS) void key_pos_fold_kernel(
-    const int32_t *__restrict__ keys, int64_t n_items, int I, const int32_t *__restrict__ chunk_hist, int nchunks, int R,
-    int N, const int32_t *__restrict__ rank_ptr, const int32_t *__restrict__ node_first_inst,
-    int32_t *__restrict__ inst_off, int32_t *__restrict__ rank_off, int32_t *__restrict__ node_off,
-    int32_t *__restrict__ perm_pos, int32_t *__restrict__ perm_src, int nbits, int src_div,
-    const int32_t *__restrict__ super_tot) {
+// One sort: keys [n_items] and nkeys of them, histograms and their super sums, offsets and positions.
+struct KeySort {
+    const int32_t *keys;
+    int nkeys, nbits;
+    const int32_t *chunk_hist, *super_tot;
+    int32_t *off, *pos, *src;
+};
+
+__device__ __forceinline__ void key_pos_fold(const KeySort &s, int64_t n_items, int nchunks, int R, int N,
+                                             const int32_t *__restrict__ rank_ptr, const int32_t *__restrict__ node_first_inst,
+                                             int32_t *__restrict__ rank_off, int32_t *__restrict__ node_off, int src_div) {
+    const int32_t *__restrict__ keys = s.keys, *__restrict__ chunk_hist = s.chunk_hist, *__restrict__ super_tot = s.super_tot;
+    int32_t *__restrict__ inst_off = s.off, *__restrict__ perm_pos = s.pos, *__restrict__ perm_src = s.src;
+    const int I = s.nkeys, nbits = s.nbits;
     __shared__ int32_t cnt[GRACE_MAX_INSTANCES];      // items of each key in the chunks before this one, then positions
     __shared__ int32_t off[GRACE_MAX_INSTANCES + 1];  // items of each key in all chunks, then exclusive offsets
     __shared__ int32_t wcnt[POS_WAVES][POS_PAR_KEYS];
@@ -165,7 +175,15 @@ static __global__ __launch_bounds__(POS_FOLD_THREADS) void key_pos_fold_kernel(
         off[i] = 0;
     }
     __syncthreads();
-    if (super_tot) {
+    if (!chunk_hist) {
+        if (par) {
+            if ((unsigned)g_one < (unsigned)I) atomicAdd(&off[g_one], 1);
+        } else if (wave == 0) {
+#pragma unroll
+            for (int q = 0; q < CHUNK_ROUNDS; ++q)
+                if ((unsigned)g[q] < (unsigned)I) atomicAdd(&off[g[q]], 1);
+        }
+    } else if (super_tot) {
         const int s = chunk / FOLD_SUPER, nsuper = (nchunks + FOLD_SUPER - 1) / FOLD_SUPER;
         block_add_rows<POS_FOLD_THREADS>(super_tot, 0, nsuper, I, off, tid, cnt, s);
         block_add_rows<POS_FOLD_THREADS>(chunk_hist, s * FOLD_SUPER, chunk, I, cnt, tid);
@@ -229,6 +247,16 @@ static __global__ __launch_bounds__(POS_FOLD_THREADS) void key_pos_fold_kernel(
     }
 }
 
+static __global__ __launch_bounds__(POS_FOLD_THREADS) void key_pos_fold_kernel(
+    const KeySort s, int64_t n_items, int nchunks, int R, int N, const int32_t *__restrict__ rank_ptr,
+    const int32_t *__restrict__ node_first_inst, int32_t *__restrict__ rank_off, int32_t *__restrict__ node_off, int src_div) {
+    key_pos_fold(s, n_items, nchunks, R, N, rank_ptr, node_first_inst, rank_off, node_off, src_div);
+}
+static __global__ __launch_bounds__(POS_FOLD_THREADS) void key_pos_fold_pair_kernel(const KeySort s0, const KeySort s1, int64_t n_items,
+                                                                             int nchunks, int src_div) {
+    key_pos_fold(blockIdx.y == 0 ? s0 : s1, n_items, nchunks, 0, 0, nullptr, nullptr, nullptr, nullptr, src_div);
+}
+
 // Host side: the launches of one stable counting sort.  hist / base: workspace of nchunks * nkeys
 // ints each.  rank_ptr .. node_off may be null (plain sort: only `off` is produced).
 // hist_ready: an earlier kernel on the stream already wrote the chunk histograms into `hist`.
@@ -240,11 +268,12 @@ static inline const char *stable_sort_launch(const grace_table *table, const int
     const int nchunks = (int)ceil_div(n, PERM_CHUNK);
     int nbits = 0;
     while ((1 << nbits) < nkeys) ++nbits;
-    if (nchunks > 0 && !hist_ready) {
+    const int mode = fold_mode(table, nchunks, nkeys);
+    const bool count_self = nchunks == 1 && mode == 1;   // not worth reading a row of counts, let alone a launch that writes it
+    if (nchunks > 0 && !hist_ready && !count_self) {
         key_hist_kernel<<<nchunks, 64, 0, st>>>(keys, n, nkeys, hist);
         if (hipGetLastError() != hipSuccess) return "key_hist_kernel";
     }
-    const int mode = fold_mode(table, nchunks, nkeys);
     if (mode != 0) {
         const int32_t *super_tot = nullptr;
         if (mode == 2) {  // column sums per super-chunk of rows, into the (otherwise unused) scan buffer
@@ -252,8 +281,9 @@ static inline const char *stable_sort_launch(const grace_table *table, const int
             if (hipGetLastError() != hipSuccess) return "super_sum_kernel";
             super_tot = base;
         }
-        key_pos_fold_kernel<<<nchunks, POS_FOLD_THREADS, 0, st>>>(keys, n, nkeys, hist, nchunks, R, N, rank_ptr, node_first_inst, off,
-                                                    rank_off, node_off, pos, src, nbits, src_div, super_tot);
+        const KeySort s = {keys, nkeys, nbits, count_self ? nullptr : hist, super_tot, off, pos, src};
+        key_pos_fold_kernel<<<nchunks, POS_FOLD_THREADS, 0, st>>>(s, n, nchunks, R, N, rank_ptr, node_first_inst, rank_off, node_off,
+                                                                  src_div);
         if (hipGetLastError() != hipSuccess) return "key_pos_fold_kernel";
         return nullptr;
     }

@@ -394,6 +394,34 @@ def test_send_list_block_edges(nodes, gpus, T, k):
     assert tr[3] == int(((dest // gpus == other) & (dest != R - 1)).sum())
 
 
+@pytest.mark.parametrize("R,T,k", [(1, 1, 1), (8, 1, 64), (5, 8, 64), (64, 170, 3), (512, 256, 2), (513, 256, 2), (6, 57, 9)])
+def test_send_lists_in_one_workgroup(R, T, k):
+    """At most 512 assignments and ranks in one launch: bit for bit the general kernels (separate scans), with several experts
+    of a token on one rank, ids outside the table, and list entries past the ends."""
+    nodes = max(1, R // 4)
+    E = min(256, 2 * R)
+    rng = np.random.default_rng(R + T)
+    ptr, ranks = [0], []
+    for e in range(E):
+        ranks += sorted(rng.choice(R, size=min(R, int(rng.integers(1, 4))), replace=False).tolist())
+        ptr.append(len(ranks))
+    table = grace.GraceTable(E, R, nodes, [r * nodes // R for r in range(R)], [1] * R, ptr, ranks)
+    ti = rng.integers(-2, table.I + 2, size=(T, k)).astype(np.int32)
+    for local_rank in {0, R - 1}:
+        got = [t.cpu().numpy() for t in grace.grace_send_lists(table, local_rank, torch.from_numpy(ti).cuda())]
+        order = [t.cpu().numpy() for t in grace.grace_permute(table, torch.from_numpy(ti).cuda(), None)[:5]]
+        table.set_fold_limits(0, 0)
+        want = [t.cpu().numpy() for t in grace.grace_send_lists(table, local_rank, torch.from_numpy(ti).cuda())]
+        order_want = [t.cpu().numpy() for t in grace.grace_permute(table, torch.from_numpy(ti).cuda(), None)[:5]]
+        table.set_fold_limits()
+        n_rows = int(order_want[2][-1])
+        for g, w in zip(got, want):
+            np.testing.assert_array_equal(g, w)
+        assert (got[1][got[0][-1]:] == -1).all() and (got[3][got[2][-1]:] == -1).all()
+        for i, (g, w) in enumerate(zip(order, order_want)):
+            np.testing.assert_array_equal(g[:n_rows] if i == 1 else g, w[:n_rows] if i == 1 else w)
+
+
 # ------------------------------------------- kernels that a test must reach, with the choice asserted --
 def kernels_of(T, k, d, f, S, I, n_shared=0, dtype="bf16"):
     """Kernels of the gate+up and the down projection on the current device."""
