@@ -31,6 +31,7 @@ from .binding import (  # noqa: F401
     grace_route_permute,
     grace_route_permute_static,
     grace_send_lists,
+    grace_send_lists_fresh,
     grace_shared_ffn,
     grace_shared_ffn_down,
     grace_shared_ffn_up,

@@ -304,10 +304,17 @@ def grace_send_lists(table: GraceTable, local_rank: int, topk_inst: torch.Tensor
     np_, nt = torch.empty(table.N + 1, **i32), torch.empty(T * k, **i32)
     ex = torch.empty(T * k, **i32)
     tr = torch.empty(4, dtype=torch.int64, device=dev)
-    ws = _ws(ws, grace_workspace_bytes(T, table.E, k, table.I), dev)
+    grace_send_lists_fresh(table, local_rank, topk_inst, (rp, rt, np_, nt, ex, tr), ws)
+    return rp, rt, np_, nt, ex, tr
+
+
+def grace_send_lists_fresh(table: GraceTable, local_rank: int, topk_inst: torch.Tensor, out, ws: Optional[torch.Tensor] = None) -> None:
+    """grace_send_lists into the caller's tensors, all of whose entries are written (-1 past the ends of the lists)."""
+    T, k = topk_inst.shape
+    rp, rt, np_, nt, ex, tr = out
+    ws = _ws(ws, grace_workspace_bytes(T, table.E, k, table.I), topk_inst.device)
     _check(load_library().grace_send_lists_fresh(table.handle, local_rank, _dp(topk_inst), T, k, _dp(rp), _dp(rt), _dp(np_),
                                                  _dp(nt), _dp(ex), _dp(tr), _dp(ws), _stream()))
-    return rp, rt, np_, nt, ex, tr
 
 
 def grace_expert_ffn(table: GraceTable, rank: int, xp: torch.Tensor, inst_off: torch.Tensor, T: int, k: int,
