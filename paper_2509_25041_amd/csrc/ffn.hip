@@ -23,7 +23,7 @@
 #include "gemm_bf16_persist.h"
 #include "gemm_common.h"
 #include "gemm_f32.h"
-#include "gemm_f32_mid.h"
+#include "gemm_f32_split.h"
 #include "gemm_stream.h"
 
 namespace grace {
@@ -48,7 +48,7 @@ static int compute_units() {
 
 // The persistent kernel needs the 160 KB of dynamic LDS opted in, once per kernel and device.
 static bool allow_full_lds(const void *kernel, const char *what) {
-    constexpr int MAX_KERNELS = 8, MAX_DEVICES = 64;
+    constexpr int MAX_KERNELS = 24, MAX_DEVICES = 64;
     static std::mutex mu;
     static const void *known[MAX_KERNELS] = {nullptr};
     static bool done[MAX_KERNELS][MAX_DEVICES] = {{false}};
@@ -147,24 +147,46 @@ static Grid mid_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
     const bool exact = g.M_single > 0;   // the shared experts
     return {mid::grid_blocks((exact ? (expected + mid::BM - 1) / mid::BM : expected / mid::BM + g.S) * n_strips, n_cu, exact), mid::THREADS};
 }
+// fp32, batches of more than 64 tokens: the split kernel, whichever the route (they differ in what else can take the launch), but for
+// short K, where the streaming kernel's wavefronts share K and start at once (K = 256 6 us each), and down projections of few tiles (us, streaming
+// kernel / split kernel: 200 rows in 9 segments, K = 2816, N = 548, 110 half tiles 28.5 / 32.8; 500 rows, K = 1388, N = 548, 150 19.0 / 21.0;
+// 100 rows, K = 2816, N = 1024, 160 42.9 / 35.3; 1000 rows, K = 1388, N = 1024, 336 43.1 / 44.6).  Gate+up, K = 548 92 -> 59 us with
+// 1000 rows, 41.8 -> 35.8 with 500 and N = 1388.  Groups that share K: up to one and a half tiles per unit.
 template <bool FUSED_UP>
-static Grid mid_f32_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
-    const int64_t n_strips = (g.N + midf::Shape<FUSED_UP>::BN - 1) / midf::Shape<FUSED_UP>::BN;
-    const int64_t expected = rows.even_only ? rows.m_bound : rows.at(20);
-    return {(std::max<int64_t>((expected / midf::BM + g.S) * n_strips, n_cu) + 63) / 64 * 64, midf::THREADS};
+static int64_t split_tiles(const GemmArgs &g, const Rows &rows, int64_t m) {
+    constexpr int BN = split::Shape<FUSED_UP>::BN;
+    return (m / split::BM + std::min<int64_t>(g.S, m)) * ((g.N + BN - 1) / BN);
+}
+template <bool FUSED_UP>
+static bool split_takes(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
+    if (dt != GRACE_F32 || (route != Route::MID && route != Route::STREAM)) return false;
+    if (route == Route::MID) return true;
+    if (!stream_pieces<4>(rows)) return false;
+    return FUSED_UP ? g.K >= 512 : g.K >= 1024 && 16 * split_tiles<false>(g, rows, rows.at(4)) >= 5 * n_cu;
+}
+template <bool FUSED_UP>
+static int split_groups(const GemmArgs &g, const Rows &rows, int n_cu) {
+    return !FUSED_UP && 2 * split_tiles<false>(g, rows, rows.at(4)) <= 3 * n_cu ? 2 : 1;
+}
+template <bool FUSED_UP>
+static Grid split_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
+    const int64_t tiles = split_tiles<FUSED_UP>(g, rows, rows.even_only ? rows.m_bound : rows.at(20));
+    const int groups = split_groups<FUSED_UP>(g, rows, n_cu);
+    return {(std::max<int64_t>(tiles, 2 / groups * n_cu) + 63) / 64 * 64, 256 * groups};
 }
 // All tiles of the rows that a rank could hold, in whole runs of the XCDs, are one launch at most: their numbers fit 32 bits and so
 // does every grid above (a hot rank's are walked by fewer workgroups).
-template <bool FUSED_UP, typename SHAPE>
+template <bool FUSED_UP, typename SHAPE, int TILE_ROWS>
 static bool mid_tiles_fit(const GemmArgs &g, const Rows &rows) {
     const int64_t n_strips = (g.N + SHAPE::BN - 1) / SHAPE::BN;
-    return launchable({((rows.m_bound / mid::BM + g.S) * n_strips + 63) / 64 * 64, mid::THREADS});
+    return launchable({((rows.m_bound / TILE_ROWS + g.S) * n_strips + 63) / 64 * 64, mid::THREADS});
 }
 template <bool FUSED_UP>
 static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
+    if (split_takes<FUSED_UP>(route, g, dt, rows, n_cu)) return split_grid<FUSED_UP>(g, rows, n_cu);
     if (route == Route::STREAM)
         return dt == GRACE_BF16 ? stream_grid<FUSED_UP, 2>(g, rows, n_cu) : stream_grid<FUSED_UP, 4>(g, rows, n_cu);
-    if (route == Route::MID) return dt == GRACE_BF16 ? mid_grid<FUSED_UP>(g, rows, n_cu) : mid_f32_grid<FUSED_UP>(g, rows, n_cu);
+    if (route == Route::MID) return mid_grid<FUSED_UP>(g, rows, n_cu);
     if (route == Route::PERSIST) return {pers::grid_blocks(n_cu), pers::THREADS};
     if (route == Route::GENERIC) {
         constexpr int BN = FUSED_UP ? 64 : 128;
@@ -222,9 +244,9 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
     return (m / mid::BM + hit) * strips <= n_cu * rounds * (FUSED_UP ? 3 : 2);
 }
 
-// fp32, batches of more than 64 tokens: the 96-row kernel against the streaming kernel, whose pieces of 64 rows and 32 weight rows
-// are a third of its tiles.  Long launches are faster on the 96-row kernel; with few tiles per compute unit that depends on
-// how the rank's rows fall into them, which the host does not know.  Measured over 1332 expert FFNs, each kernel alone (8 to 128
+// fp32, batches of more than 64 tokens: the route of long launches (MID) or of short ones (STREAM).  Both take the split kernel where
+// split_takes says so; MID always does.  The line was drawn for a kernel with the same staging on the fp32 matrix instruction (96 rows x 64 weight
+// rows) against the streaming kernel, whose pieces of 64 rows and 32 weight rows are a third of its tiles.  Measured then over 1332 expert FFNs, each kernel alone (8 to 128
 // experts on 1 to 4 ranks, Zipf-shaped shares, 65 to 5000 tokens, k = 2 and 8, d x f from 128 x 256 to 2048 x 2048, also 548 and
 // 1388, whose rows are no whole lines), and 234 of shared experts:
 //  * five tiles per compute unit at the even share and K of 20 steps or more: streaming 66.3 ms, 96 rows 57.1 ms, in 170 expert
@@ -236,9 +258,10 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
 // In all 226.3 ms with the streaming kernel, 206.4 with 96 rows, 209.3 with this rule.
 template <bool FUSED_UP>
 static bool mid_f32_is_faster(const GemmArgs &g, const Rows &rows, int n_cu) {
-    const int64_t strips = (g.N + midf::Shape<FUSED_UP>::BN - 1) / midf::Shape<FUSED_UP>::BN;
-    const int64_t work = rows.at(4) * strips, round = (int64_t)n_cu * midf::BM;   // of one tile per compute unit
-    const bool long_k = g.K >= 20 * midf::BK;
+    constexpr int COLS = FUSED_UP ? 32 : 64;
+    const int64_t strips = (g.N + COLS - 1) / COLS;
+    const int64_t work = rows.at(4) * strips, round = (int64_t)n_cu * 96;   // of one tile per compute unit
+    const bool long_k = g.K >= 640;
     if (long_k && work >= 5 * round) return true;
     if (FUSED_UP) return (g.S >= 8 && g.N >= 2048 && g.K >= 512) || (g.S >= 16 && g.N >= 1024 && long_k && 2 * work >= round);
     return g.S >= 8 && g.N >= 2048 && long_k && work >= 2 * round;
@@ -261,11 +284,11 @@ static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int
         const bool stream = stream_ok<4>(g) && fits(Route::STREAM);
         // output rows of whole 16-byte vectors; K segments of any length (shared experts' down projection, f = 1388, two of them, d =
         // 1024, 65 to 5000 tokens: vector ALUs 329 to 577 us, 96 rows 38 to 289 us)
-        const bool mid = rows.max_rows > strm::MAX_ROWS && g.N % 4 == 0 && stream_ok<4>(g, 4) && mid_tiles_fit<FUSED_UP, midf::Shape<FUSED_UP>>(g, rows);
+        const bool mid = rows.max_rows > strm::MAX_ROWS && g.N % 4 == 0 && stream_ok<4>(g, 4) && mid_tiles_fit<FUSED_UP, split::Shape<FUSED_UP>, split::BM>(g, rows);
         if (mid && (!stream || mid_f32_is_faster<FUSED_UP>(g, rows, n_cu))) return Route::MID;
         return stream ? Route::STREAM : Route::VECTOR_F32;
     }
-    const bool mid_ok = stream_ok<2>(g, 8) && mid_tiles_fit<FUSED_UP, mid::Shape<FUSED_UP>>(g, rows);
+    const bool mid_ok = stream_ok<2>(g, 8) && mid_tiles_fit<FUSED_UP, mid::Shape<FUSED_UP>, mid::BM>(g, rows);
     if (rows.max_rows <= strm::MAX_ROWS && stream_ok<2>(g) && fits(Route::STREAM)) {
         const int64_t busy = std::max<int64_t>(1, std::min<int64_t>(g.S, rows.at(12)));
         const int64_t tiles = busy * ((g.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN);
@@ -299,16 +322,23 @@ static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, hi
 }
 
 template <bool FUSED_UP>
-static void launch_mid_f32(const GemmArgs &g, const Grid &l, int n_cu, hipStream_t st) {
-    const int n_strips = (g.N + midf::Shape<FUSED_UP>::BN - 1) / midf::Shape<FUSED_UP>::BN;
-    if constexpr (!FUSED_UP) {
-        if (g.kseg_len < g.K) {
-            midf::gemm_f32_mid_kernel<false, true, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
-            return;
-        }
+static int launch_split(const GemmArgs &g, const Grid &l, int n_cu, hipStream_t st, const char *what) {
+    const int n_strips = (g.N + split::Shape<FUSED_UP>::BN - 1) / split::Shape<FUSED_UP>::BN;
+    auto launch = [&](auto *kernel) {
+        if (!allow_full_lds((const void *)kernel, what)) return (int)GRACE_EHIP;
+        kernel<<<(unsigned)l.groups, l.threads, l.threads / 256 * split::GROUP_BYTES, st>>>(g, n_strips, n_cu);
+        return (int)GRACE_OK;
+    };
+    if constexpr (FUSED_UP) {
+        return g.S <= 64 ? launch(&split::gemm_f32_split_kernel<true, false, 1, 1>) : launch(&split::gemm_f32_split_kernel<true, false, 4, 1>);
+    } else {
+        auto of = [&](auto groups) {
+            constexpr int G = decltype(groups)::value;
+            if (g.kseg_len < g.K) return launch(&split::gemm_f32_split_kernel<false, true, 1, G>);
+            return g.S <= 64 ? launch(&split::gemm_f32_split_kernel<false, false, 1, G>) : launch(&split::gemm_f32_split_kernel<false, false, 4, G>);
+        };
+        return l.threads == 256 ? of(std::integral_constant<int, 1>{}) : of(std::integral_constant<int, 2>{});
     }
-    if (g.S <= 64) midf::gemm_f32_mid_kernel<FUSED_UP, false, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
-    else midf::gemm_f32_mid_kernel<FUSED_UP, false, 4><<<(unsigned)l.groups, l.threads, 0, st>>>(g, n_strips, n_cu);
 }
 
 template <bool FUSED_UP>
@@ -332,12 +362,14 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipS
     const Route route = route_gemm<FUSED_UP>(g, dt, rows, n_cu);
     const Grid l = grid_of<FUSED_UP>(route, g, dt, rows, n_cu);
     if (!launchable(l)) return fail(GRACE_ESHAPE, "%s: grid too large", what);
-    if (route == Route::STREAM) {
+    if (split_takes<FUSED_UP>(route, g, dt, rows, n_cu)) {
+        const int rc = launch_split<FUSED_UP>(g, l, n_cu, st, what);
+        if (rc != GRACE_OK) return rc;
+    } else if (route == Route::STREAM) {
         if (dt == GRACE_BF16) launch_stream<FUSED_UP, 2>(g, rows, l, st);
         else launch_stream<FUSED_UP, 4>(g, rows, l, st);
     } else if (route == Route::MID) {
-        if (dt == GRACE_BF16) launch_mid<FUSED_UP>(g, l, n_cu, st);
-        else launch_mid_f32<FUSED_UP>(g, l, n_cu, st);
+        launch_mid<FUSED_UP>(g, l, n_cu, st);
     } else if (route == Route::PERSIST) {
         // persistent large-tile kernel: one workgroup per compute unit, 160 KB of dynamic LDS
         using SH = pers::Shape<FUSED_UP>;

@@ -1,0 +1,441 @@
+// fp32 grouped GEMM on the bf16 matrix cores, for batches of more than 64 tokens: every fp32 value is split into three bf16 values whose
+// sum it is, and a product is the sum of the six partial products down to 2^-18 of it.
+//
+// x = x1 + x2 + x3 exactly, each part x's next 8 bits (rounded to nearest, so the parts have signs of their own); a product a b is
+// a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1), each of them exact in fp32, and what is left out, about 2^-26 of it, is less than the
+// rounding of one fp32 product.  The leading products have accumulators of their own, so what an addition rounds away is a part of
+// their sum once per 32 K, and of the others 2^-8 of that.  Error of expert FFNs against 64 bits (2-norm; the fp32 matrix
+// instruction with its chains of K / 16 -> this kernel): d = 1024, f = 2816 6.4e-7 -> 3.8e-7, d = 2048, f = 768 6.5e-7 ->
+// 4.5e-7, d = 548, f = 1388 4.6e-7 -> 3.9e-7.  A row whose largest value lies outside 2^-40 .. 2^60 (or is infinite) sends its
+// tiles to the fp32 instruction; NaNs pass through the parts.
+//
+// Bound by what the fp32 instruction is not: six bf16 instructions of 16 cycles take 96 for what takes that one 256, so what is left
+// is the split, the LDS and above all the operands' way to the compute units (a tile of 80 x 128 has 25 operations per byte).
+// Hence: values are split once, on their way to LDS (three planes, 1.5 times the bytes), between the matrix instructions of the step before
+// (multiplied first and split then 114 instead of 100 us below); a step's loads are issued as soon as the registers they land in have been
+// split, so they have AHEAD whole steps; two weight fragments per wavefront share each activation fragment's read where there
+// are tiles enough.  80 rows: two groups of four wavefronts fill the LDS.
+// Where a launch's tiles are few, K long (down projections), the two groups of a compute unit share a tile, each with half of K (d =
+// 1024, f = 2816, 1000 rows in 9 segments 84 -> 80 us, 300 rows 46 -> 38, 100 rows 46 -> 35, 2000 rows in 16 107 -> 91 us).
+//
+// d = 1024, f = 2816, cold weights, fp32 instruction (96 x 64 tiles, or streamed) -> this kernel, us: 1000 rows in 9 segments, gate+up 161 ->
+// 106, down 92 -> 80; 300 rows 62 -> 48, 62 -> 38; 2000 rows in 16 segments 253 -> 184, 159 -> 91; 16000 rows 1633 -> 1079 (171
+// TFLOP/s, the fp32 instruction's own peak is 157), 793 -> 553.  70 rows, bound by the weights (207 MB), 45 -> 47.
+#pragma once
+#include "bf16.h"
+#include "gemm_bf16_mid.h"
+
+namespace grace {
+namespace split {
+
+constexpr int BM = 80, BK = 32;   // a step is one 128-byte line of fp32 per row
+constexpr int MAX_MF = BM / 16, B_WAVE_ROWS = 32;
+constexpr int A_PLANE = BM * BK * 2, B_PLANE = B_WAVE_ROWS * BK * 2;
+constexpr int BUFFER_BYTES = 3 * (A_PLANE + 4 * B_PLANE), GROUP_BYTES = 2 * BUFFER_BYTES;   // LDS of four wavefronts
+static_assert(2 * GROUP_BYTES <= 160 * 1024, "two groups per compute unit");
+
+// Magnitudes up to which a row's largest value may go for the split: outside, a partial product or the third part of a value could leave
+// the range of normal numbers, and an infinity has no parts.  Tiles with such a row take the fp32 matrix instruction.
+constexpr uint32_t MAX_BITS = (uint32_t)(127 + 60) << 23, MIN_BITS = (uint32_t)(127 - 40) << 23;
+
+template <bool FUSED_UP>
+struct Shape {
+    static constexpr int BN = FUSED_UP ? 64 : 128;    // output columns of a whole tile
+};
+
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+
+// bytes from a plane's start: two rows of 64 bytes per 128-byte line, the 16-byte chunks of a line permuted (no bank conflicts)
+__device__ __forceinline__ int chunk_at(int row, int c) {
+    const int line = row >> 1;
+    return line * 128 + ((((row & 1) * 4 + c) ^ (line & 7)) * 16);
+}
+
+// x = hi + mid + lo, each rounded to bf16: the remainders are exact, and 24 bits fit three times 8.
+__device__ __forceinline__ void split2(float x, float y, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    hi = pack_bf16x2(x, y);
+    x -= bf16_lo_to_f32(hi);
+    y -= bf16_hi_to_f32(hi);
+    mid = pack_bf16x2(x, y);
+    x -= bf16_lo_to_f32(mid);
+    y -= bf16_hi_to_f32(mid);
+    lo = pack_bf16x2(x, y);
+}
+
+// The tile without splitting: fragments straight from memory, no look-ahead.
+template <bool FUSED_UP, bool SEG_K, int MF, int NJ>
+__device__ __forceinline__ void tile_by_f32(const GemmArgs &g, __amdgpu_buffer_rsrc_t a_rsrc, __amdgpu_buffer_rsrc_t b0_rsrc, __amdgpu_buffer_rsrc_t b1_rsrc,
+                                            int rows, int cols, int lane, f32x4_t (&acc)[MF][NJ]) {
+    const int r = lane & 15, q = lane >> 4;
+    f32x4_t part[4][MF][NJ];   // chains of K / 16 additions
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) part[v][i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int k0 = 0; k0 < g.K; k0 += 16) {
+        const int k = k0 + 4 * q;
+        const uint32_t none = k < g.K ? 0u : NO_DATA;
+        const uint32_t kb = none ? none : (uint32_t)((SEG_K ? koff(g, k) : (int64_t)k) * 4);
+        f32x4_t fb[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int n = FUSED_UP ? (NJ == 2 ? r : r & 7) : j * 16 + r;
+            const uint32_t off = n < cols ? (uint32_t)n * (uint32_t)(g.ldb * 4) : NO_DATA;
+            // (both matrices' loads for gate+up with one fragment, whose halves are 8 rows of each)
+            fb[j] = __builtin_bit_cast(f32x4_t, load16(FUSED_UP && j == 1 ? b1_rsrc : b0_rsrc, offset_with(off, kb), 0));
+            if constexpr (FUSED_UP && NJ == 1) {
+                const f32x4_t up = __builtin_bit_cast(f32x4_t, load16(b1_rsrc, offset_with(off, kb), 0));
+                fb[j] = r >= 8 ? up : fb[j];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            const int row = i * 16 + r;
+            const uint32_t off = row < rows ? (uint32_t)row * (uint32_t)(g.lda * 4) : NO_DATA;
+            const f32x4_t fa = __builtin_bit_cast(f32x4_t, load16(a_rsrc, offset_with(off, none ? none : (uint32_t)k * 4u), 0));
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) part[v][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][v], fa[v], part[v][i][j], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]);
+}
+
+// MF: activation fragments of 16 rows.  NJ: weight fragments per wavefront, 2, or 1 for half a tile's weight rows (gate+up: then 8
+// rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K axis is cut in segments.
+template <bool FUSED_UP, bool SEG_K, int K_GROUPS, int MF, int NJ>
+__device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int rotation, char *smem) {
+    constexpr int AHEAD = MF > 3 ? 2 : 4;   // steps in flight (even)
+    constexpr int AL = MF / 2;              // activation loads of 16 bytes per thread and step: 32 rows each
+    constexpr bool HALF = MF % 2 != 0;      // and one of 8 bytes for the last 16 rows
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));           // what follows from it stays out of the kernel's loop over tiles
+    const int group = K_GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+    tid &= 255;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, q = lane >> 4;
+    const int nk = ((g.K + BK - 1) / BK + K_GROUPS - 1) / K_GROUPS;   // steps of each group
+    const int k_begin = group * nk * BK, k_end = k_begin + nk * BK;
+    char *const all = smem;
+    smem += group * GROUP_BYTES;
+
+    // ---- load sources (offsets without data give zeros: past the rows, past N, past K) ----
+    const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 4);
+    const int row_of = tid >> 3, chunk = tid & 7;
+    uint32_t a_off[AL];
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+        const int row = i * 32 + row_of;
+        a_off[i] = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 4) + (uint32_t)chunk * 16u : NO_DATA;
+    }
+    const int h_row = AL * 32 + (tid >> 4), h_chunk = tid & 15;
+    const uint32_t h_off = m0 + h_row < m_end ? (uint32_t)h_row * (uint32_t)(g.lda * 4) + (uint32_t)h_chunk * 8u : NO_DATA;
+    const int wn = n0 + wave * (FUSED_UP ? 8 : 16) * NJ;   // first output column of the wavefront
+    const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 4;
+    const auto b0_rsrc = rsrc_of((const char *)g.B0 + b_first);
+    const auto b1_rsrc = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
+    const int b_row = lane >> 3;
+    uint32_t b_off[2 * NJ];   // FUSED_UP: the first half of the rows gate, the second up
+#pragma unroll
+    for (int i = 0; i < 2 * NJ; ++i) {
+        const int n = FUSED_UP ? (i % NJ) * 8 + b_row : i * 8 + b_row;
+        b_off[i] = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 4) + (uint32_t)chunk * 16u : NO_DATA;
+    }
+    char *const sb = smem + 3 * A_PLANE + wave * 3 * B_PLANE;
+    KSegWalk walk{k_begin + chunk * 4};
+    // places in a plane: this thread's loads', the fragments' (16 rows, 8 lines, keep the order of the chunks)
+    const int a_at = chunk_at(row_of, chunk >> 1) + (chunk & 1) * 8, h_at = chunk_at(h_row, h_chunk >> 2) + (h_chunk & 3) * 4;
+    const int b_at[2] = {chunk_at(b_row, chunk >> 1) + (chunk & 1) * 8, chunk_at(8 + b_row, chunk >> 1) + (chunk & 1) * 8};
+    const int frag_at = chunk_at(r, q);
+
+    u32x2_t rh[AHEAD];
+    u32x4_t ra[AHEAD][AL], rb[AHEAD][2 * NJ];
+    f32x4_t acc[MF][NJ], low[MF][NJ];   // sums of the products of the leading parts; of the others, 2^-8 of them and less
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = low[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    float a_max[AL], h_max = 0.0f, b_max[2 * NJ];     // largest magnitudes that this thread has seen of its rows
+#pragma unroll
+    for (int i = 0; i < AL; ++i) a_max[i] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 2 * NJ; ++i) b_max[i] = 0.0f;
+
+    // loads of one step: K, whether there is data, then one load per slot (A: 0 .. AL - 1, the half one, B)
+    int k0 = k_begin + (SEG_K ? 0 : rotation % nk * BK), left = nk, k_load = 0;   // K of the next loads and how many there are (scalar)
+    uint32_t a_none = 0, h_none = 0, b_add = 0;
+    auto next_loads = [&]() {
+        const int k = k0 + chunk * 4;
+        a_none = left > 0 && k < g.K ? 0u : NO_DATA;
+        if (HALF) h_none = left > 0 && k0 + h_chunk * 2 < g.K ? 0u : NO_DATA;   // (K is a multiple of 4)
+        b_add = SEG_K ? walk.next(k, g.K, g.kseg_len, g.kseg_stride, BK, 4) : a_none;
+        k_load = k0 * 4;
+        --left;
+        k0 = SEG_K || k0 + BK != k_end ? k0 + BK : k_begin;
+    };
+    auto load_a = [&](int set, int i) { ra[set][i] = load16(a_rsrc, a_off[i] | a_none, (uint32_t)k_load); };
+    auto load_h = [&](int set) { rh[set] = __builtin_amdgcn_raw_buffer_load_b64(a_rsrc, (int)(h_off | h_none), k_load, 0); };
+    auto load_b = [&](int set, int i) {
+        rb[set][i] = load16(FUSED_UP && i >= NJ ? b1_rsrc : b0_rsrc, SEG_K ? offset_with(b_off[i], b_add) : b_off[i] | b_add, (uint32_t)k_load);
+    };
+    // The values of a step, two at a time, in four stages of about three vector instructions; behind every second pair (or the half
+    // load's one) the parts go to LDS.
+    constexpr int PAIRS = 2 * AL + HALF + 4 * NJ, STAGES = 4 * PAIRS;
+    float x, y;
+    uint2 hi, mid, lo;
+    auto stage = [&](int s, int set, int buf) {
+        const int pair = s / 4, is_b = pair >= 2 * AL + HALF, v = is_b ? pair - 2 * AL - HALF : pair, i = v >> 1;
+        const bool half = HALF && pair == 2 * AL, second = !half && (v & 1);
+        float &most = half ? h_max : is_b ? b_max[i] : a_max[is_b || half ? 0 : i];
+        uint32_t &h = second ? hi.y : hi.x, &m = second ? mid.y : mid.x, &l = second ? lo.y : lo.x;
+        if (s % 4 == 0) {
+            if (half) {
+                x = __uint_as_float(rh[set][0]), y = __uint_as_float(rh[set][1]);
+            } else {
+                const u32x4_t w = is_b ? rb[set][i] : ra[set][is_b ? 0 : i];
+                x = __uint_as_float(w[second ? 2 : 0]), y = __uint_as_float(w[second ? 3 : 1]);
+            }
+            asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(x), "v"(y));
+            h = pack_bf16x2(x, y);
+        } else if (s % 4 == 1) {
+            x -= bf16_lo_to_f32(h);
+            y -= bf16_hi_to_f32(h);
+            // the registers are free: on to the step AHEAD of this one
+            if (half) load_h(set);
+            else if (second && is_b) load_b(set, i);
+            else if (second) load_a(set, is_b ? 0 : i);
+        } else if (s % 4 == 2) {
+            m = pack_bf16x2(x, y);
+            x -= bf16_lo_to_f32(m);
+        } else {
+            y -= bf16_hi_to_f32(m);
+            l = pack_bf16x2(x, y);
+            char *const base = is_b ? sb + buf * BUFFER_BYTES : smem + buf * BUFFER_BYTES;
+            const int plane = is_b ? B_PLANE : A_PLANE;
+            if (half) {
+                char *const at = base + h_at;
+                *(uint32_t *)at = hi.x;
+                *(uint32_t *)(at + plane) = mid.x;
+                *(uint32_t *)(at + 2 * plane) = lo.x;
+            } else if (second) {
+                char *const at = base + (is_b ? b_at[i & 1] + (i >> 1) * 16 * BK * 2 : a_at + i * 32 * BK * 2);
+                *(uint2 *)at = hi;
+                *(uint2 *)(at + plane) = mid;
+                *(uint2 *)(at + 2 * plane) = lo;
+            }
+        }
+    };
+    // One step: LDS buffer `buf` is multiplied while the other one gets the parts of register set `set`.  A matrix instruction
+    // holds its unit for 16 cycles, as long as four vector instructions theirs, and a wavefront issues in order, so the two are
+    // dealt out one to one; the compiler's own order multiplies first and splits then (MEASURE_ORDER).
+    auto step_body = [&](int buf, int set) {
+        constexpr int MFMAS = 6 * MF * NJ;
+        const char *const a = smem + buf * BUFFER_BYTES, *const b = sb + buf * BUFFER_BYTES;
+        bf16x8_t fb[NJ][3], fa[2][2][3];
+        auto read_a = [&](int f, int p) { fa[(f >> 1) & 1][f & 1][p] = *(const bf16x8_t *)(a + p * A_PLANE + f * 16 * BK * 2 + frag_at); };
+#pragma unroll
+        for (int p = 2; p >= 0; --p) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) fb[j][p] = *(const bf16x8_t *)(b + p * B_PLANE + j * 16 * BK * 2 + frag_at);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) read_a(f, 2 - p);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        int s = 0, m = 0;
+#pragma unroll
+        for (int f0 = 0; f0 < MF; f0 += 2) {
+            const int fn = MF - f0 < 2 ? 1 : 2;   // fragments of this round
+#pragma unroll
+            for (int t = 0; t < 6; ++t) {         // the smallest products first
+                constexpr int PB[6] = {2, 1, 0, 1, 0, 0}, PA[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (u >= fn) continue;
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) {
+                        f32x4_t &sum = t == 5 ? acc[f0 + u][j] : low[f0 + u][j];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][PB[t]], fa[(f0 >> 1) & 1][u][PA[t]], sum, 0, 0, 0);
+                        ++m;
+                        // the next round's fragments, one read for each of the first products
+                        const int next = t * fn * NJ + u * NJ + j;
+                        if (next < 6 && f0 + 2 + (next & 1) < MF) read_a(f0 + 2 + (next & 1), next >> 1);
+#pragma unroll
+                        for (; s * MFMAS < m * STAGES; ++s) stage(s, set, buf ^ 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+        }
+    };
+    // step s multiplies LDS buffer s % 2, splits and stores step s + 1's data and loads step s + 1 + AHEAD's in their place
+    auto step = [&](int p) {
+        next_loads();
+        __builtin_amdgcn_sched_barrier(0);
+        step_body(p & 1, (p + 1) % AHEAD);
+        __syncthreads();
+    };
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p) {
+        next_loads();
+#pragma unroll
+        for (int i = 0; i < AL; ++i) load_a(p, i);
+        if (HALF) load_h(p);
+#pragma unroll
+        for (int i = 0; i < 2 * NJ; ++i) load_b(p, i);
+    }
+    next_loads();
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s) stage(s, 0, 0);
+    __syncthreads();
+    int s0 = 0;
+    for (; s0 + AHEAD <= nk; s0 += AHEAD) {
+#pragma unroll
+        for (int p = 0; p < AHEAD; ++p) step(p);
+    }
+#pragma unroll
+    for (int p = 0; p < AHEAD - 1; ++p) {
+        if (s0 + p >= nk) break;
+        step(p);
+    }
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] += low[i][j];
+
+    // ---- rows out of the split's range (the lanes of a row are neighbours) ----
+    bool out_of_range = false;
+    auto look = [&](float most, int lanes) {
+#pragma unroll
+        for (int o = 1; o < lanes; o <<= 1) most = fmaxf(most, __shfl_xor(most, o, 64));
+        const uint32_t bits = __float_as_uint(most);
+        out_of_range |= bits > MAX_BITS || (bits != 0u && bits < MIN_BITS);
+    };
+#pragma unroll
+    for (int i = 0; i < AL; ++i) look(a_max[i], 8);
+#pragma unroll
+    for (int i = 0; i < 2 * NJ; ++i) look(b_max[i], 8);
+    if (HALF) look(h_max, 16);
+    // ---- the other group's sums (the last step ended with a barrier) ----
+    uint64_t *const found = (uint64_t *)all;
+    const uint64_t mine = __ballot(out_of_range);
+    if (lane == 0) found[group * 4 + wave] = mine;
+    [[maybe_unused]] f32x4_t *const sums = (f32x4_t *)(all + GROUP_BYTES) + (wave * MF * NJ) * 64 + lane;
+    if (group != 0) {
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) sums[(i * NJ + j) * 64] = acc[i][j];
+    }
+    __syncthreads();
+    if (group != 0) return;
+    if constexpr (K_GROUPS > 1) {
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] += sums[(i * NJ + j) * 64];
+    }
+    uint64_t any = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * K_GROUPS; ++i) any |= found[i];
+    if (any) tile_by_f32<FUSED_UP, SEG_K, MF, NJ>(g, a_rsrc, b0_rsrc, b1_rsrc, m_end - m0, g.N - wn, lane, acc);
+
+    // ---- epilogue: element v of lane l of a fragment is output column 4 * (l / 16) + v, row l % 16 ----
+    float *const out = (float *)g.out;
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+        const int row = m0 + i * 16 + r;
+        float up[4];
+        if constexpr (FUSED_UP) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) up[v] = NJ == 2 ? acc[i][NJ - 1][v] : __shfl_xor(acc[i][0][v], 32, 64);
+        }
+        if (row >= m_end) continue;
+#pragma unroll
+        for (int j = 0; j < (FUSED_UP ? 1 : NJ); ++j) {
+            const int col = wn + j * 16 + 4 * q;
+            if (col >= g.N || (FUSED_UP && NJ == 1 && q >= 2)) continue;
+            float h[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                h[v] = acc[i][j][v];
+                if (FUSED_UP) h[v] = h[v] / (1.0f + expf(-h[v])) * up[v];
+            }
+            float *const o = out + (int64_t)row * g.ldo + col;
+            if (g.N % 4 == 0) {
+                *(float4 *)o = make_float4(h[0], h[1], h[2], h[3]);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (col + v < g.N) o[v] = h[v];
+            }
+        }
+    }
+}
+
+// SEG_PER_LANE: 1 for up to 64 row segments, 4 for up to 256.  Pieces of a segment have one size, and tiles are numbered and dealt to the
+// XCDs as gemm_bf16_mid_kernel's.  Half
+// tiles, and lower pieces, while there is a place for each (the places: two workgroups per compute unit, one if its groups share K).
+template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE, int K_GROUPS>
+__global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_kernel(const GemmArgs g, int n_strips, int n_cu) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    StaleRows stale;
+    if (!FUSED_UP) stale = stale_rows(g);   // in flight during the work, used at the end
+    for (int b = (int)blockIdx.x;;) {       // once, unless the rank has far more rows than its share
+        int lane = (int)threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));      // the table is read again each time: kept, it would cost the tile its registers
+        SegTable<SEG_PER_LANE> segs;
+        segs.load(g, lane);
+        segs.cut(lane, BM);
+        const int places = 2 / K_GROUPS * n_cu;   // workgroups that run at once
+        const bool halves = 2 * segs.total * n_strips <= places;
+        if (halves) {
+            if (2 * segs.count(32) * n_strips <= places) segs.cut(lane, 32);
+            else if (2 * segs.count(48) * n_strips <= places) segs.cut(lane, 48);
+        }
+        const int strips = halves ? 2 * n_strips : n_strips, total = segs.total * strips;
+        const int blocks = (total + 63) & ~63;
+        if (b >= blocks) break;
+        const int t = mid::of_runs(b, total);
+        const bool again = b >= (int)gridDim.x;
+        b += (int)gridDim.x;
+        const bool more = b < blocks;
+        if (t < 0) {
+            if (more) continue;
+            break;
+        }
+        const Segment s = segs.segment(t / strips, lane);
+        const int in_seg = t - s.first_tile * strips, strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
+        const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
+        const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows);
+        const int n0 = strip * (halves ? Shape<FUSED_UP>::BN / 2 : Shape<FUSED_UP>::BN);
+        const int rotation = (s.slot * strips + strip) / 4;
+        if (again) __syncthreads();   // the tile before has been read
+        auto tile = [&](auto nj) {
+            constexpr int NJ = decltype(nj)::value;
+            switch ((m_end - m0 + 15) >> 4) {
+                case 1:
+                case 2: tile_body<FUSED_UP, SEG_K, K_GROUPS, 2, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
+                case 3: tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
+                case 4: tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
+                case 5: tile_body<FUSED_UP, SEG_K, K_GROUPS, 5, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
+                default: break;   // no rows
+            }
+        };
+        if (n0 < g.N) {
+            if (halves) tile(std::integral_constant<int, 1>{});
+            else tile(std::integral_constant<int, 2>{});
+        }
+        if (!more) break;
+    }
+    if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
+}
+
+}  // namespace split
+}  // namespace grace

@@ -1,5 +1,5 @@
 // MFMA grouped GEMM that reads both operands straight into registers: few rows per segment (decode batches, bf16 and
-// fp32), and fp32 of any size whose launch is not long enough for gemm_f32_mid.h or whose output rows are no whole 16-byte vectors.
+// fp32), and fp32 of any size whose K or tiles are too few for gemm_f32_split.h.
 //
 // A workgroup owns 32 weight rows of one segment (gate+up: 16 of each matrix, i.e. 16 output columns; down: 32
 // columns) and up to 64 of the segment's rows, and its wavefronts split K, so that the 32 weight rows, which lie
@@ -26,8 +26,8 @@
 // fp32, any number of rows: d = 1024, f = 2816, 8 segments and 977 rows in all, up / down projection 351 / 492 us on the
 // vector ALUs -> 175 / 108 us (64 / 52 TFLOP/s; the matrix cores are busy 45 % of the time).  What bounds it is the
 // address unit: in the MFMA's layout consecutive lanes lie in different rows, so a load touches a line per lane.
-// Register depths of 3 and 4 steps change nothing, pieces of 32 rows take 198 / 116 us; staged through LDS 156 / 96 us
-// (gemm_f32_mid.h).  Wavefronts that start at different steps of their part of K, as the 96-row kernel's tiles do, are even (16
+// Register depths of 3 and 4 steps change nothing, pieces of 32 rows take 198 / 116 us; staged through LDS 156 / 96 us, on the
+// bf16 matrix cores about 105 / 80 us (gemm_f32_split.h).  Wavefronts that start at different steps of their part of K, as the 96-row kernel's tiles do, are even (16
 // tokens, 12.8 / 7.8 -> 12.4 / 8.2 us).  Error against 64 bits
 // 6.4e-7, half of the vector kernel's 1.3e-6 (shorter chains of additions).
 #pragma once

@@ -237,9 +237,55 @@ def ffn_rows_of_segments(seg_rows, T, k, d, f, dt, first=0, I=None, S=None):
     ([0, 1, 95, 96, 97] * 14 + [2154], 6200, 1, 1280, 640, ("mid", "mid")),    # more segments than lanes
 ])
 def test_f32_long_launches(seg_rows, T, k, d, f, want):
-    """fp32 in tiles of 96 rows and 64 weight rows."""
+    """fp32 in tiles of up to 80 rows and 128 weight rows."""
     assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows), dtype="f32") == want
     ffn_rows_of_segments(seg_rows, T, k, d, f, "f32")
+
+
+@pytest.mark.parametrize("seg_rows,T,k,d,f", [
+    ([16, 17, 33, 49, 65, 80, 81, 161], 260, 2, 516, 515),     # pieces of two to five fragments; N no multiple of 4; K of 16 steps and 4
+    ([120, 0, 1, 70, 3, 9, 200, 64], 250, 2, 1024, 1100),      # down: few tiles, the groups share a K of 34 steps and 12
+    ([90, 300, 10, 0, 0, 0, 0, 0], 210, 2, 2052, 2820),        # both projections; an odd number of steps
+    ([70] * 70, 2500, 2, 512, 1024),                           # more segments than lanes
+])
+@pytest.mark.parametrize("scale", [1.0, 1e-15, 1e20])          # inside the split's range and on either side of it
+def test_f32_split_kernel(seg_rows, T, k, d, f, scale):
+    if scale != 1.0 and len(seg_rows) > 8:
+        pytest.skip("the range does not depend on the number of segments")
+    S = len(seg_rows)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    table = grace.GraceTable(S, 1, 1, [0], [1], list(range(S + 1)), [0] * S)
+    x = scale * torch.randn((T * k, d), generator=gen, device="cuda")
+    wg, wu, wd = (0.05 * torch.randn(n, generator=gen, device="cuda") for n in ((S, f, d), (S, f, d), (S, d, f)))
+    if scale > 1.0:
+        wu /= scale   # (the hidden activation stays finite)
+    off = np.concatenate([[0], np.cumsum(seg_rows)]).astype(np.int32)
+    y = grace.grace_expert_ffn(table, 0, x, torch.from_numpy(off).cuda(), T, k, wg, wu, wd)
+    for s in range(S):
+        if off[s] == off[s + 1]:
+            continue
+        xs = x[off[s]:off[s + 1]].double()
+        h = torch.nn.functional.silu(xs @ wg[s].double().T) * (xs @ wu[s].double().T)
+        want = h @ wd[s].double().T
+        assert rel_err(y[off[s]:off[s + 1]].cpu().numpy().astype(np.float64), want.cpu().numpy()) <= TOL["f32"], s
+
+
+def test_f32_split_kernel_infinities_and_nans():
+    """An infinity or a NaN in one row: that row is what fp32 arithmetic gives, the others are as without it."""
+    T, d, f = 200, 1024, 2816
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    table = grace.GraceTable(1, 1, 1, [0], [1], [0, 1], [0])
+    x = torch.randn((T, d), generator=gen, device="cuda")
+    wg, wu, wd = (0.05 * torch.rand(n, generator=gen, device="cuda") for n in ((1, f, d), (1, f, d), (1, d, f)))
+    off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    plain = grace.grace_expert_ffn(table, 0, x, off, T, 1, wg, wu, wd)
+    x[7, 100] = float("inf")
+    x[90, 3] = float("nan")
+    x[150] = 0.0
+    y = grace.grace_expert_ffn(table, 0, x, off, T, 1, wg, wu, wd)
+    assert torch.isposinf(y[7]).all() and torch.isnan(y[90]).all() and not y[150].any()
+    rest = [i for i in range(T) if i not in (7, 90, 150)]
+    assert rel_err(y[rest].cpu().numpy().astype(np.float64), plain[rest].cpu().numpy().astype(np.float64)) <= TOL["f32"]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
