@@ -316,6 +316,15 @@ int grace_expert_ffn_down_share(const grace_table *table, int32_t rank, const in
                                 int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state,
                                 void *ws, void *stream);
 
+/* grace_permute_rows followed by grace_expert_ffn_up_share on the rows it has moved, as one call: for prefill batches, where the
+ * large-tile kernel takes the projection (GRACE_KERNEL_PERSIST of grace_ffn_kernel), that launch reads the
+ * rank's rows from x and moves all rows to xp as it runs.  Same results as the two calls, bit for bit.
+ * DEVICE: x [T,d]; perm_pos, perm_src [T*k] and inst_off of grace_permute / grace_route_permute called with x == NULL; xp [T*k,d]. */
+int grace_expert_ffn_up_share_scatter(const grace_table *table, int32_t rank, const void *x, const int32_t *perm_pos,
+                                      const int32_t *perm_src, void *xp, const int32_t *inst_off, int32_t T, int32_t k, int32_t d,
+                                      int32_t f, grace_dtype dt, const void *w_gate, const void *w_up, int32_t *state, void *ws,
+                                      void *stream);
+
 /* Always-on shared experts evaluated on all T token rows and summed:
  *     y_shared[t] = sum_s W_down[s] ( silu(W_gate[s] x[t]) * (W_up[s] x[t]) ).
  * DEVICE: x [T,d]; w_gate, w_up [n_shared,f,d]; w_down [n_shared,d,f];

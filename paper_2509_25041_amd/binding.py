@@ -20,7 +20,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_table_instances", "grace_table_local_experts", "grace_table_set_fold_limits", "grace_workspace_bytes",
            "grace_route",
            "grace_permute", "grace_permute_rows", "grace_route_permute", "grace_route_permute_static", "grace_send_lists", "grace_send_lists_fresh", "grace_expert_ffn", "grace_expert_ffn_up",
-           "grace_expert_ffn_down", "grace_expert_ffn_down_fresh", "grace_expert_ffn_up_share", "grace_expert_ffn_down_share",
+           "grace_expert_ffn_down", "grace_expert_ffn_down_fresh", "grace_expert_ffn_up_share", "grace_expert_ffn_up_share_scatter", "grace_expert_ffn_down_share",
            "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_combine_share", "grace_mfma_sustained",
            "grace_ffn_kernel",
            "grace_last_error")
@@ -74,6 +74,7 @@ def load_library() -> C.CDLL:
     lib.grace_expert_ffn_down.argtypes = [vp, i32, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_expert_ffn_down_fresh.argtypes = lib.grace_expert_ffn_down.argtypes
     lib.grace_expert_ffn_up_share.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp]
+    lib.grace_expert_ffn_up_share_scatter.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp]
     lib.grace_expert_ffn_down_share.argtypes = [vp, i32, vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp]
     lib.grace_shared_ffn.argtypes = [vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp]
     lib.grace_shared_ffn_up.argtypes = [vp, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp]
@@ -381,6 +382,18 @@ def grace_expert_ffn_up_share(table: GraceTable, rank: int, xp: torch.Tensor, in
     _check(load_library().grace_expert_ffn_up_share(table.handle, rank, _dp(xp), _dp(inst_off), T, k, d, f, _dtype_code(xp),
                                                     _dp(w_gate) if S else None, _dp(w_up) if S else None, _dp(state),
                                                     _dp(ws), _stream()))
+
+
+def grace_expert_ffn_up_share_scatter(table: GraceTable, rank: int, x: torch.Tensor, perm_pos: torch.Tensor, perm_src: torch.Tensor,
+                                      xp: torch.Tensor, inst_off: torch.Tensor, k: int, w_gate: torch.Tensor, w_up: torch.Tensor,
+                                      state: torch.Tensor, ws: torch.Tensor) -> None:
+    """grace_permute_rows (rows of x into xp) and grace_expert_ffn_up_share on them as one call; see grace_moe.h."""
+    if state.dtype != torch.int32 or state.numel() < SHARE_STATE_INTS:
+        raise ValueError(f"state must hold {SHARE_STATE_INTS} int32")
+    S, f, d = w_gate.shape
+    _check(load_library().grace_expert_ffn_up_share_scatter(table.handle, rank, _dp(x), _dp(perm_pos), _dp(perm_src), _dp(xp), _dp(inst_off),
+                                                            x.shape[0], k, d, f, _dtype_code(x), _dp(w_gate) if S else None,
+                                                            _dp(w_up) if S else None, _dp(state), _dp(ws), _stream()))
 
 
 def grace_expert_ffn_down_share(table: GraceTable, rank: int, inst_off: torch.Tensor, T: int, k: int, w_down: torch.Tensor,

@@ -378,7 +378,7 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipS
         if (g.S <= 64) {
             if (!allow_full_lds((const void *)pers::gemm_bf16_persist_kernel<FUSED_UP, 1, WHO>, what)) return GRACE_EHIP;
             pers::gemm_bf16_persist_kernel<FUSED_UP, 1, WHO><<<(unsigned)l.groups, l.threads, pers::LDS_BYTES, st>>>(g, ntn);
-        } else if constexpr (WHO == pers::EXPERTS) {  // the shared experts are a single row segment
+        } else if constexpr (WHO != pers::SHARED) {  // the shared experts are a single row segment
             if (!allow_full_lds((const void *)pers::gemm_bf16_persist_kernel<FUSED_UP, 4, WHO>, what)) return GRACE_EHIP;
             pers::gemm_bf16_persist_kernel<FUSED_UP, 4, WHO><<<(unsigned)l.groups, l.threads, pers::LDS_BYTES, st>>>(g, ntn);
         }
@@ -450,13 +450,20 @@ static int expert_ffn_common(const char *who, const grace_table *table, int32_t 
     return GRACE_OK;
 }
 
+// Row scatter that a projection is to do as well: xp[pos[a]] = x[a / k]; src is the inverse of pos.
+struct Scatter {
+    const void *x;
+    const int32_t *pos, *src;
+};
+
 static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
                          int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_gate, const void *w_up,
-                         int32_t *state, void *ws, void *stream) {
+                         int32_t *state, void *ws, void *stream, const Scatter *sc = nullptr) {
     int g0, S;
     int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
     if (rc != GRACE_OK) return rc;
-    if (S == 0 || T == 0) return GRACE_OK;
+    if (T == 0) return GRACE_OK;
+    if (S == 0) return sc ? grace_permute_rows(sc->x, sc->pos, T, k, d, dt, (void *)xp, stream) : GRACE_OK;
     if (!xp || !inst_off || !w_gate || !w_up || !ws) return fail(GRACE_EINVAL, "%s: null device pointer", who);
     if ((((uintptr_t)xp) | ((uintptr_t)w_gate) | ((uintptr_t)w_up) | ((uintptr_t)ws)) & 15)
         return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
@@ -464,7 +471,24 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     up.A = xp; up.B0 = w_gate; up.B1 = w_up; up.out = ws;
     up.seg_off = inst_off + g0;
     up.share_state = state;
-    return launch_gemm<true, pers::EXPERTS>(up, dt, expert_rows(S, table->I, T, k), (hipStream_t)stream, who);
+    const Rows rows = expert_rows(S, table->I, T, k);
+    if (sc) {
+        // the scatter rides on the persistent bf16 kernel, which then reads the tokens themselves, when rows are whole 1 KB pieces, their
+        // offsets fit 32 bits and there are three steps along K; otherwise it is a launch of its own ahead of the projection.  Steps, two launches ->
+        // one, us: d = 2048, k = 8, 4096 tokens of f = 1024 202 -> 187, 8000 306 -> 284, 7001 of f = 768 180 -> 172, 4000 132 -> 123; d = 4096, k = 2, f =
+        // 14336, 3000 tokens 424 -> 407, 1500 and 8192 (power limit) even
+        const int64_t row_bytes = (int64_t)d * 2;
+        const int n_cu = compute_units();
+        if (dt == GRACE_BF16 && n_cu > 0 && route_gemm<true>(up, dt, rows, n_cu) == Route::PERSIST && row_bytes % 1024 == 0 && d >= 3 * pers::BK &&
+            k <= 64 && (int64_t)T * k < ((int64_t)1 << 29) && T * row_bytes <= (int64_t)INT32_MAX) {
+            up.A = sc->src;
+            up.sc_x = sc->x; up.sc_xp = (void *)xp; up.sc_pos = sc->pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = (int)row_bytes;
+            return launch_gemm<true, pers::EXPERTS_GATHER>(up, dt, rows, (hipStream_t)stream, who);
+        }
+        rc = grace_permute_rows(sc->x, sc->pos, T, k, d, dt, (void *)xp, stream);
+        if (rc != GRACE_OK) return rc;
+    }
+    return launch_gemm<true, pers::EXPERTS>(up, dt, rows, (hipStream_t)stream, who);
 }
 
 extern "C" int grace_expert_ffn_up(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
@@ -478,6 +502,17 @@ extern "C" int grace_expert_ffn_up_share(const grace_table *table, int32_t rank,
                                          const void *w_up, int32_t *state, void *ws, void *stream) {
     if (!state) return fail(GRACE_EINVAL, "expert_ffn_up_share: state is null");
     return expert_ffn_up("expert_ffn_up_share", table, rank, xp, inst_off, T, k, d, f, dt, w_gate, w_up, state, ws, stream);
+}
+
+extern "C" int grace_expert_ffn_up_share_scatter(const grace_table *table, int32_t rank, const void *x, const int32_t *perm_pos,
+                                                 const int32_t *perm_src, void *xp, const int32_t *inst_off, int32_t T, int32_t k,
+                                                 int32_t d, int32_t f, grace_dtype dt, const void *w_gate, const void *w_up,
+                                                 int32_t *state, void *ws, void *stream) {
+    if (!state) return fail(GRACE_EINVAL, "expert_ffn_up_share_scatter: state is null");
+    if (T > 0 && (!x || !perm_pos || !perm_src || !xp)) return fail(GRACE_EINVAL, "expert_ffn_up_share_scatter: null device pointer");
+    if (((uintptr_t)x | (uintptr_t)xp) & 15) return fail(GRACE_EINVAL, "expert_ffn_up_share_scatter: x and xp must be 16-byte aligned");
+    const Scatter sc = {x, perm_pos, perm_src};
+    return expert_ffn_up("expert_ffn_up_share_scatter", table, rank, xp, inst_off, T, k, d, f, dt, w_gate, w_up, state, ws, stream, &sc);
 }
 
 static_assert(SHARE_STATE_INTS == GRACE_SHARE_STATE_INTS, "header and kernels must agree on the state size");

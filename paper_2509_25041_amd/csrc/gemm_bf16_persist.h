@@ -102,7 +102,9 @@ __device__ __forceinline__ void load16_to_lds(const char *base, uint32_t voff, c
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(voff), "s"(lds_addr) : "memory");
 }
 
-enum Who { EXPERTS = 0, SHARED = 1 };
+// EXPERTS_GATHER: the experts' gate+up projection ahead of the row scatter, which it carries: its rows come from the tokens (g.sc_x) through the
+// source assignments of the dispatch rows (g.A).
+enum Who { EXPERTS = 0, SHARED = 1, EXPERTS_GATHER = 2 };
 
 // HF: activation fragments (of 16 rows) per wavefront, i.e. the m-tile holds 32 * HF rows, HF * 16 for each
 // of the two wavefront rows.  8 is the full tile; 7, 6, 5 make tiles of 224, 192, 160 rows whose K loop
@@ -166,7 +168,7 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
         }
     };
     // rank-share upkeep of the expert down projection's output (no-op unless the launcher asks for it)
-    if (WHO == EXPERTS) {
+    if (WHO != SHARED) {
         if (FUSED_UP) share_record(g); else share_clear_stale(g);
     }
     // Lane-dependent values that are only needed at tile boundaries are recomputed there from an
@@ -176,7 +178,7 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
         asm volatile("" : "+v"(l));
         return l;
     };
-    // ---- row scatter carried along (shared experts' gate+up projection only) ---------------------
+    // ---- row scatter carried along (gate+up projections) ------------------------------------------
     // The kernel is bound by the matrix cores and leaves most of the HBM bandwidth unused, the row
     // scatter of the dispatch permutation is bound by HBM and leaves the matrix cores idle, and the
     // two are independent.  Every wavefront therefore moves SC_NU 1 KB pieces of token rows every
@@ -188,12 +190,28 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
     // workload).  Pieces are dealt round-robin to all wavefronts of the grid;
     // whatever is left when a wavefront runs out of K steps is moved at the end, so the scatter is
     // complete whatever the tile count.
-    constexpr bool COPY = FUSED_UP && WHO == SHARED;
+    constexpr bool GATHER = WHO == EXPERTS_GATHER, COPY = FUSED_UP && (WHO == SHARED || GATHER);
     const bool copy_on = COPY && g.sc_x != nullptr;                       // uniform
     const int sc_cpr = copy_on ? g.sc_row_bytes / 1024 : 1;                // 1 KB pieces per row
     const int sc_units = copy_on ? g.sc_T * sc_cpr : 0;
-    const int sc_stride = (int)gridDim.x * (THREADS / 64);
+    int sc_stride = (int)gridDim.x * (THREADS / 64);
     int sc_u = (int)blockIdx.x * (THREADS / 64) + wave;                    // this wavefront's next piece
+    if constexpr (GATHER) {
+        // Tiles are dealt in whole rounds, so the workgroups that have none in the last one wait a tile's time for the others: where they
+        // are a quarter of the grid or more, they move the rows, while and after they work on their own tiles, and the others
+        // none.  All workgroups alike -> those (steps, us): d = 4096, f = 7168, 4001 tokens, k = 2, 1.1 rounds 339 -> 334; d = 2048, f = 1024,
+        // 4096 tokens, k = 8 187 -> 182, d = 2048, f = 768, 4000 tokens 127 -> 122.
+        const int rounds = flat ? rounds_f : rounds_m, rem = flat ? j_rem : mt_rem;
+        const int jobs_lo = flat ? j_each : mt_each * n_tiles_n, jobs_hi = flat ? j_each + 1 : (mt_each + 1) * n_tiles_n;
+        const int busy_lo = max(0, min(nblk, jobs_lo - (rounds - 1) * nblk)), busy_hi = max(0, min(nblk, jobs_hi - (rounds - 1) * nblk));
+        const int light = rem * (nblk - busy_hi) + (N_XCD - rem) * (nblk - busy_lo);
+        if (4 * light >= (int)gridDim.x) {
+            const int my_busy = xcd < rem ? busy_hi : busy_lo;
+            const int before = min(xcd, rem) * (nblk - busy_hi) + max(0, xcd - rem) * (nblk - busy_lo) + bslot - my_busy;
+            sc_stride = light * (THREADS / 64);
+            sc_u = bslot >= my_busy ? before * (THREADS / 64) + wave : sc_units;
+        }
+    }
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     // Measured on the 32768-token workload (k = 6) with the first version (stores after the step, a piece every
     // 4th step): +83 us on the 577 us projection for a 188 us scatter; four pieces every 16th step cost 30 us more
@@ -247,11 +265,35 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
         }
         sc_pending = 0;
     };
+    auto copy_due = [&]() {   // is it time for the next piece?
+        if (!COPY || --sc_countdown > 0) return false;
+        sc_countdown = sc_period;
+        return true;
+    };
+    // What is left when no K step is (nothing of the K loop is in flight any more): four pieces at a time.
     auto copy_rest = [&]() {
-        while (copy_on && sc_u < sc_units) {
-            copy_issue();
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            copy_store();
+        if (!copy_on) return;
+        constexpr int BATCH = 4;
+        const int ll = opaque_lane();
+        const int64_t n_rows = (int64_t)g.sc_T * g.sc_k;
+        for (; sc_u < sc_units; sc_u += BATCH * sc_stride) {
+            uint4 data[BATCH];
+            int pos[BATCH], q[BATCH];
+#pragma unroll
+            for (int n = 0; n < BATCH; ++n) {
+                const int u = min(sc_u + n * sc_stride, sc_units - 1), t = u / sc_cpr;   // (T * pieces per row < 2^31 - 4 strides: launcher)
+                q[n] = u - t * sc_cpr;
+                pos[n] = g.sc_pos[t * g.sc_k + min(ll, g.sc_k - 1)];
+                data[n] = *(const uint4 *)((const char *)g.sc_x + (int64_t)t * g.sc_row_bytes + q[n] * 1024 + ll * 16);
+            }
+#pragma unroll
+            for (int n = 0; n < BATCH; ++n) {
+                if (sc_u + n * sc_stride >= sc_units) break;
+                for (int j = 0; j < g.sc_k; ++j) {
+                    const int p = __builtin_amdgcn_readlane(pos[n], j);
+                    if (p >= 0 && p < n_rows) nt_store16(data[n], (uint4 *)((char *)g.sc_xp + (int64_t)p * g.sc_row_bytes + q[n] * 1024) + ll);
+                }
+            }
         }
     };
     int job = bslot;
@@ -268,7 +310,10 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
     if (COPY && copy_on) {
         const int my_tiles = (njobs - bslot + nblk - 1) / nblk;                           // > 0 here
         const int my_pieces = sc_u < sc_units ? (sc_units - sc_u + sc_stride - 1) / sc_stride : 0;
-        sc_period = max(1, my_tiles * max(nk - 2, 0) / max(my_pieces, 1));
+        // The experts' launches are shorter for their rows and their tiles' weights colder: a piece every 3rd step at most there, the rest afterwards
+        // (8000 tokens, k = 8, 57 us of rows on a 148 us projection: 191 us with as many pieces as fit, 175 every 3rd step, 180 every 6th, 177 all
+        // afterwards).
+        sc_period = max(GATHER ? 3 : 1, my_tiles * max(nk - 2, 0) / max(my_pieces, 1));
     }
 
     // ---- load sources: a scalar base per operand (advancing along K) + a 32-bit byte offset per lane ----
@@ -279,8 +324,29 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
     uint32_t a_voff[LOADS], b_voff[LOADS];
     int kpos = 0;
     int a_iss = 0, b_iss = 0;  // buffers the next loads go to
+    // GATHER: lane 8 i + r holds the source assignment of the tile row that load i's lanes of row r read.  The next tile's
+    // are loaded ahead of the current one's first K step, whose wait covers them as it does the carried scatter's loads.
+    int src_of = 0;
+    auto src_offset = [&](const Tile &t) {
+        const int ll = opaque_lane() & 31, tr = ((ll >> 3) * 8 + wave) * ROWS_PER_LOAD + (ll & 7);
+        return (uint32_t)(t.m0 + min(tr, t.m_end - 1 - t.m0)) * 4u;   // T * k < 2^29 (launcher)
+    };
+    static_assert(LOADS * ROWS_PER_LOAD == 32, "one lane per row that a wavefront loads");
+    auto src_issue = [&](const Tile &t) {
+        asm volatile("s_nop 4\n\tglobal_load_dword %0, %1, %2" : "=&v"(src_of) : "v"(src_offset(t)), "s"(g.A) : "memory");
+    };
     auto set_a_sources = [&](const Tile &t) {
         const int ll = opaque_lane(), lrow = ll / CPR, lpos = ll % CPR;
+        if constexpr (GATHER) {
+            const uint32_t token = min((uint32_t)src_of / (uint32_t)g.sc_k, (uint32_t)(g.sc_T - 1));
+            a_ptr = (const char *)g.sc_x;
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int gchunk = lpos ^ swizzle_key((i * 8 + wave) * ROWS_PER_LOAD + lrow);
+                a_voff[i] = (uint32_t)__shfl((int)token, i * ROWS_PER_LOAD + lrow, 64) * (uint32_t)g.sc_row_bytes + (uint32_t)gchunk * 16u;
+            }
+            return;
+        }
         a_ptr = (const char *)g.A + (int64_t)t.m0 * g.lda * 2;
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
@@ -465,12 +531,13 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
         group_sched(false, CROSS, false);
     };
     // the same step for a wavefront with no valid rows in this tile: synchronise and load only
-    auto idle_step = [&]() {
+    auto idle_step = [&](bool store_copy = false) {
         a_con ^= 1;
         b_con = (b_con + 1 == NBUF_B) ? 0 : b_con + 1;
         issue_b();
         asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
         asm volatile("s_barrier" ::: "memory");
+        if (COPY && store_copy) copy_store();
         issue_a();
     };
     using T_ = std::integral_constant<bool, true>;
@@ -543,6 +610,8 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
     int cur_mt, cur_n0;
     job_tile(job, cur_mt, cur_n0);
     Tile cur = lookup(cur_mt);
+    if constexpr (GATHER)
+        asm volatile("s_nop 4\n\tglobal_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=&v"(src_of) : "v"(src_offset(cur)), "s"(g.A) : "memory");
     set_a_sources(cur);
     set_b_sources(cur, cur_n0);
     issue_a();
@@ -573,11 +642,8 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
                     for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
             fetch_entry(0, smem + a_con * A_BYTES, smem + B_BASE + b_con * B_BYTES, 0);
             for (int kt = 0; kt + 2 < nk; ++kt) {
-                bool copy_now = false;
-                if (COPY && --sc_countdown <= 0) {
-                    copy_now = true;
-                    sc_countdown = sc_period;
-                }
+                const bool copy_now = copy_due();
+                if (GATHER && kt == 0 && has_next) src_issue(nxt);
                 if (copy_now) copy_issue();
                 step(acc, T_{}, copy_now);
             }
@@ -588,7 +654,12 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
             epilogue(acc, cur, cur_n0, n_valid);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // staging reads done before the buffer is refilled
         } else {
-            for (int kt = 0; kt + 2 < nk; ++kt) idle_step();
+            for (int kt = 0; kt + 2 < nk; ++kt) {
+                const bool copy_now = copy_due();
+                if (GATHER && kt == 0 && has_next) src_issue(nxt);
+                if (copy_now) copy_issue();
+                idle_step(copy_now);
+            }
             set_a_sources(nxt);
             set_b_sources(nxt, nxt_n0);
             idle_step();

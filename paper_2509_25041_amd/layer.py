@@ -7,7 +7,7 @@ from typing import List, Optional, Tuple
 
 import torch
 
-from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_workspace_bytes, load_library
+from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_ffn_kernel, grace_workspace_bytes, load_library
 
 STAGES = ("route", "permute", "route_permute", "ffn_up", "ffn_down", "shared_up", "shared_down", "combine")
 
@@ -71,6 +71,9 @@ class GraceMoELayer:
         # experts' gate+up projection (grace_shared_ffn_up_scatter: carried by its launch for large batches, a launch
         # ahead of it otherwise), which then runs ahead of the expert FFN; False: the scatter is part of the dispatch call
         self.fuse_scatter = self.n_shared > 0
+        # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows
+        self.gather_rows = (not self.n_shared and S > 0 and T > 0 and
+                            grace_ffn_kernel(True, T, d, f, self.dt, k=k, S=S, I=table.I)[0] == "persist")
         self.ws_shared = None
         self._key = None
         self._calls: List[Tuple[str, object, tuple]] = []
@@ -93,7 +96,7 @@ class GraceMoELayer:
         S = wg.shape[0]
         ws = p(self.ws)
         fuse = self.fuse_scatter and self.shared is not None
-        xr, xpr = (None, None) if fuse else (p(x), p(self.xp))     # rows moved by the dispatch call, or not
+        xr, xpr = (None, None) if fuse or self.gather_rows else (p(x), p(self.xp))     # rows moved by the dispatch call, or not
         if self.single_call_dispatch:
             calls = [("route_permute", lib.grace_route_permute,
                       (h, lr, self.policy, p(logits), T, self.table.E, k, self.renorm, p(rr_in), p(rr_out), p(te), p(tw),
@@ -114,9 +117,13 @@ class GraceMoELayer:
                                              device=self.xp.device)
             calls.append(("shared_up", lib.grace_shared_ffn_up_scatter, (p(x), T, d, f, self.n_shared, dt, p(sg), p(su),
                                                                         p(self.ws_shared), p(pos), k, p(self.xp), st)))
+        if self.gather_rows:
+            calls.append(("ffn_up", lib.grace_expert_ffn_up_share_scatter,
+                          (h, lr, p(x), p(pos), p(src), p(self.xp), p(ioff), T, k, d, f, dt, p(wg), p(wu), p(self.y_state), ws, st)))
+        else:
+            calls.append(("ffn_up", lib.grace_expert_ffn_up_share, (h, lr, p(self.xp), p(ioff), T, k, d, f, dt, p(wg) if S else None,
+                                                                    p(wu) if S else None, p(self.y_state), ws, st)))
         calls += [
-            ("ffn_up", lib.grace_expert_ffn_up_share, (h, lr, p(self.xp), p(ioff), T, k, d, f, dt, p(wg) if S else None,
-                                                       p(wu) if S else None, p(self.y_state), ws, st)),
             ("ffn_down", lib.grace_expert_ffn_down_share, (h, lr, p(ioff), T, k, d, f, dt, p(wd) if S else None,
                                                            p(self.y), p(self.y_state), ws, st)),
         ]

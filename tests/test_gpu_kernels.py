@@ -534,3 +534,46 @@ def test_rank_share_after_routing_changes_by_kernel(monkeypatch, T, E, k, d, f, 
     assert kernels_of(T, k, d, f, len(table.local_experts(1)), table.I, dtype=dtype) == want
     monkeypatch.setitem(parity.SMALL, cfg.name, cfg)
     parity.test_layer_rank_share_after_routing_changes(cfg.name)
+
+
+@pytest.mark.parametrize("T,k,d,f,S,I,dtype,want", [
+    (3000, 8, 2048, 1024, 18, 72, "bf16", "persist"),    # ragged tiles, some with an idle half; idle workgroups in the last round move the rows
+    (12000, 2, 512, 1024, 4, 16, "bf16", "persist"),     # k = 2, a piece per row
+    (9000, 8, 512, 256, 90, 90, "bf16", "persist"),      # more segments than lanes; every row is the rank's
+    (6000, 8, 512, 384, 8, 16, "bf16", "persist"),
+    (2100, 17, 1024, 512, 8, 8, "bf16", "persist"),
+    (40, 4, 512, 256, 4, 8, "bf16", "stream"),           # other kernels: the rows move in a launch of their own
+    (3000, 8, 544, 256, 8, 16, "bf16", None),            # rows that are no whole 1 KB pieces
+    (90, 2, 512, 256, 4, 8, "f32", "stream"),
+])
+def test_gate_up_projection_that_moves_the_rows(T, k, d, f, S, I, dtype, want):
+    """Bit for bit the row scatter and then the projection on the moved rows; ids outside the table leave no row."""
+    kernel = kernels_of(T, k, d, f, S, I, dtype=dtype)[0]
+    assert want is None or kernel == want
+    R, rank = I // S, I // S - 1
+    table = grace.GraceTable(I, R, 1, [0] * R, [1] * R, list(range(I + 1)), [e // S for e in range(I)])
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn((T, d), generator=gen, device="cuda").to(tdt)
+    wg, wu = ((0.05 * torch.randn((S, f, d), generator=gen, device="cuda")).to(tdt) for _ in range(2))
+    share = torch.rand(I, generator=gen, device="cuda") ** 3
+    ti = torch.multinomial(share, T * k, replacement=True, generator=gen).to(torch.int32).reshape(T, k)
+    ti[T // 2, k - 1] = I + 3
+    ti[0, 0] = -1
+    pos, src, ioff, _, _, _ = grace.grace_permute(table, ti, None)
+    n = int(ioff[-1])
+    src[n:] = -7   # (positions of no row; whatever they hold, they are not the rank's)
+    nbytes = grace.grace_workspace_bytes(T, I, k, I, d, f, 0, grace.GRACE_F32 if dtype == "f32" else grace.GRACE_BF16)
+    results = []
+    for one_call in (True, False):
+        xp = torch.full((T * k, d), 3.0, dtype=tdt, device="cuda")
+        ws, state = torch.zeros(nbytes, dtype=torch.uint8, device="cuda"), torch.zeros(8, dtype=torch.int32, device="cuda")
+        if one_call:
+            grace.grace_expert_ffn_up_share_scatter(table, rank, x, pos, src, xp, ioff, k, wg, wu, state, ws)
+        else:
+            grace.grace_permute_rows(x, pos, k, xp)
+            grace.grace_expert_ffn_up_share(table, rank, xp, ioff, T, k, wg, wu, state, ws)
+        results.append((xp, ws, state))
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+    assert torch.equal(results[0][0][:n], x[(src[:n] // k).long()])
