@@ -176,7 +176,9 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
         if not stage.startswith("shared") or n_sh:
             kernels[stage] = grace.grace_ffn_kernel(up, T, d, f, layer.dt, k=k, S=max(1, len(experts)), I=table.I, n_shared=n_sh)[0]
     carries_rows = fused_scatter and kernels["shared_up"] == "persist" and d * el % 1024 == 0
-    bytes_dispatch = bytes_route + (12 * T * k if fused_scatter else bytes_permute)
+    # without them the experts' gate+up projection reads the tokens and moves the rows, where the large tiles take it
+    gathers_rows = bool(getattr(layer, "gather_rows", False))
+    bytes_dispatch = bytes_route + (12 * T * k if fused_scatter or gathers_rows else bytes_permute)
     # algorithmic work per launch of the kernel behind each call: (bound, amount, unit scale, peak)
     work = {
         "ffn_up": ("mfma", 4.0 * d * f * m_loc), "ffn_down": ("mfma", 2.0 * d * f * m_loc),
@@ -312,6 +314,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
                    "rows_per_slot_min_max": [int(seg.min()), int(seg.max())] if len(seg) else [0, 0],
                    "n_shared": cfg.n_shared, "working_set_MB": ws_bytes / 1e6,
                    "row_scatter": "carried by the shared gate+up projection's launch" if carries_rows else
+                   "carried by the experts' gate+up projection's launch" if gathers_rows else
                    "a launch of its own ahead of the shared gate+up projection" if fused_scatter else "in the dispatch call"},
         "roofline": {"kernel": KERNEL_OF_STAGE[dominant] if kernels.get(dominant, "persist") == "persist"
                      else f"{OTHER_KERNEL[kernels[dominant]]} ({dominant})",
