@@ -344,9 +344,9 @@ int grace_shared_ffn_down(int32_t T, int32_t d, int32_t f, int32_t n_shared, gra
 /* grace_shared_ffn_up and grace_permute_rows (the row movement of Section 5's dispatch order) as one
  * call: both read only x (and perm_pos), the projection is bound by the matrix cores and the row
  * movement by HBM, so where the large-tile kernel takes the projection (GRACE_KERNEL_PERSIST of
- * grace_ffn_kernel: large batches, d a multiple of 64) and rows are multiples of 1024 bytes it carries
- * them along (every wavefront moves a 1 KB piece of a token row every few K steps) instead of a launch
- * of its own; other shapes and batches run the two launches.  Outputs are those of the two calls, bit
+ * grace_ffn_kernel: large batches, d a multiple of 64), rows are multiples of 1024 bytes and a token has 64 choices
+ * at most it carries them along (every wavefront moves a 1 KB piece of a token row every few K steps) instead
+ * of a launch of its own; other shapes and batches run the two launches.  Outputs are those of the two calls, bit
  * for bit: the hidden activation in ws and xp[perm_pos[t*k+j]] = x[t].
  * DEVICE: perm_pos [T*k] from grace_permute / grace_route_permute called with x == NULL; xp [T*k,d];
  * the rest as for grace_shared_ffn_up.  xp must not overlap x or ws. */

@@ -450,6 +450,17 @@ static int expert_ffn_common(const char *who, const grace_table *table, int32_t 
     return GRACE_OK;
 }
 
+// Does the launch of a gate+up projection move the dispatch rows as well?  The large-tile kernel does, rows in whole 1 KB pieces of
+// which a wavefront holds one with the positions of its token, a lane each (up to 64 choices); offsets of positions in 32 bits, and piece
+// numbers (a wavefront looks at four strides of the grid at a time) below 2^31.  The experts' projection reads the tokens themselves then: their
+// offsets fit 32 bits, and the rows of the next tile are looked up while three steps along K or more run.
+static bool carries_rows(Route route, grace_dtype dt, int32_t T, int32_t k, int32_t d, bool experts) {
+    const int64_t row_bytes = (int64_t)d * 2;
+    if (route != Route::PERSIST || dt != GRACE_BF16 || row_bytes % 1024 != 0 || row_bytes > INT32_MAX) return false;
+    if (k > 64 || (int64_t)T * k >= ((int64_t)1 << 29) || T * (row_bytes / 1024) > ((int64_t)1 << 30)) return false;
+    return !experts || (d >= 3 * pers::BK && T * row_bytes <= (int64_t)INT32_MAX);
+}
+
 // Row scatter that a projection is to do as well: xp[pos[a]] = x[a / k]; src is the inverse of pos.
 struct Scatter {
     const void *x;
@@ -473,16 +484,12 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     up.share_state = state;
     const Rows rows = expert_rows(S, table->I, T, k);
     if (sc) {
-        // the scatter rides on the persistent bf16 kernel, which then reads the tokens themselves, when rows are whole 1 KB pieces, their
-        // offsets fit 32 bits and there are three steps along K; otherwise it is a launch of its own ahead of the projection.  Steps, two launches ->
-        // one, us: d = 2048, k = 8, 4096 tokens of f = 1024 202 -> 187, 8000 306 -> 284, 7001 of f = 768 180 -> 172, 4000 132 -> 123; d = 4096, k = 2, f =
+        // the scatter rides on the projection's launch (carries_rows), or is one of its own ahead of it.  Steps, two launches -> one, us: d = 2048, k = 8, 4096 tokens of f = 1024 202 -> 187, 8000 306 -> 284, 7001 of f = 768 180 -> 172, 4000 132 -> 123; d = 4096, k = 2, f =
         // 14336, 3000 tokens 424 -> 407, 1500 and 8192 (power limit) even
-        const int64_t row_bytes = (int64_t)d * 2;
         const int n_cu = compute_units();
-        if (dt == GRACE_BF16 && n_cu > 0 && route_gemm<true>(up, dt, rows, n_cu) == Route::PERSIST && row_bytes % 1024 == 0 && d >= 3 * pers::BK &&
-            k <= 64 && (int64_t)T * k < ((int64_t)1 << 29) && T * row_bytes <= (int64_t)INT32_MAX) {
+        if (n_cu > 0 && carries_rows(route_gemm<true>(up, dt, rows, n_cu), dt, T, k, d, true)) {
             up.A = sc->src;
-            up.sc_x = sc->x; up.sc_xp = (void *)xp; up.sc_pos = sc->pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = (int)row_bytes;
+            up.sc_x = sc->x; up.sc_xp = (void *)xp; up.sc_pos = sc->pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = d * 2;
             return launch_gemm<true, pers::EXPERTS_GATHER>(up, dt, rows, (hipStream_t)stream, who);
         }
         rc = grace_permute_rows(sc->x, sc->pos, T, k, d, dt, (void *)xp, stream);
@@ -590,13 +597,10 @@ static int shared_ffn_up(const char *who, const void *x, int32_t T, int32_t d, i
     GemmArgs up = shared_shape(true, T, d, f, n_shared);
     up.A = x; up.B0 = w_gate; up.B1 = w_up; up.out = ws;
     if (perm_pos) {
-        // the row scatter rides on the persistent bf16 kernel when rows are whole 1 KB pieces; otherwise it
-        // is a launch of its own ahead of the projection
-        const size_t row_bytes = (size_t)d * (dt == GRACE_F32 ? 4 : 2);
+        // the row scatter rides on the projection's launch, or is one of its own ahead of it
         const int n_cu = compute_units();
-        const bool persistent = n_cu > 0 && route_gemm<true>(up, dt, shared_rows(T), n_cu) == Route::PERSIST;
-        if (persistent && row_bytes % 1024 == 0 && (int64_t)T * k < ((int64_t)1 << 29) && row_bytes <= (size_t)INT32_MAX) {
-            up.sc_x = x; up.sc_xp = xp; up.sc_pos = perm_pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = (int)row_bytes;
+        if (n_cu > 0 && carries_rows(route_gemm<true>(up, dt, shared_rows(T), n_cu), dt, T, k, d, false)) {
+            up.sc_x = x; up.sc_xp = xp; up.sc_pos = perm_pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = d * 2;
         } else {
             rc = grace_permute_rows(x, perm_pos, T, k, d, dt, xp, stream);
             if (rc != GRACE_OK) return rc;

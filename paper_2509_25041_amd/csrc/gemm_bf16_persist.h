@@ -281,7 +281,7 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
             int pos[BATCH], q[BATCH];
 #pragma unroll
             for (int n = 0; n < BATCH; ++n) {
-                const int u = min(sc_u + n * sc_stride, sc_units - 1), t = u / sc_cpr;   // (T * pieces per row < 2^31 - 4 strides: launcher)
+                const int u = min(sc_u + n * sc_stride, sc_units - 1), t = u / sc_cpr;   // (T * pieces per row <= 2^30: launcher)
                 q[n] = u - t * sc_cpr;
                 pos[n] = g.sc_pos[t * g.sc_k + min(ll, g.sc_k - 1)];
                 data[n] = *(const uint4 *)((const char *)g.sc_x + (int64_t)t * g.sc_row_bytes + q[n] * 1024 + ll * 16);

@@ -509,6 +509,7 @@ def test_operands_past_two_gigabytes():
     (1500, 512, 1024, 2, 64),    # the largest top-k: nearly all rows are moved after the tile loop
     (700, 2048, 1344, 3, 64),    # 4 KB rows, 3 x 32 tiles
     (1500, 4096, 2048, 1, 3),    # 8 KB rows, 6 x 16 tiles
+    (1500, 512, 1024, 2, 65),    # more choices than a wavefront has lanes: the rows move in a launch of their own
 ])
 def test_row_scatter_carried_by_the_large_tiles(T, d, f, n_shared, k):
     """grace_shared_ffn_up_scatter where the projection's launch moves the rows (k > 1, dropped positions)."""
