@@ -204,6 +204,12 @@ def _ws(ws: Optional[torch.Tensor], nbytes: int, device) -> torch.Tensor:
     return ws
 
 
+def _need(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, numel: int) -> None:
+    """A caller's tensor that a kernel reads or writes `numel` entries of."""
+    if t is None or t.dtype != dtype or t.numel() < numel:
+        raise ValueError(f"{name} must hold {numel} {str(dtype).replace('torch.', '')}")
+
+
 def grace_route(table: GraceTable, local_rank: int, logits: torch.Tensor, k: int, renorm: int = 1,
                 rr_in: Optional[torch.Tensor] = None, rr_out: Optional[torch.Tensor] = None,
                 ws: Optional[torch.Tensor] = None, out=None, policy: int = GRACE_POLICY_TAR):
@@ -305,14 +311,25 @@ def grace_send_lists(table: GraceTable, local_rank: int, topk_inst: torch.Tensor
     np_, nt = torch.empty(table.N + 1, **i32), torch.empty(T * k, **i32)
     ex = torch.empty(T * k, **i32)
     tr = torch.empty(4, dtype=torch.int64, device=dev)
-    grace_send_lists_fresh(table, local_rank, topk_inst, (rp, rt, np_, nt, ex, tr), ws)
+    _send_lists_fresh(table, local_rank, topk_inst, rp, rt, np_, nt, ex, tr, ws)
     return rp, rt, np_, nt, ex, tr
 
 
 def grace_send_lists_fresh(table: GraceTable, local_rank: int, topk_inst: torch.Tensor, out, ws: Optional[torch.Tensor] = None) -> None:
-    """grace_send_lists into the caller's tensors, all of whose entries are written (-1 past the ends of the lists)."""
+    """grace_send_lists into the caller's tensors, all of whose entries are written (-1 past the ends of the lists);
+    `out` as grace_send_lists returns it, traffic may be None."""
     T, k = topk_inst.shape
     rp, rt, np_, nt, ex, tr = out
+    for t, name, n in ((rp, "rank_send_ptr", table.R + 1), (rt, "rank_send_tok", T * k), (np_, "node_send_ptr", table.N + 1),
+                       (nt, "node_send_tok", T * k), (ex, "expand", T * k)):
+        _need(t, name, torch.int32, n)
+    if tr is not None:
+        _need(tr, "traffic", torch.int64, 4)
+    _send_lists_fresh(table, local_rank, topk_inst, rp, rt, np_, nt, ex, tr, ws)
+
+
+def _send_lists_fresh(table, local_rank, topk_inst, rp, rt, np_, nt, ex, tr, ws) -> None:
+    T, k = topk_inst.shape
     ws = _ws(ws, grace_workspace_bytes(T, table.E, k, table.I), topk_inst.device)
     _check(load_library().grace_send_lists_fresh(table.handle, local_rank, _dp(topk_inst), T, k, _dp(rp), _dp(rt), _dp(np_),
                                                  _dp(nt), _dp(ex), _dp(tr), _dp(ws), _stream()))
@@ -391,8 +408,15 @@ def grace_expert_ffn_up_share_scatter(table: GraceTable, rank: int, x: torch.Ten
     if state.dtype != torch.int32 or state.numel() < SHARE_STATE_INTS:
         raise ValueError(f"state must hold {SHARE_STATE_INTS} int32")
     S, f, d = w_gate.shape
+    T = x.shape[0]
+    if tuple(x.shape) != (T, d) or tuple(w_up.shape) != (S, f, d) or w_gate.dtype != x.dtype or w_up.dtype != x.dtype:
+        raise ValueError("x must be [T,d], w_gate and w_up [S,f,d], of one dtype")
+    for t, name, n in ((perm_pos, "perm_pos", T * k), (perm_src, "perm_src", T * k), (inst_off, "inst_off", table.I + 1)):
+        _need(t, name, torch.int32, n)
+    _need(xp, "xp", x.dtype, T * k * d)
+    ws = _ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, _dtype_code(x)), x.device)
     _check(load_library().grace_expert_ffn_up_share_scatter(table.handle, rank, _dp(x), _dp(perm_pos), _dp(perm_src), _dp(xp), _dp(inst_off),
-                                                            x.shape[0], k, d, f, _dtype_code(x), _dp(w_gate) if S else None,
+                                                            T, k, d, f, _dtype_code(x), _dp(w_gate) if S else None,
                                                             _dp(w_up) if S else None, _dp(state), _dp(ws), _stream()))
 
 

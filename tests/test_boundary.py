@@ -3,6 +3,7 @@ declares, and rejects malformed tables / arguments on the host."""
 import ctypes as C
 import os
 import re
+import types
 
 import numpy as np
 import pytest
@@ -125,3 +126,32 @@ def test_workspace_bytes():
     big = grace.grace_workspace_bytes(4096, 64, 8, 76, 2048, 1024, 0, grace.GRACE_BF16)
     assert big >= 4096 * 8 * 1024 * 2
     assert grace.grace_workspace_bytes(4096, 64, 8, 76, 2048, 1024, 0, grace.GRACE_F32) >= 2 * (big - 256)
+
+
+def test_caller_tensors_are_checked_before_a_kernel_writes_them():
+    """Tensors that kernels of these calls write or read whole: too small or of another type is an error, not an access out of
+    bounds.  (Tensors of the right size get as far as the check that they are on the device.)"""
+    T, k, R, N, I, d, f = 6, 3, 4, 2, 5, 16, 8
+    table = types.SimpleNamespace(R=R, N=N, I=I, E=I, handle=None)
+    sizes = dict(rank_send_ptr=R + 1, rank_send_tok=T * k, node_send_ptr=N + 1, node_send_tok=T * k, expand=T * k)
+    good = {n: torch.zeros(c, dtype=torch.int32) for n, c in sizes.items()}
+    good["traffic"] = torch.zeros(4, dtype=torch.int64)
+    ti = torch.zeros((T, k), dtype=torch.int32)
+    with pytest.raises(ValueError, match="live on the GPU"):
+        grace.grace_send_lists_fresh(table, 0, ti, tuple(good.values()))
+    for name, t in good.items():
+        for bad in (t[:-1], t.double()) + (() if name == "traffic" else (t.long(), None)):
+            with pytest.raises(ValueError, match=name):
+                grace.grace_send_lists_fresh(table, 0, ti, tuple({**good, name: bad}.values()))
+
+    bf = torch.bfloat16
+    a = dict(x=torch.zeros(T, d, dtype=bf), perm_pos=torch.zeros(T * k, dtype=torch.int32), perm_src=torch.zeros(T * k, dtype=torch.int32),
+             xp=torch.zeros(T * k, d, dtype=bf), inst_off=torch.zeros(I + 1, dtype=torch.int32), k=k, w_gate=torch.zeros(2, f, d, dtype=bf),
+             w_up=torch.zeros(2, f, d, dtype=bf), state=torch.zeros(8, dtype=torch.int32), ws=torch.zeros(1 << 20, dtype=torch.uint8))
+    with pytest.raises(ValueError, match="live on the GPU"):
+        grace.grace_expert_ffn_up_share_scatter(table, 0, **a)
+    for name, bad, said in (("perm_pos", a["perm_pos"][:-1], "perm_pos"), ("perm_src", a["perm_src"].long(), "perm_src"), ("inst_off", a["inst_off"][:I], "inst_off"),
+                            ("xp", a["xp"][:-1], "xp"), ("xp", a["xp"].float(), "xp"), ("w_up", a["w_up"][:1], "w_up"), ("x", a["x"].float(), "one dtype"),
+                            ("w_gate", a["w_gate"].float(), "one dtype"), ("state", a["state"][:7], "state"), ("ws", a["ws"][:64], "workspace")):
+        with pytest.raises(ValueError, match=said):
+            grace.grace_expert_ffn_up_share_scatter(table, 0, **{**a, name: bad})
