@@ -175,8 +175,8 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
     for stage, up, n_sh in (("ffn_up", True, 0), ("ffn_down", False, 0), ("shared_up", True, cfg.n_shared), ("shared_down", False, cfg.n_shared)):
         if not stage.startswith("shared") or n_sh:
             kernels[stage] = grace.grace_ffn_kernel(up, T, d, f, layer.dt, k=k, S=max(1, len(experts)), I=table.I, n_shared=n_sh)[0]
-    carries_rows = fused_scatter and kernels["shared_up"] == "persist" and d * el % 1024 == 0
-    # without them the experts' gate+up projection reads the tokens and moves the rows, where the large tiles take it
+    carries_rows = fused_scatter and grace.grace_ffn_carries_rows(T, d, f, layer.dt, k=k, n_shared=cfg.n_shared)
+    # without them the experts' gate+up projection reads the tokens and moves the rows, where its launch can
     gathers_rows = bool(getattr(layer, "gather_rows", False))
     bytes_dispatch = bytes_route + (12 * T * k if fused_scatter or gathers_rows else bytes_permute)
     # algorithmic work per launch of the kernel behind each call: (bound, amount, unit scale, peak)

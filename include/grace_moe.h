@@ -317,8 +317,8 @@ int grace_expert_ffn_down_share(const grace_table *table, int32_t rank, const in
                                 void *ws, void *stream);
 
 /* grace_permute_rows followed by grace_expert_ffn_up_share on the rows it has moved, as one call: for prefill batches, where the
- * large-tile kernel takes the projection (GRACE_KERNEL_PERSIST of grace_ffn_kernel), that launch reads the
- * rank's rows from x and moves all rows to xp as it runs.  Same results as the two calls, bit for bit.
+ * large-tile kernel takes the projection, that launch reads the rank's rows from x and moves all rows to xp as it runs
+ * (grace_ffn_carries_rows; two launches elsewhere).  Same results as the two calls, bit for bit.
  * DEVICE: x [T,d]; perm_pos, perm_src [T*k] and inst_off of grace_permute / grace_route_permute called with x == NULL; xp [T*k,d]. */
 int grace_expert_ffn_up_share_scatter(const grace_table *table, int32_t rank, const void *x, const int32_t *perm_pos,
                                       const int32_t *perm_src, void *xp, const int32_t *inst_off, int32_t T, int32_t k, int32_t d,
@@ -345,8 +345,8 @@ int grace_shared_ffn_down(int32_t T, int32_t d, int32_t f, int32_t n_shared, gra
  * call: both read only x (and perm_pos), the projection is bound by the matrix cores and the row
  * movement by HBM, so where the large-tile kernel takes the projection (GRACE_KERNEL_PERSIST of
  * grace_ffn_kernel: large batches, d a multiple of 64), rows are multiples of 1024 bytes and a token has 64 choices
- * at most it carries them along (every wavefront moves a 1 KB piece of a token row every few K steps) instead
- * of a launch of its own; other shapes and batches run the two launches.  Outputs are those of the two calls, bit
+ * at most it carries them along (grace_ffn_carries_rows; every wavefront moves a 1 KB piece of a token row every few
+ * K steps) instead of a launch of its own; other shapes and batches run the two launches.  Outputs are those of the two calls, bit
  * for bit: the hidden activation in ws and xp[perm_pos[t*k+j]] = x[t].
  * DEVICE: perm_pos [T*k] from grace_permute / grace_route_permute called with x == NULL; xp [T*k,d];
  * the rest as for grace_shared_ffn_up.  xp must not overlap x or ws. */
@@ -397,6 +397,11 @@ typedef enum {
 } grace_kernel;
 int grace_ffn_kernel(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I,
                      grace_dtype dt, int32_t n_cu, int32_t *kernel, int64_t *work_items);
+
+/* Does the launch of the gate+up projection of these sizes (as for grace_ffn_kernel) move the dispatch rows as well when
+ * grace_expert_ffn_up_share_scatter or grace_shared_ffn_up_scatter asks for it?  0: a launch of its own does, ahead of it. */
+int grace_ffn_carries_rows(int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I, grace_dtype dt,
+                           int32_t n_cu, int32_t *carried);
 
 /* Text of the calling thread's most recent error ("" if none).  The pointer
  * stays valid until the thread's next failing call. */

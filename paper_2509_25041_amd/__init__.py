@@ -23,6 +23,7 @@ from .binding import (  # noqa: F401
     grace_expert_ffn_up,
     grace_expert_ffn_up_share,
     grace_expert_ffn_up_share_scatter,
+    grace_ffn_carries_rows,
     grace_ffn_kernel,
     grace_last_error,
     grace_mfma_sustained,

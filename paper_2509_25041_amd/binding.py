@@ -22,7 +22,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_permute", "grace_permute_rows", "grace_route_permute", "grace_route_permute_static", "grace_send_lists", "grace_send_lists_fresh", "grace_expert_ffn", "grace_expert_ffn_up",
            "grace_expert_ffn_down", "grace_expert_ffn_down_fresh", "grace_expert_ffn_up_share", "grace_expert_ffn_up_share_scatter", "grace_expert_ffn_down_share",
            "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_combine_share", "grace_mfma_sustained",
-           "grace_ffn_kernel",
+           "grace_ffn_kernel", "grace_ffn_carries_rows",
            "grace_last_error")
 
 _lib: Optional[C.CDLL] = None
@@ -84,6 +84,7 @@ def load_library() -> C.CDLL:
     lib.grace_combine_share.argtypes = [vp, vp, vp, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_mfma_sustained.argtypes = [i32, i32, C.POINTER(C.c_double), vp]
     lib.grace_ffn_kernel.argtypes = [i32] * 8 + [C.c_int, i32, C.POINTER(i32), C.POINTER(C.c_int64)]
+    lib.grace_ffn_carries_rows.argtypes = [i32, i32, i32, i32, i32, i32, i32, C.c_int, i32, vp]
     for name in EXPORTS:
         if name not in ("grace_last_error", "grace_workspace_bytes"):
             getattr(lib, name).restype = C.c_int
@@ -529,3 +530,11 @@ def grace_ffn_kernel(up: bool, T: int, d: int, f: int, dt: int = GRACE_BF16, *, 
     kernel, items = C.c_int32(), C.c_int64()
     _check(load_library().grace_ffn_kernel(int(up), T, k, d, f, n_shared, S, I, dt, n_cu, C.byref(kernel), C.byref(items)))
     return FFN_KERNELS[kernel.value], int(items.value)
+
+
+def grace_ffn_carries_rows(T: int, d: int, f: int, dt: int = GRACE_BF16, *, k: int = 1, S: int = 1, I: int = 1, n_shared: int = 0,
+                           n_cu: int = 0) -> bool:
+    """Does the gate+up projection's launch move the dispatch rows too (see grace_moe.h)?"""
+    carried = C.c_int32()
+    _check(load_library().grace_ffn_carries_rows(T, k, d, f, n_shared, S, I, dt, n_cu, C.byref(carried)))
+    return bool(carried.value)

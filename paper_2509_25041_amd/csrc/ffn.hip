@@ -667,3 +667,13 @@ extern "C" int grace_ffn_kernel(int32_t up, int32_t T, int32_t k, int32_t d, int
     *work_items = l.groups * l.threads;
     return GRACE_OK;
 }
+
+extern "C" int grace_ffn_carries_rows(int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I, grace_dtype dt,
+                                      int32_t n_cu, int32_t *carried) {
+    if (!carried) return fail(GRACE_EINVAL, "ffn_carries_rows: null output");
+    int32_t kernel;
+    int64_t work_items;
+    const int rc = grace_ffn_kernel(1, T, k, d, f, n_shared, S, I, dt, n_cu, &kernel, &work_items);
+    if (rc == GRACE_OK) *carried = carries_rows((Route)kernel, dt, T, k, d, n_shared == 0);
+    return rc;
+}

@@ -7,7 +7,7 @@ from typing import List, Optional, Tuple
 
 import torch
 
-from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_ffn_kernel, grace_workspace_bytes, load_library
+from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_ffn_carries_rows, grace_workspace_bytes, load_library
 
 STAGES = ("route", "permute", "route_permute", "ffn_up", "ffn_down", "shared_up", "shared_down", "combine")
 
@@ -71,9 +71,9 @@ class GraceMoELayer:
         # experts' gate+up projection (grace_shared_ffn_up_scatter: carried by its launch for large batches, a launch
         # ahead of it otherwise), which then runs ahead of the expert FFN; False: the scatter is part of the dispatch call
         self.fuse_scatter = self.n_shared > 0
-        # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows
-        self.gather_rows = (not self.n_shared and S > 0 and T > 0 and
-                            grace_ffn_kernel(True, T, d, f, self.dt, k=k, S=S, I=table.I)[0] == "persist")
+        # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows;
+        # elsewhere the dispatch call moves them (small batches in its one launch)
+        self.gather_rows = not self.n_shared and S > 0 and T > 0 and grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I)
         self.ws_shared = None
         self._key = None
         self._calls: List[Tuple[str, object, tuple]] = []

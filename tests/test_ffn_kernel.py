@@ -100,3 +100,27 @@ def test_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
 ])
 def test_f32_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
     assert grace.grace_ffn_kernel(up, T, d, f, F32, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU)[0] == want
+
+
+@pytest.mark.parametrize("T,k,d,f,n_shared,S,I,dt,want", [
+    (7001, 8, 2048, 768, 0, 16, 130, BF16, True), (32768, 6, 2048, 1408, 2, 1, 1, BF16, True),
+    (100, 8, 2112, 1024, 0, 32, 64, BF16, False),        # large tiles, rows that are no whole 1 KB
+    (2000, 65, 2048, 1024, 0, 66, 66, BF16, False),      # more choices than a wavefront has lanes
+    (1500, 65, 512, 1024, 2, 1, 1, BF16, False), (1500, 64, 512, 1024, 2, 1, 1, BF16, True),
+    (524288, 2, 2048, 1024, 0, 8, 8, BF16, False),       # tokens of 2 GB: the experts' kernel reads them at 32-bit offsets ...
+    (524288, 2, 2048, 1024, 1, 1, 1, BF16, True),        # ... the shared experts' moves rows at 64-bit ones
+    (2 ** 28, 2, 512, 1024, 1, 1, 1, BF16, False),       # T * k of 2^29
+    (200, 8, 2048, 1024, 0, 16, 66, BF16, False), (5000, 8, 2048, 768, 0, 4, 8, F32, False),   # other kernels
+])
+def test_rows_carried_by_the_gate_up_projection(T, k, d, f, n_shared, S, I, dt, want):
+    kernel = grace.grace_ffn_kernel(True, T, d, f, dt, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU)[0]
+    assert grace.grace_ffn_carries_rows(T, d, f, dt, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU) == want
+    assert kernel == ("persist" if S != 16 or I != 66 else "mid") or dt == F32
+
+
+def test_row_query_refuses_what_the_kernel_query_refuses():
+    for bad in (dict(T=0), dict(k=0), dict(d=12, f=8), dict(S=3, I=2)):
+        a = {**dict(T=4, d=64, f=64, k=1, S=1, I=1), **bad}
+        with pytest.raises(grace.GraceError):
+            grace.grace_ffn_carries_rows(a["T"], a["d"], a["f"], BF16, k=a["k"], S=a["S"], I=a["I"], n_cu=N_CU)
+    assert grace.load_library().grace_ffn_carries_rows(4, 1, 64, 64, 0, 1, 1, BF16, N_CU, None) == -1

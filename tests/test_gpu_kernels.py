@@ -578,3 +578,19 @@ def test_gate_up_projection_that_moves_the_rows(T, k, d, f, S, I, dtype, want):
     for a, b in zip(*results):
         assert torch.equal(a, b)
     assert torch.equal(results[0][0][:n], x[(src[:n] // k).long()])
+
+
+@pytest.mark.parametrize("T,k,d,f,S,I,want", [(2100, 17, 1024, 512, 20, 40, True), (100, 8, 2112, 1024, 32, 64, False), (1500, 64, 512, 512, 66, 66, True)])
+def test_layer_has_its_rows_moved_where_the_projection_carries_them(T, k, d, f, S, I, want):
+    """... and by the dispatch call elsewhere, also where the large tiles take the projection."""
+    assert kernels_of(T, k, d, f, S, I)[0] == "persist"
+    table = grace.GraceTable(I, I // S, 1, [0] * (I // S), [1] * (I // S), list(range(I + 1)), [e // S for e in range(I)])
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    w = [(0.05 * torch.randn(s, generator=gen, device="cuda")).bfloat16() for s in ((S, f, d), (S, f, d), (S, d, f))]
+    layer = grace.GraceMoELayer(table, 0, T, k, d, f, torch.bfloat16, *w)
+    assert layer.gather_rows is want
+    x, logits = torch.randn((T, d), generator=gen, device="cuda").bfloat16(), torch.randn((T, I), generator=gen, device="cuda")
+    layer.forward(logits, x)
+    assert torch.equal(layer.xp, x[(layer.perm_out[1] // k).long()])
+    y = grace.grace_expert_ffn(table, 0, layer.xp, layer.perm_out[2], T, k, *w)
+    assert torch.equal(layer.y, y)
