@@ -2,12 +2,17 @@
 // sum it is, and a product is the sum of the six partial products down to 2^-18 of it.
 //
 // x = x1 + x2 + x3 exactly, each part x's next 8 bits (rounded to nearest, so the parts have signs of their own); a product a b is
-// a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1), each of them exact in fp32, and what is left out, about 2^-26 of it, is less than the
-// rounding of one fp32 product.  The leading products have accumulators of their own, so what an addition rounds away is a part of
-// their sum once per 32 K, and of the others 2^-8 of that.  Error of expert FFNs against 64 bits (2-norm; the fp32 matrix
-// instruction with its chains of K / 16 -> this kernel): d = 1024, f = 2816 6.4e-7 -> 3.8e-7, d = 2048, f = 768 6.5e-7 ->
-// 4.5e-7, d = 548, f = 1388 4.6e-7 -> 3.9e-7.  A row whose largest value lies outside 2^-40 .. 2^60 (or is infinite) sends its
-// tiles to the fp32 instruction; NaNs pass through the parts.
+// a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1), each of them exact in fp32.  What is left out, a2 b3 + a3 b2 + a3 b3, is 2^-27.5 of the
+// product (root mean square; the rounding of one fp32 product 2^-25.2), 0.85 * 2^-24 at most.  The leading products have accumulators of
+// their own, so what an addition rounds away is a part of their sum once per 32 K, and of the others 2^-8 of that.  Error of expert FFNs
+// against 64 bits (2-norm; the fp32 matrix instruction with its chains of K / 16 -> this kernel): d = 1024, f = 2816 6.4e-7 -> 3.8e-7, d =
+// 2048, f = 768 6.5e-7 -> 4.5e-7, d = 548, f = 1388 4.6e-7 -> 3.9e-7.  Of a sum with a single product other than zero, 2^-24: 0.424 -> 0.433
+// (root mean square), 1.0 -> 1.6 at most.
+//
+// Values below 2^-110 lose their third part and products can leave the range of fp32 on the way that their sum stays in, so every sum is
+// looked at when it is done: one that is not far above all that can have got lost, or not finite, is computed again with the fp32
+// instruction (doubtful, by_f32: about 1e-26 with rows of ordinary size).  It is each element's own matter, and the order in which a sum is
+// taken depends on its weights and the host's sizes alone: a row's result does not depend on the batch around it.
 //
 // Bound by what the fp32 instruction is not: six bf16 instructions of 16 cycles take 96 for what takes that one 256, so what is left
 // is the split, the LDS and above all the operands' way to the compute units (a tile of 80 x 128 has 25 operations per byte).
@@ -34,9 +39,24 @@ constexpr int A_PLANE = BM * BK * 2, B_PLANE = B_WAVE_ROWS * BK * 2;
 constexpr int BUFFER_BYTES = 3 * (A_PLANE + 4 * B_PLANE), GROUP_BYTES = 2 * BUFFER_BYTES;   // LDS of four wavefronts
 static_assert(2 * GROUP_BYTES <= 160 * 1024, "two groups per compute unit");
 
-// Magnitudes up to which a row's largest value may go for the split: outside, a partial product or the third part of a value could leave
-// the range of normal numbers, and an infinity has no parts.  Tiles with such a row take the fp32 matrix instruction.
-constexpr uint32_t MAX_BITS = (uint32_t)(127 + 60) << 23, MIN_BITS = (uint32_t)(127 - 40) << 23;
+// Can underflow or overflow have touched a sum of K products, as the parts give it?  am, bm: the largest magnitudes of its two rows.  What can
+// get lost on the way, parts, partial products and sums below 2^-126, is less than K * 2^-125 * (am + bm + 8); a sum of 2^25 times that
+// does not feel it.
+__device__ __forceinline__ float least_of(float am, float bm, int K) { return (float)K * 0x1p-100f * (am + bm + 8.0f); }
+__device__ __forceinline__ bool doubtful(float sum, float am, float bm, int K) {
+    const float s = fabsf(sum);
+    if (s >= least_of(am, bm, K) && s < INFINITY) return false;
+    if (s == 0.0f && (am == 0.0f || bm == 0.0f)) return false;
+    return !(s != s && am < 0x1p47f && bm < 0x1p47f);   // no product overflows: it is the NaN of an operand
+}
+// Is one of the four sums too small for `least` or not finite?  (how all but the odd tile are done with: three instructions per sum)
+__device__ __forceinline__ bool any_out(const f32x4_t &sum, float least) {
+    const uint32_t from = __float_as_uint(least);
+    uint32_t most = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) most = max(most, (__float_as_uint(sum[v]) & 0x7fffffffu) - from);
+    return most >= 0x7f800000u - from;
+}
 
 template <bool FUSED_UP>
 struct Shape {
@@ -62,55 +82,56 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t &hi, uint32_t 
     lo = pack_bf16x2(x, y);
 }
 
-// The tile without splitting: fragments straight from memory, no look-ahead.
-template <bool FUSED_UP, bool SEG_K, int MF, int NJ>
-__device__ __forceinline__ void tile_by_f32(const GemmArgs &g, __amdgpu_buffer_rsrc_t a_rsrc, __amdgpu_buffer_rsrc_t b0_rsrc, __amdgpu_buffer_rsrc_t b1_rsrc,
-                                            int rows, int cols, int lane, f32x4_t (&acc)[MF][NJ]) {
+// The elements of a tile whose bits are set in `bad` (four per fragment, as tile_body numbers them) with the fp32 matrix instruction:
+// fragments straight from memory, one after the other.  wn: the wavefront's first output column; nj: its fragments per 16 rows.
+template <bool FUSED_UP, bool SEG_K>
+__device__ __forceinline__ void by_f32(const GemmArgs &g, int slot, int m0, int m_end, int wn, int nj, uint64_t bad, int lane) {
     const int r = lane & 15, q = lane >> 4;
-    f32x4_t part[4][MF][NJ];   // chains of K / 16 additions
+    const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 4);
+    const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 4;
+    const auto b0_rsrc = rsrc_of((const char *)g.B0 + b_first);
+    const auto b1_rsrc = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
+    constexpr int NB = FUSED_UP ? 2 : 1;
+    for (int f = 0; __any(bad != 0); ++f, bad >>= 4) {
+        const int mine = (int)bad & 15;
+        if (!__any(mine)) continue;
+        const int i = f / nj, j = f - i * nj, row = i * 16 + r, n = j * 16 + r;
+        const uint32_t a_off = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 4) : NO_DATA;
+        const uint32_t b_off = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 4) : NO_DATA;
+        f32x4_t part[NB][4];   // chains of K / 16 additions
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int i = 0; i < MF; ++i)
+            for (int m = 0; m < NB; ++m) part[m][v] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+        for (int k0 = 0; k0 < g.K; k0 += 16) {
+            const int k = k0 + 4 * q;   // (K is a multiple of 4)
+            const uint32_t ka = k < g.K ? (uint32_t)k * 4u : NO_DATA;
+            const uint32_t kb = SEG_K && k < g.K ? (uint32_t)(koff(g, k) * 4) : ka;
+            const f32x4_t fa = __builtin_bit_cast(f32x4_t, load16(a_rsrc, offset_with(a_off, ka), 0));
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) part[v][i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k0 = 0; k0 < g.K; k0 += 16) {
-        const int k = k0 + 4 * q;
-        const uint32_t none = k < g.K ? 0u : NO_DATA;
-        const uint32_t kb = none ? none : (uint32_t)((SEG_K ? koff(g, k) : (int64_t)k) * 4);
-        f32x4_t fb[NJ];
+            for (int m = 0; m < NB; ++m) {
+                const f32x4_t fb = __builtin_bit_cast(f32x4_t, load16(m ? b1_rsrc : b0_rsrc, offset_with(b_off, kb), 0));
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int n = FUSED_UP ? (NJ == 2 ? r : r & 7) : j * 16 + r;
-            const uint32_t off = n < cols ? (uint32_t)n * (uint32_t)(g.ldb * 4) : NO_DATA;
-            // (both matrices' loads for gate+up with one fragment, whose halves are 8 rows of each)
-            fb[j] = __builtin_bit_cast(f32x4_t, load16(FUSED_UP && j == 1 ? b1_rsrc : b0_rsrc, offset_with(off, kb), 0));
-            if constexpr (FUSED_UP && NJ == 1) {
-                const f32x4_t up = __builtin_bit_cast(f32x4_t, load16(b1_rsrc, offset_with(off, kb), 0));
-                fb[j] = r >= 8 ? up : fb[j];
+                for (int v = 0; v < 4; ++v) part[m][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[v], fa[v], part[m][v], 0, 0, 0);
             }
         }
+        float *const o = (float *)g.out + (int64_t)(m0 + row) * g.ldo + wn + j * 16 + 4 * q;
 #pragma unroll
-        for (int i = 0; i < MF; ++i) {
-            const int row = i * 16 + r;
-            const uint32_t off = row < rows ? (uint32_t)row * (uint32_t)(g.lda * 4) : NO_DATA;
-            const f32x4_t fa = __builtin_bit_cast(f32x4_t, load16(a_rsrc, offset_with(off, none ? none : (uint32_t)k * 4u), 0));
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) part[v][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][v], fa[v], part[v][i][j], 0, 0, 0);
+        for (int v = 0; v < 4; ++v) {
+            float h = (part[0][0][v] + part[0][1][v]) + (part[0][2][v] + part[0][3][v]);
+            if constexpr (FUSED_UP) h = h / (1.0f + expf(-h)) * ((part[1][0][v] + part[1][1][v]) + (part[1][2][v] + part[1][3][v]));
+            if (mine >> v & 1) o[v] = h;
         }
     }
-#pragma unroll
-    for (int i = 0; i < MF; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]);
 }
 
 // MF: activation fragments of 16 rows.  NJ: weight fragments per wavefront, 2, or 1 for half a tile's weight rows (gate+up: then 8
 // rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K axis is cut in segments.
+// Returns this lane's doubtful elements, which by_f32 is to compute: bit 4 f + v for element v of output fragment f (16 rows after 16
+// rows, the columns of one after the other).
 template <bool FUSED_UP, bool SEG_K, int K_GROUPS, int MF, int NJ>
-__device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int rotation, char *smem) {
+__device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int rotation, char *smem) {
     constexpr int AHEAD = MF > 3 ? 2 : 4;   // steps in flight (even)
     constexpr int AL = MF / 2;              // activation loads of 16 bytes per thread and step: 32 rows each
     constexpr bool HALF = MF % 2 != 0;      // and one of 8 bytes for the last 16 rows
@@ -234,7 +255,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
     };
     // One step: LDS buffer `buf` is multiplied while the other one gets the parts of register set `set`.  A matrix instruction
     // holds its unit for 16 cycles, as long as four vector instructions theirs, and a wavefront issues in order, so the two are
-    // dealt out one to one; the compiler's own order multiplies first and splits then (MEASURE_ORDER).
+    // dealt out one to one; the compiler's own order multiplies first and splits then (114 instead of 100 us, see above).
     auto step_body = [&](int buf, int set) {
         constexpr int MFMAS = 6 * MF * NJ;
         const char *const a = smem + buf * BUFFER_BYTES, *const b = sb + buf * BUFFER_BYTES;
@@ -309,23 +330,28 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] += low[i][j];
 
-    // ---- rows out of the split's range (the lanes of a row are neighbours) ----
-    bool out_of_range = false;
-    auto look = [&](float most, int lanes) {
+    // ---- largest magnitudes of the rows (the lanes of a row are neighbours) and the other group's sums, through LDS (the last step
+    // ended with a barrier) ----
+    float *const a_most = (float *)all, *const b_most = a_most + K_GROUPS * BM;   // [K_GROUPS][BM], [K_GROUPS][4][B_WAVE_ROWS]
+    auto of_row = [&](float most, int lanes) {
 #pragma unroll
         for (int o = 1; o < lanes; o <<= 1) most = fmaxf(most, __shfl_xor(most, o, 64));
-        const uint32_t bits = __float_as_uint(most);
-        out_of_range |= bits > MAX_BITS || (bits != 0u && bits < MIN_BITS);
+        return most;
     };
 #pragma unroll
-    for (int i = 0; i < AL; ++i) look(a_max[i], 8);
+    for (int i = 0; i < AL; ++i) {
+        const float most = of_row(a_max[i], 8);
+        if (chunk == 0) a_most[group * BM + i * 32 + row_of] = most;
+    }
+    if (HALF) {
+        const float most = of_row(h_max, 16);
+        if (h_chunk == 0) a_most[group * BM + h_row] = most;
+    }
 #pragma unroll
-    for (int i = 0; i < 2 * NJ; ++i) look(b_max[i], 8);
-    if (HALF) look(h_max, 16);
-    // ---- the other group's sums (the last step ended with a barrier) ----
-    uint64_t *const found = (uint64_t *)all;
-    const uint64_t mine = __ballot(out_of_range);
-    if (lane == 0) found[group * 4 + wave] = mine;
+    for (int i = 0; i < 2 * NJ; ++i) {
+        const float most = of_row(b_max[i], 8);
+        if (chunk == 0) b_most[(group * 4 + wave) * B_WAVE_ROWS + i * 8 + b_row] = most;
+    }
     [[maybe_unused]] f32x4_t *const sums = (f32x4_t *)(all + GROUP_BYTES) + (wave * MF * NJ) * 64 + lane;
     if (group != 0) {
 #pragma unroll
@@ -334,20 +360,36 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
             for (int j = 0; j < NJ; ++j) sums[(i * NJ + j) * 64] = acc[i][j];
     }
     __syncthreads();
-    if (group != 0) return;
+    if (group != 0) return 0;
     if constexpr (K_GROUPS > 1) {
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] += sums[(i * NJ + j) * 64];
     }
-    uint64_t any = 0;
+    auto a_most_of = [&](int row) { return K_GROUPS > 1 ? fmaxf(a_most[row], a_most[BM + row]) : a_most[row]; };
+    auto b_most_of = [&](int row) {
+        const float *const at = b_most + wave * B_WAVE_ROWS + row;
+        return K_GROUPS > 1 ? fmaxf(at[0], at[4 * B_WAVE_ROWS]) : at[0];
+    };
+    float b_most4[NJ];   // of the four columns that a lane has of a fragment
 #pragma unroll
-    for (int i = 0; i < 4 * K_GROUPS; ++i) any |= found[i];
-    if (any) tile_by_f32<FUSED_UP, SEG_K, MF, NJ>(g, a_rsrc, b0_rsrc, b1_rsrc, m_end - m0, g.N - wn, lane, acc);
+    for (int j = 0; j < NJ; ++j) b_most4[j] = fmaxf(fmaxf(b_most_of(j * 16 + 4 * q), b_most_of(j * 16 + 4 * q + 1)), fmaxf(b_most_of(j * 16 + 4 * q + 2), b_most_of(j * 16 + 4 * q + 3)));
+    bool out_of_range = false;
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+        const float am = a_most_of(i * 16 + r);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int col = FUSED_UP ? (NJ == 2 ? wn + 4 * q : wn + 4 * (q & 1)) : wn + j * 16 + 4 * q;
+            out_of_range |= any_out(acc[i][j], least_of(am, b_most4[j], g.K)) && m0 + i * 16 + r < m_end && col < g.N;
+        }
+    }
+    const bool look = __any(out_of_range);   // at each of them
 
     // ---- epilogue: element v of lane l of a fragment is output column 4 * (l / 16) + v, row l % 16 ----
     float *const out = (float *)g.out;
+    uint64_t bad = 0;
 #pragma unroll
     for (int i = 0; i < MF; ++i) {
         const int row = m0 + i * 16 + r;
@@ -366,6 +408,12 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
             for (int v = 0; v < 4; ++v) {
                 h[v] = acc[i][j][v];
                 if (FUSED_UP) h[v] = h[v] / (1.0f + expf(-h[v])) * up[v];
+                if (look) {
+                    const float am = a_most_of(i * 16 + r);
+                    bool again = doubtful(acc[i][j][v], am, b_most_of(j * 16 + 4 * q + v), g.K);
+                    if (FUSED_UP) again |= doubtful(up[v], am, b_most_of(NJ * 8 + 4 * q + v), g.K);
+                    if (again && col + v < g.N) bad |= (uint64_t)1 << ((FUSED_UP ? i : i * NJ + j) * 4 + v);
+                }
             }
             float *const o = out + (int64_t)row * g.ldo + col;
             if (g.N % 4 == 0) {
@@ -377,6 +425,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
             }
         }
     }
+    return bad;
 }
 
 // SEG_PER_LANE: 1 for up to 64 row segments, 4 for up to 256.  Pieces of a segment have one size, and tiles are numbered and dealt to the
@@ -415,22 +464,25 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
         const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
         const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows);
         const int n0 = strip * (halves ? Shape<FUSED_UP>::BN / 2 : Shape<FUSED_UP>::BN);
-        const int rotation = (s.slot * strips + strip) / 4;
+        const int rotation = (s.slot * n_strips + (halves ? strip >> 1 : strip)) / 4;   // (of the weights alone: see above)
         if (again) __syncthreads();   // the tile before has been read
         auto tile = [&](auto nj) {
             constexpr int NJ = decltype(nj)::value;
             switch ((m_end - m0 + 15) >> 4) {
                 case 1:
-                case 2: tile_body<FUSED_UP, SEG_K, K_GROUPS, 2, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
-                case 3: tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
-                case 4: tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
-                case 5: tile_body<FUSED_UP, SEG_K, K_GROUPS, 5, NJ>(g, s.slot, m0, m_end, n0, rotation, smem); break;
-                default: break;   // no rows
+                case 2: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 2, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
+                case 3: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
+                case 4: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
+                case 5: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 5, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
+                default: return (uint64_t)0;   // no rows
             }
         };
         if (n0 < g.N) {
-            if (halves) tile(std::integral_constant<int, 1>{});
-            else tile(std::integral_constant<int, 2>{});
+            const uint64_t bad = halves ? tile(std::integral_constant<int, 1>{}) : tile(std::integral_constant<int, 2>{});
+            if (__any(bad != 0)) {
+                const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) & 3, nj = halves ? 1 : 2;
+                by_f32<FUSED_UP, SEG_K>(g, s.slot, m0, m_end, n0 + wave * (FUSED_UP ? 8 : 16) * nj, FUSED_UP ? 1 : nj, bad, lane);
+            }
         }
         if (!more) break;
     }

@@ -288,6 +288,69 @@ def test_f32_split_kernel_infinities_and_nans():
     assert rel_err(y[rest].cpu().numpy().astype(np.float64), plain[rest].cpu().numpy().astype(np.float64)) <= TOL["f32"]
 
 
+def test_f32_split_rows_do_not_depend_on_their_neighbours():
+    """Bit for bit the same row whatever else is in the batch: few rows (half tiles, low pieces) or many (whole tiles), ordinary ones or such
+    as are computed without the split."""
+    T, k, d, f = 1000, 2, 1024, 2816
+    few, many = [40, 3, 1, 0], [700, 600, 300, 400]
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    table = grace.GraceTable(4, 1, 1, [0], [1], list(range(5)), [0] * 4)
+    w = [0.05 * torch.randn(s, generator=gen, device="cuda") for s in ((4, f, d), (4, f, d), (4, d, f))]
+    w[0][1, 7, 5] = 1e-36      # (one of a column's values: that column alone is affected, if any)
+    x = torch.randn((T * k, d), generator=gen, device="cuda")
+    first = np.concatenate([[0], np.cumsum(many)])
+    y = []
+    for segs, odd in ((few, False), (many, False), (many, True)):
+        off = np.concatenate([[0], np.cumsum(segs)]).astype(np.int32)
+        xs = x.clone()
+        for s in range(4):
+            xs[off[s]:off[s] + few[s]] = x[first[s]:first[s] + few[s]]
+            if odd:
+                xs[off[s] + few[s]:off[s + 1]:3] = torch.tensor([1e-30, 1e25, float("inf"), float("nan")][s], device="cuda")
+        out = grace.grace_expert_ffn(table, 0, xs, torch.from_numpy(off).cuda(), T, k, *w)
+        y.append(torch.cat([out[off[s]:off[s] + few[s]] for s in range(4)]))
+    assert torch.equal(y[0], y[1]) and torch.equal(y[0], y[2])
+
+
+def test_f32_split_keeps_small_values_of_a_row_with_large_ones():
+    """An element of 2^-120 next to 1: its lowest parts lie below the range of bf16, and it is all that its column sees."""
+    T, d, f = 200, 1024, 512
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    table = grace.GraceTable(1, 1, 1, [0], [1], [0, 1], [0])
+    x = torch.zeros((T, d), device="cuda")
+    x[:, 0] = 1.0
+    x[:, 1] = 2.0 ** -120 * (1.0 + torch.rand(T, generator=gen, device="cuda"))
+    wg, wu, wd = (torch.randn(s, generator=gen, device="cuda") for s in ((1, f, d), (1, f, d), (1, d, f)))
+    wg[0, :, 0] = 0.0
+    wg[0, :, 1] = 2.0 ** 30 * (1.0 + torch.rand(f, generator=gen, device="cuda"))
+    wu[0, :, 0] *= 2.0 ** 50
+    y = grace.grace_expert_ffn(table, 0, x, torch.tensor([0, T], dtype=torch.int32, device="cuda"), T, 1, wg, wu, wd)
+    h = torch.nn.functional.silu(x.double() @ wg[0].double().T) * (x.double() @ wu[0].double().T)
+    assert rel_err(y.cpu().numpy().astype(np.float64), (h @ wd[0].double().T).cpu().numpy()) <= TOL["f32"]   # (1.3e-6; 5.9e-5 without)
+
+
+@pytest.mark.parametrize("T", [97, 7000])           # both numbers of groups that share K
+@pytest.mark.parametrize("odd", ["small", "infinite"])
+def test_f32_split_of_segmented_k_out_of_range(T, odd):
+    """Shared experts' down projection, K segments off the step: sums too small for the split, and infinities among the weights."""
+    d, f, n_shared = 520, 200, 3
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn((T, d), generator=gen, device="cuda") * (1e-14 if odd == "small" else 1.0)
+    wg, wu, wd = (0.05 * torch.randn(s, generator=gen, device="cuda") for s in ((n_shared, f, d), (n_shared, f, d), (n_shared, d, f)))
+    if odd == "infinite":
+        wd[1, 17, 150] = float("inf")
+    y = grace.grace_shared_ffn(x, wg, wu, wd).cpu().numpy().astype(np.float64)
+    want = 0.0
+    for s in range(n_shared):
+        h = torch.nn.functional.silu(x.double() @ wg[s].double().T) * (x.double() @ wu[s].double().T)
+        want = want + h @ wd[s].double().T
+    want = want.cpu().numpy()
+    if odd == "infinite":
+        assert (y[:, 17] == want[:, 17]).all() and np.isinf(y[:, 17]).all()
+        y, want = np.delete(y, 17, axis=1), np.delete(want, 17, axis=1)
+    assert rel_err(y, want) <= TOL["f32"]
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,d,f,n_shared", [(1, 2048, 1408, 2), (64, 512, 96, 3), (33, 136, 200, 2), (97, 520, 40, 3),
                                             (1100, 1024, 200, 3),    # 12 pieces x 8 strips: more than one tile per run of an XCD
