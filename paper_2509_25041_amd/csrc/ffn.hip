@@ -48,7 +48,7 @@ static int compute_units() {
 
 // The persistent kernel needs the 160 KB of dynamic LDS opted in, once per kernel and device.
 static bool allow_full_lds(const void *kernel, const char *what) {
-    constexpr int MAX_KERNELS = 24, MAX_DEVICES = 64;
+    constexpr int MAX_KERNELS = 16, MAX_DEVICES = 64;
     static std::mutex mu;
     static const void *known[MAX_KERNELS] = {nullptr};
     static bool done[MAX_KERNELS][MAX_DEVICES] = {{false}};
@@ -323,22 +323,14 @@ static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, hi
 
 template <bool FUSED_UP>
 static int launch_split(const GemmArgs &g, const Grid &l, int n_cu, hipStream_t st, const char *what) {
-    const int n_strips = (g.N + split::Shape<FUSED_UP>::BN - 1) / split::Shape<FUSED_UP>::BN;
-    auto launch = [&](auto *kernel) {
-        if (!allow_full_lds((const void *)kernel, what)) return (int)GRACE_EHIP;
-        kernel<<<(unsigned)l.groups, l.threads, l.threads / 256 * split::GROUP_BYTES, st>>>(g, n_strips, n_cu);
-        return (int)GRACE_OK;
-    };
-    if constexpr (FUSED_UP) {
-        return g.S <= 64 ? launch(&split::gemm_f32_split_kernel<true, false, 1, 1>) : launch(&split::gemm_f32_split_kernel<true, false, 4, 1>);
-    } else {
-        auto of = [&](auto groups) {
-            constexpr int G = decltype(groups)::value;
-            if (g.kseg_len < g.K) return launch(&split::gemm_f32_split_kernel<false, true, 1, G>);
-            return g.S <= 64 ? launch(&split::gemm_f32_split_kernel<false, false, 1, G>) : launch(&split::gemm_f32_split_kernel<false, false, 4, G>);
-        };
-        return l.threads == 256 ? of(std::integral_constant<int, 1>{}) : of(std::integral_constant<int, 2>{});
-    }
+    const int groups = l.threads / 256;
+    const void *kernel = FUSED_UP ? split::up_kernel() : g.kseg_len < g.K ? split::shared_down_kernel(groups) : split::down_kernel(groups);
+    if (!allow_full_lds(kernel, what)) return GRACE_EHIP;
+    GemmArgs args = g;
+    int n_strips = (g.N + split::Shape<FUSED_UP>::BN - 1) / split::Shape<FUSED_UP>::BN;
+    void *params[] = {&args, &n_strips, &n_cu};
+    const hipError_t e = hipLaunchKernel(kernel, dim3((unsigned)l.groups), dim3(l.threads), params, groups * split::GROUP_BYTES, st);
+    return e == hipSuccess ? (int)GRACE_OK : fail(GRACE_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
 template <bool FUSED_UP>

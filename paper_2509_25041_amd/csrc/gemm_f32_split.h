@@ -27,6 +27,9 @@
 // 106, down 92 -> 80; 300 rows 62 -> 48, 62 -> 38; 2000 rows in 16 segments 253 -> 184, 159 -> 91; 16000 rows 1633 -> 1079 (171
 // TFLOP/s, the fp32 instruction's own peak is 157), 793 -> 553.  70 rows, bound by the weights (207 MB), 45 -> 47.
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "bf16.h"
 #include "gemm_bf16_mid.h"
 
@@ -38,6 +41,19 @@ constexpr int MAX_MF = BM / 16, B_WAVE_ROWS = 32;
 constexpr int A_PLANE = BM * BK * 2, B_PLANE = B_WAVE_ROWS * BK * 2;
 constexpr int BUFFER_BYTES = 3 * (A_PLANE + 4 * B_PLANE), GROUP_BYTES = 2 * BUFFER_BYTES;   // LDS of four wavefronts
 static_assert(2 * GROUP_BYTES <= 160 * 1024, "two groups per compute unit");
+
+// The products that make one, the smallest first: part of the weight, part of the activation (0: the leading ones).
+constexpr int PRODUCTS = 6, PART_B[] = {2, 1, 0, 1, 0, 0}, PART_A[] = {0, 1, 2, 0, 1, 0};
+
+// f(0) .. f(N - 1) with the numbers as types: the order of the instructions and which register each uses are set here, not by unrolling
+template <typename F, int... I>
+__device__ __forceinline__ void each_of(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void each(F &&f) {
+    each_of(f, std::make_integer_sequence<int, N>{});
+}
 
 // Can underflow or overflow have touched a sum of K products, as the parts give it?  am, bm: the largest magnitudes of its two rows.  What can
 // get lost on the way, parts, partial products and sums below 2^-126, is less than K * 2^-125 * (am + bm + 8); a sum of 2^25 times that
@@ -57,6 +73,11 @@ __device__ __forceinline__ bool any_out(const f32x4_t &sum, float least) {
     for (int v = 0; v < 4; ++v) most = max(most, (__float_as_uint(sum[v]) & 0x7fffffffu) - from);
     return most >= 0x7f800000u - from;
 }
+
+// the kernels, each compiled in a .hip file of its own (shared_down: weights' K axis in segments)
+const void *up_kernel();
+const void *down_kernel(int k_groups);
+const void *shared_down_kernel(int k_groups);
 
 template <bool FUSED_UP>
 struct Shape {
@@ -82,20 +103,43 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t &hi, uint32_t 
     lo = pack_bf16x2(x, y);
 }
 
-// The elements of a tile whose bits are set in `bad` (four per fragment, as tile_body numbers them) with the fp32 matrix instruction:
-// fragments straight from memory, one after the other.  wn: the wavefront's first output column; nj: its fragments per 16 rows.
-template <bool FUSED_UP, bool SEG_K>
-__device__ __forceinline__ void by_f32(const GemmArgs &g, int slot, int m0, int m_end, int wn, int nj, uint64_t bad, int lane) {
+// What a tile leaves in LDS for the check of its sums: the largest magnitudes of its rows, and the sums of a tile that did not pass at once.
+template <int K_GROUPS>
+struct Left {
+    float a_most[K_GROUPS][BM], b_most[K_GROUPS][4][B_WAVE_ROWS];
+    f32x4_t sums[4][MAX_MF * 2][64];   // [wavefront][fragment][lane]
+    __device__ __forceinline__ float a(int row) const { return K_GROUPS > 1 ? fmaxf(a_most[0][row], a_most[K_GROUPS - 1][row]) : a_most[0][row]; }
+    __device__ __forceinline__ float b(int wave, int row) const {
+        return K_GROUPS > 1 ? fmaxf(b_most[0][wave][row], b_most[K_GROUPS - 1][wave][row]) : b_most[0][wave][row];
+    }
+};
+static_assert(sizeof(Left<2>) <= GROUP_BYTES, "one group's LDS holds it");
+
+// The doubtful sums of a wavefront's part of a tile with the fp32 matrix instruction: fragments straight from memory, one after the
+// other.  wn: its first output column; nj: its weight fragments.
+template <bool FUSED_UP, bool SEG_K, int K_GROUPS>
+__device__ __forceinline__ void by_f32(const GemmArgs &g, const Left<K_GROUPS> &left, int slot, int m0, int m_end, int wn, int wave, int nj, int lane) {
     const int r = lane & 15, q = lane >> 4;
     const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 4);
     const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 4;
     const auto b0_rsrc = rsrc_of((const char *)g.B0 + b_first);
     const auto b1_rsrc = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
     constexpr int NB = FUSED_UP ? 2 : 1;
-    for (int f = 0; __any(bad != 0); ++f, bad >>= 4) {
-        const int mine = (int)bad & 15;
-        if (!__any(mine)) continue;
-        const int i = f / nj, j = f - i * nj, row = i * 16 + r, n = j * 16 + r;
+    const int frags = ((m_end - m0 + 15) >> 4) * (FUSED_UP ? 1 : nj);
+    for (int f = 0; f < frags; ++f) {
+        const int i = FUSED_UP ? f : f / nj, j = FUSED_UP ? 0 : f - i * nj, row = i * 16 + r, n = j * 16 + r, col = wn + j * 16 + 4 * q;
+        const f32x4_t sum = left.sums[wave][i * nj + j][lane];
+        f32x4_t up = sum;
+        if constexpr (FUSED_UP) up = nj == 2 ? left.sums[wave][i * nj + 1][lane] : left.sums[wave][i][lane ^ 32];
+        const bool here = m0 + row < m_end && !(FUSED_UP && nj == 1 && q >= 2);
+        int again = 0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            bool one = doubtful(sum[v], left.a(row), left.b(wave, j * 16 + 4 * q + v), g.K);
+            if constexpr (FUSED_UP) one |= doubtful(up[v], left.a(row), left.b(wave, (nj * 8 + 4 * q + v) & (B_WAVE_ROWS - 1)), g.K);
+            again |= (int)(one && here && col + v < g.N) << v;
+        }
+        if (!__any(again)) continue;
         const uint32_t a_off = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 4) : NO_DATA;
         const uint32_t b_off = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 4) : NO_DATA;
         f32x4_t part[NB][4];   // chains of K / 16 additions
@@ -116,22 +160,21 @@ __device__ __forceinline__ void by_f32(const GemmArgs &g, int slot, int m0, int 
                 for (int v = 0; v < 4; ++v) part[m][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[v], fa[v], part[m][v], 0, 0, 0);
             }
         }
-        float *const o = (float *)g.out + (int64_t)(m0 + row) * g.ldo + wn + j * 16 + 4 * q;
+        float *const o = (float *)g.out + (int64_t)(m0 + row) * g.ldo + col;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             float h = (part[0][0][v] + part[0][1][v]) + (part[0][2][v] + part[0][3][v]);
             if constexpr (FUSED_UP) h = h / (1.0f + expf(-h)) * ((part[1][0][v] + part[1][1][v]) + (part[1][2][v] + part[1][3][v]));
-            if (mine >> v & 1) o[v] = h;
+            if (again >> v & 1) o[v] = h;
         }
     }
 }
 
 // MF: activation fragments of 16 rows.  NJ: weight fragments per wavefront, 2, or 1 for half a tile's weight rows (gate+up: then 8
 // rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K axis is cut in segments.
-// Returns this lane's doubtful elements, which by_f32 is to compute: bit 4 f + v for element v of output fragment f (16 rows after 16
-// rows, the columns of one after the other).
+// Returns (to all lanes) whether by_f32 is to look at the wavefront's sums, which are in LDS then.
 template <bool FUSED_UP, bool SEG_K, int K_GROUPS, int MF, int NJ>
-__device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int rotation, char *smem) {
+__device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int rotation, char *smem) {
     constexpr int AHEAD = MF > 3 ? 2 : 4;   // steps in flight (even)
     constexpr int AL = MF / 2;              // activation loads of 16 bytes per thread and step: 32 rows each
     constexpr bool HALF = MF % 2 != 0;      // and one of 8 bytes for the last 16 rows
@@ -211,41 +254,43 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
     constexpr int PAIRS = 2 * AL + HALF + 4 * NJ, STAGES = 4 * PAIRS;
     float x, y;
     uint2 hi, mid, lo;
-    auto stage = [&](int s, int set, int buf) {
-        const int pair = s / 4, is_b = pair >= 2 * AL + HALF, v = is_b ? pair - 2 * AL - HALF : pair, i = v >> 1;
-        const bool half = HALF && pair == 2 * AL, second = !half && (v & 1);
-        float &most = half ? h_max : is_b ? b_max[i] : a_max[is_b || half ? 0 : i];
+    auto stage = [&](auto number, int set, int buf) {
+        constexpr int s = decltype(number)::value, pair = s / 4;
+        constexpr bool is_b = pair >= 2 * AL + HALF, half = HALF && pair == 2 * AL;
+        constexpr int v = is_b ? pair - 2 * AL - HALF : pair, i = half ? 0 : v >> 1;
+        constexpr bool second = !half && (v & 1);
         uint32_t &h = second ? hi.y : hi.x, &m = second ? mid.y : mid.x, &l = second ? lo.y : lo.x;
-        if (s % 4 == 0) {
-            if (half) {
+        if constexpr (s % 4 == 0) {
+            if constexpr (half) {
                 x = __uint_as_float(rh[set][0]), y = __uint_as_float(rh[set][1]);
             } else {
-                const u32x4_t w = is_b ? rb[set][i] : ra[set][is_b ? 0 : i];
+                const u32x4_t w = [&]() { if constexpr (is_b) return rb[set][i]; else return ra[set][i]; }();
                 x = __uint_as_float(w[second ? 2 : 0]), y = __uint_as_float(w[second ? 3 : 1]);
             }
+            float &most = [&]() -> float & { if constexpr (half) return h_max; else if constexpr (is_b) return b_max[i]; else return a_max[i]; }();
             asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(x), "v"(y));
             h = pack_bf16x2(x, y);
-        } else if (s % 4 == 1) {
+        } else if constexpr (s % 4 == 1) {
             x -= bf16_lo_to_f32(h);
             y -= bf16_hi_to_f32(h);
             // the registers are free: on to the step AHEAD of this one
-            if (half) load_h(set);
-            else if (second && is_b) load_b(set, i);
-            else if (second) load_a(set, is_b ? 0 : i);
-        } else if (s % 4 == 2) {
+            if constexpr (half) load_h(set);
+            else if constexpr (second && is_b) load_b(set, i);
+            else if constexpr (second) load_a(set, i);
+        } else if constexpr (s % 4 == 2) {
             m = pack_bf16x2(x, y);
             x -= bf16_lo_to_f32(m);
         } else {
             y -= bf16_hi_to_f32(m);
             l = pack_bf16x2(x, y);
             char *const base = is_b ? sb + buf * BUFFER_BYTES : smem + buf * BUFFER_BYTES;
-            const int plane = is_b ? B_PLANE : A_PLANE;
-            if (half) {
+            constexpr int plane = is_b ? B_PLANE : A_PLANE;
+            if constexpr (half) {
                 char *const at = base + h_at;
                 *(uint32_t *)at = hi.x;
                 *(uint32_t *)(at + plane) = mid.x;
                 *(uint32_t *)(at + 2 * plane) = lo.x;
-            } else if (second) {
+            } else if constexpr (second) {
                 char *const at = base + (is_b ? b_at[i & 1] + (i >> 1) * 16 * BK * 2 : a_at + i * 32 * BK * 2);
                 *(uint2 *)at = hi;
                 *(uint2 *)(at + plane) = mid;
@@ -257,7 +302,7 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
     // holds its unit for 16 cycles, as long as four vector instructions theirs, and a wavefront issues in order, so the two are
     // dealt out one to one; the compiler's own order multiplies first and splits then (114 instead of 100 us, see above).
     auto step_body = [&](int buf, int set) {
-        constexpr int MFMAS = 6 * MF * NJ;
+        constexpr int MFMAS = PRODUCTS * MF * NJ;
         const char *const a = smem + buf * BUFFER_BYTES, *const b = sb + buf * BUFFER_BYTES;
         bf16x8_t fb[NJ][3], fa[2][2][3];
         auto read_a = [&](int f, int p) { fa[(f >> 1) & 1][f & 1][p] = *(const bf16x8_t *)(a + p * A_PLANE + f * 16 * BK * 2 + frag_at); };
@@ -269,31 +314,18 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
             for (int f = 0; f < 2; ++f) read_a(f, 2 - p);
         }
         __builtin_amdgcn_sched_barrier(0);
-        int s = 0, m = 0;
-#pragma unroll
-        for (int f0 = 0; f0 < MF; f0 += 2) {
-            const int fn = MF - f0 < 2 ? 1 : 2;   // fragments of this round
-#pragma unroll
-            for (int t = 0; t < 6; ++t) {         // the smallest products first
-                constexpr int PB[6] = {2, 1, 0, 1, 0, 0}, PA[6] = {0, 1, 2, 0, 1, 0};
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    if (u >= fn) continue;
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        f32x4_t &sum = t == 5 ? acc[f0 + u][j] : low[f0 + u][j];
-                        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][PB[t]], fa[(f0 >> 1) & 1][u][PA[t]], sum, 0, 0, 0);
-                        ++m;
-                        // the next round's fragments, one read for each of the first products
-                        const int next = t * fn * NJ + u * NJ + j;
-                        if (next < 6 && f0 + 2 + (next & 1) < MF) read_a(f0 + 2 + (next & 1), next >> 1);
-#pragma unroll
-                        for (; s * MFMAS < m * STAGES; ++s) stage(s, set, buf ^ 1);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-            }
-        }
+        // products by rounds of two activation fragments (the last one's may be one), then the smallest first
+        each<MFMAS>([&](auto number) {
+            constexpr int m = decltype(number)::value, f0 = m / (2 * NJ * PRODUCTS) * 2, fn = MF - f0 < 2 ? 1 : 2;
+            constexpr int next = m - f0 * NJ * PRODUCTS, t = next / (fn * NJ), u = next / NJ % fn, j = next % NJ;
+            f32x4_t &sum = t == PRODUCTS - 1 ? acc[f0 + u][j] : low[f0 + u][j];
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][PART_B[t]], fa[(f0 >> 1) & 1][u][PART_A[t]], sum, 0, 0, 0);
+            // the next round's fragments, one read for each of the first products
+            if constexpr (next < 6 && f0 + 2 + (next & 1) < MF) read_a(f0 + 2 + (next & 1), next >> 1);
+            constexpr int from = (m * STAGES + MFMAS - 1) / MFMAS, to = ((m + 1) * STAGES + MFMAS - 1) / MFMAS;
+            each<to - from>([&](auto n) { stage(std::integral_constant<int, from + decltype(n)::value>{}, set, buf ^ 1); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
     // step s multiplies LDS buffer s % 2, splits and stores step s + 1's data and loads step s + 1 + AHEAD's in their place
     auto step = [&](int p) {
@@ -312,8 +344,7 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
         for (int i = 0; i < 2 * NJ; ++i) load_b(p, i);
     }
     next_loads();
-#pragma unroll
-    for (int s = 0; s < STAGES; ++s) stage(s, 0, 0);
+    each<STAGES>([&](auto number) { stage(number, 0, 0); });
     __syncthreads();
     int s0 = 0;
     for (; s0 + AHEAD <= nk; s0 += AHEAD) {
@@ -332,7 +363,7 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
 
     // ---- largest magnitudes of the rows (the lanes of a row are neighbours) and the other group's sums, through LDS (the last step
     // ended with a barrier) ----
-    float *const a_most = (float *)all, *const b_most = a_most + K_GROUPS * BM;   // [K_GROUPS][BM], [K_GROUPS][4][B_WAVE_ROWS]
+    Left<K_GROUPS> &left_here = *(Left<K_GROUPS> *)all;
     auto of_row = [&](float most, int lanes) {
 #pragma unroll
         for (int o = 1; o < lanes; o <<= 1) most = fmaxf(most, __shfl_xor(most, o, 64));
@@ -341,16 +372,16 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
 #pragma unroll
     for (int i = 0; i < AL; ++i) {
         const float most = of_row(a_max[i], 8);
-        if (chunk == 0) a_most[group * BM + i * 32 + row_of] = most;
+        if (chunk == 0) left_here.a_most[group][i * 32 + row_of] = most;
     }
     if (HALF) {
         const float most = of_row(h_max, 16);
-        if (h_chunk == 0) a_most[group * BM + h_row] = most;
+        if (h_chunk == 0) left_here.a_most[group][h_row] = most;
     }
 #pragma unroll
     for (int i = 0; i < 2 * NJ; ++i) {
         const float most = of_row(b_max[i], 8);
-        if (chunk == 0) b_most[(group * 4 + wave) * B_WAVE_ROWS + i * 8 + b_row] = most;
+        if (chunk == 0) left_here.b_most[group][wave][i * 8 + b_row] = most;
     }
     [[maybe_unused]] f32x4_t *const sums = (f32x4_t *)(all + GROUP_BYTES) + (wave * MF * NJ) * 64 + lane;
     if (group != 0) {
@@ -360,36 +391,33 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
             for (int j = 0; j < NJ; ++j) sums[(i * NJ + j) * 64] = acc[i][j];
     }
     __syncthreads();
-    if (group != 0) return 0;
+    if (group != 0) return false;
     if constexpr (K_GROUPS > 1) {
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] += sums[(i * NJ + j) * 64];
     }
-    auto a_most_of = [&](int row) { return K_GROUPS > 1 ? fmaxf(a_most[row], a_most[BM + row]) : a_most[row]; };
-    auto b_most_of = [&](int row) {
-        const float *const at = b_most + wave * B_WAVE_ROWS + row;
-        return K_GROUPS > 1 ? fmaxf(at[0], at[4 * B_WAVE_ROWS]) : at[0];
-    };
     float b_most4[NJ];   // of the four columns that a lane has of a fragment
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) b_most4[j] = fmaxf(fmaxf(b_most_of(j * 16 + 4 * q), b_most_of(j * 16 + 4 * q + 1)), fmaxf(b_most_of(j * 16 + 4 * q + 2), b_most_of(j * 16 + 4 * q + 3)));
+    for (int j = 0; j < NJ; ++j) {
+        b_most4[j] = 0.0f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) b_most4[j] = fmaxf(b_most4[j], left_here.b(wave, j * 16 + 4 * q + v));
+    }
     bool out_of_range = false;
 #pragma unroll
     for (int i = 0; i < MF; ++i) {
-        const float am = a_most_of(i * 16 + r);
+        const float am = left_here.a(i * 16 + r);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const int col = FUSED_UP ? (NJ == 2 ? wn + 4 * q : wn + 4 * (q & 1)) : wn + j * 16 + 4 * q;
             out_of_range |= any_out(acc[i][j], least_of(am, b_most4[j], g.K)) && m0 + i * 16 + r < m_end && col < g.N;
         }
     }
-    const bool look = __any(out_of_range);   // at each of them
 
     // ---- epilogue: element v of lane l of a fragment is output column 4 * (l / 16) + v, row l % 16 ----
     float *const out = (float *)g.out;
-    uint64_t bad = 0;
 #pragma unroll
     for (int i = 0; i < MF; ++i) {
         const int row = m0 + i * 16 + r;
@@ -408,12 +436,6 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
             for (int v = 0; v < 4; ++v) {
                 h[v] = acc[i][j][v];
                 if (FUSED_UP) h[v] = h[v] / (1.0f + expf(-h[v])) * up[v];
-                if (look) {
-                    const float am = a_most_of(i * 16 + r);
-                    bool again = doubtful(acc[i][j][v], am, b_most_of(j * 16 + 4 * q + v), g.K);
-                    if (FUSED_UP) again |= doubtful(up[v], am, b_most_of(NJ * 8 + 4 * q + v), g.K);
-                    if (again && col + v < g.N) bad |= (uint64_t)1 << ((FUSED_UP ? i : i * NJ + j) * 4 + v);
-                }
             }
             float *const o = out + (int64_t)row * g.ldo + col;
             if (g.N % 4 == 0) {
@@ -425,13 +447,41 @@ __device__ __forceinline__ uint64_t tile_body(const GemmArgs &g, int slot, int m
             }
         }
     }
-    return bad;
+    if (!__any(out_of_range)) return false;
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) left_here.sums[wave][i * NJ + j][lane] = acc[i][j];
+    return true;
 }
 
-// SEG_PER_LANE: 1 for up to 64 row segments, 4 for up to 256.  Pieces of a segment have one size, and tiles are numbered and dealt to the
-// XCDs as gemm_bf16_mid_kernel's.  Half
+// Where workgroup number b works: tile t (-1: none) of `blocks` numbers, in segment s.  SEG_PER_LANE: 1 for up to 64 row segments, 4 for
+// up to 256.  Pieces of a segment have one size, and tiles are numbered and dealt to the XCDs as gemm_bf16_mid_kernel's.  Half
 // tiles, and lower pieces, while there is a place for each (the places: two workgroups per compute unit, one if its groups share K).
-template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE, int K_GROUPS>
+struct Place {
+    int blocks, t;
+    bool halves;
+    Segment s;
+};
+template <int SEG_PER_LANE>
+__device__ __forceinline__ Place place_of(const GemmArgs &g, int b, int n_strips, int places, int lane) {
+    SegTable<SEG_PER_LANE> segs;
+    segs.load(g, lane);
+    segs.cut(lane, BM);
+    Place p;
+    p.halves = 2 * segs.total * n_strips <= places;
+    if (p.halves) {
+        if (2 * segs.count(32) * n_strips <= places) segs.cut(lane, 32);
+        else if (2 * segs.count(48) * n_strips <= places) segs.cut(lane, 48);
+    }
+    const int strips = p.halves ? 2 * n_strips : n_strips, total = segs.total * strips;
+    p.blocks = (total + 63) & ~63;
+    p.t = b < p.blocks ? mid::of_runs(b, total) : -1;
+    p.s = segs.segment(max(p.t, 0) / strips, lane);
+    return p;
+}
+
+template <bool FUSED_UP, bool SEG_K, int K_GROUPS>
 __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_kernel(const GemmArgs g, int n_strips, int n_cu) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     StaleRows stale;
@@ -439,28 +489,19 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
     for (int b = (int)blockIdx.x;;) {       // once, unless the rank has far more rows than its share
         int lane = (int)threadIdx.x & 63;
         asm volatile("" : "+v"(lane));      // the table is read again each time: kept, it would cost the tile its registers
-        SegTable<SEG_PER_LANE> segs;
-        segs.load(g, lane);
-        segs.cut(lane, BM);
-        const int places = 2 / K_GROUPS * n_cu;   // workgroups that run at once
-        const bool halves = 2 * segs.total * n_strips <= places;
-        if (halves) {
-            if (2 * segs.count(32) * n_strips <= places) segs.cut(lane, 32);
-            else if (2 * segs.count(48) * n_strips <= places) segs.cut(lane, 48);
-        }
-        const int strips = halves ? 2 * n_strips : n_strips, total = segs.total * strips;
-        const int blocks = (total + 63) & ~63;
-        if (b >= blocks) break;
-        const int t = mid::of_runs(b, total);
+        const int places = 2 / K_GROUPS * n_cu;
+        const Place p = SEG_K || g.S <= 64 ? place_of<1>(g, b, n_strips, places, lane) : place_of<4>(g, b, n_strips, places, lane);
+        if (b >= p.blocks) break;
         const bool again = b >= (int)gridDim.x;
         b += (int)gridDim.x;
-        const bool more = b < blocks;
-        if (t < 0) {
+        const bool more = b < p.blocks;
+        if (p.t < 0) {
             if (more) continue;
             break;
         }
-        const Segment s = segs.segment(t / strips, lane);
-        const int in_seg = t - s.first_tile * strips, strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
+        const bool halves = p.halves;
+        const Segment s = p.s;
+        const int in_seg = p.t - s.first_tile * (halves ? 2 * n_strips : n_strips), strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
         const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
         const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows);
         const int n0 = strip * (halves ? Shape<FUSED_UP>::BN / 2 : Shape<FUSED_UP>::BN);
@@ -474,14 +515,14 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
                 case 3: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
                 case 4: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
                 case 5: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 5, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
-                default: return (uint64_t)0;   // no rows
+                default: return false;   // no rows
             }
         };
         if (n0 < g.N) {
-            const uint64_t bad = halves ? tile(std::integral_constant<int, 1>{}) : tile(std::integral_constant<int, 2>{});
-            if (__any(bad != 0)) {
+            const bool look = halves ? tile(std::integral_constant<int, 1>{}) : tile(std::integral_constant<int, 2>{});
+            if (look) {
                 const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) & 3, nj = halves ? 1 : 2;
-                by_f32<FUSED_UP, SEG_K>(g, s.slot, m0, m_end, n0 + wave * (FUSED_UP ? 8 : 16) * nj, FUSED_UP ? 1 : nj, bad, lane);
+                by_f32<FUSED_UP, SEG_K>(g, *(const Left<K_GROUPS> *)smem, s.slot, m0, m_end, n0 + wave * (FUSED_UP ? 8 : 16) * nj, wave, nj, lane);
             }
         }
         if (!more) break;
