@@ -174,7 +174,7 @@ __device__ __forceinline__ void by_f32(const GemmArgs &g, const Left<K_GROUPS> &
 // rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K axis is cut in segments.
 // Returns (to all lanes) whether by_f32 is to look at the wavefront's sums, which are in LDS then.
 template <bool FUSED_UP, bool SEG_K, int K_GROUPS, int MF, int NJ>
-__device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int rotation, char *smem) {
+__device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int rotation, KSegDiv seg_of, char *smem) {
     constexpr int AHEAD = MF > 3 ? 2 : 4;   // steps in flight (even)
     constexpr int AL = MF / 2;              // activation loads of 16 bytes per thread and step: 32 rows each
     constexpr bool HALF = MF % 2 != 0;      // and one of 8 bytes for the last 16 rows
@@ -213,7 +213,6 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
         b_off[i] = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 4) + (uint32_t)chunk * 16u : NO_DATA;
     }
     char *const sb = smem + 3 * A_PLANE + wave * 3 * B_PLANE;
-    KSegWalk walk{k_begin + chunk * 4};
     // places in a plane: this thread's loads', the fragments' (16 rows, 8 lines, keep the order of the chunks)
     const int a_at = chunk_at(row_of, chunk >> 1) + (chunk & 1) * 8, h_at = chunk_at(h_row, h_chunk >> 2) + (h_chunk & 3) * 4;
     const int b_at[2] = {chunk_at(b_row, chunk >> 1) + (chunk & 1) * 8, chunk_at(8 + b_row, chunk >> 1) + (chunk & 1) * 8};
@@ -239,7 +238,8 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
         const int k = k0 + chunk * 4;
         a_none = left > 0 && k < g.K ? 0u : NO_DATA;
         if (HALF) h_none = left > 0 && k0 + h_chunk * 2 < g.K ? 0u : NO_DATA;   // (K is a multiple of 4)
-        b_add = SEG_K ? walk.next(k, g.K, g.kseg_len, g.kseg_stride, BK, 4) : a_none;
+        if constexpr (SEG_K) b_add = k < g.K ? seg_of(k) * (uint32_t)((g.kseg_stride - g.kseg_len) * 4) : NO_DATA;   // (wraps past K alone)
+        else b_add = a_none;
         k_load = k0 * 4;
         --left;
         k0 = SEG_K || k0 + BK != k_end ? k0 + BK : k_begin;
@@ -486,6 +486,7 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     StaleRows stale;
     if (!FUSED_UP) stale = stale_rows(g);   // in flight during the work, used at the end
+    const KSegDiv seg_of(SEG_K ? g.kseg_len : 2);
     for (int b = (int)blockIdx.x;;) {       // once, unless the rank has far more rows than its share
         int lane = (int)threadIdx.x & 63;
         asm volatile("" : "+v"(lane));      // the table is read again each time: kept, it would cost the tile its registers
@@ -511,10 +512,10 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
             constexpr int NJ = decltype(nj)::value;
             switch ((m_end - m0 + 15) >> 4) {
                 case 1:
-                case 2: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 2, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
-                case 3: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
-                case 4: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
-                case 5: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 5, NJ>(g, s.slot, m0, m_end, n0, rotation, smem);
+                case 2: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 2, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
+                case 3: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
+                case 4: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
+                case 5: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 5, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
                 default: return false;   // no rows
             }
         };

@@ -25,6 +25,20 @@ struct KSegWalk {
     }
 };
 
+// k / len for k below 2^31 by one multiplication, for lanes that keep nothing from step to step: with 2^(31+b) = q len + r, b the bits
+// that len - 1 takes, the factor q + 1 is too large by less than len / len, which moves no quotient (k (len - r) < 2^(31+b)).
+struct KSegDiv {
+    uint32_t factor;
+    int shift;
+    constexpr explicit KSegDiv(int len) : factor(0), shift(0) {   // len >= 2
+        int b = 1;
+        while ((uint32_t)len > (uint32_t)1 << b) ++b;
+        factor = (uint32_t)(((uint64_t)1 << (31 + b)) / (uint32_t)len + 1);
+        shift = b - 1;
+    }
+    constexpr uint32_t operator()(int k) const { return (uint32_t)(((uint64_t)(uint32_t)k * factor) >> 32) >> shift; }
+};
+
 // offset + add, or no data where either has none
 constexpr uint32_t offset_with(uint32_t offset, uint32_t add) { return (offset + add) | (offset & NO_DATA) | (add & NO_DATA); }
 

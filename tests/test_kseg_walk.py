@@ -47,3 +47,32 @@ def test_offsets_along_k_segments(tmp_path, n_seg, seg_len, stride, el):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe), str(n_seg), str(seg_len), str(stride), str(el)], check=True, capture_output=True, text=True)
     assert int(out.stdout) == 0
+
+
+DIVISIONS = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "kseg_walk.h"
+// wrong quotients of numbers below 2^31: those next to the multiples of every length, first ones, last ones and some between
+int main() {
+    long long wrong = 0;
+    for (int e = 1; e < 31; ++e)
+        for (int len : {(1 << e) - 1, 1 << e, (1 << e) + 1, (1 << e) + (1 << e) / 3, 4 * e, 1388 + 4 * e})
+            if (len >= 2) {
+                const grace::KSegDiv div(len);
+                const long long most = 0x7fffffffll / len;
+                for (long long q = 0; q <= most; q += 1 + (q > 40 && q < most - 40) * (most / 50))
+                    for (long long k = q * len - 1; k <= q * len + 1; ++k)
+                        if (k >= 0 && k <= 0x7fffffffll) wrong += div((int)k) != (unsigned)(k / len);
+                wrong += div(0x7fffffff) != (unsigned)(0x7fffffff / len);
+            }
+    printf("%lld\n", wrong);
+}
+"""
+
+
+def test_segment_numbers_by_multiplication(tmp_path):
+    src, exe = tmp_path / "div.cpp", tmp_path / "div"
+    src.write_text(DIVISIONS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    assert int(subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout) == 0
