@@ -193,7 +193,7 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
     // ---- load sources (offsets without data give zeros: past the rows, past N, past K) ----
     const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 4);
     const int row_of = tid >> 3, chunk = tid & 7;
-    uint32_t a_off[AL];
+    uint32_t a_off[AL + 1];                  // (AL is 0 for 16 rows)
 #pragma unroll
     for (int i = 0; i < AL; ++i) {
         const int row = i * 32 + row_of;
@@ -219,13 +219,13 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
     const int frag_at = chunk_at(r, q);
 
     u32x2_t rh[AHEAD];
-    u32x4_t ra[AHEAD][AL], rb[AHEAD][2 * NJ];
+    u32x4_t ra[AHEAD][AL + 1], rb[AHEAD][2 * NJ];
     f32x4_t acc[MF][NJ], low[MF][NJ];   // sums of the products of the leading parts; of the others, 2^-8 of them and less
 #pragma unroll
     for (int i = 0; i < MF; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = low[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    float a_max[AL], h_max = 0.0f, b_max[2 * NJ];     // largest magnitudes that this thread has seen of its rows
+    float a_max[AL + 1], h_max = 0.0f, b_max[2 * NJ];     // largest magnitudes that this thread has seen of its rows
 #pragma unroll
     for (int i = 0; i < AL; ++i) a_max[i] = 0.0f;
 #pragma unroll
@@ -311,7 +311,7 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
 #pragma unroll
             for (int j = 0; j < NJ; ++j) fb[j][p] = *(const bf16x8_t *)(b + p * B_PLANE + j * 16 * BK * 2 + frag_at);
 #pragma unroll
-            for (int f = 0; f < 2; ++f) read_a(f, 2 - p);
+            for (int f = 0; f < min(MF, 2); ++f) read_a(f, 2 - p);
         }
         __builtin_amdgcn_sched_barrier(0);
         // products by rounds of two activation fragments (the last one's may be one), then the smallest first
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
         auto tile = [&](auto nj) {
             constexpr int NJ = decltype(nj)::value;
             switch ((m_end - m0 + 15) >> 4) {
-                case 1:
+                case 1: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 1, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
                 case 2: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 2, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
                 case 3: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
                 case 4: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
