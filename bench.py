@@ -36,7 +36,7 @@ KERNEL_OF_STAGE = {
     "route_permute": "topk + pick + positions + scatter_rows_kernel (one call; the row scatter moves the bytes), one kernel for the smallest batches",
 }
 # the projections where the library chooses another kernel than the large tiles for the batch
-OTHER_KERNEL = {"stream": "gemm_stream kernel", "mid": "gemm_bf16_mid_kernel / gemm_f32_mid_kernel", "generic": "gemm_bf16_kernel",
+OTHER_KERNEL = {"stream": "gemm_stream kernel", "mid": "gemm_bf16_mid_kernel / gemm_f32_split_kernel", "generic": "gemm_bf16_kernel",
                 "vector_f32": "gemm_f32_kernel"}
 
 

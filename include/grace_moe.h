@@ -388,9 +388,8 @@ int grace_mfma_sustained(int32_t random_operands, int32_t lds_fed, double *tflop
  * these sizes alone.  up: 1 for the gate+up projection, 0 for the down projection.  n_cu: compute units (0: of the
  * current device; no device is touched otherwise).  HOST outputs. */
 typedef enum {
-    GRACE_KERNEL_STREAM = 0,     /* weights streamed, few rows per segment; fp32 of any size (past 64 tokens and 512 (down: 1024) of K with the
-                                  * kernel of MID where there are tiles enough) */
-    GRACE_KERNEL_MID = 1,        /* pieces of up to 96 (fp32: 80) rows x 128 weight rows */
+    GRACE_KERNEL_STREAM = 0,     /* weights streamed, few rows per segment; fp32 of any size */
+    GRACE_KERNEL_MID = 1,        /* pieces of up to 96 rows x 128 weight rows; fp32: of up to 80, values split into three bf16 parts */
     GRACE_KERNEL_PERSIST = 2,    /* 256 x 256 tiles, one workgroup per compute unit */
     GRACE_KERNEL_GENERIC = 3,    /* 128 x 128 tiles: K no multiple of 64 and operands past 2 GB, or too many work-items */
     GRACE_KERNEL_VECTOR_F32 = 4  /* fp32 on the vector ALUs: rows that are no whole 16-byte vectors */

@@ -147,26 +147,23 @@ static Grid mid_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
     const bool exact = g.M_single > 0;   // the shared experts
     return {mid::grid_blocks((exact ? (expected + mid::BM - 1) / mid::BM : expected / mid::BM + g.S) * n_strips, n_cu, exact), mid::THREADS};
 }
-// fp32, batches of more than 64 tokens: the split kernel, whichever the route (they differ in what else can take the launch), but for
-// short K, where the streaming kernel's wavefronts share K and start at once (K = 256 6 us each), and down projections of few tiles (us, streaming
-// kernel / split kernel: 200 rows in 9 segments, K = 2816, N = 548, 110 half tiles 28.5 / 32.8; 500 rows, K = 1388, N = 548, 150 19.0 / 21.0;
-// 100 rows, K = 2816, N = 1024, 160 42.9 / 35.3; 1000 rows, K = 1388, N = 1024, 336 43.1 / 44.6).  Gate+up, K = 548 92 -> 59 us with
-// 1000 rows, 41.8 -> 35.8 with 500 and N = 1388.  Groups that share K: up to one and a half tiles per unit.
+// Tiles of the fp32 split kernel at `m` rows, a piece extra for every segment.
 template <bool FUSED_UP>
 static int64_t split_tiles(const GemmArgs &g, const Rows &rows, int64_t m) {
     constexpr int BN = split::Shape<FUSED_UP>::BN;
     return (m / split::BM + std::min<int64_t>(g.S, m)) * ((g.N + BN - 1) / BN);
 }
-template <bool FUSED_UP>
-static bool split_takes(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
-    if (dt != GRACE_F32 || (route != Route::MID && route != Route::STREAM)) return false;
-    if (route == Route::MID) return true;
-    if (!stream_pieces<4>(rows)) return false;
-    return FUSED_UP ? g.K >= 512 : g.K >= 1024 && 16 * split_tiles<false>(g, rows, rows.at(4)) >= 5 * n_cu;
-}
+// Groups of wavefronts that share a tile's K: two in down projections, whose K is long, while the tiles (half a piece extra for every segment)
+// are one round of one per compute unit; with more, tiles run two to a unit.  Time with one group over time with two (median of 600 shared
+// experts): up to a quarter of a round 1.33, to half 1.27, to one 1.11, to one and a half 0.91.  A rank's segments may make fewer tiles: K of 1024 or
+// more, up to five quarters of a round 1.03 (0.92 to 1.24).
 template <bool FUSED_UP>
 static int split_groups(const GemmArgs &g, const Rows &rows, int n_cu) {
-    return !FUSED_UP && 2 * split_tiles<false>(g, rows, rows.at(4)) <= 3 * n_cu ? 2 : 1;
+    if (FUSED_UP) return 1;
+    const int64_t m = rows.at(4), strips = (g.N + split::Shape<false>::BN - 1) / split::Shape<false>::BN;
+    if (g.S == 1) return (m + split::BM - 1) / split::BM * strips <= n_cu ? 2 : 1;
+    const int64_t half_tiles = (2 * m / split::BM + std::min<int64_t>(g.S, m)) * strips;
+    return 2 * half_tiles <= (g.K >= 1024 ? 5 : 4) * n_cu ? 2 : 1;
 }
 template <bool FUSED_UP>
 static Grid split_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
@@ -183,10 +180,9 @@ static bool mid_tiles_fit(const GemmArgs &g, const Rows &rows) {
 }
 template <bool FUSED_UP>
 static Grid grid_of(Route route, const GemmArgs &g, grace_dtype dt, const Rows &rows, int n_cu) {
-    if (split_takes<FUSED_UP>(route, g, dt, rows, n_cu)) return split_grid<FUSED_UP>(g, rows, n_cu);
     if (route == Route::STREAM)
         return dt == GRACE_BF16 ? stream_grid<FUSED_UP, 2>(g, rows, n_cu) : stream_grid<FUSED_UP, 4>(g, rows, n_cu);
-    if (route == Route::MID) return mid_grid<FUSED_UP>(g, rows, n_cu);
+    if (route == Route::MID) return dt == GRACE_BF16 ? mid_grid<FUSED_UP>(g, rows, n_cu) : split_grid<FUSED_UP>(g, rows, n_cu);
     if (route == Route::PERSIST) return {pers::grid_blocks(n_cu), pers::THREADS};
     if (route == Route::GENERIC) {
         constexpr int BN = FUSED_UP ? 64 : 128;
@@ -244,27 +240,30 @@ static bool mid_is_cheaper(const GemmArgs &g, const Rows &rows, int n_cu) {
     return (m / mid::BM + hit) * strips <= n_cu * rounds * (FUSED_UP ? 3 : 2);
 }
 
-// fp32, batches of more than 64 tokens: the route of long launches (MID) or of short ones (STREAM).  Both take the split kernel where
-// split_takes says so; MID always does.  The line was drawn for a kernel with the same staging on the fp32 matrix instruction (96 rows x 64 weight
-// rows) against the streaming kernel, whose pieces of 64 rows and 32 weight rows are a third of its tiles.  Measured then over 1332 expert FFNs, each kernel alone (8 to 128
-// experts on 1 to 4 ranks, Zipf-shaped shares, 65 to 5000 tokens, k = 2 and 8, d x f from 128 x 256 to 2048 x 2048, also 548 and
-// 1388, whose rows are no whole lines), and 234 of shared experts:
-//  * five tiles per compute unit at the even share and K of 20 steps or more: streaming 66.3 ms, 96 rows 57.1 ms, in 170 expert
-//    projections and 23 of shared experts none slower by more than 1 %;
-//  * many segments even out what their ragged ends take.  Gate+up, 8 segments or more, N >= 2048, K >= 512 38.2 -> 31.9 ms in 242, 20
-//    slower by 3 to 15 % (with fewer segments ten of 60); 16 segments, N >= 1024, a tile for every other unit 4.9 -> 4.0 ms in 34
-//    more, none slower; down, 8 segments, N >= 2048, two tiles per unit 4.6 -> 4.0 ms in 28, none slower by more than 3 %;
-//  * the other 2190: 0.47 to 1.69 times as fast, 697 faster and 1110 slower by more than 3 %.
-// In all 226.3 ms with the streaming kernel, 206.4 with 96 rows, 209.3 with this rule.
+// fp32, batches of more than 64 tokens: the split kernel (MID) against the streaming one, whose pieces of 64 rows and 32 weight rows make
+// eight times as many workgroups and whose wavefronts share K.  Few tiles, short K and segments of a few rows each, whose weights are all
+// that there is to move, are for that one.  The host knows the rows of the shared experts and of a rank that hosts all instances, elsewhere
+// their even share.
+//
+// Measured over 1889 gate+up and as many down projections (1289 of experts: 15 sizes from 128 x 256 to 4096 x 512, 768 x 3072 and 2048 x 2048, 548
+// and 1388 among them, 1 to 128 segments on 1 to 4 ranks, even to Zipf-shaped shares, 65 to 5000 tokens, k = 1, 2 and 8; 600 of one
+// to four shared experts), weights of 700 MB or more in turn, each kernel alone:
+//   gate+up: streaming 296.5 ms, split 194.3, this rule 192.8, the better one each time 191.8;
+//   down: streaming 164.1, split 132.0 (one group) and 127.7 (two), this rule 119.8, the best one each time 117.6.
+// With the fp32 matrix instruction alone (streamed, or 96 x 64 tiles where they were faster) they took 268.4 and 159.2; 246 of the 3778 are slower than
+// that by more than 3 %, 64 by more than 10 %, by 47 % at most: ranks that hold far fewer rows than their share, and segments of a few rows.
 template <bool FUSED_UP>
-static bool mid_f32_is_faster(const GemmArgs &g, const Rows &rows, int n_cu) {
-    constexpr int COLS = FUSED_UP ? 32 : 64;
-    const int64_t strips = (g.N + COLS - 1) / COLS;
-    const int64_t work = rows.at(4) * strips, round = (int64_t)n_cu * 96;   // of one tile per compute unit
-    const bool long_k = g.K >= 640;
-    if (long_k && work >= 5 * round) return true;
-    if (FUSED_UP) return (g.S >= 8 && g.N >= 2048 && g.K >= 512) || (g.S >= 16 && g.N >= 1024 && long_k && 2 * work >= round);
-    return g.S >= 8 && g.N >= 2048 && long_k && work >= 2 * round;
+static bool split_is_faster(const GemmArgs &g, const Rows &rows, int n_cu) {
+    const int64_t m = rows.at(4), segments = std::min<int64_t>(g.S, std::max<int64_t>(m, 1));
+    const int64_t percent = 100 * split_tiles<FUSED_UP>(g, rows, m) / n_cu;   // tiles per compute unit
+    if constexpr (FUSED_UP) {
+        if (m <= 3 * segments) return percent >= 500;
+        return percent >= (g.K >= 512 ? 42 : g.K >= 192 ? 70 : 125);
+    } else {
+        // (rows of a segment times K: what its weights, of whatever width, are multiplied with)
+        if (split_groups<false>(g, rows, n_cu) == 2) return percent >= 30 && g.K >= 512 && m * g.K > (percent >= 50 ? 8000 : 20000) * segments;
+        return percent > 400 || m * g.K > 6000 * segments;
+    }
 }
 
 // bf16, up to 64 rows per segment: the streaming kernel, which splits the work finest, while the 96-row kernel's tiles
@@ -282,10 +281,10 @@ static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int
     auto fits = [&](Route r) { return launchable(grid_of<FUSED_UP>(r, g, dt, rows, n_cu)); };
     if (dt == GRACE_F32) {
         const bool stream = stream_ok<4>(g) && fits(Route::STREAM);
-        // output rows of whole 16-byte vectors; K segments of any length (shared experts' down projection, f = 1388, two of them, d =
-        // 1024, 65 to 5000 tokens: vector ALUs 329 to 577 us, 96 rows 38 to 289 us)
-        const bool mid = rows.max_rows > strm::MAX_ROWS && g.N % 4 == 0 && stream_ok<4>(g, 4) && mid_tiles_fit<FUSED_UP, split::Shape<FUSED_UP>, split::BM>(g, rows);
-        if (mid && (!stream || mid_f32_is_faster<FUSED_UP>(g, rows, n_cu))) return Route::MID;
+        // K segments of any length (shared experts' down projection, f = 1388, two of them, d = 1024, 65 to 5000 tokens: vector ALUs
+        // 329 to 577 us, with 96 x 64 tiles of the fp32 instruction 38 to 289)
+        const bool split = stream_pieces<4>(rows) && stream_ok<4>(g, 4) && mid_tiles_fit<FUSED_UP, split::Shape<FUSED_UP>, split::BM>(g, rows);
+        if (split && (!stream || split_is_faster<FUSED_UP>(g, rows, n_cu))) return Route::MID;
         return stream ? Route::STREAM : Route::VECTOR_F32;
     }
     const bool mid_ok = stream_ok<2>(g, 8) && mid_tiles_fit<FUSED_UP, mid::Shape<FUSED_UP>, mid::BM>(g, rows);
@@ -354,12 +353,12 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipS
     const Route route = route_gemm<FUSED_UP>(g, dt, rows, n_cu);
     const Grid l = grid_of<FUSED_UP>(route, g, dt, rows, n_cu);
     if (!launchable(l)) return fail(GRACE_ESHAPE, "%s: grid too large", what);
-    if (split_takes<FUSED_UP>(route, g, dt, rows, n_cu)) {
-        const int rc = launch_split<FUSED_UP>(g, l, n_cu, st, what);
-        if (rc != GRACE_OK) return rc;
-    } else if (route == Route::STREAM) {
+    if (route == Route::STREAM) {
         if (dt == GRACE_BF16) launch_stream<FUSED_UP, 2>(g, rows, l, st);
         else launch_stream<FUSED_UP, 4>(g, rows, l, st);
+    } else if (route == Route::MID && dt == GRACE_F32) {
+        const int rc = launch_split<FUSED_UP>(g, l, n_cu, st, what);
+        if (rc != GRACE_OK) return rc;
     } else if (route == Route::MID) {
         launch_mid<FUSED_UP>(g, l, n_cu, st);
     } else if (route == Route::PERSIST) {

@@ -80,23 +80,33 @@ def test_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
 
 
 @pytest.mark.parametrize("up,T,k,d,f,n_shared,S,I,want", [
-    # streaming kernel / 96-row kernel, us
-    (True, 2000, 8, 2048, 768, 0, 4, 8, "mid"),          # 524 / 428: more than five tiles per compute unit
-    (False, 2000, 8, 2048, 768, 0, 4, 8, "mid"),         # 279 / 231
-    (False, 5000, 1, 2048, 768, 1, 1, 1, "mid"),         # 180 / 150
-    (True, 500, 8, 1024, 2816, 0, 16, 64, "mid"),        # 191 / 152: gate+up of many segments, wide and long
-    (False, 500, 8, 1024, 2816, 0, 16, 64, "stream"),    # 92.5 / 135
-    (True, 500, 2, 548, 2816, 0, 8, 16, "mid"),          # 63.6 / 60.9
-    (True, 300, 8, 1024, 1388, 0, 16, 16, "mid"),        # 183 / 151
-    (True, 65, 2, 1024, 1388, 0, 16, 64, "stream"),      # 22.3 / 18.6: less than a tile for every other unit
-    (False, 1000, 8, 2048, 768, 0, 16, 16, "mid"),       # 287 / 244: two tiles per unit of many segments
-    (False, 128, 8, 2048, 768, 0, 16, 16, "stream"),     # 51.2 / 59.4
-    (True, 200, 8, 2048, 768, 0, 4, 8, "stream"),        # 68.5 / 93.9
-    (True, 500, 2, 548, 1388, 0, 16, 16, "stream"),      # 58.8 / 62.6
-    (True, 1000, 1, 2048, 768, 1, 1, 1, "stream"),       # 69.8 / 106
-    (False, 1000, 1, 2048, 2048, 2, 1, 1, "stream"),     # 177 / 211
-    (False, 65, 1, 1024, 1388, 2, 1, 1, "mid"),          # vector ALUs 329 / 37.5: K segments of 1388 are not for the streaming kernel
+    # streaming kernel / split kernel ("mid"), us
+    (True, 2000, 8, 2048, 768, 0, 4, 8, "mid"),          # 493 / 238
+    (False, 2000, 8, 2048, 768, 0, 4, 8, "mid"),         # 241 / 140
+    (False, 5000, 1, 2048, 768, 1, 1, 1, "mid"),         # 179 / 96
+    (True, 500, 8, 1024, 2816, 0, 16, 64, "mid"),        # 231 / 136
+    (False, 500, 8, 1024, 2816, 0, 16, 64, "mid"),       # 127 / 78
+    (True, 500, 2, 548, 2816, 0, 8, 16, "mid"),          # 69 / 41
+    (True, 300, 8, 1024, 1388, 0, 16, 16, "mid"),        # 156 / 91
+    (True, 65, 2, 1024, 1388, 0, 16, 64, "stream"),      # 33 / 28: two rows per segment are expected, there may be fewer
+    (False, 1000, 8, 2048, 768, 0, 16, 16, "mid"),       # 236 / 140
+    (False, 128, 8, 2048, 768, 0, 16, 16, "mid"),        # 53 / 43
+    (True, 200, 8, 2048, 768, 0, 4, 8, "mid"),           # 72 / 48
+    (True, 500, 2, 548, 1388, 0, 16, 16, "mid"),         # 65 / 41
+    (True, 1000, 1, 2048, 768, 1, 1, 1, "mid"),          # 68 / 57
+    (False, 1000, 1, 2048, 2048, 2, 1, 1, "mid"),        # 172 / 127
+    (False, 100, 2, 1024, 2816, 0, 9, 18, "mid"),        # 56 / 35: groups that share K
+    (False, 2000, 2, 1024, 1388, 0, 9, 18, "mid"),       # 60 / 45
+    (True, 130, 1, 2048, 768, 1, 1, 1, "stream"),        # 23 / 35: few tiles
+    (False, 130, 1, 2048, 768, 1, 1, 1, "stream"),       # 11.4 / 13.6
+    (True, 70, 1, 2048, 352, 0, 1, 4, "stream"),         # 14.3 / 27.8
+    (True, 338, 1, 512, 1024, 0, 2, 4, "stream"),        # 15.6 / 13.2
+    (True, 74, 1, 1024, 512, 0, 64, 128, "stream"),      # 20.2 / 22.0: fewer rows than segments
+    (False, 300, 8, 768, 256, 0, 16, 16, "stream"),      # 18.7 / 16.7: short K, about a tile per unit
+    (False, 65, 1, 1024, 1388, 2, 1, 1, "mid"),          # vector ALUs 329 / 34: K segments of 1388 are not for the streaming kernel
     (False, 64, 1, 1024, 1388, 2, 1, 1, "vector_f32"),
+    (False, 90, 1, 515, 200, 3, 1, 1, "mid"),            # output rows that are no whole vectors
+    (True, 64, 2, 1024, 2816, 0, 16, 16, "stream"), (False, 64, 2, 1024, 2816, 0, 16, 16, "stream"),    # up to 64 tokens
 ])
 def test_f32_kernels_over_the_batch_sizes(up, T, k, d, f, n_shared, S, I, want):
     assert grace.grace_ffn_kernel(up, T, d, f, F32, k=k, S=S, I=I, n_shared=n_shared, n_cu=N_CU)[0] == want

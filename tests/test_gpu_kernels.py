@@ -149,21 +149,22 @@ def test_rank_without_instances_gives_zeros(T, k, d, f, dtype):
     assert torch.equal(grace.grace_expert_ffn(table, 1, x, off, T, k, *w, ws=ws), torch.zeros_like(x))
 
 
-@pytest.mark.parametrize("T,k,d,f,S,dtype,up,bn", [
-    (3000, 8, 200, 1032, 1, "bf16", True, 64),
-    (3000, 8, 200, 1032, 1, "bf16", False, 128),
-    (200, 8, 1024, 2048, 8, "f32", True, 32),
-    (1000, 8, 8192, 640, 8, "f32", False, 64),
+@pytest.mark.parametrize("T,k,d,f,S,I,dtype,up,threads", [
+    (3000, 8, 200, 1032, 1, 64, "bf16", True, 256),
+    (3000, 8, 200, 1032, 1, 64, "bf16", False, 256),
+    (200, 8, 1024, 2048, 8, 64, "f32", True, 256),
+    (1000, 8, 8192, 640, 8, 64, "f32", False, 256),
+    (400, 8, 1024, 1024, 8, 128, "f32", False, 512),    # two groups of wavefronts share K
 ])
-def test_more_rows_than_a_rank_is_expected_to_hold(T, k, d, f, S, dtype, up, bn):
-    """The 96-row kernels' grids cover five times a rank's even share; here one rank of many holds every row, so that workgroups
-    take several tiles."""
-    dt = grace.GRACE_F32 if dtype == "f32" else grace.GRACE_BF16
+def test_more_rows_than_a_rank_is_expected_to_hold(T, k, d, f, S, I, dtype, up, threads):
+    """The 96-row and the split kernels' grids cover five times a rank's even share; here one rank of many holds every row, so that
+    workgroups take several tiles."""
+    dt, tile_rows = (grace.GRACE_F32, 80) if dtype == "f32" else (grace.GRACE_BF16, 96)
     seg_rows = [T * k // S] * S
-    kernel, items = grace.grace_ffn_kernel(up, T, d, f, dt, k=k, S=S, I=64)
-    strips = -(-(f if up else d) // bn)
-    assert kernel == "mid" and items < S * -(-seg_rows[0] // 96) * strips * 256     # fewer workgroups than tiles
-    ffn_rows_of_segments(seg_rows, T, k, d, f, dtype, first=8, I=64, S=S)
+    kernel, items = grace.grace_ffn_kernel(up, T, d, f, dt, k=k, S=S, I=I)
+    strips = -(-f // 64) if up else -(-d // 128)
+    assert kernel == "mid" and items < S * -(-seg_rows[0] // tile_rows) * strips * threads     # fewer workgroups than whole tiles
+    ffn_rows_of_segments(seg_rows, T, k, d, f, dtype, first=8, I=I, S=S)
 
 
 def test_up_projection_of_decode_batches():
@@ -184,7 +185,7 @@ def test_large_tiles():
     ([1, 0, 2], 3, 1, 1024, 256, ("stream", "stream")),          # few rows: one workgroup per strip and segment
     ([40, 0, 25], 64, 2, 100, 76, ("stream", "stream")),         # K of 6 whole steps and 4 left over; strips past N
     ([65, 64, 0, 1], 65, 2, 128, 256, ("stream", "stream")),     # pieces: 65 rows in two, one full, one row
-    ([0, 130, 17, 300], 300, 2, 548, 1388, ("stream", "stream")),   # pieces of one, two and three fragments with ragged ends
+    ([0, 130, 17, 300], 300, 2, 180, 260, ("stream", "stream")),    # pieces of one, two and three fragments with ragged ends
     ([33, 97], 100, 2, 36, 77, ("stream", "vector_f32")),        # odd N up; the down projection's K takes the vector kernel
     ([33, 97], 100, 2, 34, 64, ("vector_f32", "stream")),        # odd N down
     ([1] * 70 + [80] * 3, 160, 2, 64, 32, ("stream", "stream")),    # more segments than lanes
@@ -228,11 +229,11 @@ def ffn_rows_of_segments(seg_rows, T, k, d, f, dt, first=0, I=None, S=None):
 
 
 @pytest.mark.parametrize("seg_rows,T,k,d,f,want", [
-    ([1, 0, 17, 33, 49, 65, 81, 96], 96, 8, 1024, 2048, ("mid", "stream")),    # pieces of one to six fragments
-    ([1, 0, 0, 0, 0, 0, 0, 2], 65, 2, 1028, 2052, ("mid", "stream")),          # few tiles: pieces of 16; K and N off the steps
+    ([1, 0, 17, 33, 49, 65, 81, 96], 96, 8, 1024, 2048, ("mid", "mid")),       # pieces of one to five fragments
+    ([1, 0, 0, 0, 0, 0, 0, 2], 65, 2, 1028, 2052, ("mid", "mid")),             # few tiles, of 16 rows; K and N off the steps
     ([40, 0, 0, 0, 0, 0, 0, 24], 65, 2, 1024, 2048, ("mid", "stream")),        # of 32
-    ([130, 0, 0, 0, 0, 0, 0, 0], 130, 2, 1024, 2048, ("mid", "stream")),       # of 64
-    ([300, 0, 0, 0, 0, 0, 50, 0], 300, 2, 1024, 2048, ("mid", "stream")),      # more tiles than compute units: of 96
+    ([130, 0, 0, 0, 0, 0, 0, 0], 130, 2, 1024, 2048, ("mid", "mid")),          # of 32 and 48, half the weight rows
+    ([300, 0, 0, 0, 0, 0, 50, 0], 300, 2, 1024, 2048, ("mid", "mid")),         # of 80
     ([0, 3000, 1, 97, 1500, 95, 700, 807], 3100, 2, 1284, 644, ("mid", "mid")),    # long launches; K and N off the steps and strips
     ([0, 1, 95, 96, 97] * 14 + [2154], 6200, 1, 1280, 640, ("mid", "mid")),    # more segments than lanes
 ])
@@ -242,14 +243,15 @@ def test_f32_long_launches(seg_rows, T, k, d, f, want):
     ffn_rows_of_segments(seg_rows, T, k, d, f, "f32")
 
 
-@pytest.mark.parametrize("seg_rows,T,k,d,f", [
-    ([16, 17, 33, 49, 65, 80, 81, 161], 260, 2, 516, 515),     # pieces of two to five fragments; N no multiple of 4; K of 16 steps and 4
-    ([120, 0, 1, 70, 3, 9, 200, 64], 250, 2, 1024, 1100),      # down: few tiles, the groups share a K of 34 steps and 12
-    ([90, 300, 10, 0, 0, 0, 0, 0], 210, 2, 2052, 2820),        # both projections; an odd number of steps
-    ([70] * 70, 2500, 2, 512, 1024),                           # more segments than lanes
+@pytest.mark.parametrize("seg_rows,T,k,d,f,want", [
+    ([16, 17, 33, 49, 65, 80, 81, 161], 260, 2, 516, 515, ("mid", "vector_f32")),     # pieces of one to five fragments; N no multiple of 4; K of 16 steps and 4
+    ([120, 0, 1, 70, 3, 9, 200, 64], 250, 2, 1024, 1100, ("mid", "mid")),      # down: few tiles, the groups share a K of 34 steps and 12
+    ([90, 300, 10, 0, 0, 0, 0, 0], 210, 2, 2052, 2820, ("mid", "mid")),        # an odd number of steps
+    ([70] * 70, 2500, 2, 512, 1024, ("mid", "mid")),                           # more segments than lanes
 ])
 @pytest.mark.parametrize("scale", [1.0, 1e-15, 1e20])          # inside the split's range and on either side of it
-def test_f32_split_kernel(seg_rows, T, k, d, f, scale):
+def test_f32_split_kernel(seg_rows, T, k, d, f, want, scale):
+    assert kernels_of(T, k, d, f, len(seg_rows), len(seg_rows), dtype="f32") == want
     if scale != 1.0 and len(seg_rows) > 8:
         pytest.skip("the range does not depend on the number of segments")
     S = len(seg_rows)
@@ -266,13 +268,13 @@ def test_f32_split_kernel(seg_rows, T, k, d, f, scale):
             continue
         xs = x[off[s]:off[s + 1]].double()
         h = torch.nn.functional.silu(xs @ wg[s].double().T) * (xs @ wu[s].double().T)
-        want = h @ wd[s].double().T
-        assert rel_err(y[off[s]:off[s + 1]].cpu().numpy().astype(np.float64), want.cpu().numpy()) <= TOL["f32"], s
+        ref = h @ wd[s].double().T
+        assert rel_err(y[off[s]:off[s + 1]].cpu().numpy().astype(np.float64), ref.cpu().numpy()) <= TOL["f32"], s
 
 
 def test_f32_split_kernel_infinities_and_nans():
     """An infinity or a NaN in one row: that row is what fp32 arithmetic gives, the others are as without it."""
-    T, d, f = 200, 1024, 2816
+    T, d, f = 900, 1024, 2816
     gen = torch.Generator(device="cuda").manual_seed(3)
     table = grace.GraceTable(1, 1, 1, [0], [1], [0, 1], [0])
     x = torch.randn((T, d), generator=gen, device="cuda")
@@ -283,6 +285,7 @@ def test_f32_split_kernel_infinities_and_nans():
     x[90, 3] = float("nan")
     x[150] = 0.0
     y = grace.grace_expert_ffn(table, 0, x, off, T, 1, wg, wu, wd)
+    assert kernels_of(T, 1, d, f, 1, 1, dtype="f32") == ("mid", "mid")
     assert torch.isposinf(y[7]).all() and torch.isnan(y[90]).all() and not y[150].any()
     rest = [i for i in range(T) if i not in (7, 90, 150)]
     assert rel_err(y[rest].cpu().numpy().astype(np.float64), plain[rest].cpu().numpy().astype(np.float64)) <= TOL["f32"]
@@ -293,6 +296,7 @@ def test_f32_split_rows_do_not_depend_on_their_neighbours():
     as are computed without the split."""
     T, k, d, f = 1000, 2, 1024, 2816
     few, many = [40, 3, 1, 0], [700, 600, 300, 400]
+    assert kernels_of(T, k, d, f, 4, 4, dtype="f32") == ("mid", "mid")
     gen = torch.Generator(device="cuda").manual_seed(11)
     table = grace.GraceTable(4, 1, 1, [0], [1], list(range(5)), [0] * 4)
     w = [0.05 * torch.randn(s, generator=gen, device="cuda") for s in ((4, f, d), (4, f, d), (4, d, f))]
@@ -314,7 +318,8 @@ def test_f32_split_rows_do_not_depend_on_their_neighbours():
 
 def test_f32_split_keeps_small_values_of_a_row_with_large_ones():
     """An element of 2^-120 next to 1: its lowest parts lie below the range of bf16, and it is all that its column sees."""
-    T, d, f = 200, 1024, 512
+    T, d, f = 1000, 1024, 1024
+    assert kernels_of(T, 1, d, f, 1, 1, dtype="f32")[0] == "mid"
     gen = torch.Generator(device="cuda").manual_seed(5)
     table = grace.GraceTable(1, 1, 1, [0], [1], [0, 1], [0])
     x = torch.zeros((T, d), device="cuda")
@@ -329,11 +334,12 @@ def test_f32_split_keeps_small_values_of_a_row_with_large_ones():
     assert rel_err(y.cpu().numpy().astype(np.float64), (h @ wd[0].double().T).cpu().numpy()) <= TOL["f32"]   # (1.3e-6; 5.9e-5 without)
 
 
-@pytest.mark.parametrize("T", [97, 7000])           # both numbers of groups that share K
+@pytest.mark.parametrize("T,d", [(97, 520), (7000, 520), (90, 515)])     # both numbers of groups that share K; rows of no whole vectors
 @pytest.mark.parametrize("odd", ["small", "infinite"])
-def test_f32_split_of_segmented_k_out_of_range(T, odd):
+def test_f32_split_of_segmented_k_out_of_range(T, d, odd):
     """Shared experts' down projection, K segments off the step: sums too small for the split, and infinities among the weights."""
-    d, f, n_shared = 520, 200, 3
+    f, n_shared = 200, 3
+    assert kernels_of(T, 1, d, f, 1, 1, n_shared=n_shared, dtype="f32")[1] == "mid"
     gen = torch.Generator(device="cuda").manual_seed(T)
     x = torch.randn((T, d), generator=gen, device="cuda") * (1e-14 if odd == "small" else 1.0)
     wg, wu, wd = (0.05 * torch.randn(s, generator=gen, device="cuda") for s in ((n_shared, f, d), (n_shared, f, d), (n_shared, d, f)))
