@@ -115,57 +115,100 @@ struct Left {
 };
 static_assert(sizeof(Left<2>) <= GROUP_BYTES, "one group's LDS holds it");
 
-// The doubtful sums of a wavefront's part of a tile with the fp32 matrix instruction: fragments straight from memory, one after the
-// other.  wn: its first output column; nj: its weight fragments.
+// Operands of a wavefront's part of a tile straight from memory.  Two fragments of weights: gate and up, or the wavefront's two (wn: its
+// first output column; nj: how many it has).
+template <bool FUSED_UP>
+struct FromMemory {
+    __amdgpu_buffer_rsrc_t a, b[2];
+    uint32_t b_off[2];
+    __device__ __forceinline__ FromMemory(const GemmArgs &g, int slot, int m0, int wn, int nj, int r) {
+        const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 4;
+        a = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 4);
+        b[0] = rsrc_of((const char *)g.B0 + b_first);
+        b[1] = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = FUSED_UP ? r : j * 16 + r;
+            b_off[j] = wn + n < g.N && (FUSED_UP || j < nj) ? (uint32_t)n * (uint32_t)(g.ldb * 4) : NO_DATA;
+        }
+    }
+};
+// COUNT times 16 rows from row `first` on (of the tile) with the fp32 matrix instruction; the sums whose bits are set go out.
+template <bool FUSED_UP, bool SEG_K, int COUNT>
+__device__ __forceinline__ void rows_by_f32(const GemmArgs &g, const FromMemory<FUSED_UP> &from, int m0, int m_end, int first, int wn, int lane, uint64_t again) {
+    const int r = lane & 15, q = lane >> 4;
+    uint32_t a_off[COUNT];
+    f32x4_t part[COUNT][2][4];   // chains of K / 16 additions
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) {
+        const int row = first + i * 16 + r;
+        a_off[i] = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 4) : NO_DATA;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[i][0][v] = part[i][1][v] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    constexpr int UNROLL = COUNT == 1 ? 8 : 1;
+#pragma unroll UNROLL
+    for (int k0 = 0; k0 < g.K; k0 += 16) {
+        const int k = k0 + 4 * q;   // (K is a multiple of 4)
+        const uint32_t ka = k < g.K ? (uint32_t)k * 4u : NO_DATA;
+        const uint32_t kb = SEG_K && k < g.K ? (uint32_t)(koff(g, k) * 4) : ka;
+        f32x4_t fb[2], fa[COUNT];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fb[j] = __builtin_bit_cast(f32x4_t, load16(from.b[j], offset_with(from.b_off[j], kb), 0));
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) fa[i] = __builtin_bit_cast(f32x4_t, load16(from.a, offset_with(a_off[i], ka), 0));
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) part[i][j][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][v], fa[i][v], part[i][j][v], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) {
+        float *const o = (float *)g.out + (int64_t)(m0 + first + i * 16 + r) * g.ldo + wn + 4 * q;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float h = (part[i][0][0][v] + part[i][0][1][v]) + (part[i][0][2][v] + part[i][0][3][v]);
+            const float h1 = (part[i][1][0][v] + part[i][1][1][v]) + (part[i][1][2][v] + part[i][1][3][v]);
+            if (again >> (8 * i + v) & 1) o[v] = FUSED_UP ? h / (1.0f + expf(-h)) * h1 : h;
+            if (again >> (8 * i + 4 + v) & 1) o[16 + v] = h1;
+        }
+    }
+}
+// The doubtful sums of a wavefront's part of a tile: 16 rows after the other if one or two times 16 have some, else all rows, which share the
+// weights' loads (d = 1024, f = 2816, 2000 rows in 16 segments: all sums doubtful, gate+up 183 -> 548, down 94 -> 304 us, 16 rows after the other 876
+// and 662; an infinity in every 97th row 283 and 175; the fp32 instruction with tiles made for it 250 and 168).
 template <bool FUSED_UP, bool SEG_K, int K_GROUPS>
 __device__ __forceinline__ void by_f32(const GemmArgs &g, const Left<K_GROUPS> &left, int slot, int m0, int m_end, int wn, int wave, int nj, int lane) {
     const int r = lane & 15, q = lane >> 4;
-    const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 4);
-    const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 4;
-    const auto b0_rsrc = rsrc_of((const char *)g.B0 + b_first);
-    const auto b1_rsrc = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
-    constexpr int NB = FUSED_UP ? 2 : 1;
-    const int frags = ((m_end - m0 + 15) >> 4) * (FUSED_UP ? 1 : nj);
-    for (int f = 0; f < frags; ++f) {
-        const int i = FUSED_UP ? f : f / nj, j = FUSED_UP ? 0 : f - i * nj, row = i * 16 + r, n = j * 16 + r, col = wn + j * 16 + 4 * q;
-        const f32x4_t sum = left.sums[wave][i * nj + j][lane];
-        f32x4_t up = sum;
-        if constexpr (FUSED_UP) up = nj == 2 ? left.sums[wave][i * nj + 1][lane] : left.sums[wave][i][lane ^ 32];
+    uint64_t again = 0;   // this lane's sums: bit 8 i + 4 j + v
+    int need = 0;         // 16 rows of anyone's (scalar)
+    for (int i = 0; i * 16 < m_end - m0; ++i) {
+        const int row = i * 16 + r;
         const bool here = m0 + row < m_end && !(FUSED_UP && nj == 1 && q >= 2);
-        int again = 0;
+        int mine = 0;
+        for (int j = 0; j < (FUSED_UP ? 1 : nj); ++j) {
+            const f32x4_t sum = left.sums[wave][i * nj + j][lane];
+            f32x4_t up = sum;
+            if constexpr (FUSED_UP) up = nj == 2 ? left.sums[wave][i * nj + 1][lane] : left.sums[wave][i][lane ^ 32];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            bool one = doubtful(sum[v], left.a(row), left.b(wave, j * 16 + 4 * q + v), g.K);
-            if constexpr (FUSED_UP) one |= doubtful(up[v], left.a(row), left.b(wave, (nj * 8 + 4 * q + v) & (B_WAVE_ROWS - 1)), g.K);
-            again |= (int)(one && here && col + v < g.N) << v;
-        }
-        if (!__any(again)) continue;
-        const uint32_t a_off = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 4) : NO_DATA;
-        const uint32_t b_off = wn + n < g.N ? (uint32_t)n * (uint32_t)(g.ldb * 4) : NO_DATA;
-        f32x4_t part[NB][4];   // chains of K / 16 additions
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-            for (int m = 0; m < NB; ++m) part[m][v] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-        for (int k0 = 0; k0 < g.K; k0 += 16) {
-            const int k = k0 + 4 * q;   // (K is a multiple of 4)
-            const uint32_t ka = k < g.K ? (uint32_t)k * 4u : NO_DATA;
-            const uint32_t kb = SEG_K && k < g.K ? (uint32_t)(koff(g, k) * 4) : ka;
-            const f32x4_t fa = __builtin_bit_cast(f32x4_t, load16(a_rsrc, offset_with(a_off, ka), 0));
-#pragma unroll
-            for (int m = 0; m < NB; ++m) {
-                const f32x4_t fb = __builtin_bit_cast(f32x4_t, load16(m ? b1_rsrc : b0_rsrc, offset_with(b_off, kb), 0));
-#pragma unroll
-                for (int v = 0; v < 4; ++v) part[m][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[v], fa[v], part[m][v], 0, 0, 0);
+            for (int v = 0; v < 4; ++v) {
+                bool one = doubtful(sum[v], left.a(row), left.b(wave, j * 16 + 4 * q + v), g.K);
+                if constexpr (FUSED_UP) one |= doubtful(up[v], left.a(row), left.b(wave, (nj * 8 + 4 * q + v) & (B_WAVE_ROWS - 1)), g.K);
+                mine |= (int)(one && here && wn + j * 16 + 4 * q + v < g.N) << (j * 4 + v);
             }
         }
-        float *const o = (float *)g.out + (int64_t)(m0 + row) * g.ldo + col;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            float h = (part[0][0][v] + part[0][1][v]) + (part[0][2][v] + part[0][3][v]);
-            if constexpr (FUSED_UP) h = h / (1.0f + expf(-h)) * ((part[1][0][v] + part[1][1][v]) + (part[1][2][v] + part[1][3][v]));
-            if (again >> v & 1) o[v] = h;
+        again |= (uint64_t)mine << (8 * i);
+        need |= __any(mine) ? 1 << i : 0;
+    }
+    const FromMemory<FUSED_UP> from(g, slot, m0, wn, nj, r);
+    if (__popc(need) > 2) {
+        rows_by_f32<FUSED_UP, SEG_K, MAX_MF>(g, from, m0, m_end, 0, wn, lane, again);
+    } else {
+        for (; need; need &= need - 1) {
+            const int i = __ffs(need) - 1;
+            rows_by_f32<FUSED_UP, SEG_K, 1>(g, from, m0, m_end, i * 16, wn, lane, again >> (8 * i));
         }
     }
 }
@@ -412,7 +455,8 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const int col = FUSED_UP ? (NJ == 2 ? wn + 4 * q : wn + 4 * (q & 1)) : wn + j * 16 + 4 * q;
-            out_of_range |= any_out(acc[i][j], least_of(am, b_most4[j], g.K)) && m0 + i * 16 + r < m_end && col < g.N;
+            const float least = am > 0.0f && b_most4[j] > 0.0f ? least_of(am, b_most4[j], g.K) : 0.0f;   // (zeros times whatever)
+            out_of_range |= any_out(acc[i][j], least) && m0 + i * 16 + r < m_end && col < g.N;
         }
     }
 
