@@ -261,7 +261,7 @@ static bool split_is_faster(const GemmArgs &g, const Rows &rows, int n_cu) {
         return percent >= (g.K >= 512 ? 42 : g.K >= 192 ? 70 : 125);
     } else {
         // (rows of a segment times K: what its weights, of whatever width, are multiplied with)
-        if (split_groups<false>(g, rows, n_cu) == 2) return percent >= 30 && g.K >= 512 && m * g.K > (percent >= 50 ? 8000 : 20000) * segments;
+        if (split_groups<false>(g, rows, n_cu) == 2) return percent >= 30 && g.K >= 512 && m * g.K > (percent >= 50 ? 8000 : 16000) * segments;
         return percent > 400 || m * g.K > 6000 * segments;
     }
 }
