@@ -65,15 +65,6 @@ __device__ __forceinline__ bool doubtful(float sum, float am, float bm, int K) {
     if (s == 0.0f && (am == 0.0f || bm == 0.0f)) return false;
     return !(s != s && am < 0x1p47f && bm < 0x1p47f);   // no product overflows: it is the NaN of an operand
 }
-// Is one of the four sums too small for `least` or not finite?  (how all but the odd tile are done with: three instructions per sum)
-__device__ __forceinline__ bool any_out(const f32x4_t &sum, float least) {
-    const uint32_t from = __float_as_uint(least);
-    uint32_t most = 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) most = max(most, (__float_as_uint(sum[v]) & 0x7fffffffu) - from);
-    return most >= 0x7f800000u - from;
-}
-
 // the kernels, each compiled in a .hip file of its own (shared_down: weights' K axis in segments)
 const void *up_kernel();
 const void *down_kernel(int k_groups);
@@ -106,9 +97,19 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t &hi, uint32_t 
 // What a tile leaves in LDS for the check of its sums: the largest magnitudes of its rows, and the sums of a tile that did not pass at once.
 template <int K_GROUPS>
 struct Left {
-    float a_most[K_GROUPS][BM], b_most[K_GROUPS][4][B_WAVE_ROWS];
+    alignas(16) float a_most[K_GROUPS][BM];
+    alignas(16) float b_most[K_GROUPS][4][B_WAVE_ROWS];
     f32x4_t sums[4][MAX_MF * 2][64];   // [wavefront][fragment][lane]
     __device__ __forceinline__ float a(int row) const { return K_GROUPS > 1 ? fmaxf(a_most[0][row], a_most[K_GROUPS - 1][row]) : a_most[0][row]; }
+    __device__ __forceinline__ float b4(int wave, int row) const {   // of four rows, the first a multiple of 4
+        f32x4_t m = *(const f32x4_t *)&b_most[0][wave][row];
+        float most = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+        if (K_GROUPS > 1) {
+            m = *(const f32x4_t *)&b_most[K_GROUPS - 1][wave][row];
+            most = fmaxf(most, fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])));
+        }
+        return most;
+    }
     __device__ __forceinline__ float b(int wave, int row) const {
         return K_GROUPS > 1 ? fmaxf(b_most[0][wave][row], b_most[K_GROUPS - 1][wave][row]) : b_most[0][wave][row];
     }
@@ -435,31 +436,17 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
     }
     __syncthreads();
     if (group != 0) return false;
+    float a_here[MF], b_here[NJ];   // of this lane's row and four columns of each fragment: read here, looked at when the sums are on their way out
+#pragma unroll
+    for (int i = 0; i < MF; ++i) a_here[i] = left_here.a(i * 16 + r);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b_here[j] = left_here.b4(wave, j * 16 + 4 * q);
     if constexpr (K_GROUPS > 1) {
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] += sums[(i * NJ + j) * 64];
     }
-    float b_most4[NJ];   // of the four columns that a lane has of a fragment
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        b_most4[j] = 0.0f;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) b_most4[j] = fmaxf(b_most4[j], left_here.b(wave, j * 16 + 4 * q + v));
-    }
-    bool out_of_range = false;
-#pragma unroll
-    for (int i = 0; i < MF; ++i) {
-        const float am = left_here.a(i * 16 + r);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int col = FUSED_UP ? (NJ == 2 ? wn + 4 * q : wn + 4 * (q & 1)) : wn + j * 16 + 4 * q;
-            const float least = am > 0.0f && b_most4[j] > 0.0f ? least_of(am, b_most4[j], g.K) : 0.0f;   // (zeros times whatever)
-            out_of_range |= any_out(acc[i][j], least) && m0 + i * 16 + r < m_end && col < g.N;
-        }
-    }
-
     // ---- epilogue: element v of lane l of a fragment is output column 4 * (l / 16) + v, row l % 16 ----
     float *const out = (float *)g.out;
 #pragma unroll
@@ -491,6 +478,28 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
             }
         }
     }
+    // Is any of the lane's sums small for its largest rows, or not finite?  (Rows of zeros give zeros, as do those past the tile's; few instructions,
+    // for they are cold at the end of a tile: one test per sum took 2 us of a layer's 50 us projection.)
+    float smallest = INFINITY, all_sums = 0.0f, am = 0.0f, bm = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) bm = fmaxf(bm, b_here[j]);
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+        float of_rows = INFINITY;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const f32x4_t &x = acc[i][j];
+            const float m = fminf(fminf(fabsf(x[0]), fabsf(x[1])), fminf(fabsf(x[2]), fabsf(x[3])));
+            of_rows = fminf(of_rows, b_here[j] > 0.0f ? m : INFINITY);
+            all_sums += x[0];
+            all_sums += x[1];
+            all_sums += x[2];
+            all_sums += x[3];
+        }
+        smallest = fminf(smallest, a_here[i] > 0.0f ? of_rows : INFINITY);
+        am = fmaxf(am, a_here[i]);
+    }
+    const bool out_of_range = !(smallest >= least_of(am, bm, g.K)) || !(fabsf(all_sums) < INFINITY);
     if (!__any(out_of_range)) return false;
 #pragma unroll
     for (int i = 0; i < MF; ++i)
@@ -502,9 +511,12 @@ __device__ __forceinline__ bool tile_body(const GemmArgs &g, int slot, int m0, i
 // Where workgroup number b works: tile t (-1: none) of `blocks` numbers, in segment s.  SEG_PER_LANE: 1 for up to 64 row segments, 4 for
 // up to 256.  Pieces of a segment have one size, and tiles are numbered and dealt to the XCDs as gemm_bf16_mid_kernel's.  Half
 // tiles, and lower pieces, while there is a place for each (the places: two workgroups per compute unit, one if its groups share K).
+// few_rows: most segments have no more than 16.  Gate+up projections then take tiles of 16 rows where that is enough (300 to 1200 rows in
+// 64 segments, time over that of the fp32 instruction 0.985 -> 0.956, median of 752); elsewhere the code of one more height, cold in each
+// launch, costs more than it saves (500 tokens, d = 548, f = 2816, layer step 144 -> 148 us), and down projections are even.
 struct Place {
     int blocks, t;
-    bool halves;
+    bool halves, few_rows;
     Segment s;
 };
 template <int SEG_PER_LANE>
@@ -513,6 +525,13 @@ __device__ __forceinline__ Place place_of(const GemmArgs &g, int b, int n_strips
     segs.load(g, lane);
     segs.cut(lane, BM);
     Place p;
+    int more = 0, any = 0;   // segments of more than 16 rows, of any
+#pragma unroll
+    for (int q = 0; q < SEG_PER_LANE; ++q) {
+        more += (int)__popcll(__ballot(segs.hi[q] - segs.lo[q] > 16));
+        any += (int)__popcll(__ballot(segs.hi[q] > segs.lo[q]));
+    }
+    p.few_rows = 2 * more <= any;
     p.halves = 2 * segs.total * n_strips <= places;
     if (p.halves) {
         if (2 * segs.count(32) * n_strips <= places) segs.cut(lane, 32);
@@ -521,7 +540,8 @@ __device__ __forceinline__ Place place_of(const GemmArgs &g, int b, int n_strips
     const int strips = p.halves ? 2 * n_strips : n_strips, total = segs.total * strips;
     p.blocks = (total + 63) & ~63;
     p.t = b < p.blocks ? mid::of_runs(b, total) : -1;
-    p.s = segs.segment(max(p.t, 0) / strips, lane);
+    p.s = Segment{0, 0, 0, 0, 1};
+    if (p.t >= 0) p.s = segs.segment(p.t / strips, lane);   // (surplus workgroups leave without)
     return p;
 }
 
@@ -555,7 +575,10 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
         auto tile = [&](auto nj) {
             constexpr int NJ = decltype(nj)::value;
             switch ((m_end - m0 + 15) >> 4) {
-                case 1: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 1, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
+                case 1:
+                    if constexpr (FUSED_UP)
+                        if (p.few_rows) return tile_body<FUSED_UP, SEG_K, K_GROUPS, 1, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
+                    [[fallthrough]];
                 case 2: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 2, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
                 case 3: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 3, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
                 case 4: return tile_body<FUSED_UP, SEG_K, K_GROUPS, 4, NJ>(g, s.slot, m0, m_end, n0, rotation, seg_of, smem);
