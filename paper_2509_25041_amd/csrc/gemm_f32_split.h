@@ -21,11 +21,11 @@
 // split, so they have AHEAD whole steps; two weight fragments per wavefront share each activation fragment's read where there
 // are tiles enough.  80 rows: two groups of four wavefronts fill the LDS.
 // Where a launch's tiles are few, K long (down projections), the two groups of a compute unit share a tile, each with half of K (d =
-// 1024, f = 2816, 1000 rows in 9 segments 84 -> 80 us, 300 rows 46 -> 38, 100 rows 46 -> 35, 2000 rows in 16 107 -> 91 us).
+// 1024, f = 2816, 989 rows in 9 segments 84 -> 68 us, 332 rows 46 -> 39, 114 rows 46 -> 35; where: split_groups in ffn.hip).
 //
-// d = 1024, f = 2816, cold weights, fp32 instruction (96 x 64 tiles, or streamed) -> this kernel, us: 1000 rows in 9 segments, gate+up 161 ->
-// 106, down 92 -> 80; 300 rows 62 -> 48, 62 -> 38; 2000 rows in 16 segments 253 -> 184, 159 -> 91; 16000 rows 1633 -> 1079 (171
-// TFLOP/s, the fp32 instruction's own peak is 157), 793 -> 553.  70 rows, bound by the weights (207 MB), 45 -> 47.
+// d = 1024, f = 2816, cold weights, fp32 instruction (96 x 64 tiles, or streamed) -> this kernel, us: 989 rows in 9 segments, gate+up 135 ->
+// 103, down 101 -> 68; 332 rows 78 -> 55, 63 -> 39; 2000 rows in 16 segments 260 -> 181, 160 -> 132; 16000 rows 1725 -> 1140 (162
+// TFLOP/s, the fp32 instruction's own peak is 157), 840 -> 570.  66 rows, bound by the weights (207 MB), 43 -> 47.
 #pragma once
 #include <type_traits>
 #include <utility>
