@@ -35,13 +35,10 @@ template <int VPL, int TOPK_TOK_PER_WAVE>
 __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float *__restrict__ logits, int T, int E, int k,
                                                             int renorm, int32_t *__restrict__ topk_expert,
                                                             float *__restrict__ topk_weight,
-                                                            int32_t *__restrict__ chunk_hist,
-                                                            int32_t *__restrict__ clear, int n_clear) {
+                                                            int32_t *__restrict__ chunk_hist) {
     __shared__ int32_t hist[GRACE_MAX_EXPERTS];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int i = tid; i < E; i += TOPK_THREADS) hist[i] = 0;
-    // counters a later kernel of the same call accumulates into
-    for (int64_t i = (int64_t)blockIdx.x * TOPK_THREADS + tid; i < n_clear; i += (int64_t)gridDim.x * TOPK_THREADS) clear[i] = 0;
     __syncthreads();
     const int chunk = (int)blockIdx.x;
     const int t_begin = (chunk * (TOPK_THREADS / 64) + wave) * TOPK_TOK_PER_WAVE;
@@ -123,15 +120,13 @@ template <int NV, int K>
 __global__ __launch_bounds__(64 * TOPK_LANES) void topk_lanes_kernel(const float *__restrict__ logits, int T, int E, int k, int renorm,
                                                             int32_t *__restrict__ topk_expert,
                                                             float *__restrict__ topk_weight,
-                                                            int32_t *__restrict__ chunk_hist, int32_t *__restrict__ clear,
-                                                            int n_clear, int chunk_tokens) {
+                                                            int32_t *__restrict__ chunk_hist, int chunk_tokens) {
     constexpr int L = TOPK_LANES;
     static_assert(L == 4, "the merge and the broadcasts below are written for quads of lanes");
     static_assert(NV % 4 == 0, "16-byte loads");
     __shared__ int32_t hist[GRACE_MAX_EXPERTS];
     const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
     for (int i = tid; i < E; i += nthr) hist[i] = 0;
-    for (int64_t i = (int64_t)blockIdx.x * nthr + tid; i < n_clear; i += (int64_t)gridDim.x * nthr) clear[i] = 0;
     __syncthreads();
     const int chunk = (int)blockIdx.x;
     const int q = tid % L;
@@ -233,8 +228,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void route_scan_kernel(const int32_t 
 // an exclusive scan over the eight rows, continued from cnt (requests before this round), gives each
 // wavefront the number of earlier requests of every expert, and request number c of expert e maps to
 // the candidate of the tier Algorithm 4 selects whose cumulative polling-weight interval holds c mod W.
-// With inst_hist (zeroed beforehand) every pick is also counted per chunk of PERM_CHUNK assignments
-// and instance: the histogram the dispatch permutation starts from (integer atomics: exact in any order).
 constexpr int PICK_LDS_CANDS = 1024;  // candidate entries of one view that are staged in LDS (else read from global memory)
 constexpr int PICK_THREADS = 512, PICK_WAVES = PICK_THREADS / 64;
 constexpr int PICK_TOKENS = 64;       // tokens per workgroup
@@ -250,7 +243,6 @@ __global__ __launch_bounds__(PICK_THREADS) void pick_kernel(const int32_t *__res
                                                             const int32_t *__restrict__ cand_g,
                                                             const uint32_t *__restrict__ cand_cum,
                                                             int32_t *__restrict__ topk_inst, int nbits,
-                                                            int32_t *__restrict__ inst_hist, int I,
                                                             const int32_t *__restrict__ super_tot, int c_first,
                                                             int n_cand) {
     __shared__ int32_t cnt[GRACE_MAX_EXPERTS];                // requests of each expert before the current round
@@ -318,8 +310,6 @@ __global__ __launch_bounds__(PICK_THREADS) void pick_kernel(const int32_t *__res
     const int32_t *t_g = table_in_lds ? s_g : cand_g;
     const uint32_t *t_cum = table_in_lds ? s_cum : cand_cum;
     const uint64_t lt = lanemask_lt();
-    const int ibits = bits_for(I);
-    static_assert(PERM_CHUNK % 64 == 0, "a wavefront's assignments must not straddle permutation chunks");
     for (int64_t b0 = a0; b0 < a1; b0 += PICK_THREADS) {
         const int64_t a = b0 + tid;
         const int e_raw = (b0 == a0) ? e_first : (a < a1 ? topk_expert[a] : -1);
@@ -340,18 +330,9 @@ __global__ __launch_bounds__(PICK_THREADS) void pick_kernel(const int32_t *__res
             cnt[i] = run;
         }
         __syncthreads();
-        int g = 0;
         if (valid) {
             const uint64_t c = (uint64_t)(uint32_t)wcnt[wave][e] + (uint32_t)__popcll(same & lt) + (uint64_t)(rr_in ? rr_in[e] : 0u);
-            g = pick_candidate(c, e, t_ptr, t_g, t_cum);
-            topk_inst[a] = g;
-        }
-        if (inst_hist) {
-            // a wavefront's 64 assignments lie in one permutation chunk (both are multiples of 64):
-            // one atomic per distinct instance, by the highest lane of its match set
-            const bool counted = valid && (unsigned)g < (unsigned)I;
-            const uint64_t same_g = wave_match((uint32_t)g, counted, ibits);
-            if (counted && is_last_of(same_g)) atomicAdd(&inst_hist[(a / PERM_CHUNK) * I + g], (int32_t)__popcll(same_g));
+            topk_inst[a] = pick_candidate(c, e, t_ptr, t_g, t_cum);
         }
         __syncthreads();  // wcnt is cleared again in the next round
     }
@@ -371,7 +352,7 @@ namespace grace {
 
 // Top-k gate of T >= 1 tokens; chunk_hist receives ceil(T / route_chunk_tokens(T)) x E expert counts.
 int launch_topk(const float *logits, int T, int E, int k, int renorm, int32_t *topk_expert, float *topk_weight,
-                int32_t *chunk_hist, int32_t *clear, int n_clear, hipStream_t st) {
+                int32_t *chunk_hist, hipStream_t st) {
     const int chunk_tokens = route_chunk_tokens(T);
     const int nchunks = (int)ceil_div(T, chunk_tokens);
     if (T >= TOPK_LANES_MIN_T && E >= TOPK_LANES_MIN_E && k <= 8 && E % 4 == 0 && ((uintptr_t)logits & 15) == 0) {
@@ -380,8 +361,7 @@ int launch_topk(const float *logits, int T, int E, int k, int renorm, int32_t *t
             constexpr int NV = decltype(nv)::value;
             auto *kern = k <= 2 ? topk_lanes_kernel<NV, 2> : k <= 4 ? topk_lanes_kernel<NV, 4> : k <= 6 ? topk_lanes_kernel<NV, 6>
                                                                                                        : topk_lanes_kernel<NV, 8>;
-            kern<<<nchunks, thr, 0, st>>>(logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist, clear, n_clear,
-                                          chunk_tokens);
+            kern<<<nchunks, thr, 0, st>>>(logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist, chunk_tokens);
         };
         if (E <= 64) launch(std::integral_constant<int, 16>{});
         else if (E <= 128) launch(std::integral_constant<int, 32>{});
@@ -392,13 +372,13 @@ int launch_topk(const float *logits, int T, int E, int k, int renorm, int32_t *t
 #define GRACE_TOPK(VPL)                                                                                              \
     if (chunk_tokens == ROUTE_CHUNK_SMALL)                                                                           \
         topk_kernel<VPL, ROUTE_CHUNK_SMALL / (TOPK_THREADS / 64)><<<nchunks, TOPK_THREADS, 0, st>>>(                \
-            logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist, clear, n_clear);                          \
+            logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist);                                          \
     else if (chunk_tokens == ROUTE_CHUNK_LARGE)                                                                      \
         topk_kernel<VPL, ROUTE_CHUNK_LARGE / (TOPK_THREADS / 64)><<<nchunks, TOPK_THREADS, 0, st>>>(                \
-            logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist, clear, n_clear);                          \
+            logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist);                                          \
     else                                                                                                             \
         topk_kernel<VPL, ROUTE_CHUNK_HUGE / (TOPK_THREADS / 64)><<<nchunks, TOPK_THREADS, 0, st>>>(                 \
-            logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist, clear, n_clear)
+            logits, T, E, k, renorm, topk_expert, topk_weight, chunk_hist)
     switch ((E + 63) / 64) {
         case 1: GRACE_TOPK(1); break;
         case 2: GRACE_TOPK(2); break;
@@ -433,25 +413,24 @@ int check_route_args(const grace_table *table, int32_t local_rank, grace_policy 
 
 }  // namespace grace
 
-namespace grace {
+using namespace grace;
 
-// The launches of grace_route for T >= 0 checked arguments.  With inst_hist (ceil(T*k / PERM_CHUNK) x I
-// counters, T >= 1) the picks are also counted per permutation chunk and instance.
-int launch_route(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T,
-                 int32_t E, int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out, int32_t *topk_expert,
-                 float *topk_weight, int32_t *topk_inst, int32_t *expert_count, void *ws, int32_t *inst_hist,
-                 hipStream_t st) {
+extern "C" int grace_route(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T, int32_t E,
+                           int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out, int32_t *topk_expert,
+                           float *topk_weight, int32_t *topk_inst, int32_t *expert_count, void *ws, void *stream) {
+    const int rc = check_route_args(table, local_rank, policy, logits, T, E, k, rr_in, rr_out, topk_expert, topk_weight,
+                                    topk_inst, expert_count, ws);
+    if (rc != GRACE_OK) return rc;
+    hipStream_t st = (hipStream_t)stream;
     const int chunk_tokens = route_chunk_tokens(T);
     const int nchunks = (int)ceil_div(T, chunk_tokens);
-    const int I = table->I;
     int32_t *hist = (int32_t *)ws;
     int32_t *base = (int32_t *)((char *)ws + align_up((size_t)nchunks * E * 4, 256));
     const int view = policy == GRACE_POLICY_WRR ? table->R : local_rank;
     const int32_t *cand_ptr = table->d_cand_ptr + (size_t)view * E;
     const int c_first = table->cand_view[view], n_cand = table->cand_view[view + 1] - c_first;
     if (nchunks > 0) {
-        const int64_t n_clear = inst_hist ? ceil_div((int64_t)T * k, PERM_CHUNK) * I : 0;
-        const int rc_topk = launch_topk(logits, T, E, k, renorm, topk_expert, topk_weight, hist, inst_hist, (int)n_clear, st);
+        const int rc_topk = launch_topk(logits, T, E, k, renorm, topk_expert, topk_weight, hist, st);
         if (rc_topk != GRACE_OK) return rc_topk;
     }
     int nbits = 0;
@@ -471,7 +450,7 @@ int launch_route(const grace_table *table, int32_t local_rank, grace_policy poli
         pick_kernel<true><<<pick_blocks, PICK_THREADS, 0, st>>>(topk_expert, (int64_t)T * k, E, k, hist, nchunks,
                                                                 rows_per_block, rr_in, rr_out, expert_count, cand_ptr,
                                                                 table->d_cand_g, table->d_cand_cum, topk_inst, nbits,
-                                                                inst_hist, I, super_tot, c_first, n_cand);
+                                                                super_tot, c_first, n_cand);
         GRACE_LAUNCH_CHECK("pick_kernel");
         return GRACE_OK;
     }
@@ -482,22 +461,8 @@ int launch_route(const grace_table *table, int32_t local_rank, grace_policy poli
         pick_kernel<false><<<pick_blocks, PICK_THREADS, 0, st>>>(topk_expert, (int64_t)T * k, E, k, base, nchunks,
                                                                  rows_per_block, rr_in, rr_out, expert_count, cand_ptr,
                                                                  table->d_cand_g, table->d_cand_cum, topk_inst, nbits,
-                                                                 inst_hist, I, nullptr, c_first, n_cand);
+                                                                 nullptr, c_first, n_cand);
         GRACE_LAUNCH_CHECK("pick_kernel");
     }
     return GRACE_OK;
-}
-
-}  // namespace grace
-
-using namespace grace;
-
-extern "C" int grace_route(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T, int32_t E,
-                           int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out, int32_t *topk_expert,
-                           float *topk_weight, int32_t *topk_inst, int32_t *expert_count, void *ws, void *stream) {
-    const int rc = check_route_args(table, local_rank, policy, logits, T, E, k, rr_in, rr_out, topk_expert, topk_weight,
-                                    topk_inst, expert_count, ws);
-    if (rc != GRACE_OK) return rc;
-    return launch_route(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight,
-                        topk_inst, expert_count, ws, nullptr, (hipStream_t)stream);
 }

@@ -1,20 +1,12 @@
 // grace_route_permute: grace_route followed by grace_permute as one call.
 //
-// Any batch: the replica pick also counts its choices per permutation chunk and
-// instance (into counters the top-k kernel cleared), so the permutation's own
-// histogram launch is dropped: top-k, pick, positions, row scatter.
-//
-// Decode-sized batches (a few hundred tokens) are bound by launch latency: the
-// two calls need five launches of kernels that each run a few microseconds.  When
-// the batch is small enough, the top-k gate (one wavefront per token, spread over
-// the device) is followed by ONE single-workgroup kernel that does all the index
-// work, every wavefront owning a contiguous range of assignments:
-//   1. request counters    scan of the per-wavefront expert counts (Section 4.3)
-//   2. replica pick        Algorithm 4 tier + weighted round-robin, per wavefront in order
-//   3. offsets             per instance / rank / node, scan of the per-wavefront instance counts
-//   4. positions           stable rank of every assignment in (node, rank, slot) order (Section 5)
-// and by the row scatter: three launches.  Still smaller ones take a single launch (route_permute_tiny_kernel).
+//   1. topk_kernel / topk_lanes_kernel (route.hip): choices, gate weights, a histogram of the chosen experts per chunk of tokens
+//   2. place_kernel: request counters, replica pick (Algorithm 4 tier + weighted round-robin), offsets per instance / rank / node
+//      and the stable position of every assignment in (node, rank, slot) order (Section 5)
+//   3. scatter_rows_kernel (permute.hip): the rows
+// The smallest batches take a single launch (route_permute_tiny_kernel).
 // Outputs are identical either way (all integer work is exact and order-independent).
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -26,155 +18,177 @@
 
 namespace grace {
 
-constexpr int SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
-constexpr int SMALL_MAX_KEYS = 256;      // experts and instances the LDS tables hold
-constexpr int SMALL_MAX_PER_WAVE = 256;  // assignments one wavefront walks
+// Index work behind the top-k gate, one launch.  A request's number c among its expert's requests decides its instance (c mod W falls into
+// a candidate's interval of cumulative polling weights) and, as every instance belongs to one expert, also how many earlier rows
+// that instance has: of the requests 0 .. c - 1 those in the candidate's interval, (c / W) w + clamp(c mod W - first, 0, w).  So neither rows per
+// instance nor a second ranking by instance are needed: the gate's histograms of experts give every workgroup the totals (the
+// offsets) and the requests before its own tokens, and one ranking by expert gives instances and positions alike.  Bound by latency: the
+// sums of the histogram rows, then four barriers.  A kernel for the picks and one for the positions -> this one, us: 1000 tokens of 64
+// experts, k = 8 15.2 -> 9.2, 3001, k = 6 13.6 -> 7.9, 7001 of 128, k = 8 19.6 -> 10.7, 32768 of 64, k = 6 28.1 -> 12.3; a single workgroup for both
+// -> this one: 512 tokens, k = 8 11.0 -> 6.4, 1000, k = 2 8.7 -> 7.3.
+//
+// A workgroup takes rows_per_block rows of the histogram, in rounds of PLACE_THREADS assignments.
+constexpr int MAX_KEYS = 256;             // experts and instances that the tables in LDS of the smallest batches hold
+constexpr int PLACE_THREADS = 512, PLACE_WAVES = PLACE_THREADS / 64;
+constexpr int PLACE_LDS_CANDS = 1024;     // candidates of one view that are kept in LDS (else read from memory)
 
-inline bool small_batch(int T, int k, int E, int I) {
-    return T >= 1 && E <= SMALL_MAX_KEYS && I <= SMALL_MAX_KEYS &&
-           ceil_div(T, SMALL_WAVES) * k <= SMALL_MAX_PER_WAVE;
+// Of requests number 0 .. c - 1 of an expert with weight sum W, those that the candidate with the interval [first, first + w) gets.
+__device__ __forceinline__ uint32_t requests_to(uint32_t turns, uint32_t rest, uint32_t first, uint32_t w) {
+    return turns * w + (rest <= first ? 0u : min(rest - first, w));   // c = turns * W + rest
 }
 
-// Bound by latency: a lane's assignments (four at most) are loaded at once and stay in registers, and the candidates of every
-// expert are loaded ahead of the loops, which have no global load left but those of experts with several candidates (a chain
-// of three per group of 64 assignments before: 512 tokens, k = 8 15.1 -> 11.4 us, 1000 tokens, k = 2 9.5 -> 7.5 us).
-__global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
-    int T, int E, int k, const uint32_t *__restrict__ rr_in, uint32_t *__restrict__ rr_out,
-    const int32_t *__restrict__ cand_ptr, const int32_t *__restrict__ cand_g, const uint32_t *__restrict__ cand_cum, int I,
-    int R, int N, const int32_t *__restrict__ rank_ptr, const int32_t *__restrict__ node_first_inst,
-    const int32_t *__restrict__ topk_expert, int32_t *__restrict__ topk_inst, int32_t *__restrict__ expert_count,
-    int32_t *__restrict__ perm_pos, int32_t *__restrict__ perm_src, int32_t *__restrict__ inst_off,
-    int32_t *__restrict__ rank_off, int32_t *__restrict__ node_off) {
-    constexpr int GROUPS = SMALL_MAX_PER_WAVE / 64;
-    __shared__ int32_t ecnt[SMALL_WAVES][SMALL_MAX_KEYS];  // requests per expert of a wavefront, then before it
-    __shared__ int32_t icnt[SMALL_WAVES][SMALL_MAX_KEYS];  // rows per instance of a wavefront, then before it
-    __shared__ int32_t count[SMALL_MAX_KEYS], only[SMALL_MAX_KEYS];   // candidates of an expert; the first one
-    __shared__ uint32_t rr[SMALL_MAX_KEYS];
-    __shared__ int32_t ioff[SMALL_MAX_KEYS + 1];
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tpw = (T + SMALL_WAVES - 1) / SMALL_WAVES;  // tokens per wavefront
-    const int t0 = min(T, wave * tpw), t1 = min(T, t0 + tpw);
-    const int n_w = (t1 - t0) * k;                         // assignments of this wavefront, in order
-    const int64_t a0 = (int64_t)t0 * k;
-    int key[GROUPS];   // expert, then instance, of this lane's assignments; -1: none, or an expert id outside the table
+__global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
+    const int32_t *__restrict__ topk_expert, int64_t n_assign, int E, int k, const int32_t *__restrict__ hist, int nrows, int chunk_tokens,
+    int rows_per_block, const int32_t *__restrict__ super_tot, const uint32_t *__restrict__ rr_in, uint32_t *__restrict__ rr_out,
+    int32_t *__restrict__ expert_count, const int32_t *__restrict__ cand_ptr, const int32_t *__restrict__ cand_g,
+    const uint32_t *__restrict__ cand_cum, int c_first, int n_cand, int I, int R, int N, const int32_t *__restrict__ rank_ptr,
+    const int32_t *__restrict__ node_first_inst, int32_t *__restrict__ topk_inst, int32_t *__restrict__ perm_pos,
+    int32_t *__restrict__ perm_src, int32_t *__restrict__ inst_off, int32_t *__restrict__ rank_off, int32_t *__restrict__ node_off) {
+    __shared__ int32_t all[GRACE_MAX_EXPERTS], cnt[GRACE_MAX_EXPERTS];   // requests of each expert: in all, before the current round
+    __shared__ uint32_t start[GRACE_MAX_EXPERTS];                        // number of its first one (mod W)
+    __shared__ int32_t wcnt[PLACE_WAVES][GRACE_MAX_EXPERTS];             // match set sizes of a wavefront, then requests before it
+    __shared__ int32_t s_ptr[GRACE_MAX_EXPERTS + 1], s_g[PLACE_LDS_CANDS];
+    __shared__ uint32_t s_cum[PLACE_LDS_CANDS];
+    __shared__ int32_t off[GRACE_MAX_INSTANCES + 1], wave_sum[PLACE_WAVES];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, blk = (int)blockIdx.x;
+    const int row0 = blk * rows_per_block;
+    const int64_t per_block = (int64_t)rows_per_block * chunk_tokens * k, a0 = blk * per_block, a1 = min(n_assign, a0 + per_block);
+    // the first round's experts and the candidates are in flight while the histogram rows are summed
+    const int e_first = a0 + tid < a1 ? topk_expert[a0 + tid] : -1;
+    const bool in_lds = n_cand <= PLACE_LDS_CANDS;   // uniform
+    constexpr int CANDS = PLACE_LDS_CANDS / PLACE_THREADS;
+    static_assert(GRACE_MAX_EXPERTS + 1 <= PLACE_THREADS && PLACE_LDS_CANDS % PLACE_THREADS == 0, "one offset, whole entries per thread");
+    const int32_t st_ptr = tid <= E ? cand_ptr[tid] : 0;
+    const uint32_t rr_own = rr_in && tid < E ? rr_in[tid] : 0u;
+    int32_t st_g[CANDS];
+    uint32_t st_cum[CANDS];
 #pragma unroll
-    for (int q = 0; q < GROUPS; ++q) key[q] = q * 64 + lane < n_w ? topk_expert[a0 + q * 64 + lane] : -1;
-    const int e_own = min(tid, E - 1);
-    const int cb = cand_ptr[e_own], ce = cand_ptr[e_own + 1];
-    const uint32_t rr_own = rr_in ? rr_in[e_own] : 0u;
-    for (int i = lane; i < SMALL_MAX_KEYS; i += 64) {
-        ecnt[wave][i] = 0;
-        icnt[wave][i] = 0;
+    for (int q = 0; q < CANDS; ++q) {
+        const int i = tid + q * PLACE_THREADS;
+        st_g[q] = in_lds && i < n_cand ? cand_g[c_first + i] : 0;
+        st_cum[q] = in_lds && i < n_cand ? cand_cum[c_first + i] : 0u;
     }
-    const int ebits = bits_for(E), ibits = bits_for(I);
-    const uint64_t lt = lanemask_lt();
-    // The LDS operations of one wavefront execute in program order, so a counter updated by the last
-    // lane of a match set is seen by the next group of 64 assignments.
-    // ---- 0. this wavefront's experts and their counts ---------------------------------------------
-#pragma unroll
-    for (int q = 0; q < GROUPS; ++q) {
-        if (q * 64 >= n_w) break;   // uniform per wavefront
-        if ((unsigned)key[q] >= (unsigned)E) key[q] = -1;
-        const bool valid = key[q] >= 0;
-        const int e = valid ? key[q] : 0;
-        const uint64_t same = wave_match((uint32_t)e, valid, ebits);
-        if (valid && is_last_of(same)) wave_ctr_add(&ecnt[wave][e], (int32_t)__popcll(same));
-        wave_ctr_fence();
-    }
-    const uint32_t weight_sum = cand_cum[ce - 1];
-    if (tid < E) {
-        count[tid] = ce - cb;
-        only[tid] = cand_g[cb];
-        rr[tid] = rr_own;
-    }
+    for (int i = tid; i < E; i += PLACE_THREADS) all[i] = cnt[i] = 0;
+    for (int i = tid; i <= I; i += PLACE_THREADS) off[i] = 0;
     __syncthreads();
-    // ---- 1. requests of each expert before each wavefront; totals -----------------------------
-    if (tid < E) {
-        int32_t run = 0;
+    if (super_tot) {   // sums of FOLD_SUPER rows each, then the rows behind the last whole one
+        const int s = row0 / FOLD_SUPER;
+        block_add_rows<PLACE_THREADS>(super_tot, 0, (nrows + FOLD_SUPER - 1) / FOLD_SUPER, E, all, tid, cnt, s);
+        block_add_rows<PLACE_THREADS>(hist, s * FOLD_SUPER, row0, E, cnt, tid);
+    } else {
+        block_add_rows<PLACE_THREADS>(hist, 0, nrows, E, all, tid, cnt, row0);
+    }
+    if (tid <= E) s_ptr[tid] = in_lds ? st_ptr - c_first : st_ptr;
+    if (tid < E) start[tid] = rr_own;
 #pragma unroll
-        for (int w = 0; w < SMALL_WAVES; ++w) {
-            const int32_t c = ecnt[w][tid];
-            ecnt[w][tid] = run;
-            run += c;
+    for (int q = 0; q < CANDS; ++q) {
+        const int i = tid + q * PLACE_THREADS;
+        if (in_lds && i < n_cand) {
+            s_g[i] = st_g[q];
+            s_cum[i] = st_cum[q];
         }
-        expert_count[tid] = run;
-        const uint64_t c = (uint64_t)rr_own + (uint64_t)(uint32_t)run;
-        if (rr_out) rr_out[tid] = (c >> 32) ? (uint32_t)(c % weight_sum) : (uint32_t)c % weight_sum;
     }
-    __syncthreads();
-    // ---- 2. replica pick, in assignment order; instance counts ---------------------------------
+    const int32_t *const t_g = in_lds ? s_g : cand_g;
+    const uint32_t *const t_cum = in_lds ? s_cum : cand_cum;
+    // sizes of the match sets of 64 assignments, in the wavefront's row of wcnt (its LDS operations execute in order)
+    const int nbits = bits_for(E);
+    bool valid;
+    int e;
+    uint64_t same;
+    auto match = [&](int e_raw) {
+        valid = (unsigned)e_raw < (unsigned)E;   // -1 past the end
+        e = valid ? e_raw : 0;
+        for (int i = lane; i < E; i += 64) wcnt[wave][i] = 0;
+        same = wave_match((uint32_t)e, valid, nbits);
+        if (valid && is_last_of(same)) wcnt[wave][e] = (int32_t)__popcll(same);
+    };
+    auto scan_waves = [&]() {
+        for (int i = tid; i < E; i += PLACE_THREADS) {
+            int32_t run = cnt[i];
 #pragma unroll
-    for (int q = 0; q < GROUPS; ++q) {
-        if (q * 64 >= n_w) break;
-        const bool valid = key[q] >= 0;
-        const int e = valid ? key[q] : 0;
-        const uint64_t same = wave_match((uint32_t)e, valid, ebits);
-        int g = 0;
-        if (valid) {
-            g = only[e];
-            if (count[e] > 1) {
-                const uint64_t c = (uint64_t)(uint32_t)wave_ctr_load(&ecnt[wave][e]) + (uint32_t)__popcll(same & lt) + (uint64_t)rr[e];
-                g = pick_candidate(c, e, cand_ptr, cand_g, cand_cum);
+            for (int w = 0; w < PLACE_WAVES; ++w) {
+                const int32_t c = wcnt[w][i];
+                wcnt[w][i] = run;
+                run += c;
             }
-            topk_inst[a0 + q * 64 + lane] = g;
-            key[q] = g;
+            cnt[i] = run;
         }
-        if (valid && is_last_of(same)) wave_ctr_add(&ecnt[wave][e], (int32_t)__popcll(same));
-        const uint64_t same_g = wave_match((uint32_t)g, valid, ibits);
-        if (valid && is_last_of(same_g)) wave_ctr_add(&icnt[wave][g], (int32_t)__popcll(same_g));
-        wave_ctr_fence();
-    }
+    };
+    match(e_first);
     __syncthreads();
-    // ---- 3. rows of each instance before each wavefront; offsets --------------------------------
-    int32_t total = 0;
-    if (tid < I) {
-#pragma unroll
-        for (int w = 0; w < SMALL_WAVES; ++w) {
-            const int32_t c = icnt[w][tid];
-            icnt[w][tid] = total;
-            total += c;
+    // ---- rows of every instance: several threads per expert, a candidate each
+    const int subs = PLACE_THREADS / E, e_own = tid / subs;
+    uint32_t first_number = 0;
+    if (e_own < E) {
+        const int cb = s_ptr[e_own], ce = s_ptr[e_own + 1];
+        const uint32_t W = t_cum[ce - 1];
+        first_number = start[e_own] % W;
+        const uint32_t end = first_number + (uint32_t)all[e_own];   // < 2^31 + 2^26
+        const uint32_t turns = end / W, rest = end % W;
+        for (int i = cb + tid % subs; i < ce; i += subs) {
+            const uint32_t lo = i > cb ? t_cum[i - 1] : 0u, w = t_cum[i] - lo;
+            off[t_g[i]] = (int32_t)(requests_to(turns, rest, lo, w) - requests_to(0u, first_number, lo, w));
+        }
+        if (blk == 0 && tid % subs == 0) {
+            expert_count[e_own] = all[e_own];
+            if (rr_out) rr_out[e_own] = rest;
         }
     }
-    if (tid < SMALL_MAX_KEYS) ioff[tid] = total;  // totals, scanned below (zero for ids >= I)
+    scan_waves();
     __syncthreads();
-    if (wave == 0) {
-        // exclusive scan over the ids: each lane owns four consecutive ids
-        int32_t c[4], s = 0;
+    // ---- offsets: exclusive scan over the instances, consecutive ones per thread
+    if (e_own < E && tid % subs == 0) start[e_own] = first_number;
+    const int per = (I + PLACE_THREADS - 1) / PLACE_THREADS, i0 = min(I, tid * per), i1 = min(I, i0 + per);
+    int32_t sum = 0;
+    for (int i = i0; i < i1; ++i) sum += off[i];
+    const int32_t incl = wave_scan_add(sum);
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int32_t run = incl - sum;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            c[q] = ioff[lane * 4 + q];
-            s += c[q];
-        }
-        const int32_t incl = wave_scan_add(s);
-        int32_t run = incl - s;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            ioff[lane * 4 + q] = run;
-            run += c[q];
-        }
-        if (lane == 63) ioff[SMALL_MAX_KEYS] = incl;  // grand total = offset of every id >= I
+    for (int w = 0; w < PLACE_WAVES; ++w) run += w < wave ? wave_sum[w] : 0;
+    for (int i = i0; i < i1; ++i) {
+        const int32_t c = off[i];
+        off[i] = run;
+        run += c;
     }
+    if (tid == PLACE_THREADS - 1) off[I] = run;
     __syncthreads();
-    for (int i = tid; i <= I; i += SMALL_THREADS) inst_off[i] = ioff[i];
-    for (int r = tid; r <= R; r += SMALL_THREADS) rank_off[r] = ioff[rank_ptr[r]];
-    for (int n = tid; n <= N; n += SMALL_THREADS) node_off[n] = ioff[node_first_inst[n]];
-    // ---- 4. positions ---------------------------------------------------------------------------
-#pragma unroll
-    for (int q = 0; q < GROUPS; ++q) {
-        if (q * 64 >= n_w) break;
-        const int64_t a = a0 + q * 64 + lane;
-        const bool valid = key[q] >= 0;
-        const int g = valid ? key[q] : 0;
-        const uint64_t same = wave_match((uint32_t)g, valid, ibits);
+    if (blk == 0) {
+        for (int i = tid; i <= I; i += PLACE_THREADS) inst_off[i] = off[i];
+        for (int r = tid; r <= R; r += PLACE_THREADS) rank_off[r] = off[rank_ptr[r]];
+        for (int n = tid; n <= N; n += PLACE_THREADS) node_off[n] = off[node_first_inst[n]];
+    }
+    // ---- instances and positions
+    const uint64_t lt = lanemask_lt();
+    for (int64_t b0 = a0;;) {
+        const int64_t a = b0 + tid;
         if (valid) {
-            const int32_t pos = ioff[g] + wave_ctr_load(&icnt[wave][g]) + (int32_t)__popcll(same & lt);
-            perm_pos[a] = pos;
-            perm_src[pos] = (int32_t)a;
-        } else if (q * 64 + lane < n_w) {
-            perm_pos[a] = -1;  // expert id outside the table: no row
+            const int cb = s_ptr[e], ce = s_ptr[e + 1];
+            const uint32_t from = start[e], W = t_cum[ce - 1], c = from + (uint32_t)wcnt[wave][e] + (uint32_t)__popcll(same & lt);
+            const uint32_t turns = c / W, rest = c - turns * W;
+            uint32_t lo = 0, hi = t_cum[cb];
+            int s = cb;
+            while (s < ce - 1 && hi <= rest) {
+                lo = hi;
+                hi = t_cum[++s];
+            }
+            const int g = t_g[s];
+            const int64_t pos = (int64_t)off[g] + (int32_t)(requests_to(turns, rest, lo, hi - lo) - requests_to(0u, from, lo, hi - lo));
+            topk_inst[a] = g;
+            const bool inside = pos >= 0 && pos < n_assign;   // (always, unless the gate left an entry unwritten: logits that are all NaN)
+            perm_pos[a] = inside ? (int32_t)pos : -1;
+            if (inside) perm_src[pos] = (int32_t)a;
+        } else if (a < a1) {
+            perm_pos[a] = -1;   // expert id outside the table: no row
         }
-        if (valid && is_last_of(same)) wave_ctr_add(&icnt[wave][g], (int32_t)__popcll(same));
-        wave_ctr_fence();
+        b0 += PLACE_THREADS;
+        if (b0 >= a1) break;
+        __syncthreads();   // wcnt has been read
+        match(b0 + tid < a1 ? topk_expert[b0 + tid] : -1);
+        __syncthreads();
+        scan_waves();
+        __syncthreads();
     }
 }
 
@@ -194,8 +208,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(
 constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
 constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_TOP2 = 16 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;
 inline bool tiny_batch(int T, int k, int E, int I) {
-    return T >= 1 && T <= (E > 64 ? TINY_MAX_T_WIDE : k > 2 ? TINY_MAX_T : TINY_MAX_T_TOP2) && (int64_t)T * k <= TINY_MAX_ASG && E <= SMALL_MAX_KEYS &&
-           I <= SMALL_MAX_KEYS;
+    return T >= 1 && T <= (E > 64 ? TINY_MAX_T_WIDE : k > 2 ? TINY_MAX_T : TINY_MAX_T_TOP2) && (int64_t)T * k <= TINY_MAX_ASG && E <= MAX_KEYS &&
+           I <= MAX_KEYS;
 }
 
 // VPL: experts per lane where a wavefront takes a token; ROWS: a wavefront takes four tokens at a time.  PASSES: how often.
@@ -208,12 +222,12 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
     int32_t *__restrict__ topk_inst, int32_t *__restrict__ expert_count, int32_t *__restrict__ perm_pos,
     int32_t *__restrict__ perm_src, int32_t *__restrict__ inst_off, int32_t *__restrict__ rank_off,
     int32_t *__restrict__ node_off, const uint4 *__restrict__ x, int row_vec, uint4 *__restrict__ xp) {
-    __shared__ int32_t ecnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // requests per expert of a wavefront, then before it
-    __shared__ int32_t icnt[TINY_MAX_WAVES][SMALL_MAX_KEYS];   // rows per instance of a wavefront, then before it
+    __shared__ int32_t ecnt[TINY_MAX_WAVES][MAX_KEYS];   // requests per expert of a wavefront, then before it
+    __shared__ int32_t icnt[TINY_MAX_WAVES][MAX_KEYS];   // rows per instance of a wavefront, then before it
     __shared__ int32_t asg[TINY_MAX_ASG], where[TINY_MAX_ASG]; // expert of every assignment; its position
-    __shared__ int32_t count[SMALL_MAX_KEYS], only[SMALL_MAX_KEYS];   // candidates of an expert; the first one
-    __shared__ uint32_t weight_sum[SMALL_MAX_KEYS], rr[SMALL_MAX_KEYS];
-    __shared__ int32_t ioff[SMALL_MAX_KEYS + 1];
+    __shared__ int32_t count[MAX_KEYS], only[MAX_KEYS];   // candidates of an expert; the first one
+    __shared__ uint32_t weight_sum[MAX_KEYS], rr[MAX_KEYS];
+    __shared__ int32_t ioff[MAX_KEYS + 1];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, threads = (int)blockDim.x, waves = threads >> 6;
     const int n = T * k, groups = (n + 63) >> 6, me = (int)blockIdx.x;   // groups <= waves; a workgroup per token
     // ---- loads ahead: this wavefront's logits, the experts' candidates, the row to move
@@ -242,7 +256,7 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
         own[v] = (wave == waves - 1 && e < E) ? logits[(size_t)me * E + e] : -INFINITY;
     }
     for (int i = tid; i < n; i += threads) asg[i] = -1;
-    for (int i = lane; i < SMALL_MAX_KEYS; i += 64) {
+    for (int i = lane; i < MAX_KEYS; i += 64) {
         ecnt[wave][i] = 0;
         icnt[wave][i] = 0;
     }
@@ -313,7 +327,7 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
         if (valid && is_last_of(same)) icnt[wave][g] = (int32_t)__popcll(same);
     }
     __syncthreads();
-    if (tid < SMALL_MAX_KEYS) {
+    if (tid < MAX_KEYS) {
         int32_t total = 0;
         for (int w = 0; w < groups; ++w) {
             const int32_t c = icnt[w][tid];
@@ -337,7 +351,7 @@ __global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel
             ioff[lane * 4 + q] = run;
             run += c[q];
         }
-        if (lane == 63) ioff[SMALL_MAX_KEYS] = incl;
+        if (lane == 63) ioff[MAX_KEYS] = incl;
     }
     __syncthreads();
     // ---- positions, offsets, rows
@@ -399,32 +413,8 @@ static int route_permute_impl(const grace_table *table, int32_t local_rank, grac
                              int32_t *inst_off, int32_t *rank_off, int32_t *node_off, void *xp, void *ws, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     int rc;
-    // the shared-histogram path counts with 32-bit indices; sizes beyond that take the two calls
-    const bool hist_fits = ceil_div((int64_t)T * k, PERM_CHUNK) * table->I <= (int64_t)1 << 30;
-    if (T == 0 || !hist_fits) {
-        rc = grace_route(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight,
-                         topk_inst, expert_count, ws, stream);
-        if (rc != GRACE_OK) return rc;
-        return grace_permute(table, topk_inst, T, k, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws,
-                             stream);
-    }
-    if (!small_batch(T, k, E, table->I)) {
-        const int I = table->I;
-        const int64_t n = (int64_t)T * k;
-        const int nchunks = (int)ceil_div(n, PERM_CHUNK);
-        int32_t *phist = (int32_t *)((char *)ws + fused_perm_ws_offset(T, E));
-        int32_t *pbase = (int32_t *)((char *)phist + align_up((size_t)nchunks * I * 4, 256));
-        rc = launch_route(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight,
-                          topk_inst, expert_count, ws, phist, st);
-        if (rc != GRACE_OK) return rc;
-        const char *failed = stable_sort_launch(table, topk_inst, n, I, 1, phist, pbase, table->R, table->N, table->d_rank_ptr,
-                                                table->d_node_first_inst, inst_off, rank_off, node_off, perm_pos, perm_src,
-                                                st, /*hist_ready=*/true);
-        if (failed) return fail(GRACE_EHIP, "route_permute: launch of %s failed", failed);
-        if (x) return launch_scatter_rows(x, T, k, d, dt, perm_pos, xp, st);
-        return GRACE_OK;
-    }
-    const int32_t *cand_ptr = table->d_cand_ptr + (size_t)(policy == GRACE_POLICY_WRR ? table->R : local_rank) * E;
+    const int view = policy == GRACE_POLICY_WRR ? table->R : local_rank;
+    const int32_t *cand_ptr = table->d_cand_ptr + (size_t)view * E;
     if (tiny_batch(T, k, E, table->I)) {
         const int row_vec = x ? (int)((int64_t)d * (dt == GRACE_F32 ? 4 : 2) / 16) : 1;
         int waves = 4;   // a thread per expert and instance, a wavefront per 64 assignments and, up to the most, per token or four
@@ -452,13 +442,30 @@ static int route_permute_impl(const grace_table *table, int32_t local_rank, grac
         GRACE_LAUNCH_CHECK("route_permute_tiny_kernel");
         return GRACE_OK;
     }
-    rc = launch_topk(logits, T, E, k, renorm, topk_expert, topk_weight, (int32_t *)ws, nullptr, 0, st);
+    const int chunk_tokens = route_chunk_tokens(T), nrows = (int)ceil_div(T, chunk_tokens), mode = fold_mode(table, nrows, E);
+    if (mode == 0) {   // no tokens, or so many that the histograms are scanned by launches of their own
+        rc = grace_route(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight,
+                         topk_inst, expert_count, ws, stream);
+        if (rc != GRACE_OK) return rc;
+        return grace_permute(table, topk_inst, T, k, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws,
+                             stream);
+    }
+    int32_t *hist = (int32_t *)ws;
+    rc = launch_topk(logits, T, E, k, renorm, topk_expert, topk_weight, hist, st);
     if (rc != GRACE_OK) return rc;
-    dispatch_small_kernel<<<1, SMALL_THREADS, 0, st>>>(T, E, k, rr_in, rr_out, cand_ptr, table->d_cand_g, table->d_cand_cum,
-                                                      table->I, table->R, table->N, table->d_rank_ptr,
-                                                      table->d_node_first_inst, topk_expert, topk_inst, expert_count,
-                                                      perm_pos, perm_src, inst_off, rank_off, node_off);
-    GRACE_LAUNCH_CHECK("dispatch_small_kernel");
+    const int32_t *super_tot = nullptr;
+    if (mode == 2) {
+        int32_t *sums = (int32_t *)((char *)ws + align_up((size_t)nrows * E * 4, 256));
+        super_sum_kernel<<<(unsigned)ceil_div(nrows, FOLD_SUPER), SUPER_THREADS, 0, st>>>(hist, nrows, E, sums);
+        GRACE_LAUNCH_CHECK("super_sum_kernel");
+        super_tot = sums;
+    }
+    const int rows_per_block = std::max(1, PLACE_THREADS / (k * chunk_tokens));
+    place_kernel<<<(unsigned)ceil_div(nrows, rows_per_block), PLACE_THREADS, 0, st>>>(
+        topk_expert, (int64_t)T * k, E, k, hist, nrows, chunk_tokens, rows_per_block, super_tot, rr_in, rr_out, expert_count, cand_ptr,
+        table->d_cand_g, table->d_cand_cum, table->cand_view[view], table->cand_view[view + 1] - table->cand_view[view], table->I, table->R,
+        table->N, table->d_rank_ptr, table->d_node_first_inst, topk_inst, perm_pos, perm_src, inst_off, rank_off, node_off);
+    GRACE_LAUNCH_CHECK("place_kernel");
     if (x) return launch_scatter_rows(x, T, k, d, dt, perm_pos, xp, st);
     return GRACE_OK;
 }

@@ -214,15 +214,13 @@ def run_fused(wl, pl, k, local_rank, rr_in=None, renorm=1, with_rows=True, polic
 
 
 @pytest.mark.parametrize("name,T,local_rank", [
-    ("tiny", None, 0), ("tiny", 1, 1), ("tiny", 15, 3), ("tiny", 17, 2), ("tiny", 2048, 0),   # 2048: single kernel at k=2
+    ("tiny", None, 0), ("tiny", 1, 1), ("tiny", 15, 3), ("tiny", 17, 2), ("tiny", 2048, 0),
     ("olmoe_decode64", None, 0), ("olmoe_decode512", None, 0), ("olmoe", 100, 2), ("olmoe", 513, 1),
     ("qwen", 200, 5), ("dsv2lite", 300, 17), ("mixtral", 1000, 6),
-    # larger batches: the pick kernel also fills the permutation's chunk histograms
     ("olmoe", None, 0), ("qwen", 5001, 5), ("dsv2lite", None, 17), ("mixtral", None, 6), ("qwen3moe", 3000, 3),
 ])
 def test_route_permute_single_call_bit_exact(name, T, local_rank):
-    """grace_route_permute gives the outputs of the two calls, on the single-workgroup path
-    (decode-sized batches) and on the path for larger batches alike."""
+    """grace_route_permute gives the outputs of the two calls, in one launch (the smallest batches) and in three alike."""
     cfg = CONFIGS[name]
     wl = make_workload(cfg, T=T)
     ref = oracle.route_permute(wl.logits, wl.placement, cfg.k, local_rank)
@@ -306,6 +304,33 @@ def test_route_large_batches_few_lanes_per_token(E, k, T, renorm):
     ref = oracle.route_permute(logits, pl, k, 4, renorm=renorm)
     _, g = run_route_permute(wl, pl, k, 4, renorm=renorm)
     check_route_permute(g, ref, wl, k)
+
+
+@pytest.mark.parametrize("E,k,T,R,spread,policy,limits", [
+    (5, 2, 257, 6, 3, 0, None),          # hardly any experts; one assignment in the last workgroup's rows
+    (64, 64, 130, 32, 32, 1, None),      # 1024 assignments per histogram row: two rounds; 2048 candidates, read from memory
+    (256, 3, 703, 16, 16, 1, None),      # as many instances as a table holds: eight per thread in the scan
+    (33, 1, 8193, 6, 2, 0, None),        # k = 1, rows of 32 tokens
+    (96, 7, 16385, 6, 3, 1, None),       # rows of 64 tokens, 448 assignments a workgroup
+    (40, 3, 3000, 6, 3, 0, (0, -1)),     # two-level sums
+    (40, 3, 3000, 6, 3, 0, (0, 0)),      # the two calls
+])
+def test_route_permute_positions_from_request_numbers(E, k, T, R, spread, policy, limits):
+    """Past the smallest batches one kernel takes instances and positions from the request numbers: polling weights up to
+    the largest, counters carried over from anywhere in 32 bits, ties."""
+    rng = np.random.default_rng(E * k + T)
+    hosts = [sorted(rng.choice(R, size=spread if spread >= 16 else rng.integers(1, spread + 1), replace=False).tolist()) for _ in range(E)]
+    inst_ptr = np.concatenate([[0], np.cumsum([len(h) for h in hosts])]).astype(np.int32)
+    weight = rng.integers(1, 9, size=R).astype(np.uint32)
+    weight[::4] = 65535
+    pl = SimpleNamespace(E=E, R=R, N=2, rank_node=(np.arange(R) >= R // 2).astype(np.int32), poll_weight=weight, inst_ptr=inst_ptr,
+                         inst_rank=np.concatenate(hosts).astype(np.int32))
+    logits = np.round(rng.standard_normal((T, E)) * 4).astype(np.float32) / 4
+    rr_in = rng.integers(0, 2 ** 32, size=E, dtype=np.uint64).astype(np.uint32)
+    rr_in[:4] = [0, 2 ** 32 - 1, 2 ** 31, 65535]
+    wl = SimpleNamespace(logits=logits, x=rng.standard_normal((T, 8)).astype(np.float32))
+    ref = oracle.route_permute(logits, pl, k, 1, rr_in=rr_in, policy=policy)
+    check_route_permute(run_fused(wl, pl, k, 1, rr_in=rr_in, policy=policy, fold_limits=limits), ref, wl, k)
 
 
 def test_empty_call_and_argument_errors():
