@@ -29,6 +29,7 @@ ROTATE_BELOW_BYTES = 256 << 20   # Infinity Cache: smaller working sets are also
 
 KERNEL_OF_STAGE = {
     "ffn_up": "gemm_bf16_persist_kernel<true, *, EXPERTS> (grouped gate+up projection, fused SwiGLU)",
+    "dispatch_ffn_up": "tiny_up_kernel (grouped gate+up projection, fused SwiGLU, with the dispatch in the same launch)",
     "ffn_down": "gemm_bf16_persist_kernel<false, *, EXPERTS> (grouped down projection)",
     "shared_up": "gemm_bf16_persist_kernel<true, 1, SHARED> (shared experts' gate+up projection, fused SwiGLU; carries the row scatter)",
     "shared_down": "gemm_bf16_persist_kernel<false, 1, SHARED> (shared experts' down projection)",
@@ -170,7 +171,8 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
     bytes_combine = m_loc * d * el + T * d * el * (2 if sh is not None else 1) + 8 * T * k
     # with shared experts the dispatch call builds only the index arrays; the row scatter rides on the shared gate+up
     # projection's launch where the large tiles take that, else it is a launch of its own
-    fused_scatter = bool(getattr(layer, "fuse_scatter", False)) and sh is not None
+    joined = bool(getattr(layer, "join_dispatch", False))   # smallest batches: dispatch and gate+up projection are one launch
+    fused_scatter = bool(getattr(layer, "fuse_scatter", False)) and sh is not None and not joined
     kernels = {}
     for stage, up, n_sh in (("ffn_up", True, 0), ("ffn_down", False, 0), ("shared_up", True, cfg.n_shared), ("shared_down", False, cfg.n_shared)):
         if not stage.startswith("shared") or n_sh:
@@ -182,6 +184,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
     # algorithmic work per launch of the kernel behind each call: (bound, amount, unit scale, peak)
     work = {
         "ffn_up": ("mfma", 4.0 * d * f * m_loc), "ffn_down": ("mfma", 2.0 * d * f * m_loc),
+        "dispatch_ffn_up": ("mfma", 4.0 * d * f * m_loc),
         "shared_up": ("mfma", 4.0 * d * f * cfg.n_shared * T), "shared_down": ("mfma", 2.0 * d * f * cfg.n_shared * T),
         "combine": ("hbm", float(bytes_combine)), "route_permute": ("hbm", float(bytes_dispatch)),
     }
@@ -299,7 +302,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
         if s in work:
             a, p, u = achieved(s, stage_ms[s])
             stages_achieved[s] = {"achieved": a, "unit": u, "frac": a / p}
-    if not fused_scatter:
+    if not fused_scatter and not joined:
         t_hbm = stage_ms.get("combine", 0.0) + stage_ms.get("route_permute", 0.0)
         stages_achieved["route_permute_combine"] = {
             "achieved": (bytes_route + bytes_permute + bytes_combine) / (t_hbm * 1e-3) / 1e9, "unit": "GB/s",
@@ -313,7 +316,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
                    "local_rows": m_loc, "local_slots": int(len(experts)),
                    "rows_per_slot_min_max": [int(seg.min()), int(seg.max())] if len(seg) else [0, 0],
                    "n_shared": cfg.n_shared, "working_set_MB": ws_bytes / 1e6,
-                   "row_scatter": "carried by the shared gate+up projection's launch" if carries_rows else
+                   "row_scatter": "in the launch of dispatch and gate+up projection" if joined else "carried by the shared gate+up projection's launch" if carries_rows else
                    "carried by the experts' gate+up projection's launch" if gathers_rows else
                    "a launch of its own ahead of the shared gate+up projection" if fused_scatter else "in the dispatch call"},
         "roofline": {"kernel": KERNEL_OF_STAGE[dominant] if kernels.get(dominant, "persist") == "persist"

@@ -188,15 +188,11 @@ int grace_permute_rows(const void *x, const int32_t *perm_pos, int32_t T, int32_
 /* ---- grace_route_permute: grace_route then grace_permute in one call ----------
  * Same arguments, outputs (bit for bit) and errors as grace_route (Section 3,
  * Section 4.3, Algorithms 3 and 4) followed by grace_permute (Section 5) on its
- * topk_inst, with fewer kernel launches.  Decode-sized batches, which are bound
+ * topk_inst, with fewer kernel launches.  The smallest batches, which are bound
  * by launch latency, take one launch (T <= 96, 256 with k <= 2, 32 with more than
- * 64 experts; T * k <= 1024), or the top-k kernel, one single-workgroup kernel
- * and the row scatter instead of five launches (ceil(T / 16) * k <= 256); both
- * with E <= 256 and at most 256 instances in the table.
- * For every other size the replica pick also produces the histograms the
- * permutation starts from, which saves one launch.  The workspace holds the
- * routing and the permutation histograms side by side during this call
- * (grace_workspace_bytes covers it).
+ * 64 experts; T * k <= 1024; E <= 256 and at most 256 instances in the table);
+ * others three instead of five: the top-k kernel, one kernel for the picks,
+ * offsets and positions, and the row scatter.
  */
 int grace_route_permute(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T,
                         int32_t E, int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out,
@@ -315,6 +311,25 @@ int grace_expert_ffn_up_share(const grace_table *table, int32_t rank, const void
 int grace_expert_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k,
                                 int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state,
                                 void *ws, void *stream);
+
+/* grace_route_permute followed by grace_expert_ffn_up_share (rank = local_rank) as one call, and the down projection that belongs
+ * to it: for the smallest batches, where the weight-streaming kernel takes the projection (grace_dispatch_joins_ffn), the dispatch and the
+ * projection are one launch that lays the hidden activation out in ws by slots (row j of slot s at row s * T + j of [S * T, f]), which
+ * _down_share then expects; the two launches and their layout elsewhere.  The same sizes, table and rank in both calls.  Same
+ * results as grace_route_permute, grace_expert_ffn_up_share and grace_expert_ffn_down_share, bit for bit.
+ * DEVICE: as for these; x is not NULL (unless T == 0). */
+int grace_dispatch_ffn_up_share(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T, int32_t E,
+                                int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out, int32_t *topk_expert,
+                                float *topk_weight, int32_t *topk_inst, int32_t *expert_count, const void *x, int32_t d, int32_t f,
+                                grace_dtype dt, int32_t *perm_pos, int32_t *perm_src, int32_t *inst_off, int32_t *rank_off,
+                                int32_t *node_off, void *xp, const void *w_gate, const void *w_up, int32_t *state, void *ws,
+                                void *stream);
+int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k, int32_t d,
+                                  int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state, void *ws, void *stream);
+/* Whether one launch does the dispatch and the gate+up projection of these sizes.  n_cu: compute units (0: of the current device;
+ * no device is touched otherwise).  HOST output. */
+int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt,
+                             int32_t n_cu, int32_t *joined);
 
 /* grace_permute_rows followed by grace_expert_ffn_up_share on the rows it has moved, as one call: for prefill batches, where the
  * large-tile kernel takes the projection, that launch reads the rank's rows from x and moves all rows to xp as it runs

@@ -16,6 +16,9 @@ from .binding import (  # noqa: F401
     GraceTable,
     grace_combine,
     grace_combine_share,
+    grace_dispatch_ffn_down_share,
+    grace_dispatch_ffn_up_share,
+    grace_dispatch_joins_ffn,
     grace_expert_ffn,
     grace_expert_ffn_down,
     grace_expert_ffn_down_fresh,

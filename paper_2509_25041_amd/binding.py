@@ -23,6 +23,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_expert_ffn_down", "grace_expert_ffn_down_fresh", "grace_expert_ffn_up_share", "grace_expert_ffn_up_share_scatter", "grace_expert_ffn_down_share",
            "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_combine_share", "grace_mfma_sustained",
            "grace_ffn_kernel", "grace_ffn_carries_rows",
+           "grace_dispatch_ffn_up_share", "grace_dispatch_ffn_down_share", "grace_dispatch_joins_ffn",
            "grace_last_error")
 
 _lib: Optional[C.CDLL] = None
@@ -84,6 +85,10 @@ def load_library() -> C.CDLL:
     lib.grace_combine_share.argtypes = [vp, vp, vp, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_mfma_sustained.argtypes = [i32, i32, C.POINTER(C.c_double), vp]
     lib.grace_ffn_kernel.argtypes = [i32] * 8 + [C.c_int, i32, C.POINTER(i32), C.POINTER(C.c_int64)]
+    lib.grace_dispatch_ffn_up_share.argtypes = [vp, i32, C.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, i32, i32, C.c_int, vp, vp, vp,
+                                                vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.grace_dispatch_ffn_down_share.argtypes = lib.grace_expert_ffn_down_share.argtypes
+    lib.grace_dispatch_joins_ffn.argtypes = [vp, i32, i32, i32, i32, i32, C.c_int, i32, vp]
     lib.grace_ffn_carries_rows.argtypes = [i32, i32, i32, i32, i32, i32, i32, C.c_int, i32, vp]
     for name in EXPORTS:
         if name not in ("grace_last_error", "grace_workspace_bytes"):
@@ -431,6 +436,50 @@ def grace_expert_ffn_down_share(table: GraceTable, rank: int, inst_off: torch.Te
     S, d, f = w_down.shape
     _check(load_library().grace_expert_ffn_down_share(table.handle, rank, _dp(inst_off), T, k, d, f, _dtype_code(y),
                                                       _dp(w_down) if S else None, _dp(y), _dp(state), _dp(ws), _stream()))
+
+
+def grace_dispatch_ffn_up_share(table: GraceTable, local_rank: int, logits: torch.Tensor, k: int, x: torch.Tensor, w_gate: torch.Tensor,
+                                w_up: torch.Tensor, state: torch.Tensor, ws: torch.Tensor, renorm: int = 1,
+                                rr_in: Optional[torch.Tensor] = None, rr_out: Optional[torch.Tensor] = None,
+                                policy: int = GRACE_POLICY_TAR):
+    """grace_route_permute and grace_expert_ffn_up_share of the local rank as one call (one launch for the smallest batches); its
+    down projection is grace_dispatch_ffn_down_share.  -> what grace_route_permute returns; see grace_moe.h."""
+    _need(state, "state", torch.int32, SHARE_STATE_INTS)
+    T, E = logits.shape
+    S, f, d = w_gate.shape
+    if logits.dtype != torch.float32:
+        raise ValueError("logits must be float32")
+    if tuple(x.shape) != (T, d) or tuple(w_up.shape) != (S, f, d) or w_gate.dtype != x.dtype or w_up.dtype != x.dtype:
+        raise ValueError("x must be [T,d], w_gate and w_up [S,f,d], of one dtype")
+    dt, dev = _dtype_code(x), logits.device
+    _ws(ws, grace_workspace_bytes(T, E, max(k, 1), table.I, d, f, 0, dt), dev)
+    i32 = dict(dtype=torch.int32, device=dev)
+    te, tw = torch.empty((T, k), **i32), torch.empty((T, k), dtype=torch.float32, device=dev)
+    ti, cnt = torch.empty((T, k), **i32), torch.empty((E,), **i32)
+    pos, src = torch.empty(T * k, **i32), torch.empty(T * k, **i32)
+    ioff, roff, noff = torch.empty(table.I + 1, **i32), torch.empty(table.R + 1, **i32), torch.empty(table.N + 1, **i32)
+    xp = torch.empty((T * k, d), dtype=x.dtype, device=dev)
+    _check(load_library().grace_dispatch_ffn_up_share(
+        table.handle, local_rank, policy, _dp(logits), T, E, k, renorm, _dp(rr_in), _dp(rr_out), _dp(te), _dp(tw), _dp(ti), _dp(cnt), _dp(x), d,
+        f, dt, _dp(pos), _dp(src), _dp(ioff), _dp(roff), _dp(noff), _dp(xp), _dp(w_gate) if S else None, _dp(w_up) if S else None,
+        _dp(state), _dp(ws), _stream()))
+    return (te, tw, ti, cnt), (pos, src, ioff, roff, noff, xp)
+
+
+def grace_dispatch_ffn_down_share(table: GraceTable, rank: int, inst_off: torch.Tensor, T: int, k: int, w_down: torch.Tensor,
+                                  y: torch.Tensor, state: torch.Tensor, ws: torch.Tensor) -> None:
+    """grace_expert_ffn_down_share behind grace_dispatch_ffn_up_share; see grace_moe.h."""
+    _need(state, "state", torch.int32, SHARE_STATE_INTS)
+    S, d, f = w_down.shape
+    _check(load_library().grace_dispatch_ffn_down_share(table.handle, rank, _dp(inst_off), T, k, d, f, _dtype_code(y),
+                                                        _dp(w_down) if S else None, _dp(y), _dp(state), _dp(ws), _stream()))
+
+
+def grace_dispatch_joins_ffn(table: GraceTable, local_rank: int, T: int, k: int, d: int, f: int, dt: int = GRACE_BF16, n_cu: int = 0) -> bool:
+    """Does one launch do the dispatch and the gate+up projection (see grace_moe.h)?"""
+    joined = C.c_int32()
+    _check(load_library().grace_dispatch_joins_ffn(table.handle, local_rank, T, k, d, f, dt, n_cu, C.byref(joined)))
+    return bool(joined.value)
 
 
 def grace_shared_ffn(x: torch.Tensor, w_gate: torch.Tensor, w_up: torch.Tensor, w_down: torch.Tensor,

@@ -76,6 +76,10 @@ int launch_topk(const float *logits, int T, int E, int k, int renorm, int32_t *t
 size_t fused_perm_ws_offset(int32_t T, int32_t E);
 // Workspace bytes of routing + permutation as one call (both sets of histograms and their prefix sums).
 size_t route_permute_ws_bytes(int32_t T, int32_t E, int32_t k, int32_t I);
+// Hidden activation with T rows for each of S slots, as the smallest batches' joined launches lay it out where S * T rows are no more
+// than T * k or fit these bytes.
+constexpr size_t SLOT_ROWS_MOST = (size_t)32 << 20;
+constexpr int SLOT_ROWS_MAX_T = 256;
 int launch_scatter_rows(const void *x, int T, int k, int d, grace_dtype dt, const int32_t *perm_pos, void *xp,
                         hipStream_t st);
 
@@ -102,6 +106,8 @@ struct grace_table {
     const int32_t *d_node_first_inst = nullptr;  // [N+1] first instance id of each node (I at the end)
     const int32_t *d_inst_rank = nullptr;        // [I] hosting rank of each instance id
     const int32_t *d_rank_node = nullptr;        // [R]
+    // [I] of each instance id: expert; first and end of its interval of polling weights among all instances of the expert; their sum
+    const uint4 *d_inst_span = nullptr;
     // switch points of the index kernels' prefix-count algorithms for calls with this table
     int fold_one_level = grace::FOLD_ONE_LEVEL_DEFAULT, fold_two_level = grace::FOLD_TWO_LEVEL_DEFAULT;
 };

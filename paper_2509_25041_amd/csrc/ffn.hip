@@ -18,6 +18,7 @@
 
 #include "bf16.h"
 #include "common.h"
+#include "ffn_tiny.h"
 #include "gemm_bf16_generic.h"
 #include "gemm_bf16_mid.h"
 #include "gemm_bf16_persist.h"
@@ -416,6 +417,34 @@ static Rows expert_rows(int S, int I, int32_t T, int32_t k) {
 }
 static Rows shared_rows(int32_t T) { return {T, T, 1, true, T, T}; }
 
+// Smallest batches: one launch for the dispatch and the experts' gate+up projection (ffn_tiny.hip), whose hidden activation the down
+// projection then finds slot by slot.
+static bool joins_dispatch(const grace_table *table, int32_t rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt, int n_cu) {
+    const int S = table->rank_ptr[rank + 1] - table->rank_ptr[rank], el = dt == GRACE_F32 ? 4 : 2;
+    if (S < 1 || T > SLOT_ROWS_MAX_T || !tiny_batch(T, k, table->E, table->I)) return false;
+    if (S > k && (size_t)T * S * f * el > SLOT_ROWS_MOST) return false;
+    const GemmArgs up = expert_shape(true, S, d, f), dn = expert_shape(false, S, d, f);
+    const Rows rows = expert_rows(S, table->I, T, k);
+    if ((up.K + T * up.lda) * el >= (int64_t)NO_DATA) return false;   // offsets of any token from the first
+    const Route r = route_gemm<false>(dn, dt, rows, n_cu);
+    if (r != Route::STREAM && !(r == Route::MID && dt == GRACE_BF16)) return false;
+    const Route u = route_gemm<true>(up, dt, rows, n_cu);
+    Grid l = grid_of<true>(u, up, dt, rows, n_cu);
+    if (u == Route::MID && dt == GRACE_BF16) {
+        if (T > mid::BM) return false;   // one piece per slot
+        l.groups = tiny_up_mid_blocks(S, up.K, (up.N + mid::Shape<true>::BN - 1) / mid::Shape<true>::BN, n_cu);
+        if (l.groups == 0) return false;
+    } else if (u == Route::STREAM) {
+        const int64_t pieces = stream_pieces<4>(rows) && dt == GRACE_F32 ? (T + strm::MAX_ROWS - 1) / strm::MAX_ROWS : 1;
+        l.groups = (int64_t)S * ((up.N + strm::Shape<true>::COLS - 1) / strm::Shape<true>::COLS) * pieces;
+        if (T > 32 && l.groups > (pieces > 1 ? 2 : 4) * (int64_t)n_cu) return false;
+    } else {
+        return false;
+    }
+    l.groups += T + 8;
+    return launchable(l);
+}
+
 static int check_ffn_shapes(const char *who, int32_t d, int32_t f, grace_dtype dt) {
     if (dt != GRACE_F32 && dt != GRACE_BF16) return fail(GRACE_EINVAL, "%s: unknown dtype %d", who, (int)dt);
     if (d < 1 || f < 1) return fail(GRACE_EINVAL, "%s: d=%d, f=%d invalid", who, d, f);
@@ -489,6 +518,48 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     return launch_gemm<true, pers::EXPERTS>(up, dt, rows, (hipStream_t)stream, who);
 }
 
+extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T,
+                                           int32_t E, int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out,
+                                           int32_t *topk_expert, float *topk_weight, int32_t *topk_inst, int32_t *expert_count,
+                                           const void *x, int32_t d, int32_t f, grace_dtype dt, int32_t *perm_pos, int32_t *perm_src,
+                                           int32_t *inst_off, int32_t *rank_off, int32_t *node_off, void *xp, const void *w_gate,
+                                           const void *w_up, int32_t *state, void *ws, void *stream) {
+    const char *const who = "dispatch_ffn_up_share";
+    if (!state) return fail(GRACE_EINVAL, "%s: state is null", who);
+    if (T > 0 && !x) return fail(GRACE_EINVAL, "%s: x is null", who);
+    int g0, S;
+    int rc = expert_ffn_common(who, table, local_rank, T, k, d, f, dt, g0, S);
+    if (rc != GRACE_OK) return rc;
+    rc = check_route_args(table, local_rank, policy, logits, T, E, k, rr_in, rr_out, topk_expert, topk_weight, topk_inst, expert_count, ws);
+    if (rc != GRACE_OK) return rc;
+    rc = check_permute_args(table, topk_inst, T, k, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws);
+    if (rc != GRACE_OK) return rc;
+    const int n_cu = compute_units();
+    if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", who);
+    if (T == 0 || !joins_dispatch(table, local_rank, T, k, d, f, dt, n_cu)) {
+        rc = grace_route_permute(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight, topk_inst,
+                                 expert_count, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws, stream);
+        if (rc != GRACE_OK) return rc;
+        return expert_ffn_up(who, table, local_rank, xp, inst_off, T, k, d, f, dt, w_gate, w_up, state, ws, stream);
+    }
+    if (!w_gate || !w_up) return fail(GRACE_EINVAL, "%s: null device pointer", who);
+    if ((((uintptr_t)w_gate) | ((uintptr_t)w_up) | ((uintptr_t)ws)) & 15) return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
+    const GemmArgs shape = expert_shape(true, S, d, f);
+    const Rows rows = expert_rows(S, table->I, T, k);
+    const Route route = route_gemm<true>(shape, dt, rows, n_cu);
+    const Grid l = grid_of<true>(route, shape, dt, rows, n_cu);
+    const int cols = route == Route::MID ? mid::Shape<true>::BN : strm::Shape<true>::COLS;
+    TinyUp a{tiny_args(table, local_rank, policy, logits, T, k, renorm, rr_in, rr_out, topk_expert, topk_weight, topk_inst, expert_count, x, d,
+                       dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp),
+             shape, table->d_inst_span + g0, g0, policy == GRACE_POLICY_WRR, (f + cols - 1) / cols};
+    a.up.A = x; a.up.B0 = w_gate; a.up.B1 = w_up; a.up.out = ws;
+    a.up.share_state = state;
+    if (route == Route::MID) launch_tiny_up_mid(a, n_cu, (hipStream_t)stream);
+    else launch_tiny_up(a, dt, l.threads / 64, dt == GRACE_F32 && stream_pieces<4>(rows), (hipStream_t)stream);
+    GRACE_LAUNCH_CHECK(who);
+    return GRACE_OK;
+}
+
 extern "C" int grace_expert_ffn_up(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
                                    int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_gate,
                                    const void *w_up, void *ws, void *stream) {
@@ -517,7 +588,7 @@ static_assert(SHARE_STATE_INTS == GRACE_SHARE_STATE_INTS, "header and kernels mu
 
 static int expert_ffn_down(const char *who, const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
                            int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state,
-                           bool clear_others, void *ws, void *stream) {
+                           bool clear_others, void *ws, void *stream, bool joined = false) {
     int g0, S;
     int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
     if (rc != GRACE_OK) return rc;
@@ -537,6 +608,11 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     GemmArgs dn = expert_shape(false, S, d, f);
     dn.A = ws; dn.B0 = w_down; dn.out = y;
     dn.seg_off = inst_off + g0;
+    if (joined) {
+        const int n_cu = compute_units();
+        if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", who);
+        if (joins_dispatch(table, rank, T, k, d, f, dt, n_cu)) dn.a_slot_rows = T;
+    }
     dn.share_state = state; dn.stale = state ? 1 : clear_others ? 2 : 0; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
     return launch_gemm<false, pers::EXPERTS>(dn, dt, expert_rows(S, table->I, T, k), (hipStream_t)stream, who);
 }
@@ -558,6 +634,25 @@ extern "C" int grace_expert_ffn_down_share(const grace_table *table, int32_t ran
                                            int32_t *state, void *ws, void *stream) {
     if (!state) return fail(GRACE_EINVAL, "expert_ffn_down_share: state is null");
     return expert_ffn_down("expert_ffn_down_share", table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream);
+}
+
+extern "C" int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
+                                             int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y,
+                                             int32_t *state, void *ws, void *stream) {
+    if (!state) return fail(GRACE_EINVAL, "dispatch_ffn_down_share: state is null");
+    return expert_ffn_down("dispatch_ffn_down_share", table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream, true);
+}
+
+extern "C" int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt,
+                                        int32_t n_cu, int32_t *joined) {
+    if (!joined) return fail(GRACE_EINVAL, "dispatch_joins_ffn: null output");
+    int g0, S;
+    const int rc = expert_ffn_common("dispatch_joins_ffn", table, local_rank, T, k, d, f, dt, g0, S);
+    if (rc != GRACE_OK) return rc;
+    if (n_cu == 0) n_cu = compute_units();
+    if (n_cu <= 0) return fail(GRACE_EHIP, "dispatch_joins_ffn: cannot query the device");
+    *joined = T > 0 && joins_dispatch(table, local_rank, T, k, d, f, dt, n_cu);
+    return GRACE_OK;
 }
 
 extern "C" int grace_expert_ffn(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,

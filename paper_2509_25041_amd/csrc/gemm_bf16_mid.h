@@ -58,10 +58,11 @@ __device__ __forceinline__ int chunk_at(int row, int c) { return row * ROW_BYTES
 
 // MF: activation fragments of 16 rows.  NJ: weight fragments per wavefront, 2 or, for half a tile's weight rows, 1 (gate+up:
 // then 8 rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K
-// axis is cut in segments (shared experts' down projection), of any length.
-template <bool FUSED_UP, bool SEG_K, int MF, int NJ>
-__device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, int first_step,
-                                          char *smem) {
+// axis is cut in segments (shared experts' down projection), of any length.  Activation rows from a0 on, or (LISTED) those that
+// `list` (LDS) names.
+template <bool FUSED_UP, bool SEG_K, int MF, int NJ, bool LISTED = false>
+__device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int a0, int n0, int first_step,
+                                          char *smem, const int16_t *list = nullptr) {
     constexpr int AHEAD = MF == 2 ? 8 : MF == 4 ? 6 : 4;   // steps in flight: what 256 registers hold (even)
     constexpr int AL = MF / 2;   // activation loads per thread and step: 32 rows each
     int tid = (int)threadIdx.x;
@@ -72,13 +73,13 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
     const int nk = (g.K + BK - 1) / BK;
 
     // ---- load sources ----
-    const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * 2);
+    const auto a_rsrc = rsrc_of((const char *)g.A + (LISTED ? 0 : (int64_t)a0 * g.lda * 2));
     uint32_t a_off[AL];
     const int a_chunk = tid & 7;
 #pragma unroll
     for (int i = 0; i < AL; ++i) {
         const int row = i * 32 + (tid >> 3);
-        a_off[i] = m0 + row < m_end ? (uint32_t)row * (uint32_t)(g.lda * 2) + (uint32_t)a_chunk * 16u : NO_DATA;
+        a_off[i] = m0 + row < m_end ? (uint32_t)(LISTED ? list[row] : row) * (uint32_t)(g.lda * 2) + (uint32_t)a_chunk * 16u : NO_DATA;
     }
     const int wn = n0 + wave * (FUSED_UP ? 8 : 16) * NJ;   // first output column of the wavefront
     const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 2;
@@ -286,15 +287,15 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArg
         const Segment s = segs.segment(t / n_strips, lane);
         const int in_seg = t - s.first_tile * n_strips, strip = in_seg / s.tiles, piece = in_seg - strip * s.tiles;
         const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
-        const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows);
+        const int m0 = s.lo + piece * rows, m_end = min(s.hi, m0 + rows), a0 = FUSED_UP ? m0 : activation_row(g, s.slot, s.lo, m0);
         const int n0 = strip * Shape<FUSED_UP>::BN + (half < 0 ? 0 : (half & 1) * (Shape<FUSED_UP>::BN / 2));
         const int first_step = SEG_K ? 0 : (s.slot * n_strips + strip) / 4 % ((g.K + BK - 1) / BK);
         if (again) __syncthreads();   // the tile before has been read
         auto tile = [&](auto nj) {
             constexpr int NJ = decltype(nj)::value;
-            if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6, NJ>(g, s.slot, m0, m_end, n0, first_step, smem);
-            else if (m_end - m0 > 32) tile_body<FUSED_UP, SEG_K, 4, NJ>(g, s.slot, m0, m_end, n0, first_step, smem);
-            else if (m_end > m0) tile_body<FUSED_UP, SEG_K, 2, NJ>(g, s.slot, m0, m_end, n0, first_step, smem);
+            if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6, NJ>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
+            else if (m_end - m0 > 32) tile_body<FUSED_UP, SEG_K, 4, NJ>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
+            else if (m_end > m0) tile_body<FUSED_UP, SEG_K, 2, NJ>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
         };
         if (half < 0) tile(std::integral_constant<int, 2>{});
         else if (n0 < g.N) tile(std::integral_constant<int, 1>{});

@@ -31,6 +31,7 @@ struct GemmArgs {
     int64_t ldb;            // elements between weight rows
     int N, K;
     int kseg_len;           // weight K axis split in segments of this length ...
+    int a_slot_rows;        // 0: activation row p belongs to output row p; else segment s has its rows from row s * a_slot_rows on
     int64_t kseg_stride;    // ... that lie this many elements apart (shared experts' down projection)
     void *out;              // output rows, row p at out + p * ldo
     int64_t ldo;
@@ -104,6 +105,9 @@ __device__ __forceinline__ void clear_stale_rows(const GemmArgs &g, const StaleR
     }
 }
 __device__ __forceinline__ void share_clear_stale(const GemmArgs &g) { clear_stale_rows(g, stale_rows(g)); }
+
+// Activation row of output row m of the segment that begins with row lo.
+__device__ __forceinline__ int activation_row(const GemmArgs &g, int slot, int lo, int m) { return g.a_slot_rows ? slot * g.a_slot_rows + m - lo : m; }
 
 // Which (slot, row range) does m-tile `mt` fall into?  Returns false for surplus tiles.
 template <int BM>

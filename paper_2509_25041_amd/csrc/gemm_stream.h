@@ -55,9 +55,16 @@ struct Shape {
 // LDS bytes of `waves` wavefronts' partial sums (2 weight fragments x mf activation fragments x 1 KB)
 inline int lds_bytes(int waves, int mf) { return waves * mf * 2 * 1024; }
 
+// The rows that a workgroup handles at a time: output rows [m0, m_end), activation rows from a0 on, or those that `list` (LDS) names.
+struct RowsOf {
+    int m0, m_end, a0;
+    const int16_t *list;
+};
+
 // MF: activation fragments of 16 rows the workgroup handles at a time
-template <bool FUSED_UP, int EL, int MF>
-__device__ __forceinline__ void rows_body(const GemmArgs &g, int slot, int m0, int m_end, int n0, float4 *red) {
+template <bool FUSED_UP, int EL, int MF, bool LISTED>
+__device__ __forceinline__ void rows_body(const GemmArgs &g, int slot, const RowsOf &rows, int n0, float4 *red) {
+    const int m0 = rows.m0, m_end = rows.m_end;
     constexpr int KSTEP = kstep<EL>();
     constexpr int DEPTH = MF == 1 ? 6 : MF == 2 ? 4 : MF == 3 ? 3 : 2;   // what 128 registers hold
     const int tid = (int)threadIdx.x, lane = tid & 63;
@@ -70,8 +77,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs &g, int slot, int m0, i
     uint32_t a_off[MF], b_off[2];
 #pragma unroll
     for (int i = 0; i < MF; ++i) {
-        const int m = min(m0 + i * 16 + r, m_end - 1);
-        a_off[i] = (uint32_t)(m - m0) * (uint32_t)(g.lda * EL) + (uint32_t)q * 16u;
+        const int m = min(i * 16 + r, m_end - m0 - 1);
+        a_off[i] = (uint32_t)(LISTED ? rows.list[m] : m) * (uint32_t)(g.lda * EL) + (uint32_t)q * 16u;
     }
     {
         const int na = min(n0 + r, g.N - 1), nb = FUSED_UP ? na : min(n0 + 16 + r, g.N - 1);
@@ -79,7 +86,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs &g, int slot, int m0, i
         b_off[1] = (uint32_t)(nb - n0) * (uint32_t)(g.ldb * EL) + (uint32_t)q * 16u;
     }
     const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)n0 * g.ldb) * EL;
-    const auto a_rsrc = rsrc_of((const char *)g.A + (int64_t)m0 * g.lda * EL);
+    const auto a_rsrc = rsrc_of((const char *)g.A + (LISTED ? 0 : (int64_t)rows.a0 * g.lda * EL));
     const auto b0_rsrc = rsrc_of((const char *)g.B0 + b_first);
     const auto b1_rsrc = rsrc_of((FUSED_UP ? (const char *)g.B1 : (const char *)g.B0) + b_first);
     // scalar offsets along K; the weights' jumps at the ends of K segments (of a length that is a multiple of the
@@ -214,14 +221,14 @@ __device__ __forceinline__ void rows_body(const GemmArgs &g, int slot, int m0, i
     }
 }
 
-// rows_body with as many fragments as the rows [m0, m_end) need, at most MF_MAX
-template <bool FUSED_UP, int EL, int MF_MAX>
-__device__ __forceinline__ void rows_any(const GemmArgs &g, int slot, int m0, int m_end, int n0, float4 *red) {
-    const int rows = m_end - m0;
-    if (MF_MAX == 1 || rows <= 16) rows_body<FUSED_UP, EL, 1>(g, slot, m0, m_end, n0, red);
-    else if (MF_MAX == 2 || rows <= 32) rows_body<FUSED_UP, EL, MF_MAX < 2 ? MF_MAX : 2>(g, slot, m0, m_end, n0, red);
-    else if (rows <= 48) rows_body<FUSED_UP, EL, MF_MAX < 3 ? MF_MAX : 3>(g, slot, m0, m_end, n0, red);
-    else rows_body<FUSED_UP, EL, MF_MAX>(g, slot, m0, m_end, n0, red);
+// rows_body with as many fragments as the rows need, at most MF_MAX
+template <bool FUSED_UP, int EL, int MF_MAX, bool LISTED = false>
+__device__ __forceinline__ void rows_any(const GemmArgs &g, int slot, const RowsOf &of, int n0, float4 *red) {
+    const int rows = of.m_end - of.m0;
+    if (MF_MAX == 1 || rows <= 16) rows_body<FUSED_UP, EL, 1, LISTED>(g, slot, of, n0, red);
+    else if (MF_MAX == 2 || rows <= 32) rows_body<FUSED_UP, EL, MF_MAX < 2 ? MF_MAX : 2, LISTED>(g, slot, of, n0, red);
+    else if (rows <= 48) rows_body<FUSED_UP, EL, MF_MAX < 3 ? MF_MAX : 3, LISTED>(g, slot, of, n0, red);
+    else rows_body<FUSED_UP, EL, MF_MAX, LISTED>(g, slot, of, n0, red);
 }
 
 // One workgroup per (segment, strip of weight rows): block = slot * n_strips + strip.  MF_MAX: fragments of 16
@@ -237,7 +244,7 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void gemm_stream_kernel(const GemmA
     const int hi = __builtin_amdgcn_readfirstlane(g.seg_off ? g.seg_off[slot + 1] : g.M_single);
     for (int m0 = lo; m0 < hi; m0 += MF_MAX * 16) {
         if (m0 > lo) __syncthreads();   // the sums of the rows before have been read
-        rows_any<FUSED_UP, EL, MF_MAX>(g, slot, m0, min(hi, m0 + MF_MAX * 16), n0, (float4 *)smem);
+        rows_any<FUSED_UP, EL, MF_MAX>(g, slot, {m0, min(hi, m0 + MF_MAX * 16), activation_row(g, slot, lo, m0), nullptr}, n0, (float4 *)smem);
     }
     if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
 }
@@ -263,7 +270,8 @@ __global__ __launch_bounds__(256, 4) void gemm_stream_tiles_kernel(const GemmArg
     const int rows = ((s.hi - s.lo + s.tiles - 1) / s.tiles + 15) & ~15;
     const int m0 = s.lo + piece * rows;
     if (m0 < s.hi)
-        rows_any<FUSED_UP, EL, MAX_ROWS / 16>(g, s.slot, m0, min(s.hi, m0 + rows), strip * Shape<FUSED_UP>::COLS, (float4 *)smem);
+        rows_any<FUSED_UP, EL, MAX_ROWS / 16>(g, s.slot, {m0, min(s.hi, m0 + rows), activation_row(g, s.slot, s.lo, m0), nullptr},
+                                              strip * Shape<FUSED_UP>::COLS, (float4 *)smem);
 }
 
 }  // namespace strm

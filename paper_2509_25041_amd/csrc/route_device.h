@@ -151,7 +151,7 @@ __device__ __forceinline__ void token_topk(const float (&raw)[VPL], int lane, in
     token_weights<VPL>(raw, lane, E, k, renorm, rank, weight);
 }
 
-// The same choice for four tokens by one wavefront, up to 64 experts: 16 lanes (a DPP row) per token, lane r of a row holds
+// The same choice for four tokens by one wavefront, up to 16 NU experts: 16 lanes (a DPP row) per token, lane r of a row holds
 // experts r + 16 u as a list in descending order (equal logits: ascending id).  In each of k rounds the row's largest
 // head is choice j and leaves its list: one chain of four DPP steps per round, where a search through all experts of a
 // lane and of the row has more than twenty (a small batch waits for the chain; gate of 64 tokens, k = 8, inside
@@ -168,9 +168,8 @@ __device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
 __device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {
     return dpp_min_step<0x140>(dpp_min_step<0x141>(dpp_min_step<0x4E>(dpp_min_step<0xB1>(v))));
 }
-template <typename F>
-__device__ __forceinline__ void row_topk(const float (&raw)[4], int r, int E, int k, F chosen) {
-    constexpr int NU = 4;
+template <int NU, typename F>
+__device__ __forceinline__ void row_topk(const float (&raw)[NU], int r, int E, int k, F chosen) {
     uint32_t key[NU], id[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {   // insertion in front of the first entry that it beats; all comparisons at once

@@ -13,6 +13,7 @@
 #include "bf16.h"
 #include "common.h"
 #include "route_device.h"
+#include "route_tiny.h"
 #include "stable_sort.h"
 #include "wave_utils.h"
 
@@ -28,7 +29,6 @@ namespace grace {
 // -> this one: 512 tokens, k = 8 11.0 -> 6.4, 1000, k = 2 8.7 -> 7.3.
 //
 // A workgroup takes rows_per_block rows of the histogram, in rounds of PLACE_THREADS assignments.
-constexpr int MAX_KEYS = 256;             // experts and instances that the tables in LDS of the smallest batches hold
 constexpr int PLACE_THREADS = 512, PLACE_WAVES = PLACE_THREADS / 64;
 constexpr int PLACE_LDS_CANDS = 1024;     // candidates of one view that are kept in LDS (else read from memory)
 
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
     const int32_t *__restrict__ node_first_inst, int32_t *__restrict__ topk_inst, int32_t *__restrict__ perm_pos,
     int32_t *__restrict__ perm_src, int32_t *__restrict__ inst_off, int32_t *__restrict__ rank_off, int32_t *__restrict__ node_off) {
     __shared__ int32_t all[GRACE_MAX_EXPERTS], cnt[GRACE_MAX_EXPERTS];   // requests of each expert: in all, before the current round
-    __shared__ uint32_t start[GRACE_MAX_EXPERTS];                        // number of its first one (mod W)
+    __shared__ uint32_t carried[GRACE_MAX_EXPERTS], start[GRACE_MAX_EXPERTS];   // number of its first one, as carried over; mod W
     __shared__ int32_t wcnt[PLACE_WAVES][GRACE_MAX_EXPERTS];             // match set sizes of a wavefront, then requests before it
     __shared__ int32_t s_ptr[GRACE_MAX_EXPERTS + 1], s_g[PLACE_LDS_CANDS];
     __shared__ uint32_t s_cum[PLACE_LDS_CANDS];
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
         block_add_rows<PLACE_THREADS>(hist, 0, nrows, E, all, tid, cnt, row0);
     }
     if (tid <= E) s_ptr[tid] = in_lds ? st_ptr - c_first : st_ptr;
-    if (tid < E) start[tid] = rr_own;
+    if (tid < E) carried[tid] = rr_own;
 #pragma unroll
     for (int q = 0; q < CANDS; ++q) {
         const int i = tid + q * PLACE_THREADS;
@@ -118,11 +118,11 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
     __syncthreads();
     // ---- rows of every instance: several threads per expert, a candidate each
     const int subs = PLACE_THREADS / E, e_own = tid / subs;
-    uint32_t first_number = 0;
     if (e_own < E) {
         const int cb = s_ptr[e_own], ce = s_ptr[e_own + 1];
         const uint32_t W = t_cum[ce - 1];
-        first_number = start[e_own] % W;
+        const uint32_t first_number = carried[e_own] % W;
+        if (tid % subs == 0) start[e_own] = first_number;
         const uint32_t end = first_number + (uint32_t)all[e_own];   // < 2^31 + 2^26
         const uint32_t turns = end / W, rest = end % W;
         for (int i = cb + tid % subs; i < ce; i += subs) {
@@ -136,28 +136,51 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
     }
     scan_waves();
     __syncthreads();
-    // ---- offsets: exclusive scan over the instances, consecutive ones per thread
-    if (e_own < E && tid % subs == 0) start[e_own] = first_number;
-    const int per = (I + PLACE_THREADS - 1) / PLACE_THREADS, i0 = min(I, tid * per), i1 = min(I, i0 + per);
-    int32_t sum = 0;
-    for (int i = i0; i < i1; ++i) sum += off[i];
-    const int32_t incl = wave_scan_add(sum);
-    if (lane == 63) wave_sum[wave] = incl;
-    __syncthreads();
-    int32_t run = incl - sum;
+    // ---- offsets: exclusive scan over the instances
+    int32_t *first = off;   // first row of every instance
+    if (I <= MAX_KEYS) {
+        // four per lane, by every wavefront for itself: two barriers fewer (128 tokens, k = 8, the whole call 12.15 -> 11.8 us)
+        constexpr int STRIDE = MAX_KEYS + 4;
+        static_assert((PLACE_WAVES + 1) * STRIDE <= GRACE_MAX_INSTANCES, "a copy per wavefront behind the totals");
+        first = off + (wave + 1) * STRIDE;
+        int32_t c[4], sum = 0;
 #pragma unroll
-    for (int w = 0; w < PLACE_WAVES; ++w) run += w < wave ? wave_sum[w] : 0;
-    for (int i = i0; i < i1; ++i) {
-        const int32_t c = off[i];
-        off[i] = run;
-        run += c;
+        for (int q = 0; q < 4; ++q) {
+            c[q] = lane * 4 + q < I ? off[lane * 4 + q] : 0;
+            sum += c[q];
+        }
+        const int32_t incl = wave_scan_add(sum);
+        int32_t run = incl - sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            first[lane * 4 + q] = run;
+            run += c[q];
+        }
+        if (lane == 63) first[MAX_KEYS] = run;
+        wave_ctr_fence();   // the wavefront's LDS operations execute in order
+    } else {
+        // consecutive ones per thread
+        const int per = (I + PLACE_THREADS - 1) / PLACE_THREADS, i0 = min(I, tid * per), i1 = min(I, i0 + per);
+        int32_t sum = 0;
+        for (int i = i0; i < i1; ++i) sum += off[i];
+        const int32_t incl = wave_scan_add(sum);
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        int32_t run = incl - sum;
+#pragma unroll
+        for (int w = 0; w < PLACE_WAVES; ++w) run += w < wave ? wave_sum[w] : 0;
+        for (int i = i0; i < i1; ++i) {
+            const int32_t c = off[i];
+            off[i] = run;
+            run += c;
+        }
+        if (tid == PLACE_THREADS - 1) off[I] = run;
+        __syncthreads();
     }
-    if (tid == PLACE_THREADS - 1) off[I] = run;
-    __syncthreads();
     if (blk == 0) {
-        for (int i = tid; i <= I; i += PLACE_THREADS) inst_off[i] = off[i];
-        for (int r = tid; r <= R; r += PLACE_THREADS) rank_off[r] = off[rank_ptr[r]];
-        for (int n = tid; n <= N; n += PLACE_THREADS) node_off[n] = off[node_first_inst[n]];
+        for (int i = tid; i <= I; i += PLACE_THREADS) inst_off[i] = first[i];
+        for (int r = tid; r <= R; r += PLACE_THREADS) rank_off[r] = first[rank_ptr[r]];
+        for (int n = tid; n <= N; n += PLACE_THREADS) node_off[n] = first[node_first_inst[n]];
     }
     // ---- instances and positions
     const uint64_t lt = lanemask_lt();
@@ -174,7 +197,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
                 hi = t_cum[++s];
             }
             const int g = t_g[s];
-            const int64_t pos = (int64_t)off[g] + (int32_t)(requests_to(turns, rest, lo, hi - lo) - requests_to(0u, from, lo, hi - lo));
+            const int64_t pos = (int64_t)first[g] + (int32_t)(requests_to(turns, rest, lo, hi - lo) - requests_to(0u, from, lo, hi - lo));
             topk_inst[a] = g;
             const bool inside = pos >= 0 && pos < n_assign;   // (always, unless the gate left an entry unwritten: logits that are all NaN)
             perm_pos[a] = inside ? (int32_t)pos : -1;
@@ -192,214 +215,20 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
     }
 }
 
-// The smallest batches: top-k, index work and row movement in one launch.  Three launches of 2 to 7 us each wait for one
-// another's first loads there, while all the index work of 64 tokens is a few microseconds for one workgroup.  So every
-// workgroup (one per token) does all of it from the logits, in LDS, and moves and writes what belongs to its token; workgroup 0 also
-// writes the counts and offsets.  Bound by latency, so: a wavefront takes a token in the gate, or four (row_topk) past 16 tokens,
-// and at most 64 assignments afterwards (each lane keeps its own in registers); candidates, the token's row and its logits
-// are loaded ahead; the gate weights, which only the caller needs, come last, under the row's stores.
+// The smallest batches: top-k, index work and row movement in one launch (route_tiny.h).  Three launches of 2 to 7 us each wait for one
+// another's first loads there, while all the index work of 64 tokens is a few microseconds for one workgroup.  A wavefront takes a token in
+// the gate, four past 16 tokens, or 64 of up to 16 experts (256 tokens of 8 experts, k = 2, four at a time 9.5, 64 at a time 6.2 us).
 // Layer steps, the three launches -> this one (1, 16, 64 tokens): 64 experts, k = 8 24.3 -> 20.8, 30.6 -> 25.0, 38.0 -> 33.9 us; 8 experts, k = 2
 // 22.8 -> 17.8, 30.8 -> 27.2, 34.9 -> 30.5 us; 128 experts, k = 8 22.8 -> 18.8, 31.1 -> 24.0 us.  Where the line lies: every workgroup
 // repeats the gate of all tokens, so the call (replayed from a graph) gains less with each.  96 tokens, 64 experts, k = 3, 4, 5, 6, 8: three
 // launches as the next larger batch takes them 10.4, 10.4, 11.0, 11.2, 11.8, this one 7.5, 8.2, 8.6, 9.4, 10.5 us; 85 tokens, k = 12 is the most
 // assignments.  Past 96 tokens k = 6 and 8 are about even in a step (128 tokens 56.7 -> 57.6, 39.1 -> 38.3 us).  256 tokens with k = 1, 2, where four
-// passes of the wavefronts end: 9.1, 10.0 to 10.6 against 10.9, 10.4 to 11.0 us.  128 and 256 experts, 32 tokens, k = 8, two passes: 9.5 and 11.4
+// passes of the wavefronts of four tokens end: 9.1, 10.0 to 10.6 against 10.9, 10.4 to 11.0 us.  128 and 256 experts, 32 tokens, k = 8, two passes: 9.5 and 11.4
 // against 12.3 and 14.0 us (33 tokens); four tokens by rows there 33 tokens 32.1 -> 32.2, 64 tokens 34.9 -> 36.1 us a step.
-constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
-constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_TOP2 = 16 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;
-inline bool tiny_batch(int T, int k, int E, int I) {
-    return T >= 1 && T <= (E > 64 ? TINY_MAX_T_WIDE : k > 2 ? TINY_MAX_T : TINY_MAX_T_TOP2) && (int64_t)T * k <= TINY_MAX_ASG && E <= MAX_KEYS &&
-           I <= MAX_KEYS;
-}
-
-// VPL: experts per lane where a wavefront takes a token; ROWS: a wavefront takes four tokens at a time.  PASSES: how often.
-template <int VPL, bool ROWS, int PASSES>
-__global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel(
-    const float *__restrict__ logits, int T, int E, int k, int renorm, const uint32_t *__restrict__ rr_in,
-    uint32_t *__restrict__ rr_out, const int32_t *__restrict__ cand_ptr, const int32_t *__restrict__ cand_g,
-    const uint32_t *__restrict__ cand_cum, int I, int R, int N, const int32_t *__restrict__ rank_ptr,
-    const int32_t *__restrict__ node_first_inst, int32_t *__restrict__ topk_expert, float *__restrict__ topk_weight,
-    int32_t *__restrict__ topk_inst, int32_t *__restrict__ expert_count, int32_t *__restrict__ perm_pos,
-    int32_t *__restrict__ perm_src, int32_t *__restrict__ inst_off, int32_t *__restrict__ rank_off,
-    int32_t *__restrict__ node_off, const uint4 *__restrict__ x, int row_vec, uint4 *__restrict__ xp) {
-    __shared__ int32_t ecnt[TINY_MAX_WAVES][MAX_KEYS];   // requests per expert of a wavefront, then before it
-    __shared__ int32_t icnt[TINY_MAX_WAVES][MAX_KEYS];   // rows per instance of a wavefront, then before it
-    __shared__ int32_t asg[TINY_MAX_ASG], where[TINY_MAX_ASG]; // expert of every assignment; its position
-    __shared__ int32_t count[MAX_KEYS], only[MAX_KEYS];   // candidates of an expert; the first one
-    __shared__ uint32_t weight_sum[MAX_KEYS], rr[MAX_KEYS];
-    __shared__ int32_t ioff[MAX_KEYS + 1];
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, threads = (int)blockDim.x, waves = threads >> 6;
-    const int n = T * k, groups = (n + 63) >> 6, me = (int)blockIdx.x;   // groups <= waves; a workgroup per token
-    // ---- loads ahead: this wavefront's logits, the experts' candidates, the row to move
-    static_assert(!ROWS || VPL == 1, "row_topk takes up to 64 experts");
-    constexpr int NU = ROWS ? 4 : VPL;   // experts per lane
-    const int r = ROWS ? lane & 15 : lane;
-    float raw[PASSES][NU];
-    auto token = [&](int i) { return ROWS ? (i * waves + wave) * 4 + (lane >> 4) : i * waves + wave; };
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i)
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int t = token(i), e = r + (ROWS ? 16 : 64) * u;
-            raw[i][u] = (t < T && e < E) ? logits[(size_t)t * E + e] : -INFINITY;
-        }
-    const int e_own = min(tid, E - 1);
-    const int cb = cand_ptr[e_own], ce = cand_ptr[e_own + 1];
-    const uint32_t rr_own = rr_in ? rr_in[e_own] : 0u;
-    const int copies = max(1, threads / row_vec), part = tid / row_vec, vec = tid - part * row_vec;   // `copies` groups of threads share the k rows
-    uint4 row = make_uint4(0u, 0u, 0u, 0u);
-    if (x && part < copies) row = x[(int64_t)me * row_vec + vec];
-    float own[VPL];   // the last wavefront's: the token's logits, for its weights
-#pragma unroll
-    for (int v = 0; v < VPL; ++v) {
-        const int e = lane + 64 * v;
-        own[v] = (wave == waves - 1 && e < E) ? logits[(size_t)me * E + e] : -INFINITY;
-    }
-    for (int i = tid; i < n; i += threads) asg[i] = -1;
-    for (int i = lane; i < MAX_KEYS; i += 64) {
-        ecnt[wave][i] = 0;
-        icnt[wave][i] = 0;
-    }
-    __syncthreads();
-    // ---- gate (the weights, which nothing here needs, at the end)
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i) {
-        const int t = token(i);
-        if ((ROWS ? (i * waves + wave) * 4 : t) >= T) break;   // uniform per wavefront
-        if constexpr (ROWS) {
-            row_topk(raw[i], r, E, k, [&](int j, int e) {
-                if (t < T && e < E) asg[t * k + j] = e;
-            });
-        } else {
-            int rank[NU];
-            token_ranks<VPL, true>(raw[i], lane, E, k, rank);
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-                if (lane + 64 * u < E && rank[u] < k) asg[t * k + rank[u]] = lane + 64 * u;
-        }
-    }
-    if (tid < E) {
-        count[tid] = ce - cb;
-        only[tid] = cand_g[cb];
-        weight_sum[tid] = cand_cum[ce - 1];
-        rr[tid] = rr_own;
-    }
-    __syncthreads();
-    // ---- requests of each expert: in the group, before it, in all
-    const uint64_t lt = lanemask_lt();
-    const int a = wave * 64 + lane;
-    int e = a < n ? asg[a] : -1;
-    const bool valid = e >= 0;
-    if (!valid) e = 0;
-    uint64_t same = 0;
-    if (wave < groups) {
-        same = wave_match((uint32_t)e, valid, bits_for(E));
-        if (valid && is_last_of(same)) ecnt[wave][e] = (int32_t)__popcll(same);
-    }
-    __syncthreads();
-    if (tid < E) {
-        int32_t run = 0;
-        for (int w = 0; w < groups; ++w) {
-            const int32_t c = ecnt[w][tid];
-            ecnt[w][tid] = run;
-            run += c;
-        }
-        if (me == 0) {
-            expert_count[tid] = run;
-            const uint64_t c = (uint64_t)rr[tid] + (uint64_t)(uint32_t)run;
-            const uint32_t W = weight_sum[tid];
-            if (rr_out) rr_out[tid] = (c >> 32) ? (uint32_t)(c % W) : (uint32_t)c % W;
-        }
-    }
-    __syncthreads();
-    // ---- replica pick; rows of each instance: in the group, before it, in all
-    int g = 0;
-    if (valid) {
-        if (count[e] == 1) {
-            g = only[e];
-        } else {
-            const uint64_t c = (uint64_t)(uint32_t)ecnt[wave][e] + (uint32_t)__popcll(same & lt) + (uint64_t)rr[e];
-            g = pick_candidate(c, e, cand_ptr, cand_g, cand_cum);
-        }
-    }
-    if (wave < groups) {
-        same = wave_match((uint32_t)g, valid, bits_for(I));
-        if (valid && is_last_of(same)) icnt[wave][g] = (int32_t)__popcll(same);
-    }
-    __syncthreads();
-    if (tid < MAX_KEYS) {
-        int32_t total = 0;
-        for (int w = 0; w < groups; ++w) {
-            const int32_t c = icnt[w][tid];
-            icnt[w][tid] = total;
-            total += c;
-        }
-        ioff[tid] = total;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        int32_t c[4], s = 0;   // exclusive scan over the ids, four per lane
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            c[q] = ioff[lane * 4 + q];
-            s += c[q];
-        }
-        const int32_t incl = wave_scan_add(s);
-        int32_t run = incl - s;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            ioff[lane * 4 + q] = run;
-            run += c[q];
-        }
-        if (lane == 63) ioff[MAX_KEYS] = incl;
-    }
-    __syncthreads();
-    // ---- positions, offsets, rows
-    if (a < n) {
-        const int pos = valid ? ioff[g] + icnt[wave][g] + (int32_t)__popcll(same & lt) : -1;
-        where[a] = pos;
-        if (a >= me * k && a < (me + 1) * k) {
-            perm_pos[a] = pos;
-            if (valid) {
-                topk_inst[a] = g;
-                perm_src[pos] = a;
-            }
-        }
-    }
-    if (me == 0) {
-        for (int i = tid; i <= I; i += threads) inst_off[i] = ioff[i];
-        for (int r = tid; r <= R; r += threads) rank_off[r] = ioff[rank_ptr[r]];
-        for (int m = tid; m <= N; m += threads) node_off[m] = ioff[node_first_inst[m]];
-    }
-    __syncthreads();
-    if (x && part < copies) {
-        for (int v = vec; v < row_vec; v += threads) {   // more than once only if a row has more vectors than the workgroup threads
-            if (v != vec) row = x[(int64_t)me * row_vec + v];
-            for (int j = part; j < k; j += copies) {
-                const int32_t p = where[me * k + j];
-                if (p >= 0) nt_store16(row, &xp[(int64_t)p * row_vec + v]);
-            }
-        }
-    }
-    // ---- what the call returns of the token's gate
-    if (wave == waves - 1) {
-        int rank[VPL];
-        float weight[VPL];
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) rank[v] = k;
-        for (int j = 0; j < k; ++j) {
-            const int e_j = asg[me * k + j];
-#pragma unroll
-            for (int v = 0; v < VPL; ++v) rank[v] = e_j == lane + 64 * v ? j : rank[v];
-        }
-        token_weights<VPL>(own, lane, E, k, renorm, rank, weight);
-#pragma unroll
-        for (int v = 0; v < VPL; ++v)
-            if (rank[v] < k) {
-                topk_expert[(size_t)me * k + rank[v]] = lane + 64 * v;
-                topk_weight[(size_t)me * k + rank[v]] = weight[v];
-            }
-    }
+template <int VPL, Gate GATE, int PASSES>
+__global__ __launch_bounds__(64 * TINY_MAX_WAVES) void route_permute_tiny_kernel(const TinyArgs d) {
+    __shared__ TinyLds lds;
+    tiny_dispatch<VPL, GATE, PASSES, true>(d, (int)blockIdx.x, lds);
 }
 
 }  // namespace grace
@@ -416,24 +245,22 @@ static int route_permute_impl(const grace_table *table, int32_t local_rank, grac
     const int view = policy == GRACE_POLICY_WRR ? table->R : local_rank;
     const int32_t *cand_ptr = table->d_cand_ptr + (size_t)view * E;
     if (tiny_batch(T, k, E, table->I)) {
-        const int row_vec = x ? (int)((int64_t)d * (dt == GRACE_F32 ? 4 : 2) / 16) : 1;
         int waves = 4;   // a thread per expert and instance, a wavefront per 64 assignments and, up to the most, per token or four
-        const bool rows = E <= 64 && T > TINY_MAX_WAVES;
-        while (waves < TINY_MAX_WAVES && waves * (rows ? 4 : 1) < T) waves *= 2;
+        const bool lanes = E <= TINY_LANE_E && T > TINY_MAX_WAVES, rows = E <= 64 && T > TINY_MAX_WAVES && !lanes;
+        while (!lanes && waves < TINY_MAX_WAVES && waves * (rows ? 4 : 1) < T) waves *= 2;
         while (waves * 64 < T * k) waves *= 2;
         auto launch = [&](auto vpl) {
             constexpr int VPL = decltype(vpl)::value;
-            auto *kern = route_permute_tiny_kernel<VPL, false, 1>;
+            auto *kern = route_permute_tiny_kernel<VPL, Gate::WAVE, 1>;
             if constexpr (VPL == 1) {
-                if (rows) kern = T <= 4 * waves ? route_permute_tiny_kernel<1, true, 1> : T <= 8 * waves ? route_permute_tiny_kernel<1, true, 2>
-                                                                                                : route_permute_tiny_kernel<1, true, 4>;
+                if (lanes) kern = route_permute_tiny_kernel<1, Gate::LANES, 1>;
+                else if (rows) kern = T <= 4 * waves ? route_permute_tiny_kernel<1, Gate::ROWS, 1> : T <= 8 * waves ? route_permute_tiny_kernel<1, Gate::ROWS, 2>
+                                                                                                                 : route_permute_tiny_kernel<1, Gate::ROWS, 4>;
             } else if (T > waves) {
-                kern = route_permute_tiny_kernel<VPL, false, 2>;
+                kern = route_permute_tiny_kernel<VPL, Gate::WAVE, 2>;
             }
-            kern<<<T, waves * 64, 0, st>>>(
-                logits, T, E, k, renorm, rr_in, rr_out, cand_ptr, table->d_cand_g, table->d_cand_cum, table->I, table->R, table->N,
-                table->d_rank_ptr, table->d_node_first_inst, topk_expert, topk_weight, topk_inst, expert_count, perm_pos, perm_src,
-                inst_off, rank_off, node_off, (const uint4 *)x, row_vec, (uint4 *)xp);
+            kern<<<T, waves * 64, 0, st>>>(tiny_args(table, local_rank, policy, logits, T, k, renorm, rr_in, rr_out, topk_expert, topk_weight,
+                                                     topk_inst, expert_count, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp));
         };
         if (E <= 64) launch(std::integral_constant<int, 1>{});
         else if (E <= 128) launch(std::integral_constant<int, 2>{});

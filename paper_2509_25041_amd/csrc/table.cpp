@@ -152,7 +152,8 @@ extern "C" int grace_table_create(grace_table **out, int32_t E, int32_t R, int32
     const size_t o_node = o_rank + al((size_t)(R + 1) * 4);
     const size_t o_irank = o_node + al((size_t)(N + 1) * 4);
     const size_t o_rnode = o_irank + al((size_t)I * 4);
-    const size_t total = o_rnode + al((size_t)R * 4);
+    const size_t o_span = o_rnode + al((size_t)R * 4);
+    const size_t total = o_span + al((size_t)I * 16);
     std::vector<char> stage(total, 0);
     memcpy(stage.data() + o_ptr, cand_ptr.data(), cand_ptr.size() * 4);
     t->cand_view.resize((size_t)R + 2);
@@ -163,6 +164,17 @@ extern "C" int grace_table_create(grace_table **out, int32_t E, int32_t R, int32
     memcpy(stage.data() + o_node, node_first_inst.data(), (size_t)(N + 1) * 4);
     memcpy(stage.data() + o_irank, t->g_rank.data(), (size_t)I * 4);
     memcpy(stage.data() + o_rnode, rank_node, (size_t)R * 4);
+    uint32_t *span = (uint32_t *)(stage.data() + o_span);
+    for (int32_t e = 0; e < E; ++e) {
+        const size_t v = (size_t)R * E + e;   // the view without locality
+        for (int32_t c = cand_ptr[v]; c < cand_ptr[v + 1]; ++c) {
+            uint32_t *const s = span + (size_t)cand_g[c] * 4;
+            s[0] = (uint32_t)e;
+            s[1] = c > cand_ptr[v] ? cand_cum[c - 1] : 0u;
+            s[2] = cand_cum[c];
+            s[3] = cand_cum[cand_ptr[v + 1] - 1];
+        }
+    }
 
     hipError_t he = hipGetDevice(&t->device);
     if (he == hipSuccess) he = hipMalloc(&t->d_base, total);
@@ -181,6 +193,7 @@ extern "C" int grace_table_create(grace_table **out, int32_t E, int32_t R, int32
     t->d_node_first_inst = (const int32_t *)(b + o_node);
     t->d_inst_rank = (const int32_t *)(b + o_irank);
     t->d_rank_node = (const int32_t *)(b + o_rnode);
+    t->d_inst_span = (const uint4 *)(b + o_span);
     *out = t;
     return GRACE_OK;
 }
@@ -263,6 +276,7 @@ extern "C" size_t grace_workspace_bytes(int32_t T, int32_t E, int32_t k, int32_t
     // routing and permutation histograms side by side (grace_route_permute uses both at once)
     size_t need = grace::route_permute_ws_bytes(T, E, k, I);
     need = std::max(need, grace::align_up(n * (size_t)f * el, 256));
+    if (T <= grace::SLOT_ROWS_MAX_T) need = std::max(need, std::min(grace::SLOT_ROWS_MOST, grace::align_up((size_t)T * std::min(E, I) * (size_t)f * el, 256)));
     need = std::max(need, grace::align_up((size_t)T * (size_t)n_shared * (size_t)f * el, 256));
     // send lists: five int32 arrays over the assignments + chunk histograms over up to GRACE_MAX_RANKS keys + counters
     need = std::max(need, 5 * grace::align_up(n * 4, 256) + 2 * grace::align_up(chunks_p * (size_t)GRACE_MAX_RANKS * 4, 256) +

@@ -7,9 +7,9 @@ from typing import List, Optional, Tuple
 
 import torch
 
-from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_ffn_carries_rows, grace_workspace_bytes, load_library
+from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_dispatch_joins_ffn, grace_ffn_carries_rows, grace_workspace_bytes, load_library
 
-STAGES = ("route", "permute", "route_permute", "ffn_up", "ffn_down", "shared_up", "shared_down", "combine")
+STAGES = ("route", "permute", "route_permute", "dispatch_ffn_up", "ffn_up", "ffn_down", "shared_up", "shared_down", "combine")
 
 
 class GraceMoELayer:
@@ -25,7 +25,7 @@ class GraceMoELayer:
     in a HIP graph).  The combine relies on it and does not read them
     (grace_combine_share), unless the rank hosts every instance.
 
-    All buffers are allocated once; a step is four to six C calls whose argument lists
+    All buffers are allocated once; a step is three to six C calls whose argument lists
     are marshalled once per (logits, x, rr_in, rr_out, stream) and reused, so the
     host cost of a step is a few microseconds per call.
     """
@@ -74,6 +74,9 @@ class GraceMoELayer:
         # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows;
         # elsewhere the dispatch call moves them (small batches in its one launch)
         self.gather_rows = not self.n_shared and S > 0 and T > 0 and grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I)
+        # the smallest batches: dispatch and the experts' gate+up projection in one launch (grace_dispatch_ffn_up_share), which the two
+        # switches above do not concern then; False: the calls above
+        self.join_dispatch = S > 0 and T > 0 and grace_dispatch_joins_ffn(table, local_rank, T, k, d, f, self.dt)
         self.ws_shared = None
         self._key = None
         self._calls: List[Tuple[str, object, tuple]] = []
@@ -95,9 +98,14 @@ class GraceMoELayer:
         wg, wu, wd = self.w
         S = wg.shape[0]
         ws = p(self.ws)
-        fuse = self.fuse_scatter and self.shared is not None
+        join = self.join_dispatch and self.single_call_dispatch
+        fuse = self.fuse_scatter and self.shared is not None and not join
         xr, xpr = (None, None) if fuse or self.gather_rows else (p(x), p(self.xp))     # rows moved by the dispatch call, or not
-        if self.single_call_dispatch:
+        if join:
+            calls = [("dispatch_ffn_up", lib.grace_dispatch_ffn_up_share,
+                      (h, lr, self.policy, p(logits), T, self.table.E, k, self.renorm, p(rr_in), p(rr_out), p(te), p(tw), p(ti), p(cnt),
+                       p(x), d, f, dt, p(pos), p(src), p(ioff), p(roff), p(noff), p(self.xp), p(wg), p(wu), p(self.y_state), ws, st))]
+        elif self.single_call_dispatch:
             calls = [("route_permute", lib.grace_route_permute,
                       (h, lr, self.policy, p(logits), T, self.table.E, k, self.renorm, p(rr_in), p(rr_out), p(te), p(tw),
                        p(ti), p(cnt), xr, d, dt, p(pos), p(src), p(ioff), p(roff), p(noff), xpr, ws, st))]
@@ -120,12 +128,12 @@ class GraceMoELayer:
         if self.gather_rows:
             calls.append(("ffn_up", lib.grace_expert_ffn_up_share_scatter,
                           (h, lr, p(x), p(pos), p(src), p(self.xp), p(ioff), T, k, d, f, dt, p(wg), p(wu), p(self.y_state), ws, st)))
-        else:
+        elif not join:
             calls.append(("ffn_up", lib.grace_expert_ffn_up_share, (h, lr, p(self.xp), p(ioff), T, k, d, f, dt, p(wg) if S else None,
                                                                     p(wu) if S else None, p(self.y_state), ws, st)))
         calls += [
-            ("ffn_down", lib.grace_expert_ffn_down_share, (h, lr, p(ioff), T, k, d, f, dt, p(wd) if S else None,
-                                                           p(self.y), p(self.y_state), ws, st)),
+            ("ffn_down", lib.grace_dispatch_ffn_down_share if join else lib.grace_expert_ffn_down_share,
+             (h, lr, p(ioff), T, k, d, f, dt, p(wd) if S else None, p(self.y), p(self.y_state), ws, st)),
         ]
         if self.shared is not None:
             sg, su, sd = self.shared
