@@ -331,8 +331,8 @@ int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const 
 int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt,
                              int32_t n_cu, int32_t *joined);
 
-/* grace_permute_rows followed by grace_expert_ffn_up_share on the rows it has moved, as one call: for prefill batches, where the
- * large-tile kernel takes the projection, that launch reads the rank's rows from x and moves all rows to xp as it runs
+/* grace_permute_rows followed by grace_expert_ffn_up_share on the rows it has moved, as one call: where the large-tile or the 96-row
+ * kernel takes the projection, that launch reads the rank's rows from x and moves all rows to xp as it runs
  * (grace_ffn_carries_rows; two launches elsewhere).  Same results as the two calls, bit for bit.
  * DEVICE: x [T,d]; perm_pos, perm_src [T*k] and inst_off of grace_permute / grace_route_permute called with x == NULL; xp [T*k,d]. */
 int grace_expert_ffn_up_share_scatter(const grace_table *table, int32_t rank, const void *x, const int32_t *perm_pos,
@@ -368,6 +368,24 @@ int grace_shared_ffn_down(int32_t T, int32_t d, int32_t f, int32_t n_shared, gra
 int grace_shared_ffn_up_scatter(const void *x, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt,
                                 const void *w_gate, const void *w_up, void *ws, const int32_t *perm_pos, int32_t k,
                                 void *xp, void *stream);
+
+/* grace_shared_ffn_up_scatter followed by grace_expert_ffn_up_share, and grace_expert_ffn_down_share followed by
+ * grace_shared_ffn_down, as one call each: where the 96-row kernel takes both projections (grace_ffn_joins_shared) they are one
+ * launch, whose gate+up form also moves the rows (the experts' tiles read the tokens); the calls one after the other elsewhere.  Same results as
+ * theirs, bit for bit.  ws and ws_shared as for grace_expert_ffn and grace_shared_ffn, not overlapping.
+ * DEVICE: as for these; perm_src [T*k] of grace_permute / grace_route_permute. */
+int grace_expert_shared_ffn_up_scatter(const grace_table *table, int32_t rank, const void *x, const int32_t *perm_pos,
+                                       const int32_t *perm_src, void *xp, const int32_t *inst_off, int32_t T, int32_t k, int32_t d,
+                                       int32_t f, int32_t n_shared, grace_dtype dt, const void *w_gate, const void *w_up,
+                                       const void *shared_gate, const void *shared_up, int32_t *state, void *ws, void *ws_shared,
+                                       void *stream);
+int grace_expert_shared_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k, int32_t d, int32_t f,
+                                 int32_t n_shared, grace_dtype dt, const void *w_down, const void *shared_down, void *y,
+                                 void *y_shared, int32_t *state, void *ws, void *ws_shared, void *stream);
+/* Whether one launch does both gate+up (up 1) or down (up 0) projections of these sizes: S of the table's I instances on the rank;
+ * n_cu: compute units (0: of the current device; no device is touched otherwise).  HOST output. */
+int grace_ffn_joins_shared(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I, grace_dtype dt,
+                           int32_t n_cu, int32_t *joined);
 
 /* ---- grace_combine: weighted aggregation back to token order ----------------
  * The aggregation step that follows the expert computation (Section 1):

@@ -26,7 +26,10 @@ from .binding import (  # noqa: F401
     grace_expert_ffn_up,
     grace_expert_ffn_up_share,
     grace_expert_ffn_up_share_scatter,
+    grace_expert_shared_ffn_down,
+    grace_expert_shared_ffn_up_scatter,
     grace_ffn_carries_rows,
+    grace_ffn_joins_shared,
     grace_ffn_kernel,
     grace_last_error,
     grace_mfma_sustained,

@@ -23,7 +23,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_expert_ffn_down", "grace_expert_ffn_down_fresh", "grace_expert_ffn_up_share", "grace_expert_ffn_up_share_scatter", "grace_expert_ffn_down_share",
            "grace_shared_ffn", "grace_shared_ffn_up", "grace_shared_ffn_down", "grace_shared_ffn_up_scatter", "grace_combine", "grace_combine_share", "grace_mfma_sustained",
            "grace_ffn_kernel", "grace_ffn_carries_rows",
-           "grace_dispatch_ffn_up_share", "grace_dispatch_ffn_down_share", "grace_dispatch_joins_ffn",
+           "grace_dispatch_ffn_up_share", "grace_dispatch_ffn_down_share", "grace_dispatch_joins_ffn", "grace_expert_shared_ffn_up_scatter", "grace_expert_shared_ffn_down", "grace_ffn_joins_shared",
            "grace_last_error")
 
 _lib: Optional[C.CDLL] = None
@@ -88,6 +88,9 @@ def load_library() -> C.CDLL:
     lib.grace_dispatch_ffn_up_share.argtypes = [vp, i32, C.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, i32, i32, C.c_int, vp, vp, vp,
                                                 vp, vp, vp, vp, vp, vp, vp, vp]
     lib.grace_dispatch_ffn_down_share.argtypes = lib.grace_expert_ffn_down_share.argtypes
+    lib.grace_expert_shared_ffn_up_scatter.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.grace_expert_shared_ffn_down.argtypes = [vp, i32, vp, i32, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.grace_ffn_joins_shared.argtypes = [i32] * 8 + [C.c_int, i32, vp]
     lib.grace_dispatch_joins_ffn.argtypes = [vp, i32, i32, i32, i32, i32, C.c_int, i32, vp]
     lib.grace_ffn_carries_rows.argtypes = [i32, i32, i32, i32, i32, i32, i32, C.c_int, i32, vp]
     for name in EXPORTS:
@@ -535,6 +538,50 @@ def grace_shared_ffn_up_scatter(x: torch.Tensor, w_gate: torch.Tensor, w_up: tor
     n_shared, f, _ = w_gate.shape
     _check(load_library().grace_shared_ffn_up_scatter(_dp(x), T, d, f, n_shared, _dtype_code(x), _dp(w_gate), _dp(w_up),
                                                       _dp(ws), _dp(perm_pos), k, _dp(xp), _stream()))
+
+
+def grace_expert_shared_ffn_up_scatter(table: GraceTable, rank: int, x: torch.Tensor, perm_pos: torch.Tensor, perm_src: torch.Tensor,
+                                       xp: torch.Tensor, inst_off: torch.Tensor, k: int, w_gate: torch.Tensor, w_up: torch.Tensor,
+                                       shared_gate: torch.Tensor, shared_up: torch.Tensor, state: torch.Tensor, ws: torch.Tensor,
+                                       ws_shared: torch.Tensor) -> None:
+    """grace_shared_ffn_up_scatter and grace_expert_ffn_up_share as one call; see grace_moe.h."""
+    _need(state, "state", torch.int32, SHARE_STATE_INTS)
+    S, f, d = w_gate.shape
+    T, n_shared, dt = x.shape[0], shared_gate.shape[0], _dtype_code(x)
+    if tuple(x.shape) != (T, d) or tuple(w_up.shape) != (S, f, d) or tuple(shared_gate.shape) != (n_shared, f, d) or \
+            tuple(shared_up.shape) != (n_shared, f, d) or any(w.dtype != x.dtype for w in (w_gate, w_up, shared_gate, shared_up)):
+        raise ValueError("x must be [T,d], w_gate and w_up [S,f,d], shared ones [n,f,d], of one dtype")
+    for t, name, n in ((perm_pos, "perm_pos", T * k), (perm_src, "perm_src", T * k), (inst_off, "inst_off", table.I + 1)):
+        _need(t, name, torch.int32, n)
+    _need(xp, "xp", x.dtype, T * k * d)
+    _ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, dt), x.device)
+    _ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt), x.device)
+    _check(load_library().grace_expert_shared_ffn_up_scatter(
+        table.handle, rank, _dp(x), _dp(perm_pos), _dp(perm_src), _dp(xp), _dp(inst_off), T, k, d, f, n_shared, dt, _dp(w_gate) if S else None,
+        _dp(w_up) if S else None, _dp(shared_gate), _dp(shared_up), _dp(state), _dp(ws), _dp(ws_shared), _stream()))
+
+
+def grace_expert_shared_ffn_down(table: GraceTable, rank: int, inst_off: torch.Tensor, T: int, k: int, w_down: torch.Tensor,
+                                 shared_down: torch.Tensor, y: torch.Tensor, y_shared: torch.Tensor, state: torch.Tensor, ws: torch.Tensor,
+                                 ws_shared: torch.Tensor) -> None:
+    """grace_expert_ffn_down_share and grace_shared_ffn_down as one call; see grace_moe.h."""
+    _need(state, "state", torch.int32, SHARE_STATE_INTS)
+    S, d, f = w_down.shape
+    _need(y, "y", w_down.dtype, T * k * d)
+    _need(y_shared, "y_shared", w_down.dtype, T * d)
+    if tuple(shared_down.shape[1:]) != (d, f) or shared_down.dtype != w_down.dtype:
+        raise ValueError("shared_down must be [n,d,f] of the dtype of w_down")
+    _check(load_library().grace_expert_shared_ffn_down(
+        table.handle, rank, _dp(inst_off), T, k, d, f, shared_down.shape[0], _dtype_code(y), _dp(w_down) if S else None, _dp(shared_down),
+        _dp(y), _dp(y_shared), _dp(state), _dp(ws), _dp(ws_shared), _stream()))
+
+
+def grace_ffn_joins_shared(up: bool, T: int, d: int, f: int, n_shared: int, dt: int = GRACE_BF16, *, k: int = 1, S: int = 1, I: int = 1,
+                           n_cu: int = 0) -> bool:
+    """Does one launch do the experts' and the shared experts' projection (see grace_moe.h)?"""
+    joined = C.c_int32()
+    _check(load_library().grace_ffn_joins_shared(int(up), T, k, d, f, n_shared, S, I, dt, n_cu, C.byref(joined)))
+    return bool(joined.value)
 
 
 def grace_combine(y: torch.Tensor, perm_pos: torch.Tensor, topk_weight: torch.Tensor,

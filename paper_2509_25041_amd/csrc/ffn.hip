@@ -384,6 +384,35 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipS
     return GRACE_OK;
 }
 
+// Shared experts' and experts' projections as one launch of the 96-row kernel, where it takes both (gemm_bf16_mid_joint_kernel).
+template <bool FUSED_UP>
+static int launch_joint(const GemmArgs *shared, const Rows &shared_rows, const GemmArgs &experts, const Rows &rows, int n_cu, hipStream_t st, const char *what) {
+    mid::Joint j{};
+    const Grid e = grid_of<FUSED_UP>(Route::MID, experts, GRACE_BF16, rows, n_cu);
+    int64_t tiles = 0;
+    if (shared) {
+        j.shared = *shared;
+        j.shared_strips = (shared->N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+        tiles = (shared_rows.m_bound + mid::BM - 1) / mid::BM * j.shared_strips;
+        j.shared_blocks = (int)mid::grid_blocks(tiles, n_cu, true);
+    }
+    j.experts = experts;
+    j.expert_strips = (experts.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
+    j.n_cu = n_cu;
+    if (FUSED_UP && experts.sc_T > 0) {
+        // about 300 KB each, which takes 20 us; 200 and 400 KB are even, 800 is slower where the rows are many (3001 tokens, k = 6, f = 352 79.8, 80.8
+        // and 87.0 us a step), and so are half as many at most (89.0)
+        const int64_t bytes = (int64_t)experts.sc_T * (1 + experts.sc_k) * experts.sc_row_bytes;
+        j.movers = (int)std::min(std::min<int64_t>(n_cu, (experts.sc_T + 3) / 4), bytes / (300 << 10) + 1);
+    }
+    const Grid l = {j.movers + j.shared_blocks + e.groups, mid::THREADS};
+    if (!launchable(l)) return fail(GRACE_ESHAPE, "%s: grid too large", what);
+    if (experts.S <= 64) mid::gemm_bf16_mid_joint_kernel<FUSED_UP, 1><<<(unsigned)l.groups, l.threads, 0, st>>>(j);
+    else mid::gemm_bf16_mid_joint_kernel<FUSED_UP, 4><<<(unsigned)l.groups, l.threads, 0, st>>>(j);
+    GRACE_LAUNCH_CHECK(what);
+    return GRACE_OK;
+}
+
 // Shapes of the two projections (operands are filled in by the entry points).
 //   up:   K = d, N = f, two weight matrices        down: K = f, N = d
 static GemmArgs expert_shape(bool up, int S, int d, int f) {
@@ -443,6 +472,18 @@ static bool joins_dispatch(const grace_table *table, int32_t rank, int32_t T, in
     }
     l.groups += T + 8;
     return launchable(l);
+}
+
+// Is a projection of the experts one launch with the shared experts' (n_shared > 0), or with the rows (n_shared == 0, gate+up)?  Offsets of the
+// tokens that the gate+up tiles read fit 32 bits.
+static bool joins_shared(bool up, int32_t T, int32_t k, int32_t d, int32_t f, int n_shared, int S, int I, grace_dtype dt, int n_cu) {
+    if (dt != GRACE_BF16 || S < 1 || T < 1 || (int64_t)T * d * 2 >= (int64_t)NO_DATA || (int64_t)n_shared * f > INT32_MAX) return false;
+    const Rows rows = expert_rows(S, I, T, k);
+    if ((up ? route_gemm<true>(expert_shape(true, S, d, f), dt, rows, n_cu) : route_gemm<false>(expert_shape(false, S, d, f), dt, rows, n_cu)) != Route::MID) return false;
+    if (n_shared == 0) return up && (S > 1 || T > 256);   // (one slot, d = 4096, k = 2: 97 and 200 tokens 0.97 to 1.01, 512 and 1000 1.02 to 1.04)
+    const Rows all = shared_rows(T);
+    return (up ? route_gemm<true>(shared_shape(true, T, d, f, n_shared), dt, all, n_cu)
+               : route_gemm<false>(shared_shape(false, T, d, f, n_shared), dt, all, n_cu)) == Route::MID;
 }
 
 static int check_ffn_shapes(const char *who, int32_t d, int32_t f, grace_dtype dt) {
@@ -511,6 +552,11 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
             up.A = sc->src;
             up.sc_x = sc->x; up.sc_xp = (void *)xp; up.sc_pos = sc->pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = d * 2;
             return launch_gemm<true, pers::EXPERTS_GATHER>(up, dt, rows, (hipStream_t)stream, who);
+        }
+        if (n_cu > 0 && joins_shared(true, T, k, d, f, 0, S, table->I, dt, n_cu)) {
+            up.A = sc->src;
+            up.sc_x = sc->x; up.sc_xp = (void *)xp; up.sc_pos = sc->pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = d * 2;
+            return launch_joint<true>(nullptr, rows, up, rows, n_cu, (hipStream_t)stream, who);
         }
         rc = grace_permute_rows(sc->x, sc->pos, T, k, d, dt, (void *)xp, stream);
         if (rc != GRACE_OK) return rc;
@@ -735,6 +781,74 @@ extern "C" int grace_shared_ffn(const void *x, int32_t T, int32_t d, int32_t f, 
     return grace_shared_ffn_down(T, d, f, n_shared, dt, w_down, y_shared, ws, stream);
 }
 
+extern "C" int grace_expert_shared_ffn_up_scatter(const grace_table *table, int32_t rank, const void *x, const int32_t *perm_pos,
+                                                  const int32_t *perm_src, void *xp, const int32_t *inst_off, int32_t T, int32_t k,
+                                                  int32_t d, int32_t f, int32_t n_shared, grace_dtype dt, const void *w_gate,
+                                                  const void *w_up, const void *shared_gate, const void *shared_up, int32_t *state,
+                                                  void *ws, void *ws_shared, void *stream) {
+    const char *const who = "expert_shared_ffn_up_scatter";
+    int g0, S;
+    int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
+    if (rc == GRACE_OK) rc = shared_ffn_common(who, T, d, f, n_shared, dt);
+    if (rc != GRACE_OK) return rc;
+    if (!state) return fail(GRACE_EINVAL, "%s: state is null", who);
+    const int n_cu = compute_units();
+    if (n_cu <= 0 || !joins_shared(true, T, k, d, f, n_shared, S, table->I, dt, n_cu)) {
+        rc = grace_shared_ffn_up_scatter(x, T, d, f, n_shared, dt, shared_gate, shared_up, ws_shared, perm_pos, k, xp, stream);
+        return rc != GRACE_OK ? rc : grace_expert_ffn_up_share(table, rank, xp, inst_off, T, k, d, f, dt, w_gate, w_up, state, ws, stream);
+    }
+    if (!x || !perm_pos || !perm_src || !xp || !inst_off || !w_gate || !w_up || !shared_gate || !shared_up || !ws || !ws_shared)
+        return fail(GRACE_EINVAL, "%s: null device pointer", who);
+    if (((uintptr_t)x | (uintptr_t)xp | (uintptr_t)w_gate | (uintptr_t)w_up | (uintptr_t)shared_gate | (uintptr_t)shared_up | (uintptr_t)ws |
+         (uintptr_t)ws_shared) & 15)
+        return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
+    GemmArgs all = shared_shape(true, T, d, f, n_shared), up = expert_shape(true, S, d, f);
+    all.A = x; all.B0 = shared_gate; all.B1 = shared_up; all.out = ws_shared;
+    up.A = perm_src; up.B0 = w_gate; up.B1 = w_up; up.out = ws;
+    up.seg_off = inst_off + g0;
+    up.share_state = state;
+    up.sc_x = x; up.sc_xp = xp; up.sc_pos = perm_pos; up.sc_T = T; up.sc_k = k; up.sc_row_bytes = d * 2;
+    return launch_joint<true>(&all, shared_rows(T), up, expert_rows(S, table->I, T, k), n_cu, (hipStream_t)stream, who);
+}
+
+extern "C" int grace_expert_shared_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k, int32_t d,
+                                            int32_t f, int32_t n_shared, grace_dtype dt, const void *w_down, const void *shared_down,
+                                            void *y, void *y_shared, int32_t *state, void *ws, void *ws_shared, void *stream) {
+    const char *const who = "expert_shared_ffn_down";
+    int g0, S;
+    int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
+    if (rc == GRACE_OK) rc = shared_ffn_common(who, T, d, f, n_shared, dt);
+    if (rc != GRACE_OK) return rc;
+    if (!state) return fail(GRACE_EINVAL, "%s: state is null", who);
+    const int n_cu = compute_units();
+    if (n_cu <= 0 || !joins_shared(false, T, k, d, f, n_shared, S, table->I, dt, n_cu)) {
+        rc = grace_expert_ffn_down_share(table, rank, inst_off, T, k, d, f, dt, w_down, y, state, ws, stream);
+        return rc != GRACE_OK ? rc : grace_shared_ffn_down(T, d, f, n_shared, dt, shared_down, y_shared, ws_shared, stream);
+    }
+    if (!inst_off || !w_down || !shared_down || !y || !y_shared || !ws || !ws_shared) return fail(GRACE_EINVAL, "%s: null device pointer", who);
+    if (((uintptr_t)w_down | (uintptr_t)shared_down | (uintptr_t)y | (uintptr_t)y_shared | (uintptr_t)ws | (uintptr_t)ws_shared) & 15)
+        return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
+    GemmArgs all = shared_shape(false, T, d, f, n_shared), dn = expert_shape(false, S, d, f);
+    all.A = ws_shared; all.B0 = shared_down; all.out = y_shared;
+    dn.A = ws; dn.B0 = w_down; dn.out = y;
+    dn.seg_off = inst_off + g0;
+    dn.share_state = state; dn.stale = 1; dn.share_rows = (int64_t)T * k; dn.share_row_vec = d * 2 / 16;
+    return launch_joint<false>(&all, shared_rows(T), dn, expert_rows(S, table->I, T, k), n_cu, (hipStream_t)stream, who);
+}
+
+extern "C" int grace_ffn_joins_shared(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I, grace_dtype dt,
+                                      int32_t n_cu, int32_t *joined) {
+    if (!joined) return fail(GRACE_EINVAL, "ffn_joins_shared: null output");
+    if (T < 1 || k < 1 || S < 0 || I < S || n_cu < 0) return fail(GRACE_EINVAL, "ffn_joins_shared: T=%d, k=%d, S=%d, I=%d, n_cu=%d invalid", T, k, S, I, n_cu);
+    const int rc = shared_ffn_common("ffn_joins_shared", T, d, f, n_shared, dt);
+    if (rc != GRACE_OK) return rc;
+    if ((int64_t)T * k > INT32_MAX) return fail(GRACE_ESHAPE, "ffn_joins_shared: T*k exceeds 2^31-1");
+    if (n_cu == 0) n_cu = compute_units();
+    if (n_cu <= 0) return fail(GRACE_EHIP, "ffn_joins_shared: cannot query the device");
+    *joined = joins_shared(up, T, k, d, f, n_shared, S, I, dt, n_cu);
+    return GRACE_OK;
+}
+
 extern "C" int grace_ffn_kernel(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I,
                                 grace_dtype dt, int32_t n_cu, int32_t *kernel, int64_t *work_items) {
     if (!kernel || !work_items) return fail(GRACE_EINVAL, "ffn_kernel: null output");
@@ -760,6 +874,8 @@ extern "C" int grace_ffn_carries_rows(int32_t T, int32_t k, int32_t d, int32_t f
     int32_t kernel;
     int64_t work_items;
     const int rc = grace_ffn_kernel(1, T, k, d, f, n_shared, S, I, dt, n_cu, &kernel, &work_items);
-    if (rc == GRACE_OK) *carried = carries_rows((Route)kernel, dt, T, k, d, n_shared == 0);
+    if (rc == GRACE_OK)
+        *carried = carries_rows((Route)kernel, dt, T, k, d, n_shared == 0) ||
+                   (n_shared == 0 && joins_shared(true, T, k, d, f, 0, S, I, dt, n_cu == 0 ? compute_units() : n_cu));
     return rc;
 }

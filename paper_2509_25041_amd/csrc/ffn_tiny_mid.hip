@@ -40,9 +40,9 @@ __global__ __launch_bounds__(mid::THREADS, 2) void tiny_up_mid_kernel(const Tiny
     const int m0 = slot * T, m_end = m0 + n, first_step = t / 4 % ((a.up.K + mid::BK - 1) / mid::BK);
     auto tile = [&](auto nj) {
         constexpr int NJ = decltype(nj)::value;
-        if (n > 64) mid::tile_body<true, false, 6, NJ, true>(a.up, slot, m0, m_end, 0, n0, first_step, smem, s.list);
-        else if (n > 32) mid::tile_body<true, false, 4, NJ, true>(a.up, slot, m0, m_end, 0, n0, first_step, smem, s.list);
-        else if (n > 0) mid::tile_body<true, false, 2, NJ, true>(a.up, slot, m0, m_end, 0, n0, first_step, smem, s.list);
+        if (n > 64) mid::tile_body<true, false, 6, NJ, mid::RowsFrom::LIST>(a.up, slot, m0, m_end, 0, n0, first_step, smem, s.list);
+        else if (n > 32) mid::tile_body<true, false, 4, NJ, mid::RowsFrom::LIST>(a.up, slot, m0, m_end, 0, n0, first_step, smem, s.list);
+        else if (n > 0) mid::tile_body<true, false, 2, NJ, mid::RowsFrom::LIST>(a.up, slot, m0, m_end, 0, n0, first_step, smem, s.list);
     };
     if (halves) tile(std::integral_constant<int, 1>{});
     else tile(std::integral_constant<int, 2>{});

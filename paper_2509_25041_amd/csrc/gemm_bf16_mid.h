@@ -58,9 +58,10 @@ __device__ __forceinline__ int chunk_at(int row, int c) { return row * ROW_BYTES
 
 // MF: activation fragments of 16 rows.  NJ: weight fragments per wavefront, 2 or, for half a tile's weight rows, 1 (gate+up:
 // then 8 rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K
-// axis is cut in segments (shared experts' down projection), of any length.  Activation rows from a0 on, or (LISTED) those that
-// `list` (LDS) names.
-template <bool FUSED_UP, bool SEG_K, int MF, int NJ, bool LISTED = false>
+// axis is cut in segments (shared experts' down projection), of any length.  Activation rows from a0 on, or those that `list` (LDS)
+// names, or the tokens (g.sc_x) of the assignments that g.A names for the rows.
+enum class RowsFrom { HERE, LIST, ASSIGNMENTS };
+template <bool FUSED_UP, bool SEG_K, int MF, int NJ, RowsFrom FROM>
 __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int a0, int n0, int first_step,
                                           char *smem, const int16_t *list = nullptr) {
     constexpr int AHEAD = MF == 2 ? 8 : MF == 4 ? 6 : 4;   // steps in flight: what 256 registers hold (even)
@@ -73,13 +74,17 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
     const int nk = (g.K + BK - 1) / BK;
 
     // ---- load sources ----
-    const auto a_rsrc = rsrc_of((const char *)g.A + (LISTED ? 0 : (int64_t)a0 * g.lda * 2));
+    const auto a_rsrc = rsrc_of(FROM == RowsFrom::ASSIGNMENTS ? (const char *)g.sc_x : (const char *)g.A + (FROM == RowsFrom::HERE ? (int64_t)a0 * g.lda * 2 : 0));
     uint32_t a_off[AL];
     const int a_chunk = tid & 7;
 #pragma unroll
     for (int i = 0; i < AL; ++i) {
         const int row = i * 32 + (tid >> 3);
-        a_off[i] = m0 + row < m_end ? (uint32_t)(LISTED ? list[row] : row) * (uint32_t)(g.lda * 2) + (uint32_t)a_chunk * 16u : NO_DATA;
+        a_off[i] = NO_DATA;
+        if (m0 + row < m_end) {
+            const int from = FROM == RowsFrom::LIST ? list[row] : FROM == RowsFrom::ASSIGNMENTS ? (int)((uint32_t)((const int32_t *)g.A)[m0 + row] / (uint32_t)g.sc_k) : row;
+            a_off[i] = (uint32_t)from * (uint32_t)(g.lda * 2) + (uint32_t)a_chunk * 16u;
+        }
     }
     const int wn = n0 + wave * (FUSED_UP ? 8 : 16) * NJ;   // first output column of the wavefront
     const int64_t b_first = ((int64_t)slot * g.b_slot_stride + (int64_t)wn * g.ldb) * 2;
@@ -256,12 +261,42 @@ inline int64_t grid_blocks(int64_t tiles, int n_cu, bool exact) {
 // of d = 4096, f = 14336, down 114 -> 60 us).  More halves than units are slower again (308 of 32 rows 16.0 us, 220 of 48 rows 15.0 us).
 // With fewer than four steps along K there is too little to cut: K = 128, 64 tiles of 4 to 16 segments whole 5.5, halved 6.7 us (K = 256, 48
 // tiles 7.0 -> 5.9 us).
-template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE>
-__global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArgs g, int n_strips, int n_cu) {
-    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
-    StaleRows stale;
-    if (!FUSED_UP) stale = stale_rows(g);   // in flight during the work, used at the end
-    for (int b = (int)blockIdx.x;;) {       // once, unless the rank has far more rows than its share
+// Rows of tokens b, b + movers, ... to their positions: a row is read once and written k times, AHEAD tokens at a time.  A token's positions
+// wait in the lanes (64 at a time), so that no store waits for a load of its own.
+__device__ __forceinline__ void move_rows(const GemmArgs &g, int b, int movers) {
+    constexpr int AHEAD = 4;
+    const int vecs = g.sc_row_bytes >> 4, n = g.sc_T * g.sc_k, lane = (int)threadIdx.x & 63;   // (n below 2^31)
+    const uint4 *const x = (const uint4 *)g.sc_x;
+    uint4 *const xp = (uint4 *)g.sc_xp;
+    for (int c0 = (int)threadIdx.x & ~63; c0 < vecs; c0 += THREADS) {   // whole wavefronts stay
+        const int c = min(c0 + lane, vecs - 1);
+        const bool store = c0 + lane < vecs;
+        for (int t0 = b; t0 < g.sc_T; t0 += AHEAD * movers)
+            for (int j0 = 0; j0 < g.sc_k; j0 += 64) {
+                uint4 v[AHEAD];
+                int pos[AHEAD];
+#pragma unroll
+                for (int i = 0; i < AHEAD; ++i) {
+                    const int64_t t = min(t0 + i * movers, g.sc_T - 1);
+                    v[i] = x[t * vecs + c];
+                    pos[i] = g.sc_pos[t * g.sc_k + min(j0 + lane, g.sc_k - 1)];
+                }
+#pragma unroll
+                for (int i = 0; i < AHEAD; ++i) {
+                    if (t0 + i * movers >= g.sc_T) break;   // uniform
+                    for (int j = 0; j < min(64, g.sc_k - j0); ++j) {
+                        const int p = __builtin_amdgcn_readlane(pos[i], j);
+                        if (p >= 0 && p < n && store) nt_store16(v[i], &xp[(int64_t)p * vecs + c]);
+                    }
+                }
+            }
+    }
+}
+
+// Workgroup number b of `grid` does its tiles.
+template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE, RowsFrom FROM>
+__device__ __forceinline__ void walk_tiles(const GemmArgs &g, int n_strips, int n_cu, int b, int grid, char *smem) {
+    for (;;) {                              // once, unless the rank has far more rows than its share
         int lane = (int)threadIdx.x & 63;
         asm volatile("" : "+v"(lane));      // the table is read again each time: kept, it would cost the tile its registers
         SegTable<SEG_PER_LANE> segs;
@@ -277,8 +312,8 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArg
         if (b >= blocks) break;
         const int half = b < whole_blocks ? -1 : of_runs(b - whole_blocks, 2 * (total - whole));
         const int t = b < whole_blocks ? of_runs(b, whole) : half < 0 ? -1 : whole + half / 2;
-        const bool again = b >= (int)gridDim.x;
-        b += (int)gridDim.x;
+        const bool again = b >= grid;
+        b += grid;
         const bool more = b < blocks;
         if (t < 0) {
             if (more) continue;
@@ -293,15 +328,56 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArg
         if (again) __syncthreads();   // the tile before has been read
         auto tile = [&](auto nj) {
             constexpr int NJ = decltype(nj)::value;
-            if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6, NJ>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
-            else if (m_end - m0 > 32) tile_body<FUSED_UP, SEG_K, 4, NJ>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
-            else if (m_end > m0) tile_body<FUSED_UP, SEG_K, 2, NJ>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
+            if (m_end - m0 > 64) tile_body<FUSED_UP, SEG_K, 6, NJ, FROM>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
+            else if (m_end - m0 > 32) tile_body<FUSED_UP, SEG_K, 4, NJ, FROM>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
+            else if (m_end > m0) tile_body<FUSED_UP, SEG_K, 2, NJ, FROM>(g, s.slot, m0, m_end, a0, n0, first_step, smem);
         };
         if (half < 0) tile(std::integral_constant<int, 2>{});
         else if (n0 < g.N) tile(std::integral_constant<int, 1>{});
         if (!more) break;   // without reading the table once more (0.3 to 0.6 us of every launch)
     }
-    if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
+}
+
+template <bool FUSED_UP, bool SEG_K, int SEG_PER_LANE>
+__global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_kernel(const GemmArgs g, int n_strips, int n_cu) {
+    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
+    StaleRows stale;
+    if (!FUSED_UP) stale = stale_rows(g);   // in flight during the work, used at the end
+    walk_tiles<FUSED_UP, SEG_K, SEG_PER_LANE, RowsFrom::HERE>(g, n_strips, n_cu, (int)blockIdx.x, (int)gridDim.x, smem);
+    if (FUSED_UP) share_record(g, blockIdx.x == 0); else clear_stale_rows(g, stale);
+}
+
+// Shared experts' and experts' projections in one launch, whose tiles run side by side: neither fills the chip by itself for all of its time, and
+// one launch starts and ends once.  The gate+up launch also moves the dispatch rows: `movers` workgroups, ahead of the others, for which
+// there are places beside the tiles; the experts' tiles read the tokens instead of the rows that are on their way.  Without shared
+// experts (shared_blocks 0) it is the experts' projection and the rows.  Layer steps, a launch each -> joint, us, d = 2048: two shared experts, k = 6, f = 352,
+// 97 tokens 54.7 -> 38.8, 800 68.0 -> 49.3, 3001 101.0 -> 80.8 (rows, shared and experts' gate+up 15.7 + 30 + 12, down 21 + 8.5); f = 1408, 400 tokens
+// 85.1 -> 64.2; four shared experts, k = 4, f = 1408, 400 tokens 145.5 -> 126.2, only the down projections joint 800 184.5 -> 167.5; 1.24 times as fast in the
+// mean of 27.  Without shared experts, k = 8, 512 tokens, f = 512 62.3 -> 59.0, 1000 80.5 -> 76.5; 37 steps of 97 to 3000 tokens 0.97 to 1.08, in the mean 1.033.
+struct Joint {
+    GemmArgs shared, experts;
+    int shared_strips, expert_strips, shared_blocks, movers, n_cu;
+};
+template <bool FUSED_UP, int SEG_PER_LANE>
+__global__ __launch_bounds__(THREADS, 2) void gemm_bf16_mid_joint_kernel(const Joint j) {
+    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
+    StaleRows stale;
+    if (!FUSED_UP) stale = stale_rows(j.experts);
+    int b = (int)blockIdx.x;
+    if (FUSED_UP && b < j.movers) {
+        move_rows(j.experts, b, j.movers);
+        return;
+    }
+    b -= j.movers;
+    if (b < j.shared_blocks) {
+        walk_tiles<FUSED_UP, !FUSED_UP, 1, RowsFrom::HERE>(j.shared, j.shared_strips, j.n_cu, b, j.shared_blocks, smem);
+    } else {
+        b -= j.shared_blocks;
+        walk_tiles<FUSED_UP, false, SEG_PER_LANE, FUSED_UP ? RowsFrom::ASSIGNMENTS : RowsFrom::HERE>(
+            j.experts, j.expert_strips, j.n_cu, b, (int)gridDim.x - j.movers - j.shared_blocks, smem);
+        if (FUSED_UP) share_record(j.experts, b == 0);
+    }
+    if (!FUSED_UP) clear_stale_rows(j.experts, stale);
 }
 
 }  // namespace mid

@@ -169,7 +169,7 @@ __device__ __forceinline__ void persist_body(const GemmArgs g, int n_tiles_n, Se
     };
     // rank-share upkeep of the expert down projection's output (no-op unless the launcher asks for it)
     if (WHO != SHARED) {
-        if (FUSED_UP) share_record(g); else share_clear_stale(g);
+        if (FUSED_UP) share_record(g, blockIdx.x == 0); else share_clear_stale(g);
     }
     // Lane-dependent values that are only needed at tile boundaries are recomputed there from an
     // opaque copy of the lane id: kept live across the K loop they would be spilled to scratch.

@@ -56,10 +56,10 @@ struct GemmArgs {
 };
 constexpr int SHARE_STATE_INTS = 8;
 
-// Up projection, first thread of the grid: what was the current range becomes the previous one, the
+// Up projection, one thread of the grid: what was the current range becomes the previous one, the
 // segments of this step the current one.
-__device__ __forceinline__ void share_record(const GemmArgs &g) {
-    if (!g.share_state || blockIdx.x != 0 || threadIdx.x != 0) return;
+__device__ __forceinline__ void share_record(const GemmArgs &g, bool first_workgroup) {
+    if (!g.share_state || !first_workgroup || threadIdx.x != 0) return;
     const int32_t p0 = g.share_state[4], p1 = g.share_state[5];
     g.share_state[0] = p0;
     g.share_state[1] = p1;

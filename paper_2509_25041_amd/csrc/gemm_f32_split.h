@@ -595,7 +595,7 @@ __global__ __launch_bounds__(256 * K_GROUPS, 2 / K_GROUPS) void gemm_f32_split_k
         }
         if (!more) break;
     }
-    if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
+    if (FUSED_UP) share_record(g, blockIdx.x == 0); else clear_stale_rows(g, stale);
 }
 
 }  // namespace split

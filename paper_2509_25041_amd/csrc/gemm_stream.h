@@ -246,7 +246,7 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void gemm_stream_kernel(const GemmA
         if (m0 > lo) __syncthreads();   // the sums of the rows before have been read
         rows_any<FUSED_UP, EL, MF_MAX>(g, slot, {m0, min(hi, m0 + MF_MAX * 16), activation_row(g, slot, lo, m0), nullptr}, n0, (float4 *)smem);
     }
-    if (FUSED_UP) share_record(g); else clear_stale_rows(g, stale);
+    if (FUSED_UP) share_record(g, blockIdx.x == 0); else clear_stale_rows(g, stale);
 }
 
 // One workgroup per (segment, strip of weight rows, piece of at most MAX_ROWS of the segment's rows), pieces of
@@ -257,7 +257,7 @@ template <bool FUSED_UP, int EL, int SEG_PER_LANE>
 __global__ __launch_bounds__(256, 4) void gemm_stream_tiles_kernel(const GemmArgs g, int n_strips) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = (int)threadIdx.x & 63;
-    if (FUSED_UP) share_record(g); else share_clear_stale(g);
+    if (FUSED_UP) share_record(g, blockIdx.x == 0); else share_clear_stale(g);
     SegTable<SEG_PER_LANE> segs;
     segs.load(g, lane);
     segs.cut(lane, MAX_ROWS);

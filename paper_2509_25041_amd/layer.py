@@ -7,9 +7,9 @@ from typing import List, Optional, Tuple
 
 import torch
 
-from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_dispatch_joins_ffn, grace_ffn_carries_rows, grace_workspace_bytes, load_library
+from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_dispatch_joins_ffn, grace_ffn_carries_rows, grace_ffn_joins_shared, grace_workspace_bytes, load_library
 
-STAGES = ("route", "permute", "route_permute", "dispatch_ffn_up", "ffn_up", "ffn_down", "shared_up", "shared_down", "combine")
+STAGES = ("route", "permute", "route_permute", "dispatch_ffn_up", "ffn_up", "ffn_down", "shared_up", "shared_down", "ffn_shared_up", "ffn_shared_down", "combine")
 
 
 class GraceMoELayer:
@@ -74,6 +74,10 @@ class GraceMoELayer:
         # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows;
         # elsewhere the dispatch call moves them (small batches in its one launch)
         self.gather_rows = not self.n_shared and S > 0 and T > 0 and grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I)
+        # with shared experts: their projections in one launch with the experts' (grace_expert_shared_ffn_up_scatter, _down) where the library
+        # does that; False: a call each
+        self.join_shared = [self.n_shared > 0 and S > 0 and T > 0 and
+                            grace_ffn_joins_shared(up, T, d, f, self.n_shared, self.dt, k=k, S=S, I=table.I) for up in (False, True)]   # down, up
         # the smallest batches: dispatch and the experts' gate+up projection in one launch (grace_dispatch_ffn_up_share), which the two
         # switches above do not concern then; False: the calls above
         self.join_dispatch = S > 0 and T > 0 and grace_dispatch_joins_ffn(table, local_rank, T, k, d, f, self.dt)
@@ -100,7 +104,8 @@ class GraceMoELayer:
         ws = p(self.ws)
         join = self.join_dispatch and self.single_call_dispatch
         fuse = self.fuse_scatter and self.shared is not None and not join
-        xr, xpr = (None, None) if fuse or self.gather_rows else (p(x), p(self.xp))     # rows moved by the dispatch call, or not
+        gather = self.gather_rows and not join
+        xr, xpr = (None, None) if fuse or gather else (p(x), p(self.xp))     # rows moved by the dispatch call, or not
         if join:
             calls = [("dispatch_ffn_up", lib.grace_dispatch_ffn_up_share,
                       (h, lr, self.policy, p(logits), T, self.table.E, k, self.renorm, p(rr_in), p(rr_out), p(te), p(tw), p(ti), p(cnt),
@@ -117,30 +122,38 @@ class GraceMoELayer:
                                                 xpr, ws, st)),
             ]
         if fuse:
-            # the shared gate+up projection first: its hidden activation needs a workspace of its own,
+            # the shared gate+up projection first, or with the experts': its hidden activation needs a workspace of its own,
             # because the expert FFN's hidden activation is written before the shared down projection runs
             sg, su, sd = self.shared
             if self.ws_shared is None:
                 self.ws_shared = torch.empty(grace_workspace_bytes(T, 1, 1, 1, d, f, self.n_shared, dt), dtype=torch.uint8,
                                              device=self.xp.device)
-            calls.append(("shared_up", lib.grace_shared_ffn_up_scatter, (p(x), T, d, f, self.n_shared, dt, p(sg), p(su),
-                                                                        p(self.ws_shared), p(pos), k, p(self.xp), st)))
-        if self.gather_rows:
+            if not self.join_shared[True]:
+                calls.append(("shared_up", lib.grace_shared_ffn_up_scatter, (p(x), T, d, f, self.n_shared, dt, p(sg), p(su),
+                                                                            p(self.ws_shared), p(pos), k, p(self.xp), st)))
+        if fuse and self.join_shared[True]:
+            calls.append(("ffn_shared_up", lib.grace_expert_shared_ffn_up_scatter,
+                          (h, lr, p(x), p(pos), p(src), p(self.xp), p(ioff), T, k, d, f, self.n_shared, dt, p(wg), p(wu), p(sg), p(su),
+                           p(self.y_state), ws, p(self.ws_shared), st)))
+        elif gather:
             calls.append(("ffn_up", lib.grace_expert_ffn_up_share_scatter,
                           (h, lr, p(x), p(pos), p(src), p(self.xp), p(ioff), T, k, d, f, dt, p(wg), p(wu), p(self.y_state), ws, st)))
         elif not join:
             calls.append(("ffn_up", lib.grace_expert_ffn_up_share, (h, lr, p(self.xp), p(ioff), T, k, d, f, dt, p(wg) if S else None,
                                                                     p(wu) if S else None, p(self.y_state), ws, st)))
-        calls += [
-            ("ffn_down", lib.grace_dispatch_ffn_down_share if join else lib.grace_expert_ffn_down_share,
-             (h, lr, p(ioff), T, k, d, f, dt, p(wd) if S else None, p(self.y), p(self.y_state), ws, st)),
-        ]
-        if self.shared is not None:
-            sg, su, sd = self.shared
-            if not fuse:
-                calls.append(("shared_up", lib.grace_shared_ffn_up, (p(x), T, d, f, self.n_shared, dt, p(sg), p(su), ws, st)))
-            calls.append(("shared_down", lib.grace_shared_ffn_down, (T, d, f, self.n_shared, dt, p(sd), p(self.y_shared),
-                                                                     p(self.ws_shared) if fuse else ws, st)))
+        if fuse and self.join_shared[False]:
+            calls.append(("ffn_shared_down", lib.grace_expert_shared_ffn_down,
+                          (h, lr, p(ioff), T, k, d, f, self.n_shared, dt, p(wd), p(sd), p(self.y), p(self.y_shared), p(self.y_state), ws,
+                           p(self.ws_shared), st)))
+        else:
+            calls.append(("ffn_down", lib.grace_dispatch_ffn_down_share if join else lib.grace_expert_ffn_down_share,
+                          (h, lr, p(ioff), T, k, d, f, dt, p(wd) if S else None, p(self.y), p(self.y_state), ws, st)))
+            if self.shared is not None:
+                sg, su, sd = self.shared
+                if not fuse:
+                    calls.append(("shared_up", lib.grace_shared_ffn_up, (p(x), T, d, f, self.n_shared, dt, p(sg), p(su), ws, st)))
+                calls.append(("shared_down", lib.grace_shared_ffn_down, (T, d, f, self.n_shared, dt, p(sd), p(self.y_shared),
+                                                                         p(self.ws_shared) if fuse else ws, st)))
         if self.hosts_all:   # no row to leave out, and finding that out takes 3 to 26 % of the combine
             calls.append(("combine", lib.grace_combine, (p(self.y), p(pos), p(tw), T, k, d, dt, p(self.y_shared), p(self.out), st)))
         else:

@@ -725,3 +725,53 @@ def test_dispatch_joined_with_the_projection(T, E, k, R, spread, policy, d, f, d
             else:
                 assert torch.equal(a, b), (step, name)
         assert torch.isfinite(y.float()).all()
+
+
+@pytest.mark.parametrize("T,E,k,R,n_shared,d,f", [
+    (70, 8, 2, 2, 2, 72, 64),          # rows of nine 16-byte vectors, K segments of a step; few tiles, in halves
+    (333, 16, 4, 4, 1, 512, 352),      # K of half a step past five
+    (3001, 16, 3, 4, 2, 264, 72),      # many tokens for every mover; strips past N; K segments of 72
+    (150, 140, 9, 2, 3, 136, 40),      # more than 64 slots
+    (600, 8, 8, 8, 4, 128, 192),       # every token on every expert
+    (90, 12, 4, 3, 0, 200, 72),        # no shared experts: projection and rows alone
+    (2000, 32, 8, 4, 0, 128, 64),
+])
+def test_shared_and_expert_projections_in_one_launch(T, E, k, R, n_shared, d, f):
+    """The joint launches give what the calls one after the other give, bit for bit, over two steps whose rows move."""
+    rng = np.random.default_rng(T + E)
+    table = grace.GraceTable(E, R, 1, [0] * R, [1] * R, list(range(E + 1)), [e * R // E for e in range(E)])
+    rank, tdt = R - 1, torch.bfloat16
+    S = len(table.local_experts(rank))
+    sizes = dict(k=k, S=S, I=E)
+    if n_shared:
+        assert grace.grace_ffn_joins_shared(True, T, d, f, n_shared, **sizes) and grace.grace_ffn_joins_shared(False, T, d, f, n_shared, **sizes)
+    else:
+        assert grace.grace_ffn_kernel(True, T, d, f, **sizes)[0] == "mid" and grace.grace_ffn_carries_rows(T, d, f, **sizes)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s: (torch.randn(s, generator=gen, device="cuda") * 0.1).to(tdt)
+    w, sh = (normal(S, f, d), normal(S, f, d), normal(S, d, f)), (normal(n_shared, f, d), normal(n_shared, f, d), normal(n_shared, d, f))
+    zeros = lambda *s: torch.zeros(s, dtype=tdt, device="cuda")
+    state, want_state = (torch.zeros(8, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws, want_ws = (torch.empty(grace.grace_workspace_bytes(T, E, k, E, d, f), dtype=torch.uint8, device="cuda") for _ in range(2))
+    ws2, want_ws2 = (torch.empty(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared), dtype=torch.uint8, device="cuda") for _ in range(2))
+    y, want_y, ys, want_ys = zeros(T * k, d), zeros(T * k, d), zeros(T, d), zeros(T, d)
+    for step in range(2):
+        logits = torch.from_numpy(rng.standard_normal((T, E)).astype(np.float32)).cuda()
+        x = normal(T, d)
+        route, (pos, src, ioff, roff, noff, _) = grace.grace_route_permute(table, rank, logits, k, None)
+        xp, want_xp = (torch.full((T * k, d), 7.0, dtype=tdt, device="cuda") for _ in range(2))
+        grace.grace_permute_rows(x, pos, k, want_xp)
+        grace.grace_expert_ffn_up_share(table, rank, want_xp, ioff, T, k, w[0], w[1], want_state, want_ws)
+        grace.grace_expert_ffn_down_share(table, rank, ioff, T, k, w[2], want_y, want_state, want_ws)
+        if n_shared:
+            grace.grace_shared_ffn_up(x, sh[0], sh[1], want_ws2)
+            grace.grace_shared_ffn_down(sh[2], want_ws2, T, want_ys)
+            grace.grace_expert_shared_ffn_up_scatter(table, rank, x, pos, src, xp, ioff, k, w[0], w[1], sh[0], sh[1], state, ws, ws2)
+            grace.grace_expert_shared_ffn_down(table, rank, ioff, T, k, w[2], sh[2], y, ys, state, ws, ws2)
+        else:
+            grace.grace_expert_ffn_up_share_scatter(table, rank, x, pos, src, xp, ioff, k, w[0], w[1], state, ws)
+            grace.grace_expert_ffn_down_share(table, rank, ioff, T, k, w[2], y, state, ws)
+        torch.cuda.synchronize()
+        for name, a, b in (("xp", xp, want_xp), ("y", y, want_y), ("y_shared", ys, want_ys), ("state", state, want_state)):
+            assert torch.equal(a, b), (step, name)
+        assert torch.isfinite(y.float()).all() and y.abs().max() > 0
