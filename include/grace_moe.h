@@ -333,7 +333,7 @@ int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32
 
 /* grace_permute_rows followed by grace_expert_ffn_up_share on the rows it has moved, as one call: where the large-tile or the 96-row
  * kernel takes the projection, that launch reads the rank's rows from x and moves all rows to xp as it runs
- * (grace_ffn_carries_rows; two launches elsewhere).  Same results as the two calls, bit for bit.
+ * (grace_ffn_carries_rows, grace_ffn_joins_shared; two launches elsewhere).  Same results as the two calls, bit for bit.
  * DEVICE: x [T,d]; perm_pos, perm_src [T*k] and inst_off of grace_permute / grace_route_permute called with x == NULL; xp [T*k,d]. */
 int grace_expert_ffn_up_share_scatter(const grace_table *table, int32_t rank, const void *x, const int32_t *perm_pos,
                                       const int32_t *perm_src, void *xp, const int32_t *inst_off, int32_t T, int32_t k, int32_t d,
@@ -382,8 +382,8 @@ int grace_expert_shared_ffn_up_scatter(const grace_table *table, int32_t rank, c
 int grace_expert_shared_ffn_down(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k, int32_t d, int32_t f,
                                  int32_t n_shared, grace_dtype dt, const void *w_down, const void *shared_down, void *y,
                                  void *y_shared, int32_t *state, void *ws, void *ws_shared, void *stream);
-/* Whether one launch does both gate+up (up 1) or down (up 0) projections of these sizes: S of the table's I instances on the rank;
- * n_cu: compute units (0: of the current device; no device is touched otherwise).  HOST output. */
+/* Whether one launch of the 96-row kernel does both gate+up (up 1) or down (up 0) projections of these sizes, with n_shared == 0 the experts'
+ * gate+up projection and the rows (grace_expert_ffn_up_share_scatter): S of the table's I instances on the rank; n_cu: compute units (0: of the current device; no device is touched otherwise).  HOST output. */
 int grace_ffn_joins_shared(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I, grace_dtype dt,
                            int32_t n_cu, int32_t *joined);
 

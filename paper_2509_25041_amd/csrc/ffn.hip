@@ -839,8 +839,9 @@ extern "C" int grace_expert_shared_ffn_down(const grace_table *table, int32_t ra
 extern "C" int grace_ffn_joins_shared(int32_t up, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared, int32_t S, int32_t I, grace_dtype dt,
                                       int32_t n_cu, int32_t *joined) {
     if (!joined) return fail(GRACE_EINVAL, "ffn_joins_shared: null output");
-    if (T < 1 || k < 1 || S < 0 || I < S || n_cu < 0) return fail(GRACE_EINVAL, "ffn_joins_shared: T=%d, k=%d, S=%d, I=%d, n_cu=%d invalid", T, k, S, I, n_cu);
-    const int rc = shared_ffn_common("ffn_joins_shared", T, d, f, n_shared, dt);
+    if (T < 1 || k < 1 || n_shared < 0 || S < 0 || I < S || n_cu < 0)
+        return fail(GRACE_EINVAL, "ffn_joins_shared: T=%d, k=%d, n_shared=%d, S=%d, I=%d, n_cu=%d invalid", T, k, n_shared, S, I, n_cu);
+    const int rc = shared_ffn_common("ffn_joins_shared", T, d, f, std::max(n_shared, 1), dt);
     if (rc != GRACE_OK) return rc;
     if ((int64_t)T * k > INT32_MAX) return fail(GRACE_ESHAPE, "ffn_joins_shared: T*k exceeds 2^31-1");
     if (n_cu == 0) n_cu = compute_units();
@@ -874,8 +875,6 @@ extern "C" int grace_ffn_carries_rows(int32_t T, int32_t k, int32_t d, int32_t f
     int32_t kernel;
     int64_t work_items;
     const int rc = grace_ffn_kernel(1, T, k, d, f, n_shared, S, I, dt, n_cu, &kernel, &work_items);
-    if (rc == GRACE_OK)
-        *carried = carries_rows((Route)kernel, dt, T, k, d, n_shared == 0) ||
-                   (n_shared == 0 && joins_shared(true, T, k, d, f, 0, S, I, dt, n_cu == 0 ? compute_units() : n_cu));
+    if (rc == GRACE_OK) *carried = carries_rows((Route)kernel, dt, T, k, d, n_shared == 0);
     return rc;
 }

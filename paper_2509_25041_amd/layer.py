@@ -73,7 +73,8 @@ class GraceMoELayer:
         self.fuse_scatter = self.n_shared > 0
         # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows;
         # elsewhere the dispatch call moves them (small batches in its one launch)
-        self.gather_rows = not self.n_shared and S > 0 and T > 0 and grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I)
+        self.gather_rows = not self.n_shared and S > 0 and T > 0 and (
+            grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I) or grace_ffn_joins_shared(True, T, d, f, 0, self.dt, k=k, S=S, I=table.I))
         # with shared experts: their projections in one launch with the experts' (grace_expert_shared_ffn_up_scatter, _down) where the library
         # does that; False: a call each
         self.join_shared = [self.n_shared > 0 and S > 0 and T > 0 and

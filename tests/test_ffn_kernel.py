@@ -134,3 +134,16 @@ def test_row_query_refuses_what_the_kernel_query_refuses():
         with pytest.raises(grace.GraceError):
             grace.grace_ffn_carries_rows(a["T"], a["d"], a["f"], BF16, k=a["k"], S=a["S"], I=a["I"], n_cu=N_CU)
     assert grace.load_library().grace_ffn_carries_rows(4, 1, 64, 64, 0, 1, 1, BF16, N_CU, None) == -1
+
+
+@pytest.mark.parametrize("up,T,k,d,f,n_shared,S,I,dt,want", [
+    (True, 3001, 6, 2048, 352, 2, 2, 69, BF16, True), (False, 3001, 6, 2048, 352, 2, 2, 69, BF16, True),
+    (True, 32768, 6, 2048, 1408, 2, 3, 69, BF16, False),      # large tiles
+    (True, 16, 6, 2048, 1408, 2, 3, 69, BF16, False),         # streamed
+    (True, 200, 4, 2048, 1408, 2, 0, 69, BF16, False),        # no instance here
+    (True, 1000, 4, 1024, 1024, 1, 4, 8, F32, False),
+    (True, 512, 8, 2048, 1024, 0, 16, 66, BF16, True), (False, 512, 8, 2048, 1024, 0, 16, 66, BF16, False),   # the rows: gate+up alone
+    (True, 200, 2, 4096, 3584, 0, 1, 10, BF16, False), (True, 512, 2, 4096, 3584, 0, 1, 10, BF16, True),
+])
+def test_projections_joined_with_the_shared_experts(up, T, k, d, f, n_shared, S, I, dt, want):
+    assert grace.grace_ffn_joins_shared(up, T, d, f, n_shared, dt, k=k, S=S, I=I, n_cu=N_CU) == want

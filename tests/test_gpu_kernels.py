@@ -746,7 +746,7 @@ def test_shared_and_expert_projections_in_one_launch(T, E, k, R, n_shared, d, f)
     if n_shared:
         assert grace.grace_ffn_joins_shared(True, T, d, f, n_shared, **sizes) and grace.grace_ffn_joins_shared(False, T, d, f, n_shared, **sizes)
     else:
-        assert grace.grace_ffn_kernel(True, T, d, f, **sizes)[0] == "mid" and grace.grace_ffn_carries_rows(T, d, f, **sizes)
+        assert grace.grace_ffn_kernel(True, T, d, f, **sizes)[0] == "mid" and grace.grace_ffn_joins_shared(True, T, d, f, 0, **sizes)
     gen = torch.Generator(device="cuda").manual_seed(T)
     normal = lambda *s: (torch.randn(s, generator=gen, device="cuda") * 0.1).to(tdt)
     w, sh = (normal(S, f, d), normal(S, f, d), normal(S, d, f)), (normal(n_shared, f, d), normal(n_shared, f, d), normal(n_shared, d, f))
