@@ -1,10 +1,12 @@
-"""Builds libgrace_moe.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libgrace_moe.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's native calls with g++, in-tree."""
 from __future__ import annotations
 
 import hashlib
 import os
 import subprocess
 import sys
+import sysconfig
+from importlib import metadata, util
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -13,7 +15,7 @@ LIB = os.path.join(HERE, "libgrace_moe.so")
 SOURCES = ["table.cpp", "route.hip", "permute.hip", "combine.hip", "ffn.hip", "gemm_f32_split_up.hip", "gemm_f32_split_down.hip",
            "gemm_f32_split_shared.hip", "calibrate.hip", "sendlist.hip", "route_permute.hip", "ffn_tiny.hip", "ffn_tiny_mid.hip"]
 
-
+CALLS = os.path.join(HERE, "_torch_calls.so")              # the binding's calls that allocate (csrc/torch_calls.cpp)
 STAMP = os.path.join(HERE, "libgrace_moe.stamp")   # digest of the sources the library was built from
 
 
@@ -22,7 +24,7 @@ def source_digest() -> str:
     modification times: a copy of the tree to another machine keeps the answer)."""
     paths = sorted(os.path.join(CSRC, n) for n in os.listdir(CSRC) if n.endswith((".hip", ".h", ".cpp")))
     paths.append(os.path.join(ROOT, "include", "grace_moe.h"))
-    h = hashlib.sha256()
+    h = hashlib.sha256(metadata.version("torch").encode())   # the calls are compiled against it
     for p in paths:
         h.update(os.path.basename(p).encode() + b"\0")
         with open(p, "rb") as fh:
@@ -32,7 +34,7 @@ def source_digest() -> str:
 
 def is_stale() -> bool:
     """True when the library is absent or was built from other sources than the ones in the tree."""
-    if not os.path.exists(LIB) or not os.path.exists(STAMP):
+    if not all(os.path.exists(p) for p in (LIB, CALLS, STAMP)):
         return True
     with open(STAMP) as fh:
         return fh.read().strip() != source_digest()
@@ -54,6 +56,13 @@ def build(verbose: bool = False) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    torch_dir = util.find_spec("torch").submodule_search_locations[0]
+    inc = os.path.join(torch_dir, "include")
+    procs.append(("torch_calls.cpp", subprocess.Popen(
+        ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=1", "-I", os.path.join(ROOT, "include"), "-isystem", inc,
+         "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+         os.path.join(CSRC, "torch_calls.cpp"), "-o", CALLS, "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"],
+        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -64,7 +73,7 @@ def build(verbose: bool = False) -> str:
         elif verbose and out:
             print(out)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compilation failed")
     digest = source_digest()
     link = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(link, check=True)

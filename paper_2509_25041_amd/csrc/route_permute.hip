@@ -217,7 +217,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_kernel(
 
 // The smallest batches: top-k, index work and row movement in one launch (route_tiny.h).  Three launches of 2 to 7 us each wait for one
 // another's first loads there, while all the index work of 64 tokens is a few microseconds for one workgroup.  A wavefront takes a token in
-// the gate, four past 16 tokens, or 64 of up to 16 experts (256 tokens of 8 experts, k = 2, four at a time 9.5, 64 at a time 6.2 us).
+// the gate, four past 16 tokens, or 64 of up to 16 experts where four would take more than one pass (256 tokens of 8 experts, k = 2, four at a time 9.5, 64 at a time 6.2 us).
 // Layer steps, the three launches -> this one (1, 16, 64 tokens): 64 experts, k = 8 24.3 -> 20.8, 30.6 -> 25.0, 38.0 -> 33.9 us; 8 experts, k = 2
 // 22.8 -> 17.8, 30.8 -> 27.2, 34.9 -> 30.5 us; 128 experts, k = 8 22.8 -> 18.8, 31.1 -> 24.0 us.  Where the line lies: every workgroup
 // repeats the gate of all tokens, so the call (replayed from a graph) gains less with each.  96 tokens, 64 experts, k = 3, 4, 5, 6, 8: three
@@ -246,7 +246,7 @@ static int route_permute_impl(const grace_table *table, int32_t local_rank, grac
     const int32_t *cand_ptr = table->d_cand_ptr + (size_t)view * E;
     if (tiny_batch(T, k, E, table->I)) {
         int waves = 4;   // a thread per expert and instance, a wavefront per 64 assignments and, up to the most, per token or four
-        const bool lanes = E <= TINY_LANE_E && T > TINY_MAX_WAVES, rows = E <= 64 && T > TINY_MAX_WAVES && !lanes;
+        const bool lanes = E <= TINY_LANE_E && T > 4 * TINY_MAX_WAVES, rows = E <= 64 && T > TINY_MAX_WAVES && !lanes;
         while (!lanes && waves < TINY_MAX_WAVES && waves * (rows ? 4 : 1) < T) waves *= 2;
         while (waves * 64 < T * k) waves *= 2;
         auto launch = [&](auto vpl) {

@@ -155,3 +155,21 @@ def test_caller_tensors_are_checked_before_a_kernel_writes_them():
                             ("w_gate", a["w_gate"].float(), "one dtype"), ("state", a["state"][:7], "state"), ("ws", a["ws"][:64], "workspace")):
         with pytest.raises(ValueError, match=said):
             grace.grace_expert_ffn_up_share_scatter(table, 0, **{**a, name: bad})
+
+
+def test_native_calls_refuse_what_the_binding_refuses():
+    """Checked before the library is reached: no device, and no table, is needed."""
+    calls = binding._native()
+    logits, inst = torch.zeros(3, 4), torch.zeros((3, 2), dtype=torch.int32)
+    refused = [(calls.route, (0, 4, 0, logits, 2, 1, None, None, 0, 0)), (calls.route, (0, 4, 0, logits.double(), 2, 1, None, None, 0, 0)),
+               (calls.route, (0, 4, 0, logits[0], 2, 1, None, None, 0, 0)), (calls.permute, (0, 4, 4, 2, 1, inst, None, 0)),
+               (calls.permute, (0, 4, 4, 2, 1, inst, logits.double(), 0)), (calls.send_lists, (0, 4, 4, 2, 1, 0, inst, 0)),
+               (calls.route_permute, (0, 4, 2, 1, 0, logits, 2, None, 1, None, None, 0, 0)),
+               (calls.route_permute, (0, 4, 2, 1, 0, logits, 2, logits[0], 1, None, None, 0, 0))]
+    for f, args in refused:
+        with pytest.raises(ValueError):
+            f(*args)
+    with pytest.raises(TypeError):
+        calls.route(0, 4, 0, None, 2, 1, None, None, 0, 0)
+    with pytest.raises(TypeError):
+        calls.permute(0)

@@ -333,6 +333,32 @@ def test_route_permute_positions_from_request_numbers(E, k, T, R, spread, policy
     check_route_permute(run_fused(wl, pl, k, 1, rr_in=rr_in, policy=policy, fold_limits=limits), ref, wl, k)
 
 
+def test_native_calls_give_what_the_calls_on_given_buffers_give():
+    """Outputs and workspace allocated by the native calls, or passed through Python."""
+    cfg = CONFIGS["qwen"]
+    wl = make_workload(cfg, T=700)
+    table = grace.GraceTable.from_placement(wl.placement)
+    logits, x = dev(wl.logits), dev(wl.x)
+    rr = torch.arange(cfg.E, dtype=torch.int32, device="cuda")
+    rout = [torch.empty_like(rr) for _ in range(3)]
+    ws = lambda: torch.empty(grace.grace_workspace_bytes(700, cfg.E, cfg.k, table.I), dtype=torch.uint8, device="cuda")
+    a = grace.grace_route(table, 3, logits, cfg.k, 0, rr, rout[0], policy=1)
+    b = grace.grace_route(table, 3, logits, cfg.k, 0, rr, rout[1], ws=ws(), policy=1)
+    c, cp = grace.grace_route_permute(table, 3, logits, cfg.k, x, 0, rr, rout[2], policy=1)
+    pa, pb = grace.grace_permute(table, a[2], x), grace.grace_permute(table, a[2], x, ws=ws())
+    la, lb = grace.grace_send_lists(table, 3, a[2]), grace.grace_send_lists(table, 3, a[2], ws=ws())
+    torch.cuda.synchronize()
+    for got, want in ((a, b), (c, b), (pa, pb), (cp, pb), (la, lb), (rout, rout[1:] + rout[:1])):
+        assert len(got) == len(want)
+        for g, w in zip(got, want):
+            assert g.dtype == w.dtype and g.device == w.device and torch.equal(g, w)
+    assert grace.grace_permute(table, a[2], None)[5] is None
+    with pytest.raises(grace.GraceError):
+        grace.grace_route(table, 99, logits, cfg.k)
+    with pytest.raises(ValueError):
+        grace.grace_route(table, 3, logits.t(), cfg.k)
+
+
 def test_empty_call_and_argument_errors():
     cfg = CONFIGS["tiny"]
     wl = make_workload(cfg)
