@@ -33,6 +33,7 @@ KERNEL_OF_STAGE = {
     "ffn_down": "gemm_bf16_persist_kernel<false, *, EXPERTS> (grouped down projection)",
     "shared_up": "gemm_bf16_persist_kernel<true, 1, SHARED> (shared experts' gate+up projection, fused SwiGLU; carries the row scatter)",
     "shared_down": "gemm_bf16_persist_kernel<false, 1, SHARED> (shared experts' down projection)",
+    "ffn_down_combine": "tiny_down_kernel (down projections and combine)",
     "ffn_shared_up": "gemm_bf16_mid_joint_kernel<true, *> (experts' and shared experts' gate+up projections, with the row scatter)",
     "ffn_shared_down": "gemm_bf16_mid_joint_kernel<false, *> (experts' and shared experts' down projections)",
     "combine": "combine_share_kernel (weighted gather of the rank's rows to token order)",
@@ -186,7 +187,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
     # algorithmic work per launch of the kernel behind each call: (bound, amount, unit scale, peak)
     work = {
         "ffn_up": ("mfma", 4.0 * d * f * m_loc), "ffn_down": ("mfma", 2.0 * d * f * m_loc),
-        "dispatch_ffn_up": ("mfma", 4.0 * d * f * m_loc),
+        "dispatch_ffn_up": ("mfma", 4.0 * d * f * (m_loc + cfg.n_shared * T)), "ffn_down_combine": ("mfma", 2.0 * d * f * (m_loc + cfg.n_shared * T)),
         "ffn_shared_up": ("mfma", 4.0 * d * f * (m_loc + cfg.n_shared * T)), "ffn_shared_down": ("mfma", 2.0 * d * f * (m_loc + cfg.n_shared * T)),
         "shared_up": ("mfma", 4.0 * d * f * cfg.n_shared * T), "shared_down": ("mfma", 2.0 * d * f * cfg.n_shared * T),
         "combine": ("hbm", float(bytes_combine)), "route_permute": ("hbm", float(bytes_dispatch)),

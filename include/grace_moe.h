@@ -312,24 +312,30 @@ int grace_expert_ffn_down_share(const grace_table *table, int32_t rank, const in
                                 int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state,
                                 void *ws, void *stream);
 
-/* grace_route_permute followed by grace_expert_ffn_up_share (rank = local_rank) as one call, and the down projection that belongs
- * to it: for the smallest batches, where the weight-streaming kernel takes the projection (grace_dispatch_joins_ffn), the dispatch and the
- * projection are one launch that lays the hidden activation out in ws by slots (row j of slot s at row s * T + j of [S * T, f]), which
- * _down_share then expects; the two launches and their layout elsewhere.  The same sizes, table and rank in both calls.  Same
- * results as grace_route_permute, grace_expert_ffn_up_share and grace_expert_ffn_down_share, bit for bit.
- * DEVICE: as for these; x is not NULL (unless T == 0). */
+/* A step in two calls, for the smallest batches: grace_route_permute, grace_expert_ffn_up_share (rank = local_rank) and grace_shared_ffn_up
+ * (n_shared > 0), and grace_expert_ffn_down_share, grace_shared_ffn_down and the combine (grace_combine if the rank hosts every instance, else
+ * grace_combine_share).  Where the weight-streaming or the 96-row kernel takes the experts' gate+up projection (grace_dispatch_joins_ffn),
+ * the dispatch and the projection are one launch that lays the hidden activation out in ws by slots (row j of slot s at row s * T + j of
+ * [S * T, f]), which _down_share then expects, and which takes the shared experts' projection along if that is streamed as well; up to 16
+ * tokens the down projections and the combine can be one launch.  Elsewhere it is the calls one after the other; with out == NULL the combine is left
+ * to the caller.  The same sizes, table
+ * and rank in both calls.  Same results as the calls', those behind the gate+up projections up to the order of their sums.
+ * DEVICE: as for these; x is not NULL (unless T == 0); shared pointers and y_shared are not used if n_shared == 0. */
 int grace_dispatch_ffn_up_share(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T, int32_t E,
                                 int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out, int32_t *topk_expert,
                                 float *topk_weight, int32_t *topk_inst, int32_t *expert_count, const void *x, int32_t d, int32_t f,
-                                grace_dtype dt, int32_t *perm_pos, int32_t *perm_src, int32_t *inst_off, int32_t *rank_off,
-                                int32_t *node_off, void *xp, const void *w_gate, const void *w_up, int32_t *state, void *ws,
+                                int32_t n_shared, grace_dtype dt, int32_t *perm_pos, int32_t *perm_src, int32_t *inst_off,
+                                int32_t *rank_off, int32_t *node_off, void *xp, const void *w_gate, const void *w_up,
+                                const void *shared_gate, const void *shared_up, int32_t *state, void *ws, void *ws_shared,
                                 void *stream);
-int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T, int32_t k, int32_t d,
-                                  int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state, void *ws, void *stream);
-/* Whether one launch does the dispatch and the gate+up projection of these sizes.  n_cu: compute units (0: of the current device;
- * no device is touched otherwise).  HOST output. */
-int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt,
-                             int32_t n_cu, int32_t *joined);
+int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, const int32_t *perm_pos,
+                                  const float *topk_weight, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared,
+                                  grace_dtype dt, const void *w_down, const void *shared_down, void *y, void *y_shared,
+                                  int32_t *state, void *ws, void *ws_shared, void *out, void *stream);
+/* Whether one launch does the dispatch and the experts' gate+up projection of these sizes: 0, no; 1, yes; 2, yes, and one does the down
+ * projections and the combine.  n_cu: compute units (0: of the current device; no device is touched otherwise).  HOST output. */
+int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared,
+                             grace_dtype dt, int32_t n_cu, int32_t *joined);
 
 /* grace_permute_rows followed by grace_expert_ffn_up_share on the rows it has moved, as one call: where the large-tile or the 96-row
  * kernel takes the projection, that launch reads the rank's rows from x and moves all rows to xp as it runs

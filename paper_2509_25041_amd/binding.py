@@ -87,13 +87,13 @@ def load_library() -> C.CDLL:
     lib.grace_combine_share.argtypes = [vp, vp, vp, i32, i32, i32, C.c_int, vp, vp, vp, vp]
     lib.grace_mfma_sustained.argtypes = [i32, i32, C.POINTER(C.c_double), vp]
     lib.grace_ffn_kernel.argtypes = [i32] * 8 + [C.c_int, i32, C.POINTER(i32), C.POINTER(C.c_int64)]
-    lib.grace_dispatch_ffn_up_share.argtypes = [vp, i32, C.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, i32, i32, C.c_int, vp, vp, vp,
-                                                vp, vp, vp, vp, vp, vp, vp, vp]
-    lib.grace_dispatch_ffn_down_share.argtypes = lib.grace_expert_ffn_down_share.argtypes
+    lib.grace_dispatch_ffn_up_share.argtypes = [vp, i32, C.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, i32, i32, i32, C.c_int,
+                                                vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.grace_dispatch_ffn_down_share.argtypes = [vp, i32, vp, vp, vp, i32, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.grace_expert_shared_ffn_up_scatter.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.grace_expert_shared_ffn_down.argtypes = [vp, i32, vp, i32, i32, i32, i32, i32, C.c_int, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.grace_ffn_joins_shared.argtypes = [i32] * 8 + [C.c_int, i32, vp]
-    lib.grace_dispatch_joins_ffn.argtypes = [vp, i32, i32, i32, i32, i32, C.c_int, i32, vp]
+    lib.grace_dispatch_joins_ffn.argtypes = [vp, i32, i32, i32, i32, i32, i32, C.c_int, i32, vp]
     lib.grace_ffn_carries_rows.argtypes = [i32, i32, i32, i32, i32, i32, i32, C.c_int, i32, vp]
     for name in EXPORTS:
         if name not in ("grace_last_error", "grace_workspace_bytes"):
@@ -468,12 +468,23 @@ def grace_expert_ffn_down_share(table: GraceTable, rank: int, inst_off: torch.Te
                                                       _dp(w_down) if S else None, _dp(y), _dp(state), _dp(ws), _stream()))
 
 
+def _shared_weights(shared, n: int, d: int, f: int, dtype: torch.dtype) -> int:
+    """Checked shared weights (`n` of them: gate and up [n,f,d], or down [n,d,f]); how many experts they are."""
+    if shared is None:
+        return 0
+    want = (shared[0].shape[0],) + ((f, d) if n == 2 else (d, f))
+    if any(tuple(w.shape) != want or w.dtype != dtype for w in shared):
+        raise ValueError("shared weights must be [n,f,d] (gate, up) and [n,d,f] (down) of one dtype")
+    return want[0]
+
+
 def grace_dispatch_ffn_up_share(table: GraceTable, local_rank: int, logits: torch.Tensor, k: int, x: torch.Tensor, w_gate: torch.Tensor,
                                 w_up: torch.Tensor, state: torch.Tensor, ws: torch.Tensor, renorm: int = 1,
                                 rr_in: Optional[torch.Tensor] = None, rr_out: Optional[torch.Tensor] = None,
-                                policy: int = GRACE_POLICY_TAR):
-    """grace_route_permute and grace_expert_ffn_up_share of the local rank as one call (one launch for the smallest batches); its
-    down projection is grace_dispatch_ffn_down_share.  -> what grace_route_permute returns; see grace_moe.h."""
+                                policy: int = GRACE_POLICY_TAR, shared: Optional[Tuple[torch.Tensor, torch.Tensor]] = None,
+                                ws_shared: Optional[torch.Tensor] = None):
+    """Dispatch and gate+up projections of the local rank as one call (one launch for the smallest batches), `shared` = the shared
+    experts' (gate, up); the rest of the step is grace_dispatch_ffn_down_share.  -> what grace_route_permute returns; see grace_moe.h."""
     _need(state, "state", torch.int32, SHARE_STATE_INTS)
     T, E = logits.shape
     S, f, d = w_gate.shape
@@ -482,34 +493,52 @@ def grace_dispatch_ffn_up_share(table: GraceTable, local_rank: int, logits: torc
     if tuple(x.shape) != (T, d) or tuple(w_up.shape) != (S, f, d) or w_gate.dtype != x.dtype or w_up.dtype != x.dtype:
         raise ValueError("x must be [T,d], w_gate and w_up [S,f,d], of one dtype")
     dt, dev = _dtype_code(x), logits.device
+    n_shared = _shared_weights(shared, 2, d, f, x.dtype)
     _ws(ws, grace_workspace_bytes(T, E, max(k, 1), table.I, d, f, 0, dt), dev)
+    if n_shared:
+        _ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt), dev)
     i32 = dict(dtype=torch.int32, device=dev)
     te, tw = torch.empty((T, k), **i32), torch.empty((T, k), dtype=torch.float32, device=dev)
     ti, cnt = torch.empty((T, k), **i32), torch.empty((E,), **i32)
     pos, src = torch.empty(T * k, **i32), torch.empty(T * k, **i32)
     ioff, roff, noff = torch.empty(table.I + 1, **i32), torch.empty(table.R + 1, **i32), torch.empty(table.N + 1, **i32)
     xp = torch.empty((T * k, d), dtype=x.dtype, device=dev)
+    sg, su = shared if n_shared else (None, None)
     _check(load_library().grace_dispatch_ffn_up_share(
         table.handle, local_rank, policy, _dp(logits), T, E, k, renorm, _dp(rr_in), _dp(rr_out), _dp(te), _dp(tw), _dp(ti), _dp(cnt), _dp(x), d,
-        f, dt, _dp(pos), _dp(src), _dp(ioff), _dp(roff), _dp(noff), _dp(xp), _dp(w_gate) if S else None, _dp(w_up) if S else None,
-        _dp(state), _dp(ws), _stream()))
+        f, n_shared, dt, _dp(pos), _dp(src), _dp(ioff), _dp(roff), _dp(noff), _dp(xp), _dp(w_gate) if S else None, _dp(w_up) if S else None,
+        _dp(sg), _dp(su), _dp(state), _dp(ws), _dp(ws_shared), _stream()))
     return (te, tw, ti, cnt), (pos, src, ioff, roff, noff, xp)
 
 
-def grace_dispatch_ffn_down_share(table: GraceTable, rank: int, inst_off: torch.Tensor, T: int, k: int, w_down: torch.Tensor,
-                                  y: torch.Tensor, state: torch.Tensor, ws: torch.Tensor) -> None:
-    """grace_expert_ffn_down_share behind grace_dispatch_ffn_up_share; see grace_moe.h."""
+def grace_dispatch_ffn_down_share(table: GraceTable, rank: int, inst_off: torch.Tensor, perm_pos: torch.Tensor, topk_weight: torch.Tensor,
+                                  w_down: torch.Tensor, y: torch.Tensor, state: torch.Tensor, ws: torch.Tensor,
+                                  shared_down: Optional[torch.Tensor] = None, y_shared: Optional[torch.Tensor] = None,
+                                  ws_shared: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Down projections and combine behind grace_dispatch_ffn_up_share -> out [T,d]; see grace_moe.h."""
     _need(state, "state", torch.int32, SHARE_STATE_INTS)
+    T, k = topk_weight.shape
     S, d, f = w_down.shape
-    _check(load_library().grace_dispatch_ffn_down_share(table.handle, rank, _dp(inst_off), T, k, d, f, _dtype_code(y),
-                                                        _dp(w_down) if S else None, _dp(y), _dp(state), _dp(ws), _stream()))
+    _need(topk_weight, "topk_weight", torch.float32, T * k)
+    _need(perm_pos, "perm_pos", torch.int32, T * k)
+    _need(y, "y", w_down.dtype, T * k * d)
+    n_shared = _shared_weights(None if shared_down is None else (shared_down,), 1, d, f, w_down.dtype)
+    if n_shared:
+        _need(y_shared, "y_shared", w_down.dtype, T * d)
+    if out is None:
+        out = torch.empty((T, d), dtype=y.dtype, device=y.device)
+    _check(load_library().grace_dispatch_ffn_down_share(
+        table.handle, rank, _dp(inst_off), _dp(perm_pos), _dp(topk_weight), T, k, d, f, n_shared, _dtype_code(y), _dp(w_down) if S else None,
+        _dp(shared_down), _dp(y), _dp(y_shared), _dp(state), _dp(ws), _dp(ws_shared), _dp(out), _stream()))
+    return out
 
 
-def grace_dispatch_joins_ffn(table: GraceTable, local_rank: int, T: int, k: int, d: int, f: int, dt: int = GRACE_BF16, n_cu: int = 0) -> bool:
-    """Does one launch do the dispatch and the gate+up projection (see grace_moe.h)?"""
+def grace_dispatch_joins_ffn(table: GraceTable, local_rank: int, T: int, k: int, d: int, f: int, dt: int = GRACE_BF16, n_cu: int = 0,
+                             n_shared: int = 0) -> int:
+    """Does one launch do the dispatch and the experts' gate+up projection: 0, no; 1, yes; 2, and one the down projections and combine."""
     joined = C.c_int32()
-    _check(load_library().grace_dispatch_joins_ffn(table.handle, local_rank, T, k, d, f, dt, n_cu, C.byref(joined)))
-    return bool(joined.value)
+    _check(load_library().grace_dispatch_joins_ffn(table.handle, local_rank, T, k, d, f, n_shared, dt, n_cu, C.byref(joined)))
+    return joined.value
 
 
 def grace_shared_ffn(x: torch.Tensor, w_gate: torch.Tensor, w_up: torch.Tensor, w_down: torch.Tensor,

@@ -49,7 +49,7 @@ static int compute_units() {
 
 // The persistent kernel needs the 160 KB of dynamic LDS opted in, once per kernel and device.
 static bool allow_full_lds(const void *kernel, const char *what) {
-    constexpr int MAX_KERNELS = 16, MAX_DEVICES = 64;
+    constexpr int MAX_KERNELS = 24, MAX_DEVICES = 64;
     static std::mutex mu;
     static const void *known[MAX_KERNELS] = {nullptr};
     static bool done[MAX_KERNELS][MAX_DEVICES] = {{false}};
@@ -129,10 +129,10 @@ static bool stream_pieces(const Rows &rows) { return EL == 4 && rows.max_rows > 
 // segments, 32 took 10.4, and 32.9 instead of 28.8 us on 16; two wavefronts per workgroup at the other end took 29.5 us.
 static int stream_fragments(const Rows &rows) { return rows.max_rows <= 16 ? 1 : rows.max_rows <= 32 ? 2 : 4; }
 template <bool FUSED_UP, int EL>
-static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu) {
+static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu, int64_t others = 0 /* busy workgroups beside them */) {
     const int64_t n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
     if (stream_pieces<EL>(rows)) return {((rows.m_bound / strm::MAX_ROWS + g.S) * n_strips + 7) / 8 * 8, 256};
-    const int64_t busy = std::min<int64_t>(g.S, rows.m_bound) * n_strips;
+    const int64_t busy = std::min<int64_t>(g.S, rows.m_bound) * n_strips + others;
     int waves = 4;
     // (no more than 64 KB of partial sums: a launch may ask for that much LDS without opting in)
     while (waves < strm::MAX_WAVES && strm::lds_bytes(waves * 2, stream_fragments(rows)) <= 65536 &&
@@ -511,6 +511,8 @@ static int expert_ffn_common(const char *who, const grace_table *table, int32_t 
     return GRACE_OK;
 }
 
+static int shared_ffn_common(const char *who, int32_t T, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt);
+
 // Does the launch of a gate+up projection move the dispatch rows as well?  The large-tile kernel does, rows in whole 1 KB pieces of
 // which a wavefront holds one with the positions of its token, a lane each (up to 64 choices); offsets of positions in 32 bits, and piece
 // numbers (a wavefront looks at four strides of the grid at a time) below 2^31.  The experts' projection reads the tokens themselves then: their
@@ -567,9 +569,10 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
 extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T,
                                            int32_t E, int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out,
                                            int32_t *topk_expert, float *topk_weight, int32_t *topk_inst, int32_t *expert_count,
-                                           const void *x, int32_t d, int32_t f, grace_dtype dt, int32_t *perm_pos, int32_t *perm_src,
-                                           int32_t *inst_off, int32_t *rank_off, int32_t *node_off, void *xp, const void *w_gate,
-                                           const void *w_up, int32_t *state, void *ws, void *stream) {
+                                           const void *x, int32_t d, int32_t f, int32_t n_shared, grace_dtype dt, int32_t *perm_pos,
+                                           int32_t *perm_src, int32_t *inst_off, int32_t *rank_off, int32_t *node_off, void *xp,
+                                           const void *w_gate, const void *w_up, const void *shared_gate, const void *shared_up,
+                                           int32_t *state, void *ws, void *ws_shared, void *stream) {
     const char *const who = "dispatch_ffn_up_share";
     if (!state) return fail(GRACE_EINVAL, "%s: state is null", who);
     if (T > 0 && !x) return fail(GRACE_EINVAL, "%s: x is null", who);
@@ -579,31 +582,51 @@ extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t loc
     rc = check_route_args(table, local_rank, policy, logits, T, E, k, rr_in, rr_out, topk_expert, topk_weight, topk_inst, expert_count, ws);
     if (rc != GRACE_OK) return rc;
     rc = check_permute_args(table, topk_inst, T, k, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws);
+    if (rc == GRACE_OK && n_shared != 0) rc = shared_ffn_common(who, T, d, f, n_shared, dt);
     if (rc != GRACE_OK) return rc;
     const int n_cu = compute_units();
     if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", who);
+    auto shared_alone = [&] { return n_shared ? grace_shared_ffn_up(x, T, d, f, n_shared, dt, shared_gate, shared_up, ws_shared, stream) : GRACE_OK; };
     if (T == 0 || !joins_dispatch(table, local_rank, T, k, d, f, dt, n_cu)) {
         rc = grace_route_permute(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight, topk_inst,
                                  expert_count, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws, stream);
         if (rc != GRACE_OK) return rc;
-        return expert_ffn_up(who, table, local_rank, xp, inst_off, T, k, d, f, dt, w_gate, w_up, state, ws, stream);
+        rc = expert_ffn_up(who, table, local_rank, xp, inst_off, T, k, d, f, dt, w_gate, w_up, state, ws, stream);
+        return rc != GRACE_OK ? rc : shared_alone();
     }
     if (!w_gate || !w_up) return fail(GRACE_EINVAL, "%s: null device pointer", who);
     if ((((uintptr_t)w_gate) | ((uintptr_t)w_up) | ((uintptr_t)ws)) & 15) return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
     const GemmArgs shape = expert_shape(true, S, d, f);
     const Rows rows = expert_rows(S, table->I, T, k);
     const Route route = route_gemm<true>(shape, dt, rows, n_cu);
-    const Grid l = grid_of<true>(route, shape, dt, rows, n_cu);
     const int cols = route == Route::MID ? mid::Shape<true>::BN : strm::Shape<true>::COLS;
     TinyUp a{tiny_args(table, local_rank, policy, logits, T, k, renorm, rr_in, rr_out, topk_expert, topk_weight, topk_inst, expert_count, x, d,
                        dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp),
-             shape, table->d_inst_span + g0, g0, policy == GRACE_POLICY_WRR, (f + cols - 1) / cols};
+             shape, table->d_inst_span + g0, g0, policy == GRACE_POLICY_WRR, (f + cols - 1) / cols, {}, 0};
     a.up.A = x; a.up.B0 = w_gate; a.up.B1 = w_up; a.up.out = ws;
     a.up.share_state = state;
-    if (route == Route::MID) launch_tiny_up_mid(a, n_cu, (hipStream_t)stream);
-    else launch_tiny_up(a, dt, l.threads / 64, dt == GRACE_F32 && stream_pieces<4>(rows), (hipStream_t)stream);
+    const bool pieces = dt == GRACE_F32 && stream_pieces<4>(rows);
+    // the shared experts' tiles run beside the others where they are streamed as well
+    bool with_shared = false;
+    if (n_shared && route == Route::STREAM && T <= strm::MAX_ROWS) {
+        a.shared = shared_shape(true, T, d, f, n_shared);
+        with_shared = route_gemm<true>(a.shared, dt, shared_rows(T), n_cu) == Route::STREAM;
+        if (with_shared) {
+            if (!shared_gate || !shared_up || !ws_shared) return fail(GRACE_EINVAL, "%s: null device pointer", who);
+            if (((uintptr_t)shared_gate | (uintptr_t)shared_up | (uintptr_t)ws_shared) & 15)
+                return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
+            a.shared.A = x; a.shared.B0 = shared_gate; a.shared.B1 = shared_up; a.shared.out = ws_shared;
+            a.shared_strips = (a.shared.N + cols - 1) / cols;
+        }
+    }
+    if (route == Route::MID) {
+        launch_tiny_up_mid(a, n_cu, (hipStream_t)stream);
+    } else {
+        const Grid l = dt == GRACE_BF16 ? stream_grid<true, 2>(shape, rows, n_cu, a.shared_strips) : stream_grid<true, 4>(shape, rows, n_cu, a.shared_strips);
+        launch_tiny_up(a, dt, l.threads / 64, pieces, (hipStream_t)stream);
+    }
     GRACE_LAUNCH_CHECK(who);
-    return GRACE_OK;
+    return with_shared ? GRACE_OK : shared_alone();
 }
 
 extern "C" int grace_expert_ffn_up(const grace_table *table, int32_t rank, const void *xp, const int32_t *inst_off,
@@ -682,22 +705,74 @@ extern "C" int grace_expert_ffn_down_share(const grace_table *table, int32_t ran
     return expert_ffn_down("expert_ffn_down_share", table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream);
 }
 
-extern "C" int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
-                                             int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y,
-                                             int32_t *state, void *ws, void *stream) {
-    if (!state) return fail(GRACE_EINVAL, "dispatch_ffn_down_share: state is null");
-    return expert_ffn_down("dispatch_ffn_down_share", table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream, true);
+// One launch for the down projections and the combine of a joined step (ffn_tiny_down.hip): its operands fit 32-bit offsets and its partial
+// sums the LDS.  A workgroup has 8 or 16 columns of everything to do, so narrow tokens leave compute units idle: with fewer
+// workgroups than 5 for 8 of them it has to be little work each, and more of it where shared experts' own launch goes too.
+// Whole steps, two or three launches -> one, bf16 | fp32, 2 to 16 tokens, rank with half the experts: d >= 1536 1.01 to 1.46 | 0.98 to 1.40 times
+// as fast (f = 1024 to 4096; with 2 shared experts 1.01 to 1.35 | 1.00 to 1.31); d = 1024 with 4 parts 1.09 to 1.24 | 1.08 to 1.25, with 8 to 32
+// 0.90 to 1.07 | 0.87 to 1.08; d = 512 with 4 1.12 to 1.20 | 1.14 to 1.25, with 8 to 32 0.77 to 0.97 | 0.75 to 0.92; with 2 shared
+// experts and 10 to 18 parts d = 1024 1.13 to 1.38 | 1.09 to 1.34, d = 512 1.02 to 1.36 | 0.95 to 1.29.
+static bool joins_combine(int32_t T, int32_t k, int32_t d, int32_t f, int n_shared, int S, grace_dtype dt, int n_cu) {
+    const int64_t row = (int64_t)f * (dt == GRACE_F32 ? 4 : 2);
+    if (T > TINY_DOWN_T || k > GRACE_MAX_TOPK || row % 16 != 0 || 16 * row >= (int64_t)NO_DATA || std::max(n_shared, 1) * T * row >= (int64_t)NO_DATA) return false;
+    if (tiny_down_lds(T, k, S, n_shared, d, n_cu) > pers::LDS_BYTES) return false;
+    const int blocks = tiny_down_blocks(d, n_cu), parts = std::min(S, T * k) + n_shared;
+    return 8 * blocks >= 5 * n_cu || parts <= (n_shared ? std::max(16, blocks / 4) : 4);
 }
 
-extern "C" int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt,
-                                        int32_t n_cu, int32_t *joined) {
+extern "C" int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, const int32_t *perm_pos,
+                                             const float *topk_weight, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared,
+                                             grace_dtype dt, const void *w_down, const void *shared_down, void *y, void *y_shared,
+                                             int32_t *state, void *ws, void *ws_shared, void *out, void *stream) {
+    const char *const who = "dispatch_ffn_down_share";
+    if (!state) return fail(GRACE_EINVAL, "%s: state is null", who);
+    int g0, S;
+    int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
+    if (rc == GRACE_OK && n_shared != 0) rc = shared_ffn_common(who, T, d, f, n_shared, dt);
+    if (rc != GRACE_OK) return rc;
+    const int n_cu = compute_units();
+    if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", who);
+    if (T == 0 || !out || !joins_dispatch(table, rank, T, k, d, f, dt, n_cu) || !joins_combine(T, k, d, f, n_shared, S, dt, n_cu)) {
+        rc = expert_ffn_down(who, table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream, true);
+        if (rc == GRACE_OK && n_shared) rc = grace_shared_ffn_down(T, d, f, n_shared, dt, shared_down, y_shared, ws_shared, stream);
+        if (rc != GRACE_OK || !out) return rc;
+        const void *ys = n_shared ? y_shared : nullptr;
+        return S == table->I ? grace_combine(y, perm_pos, topk_weight, T, k, d, dt, ys, out, stream)
+                             : grace_combine_share(y, perm_pos, topk_weight, T, k, d, dt, ys, state, out, stream);
+    }
+    if (!inst_off || !perm_pos || !topk_weight || !w_down || !y || !ws || (n_shared && (!shared_down || !y_shared || !ws_shared)))
+        return fail(GRACE_EINVAL, "%s: null device pointer", who);
+    uintptr_t at = (uintptr_t)w_down | (uintptr_t)y | (uintptr_t)ws | (uintptr_t)out;
+    if (n_shared) at |= (uintptr_t)shared_down | (uintptr_t)y_shared | (uintptr_t)ws_shared;
+    if (at & 15) return fail(GRACE_EINVAL, "%s: device pointers must be 16-byte aligned", who);
+    TinyDown a{};
+    a.experts = expert_shape(false, S, d, f);
+    a.experts.A = ws; a.experts.B0 = w_down; a.experts.out = y;
+    a.experts.seg_off = inst_off + g0;
+    a.experts.a_slot_rows = T;
+    a.experts.share_state = state; a.experts.stale = 1; a.experts.share_rows = (int64_t)T * k; a.experts.share_row_vec = (int)((size_t)d * (dt == GRACE_F32 ? 4 : 2) / 16);
+    if (n_shared) {
+        a.shared = shared_shape(false, T, d, f, n_shared);
+        a.shared.A = ws_shared; a.shared.B0 = shared_down; a.shared.out = y_shared;
+    }
+    a.perm_pos = perm_pos; a.weight = topk_weight; a.out = out;
+    a.T = T; a.k = k; a.n_shared = n_shared;
+    if (!allow_full_lds(tiny_down_kernel_of(dt, d, n_cu), who)) return GRACE_EHIP;
+    launch_tiny_down(a, dt, tiny_down_lds(T, k, S, n_shared, d, n_cu), n_cu, (hipStream_t)stream);
+    GRACE_LAUNCH_CHECK(who);
+    return GRACE_OK;
+}
+
+extern "C" int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_rank, int32_t T, int32_t k, int32_t d, int32_t f,
+                                        int32_t n_shared, grace_dtype dt, int32_t n_cu, int32_t *joined) {
     if (!joined) return fail(GRACE_EINVAL, "dispatch_joins_ffn: null output");
     int g0, S;
-    const int rc = expert_ffn_common("dispatch_joins_ffn", table, local_rank, T, k, d, f, dt, g0, S);
+    int rc = expert_ffn_common("dispatch_joins_ffn", table, local_rank, T, k, d, f, dt, g0, S);
+    if (rc == GRACE_OK && n_shared != 0) rc = shared_ffn_common("dispatch_joins_ffn", T, d, f, n_shared, dt);
     if (rc != GRACE_OK) return rc;
     if (n_cu == 0) n_cu = compute_units();
     if (n_cu <= 0) return fail(GRACE_EHIP, "dispatch_joins_ffn: cannot query the device");
-    *joined = T > 0 && joins_dispatch(table, local_rank, T, k, d, f, dt, n_cu);
+    *joined = T == 0 || !joins_dispatch(table, local_rank, T, k, d, f, dt, n_cu) ? 0 : joins_combine(T, k, d, f, n_shared, S, dt, n_cu) ? 2 : 1;
     return GRACE_OK;
 }
 

@@ -12,6 +12,8 @@ struct TinyUp {
     int slot0;                // instance id of the first one
     int several;              // the replica pick is among all instances (else every local expert's requests are the local instance's)
     int n_strips;
+    GemmArgs shared;          // shared experts' gate+up projection by the same launch (shared_strips 0: none)
+    int shared_strips;
 };
 
 // The record that the down projection's launch reads (share_record).
@@ -123,5 +125,20 @@ void launch_tiny_up(const TinyUp &a, grace_dtype dt, int waves, bool pieces, hip
 int64_t tiny_up_mid_blocks(int S, int K, int n_strips, int n_cu);
 // up to 96 tokens
 void launch_tiny_up_mid(const TinyUp &a, int n_cu, hipStream_t st);
+
+// The down projections and the combine of up to TINY_DOWN_T tokens (ffn_tiny_down.hip).
+constexpr int TINY_DOWN_T = 16;
+struct TinyDown {
+    GemmArgs experts, shared;   // hidden activations laid out by slots; the shared experts' K axis is cut in segments of K
+    const int32_t *perm_pos;
+    const float *weight;
+    void *out;
+    int T, k, n_shared;
+    int items_most;   // (the launcher's)
+};
+int tiny_down_lds(int T, int k, int S, int n_shared, int N, int n_cu);   // bytes
+int tiny_down_blocks(int N, int n_cu);   // workgroups
+const void *tiny_down_kernel_of(grace_dtype dt, int N, int n_cu);
+void launch_tiny_down(const TinyDown &a, grace_dtype dt, int lds, int n_cu, hipStream_t st);
 
 }  // namespace grace

@@ -29,6 +29,11 @@ __global__ __launch_bounds__(64 * strm::MAX_WAVES) void tiny_up_kernel(const Tin
         tiny_share_record(a, s);
         return;
     }
+    if (!PIECES) {
+        const int strip = (int)blockIdx.x - T - a.up.S * a.n_strips;
+        if (strip >= 0)
+            return strm::rows_any<true, EL, MF>(a.shared, 0, {0, T, 0, nullptr}, strip * strm::Shape<true>::COLS, (float4 *)smem);
+    }
     TinyRows &s = *(TinyRows *)smem;
     const int pieces = PIECES ? (T + strm::MAX_ROWS - 1) / strm::MAX_ROWS : 1, b = (int)blockIdx.x - T;
     int slot, strip, piece = 0;
@@ -58,7 +63,7 @@ void launch_tiny_up(const TinyUp &a, grace_dtype dt, int waves, bool pieces, hip
     const int T = a.dispatch.T, E = a.dispatch.E;
     const int mf = pieces ? 4 : T <= 16 ? 1 : T <= 32 ? 2 : 4;
     const int lds = std::max((int)sizeof(TinyLds), ROWS_BYTES + strm::lds_bytes(waves, mf));
-    const int blocks = pieces ? (a.up.S * a.n_strips * ((T + strm::MAX_ROWS - 1) / strm::MAX_ROWS) + 7) / 8 * 8 : a.up.S * a.n_strips;
+    const int blocks = pieces ? (a.up.S * a.n_strips * ((T + strm::MAX_ROWS - 1) / strm::MAX_ROWS) + 7) / 8 * 8 : a.up.S * a.n_strips + a.shared_strips;
     auto launch = [&](auto kernel) { kernel<<<(unsigned)(T + blocks), waves * 64, lds, st>>>(a); };
     auto by_rows = [&](auto vpl, auto gate, auto el) {
         constexpr int VPL = decltype(vpl)::value, EL = decltype(el)::value;

@@ -9,7 +9,7 @@ import torch
 
 from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream, grace_dispatch_joins_ffn, grace_ffn_carries_rows, grace_ffn_joins_shared, grace_workspace_bytes, load_library
 
-STAGES = ("route", "permute", "route_permute", "dispatch_ffn_up", "ffn_up", "ffn_down", "shared_up", "shared_down", "ffn_shared_up", "ffn_shared_down", "combine")
+STAGES = ("route", "permute", "route_permute", "dispatch_ffn_up", "ffn_up", "ffn_down", "shared_up", "shared_down", "ffn_shared_up", "ffn_shared_down", "ffn_down_combine", "combine")
 
 
 class GraceMoELayer:
@@ -25,7 +25,7 @@ class GraceMoELayer:
     in a HIP graph).  The combine relies on it and does not read them
     (grace_combine_share), unless the rank hosts every instance.
 
-    All buffers are allocated once; a step is three to six C calls whose argument lists
+    All buffers are allocated once; a step is two to six C calls whose argument lists
     are marshalled once per (logits, x, rr_in, rr_out, stream) and reused, so the
     host cost of a step is a few microseconds per call.
     """
@@ -79,9 +79,10 @@ class GraceMoELayer:
         # does that; False: a call each
         self.join_shared = [self.n_shared > 0 and S > 0 and T > 0 and
                             grace_ffn_joins_shared(up, T, d, f, self.n_shared, self.dt, k=k, S=S, I=table.I) for up in (False, True)]   # down, up
-        # the smallest batches: dispatch and the experts' gate+up projection in one launch (grace_dispatch_ffn_up_share), which the two
-        # switches above do not concern then; False: the calls above
-        self.join_dispatch = S > 0 and T > 0 and grace_dispatch_joins_ffn(table, local_rank, T, k, d, f, self.dt)
+        # the smallest batches: dispatch and gate+up projections in one call and launch, the down projections in another, with the combine where
+        # that is one launch (grace_dispatch_ffn_up_share, _down_share); the switches above do not concern these then; False: the calls above
+        joined = grace_dispatch_joins_ffn(table, local_rank, T, k, d, f, self.dt, n_shared=self.n_shared) if S > 0 and T > 0 else 0
+        self.join_dispatch, self.join_combine = joined > 0, joined > 1
         self.ws_shared = None
         self._key = None
         self._calls: List[Tuple[str, object, tuple]] = []
@@ -104,14 +105,25 @@ class GraceMoELayer:
         S = wg.shape[0]
         ws = p(self.ws)
         join = self.join_dispatch and self.single_call_dispatch
-        fuse = self.fuse_scatter and self.shared is not None and not join
-        gather = self.gather_rows and not join
-        xr, xpr = (None, None) if fuse or gather else (p(x), p(self.xp))     # rows moved by the dispatch call, or not
+        fuse = self.fuse_scatter and self.shared is not None
+        xr, xpr = (None, None) if fuse or self.gather_rows else (p(x), p(self.xp))     # rows moved by the dispatch call, or not
+        if self.hosts_all:   # no row to leave out, and finding that out takes 3 to 26 % of the combine
+            combine = "combine", lib.grace_combine, (p(self.y), p(pos), p(tw), T, k, d, dt, p(self.y_shared), p(self.out), st)
+        else:
+            combine = "combine", lib.grace_combine_share, (p(self.y), p(pos), p(tw), T, k, d, dt, p(self.y_shared), p(self.y_state), p(self.out), st)
         if join:
+            sg, su, sd = self.shared if self.n_shared else (None, None, None)
+            if self.n_shared and self.ws_shared is None:
+                self.ws_shared = torch.empty(grace_workspace_bytes(T, 1, 1, 1, d, f, self.n_shared, dt), dtype=torch.uint8, device=self.xp.device)
             calls = [("dispatch_ffn_up", lib.grace_dispatch_ffn_up_share,
                       (h, lr, self.policy, p(logits), T, self.table.E, k, self.renorm, p(rr_in), p(rr_out), p(te), p(tw), p(ti), p(cnt),
-                       p(x), d, f, dt, p(pos), p(src), p(ioff), p(roff), p(noff), p(self.xp), p(wg), p(wu), p(self.y_state), ws, st))]
-        elif self.single_call_dispatch:
+                       p(x), d, f, self.n_shared, dt, p(pos), p(src), p(ioff), p(roff), p(noff), p(self.xp), p(wg), p(wu), p(sg), p(su),
+                       p(self.y_state), ws, p(self.ws_shared), st)),
+                     ("ffn_down_combine" if self.join_combine else "ffn_down", lib.grace_dispatch_ffn_down_share,
+                      (h, lr, p(ioff), p(pos), p(tw), T, k, d, f, self.n_shared, dt, p(wd), p(sd), p(self.y), p(self.y_shared),
+                       p(self.y_state), ws, p(self.ws_shared), p(self.out) if self.join_combine else None, st))]
+            return calls if self.join_combine else calls + [combine]
+        if self.single_call_dispatch:
             calls = [("route_permute", lib.grace_route_permute,
                       (h, lr, self.policy, p(logits), T, self.table.E, k, self.renorm, p(rr_in), p(rr_out), p(te), p(tw),
                        p(ti), p(cnt), xr, d, dt, p(pos), p(src), p(ioff), p(roff), p(noff), xpr, ws, st))]
@@ -136,10 +148,10 @@ class GraceMoELayer:
             calls.append(("ffn_shared_up", lib.grace_expert_shared_ffn_up_scatter,
                           (h, lr, p(x), p(pos), p(src), p(self.xp), p(ioff), T, k, d, f, self.n_shared, dt, p(wg), p(wu), p(sg), p(su),
                            p(self.y_state), ws, p(self.ws_shared), st)))
-        elif gather:
+        elif self.gather_rows:
             calls.append(("ffn_up", lib.grace_expert_ffn_up_share_scatter,
                           (h, lr, p(x), p(pos), p(src), p(self.xp), p(ioff), T, k, d, f, dt, p(wg), p(wu), p(self.y_state), ws, st)))
-        elif not join:
+        else:
             calls.append(("ffn_up", lib.grace_expert_ffn_up_share, (h, lr, p(self.xp), p(ioff), T, k, d, f, dt, p(wg) if S else None,
                                                                     p(wu) if S else None, p(self.y_state), ws, st)))
         if fuse and self.join_shared[False]:
@@ -147,7 +159,7 @@ class GraceMoELayer:
                           (h, lr, p(ioff), T, k, d, f, self.n_shared, dt, p(wd), p(sd), p(self.y), p(self.y_shared), p(self.y_state), ws,
                            p(self.ws_shared), st)))
         else:
-            calls.append(("ffn_down", lib.grace_dispatch_ffn_down_share if join else lib.grace_expert_ffn_down_share,
+            calls.append(("ffn_down", lib.grace_expert_ffn_down_share,
                           (h, lr, p(ioff), T, k, d, f, dt, p(wd) if S else None, p(self.y), p(self.y_state), ws, st)))
             if self.shared is not None:
                 sg, su, sd = self.shared
@@ -155,12 +167,7 @@ class GraceMoELayer:
                     calls.append(("shared_up", lib.grace_shared_ffn_up, (p(x), T, d, f, self.n_shared, dt, p(sg), p(su), ws, st)))
                 calls.append(("shared_down", lib.grace_shared_ffn_down, (T, d, f, self.n_shared, dt, p(sd), p(self.y_shared),
                                                                          p(self.ws_shared) if fuse else ws, st)))
-        if self.hosts_all:   # no row to leave out, and finding that out takes 3 to 26 % of the combine
-            calls.append(("combine", lib.grace_combine, (p(self.y), p(pos), p(tw), T, k, d, dt, p(self.y_shared), p(self.out), st)))
-        else:
-            calls.append(("combine", lib.grace_combine_share, (p(self.y), p(pos), p(tw), T, k, d, dt, p(self.y_shared),
-                                                               p(self.y_state), p(self.out), st)))
-        return calls
+        return calls + [combine]
 
     def forward(self, logits: torch.Tensor, x: torch.Tensor, rr_in: Optional[torch.Tensor] = None,
                 rr_out: Optional[torch.Tensor] = None,

@@ -665,29 +665,31 @@ def test_layer_has_its_rows_moved_where_the_projection_carries_them(T, k, d, f, 
     assert torch.equal(layer.y, y)
 
 
-@pytest.mark.parametrize("T,E,k,R,spread,policy,d,f,dtype,kernel", [
-    (1, 64, 8, 4, 2, 0, 2048, 1024, "bf16", "stream"),       # one token, a wavefront for it
-    (4, 64, 8, 4, 2, 1, 136, 200, "bf16", "stream"),         # several candidates per expert; K of whole steps and 8 left over
-    (5, 60, 4, 8, 2, 0, 256, 96, "bf16", "stream"),          # four tokens per wavefront; experts that fill no 16 lanes
-    (17, 33, 7, 4, 3, 1, 512, 352, "bf16", "stream"),        # two fragments
-    (64, 64, 8, 32, 1, 0, 512, 96, "bf16", "stream"),        # four fragments, two experts per rank
-    (16, 128, 8, 8, 2, 0, 2048, 768, "bf16", "stream"),      # two experts per lane
-    (32, 200, 5, 8, 1, 1, 256, 64, "bf16", "stream"),        # four
-    (9, 3, 3, 2, 2, 1, 64, 32, "bf16", "stream"),            # every expert chosen; 16 tokens per look at the logits
-    (40, 16, 2, 4, 2, 0, 128, 64, "f32", "stream"),          # a lane per token
-    (256, 8, 2, 4, 2, 0, 128, 256, "f32", "stream"),         # pieces of 64 rows
-    (255, 2, 1, 2, 1, 0, 64, 40, "f32", "stream"),
-    (96, 64, 8, 2, 2, 1, 100, 36, "f32", "stream"),          # all instances here and elsewhere
-    (64, 36, 8, 4, 1, 0, 512, 1408, "bf16", "mid"),      # the 96-row kernel: four tokens per wavefront
-    (95, 12, 7, 3, 3, 1, 264, 1480, "bf16", "mid"),       # three words of tokens, several candidates
-    (32, 100, 6, 16, 1, 1, 192, 2568, "bf16", "mid"),     # eight experts per lane
-    (96, 16, 2, 4, 1, 0, 320, 2096, "bf16", "mid"),       # a lane per token
-    (70, 16, 2, 16, 1, 0, 320, 2096, "bf16", "mid"),      # tiles in halves
-    (30, 140, 7, 16, 1, 1, 128, 1672, "bf16", "mid"),     # a wavefront per token
+@pytest.mark.parametrize("T,E,k,R,spread,policy,d,f,n_shared,dtype,kernel", [
+    (1, 64, 8, 4, 2, 0, 2048, 1024, 0, "bf16", "stream"),       # one token, a wavefront for it
+    (4, 64, 8, 4, 2, 1, 136, 200, 1, "bf16", "stream"),         # several candidates per expert; K of whole steps and 8 left over
+    (5, 60, 4, 8, 2, 0, 256, 96, 3, "bf16", "stream"),          # four tokens per wavefront; experts that fill no 16 lanes
+    (17, 33, 7, 4, 3, 1, 512, 352, 2, "bf16", "stream"),        # two fragments
+    (64, 64, 8, 32, 1, 0, 512, 96, 0, "bf16", "stream"),        # four fragments, two experts per rank
+    (16, 128, 8, 8, 2, 0, 2048, 768, 0, "bf16", "stream"),      # two experts per lane
+    (32, 200, 5, 8, 1, 1, 256, 64, 0, "bf16", "stream"),        # four
+    (9, 3, 3, 2, 2, 1, 64, 32, 2, "bf16", "stream"),            # every expert chosen; 16 tokens per look at the logits
+    (40, 16, 2, 4, 2, 0, 128, 64, 1, "f32", "stream"),          # a lane per token
+    (256, 8, 2, 4, 2, 0, 128, 256, 0, "f32", "stream"),         # pieces of 64 rows
+    (255, 2, 1, 2, 1, 0, 64, 40, 0, "f32", "stream"),
+    (16, 64, 8, 1, 1, 0, 4096, 200, 1, "bf16", "stream"),      # 64 slots of one rank, 16 columns per workgroup of the down projection
+    (13, 10, 3, 2, 2, 1, 132, 68, 2, "f32", "stream"),         # last columns past the end, K of two steps and a rest
+    (96, 64, 8, 2, 2, 1, 100, 36, 0, "f32", "stream"),          # all instances here and elsewhere
+    (64, 36, 8, 4, 1, 0, 512, 1408, 0, "bf16", "mid"),      # the 96-row kernel: four tokens per wavefront
+    (95, 12, 7, 3, 3, 1, 264, 1480, 0, "bf16", "mid"),       # three words of tokens, several candidates
+    (32, 100, 6, 16, 1, 1, 192, 2568, 0, "bf16", "mid"),     # eight experts per lane
+    (96, 16, 2, 4, 1, 0, 320, 2096, 0, "bf16", "mid"),       # a lane per token
+    (70, 16, 2, 16, 1, 0, 320, 2096, 0, "bf16", "mid"),      # tiles in halves
+    (30, 140, 7, 16, 1, 1, 128, 1672, 0, "bf16", "mid"),     # a wavefront per token
 ])
-def test_dispatch_joined_with_the_projection(T, E, k, R, spread, policy, d, f, dtype, kernel):
-    """The smallest batches' one launch for dispatch and gate+up projection gives what the separate calls give, bit for bit, and the down
-    projection finds its rows: ties, masked logits, carried counters, a second step whose rows move."""
+def test_dispatch_joined_with_the_projection(T, E, k, R, spread, policy, d, f, n_shared, dtype, kernel):
+    """The smallest batches' one launch for dispatch and gate+up projection gives what the separate calls give, and the rest of
+    the step finds its rows (up to 16 tokens in one launch): ties, masked logits, carried counters, a second step whose rows move."""
     rng = np.random.default_rng(T + E)
     hosts = [sorted(rng.choice(R, size=rng.integers(1, spread + 1), replace=False).tolist()) for _ in range(E)]
     inst_ptr = np.concatenate([[0], np.cumsum([len(h) for h in hosts])]).astype(np.int32)
@@ -704,6 +706,9 @@ def test_dispatch_joined_with_the_projection(T, E, k, R, spread, policy, d, f, d
     y, want_y = torch.zeros((T * k, d), dtype=tdt, device="cuda"), torch.zeros((T * k, d), dtype=tdt, device="cuda")
     state, want_state = (torch.zeros(8, dtype=torch.int32, device="cuda") for _ in range(2))
     ws, want_ws = (torch.empty(grace.grace_workspace_bytes(T, E, k, table.I, d, f, 0, dt), dtype=torch.uint8, device="cuda") for _ in range(2))
+    ws2, want_ws2 = (torch.empty(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt), dtype=torch.uint8, device="cuda") for _ in range(2))
+    sh = [(torch.randn((n_shared, *s), generator=gen, device="cuda") * 0.1).to(tdt) for s in ((f, d), (f, d), (d, f))] if n_shared else None
+    ys, want_ys = (torch.zeros((T, d), dtype=tdt, device="cuda") if n_shared else None for _ in range(2))
     for step in range(2):
         logits = np.round(rng.standard_normal((T, E)) * 4).astype(np.float32) / 4
         logits[0, ::2] = -0.0
@@ -711,20 +716,32 @@ def test_dispatch_joined_with_the_projection(T, E, k, R, spread, policy, d, f, d
         rr = torch.from_numpy(rng.integers(0, 2 ** 32, size=E, dtype=np.uint64).astype(np.uint32).view(np.int32)).cuda()
         logits, x = torch.from_numpy(logits).cuda(), torch.randn((T, d), generator=gen, device="cuda").to(tdt)
         rr_out, want_rr = torch.empty_like(rr), torch.empty_like(rr)
-        route, perm = grace.grace_dispatch_ffn_up_share(table, rank, logits, k, x, w[0], w[1], state, ws, rr_in=rr, rr_out=rr_out, policy=policy)
-        grace.grace_dispatch_ffn_down_share(table, rank, perm[2], T, k, w[2], y, state, ws)
+        route, perm = grace.grace_dispatch_ffn_up_share(table, rank, logits, k, x, w[0], w[1], state, ws, rr_in=rr, rr_out=rr_out, policy=policy,
+                                                        shared=sh and (sh[0], sh[1]), ws_shared=ws2)
+        out = grace.grace_dispatch_ffn_down_share(table, rank, perm[2], perm[0], route[1], w[2], y, state, ws, sh and sh[2], ys, ws2)
         want_route = grace.grace_route(table, rank, logits, k, rr_in=rr, rr_out=want_rr, policy=policy)
         want_perm = grace.grace_permute(table, want_route[2], x)
         grace.grace_expert_ffn_up_share(table, rank, want_perm[5], want_perm[2], T, k, w[0], w[1], want_state, want_ws)
         grace.grace_expert_ffn_down_share(table, rank, want_perm[2], T, k, w[2], want_y, want_state, want_ws)
+        if n_shared:
+            grace.grace_shared_ffn_up(x, sh[0], sh[1], want_ws2)
+            grace.grace_shared_ffn_down(sh[2], want_ws2, T, want_ys)
         torch.cuda.synchronize()
-        for name, a, b in zip(("expert", "weight", "inst", "count", "pos", "src", "inst_off", "rank_off", "node_off", "xp", "y", "state", "rr"),
-                              (*route, *perm, y, state, rr_out), (*want_route, *want_perm, want_y, want_state, want_rr)):
-            if name == "weight":
-                torch.testing.assert_close(a, b, rtol=1e-6, atol=0)    # (sums of the exponentials in another order)
-            else:
-                assert torch.equal(a, b), (step, name)
-        assert torch.isfinite(y.float()).all()
+        for name, a, b in zip(("expert", "inst", "count", "pos", "src", "inst_off", "rank_off", "node_off", "xp", "state", "rr"),
+                              (route[0], *route[2:], *perm, state, rr_out), (want_route[0], *want_route[2:], *want_perm, want_state, want_rr)):
+            assert torch.equal(a, b), (step, name)
+        torch.testing.assert_close(route[1], want_route[1], rtol=1e-6, atol=0)    # (sums of the exponentials in another order)
+        # sums in another order: fp32 rounding of f products and, in bf16, the last bit of y and of what is made of it
+        hosts_all = S == table.I
+        want_out = grace.grace_combine(y, perm[0], route[1], ys) if hosts_all else grace.grace_combine_share(y, perm[0], route[1], state, ys)
+        for name, a, b in (("y", y, want_y), ("y_shared", ys, want_ys), ("out", out, want_out)):
+            if a is None:
+                continue
+            a, b = a.double(), b.double()
+            assert torch.isfinite(a).all(), (step, name)
+            assert (a == 0).equal(b == 0) or name == "y_shared" or dtype == "f32", (step, name)      # rows of others stay zero
+            scale = b.abs().clamp(min=float(b.pow(2).mean().sqrt()))
+            assert float(((a - b).abs() / scale).max()) <= (2.0 ** -7 if dtype == "bf16" else 1e-5), (step, name)
 
 
 @pytest.mark.parametrize("T,E,k,R,n_shared,d,f", [
