@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgrace_moe.so")
 SOURCES = ["table.cpp", "route.hip", "permute.hip", "combine.hip", "ffn.hip", "gemm_f32_split_up.hip", "gemm_f32_split_down.hip",
-           "gemm_f32_split_shared.hip", "calibrate.hip", "sendlist.hip", "route_permute.hip", "ffn_tiny.hip", "ffn_tiny_mid.hip", "ffn_tiny_down.hip"]
+           "gemm_f32_split_shared.hip", "calibrate.hip", "sendlist.hip", "route_permute.hip", "ffn_tiny.hip", "ffn_tiny_mid.hip", "ffn_tiny_cols.hip", "ffn_tiny_down.hip"]
 
 CALLS = os.path.join(HERE, "_torch_calls.so")              # the binding's calls that allocate (csrc/torch_calls.cpp)
 STAMP = os.path.join(HERE, "libgrace_moe.stamp")   # digest of the sources the library was built from

@@ -49,7 +49,7 @@ static int compute_units() {
 
 // The persistent kernel needs the 160 KB of dynamic LDS opted in, once per kernel and device.
 static bool allow_full_lds(const void *kernel, const char *what) {
-    constexpr int MAX_KERNELS = 24, MAX_DEVICES = 64;
+    constexpr int MAX_KERNELS = 32, MAX_DEVICES = 64;
     static std::mutex mu;
     static const void *known[MAX_KERNELS] = {nullptr};
     static bool done[MAX_KERNELS][MAX_DEVICES] = {{false}};
@@ -566,6 +566,16 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     return launch_gemm<true, pers::EXPERTS>(up, dt, rows, (hipStream_t)stream, who);
 }
 
+// Whether the joined gate+up projection is dealt out in units of 4 columns (ffn_tiny_cols.hip) rather than a workgroup per slot and strip (ffn_tiny.hip):
+// up to 8 tokens, K in whole 128-byte lines.  Every workgroup waits for the whole gate then, which pays where slots without rows would leave
+// workgroups idle: not for one or two slots (d = 4096, f = 3584, 1 to 8 tokens 0.91 to 1.04 times as fast), for more than 4 tokens not where a
+// slot has fewer units than half the compute units (f = 192 and 256, 5 and 8 tokens 0.97 to 1.06), and not with shared experts, whose tiles
+// need not wait (2 and 4 of f = 352 and 1408 0.88 to 1.05).  Where it is taken, steps of 1 to 8 tokens, 8 to 19 slots: f = 704 to 2816 1.01 to
+// 1.21, in the mean 1.08; f = 192 and 256, up to 4 tokens 1.05 to 1.22.
+static bool deals_columns(int S, int32_t T, int32_t d, int32_t f, grace_dtype dt, int n_cu) {
+    return S > 2 && T <= TINY_COLS_T && (T <= 4 || f >= 2 * n_cu) && (int64_t)d * (dt == GRACE_F32 ? 4 : 2) % 128 == 0;
+}
+
 extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T,
                                            int32_t E, int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out,
                                            int32_t *topk_expert, float *topk_weight, int32_t *topk_inst, int32_t *expert_count,
@@ -619,7 +629,9 @@ extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t loc
             a.shared_strips = (a.shared.N + cols - 1) / cols;
         }
     }
-    if (route == Route::MID) {
+    if (route == Route::STREAM && n_shared == 0 && deals_columns(S, T, d, f, dt, n_cu)) {
+        launch_tiny_cols(a, dt, n_cu, (hipStream_t)stream);
+    } else if (route == Route::MID) {
         launch_tiny_up_mid(a, n_cu, (hipStream_t)stream);
     } else {
         const Grid l = dt == GRACE_BF16 ? stream_grid<true, 2>(shape, rows, n_cu, a.shared_strips) : stream_grid<true, 4>(shape, rows, n_cu, a.shared_strips);
@@ -757,7 +769,7 @@ extern "C" int grace_dispatch_ffn_down_share(const grace_table *table, int32_t r
     }
     a.perm_pos = perm_pos; a.weight = topk_weight; a.out = out;
     a.T = T; a.k = k; a.n_shared = n_shared;
-    if (!allow_full_lds(tiny_down_kernel_of(dt, d, n_cu), who)) return GRACE_EHIP;
+    if (!allow_full_lds(tiny_down_kernel_of(dt, T, d, n_cu), who)) return GRACE_EHIP;
     launch_tiny_down(a, dt, tiny_down_lds(T, k, S, n_shared, d, n_cu), n_cu, (hipStream_t)stream);
     GRACE_LAUNCH_CHECK(who);
     return GRACE_OK;

@@ -126,6 +126,10 @@ int64_t tiny_up_mid_blocks(int S, int K, int n_strips, int n_cu);
 // up to 96 tokens
 void launch_tiny_up_mid(const TinyUp &a, int n_cu, hipStream_t st);
 
+// K in whole 128-byte lines (ffn_tiny_cols.hip)
+constexpr int TINY_COLS_T = 8;   // tokens
+void launch_tiny_cols(const TinyUp &a, grace_dtype dt, int n_cu, hipStream_t st);
+
 // The down projections and the combine of up to TINY_DOWN_T tokens (ffn_tiny_down.hip).
 constexpr int TINY_DOWN_T = 16;
 struct TinyDown {
@@ -138,7 +142,7 @@ struct TinyDown {
 };
 int tiny_down_lds(int T, int k, int S, int n_shared, int N, int n_cu);   // bytes
 int tiny_down_blocks(int N, int n_cu);   // workgroups
-const void *tiny_down_kernel_of(grace_dtype dt, int N, int n_cu);
+const void *tiny_down_kernel_of(grace_dtype dt, int T, int N, int n_cu);
 void launch_tiny_down(const TinyDown &a, grace_dtype dt, int lds, int n_cu, hipStream_t st);
 
 }  // namespace grace

@@ -680,6 +680,12 @@ def test_layer_has_its_rows_moved_where_the_projection_carries_them(T, k, d, f, 
     (16, 64, 8, 1, 1, 0, 4096, 200, 1, "bf16", "stream"),      # 64 slots of one rank, 16 columns per workgroup of the down projection
     (13, 10, 3, 2, 2, 1, 132, 68, 2, "f32", "stream"),         # last columns past the end, K of two steps and a rest
     (96, 64, 8, 2, 2, 1, 100, 36, 0, "f32", "stream"),          # all instances here and elsewhere
+    (7, 40, 6, 4, 2, 1, 192, 600, 0, "bf16", "stream"),        # projection in units of 4 columns: a part of K of one step
+    (8, 12, 9, 1, 1, 0, 64, 7400, 0, "bf16", "stream"),        # more than 64 units per workgroup
+    (8, 12, 5, 2, 2, 1, 96, 516, 0, "f32", "stream"),
+    (16, 12, 5, 2, 2, 1, 96, 516, 0, "f32", "stream"),
+    (3, 200, 5, 8, 1, 1, 256, 64, 0, "f32", "stream"),
+    (8, 100, 6, 8, 2, 0, 320, 520, 0, "bf16", "stream"),
     (64, 36, 8, 4, 1, 0, 512, 1408, 0, "bf16", "mid"),      # the 96-row kernel: four tokens per wavefront
     (95, 12, 7, 3, 3, 1, 264, 1480, 0, "bf16", "mid"),       # three words of tokens, several candidates
     (32, 100, 6, 16, 1, 1, 192, 2568, 0, "bf16", "mid"),     # eight experts per lane
