@@ -131,7 +131,7 @@ static int stream_fragments(const Rows &rows) { return rows.max_rows <= 16 ? 1 :
 template <bool FUSED_UP, int EL>
 static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu, int64_t others = 0 /* busy workgroups beside them */) {
     const int64_t n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
-    if (stream_pieces<EL>(rows)) return {((rows.m_bound / strm::MAX_ROWS + g.S) * n_strips + 7) / 8 * 8, 256};
+    if (stream_pieces<EL>(rows)) return {(std::max<int64_t>((rows.m_bound / strm::MAX_ROWS + g.S) * n_strips, n_cu) + 7) / 8 * 8, 256};
     const int64_t busy = std::min<int64_t>(g.S, rows.m_bound) * n_strips + others;
     int waves = 4;
     // (no more than 64 KB of partial sums: a launch may ask for that much LDS without opting in)
@@ -301,13 +301,13 @@ static Route route_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, int
 }
 
 template <bool FUSED_UP, int EL>
-static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, hipStream_t st) {
+static void launch_stream(const GemmArgs &g, const Rows &rows, const Grid &l, int n_cu, hipStream_t st) {
     const int n_strips = (g.N + strm::Shape<FUSED_UP>::COLS - 1) / strm::Shape<FUSED_UP>::COLS;
     if constexpr (EL == 4) {
         if (stream_pieces<EL>(rows)) {
             const int lds = strm::lds_bytes(4, strm::MAX_ROWS / 16);
-            if (g.S <= 64) strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 1><<<(unsigned)l.groups, l.threads, lds, st>>>(g, n_strips);
-            else strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 4><<<(unsigned)l.groups, l.threads, lds, st>>>(g, n_strips);
+            if (g.S <= 64) strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 1><<<(unsigned)l.groups, l.threads, lds, st>>>(g, n_strips, n_cu);
+            else strm::gemm_stream_tiles_kernel<FUSED_UP, EL, 4><<<(unsigned)l.groups, l.threads, lds, st>>>(g, n_strips, n_cu);
             return;
         }
     }
@@ -355,8 +355,8 @@ static int launch_gemm(const GemmArgs &g, grace_dtype dt, const Rows &rows, hipS
     const Grid l = grid_of<FUSED_UP>(route, g, dt, rows, n_cu);
     if (!launchable(l)) return fail(GRACE_ESHAPE, "%s: grid too large", what);
     if (route == Route::STREAM) {
-        if (dt == GRACE_BF16) launch_stream<FUSED_UP, 2>(g, rows, l, st);
-        else launch_stream<FUSED_UP, 4>(g, rows, l, st);
+        if (dt == GRACE_BF16) launch_stream<FUSED_UP, 2>(g, rows, l, n_cu, st);
+        else launch_stream<FUSED_UP, 4>(g, rows, l, n_cu, st);
     } else if (route == Route::MID && dt == GRACE_F32) {
         const int rc = launch_split<FUSED_UP>(g, l, n_cu, st, what);
         if (rc != GRACE_OK) return rc;
@@ -635,7 +635,7 @@ extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t loc
         launch_tiny_up_mid(a, n_cu, (hipStream_t)stream);
     } else {
         const Grid l = dt == GRACE_BF16 ? stream_grid<true, 2>(shape, rows, n_cu, a.shared_strips) : stream_grid<true, 4>(shape, rows, n_cu, a.shared_strips);
-        launch_tiny_up(a, dt, l.threads / 64, pieces, (hipStream_t)stream);
+        launch_tiny_up(a, dt, l.threads / 64, pieces, n_cu, (hipStream_t)stream);
     }
     GRACE_LAUNCH_CHECK(who);
     return with_shared ? GRACE_OK : shared_alone();

@@ -14,6 +14,7 @@ struct TinyUp {
     int n_strips;
     GemmArgs shared;          // shared experts' gate+up projection by the same launch (shared_strips 0: none)
     int shared_strips;
+    int piece_rows;           // fp32, more than 64 tokens: workgroups per that many rows at most (the launcher's)
 };
 
 // The record that the down projection's launch reads (share_record).
@@ -120,7 +121,7 @@ __device__ __forceinline__ int rows_of_slot(const TinyUp &a, int slot, TinyRows 
 }
 
 // waves: per workgroup; pieces: more than 64 tokens (fp32).  The caller checks the launch.
-void launch_tiny_up(const TinyUp &a, grace_dtype dt, int waves, bool pieces, hipStream_t st);
+void launch_tiny_up(const TinyUp &a, grace_dtype dt, int waves, bool pieces, int n_cu, hipStream_t st);
 // workgroups of the projection (the dispatch's T are extra), 0: too many tiles
 int64_t tiny_up_mid_blocks(int S, int K, int n_strips, int n_cu);
 // up to 96 tokens

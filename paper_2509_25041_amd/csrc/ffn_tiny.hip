@@ -8,7 +8,7 @@
 //
 // Bound by latency and then by the weights, as gemm_stream_kernel; what is saved is most of the dispatch's launch (the rows cost 1.5 to 2 us, mainly the
 // wait for the logits).  Dispatch and projection, two launches -> one: 1 token, 64 experts, k = 8 6.1 + 7.8 -> 9.3 us, 16 of 128 experts 9.4 + 12.1
-// -> 15.0, 256 of 8, k = 2, fp32 10.3 + 6.5 -> 10.2.  Layer steps of 1 to 64 tokens (158 of five shapes, whole and a quarter of the expert
+// -> 15.0, 256 of 8, k = 2, fp32 10.3 + 6.5 -> 9.6.  Layer steps of 1 to 64 tokens (158 of five shapes, whole and a quarter of the expert
 // width, both policies, replayed from a graph) take 1.02 to 1.42 times as long with two, in the median 1.16.  Where more workgroups than are resident at a time
 // repeat the search for rows, many of them for tiles with work, it is even (fp32, d = 1024, f = 2816, 64 tokens 90.8 -> 91.7 us), and so are pieces of 64
 // rows past two workgroups per compute unit slower (f = 704, 80 tokens 40.5 -> 50.8): the two launches there (joins_dispatch).
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(64 * strm::MAX_WAVES) void tiny_up_kernel(const Tin
             return strm::rows_any<true, EL, MF>(a.shared, 0, {0, T, 0, nullptr}, strip * strm::Shape<true>::COLS, (float4 *)smem);
     }
     TinyRows &s = *(TinyRows *)smem;
-    const int pieces = PIECES ? (T + strm::MAX_ROWS - 1) / strm::MAX_ROWS : 1, b = (int)blockIdx.x - T;
+    const int pieces = PIECES ? (T + a.piece_rows - 1) / a.piece_rows : 1, b = (int)blockIdx.x - T;
     int slot, strip, piece = 0;
     if (PIECES) {   // pieces of the same weights next to each other on one XCD, and hot and cold slots on every one
         const int total = a.up.S * a.n_strips * pieces, each = (total + 7) >> 3, j = b >> 3, t = (b & 7) * each + j;
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(64 * strm::MAX_WAVES) void tiny_up_kernel(const Tin
     const int n = rows_of_slot<VPL>(a, slot, s);
     int first = 0, end = n;
     if (PIECES && n > 0) {
-        const int parts = (n + strm::MAX_ROWS - 1) / strm::MAX_ROWS, rows = ((n + parts - 1) / parts + 15) & ~15;
+        const int parts = (n + a.piece_rows - 1) / a.piece_rows, rows = ((n + parts - 1) / parts + 15) & ~15;
         first = piece * rows;
         end = min(n, first + rows);
     }
@@ -59,11 +59,15 @@ __global__ __launch_bounds__(64 * strm::MAX_WAVES) void tiny_up_kernel(const Tin
                                            (float4 *)(smem + ROWS_BYTES));
 }
 
-void launch_tiny_up(const TinyUp &a, grace_dtype dt, int waves, bool pieces, hipStream_t st) {
+void launch_tiny_up(const TinyUp &tiles, grace_dtype dt, int waves, bool pieces, int n_cu, hipStream_t st) {
+    TinyUp a = tiles;
     const int T = a.dispatch.T, E = a.dispatch.E;
     const int mf = pieces ? 4 : T <= 16 ? 1 : T <= 32 ? 2 : 4;
     const int lds = std::max((int)sizeof(TinyLds), ROWS_BYTES + strm::lds_bytes(waves, mf));
-    const int blocks = pieces ? (a.up.S * a.n_strips * ((T + strm::MAX_ROWS - 1) / strm::MAX_ROWS) + 7) / 8 * 8 : a.up.S * a.n_strips + a.shared_strips;
+    a.piece_rows = strm::MAX_ROWS;
+    auto tiles_of = [&] { return a.up.S * a.n_strips * ((T + a.piece_rows - 1) / a.piece_rows); };
+    while (pieces && a.piece_rows > 16 && 2 * tiles_of() <= n_cu) a.piece_rows /= 2;   // as gemm_stream_tiles_kernel's, of the tiles that there may be
+    const int blocks = pieces ? (tiles_of() + 7) / 8 * 8 : a.up.S * a.n_strips + a.shared_strips;
     auto launch = [&](auto kernel) { kernel<<<(unsigned)(T + blocks), waves * 64, lds, st>>>(a); };
     auto by_rows = [&](auto vpl, auto gate, auto el) {
         constexpr int VPL = decltype(vpl)::value, EL = decltype(el)::value;

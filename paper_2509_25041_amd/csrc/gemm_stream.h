@@ -253,14 +253,20 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void gemm_stream_kernel(const GemmA
 // one size (a multiple of 16) per segment.  Numbered by segment, strip, piece, and cut into eight equal ranges,
 // one per XCD (workgroups are dealt to the XCDs round-robin): the workgroups that run together on an XCD share
 // weight strips and rows in its L2.  The grid covers the launcher's bound on the pieces; the rest exits.
+// Where all pieces leave three in four of the compute units (or every other one) without work, they have 16 (32)
+// rows: a piece of 64 keeps its matrix cores busy for several times as long, on the few that have one (12 tiles, 129 rows of 2 segments, K = 256, N = 128
+// 8.8 -> 6.7 us; layer steps, two or four slots, d = 128, f = 256, 65 to 700 tokens 1.03 to 1.16 times as fast, f = 1024 1.08 to 1.28, d = 512, f = 256 0.99 to
+// 1.20; more slots or d = 1024, where it seldom applies, 0.99 to 1.20).
 template <bool FUSED_UP, int EL, int SEG_PER_LANE>
-__global__ __launch_bounds__(256, 4) void gemm_stream_tiles_kernel(const GemmArgs g, int n_strips) {
+__global__ __launch_bounds__(256, 4) void gemm_stream_tiles_kernel(const GemmArgs g, int n_strips, int n_cu) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = (int)threadIdx.x & 63;
     if (FUSED_UP) share_record(g, blockIdx.x == 0); else share_clear_stale(g);
     SegTable<SEG_PER_LANE> segs;
     segs.load(g, lane);
     segs.cut(lane, MAX_ROWS);
+    if (4 * segs.total * n_strips <= n_cu) segs.cut(lane, MAX_ROWS / 4);
+    else if (2 * segs.total * n_strips <= n_cu) segs.cut(lane, MAX_ROWS / 2);
     const int total = segs.total * n_strips, xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
     const int each = total >> 3, rem = total & 7;
     if (j >= each + (xcd < rem ? 1 : 0)) return;

@@ -243,6 +243,14 @@ def test_f32_long_launches(seg_rows, T, k, d, f, want):
     ffn_rows_of_segments(seg_rows, T, k, d, f, "f32")
 
 
+@pytest.mark.parametrize("seg_rows,N", [([193, 1], 32 * 12), ([65, 33], 32 * 21), ([65, 33], 32 * 22), ([65, 33], 32 * 42), ([65, 33], 32 * 43)])
+def test_f32_pieces_of_16_and_32_rows(seg_rows, N):
+    """Tiles of 64 rows on a quarter and half of the compute units (256), and one strip more: pieces of 16, 32 and 64 rows."""
+    T, f = max(seg_rows), 68
+    assert kernels_of(T, 2, N, f, 2, 2, dtype="f32")[1] == "stream"
+    ffn_rows_of_segments(seg_rows, T, 2, N, f, "f32")
+
+
 @pytest.mark.parametrize("seg_rows,T,k,d,f,want", [
     ([16, 17, 33, 49, 65, 80, 81, 161], 260, 2, 516, 515, ("mid", "vector_f32")),     # pieces of one to five fragments; N no multiple of 4; K of 16 steps and 4
     ([120, 0, 1, 70, 3, 9, 200, 64], 250, 2, 1024, 1100, ("mid", "mid")),      # down: few tiles, the groups share a K of 34 steps and 12
