@@ -322,6 +322,7 @@ def run_workload(name: str, steps: int, warmup: int, rotate: int = 0, mfma_probe
                    "n_shared": cfg.n_shared, "working_set_MB": ws_bytes / 1e6,
                    "row_scatter": "in the launch of dispatch and gate+up projection" if joined else "carried by the shared gate+up projection's launch" if carries_rows else
                    "carried by the experts' gate+up projection's launch" if gathers_rows else
+                   "carried by the launch of both gate+up projections" if fused_scatter and layer.join_shared[True] else
                    "a launch of its own ahead of the shared gate+up projection" if fused_scatter else "in the dispatch call"},
         "roofline": {"kernel": KERNEL_OF_STAGE[dominant] if kernels.get(dominant, "persist") == "persist"
                      else f"{OTHER_KERNEL[kernels[dominant]]} ({dominant})",

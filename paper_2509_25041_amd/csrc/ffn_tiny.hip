@@ -8,7 +8,7 @@
 //
 // Bound by latency and then by the weights, as gemm_stream_kernel; what is saved is most of the dispatch's launch (the rows cost 1.5 to 2 us, mainly the
 // wait for the logits).  Dispatch and projection, two launches -> one: 1 token, 64 experts, k = 8 6.1 + 7.8 -> 9.3 us, 16 of 128 experts 9.4 + 12.1
-// -> 15.0, 256 of 8, k = 2, fp32 10.3 + 6.5 -> 9.6.  Layer steps of 1 to 64 tokens (158 of five shapes, whole and a quarter of the expert
+// -> 15.0 (the first is ffn_tiny_cols.hip's now), 256 of 8, k = 2, fp32 10.3 + 6.5 -> 9.6.  Layer steps of 1 to 64 tokens (158 of five shapes, whole and a quarter of the expert
 // width, both policies, replayed from a graph) take 1.02 to 1.42 times as long with two, in the median 1.16.  Where more workgroups than are resident at a time
 // repeat the search for rows, many of them for tiles with work, it is even (fp32, d = 1024, f = 2816, 64 tokens 90.8 -> 91.7 us), and so are pieces of 64
 // rows past two workgroups per compute unit slower (f = 704, 80 tokens 40.5 -> 50.8): the two launches there (joins_dispatch).
