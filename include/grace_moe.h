@@ -125,7 +125,8 @@ int grace_table_set_fold_limits(grace_table *table, int32_t one_level_max, int32
 /* Bytes of device scratch that any single call below needs for these sizes
  * (the same buffer may be reused by consecutive calls on one stream).
  * f and n_shared may be 0 when the FFN entry points are not used.  Returns 0
- * on invalid arguments.  The buffer must be 256-byte aligned. */
+ * on invalid arguments.  Never less for a larger T (the rest equal): a buffer
+ * for the largest batch does for every smaller one.  The buffer must be 256-byte aligned. */
 size_t grace_workspace_bytes(int32_t T, int32_t E, int32_t k, int32_t I, int32_t d, int32_t f, int32_t n_shared,
                              grace_dtype dt);
 

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -76,10 +77,17 @@ int launch_topk(const float *logits, int T, int E, int k, int renorm, int32_t *t
 size_t fused_perm_ws_offset(int32_t T, int32_t E);
 // Workspace bytes of routing + permutation as one call (both sets of histograms and their prefix sums).
 size_t route_permute_ws_bytes(int32_t T, int32_t E, int32_t k, int32_t I);
+// The smallest batches, whose dispatch is one launch (route_tiny.h): most tokens, 0 if the table's keys do not fit the LDS.
+constexpr int MAX_KEYS = 256;             // experts and instances that the tables in LDS hold
+constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
+constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_TOP2 = 16 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;
+inline int tiny_most_tokens(int k, int E, int I) {
+    if (k < 1 || E > MAX_KEYS || I > MAX_KEYS) return 0;
+    return std::min(E > 64 ? TINY_MAX_T_WIDE : k > 2 ? TINY_MAX_T : TINY_MAX_T_TOP2, TINY_MAX_ASG / k);
+}
 // Hidden activation with T rows for each of S slots, as the smallest batches' joined launches lay it out where S * T rows are no more
 // than T * k or fit these bytes.
 constexpr size_t SLOT_ROWS_MOST = (size_t)32 << 20;
-constexpr int SLOT_ROWS_MAX_T = 256;
 int launch_scatter_rows(const void *x, int T, int k, int d, grace_dtype dt, const int32_t *perm_pos, void *xp,
                         hipStream_t st);
 

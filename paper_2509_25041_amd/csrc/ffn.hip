@@ -450,7 +450,7 @@ static Rows shared_rows(int32_t T) { return {T, T, 1, true, T, T}; }
 // projection then finds slot by slot.
 static bool joins_dispatch(const grace_table *table, int32_t rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt, int n_cu) {
     const int S = table->rank_ptr[rank + 1] - table->rank_ptr[rank], el = dt == GRACE_F32 ? 4 : 2;
-    if (S < 1 || T > SLOT_ROWS_MAX_T || !tiny_batch(T, k, table->E, table->I)) return false;
+    if (S < 1 || !tiny_batch(T, k, table->E, table->I)) return false;
     if (S > k && (size_t)T * S * f * el > SLOT_ROWS_MOST) return false;
     const GemmArgs up = expert_shape(true, S, d, f), dn = expert_shape(false, S, d, f);
     const Rows rows = expert_rows(S, table->I, T, k);

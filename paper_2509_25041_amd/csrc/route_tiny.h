@@ -10,13 +10,7 @@
 
 namespace grace {
 
-constexpr int MAX_KEYS = 256;             // experts and instances that the tables in LDS hold
-constexpr int TINY_MAX_ASG = 1024, TINY_MAX_WAVES = 16;
-constexpr int TINY_MAX_T = 6 * TINY_MAX_WAVES, TINY_MAX_T_TOP2 = 16 * TINY_MAX_WAVES, TINY_MAX_T_WIDE = 2 * TINY_MAX_WAVES;
-inline bool tiny_batch(int T, int k, int E, int I) {
-    return T >= 1 && T <= (E > 64 ? TINY_MAX_T_WIDE : k > 2 ? TINY_MAX_T : TINY_MAX_T_TOP2) && (int64_t)T * k <= TINY_MAX_ASG && E <= MAX_KEYS &&
-           I <= MAX_KEYS;
-}
+inline bool tiny_batch(int T, int k, int E, int I) { return T >= 1 && T <= tiny_most_tokens(k, E, I); }
 
 struct TinyArgs {
     const float *logits;

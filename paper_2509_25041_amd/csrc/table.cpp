@@ -276,7 +276,9 @@ extern "C" size_t grace_workspace_bytes(int32_t T, int32_t E, int32_t k, int32_t
     // routing and permutation histograms side by side (grace_route_permute uses both at once)
     size_t need = grace::route_permute_ws_bytes(T, E, k, I);
     need = std::max(need, grace::align_up(n * (size_t)f * el, 256));
-    if (T <= grace::SLOT_ROWS_MAX_T) need = std::max(need, std::min(grace::SLOT_ROWS_MOST, grace::align_up((size_t)T * std::min(E, I) * (size_t)f * el, 256)));
+    // rows by slots, of the smallest batches; larger ones ask for as much as the largest of these, so that their buffer does for those
+    const size_t slot_T = (size_t)std::min(T, grace::tiny_most_tokens(k, E, I));
+    need = std::max(need, std::min(grace::SLOT_ROWS_MOST, grace::align_up(slot_T * std::min(E, I) * (size_t)f * el, 256)));
     need = std::max(need, grace::align_up((size_t)T * (size_t)n_shared * (size_t)f * el, 256));
     // send lists: five int32 arrays over the assignments + chunk histograms over up to GRACE_MAX_RANKS keys + counters
     need = std::max(need, 5 * grace::align_up(n * 4, 256) + 2 * grace::align_up(chunks_p * (size_t)GRACE_MAX_RANKS * 4, 256) +

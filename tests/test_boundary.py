@@ -128,6 +128,20 @@ def test_workspace_bytes():
     assert grace.grace_workspace_bytes(4096, 64, 8, 76, 2048, 1024, 0, grace.GRACE_F32) >= 2 * (big - 256)
 
 
+@pytest.mark.parametrize("E,k,I,f,dt", [
+    (64, 8, 76, 1024, grace.GRACE_BF16), (64, 8, 76, 1024, grace.GRACE_F32), (128, 8, 150, 768, grace.GRACE_BF16), (60, 4, 69, 1408, grace.GRACE_BF16),
+    (8, 2, 11, 14336, grace.GRACE_BF16), (12, 9, 12, 7400, grace.GRACE_BF16), (200, 1, 255, 2048, grace.GRACE_F32), (64, 64, 300, 512, grace.GRACE_BF16),
+])
+def test_workspace_of_a_larger_batch_does_for_a_smaller_one(E, k, I, f, dt):
+    """A serving loop sizes one buffer for its largest batch."""
+    sizes = [grace.grace_workspace_bytes(T, E, k, I, 2048, f, 0, dt) for T in range(0, 1100)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    # rows by slots are held for the batches that are laid out so: 32 tokens with more than 64 experts, 96, or 256 with k <= 2; 1024 choices
+    el, most = 4 if dt == grace.GRACE_F32 else 2, min(32 if E > 64 else 96 if k > 2 else 256, 1024 // k) if max(E, I) <= 256 else 0
+    assert sizes[most] >= min(32 << 20, most * min(E, I) * f * el)
+    assert sizes[1099] <= max(min(32 << 20, most * min(E, I) * f * el), 1099 * k * f * el, 1 << 20) + 512
+
+
 def test_caller_tensors_are_checked_before_a_kernel_writes_them():
     """Tensors that kernels of these calls write or read whole: too small or of another type is an error, not an access out of
     bounds.  (Tensors of the right size get as far as the check that they are on the device.)"""

@@ -806,3 +806,23 @@ def test_shared_and_expert_projections_in_one_launch(T, E, k, R, n_shared, d, f)
         for name, a, b in (("xp", xp, want_xp), ("y", y, want_y), ("y_shared", ys, want_ys), ("state", state, want_state)):
             assert torch.equal(a, b), (step, name)
         assert torch.isfinite(y.float()).all() and y.abs().max() > 0
+
+
+def test_joined_step_in_the_workspace_of_a_larger_batch():
+    """64 slots of one rank, rows by slots, in the buffer of 257 tokens: nothing behind it is written, and the calls without slots take it."""
+    T, larger, E, k, d, f, bf = 64, 257, 64, 8, 256, 192, torch.bfloat16
+    table = grace.GraceTable(E, 1, 1, [0], [1], list(range(E + 1)), [0] * E)
+    assert grace.grace_dispatch_joins_ffn(table, 0, T, k, d, f)
+    size = grace.grace_workspace_bytes(larger, E, k, E, d, f)
+    held = torch.full((size + (4 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+    ws = held[:size]
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    logits, x = torch.randn((T, E), generator=gen, device="cuda"), torch.randn((T, d), generator=gen, device="cuda").to(bf)
+    w = [(torch.randn(s, generator=gen, device="cuda") * 0.1).to(bf) for s in ((E, f, d), (E, f, d), (E, d, f))]
+    y, state = torch.zeros((T * k, d), dtype=bf, device="cuda"), torch.zeros(8, dtype=torch.int32, device="cuda")
+    route, perm = grace.grace_dispatch_ffn_up_share(table, 0, logits, k, x, w[0], w[1], state, ws)
+    grace.grace_dispatch_ffn_down_share(table, 0, perm[2], perm[0], route[1], w[2], y, state, ws)
+    want = grace.grace_expert_ffn(table, 0, perm[5], perm[2], T, k, *w, ws=ws)
+    torch.cuda.synchronize()
+    assert (held[size:] == 0xA5).all()
+    assert float((y.double() - want.double()).abs().max()) <= 2.0 ** -7 * float(want.abs().max())
