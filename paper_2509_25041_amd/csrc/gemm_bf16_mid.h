@@ -59,7 +59,8 @@ __device__ __forceinline__ int chunk_at(int row, int c) { return row * ROW_BYTES
 // MF: activation fragments of 16 rows.  NJ: weight fragments per wavefront, 2 or, for half a tile's weight rows, 1 (gate+up:
 // then 8 rows of each matrix, and the lanes of the upper half hold the up projection's sums).  SEG_K: the weights' K
 // axis is cut in segments (shared experts' down projection), of any length.  Activation rows from a0 on, or those that `list` (LDS)
-// names, or the tokens (g.sc_x) of the assignments that g.A names for the rows.
+// names, or the tokens (g.sc_x) of the assignments that g.A names for the rows (an entry past the batch stands for the last token: no read outside
+// the tokens).
 enum class RowsFrom { HERE, LIST, ASSIGNMENTS };
 template <bool FUSED_UP, bool SEG_K, int MF, int NJ, RowsFrom FROM>
 __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, int m_end, int a0, int n0, int first_step,
@@ -82,7 +83,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs &g, int slot, int m0, i
         const int row = i * 32 + (tid >> 3);
         a_off[i] = NO_DATA;
         if (m0 + row < m_end) {
-            const int from = FROM == RowsFrom::LIST ? list[row] : FROM == RowsFrom::ASSIGNMENTS ? (int)((uint32_t)((const int32_t *)g.A)[m0 + row] / (uint32_t)g.sc_k) : row;
+            const int from = FROM == RowsFrom::LIST ? list[row]
+                             : FROM == RowsFrom::ASSIGNMENTS ? (int)min((uint32_t)((const int32_t *)g.A)[m0 + row] / (uint32_t)g.sc_k, (uint32_t)(g.sc_T - 1)) : row;
             a_off[i] = (uint32_t)from * (uint32_t)(g.lda * 2) + (uint32_t)a_chunk * 16u;
         }
     }

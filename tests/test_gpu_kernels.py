@@ -826,3 +826,33 @@ def test_joined_step_in_the_workspace_of_a_larger_batch():
     torch.cuda.synchronize()
     assert (held[size:] == 0xA5).all()
     assert float((y.double() - want.double()).abs().max()) <= 2.0 ** -7 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("T,k,d,f,S,n_shared,kernel", [(300, 4, 128, 64, 4, 0, "mid"), (300, 4, 128, 64, 4, 2, "mid"), (9000, 8, 512, 256, 8, 0, "persist")])
+def test_stale_assignments_stay_inside_the_tokens(T, k, d, f, S, n_shared, kernel):
+    """perm_src entries that are no assignment of the batch: read as some token's, the other rows are as without them."""
+    I, bf = 2 * S, torch.bfloat16
+    assert kernels_of(T, k, d, f, S, I)[0] == kernel
+    table = grace.GraceTable(I, 2, 1, [0, 0], [1, 1], list(range(I + 1)), [e // S for e in range(I)])
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s: (torch.randn(s, generator=gen, device="cuda") * 0.1).to(bf)
+    x, w, sh = normal(T, d), (normal(S, f, d), normal(S, f, d)), (normal(n_shared, f, d), normal(n_shared, f, d))
+    _, (pos, src, ioff, _, _, _) = grace.grace_route_permute(table, 0, torch.randn((T, I), generator=gen, device="cuda"), k, None)
+    n = int(ioff[S])
+    stale = src.clone()
+    at = torch.arange(3, n, 7, device="cuda")
+    stale[at] = torch.tensor([-1, -2 ** 31, 2 ** 31 - 1, T * k], dtype=torch.int32, device="cuda")[torch.arange(len(at), device="cuda") % 4]
+    hidden = []
+    for s in (src, stale):
+        ws, state = torch.zeros(grace.grace_workspace_bytes(T, I, k, I, d, f), dtype=torch.uint8, device="cuda"), torch.zeros(8, dtype=torch.int32, device="cuda")
+        xp = torch.zeros((T * k, d), dtype=bf, device="cuda")
+        if n_shared:
+            ws2 = torch.empty(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared), dtype=torch.uint8, device="cuda")
+            assert grace.grace_ffn_joins_shared(True, T, d, f, n_shared, k=k, S=S, I=I)
+            grace.grace_expert_shared_ffn_up_scatter(table, 0, x, pos, s, xp, ioff, k, *w, *sh, state, ws, ws2)
+        else:
+            grace.grace_expert_ffn_up_share_scatter(table, 0, x, pos, s, xp, ioff, k, *w, state, ws)
+        hidden.append(ws[:n * f * 2].view(bf).view(n, f))
+    other = torch.ones(n, dtype=torch.bool, device="cuda")
+    other[at] = False
+    assert torch.equal(hidden[0][other], hidden[1][other]) and torch.isfinite(hidden[1].float()).all()
