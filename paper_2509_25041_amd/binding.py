@@ -231,6 +231,13 @@ def _ws(ws: Optional[torch.Tensor], nbytes: int, device) -> torch.Tensor:
     return ws
 
 
+def _need_ws(ws: Optional[torch.Tensor], nbytes: int) -> None:
+    """A workspace that a later call reads as well: the caller's."""
+    if ws is None:
+        raise ValueError(f"workspace missing: need {nbytes} bytes")
+    _ws(ws, nbytes, ws.device)
+
+
 def _need(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, numel: int) -> None:
     """A caller's tensor that a kernel reads or writes `numel` entries of."""
     if t is None or t.dtype != dtype or t.numel() < numel:
@@ -494,9 +501,9 @@ def grace_dispatch_ffn_up_share(table: GraceTable, local_rank: int, logits: torc
         raise ValueError("x must be [T,d], w_gate and w_up [S,f,d], of one dtype")
     dt, dev = _dtype_code(x), logits.device
     n_shared = _shared_weights(shared, 2, d, f, x.dtype)
-    _ws(ws, grace_workspace_bytes(T, E, max(k, 1), table.I, d, f, 0, dt), dev)
+    _need_ws(ws, grace_workspace_bytes(T, E, max(k, 1), table.I, d, f, 0, dt))
     if n_shared:
-        _ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt), dev)
+        _need_ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt))
     i32 = dict(dtype=torch.int32, device=dev)
     te, tw = torch.empty((T, k), **i32), torch.empty((T, k), dtype=torch.float32, device=dev)
     ti, cnt = torch.empty((T, k), **i32), torch.empty((E,), **i32)
@@ -521,14 +528,18 @@ def grace_dispatch_ffn_down_share(table: GraceTable, rank: int, inst_off: torch.
     S, d, f = w_down.shape
     _need(topk_weight, "topk_weight", torch.float32, T * k)
     _need(perm_pos, "perm_pos", torch.int32, T * k)
+    _need(inst_off, "inst_off", torch.int32, table.I + 1)
     _need(y, "y", w_down.dtype, T * k * d)
-    n_shared = _shared_weights(None if shared_down is None else (shared_down,), 1, d, f, w_down.dtype)
+    n_shared, dt = _shared_weights(None if shared_down is None else (shared_down,), 1, d, f, w_down.dtype), _dtype_code(w_down)
+    _need_ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, dt))
     if n_shared:
         _need(y_shared, "y_shared", w_down.dtype, T * d)
+        _need_ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt))
     if out is None:
         out = torch.empty((T, d), dtype=y.dtype, device=y.device)
+    _need(out, "out", w_down.dtype, T * d)
     _check(load_library().grace_dispatch_ffn_down_share(
-        table.handle, rank, _dp(inst_off), _dp(perm_pos), _dp(topk_weight), T, k, d, f, n_shared, _dtype_code(y), _dp(w_down) if S else None,
+        table.handle, rank, _dp(inst_off), _dp(perm_pos), _dp(topk_weight), T, k, d, f, n_shared, dt, _dp(w_down) if S else None,
         _dp(shared_down), _dp(y), _dp(y_shared), _dp(state), _dp(ws), _dp(ws_shared), _dp(out), _stream()))
     return out
 
@@ -610,8 +621,8 @@ def grace_expert_shared_ffn_up_scatter(table: GraceTable, rank: int, x: torch.Te
     for t, name, n in ((perm_pos, "perm_pos", T * k), (perm_src, "perm_src", T * k), (inst_off, "inst_off", table.I + 1)):
         _need(t, name, torch.int32, n)
     _need(xp, "xp", x.dtype, T * k * d)
-    _ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, dt), x.device)
-    _ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt), x.device)
+    _need_ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, dt))
+    _need_ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt))
     _check(load_library().grace_expert_shared_ffn_up_scatter(
         table.handle, rank, _dp(x), _dp(perm_pos), _dp(perm_src), _dp(xp), _dp(inst_off), T, k, d, f, n_shared, dt, _dp(w_gate) if S else None,
         _dp(w_up) if S else None, _dp(shared_gate), _dp(shared_up), _dp(state), _dp(ws), _dp(ws_shared), _stream()))
@@ -627,8 +638,12 @@ def grace_expert_shared_ffn_down(table: GraceTable, rank: int, inst_off: torch.T
     _need(y_shared, "y_shared", w_down.dtype, T * d)
     if tuple(shared_down.shape[1:]) != (d, f) or shared_down.dtype != w_down.dtype:
         raise ValueError("shared_down must be [n,d,f] of the dtype of w_down")
+    n_shared, dt = shared_down.shape[0], _dtype_code(w_down)
+    _need(inst_off, "inst_off", torch.int32, table.I + 1)
+    _need_ws(ws, grace_workspace_bytes(T, table.E, k, table.I, d, f, 0, dt))
+    _need_ws(ws_shared, grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt))
     _check(load_library().grace_expert_shared_ffn_down(
-        table.handle, rank, _dp(inst_off), T, k, d, f, shared_down.shape[0], _dtype_code(y), _dp(w_down) if S else None, _dp(shared_down),
+        table.handle, rank, _dp(inst_off), T, k, d, f, n_shared, dt, _dp(w_down) if S else None, _dp(shared_down),
         _dp(y), _dp(y_shared), _dp(state), _dp(ws), _dp(ws_shared), _stream()))
 
 

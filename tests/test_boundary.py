@@ -171,6 +171,39 @@ def test_caller_tensors_are_checked_before_a_kernel_writes_them():
             grace.grace_expert_ffn_up_share_scatter(table, 0, **{**a, name: bad})
 
 
+def test_caller_tensors_of_the_joined_calls_are_checked():
+    """The halves of a step that are one launch with other work: as the calls that they stand for, and the result too."""
+    T, k, I, d, f, n, bf = 6, 3, 5, 16, 64, 2, torch.bfloat16
+    table = types.SimpleNamespace(R=4, N=2, I=I, E=I, handle=None)
+    i32, row = lambda n: torch.zeros(n, dtype=torch.int32), lambda *s: torch.zeros(s, dtype=bf)
+    ws = torch.zeros(grace.grace_workspace_bytes(T, I, k, I, d, f), dtype=torch.uint8)
+    ws_shared = torch.zeros(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n), dtype=torch.uint8)
+    both = dict(inst_off=i32(I + 1), w_down=row(2, d, f), shared_down=row(n, d, f), y=row(T * k, d), y_shared=row(T, d), state=i32(8), ws=ws,
+                ws_shared=ws_shared)
+    bad = [(name, bad, name) for name, bads in dict(
+        inst_off=(i32(I), torch.zeros(I + 1, dtype=torch.int64), None), y=(row(T * k - 1, d), row(T * k, d).float()), y_shared=(row(T - 1, d), None),
+        state=(i32(7), None)).items() for bad in bads]
+    bad += [("ws", ws[:-1], "workspace"), ("ws_shared", ws_shared[:-1], "workspace"), ("ws", None, "workspace"), ("ws_shared", None, "workspace"),
+            ("shared_down", row(n, d, f + 8), "shared"), ("shared_down", row(n, d, f).float(), "shared")]
+    calls = ((grace.grace_dispatch_ffn_down_share, {**both, "perm_pos": i32(T * k), "topk_weight": torch.zeros(T, k), "out": row(T, d)},
+              [("perm_pos", i32(T * k - 1), "perm_pos"), ("topk_weight", torch.zeros(T, k).double(), "topk_weight"), ("out", row(T - 1, d), "out"),
+               ("out", row(T, d).float(), "out")]),
+             (grace.grace_expert_shared_ffn_down, {**both, "T": T, "k": k}, []))
+    for call, args, more in calls:
+        with pytest.raises(ValueError, match="live on the GPU"):
+            call(table, 0, **args)
+        for name, tensor, said in bad + more:
+            with pytest.raises(ValueError, match=said):
+                call(table, 0, **{**args, name: tensor})
+    up = dict(k=k, x=row(T, d), w_gate=row(2, f, d), w_up=row(2, f, d), state=i32(8), ws=ws, ws_shared=ws_shared)
+    for call, args in ((grace.grace_dispatch_ffn_up_share, {**up, "logits": torch.zeros(T, I), "shared": (row(n, f, d), row(n, f, d))}),
+                       (grace.grace_expert_shared_ffn_up_scatter, {**up, "perm_pos": i32(T * k), "perm_src": i32(T * k), "xp": row(T * k, d),
+                                                                   "inst_off": i32(I + 1), "shared_gate": row(n, f, d), "shared_up": row(n, f, d)})):
+        for name, tensor, said in (("ws", ws[:-1], "workspace"), ("ws", None, "workspace"), ("ws_shared", None, "workspace"), ("state", i32(7), "state")):
+            with pytest.raises(ValueError, match=said):
+                call(table, 0, **{**args, name: tensor})
+
+
 def test_native_calls_refuse_what_the_binding_refuses():
     """Checked before the library is reached: no device, and no table, is needed."""
     calls = binding._native()
