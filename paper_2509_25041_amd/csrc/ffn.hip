@@ -47,9 +47,11 @@ static int compute_units() {
     return cached[dev];
 }
 
-// The persistent kernel needs the 160 KB of dynamic LDS opted in, once per kernel and device.
+// Dynamic LDS that a launch may ask for without opting in.  Kernels that take more (the persistent ones 160 KB) are opted in, once per kernel and
+// device.
+constexpr int LDS_WITHOUT_ASKING = 65536;
 static bool allow_full_lds(const void *kernel, const char *what) {
-    constexpr int MAX_KERNELS = 32, MAX_DEVICES = 64;
+    constexpr int MAX_KERNELS = 64, MAX_DEVICES = 64;
     static std::mutex mu;
     static const void *known[MAX_KERNELS] = {nullptr};
     static bool done[MAX_KERNELS][MAX_DEVICES] = {{false}};
@@ -134,8 +136,7 @@ static Grid stream_grid(const GemmArgs &g, const Rows &rows, int n_cu, int64_t o
     if (stream_pieces<EL>(rows)) return {(std::max<int64_t>((rows.m_bound / strm::MAX_ROWS + g.S) * n_strips, n_cu) + 7) / 8 * 8, 256};
     const int64_t busy = std::min<int64_t>(g.S, rows.m_bound) * n_strips + others;
     int waves = 4;
-    // (no more than 64 KB of partial sums: a launch may ask for that much LDS without opting in)
-    while (waves < strm::MAX_WAVES && strm::lds_bytes(waves * 2, stream_fragments(rows)) <= 65536 &&
+    while (waves < strm::MAX_WAVES && strm::lds_bytes(waves * 2, stream_fragments(rows)) <= LDS_WITHOUT_ASKING &&
            busy * waves * 2 <= (int64_t)n_cu * 8 && g.K >= waves * 2 * 2 * strm::kstep<EL>())
         waves *= 2;
     return {n_strips * g.S, waves * 64};
@@ -635,7 +636,9 @@ extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t loc
         launch_tiny_up_mid(a, n_cu, (hipStream_t)stream);
     } else {
         const Grid l = dt == GRACE_BF16 ? stream_grid<true, 2>(shape, rows, n_cu, a.shared_strips) : stream_grid<true, 4>(shape, rows, n_cu, a.shared_strips);
-        launch_tiny_up(a, dt, l.threads / 64, pieces, n_cu, (hipStream_t)stream);
+        const int waves = l.threads / 64;   // (stream_grid's, whose partial sums alone may take 64 KB)
+        if (tiny_up_lds(T, waves, pieces) > LDS_WITHOUT_ASKING && !allow_full_lds(tiny_up_kernel_of(dt, T, E, pieces), who)) return GRACE_EHIP;
+        launch_tiny_up(a, dt, waves, pieces, n_cu, (hipStream_t)stream);
     }
     GRACE_LAUNCH_CHECK(who);
     return with_shared ? GRACE_OK : shared_alone();

@@ -120,7 +120,9 @@ __device__ __forceinline__ int rows_of_slot(const TinyUp &a, int slot, TinyRows 
     return __builtin_amdgcn_readfirstlane(n);
 }
 
-// waves: per workgroup; pieces: more than 64 tokens (fp32).  The caller checks the launch.
+// waves: per workgroup; pieces: more than 64 tokens (fp32).  The caller checks the launch, and allows the kernel LDS past 64 KB.
+int tiny_up_lds(int T, int waves, bool pieces);   // bytes
+const void *tiny_up_kernel_of(grace_dtype dt, int T, int E, bool pieces);
 void launch_tiny_up(const TinyUp &a, grace_dtype dt, int waves, bool pieces, int n_cu, hipStream_t st);
 // workgroups of the projection (the dispatch's T are extra), 0: too many tiles
 int64_t tiny_up_mid_blocks(int S, int K, int n_strips, int n_cu);

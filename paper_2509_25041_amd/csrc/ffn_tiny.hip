@@ -59,38 +59,45 @@ __global__ __launch_bounds__(64 * strm::MAX_WAVES) void tiny_up_kernel(const Tin
                                            (float4 *)(smem + ROWS_BYTES));
 }
 
-void launch_tiny_up(const TinyUp &tiles, grace_dtype dt, int waves, bool pieces, int n_cu, hipStream_t st) {
-    TinyUp a = tiles;
-    const int T = a.dispatch.T, E = a.dispatch.E;
-    const int mf = pieces ? 4 : T <= 16 ? 1 : T <= 32 ? 2 : 4;
-    const int lds = std::max((int)sizeof(TinyLds), ROWS_BYTES + strm::lds_bytes(waves, mf));
-    a.piece_rows = strm::MAX_ROWS;
-    auto tiles_of = [&] { return a.up.S * a.n_strips * ((T + a.piece_rows - 1) / a.piece_rows); };
-    while (pieces && a.piece_rows > 16 && 2 * tiles_of() <= n_cu) a.piece_rows /= 2;   // as gemm_stream_tiles_kernel's, of the tiles that there may be
-    const int blocks = pieces ? (tiles_of() + 7) / 8 * 8 : a.up.S * a.n_strips + a.shared_strips;
-    auto launch = [&](auto kernel) { kernel<<<(unsigned)(T + blocks), waves * 64, lds, st>>>(a); };
+static int up_fragments(int T, bool pieces) { return pieces ? 4 : T <= 16 ? 1 : T <= 32 ? 2 : 4; }
+int tiny_up_lds(int T, int waves, bool pieces) { return std::max((int)sizeof(TinyLds), ROWS_BYTES + strm::lds_bytes(waves, up_fragments(T, pieces))); }
+
+const void *tiny_up_kernel_of(grace_dtype dt, int T, int E, bool pieces) {
+    const int mf = up_fragments(T, pieces);
     auto by_rows = [&](auto vpl, auto gate, auto el) {
         constexpr int VPL = decltype(vpl)::value, EL = decltype(el)::value;
         constexpr Gate GATE = decltype(gate)::value;
         if constexpr (EL == 4 && VPL == 1 && GATE != Gate::WAVE) {
-            if (pieces) return launch(tiny_up_kernel<VPL, GATE, EL, 4, true>);
+            if (pieces) return (const void *)tiny_up_kernel<VPL, GATE, EL, 4, true>;
         }
-        if (mf == 1) return launch(tiny_up_kernel<VPL, GATE, EL, 1, false>);
         if constexpr (!(VPL == 1 && GATE == Gate::WAVE)) {
-            if (mf == 2) return launch(tiny_up_kernel<VPL, GATE, EL, 2, false>);
-            if constexpr (VPL == 1) launch(tiny_up_kernel<VPL, GATE, EL, 4, false>);
+            if (mf == 2) return (const void *)tiny_up_kernel<VPL, GATE, EL, 2, false>;
+            if constexpr (VPL == 1) {
+                if (mf == 4) return (const void *)tiny_up_kernel<VPL, GATE, EL, 4, false>;
+            }
         }
+        return (const void *)tiny_up_kernel<VPL, GATE, EL, 1, false>;
     };
     auto by_gate = [&](auto el) {
         using std::integral_constant;
-        if (E > 128) by_rows(integral_constant<int, 4>{}, integral_constant<Gate, Gate::WAVE>{}, el);
-        else if (E > 64) by_rows(integral_constant<int, 2>{}, integral_constant<Gate, Gate::WAVE>{}, el);
-        else if (T <= 4) by_rows(integral_constant<int, 1>{}, integral_constant<Gate, Gate::WAVE>{}, el);
-        else if (E <= TINY_LANE_E) by_rows(integral_constant<int, 1>{}, integral_constant<Gate, Gate::LANES>{}, el);
-        else by_rows(integral_constant<int, 1>{}, integral_constant<Gate, Gate::ROWS>{}, el);
+        if (E > 128) return by_rows(integral_constant<int, 4>{}, integral_constant<Gate, Gate::WAVE>{}, el);
+        if (E > 64) return by_rows(integral_constant<int, 2>{}, integral_constant<Gate, Gate::WAVE>{}, el);
+        if (T <= 4) return by_rows(integral_constant<int, 1>{}, integral_constant<Gate, Gate::WAVE>{}, el);
+        if (E <= TINY_LANE_E) return by_rows(integral_constant<int, 1>{}, integral_constant<Gate, Gate::LANES>{}, el);
+        return by_rows(integral_constant<int, 1>{}, integral_constant<Gate, Gate::ROWS>{}, el);
     };
-    if (dt == GRACE_BF16) by_gate(std::integral_constant<int, 2>{});
-    else by_gate(std::integral_constant<int, 4>{});
+    return dt == GRACE_BF16 ? by_gate(std::integral_constant<int, 2>{}) : by_gate(std::integral_constant<int, 4>{});
+}
+
+void launch_tiny_up(const TinyUp &tiles, grace_dtype dt, int waves, bool pieces, int n_cu, hipStream_t st) {
+    TinyUp a = tiles;
+    const int T = a.dispatch.T;
+    a.piece_rows = strm::MAX_ROWS;
+    auto tiles_of = [&] { return a.up.S * a.n_strips * ((T + a.piece_rows - 1) / a.piece_rows); };
+    while (pieces && a.piece_rows > 16 && 2 * tiles_of() <= n_cu) a.piece_rows /= 2;   // as gemm_stream_tiles_kernel's, of the tiles that there may be
+    const int blocks = pieces ? (tiles_of() + 7) / 8 * 8 : a.up.S * a.n_strips + a.shared_strips;
+    void *params[] = {&a};
+    (void)hipLaunchKernel(tiny_up_kernel_of(dt, T, a.dispatch.E, pieces), dim3((unsigned)(T + blocks)), dim3(waves * 64), params, tiny_up_lds(T, waves, pieces), st);
 }
 
 }  // namespace grace
