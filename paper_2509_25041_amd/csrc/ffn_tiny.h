@@ -51,7 +51,7 @@ __device__ __forceinline__ void tokens_of(const TinyArgs &d, int e, uint32_t *ma
             uint32_t key[VPL], own = 0;
 #pragma unroll
             for (int v = 0; v < VPL; ++v) {
-                key[v] = ordered_bits(raw[i][v] == 0.0f ? 0.0f : raw[i][v]);
+                key[v] = ordered_bits(raw[i][v] == 0.0f ? 0.0f : not_all_ones(raw[i][v]));
                 if (v == e >> 6) own = key[v];
             }
             own = (uint32_t)__shfl((int)own, (of << shift) + (e & (width - 1)), 64);

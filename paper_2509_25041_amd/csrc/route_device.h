@@ -11,6 +11,9 @@ __device__ __forceinline__ uint32_t ordered_bits(float v) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// A logit, the NaN of all ones as the next NaN: ordered_bits are then never the 0 that marks "no expert here".
+__device__ __forceinline__ float not_all_ones(float v) { return __uint_as_float(min(__float_as_uint(v), 0xFFFFFFFEu)); }
+
 // Maximum of v over the 64 lanes, as a uniform value: four butterfly steps inside each row of 16
 // lanes with DPP operands (quad swaps, half-row mirror, row mirror), then the four row maxima
 // through scalar registers.  All 64 lanes must be active.

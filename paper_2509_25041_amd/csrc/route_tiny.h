@@ -87,6 +87,8 @@ struct TinyGate {
             for (int i = 0; i < PASSES; ++i) {
                 const int t = token(i0 + i);
                 if (((i0 + i) * waves + wave) * AT_ONCE >= T) break;   // uniform per wavefront
+#pragma unroll
+                for (int u = 0; u < NU; ++u) raw[i][u] = not_all_ones(raw[i][u]);
                 if constexpr (GATE == Gate::LANES) {
                     uint32_t key[NU];
 #pragma unroll
@@ -100,7 +102,7 @@ struct TinyGate {
                             best = more ? key[u] : best;
                             e = more ? u : e;
                         }
-                        if (t < T && best != 0u) chosen(t, j, e);
+                        if (t < T) chosen(t, j, e);   // (k is at most E: there is one)
 #pragma unroll
                         for (int u = 0; u < NU; ++u) key[u] = e == u ? 0u : key[u];
                     }

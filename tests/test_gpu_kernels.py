@@ -856,3 +856,49 @@ def test_stale_assignments_stay_inside_the_tokens(T, k, d, f, S, n_shared, kerne
     other = torch.ones(n, dtype=torch.bool, device="cuda")
     other[at] = False
     assert torch.equal(hidden[0][other], hidden[1][other]) and torch.isfinite(hidden[1].float()).all()
+
+
+@pytest.mark.parametrize("T,E,k,d,f,dtype", [
+    (2, 3, 3, 64, 64, "f32"),            # a wavefront per token, in units of columns
+    (16, 6, 5, 64, 64, "f32"),           # a lane per token
+    (40, 16, 15, 64, 32, "f32"),
+    (13, 40, 20, 64, 32, "bf16"),        # four tokens per wavefront
+    (12, 100, 60, 64, 16, "bf16"),       # experts in a lane: broadcast, and (k small) rounds
+    (32, 70, 3, 64, 16, "bf16"),
+    (96, 16, 2, 320, 2000, "bf16"),      # the 96-row kernel
+])
+def test_joined_dispatch_with_logits_that_are_no_numbers(T, E, k, d, f, dtype):
+    """A token whose logits are NaN (any bits) or infinite spoils nothing but itself: tiles and dispatch see the same choices."""
+    table = grace.GraceTable(E, 2, 1, [0, 0], [1, 1], list(range(E + 1)), [e % 2 for e in range(E)])
+    tdt, dt = (torch.bfloat16, grace.GRACE_BF16) if dtype == "bf16" else (torch.float32, grace.GRACE_F32)
+    assert grace.grace_dispatch_joins_ffn(table, 0, T, k, d, f, dt)
+    S = len(table.local_experts(0))
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    w = [(torch.randn(s, generator=gen, device="cuda") * 0.1).to(tdt) for s in ((S, f, d), (S, f, d), (S, d, f))]
+    x, logits = torch.randn((T, d), generator=gen, device="cuda").to(tdt), torch.randn((T, E), generator=gen, device="cuda")
+    bits = logits.view(torch.int32)
+    odd = list(range(0, T, 3))
+    for n, t in enumerate(odd):     # all ones, as few as leave it chosen or all; quiet NaN of either sign; infinities
+        bits[t, (t + n) % E:] = [-1, 0x7FC00000, -1, 0x7F800000, -0x00400000][n % 5]
+        if n % 2:
+            bits[t, ::3] = [-1, -2, 0x7F800000][n % 3]
+    y, state = torch.zeros((T * k, d), dtype=tdt, device="cuda"), torch.zeros(8, dtype=torch.int32, device="cuda")
+    ws = torch.empty(grace.grace_workspace_bytes(T, E, k, E, d, f, 0, dt), dtype=torch.uint8, device="cuda")
+    route, perm = grace.grace_dispatch_ffn_up_share(table, 0, logits, k, x, w[0], w[1], state, ws)
+    out = grace.grace_dispatch_ffn_down_share(table, 0, perm[2], perm[0], route[1], w[2], y, state, ws)
+    pos, ioff = perm[0].long().view(T, k), perm[2].long()
+    assert ((pos >= 0) & (pos < T * k)).all() and pos.view(-1).unique().numel() == T * k        # every choice has its row
+    assert torch.equal(perm[5][pos.view(-1)], x.repeat_interleave(k, 0))
+    # in fp32: rows of this rank, and the tokens with ordinary logits
+    want = torch.zeros((T * k, d), device="cuda")
+    for s in range(S):
+        r = slice(int(ioff[s]), int(ioff[s + 1]))
+        a = perm[5][r].float()
+        h = (torch.nn.functional.silu(a @ w[0][s].float().T) * (a @ w[1][s].float().T)).to(tdt).float()
+        want[r] = h @ w[2][s].float().T
+    plain = torch.tensor([t not in odd for t in range(T)], device="cuda")
+    bound = 2.0 ** -6 if dtype == "bf16" else 1e-5      # two roundings of 2^-9 at most each, of values next to a rounding border the last digit
+    assert float((y.float() - want).abs().max()) <= bound * float(want.abs().max())
+    want_out = (want[pos] * route[1][..., None]).sum(1)
+    assert torch.isfinite(out[plain].float()).all()
+    assert float((out.float() - want_out)[plain].abs().max()) <= bound * float(want_out[plain].abs().max())
