@@ -4,6 +4,7 @@ from __future__ import annotations
 import ctypes as C
 import importlib
 import os
+import warnings
 from typing import Optional, Sequence, Tuple
 
 import numpy as np
@@ -28,7 +29,7 @@ EXPORTS = ("grace_table_validate", "grace_table_create", "grace_table_destroy", 
            "grace_last_error")
 
 _lib: Optional[C.CDLL] = None
-_calls = None   # the module of the calls that allocate their outputs (csrc/torch_calls.cpp)
+_calls = None   # the module of the calls that allocate their outputs (csrc/torch_calls.cpp), False: it cannot be had
 
 
 class GraceError(RuntimeError):
@@ -45,11 +46,11 @@ def load_library() -> C.CDLL:
     """Load the in-tree shared library.  It is built first when it is absent or older than any of
     its sources, so a forgotten rebuild cannot put yesterday's kernels under today's tests; where the
     sources are newer and no compiler is available the call fails instead of loading the old code."""
-    global _lib, _calls
+    global _lib
     if _lib is not None:
         return _lib
     if _build.is_stale():
-        _build.build()
+        _build.build_library()
     lib = C.CDLL(_build.LIB)
     vp, i32, u64 = C.c_void_p, C.c_int32, C.c_size_t
     lib.grace_last_error.restype = C.c_char_p
@@ -98,10 +99,7 @@ def load_library() -> C.CDLL:
     for name in EXPORTS:
         if name not in ("grace_last_error", "grace_workspace_bytes"):
             getattr(lib, name).restype = C.c_int
-    calls = importlib.import_module("._torch_calls", __package__)
-    calls.bind(*(C.cast(f, vp).value for f in (lib.grace_workspace_bytes, lib.grace_route, lib.grace_permute, lib.grace_route_permute,
-                                               lib.grace_send_lists_fresh)))
-    _lib, _calls = lib, calls
+    _lib = lib
     return lib
 
 
@@ -122,9 +120,22 @@ def _made(result):
 
 
 def _native():
+    """The module of the calls that allocate their outputs, built first where it is absent or older than its source; None where it cannot be
+    built (g++, Python's or torch's headers missing): these calls then go through Python, as those on the caller's buffers do."""
+    global _calls
     if _calls is None:
-        load_library()
-    return _calls
+        lib = load_library()
+        try:
+            if _build.calls_are_stale():
+                _build.build_calls()
+            calls = importlib.import_module("._torch_calls", __package__)
+            calls.bind(*(C.cast(f, C.c_void_p).value for f in (lib.grace_workspace_bytes, lib.grace_route, lib.grace_permute, lib.grace_route_permute,
+                                                               lib.grace_send_lists_fresh)))
+        except (OSError, RuntimeError, ImportError) as e:
+            warnings.warn(f"the binding's native calls are not available, calls that allocate go through Python: {e}")
+            calls = False
+        _calls = calls
+    return _calls or None
 
 
 def _host(a, dtype) -> np.ndarray:
@@ -248,8 +259,9 @@ def grace_route(table: GraceTable, local_rank: int, logits: torch.Tensor, k: int
                 rr_in: Optional[torch.Tensor] = None, rr_out: Optional[torch.Tensor] = None,
                 ws: Optional[torch.Tensor] = None, out=None, policy: int = GRACE_POLICY_TAR):
     """-> (topk_expert [T,k] i32, topk_weight [T,k] f32, topk_inst [T,k] i32, expert_count [E] i32)."""
-    if out is None and ws is None:
-        return _made(_native().route(table.handle.value, table.I, local_rank, logits, k, renorm, rr_in, rr_out, policy, _stream()))
+    native = _native() if out is None and ws is None else None
+    if native:
+        return _made(native.route(table.handle.value, table.I, local_rank, logits, k, renorm, rr_in, rr_out, policy, _stream()))
     T, E = logits.shape
     dev = logits.device
     if logits.dtype != torch.float32:
@@ -267,8 +279,9 @@ def grace_route(table: GraceTable, local_rank: int, logits: torch.Tensor, k: int
 def grace_permute(table: GraceTable, topk_inst: torch.Tensor, x: Optional[torch.Tensor], ws: Optional[torch.Tensor] = None,
                   out=None, xp: Optional[torch.Tensor] = None):
     """-> (perm_pos, perm_src, inst_off, rank_off, node_off, xp)."""
-    if out is None and ws is None and xp is None:
-        return _made(_native().permute(table.handle.value, table.E, table.I, table.R, table.N, topk_inst, x, _stream()))
+    native = _native() if out is None and ws is None and xp is None else None
+    if native:
+        return _made(native.permute(table.handle.value, table.E, table.I, table.R, table.N, topk_inst, x, _stream()))
     T, k = topk_inst.shape
     dev = topk_inst.device
     if out is None:
@@ -292,9 +305,10 @@ def grace_route_permute(table: GraceTable, local_rank: int, logits: torch.Tensor
                         ws: Optional[torch.Tensor] = None, policy: int = GRACE_POLICY_TAR):
     """grace_route and grace_permute as one call with fewer launches (see grace_moe.h).
     -> ((topk_expert, topk_weight, topk_inst, expert_count), (perm_pos, perm_src, inst_off, rank_off, node_off, xp))."""
-    if ws is None:
-        return _made(_native().route_permute(table.handle.value, table.I, table.R, table.N, local_rank, logits, k, x, renorm, rr_in, rr_out,
-                                             policy, _stream()))
+    native = _native() if ws is None else None
+    if native:
+        return _made(native.route_permute(table.handle.value, table.I, table.R, table.N, local_rank, logits, k, x, renorm, rr_in, rr_out,
+                                          policy, _stream()))
     T, E = logits.shape
     dev = logits.device
     if logits.dtype != torch.float32:
@@ -345,8 +359,9 @@ def grace_route_permute_static(table: GraceTable, local_rank: int, logits: torch
 def grace_send_lists(table: GraceTable, local_rank: int, topk_inst: torch.Tensor, ws: Optional[torch.Tensor] = None):
     """-> (rank_send_ptr [R+1], rank_send_tok [T*k], node_send_ptr [N+1], node_send_tok [T*k], expand [T*k],
     traffic [4] int64); see grace_moe.h."""
-    if ws is None:
-        return _made(_native().send_lists(table.handle.value, table.E, table.I, table.R, table.N, local_rank, topk_inst, _stream()))
+    native = _native() if ws is None else None
+    if native:
+        return _made(native.send_lists(table.handle.value, table.E, table.I, table.R, table.N, local_rank, topk_inst, _stream()))
     T, k = topk_inst.shape
     dev = topk_inst.device
     i32 = dict(dtype=torch.int32, device=dev)

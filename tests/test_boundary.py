@@ -3,6 +3,10 @@ declares, and rejects malformed tables / arguments on the host."""
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
+import sys
+import sysconfig
 import types
 
 import numpy as np
@@ -220,3 +224,42 @@ def test_native_calls_refuse_what_the_binding_refuses():
         calls.route(0, 4, 0, None, 2, 1, None, None, 0, 0)
     with pytest.raises(TypeError):
         calls.permute(0)
+
+
+def test_library_loads_without_the_native_calls(tmp_path):
+    """A tree without the module of the calls that allocate, and no compiler: the library loads, and the calls take the way through Python."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(grace.__file__)))
+    shutil.copytree(os.path.join(root, "include"), tmp_path / "include")
+    shutil.copytree(os.path.join(root, "paper_2509_25041_amd"), tmp_path / "paper_2509_25041_amd",
+                    ignore=shutil.ignore_patterns("_torch_calls*", "_build", "__pycache__"))
+    program = """
+import types, warnings, torch
+import paper_2509_25041_amd as grace
+table = types.SimpleNamespace(handle=types.SimpleNamespace(value=None), E=4, I=4, R=2, N=1)
+grace.binding._stream = lambda: 0
+assert grace.grace_workspace_bytes(64, 4, 2, 4) > 0
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    for call in (lambda: grace.grace_route(table, 0, torch.zeros(3, 4), 2), lambda: grace.grace_permute(table, torch.zeros((3, 2), dtype=torch.int32), None),
+                 lambda: grace.grace_route_permute(table, 0, torch.zeros(3, 4), 2, None), lambda: grace.grace_send_lists(table, 0, torch.zeros((3, 2), dtype=torch.int32))):
+        try:
+            call()
+        except ValueError as e:
+            assert "live on the GPU" in str(e), e
+        else:
+            raise AssertionError("not refused")
+assert len([w for w in said if "native" in str(w.message)]) == 1
+"""
+    run = subprocess.run([sys.executable, "-c", program], cwd=tmp_path, env={**os.environ, "PATH": str(tmp_path), "PYTHONPATH": str(tmp_path)},
+                         capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-2000:]
+
+
+def test_native_calls_belong_to_one_interpreter():
+    """The module is named and stamped for the Python and the torch that it is compiled against."""
+    from paper_2509_25041_amd import build
+    binding._native()
+    assert build.CALLS.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and binding._calls.__file__ == build.CALLS
+    assert not build.calls_are_stale()
+    with open(build.CALLS_STAMP) as fh:
+        assert fh.read().strip() == build.calls_digest() != build.source_digest()
