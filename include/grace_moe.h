@@ -209,8 +209,8 @@ int grace_route_permute(const grace_table *table, int32_t local_rank, grace_poli
  * the process ends.  The call allocates and frees nothing (no hipMalloc, no hipFree, no allocating
  * library routine); its first use on a device looks the array's address up once.
  * Limit: sizes whose histograms do not fit the array are rejected with GRACE_ESHAPE and a text
- * that says so (needed bytes = 16 * ceil(T / 16) * E + 8 * ceil(T * k / 512) * I, each term rounded
- * up to 256: e.g. T = 32768, E = 64, k = 6, I = 88 needs 2.3 MB; T = 100 000 with E = 128 does not
+ * that says so (needed bytes = 8 * ceil(T / 16) * E or 8 * ceil(T * k / 512) * I, whichever is more, rounded
+ * up to 512: e.g. T = 32768, E = 64, k = 6, I = 88 needs 1 MB; T = 100 000 with E = 128 does not
  * fit) - use grace_route_permute with a workspace then.
  * All calls on one GPU share that GPU's array: two calls that overlap in time on the same GPU (on
  * different streams or from different threads) race on it and must be serialised by the caller;

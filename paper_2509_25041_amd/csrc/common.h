@@ -72,10 +72,8 @@ int check_permute_args(const grace_table *table, const int32_t *topk_inst, int32
                        const int32_t *rank_off, const int32_t *node_off, const void *xp, const void *ws);
 int launch_topk(const float *logits, int T, int E, int k, int renorm, int32_t *topk_expert, float *topk_weight,
                 int32_t *chunk_hist, hipStream_t st);
-// Byte offset, inside the workspace, of the permutation's histograms when routing and permutation
-// share one call (the routing histograms of the same call lie below it).
-size_t fused_perm_ws_offset(int32_t T, int32_t E);
-// Workspace bytes of routing + permutation as one call (both sets of histograms and their prefix sums).
+// Workspace bytes of routing + permutation as one call: the gate's histograms and their prefix sums, or, where it is the two calls one after the
+// other, the permutation's in their place.
 size_t route_permute_ws_bytes(int32_t T, int32_t E, int32_t k, int32_t I);
 // The smallest batches, whose dispatch is one launch (route_tiny.h): most tokens, 0 if the table's keys do not fit the LDS.
 constexpr int MAX_KEYS = 256;             // experts and instances that the tables in LDS hold

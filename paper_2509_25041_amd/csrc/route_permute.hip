@@ -362,8 +362,7 @@ extern "C" int grace_route_permute_static(const grace_table *table, int32_t loca
                     "route_permute_static: T=%d, E=%d, k=%d, I=%d need %zu bytes of scratch, the static buffer holds %zu; "
                     "use grace_route_permute with a workspace",
                     T, E, k, table->I, need, (size_t)GRACE_STATIC_SCRATCH_BYTES);
-    // nothing in the scratch has to start at zero: every kernel of the call writes the histogram
-    // rows and counters it later reads (the top-k kernel clears the permutation's counters)
+    // nothing in the scratch has to start at zero: the call's kernels write every histogram row and sum that a later one reads
     return route_permute_impl(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight,
                               topk_inst, expert_count, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws,
                               stream);

@@ -249,13 +249,9 @@ int fold_mode(const grace_table *table, int nchunks, int nkeys) {
     return (nsuper + SUPER) * kb <= table->fold_two_level ? 2 : 0;
 }
 
-size_t fused_perm_ws_offset(int32_t T, int32_t E) {
-    return 2 * align_up((size_t)ceil_div(T, ROUTE_CHUNK_SMALL) * (size_t)E * 4, 256);
-}
-
 size_t route_permute_ws_bytes(int32_t T, int32_t E, int32_t k, int32_t I) {
-    const size_t chunks_p = (size_t)ceil_div((int64_t)T * k, PERM_CHUNK);
-    return fused_perm_ws_offset(T, E) + 2 * align_up(chunks_p * (size_t)I * 4, 256);
+    const size_t chunks_r = (size_t)ceil_div(T, ROUTE_CHUNK_SMALL), chunks_p = (size_t)ceil_div((int64_t)T * k, PERM_CHUNK);
+    return 2 * std::max(align_up(chunks_r * (size_t)E * 4, 256), align_up(chunks_p * (size_t)I * 4, 256));
 }
 }  // namespace grace
 
@@ -273,7 +269,6 @@ extern "C" size_t grace_workspace_bytes(int32_t T, int32_t E, int32_t k, int32_t
     const size_t el = dt == GRACE_F32 ? 4 : 2;
     const size_t n = (size_t)T * (size_t)k;
     const size_t chunks_p = (size_t)grace::ceil_div((int64_t)n, grace::PERM_CHUNK);
-    // routing and permutation histograms side by side (grace_route_permute uses both at once)
     size_t need = grace::route_permute_ws_bytes(T, E, k, I);
     need = std::max(need, grace::align_up(n * (size_t)f * el, 256));
     // rows by slots, of the smallest batches; larger ones ask for as much as the largest of these, so that their buffer does for those

@@ -46,9 +46,9 @@ def run_both(table, cfg, wl, local_rank, rr_in=None, policy=0):
 
 
 @pytest.mark.parametrize("name,sizes,local_rank", [
-    ("olmoe", (4096, 1500), 0),          # larger batches: top-k, pick (+ permutation histograms), positions, scatter
-    ("dsv2lite", (32768, 5000), 9),      # the largest config (2.3 MB of the 4 MiB array), then a smaller call
-    ("olmoe_decode512", (512, 64), 0),   # decode-sized: the single-workgroup index kernel
+    ("olmoe", (4096, 1500), 0),          # larger batches: top-k, picks and positions, scatter
+    ("dsv2lite", (32768, 5000), 9),      # the largest config (1 MB of the 4 MiB array), then a smaller call
+    ("olmoe_decode512", (512, 64), 0),   # decode-sized: the same three, then one launch
     ("tiny", (256, 1), 2),               # fp32 rows
 ])
 def test_static_scratch_matches_workspace_two_calls_in_a_row(name, sizes, local_rank):
@@ -73,3 +73,19 @@ def test_static_scratch_rejects_sizes_beyond_the_array():
     (te, tw, ti, cnt), perm = grace.grace_route_permute(table, 0, logits, cfg.k, x)
     torch.cuda.synchronize()
     assert int(perm[2][-1]) == cfg.T * cfg.k
+
+
+def test_static_scratch_holds_one_set_of_histograms():
+    """The call's kernels use the gate's histograms alone: 65536 tokens of 128 experts fill the array, whichever way the prefix counts go."""
+    T, E, k, R = 65536, 128, 8, 4
+    table = grace.GraceTable(E, R, 1, [0] * R, [1] * R, list(range(E + 1)), [e * R // E for e in range(E)])
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    logits, x = torch.randn((T, E), generator=gen, device="cuda"), torch.randn((T, 4), generator=gen, device="cuda")
+    for limits in ((-1, -1), (0, 0)):
+        table.set_fold_limits(*limits)
+        ref, got = grace.grace_route_permute(table, 0, logits, k, x), grace.grace_route_permute_static(table, 0, logits, k, x)
+        torch.cuda.synchronize()
+        for a, b in zip(ref[0] + ref[1], got[0] + got[1]):
+            assert same(a, b)
+    with pytest.raises(grace.GraceError, match="static buffer"):
+        grace.grace_route_permute_static(table, 0, torch.cat([logits, logits[:16]]), k, None)
