@@ -401,10 +401,14 @@ static int launch_joint(const GemmArgs *shared, const Rows &shared_rows, const G
     j.expert_strips = (experts.N + mid::Shape<FUSED_UP>::BN - 1) / mid::Shape<FUSED_UP>::BN;
     j.n_cu = n_cu;
     if (FUSED_UP && experts.sc_T > 0) {
-        // about 300 KB each, which takes 20 us; 200 and 400 KB are even, 800 is slower where the rows are many (3001 tokens, k = 6, f = 352 79.8, 80.8
-        // and 87.0 us a step), and so are half as many at most (89.0)
+        // One round of loads per wavefront and 300 KB per workgroup at most, up to one for each compute unit: a round of pieces takes several us
+        // whatever it moves, and short launches have no more.  d = 2048: 200 and 400 KB are even with 300, 800 slower where the rows are many (3001 tokens,
+        // k = 6, f = 352 79.8, 80.8 and 87.0 us a step), and so are half as many workgroups at most (89.0).  Layer steps, any number of rounds -> four -> two ->
+        // one: 512 tokens, k = 4, f = 352, two shared experts 51.5 -> 51.6 -> 49.3 -> 47.6 us; d = 256, 97 tokens, k = 2, f = 352, none 23.5 -> 20.4 -> 20.4 -> 20.4;
+        // 207 steps (d = 256 to 4096, 97 to 3000 tokens) with one round 3 % faster in the mean than with any number, 0.4 % than with four.
         const int64_t bytes = (int64_t)experts.sc_T * (1 + experts.sc_k) * experts.sc_row_bytes;
-        j.movers = (int)std::min(std::min<int64_t>(n_cu, (experts.sc_T + 3) / 4), bytes / (300 << 10) + 1);
+        const int64_t pieces = (int64_t)experts.sc_T * mid::move_pieces(experts.sc_row_bytes), round = mid::MOVE_AHEAD * (mid::THREADS / 64);
+        j.movers = (int)std::min<int64_t>(n_cu, std::max(bytes / (300 << 10) + 1, (pieces + round - 1) / round));
     }
     const Grid l = {j.movers + j.shared_blocks + e.groups, mid::THREADS};
     if (!launchable(l)) return fail(GRACE_ESHAPE, "%s: grid too large", what);

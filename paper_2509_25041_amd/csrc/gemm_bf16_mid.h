@@ -263,36 +263,37 @@ inline int64_t grid_blocks(int64_t tiles, int n_cu, bool exact) {
 // of d = 4096, f = 14336, down 114 -> 60 us).  More halves than units are slower again (308 of 32 rows 16.0 us, 220 of 48 rows 15.0 us).
 // With fewer than four steps along K there is too little to cut: K = 128, 64 tiles of 4 to 16 segments whole 5.5, halved 6.7 us (K = 256, 48
 // tiles 7.0 -> 5.9 us).
-// Rows of tokens b, b + movers, ... to their positions: a row is read once and written k times, AHEAD tokens at a time.  A token's positions
-// wait in the lanes (64 at a time), so that no store waits for a load of its own.
+// Rows to their positions: a piece of 64 16-byte vectors of a token's row is read once and written k times, by one wavefront, AHEAD pieces at a time.  A
+// token's positions wait in the lanes (64 at a time), so that no store waits for a load of its own.  (By pieces, not with a workgroup per token:
+// narrow rows would leave its wavefronts idle.  Layer steps of 97 tokens, k = 2, f = 352, d = 256, 512, 1024 45.0, 45.7, 32.8 -> 20.4, 21.6, 24.6 us.)
+constexpr int MOVE_AHEAD = 4;
+__host__ __device__ inline int move_pieces(int row_bytes) { return (row_bytes + 1023) >> 10; }   // of a row
 __device__ __forceinline__ void move_rows(const GemmArgs &g, int b, int movers) {
-    constexpr int AHEAD = 4;
-    const int vecs = g.sc_row_bytes >> 4, n = g.sc_T * g.sc_k, lane = (int)threadIdx.x & 63;   // (n below 2^31)
+    const int vecs = g.sc_row_bytes >> 4, per_row = move_pieces(g.sc_row_bytes), n = g.sc_T * g.sc_k, lane = (int)threadIdx.x & 63;   // (n below 2^31)
+    const int wave = __builtin_amdgcn_readfirstlane(b * (THREADS / 64) + ((int)threadIdx.x >> 6)), waves = movers * (THREADS / 64);
+    const int64_t pieces = (int64_t)g.sc_T * per_row;   // (below 2^31, as the tokens' bytes are)
     const uint4 *const x = (const uint4 *)g.sc_x;
     uint4 *const xp = (uint4 *)g.sc_xp;
-    for (int c0 = (int)threadIdx.x & ~63; c0 < vecs; c0 += THREADS) {   // whole wavefronts stay
-        const int c = min(c0 + lane, vecs - 1);
-        const bool store = c0 + lane < vecs;
-        for (int t0 = b; t0 < g.sc_T; t0 += AHEAD * movers)
-            for (int j0 = 0; j0 < g.sc_k; j0 += 64) {
-                uint4 v[AHEAD];
-                int pos[AHEAD];
+    for (int64_t p0 = wave; p0 < pieces; p0 += MOVE_AHEAD * waves)
+        for (int j0 = 0; j0 < g.sc_k; j0 += 64) {
+            uint4 v[MOVE_AHEAD];
+            int pos[MOVE_AHEAD], c[MOVE_AHEAD];
 #pragma unroll
-                for (int i = 0; i < AHEAD; ++i) {
-                    const int64_t t = min(t0 + i * movers, g.sc_T - 1);
-                    v[i] = x[t * vecs + c];
-                    pos[i] = g.sc_pos[t * g.sc_k + min(j0 + lane, g.sc_k - 1)];
-                }
+            for (int i = 0; i < MOVE_AHEAD; ++i) {
+                const uint32_t piece = (uint32_t)min(p0 + i * waves, pieces - 1), t = piece / (uint32_t)per_row;
+                c[i] = (int)(piece - t * (uint32_t)per_row) * 64 + lane;
+                v[i] = x[(int64_t)t * vecs + min(c[i], vecs - 1)];
+                pos[i] = g.sc_pos[(int64_t)t * g.sc_k + min(j0 + lane, g.sc_k - 1)];
+            }
 #pragma unroll
-                for (int i = 0; i < AHEAD; ++i) {
-                    if (t0 + i * movers >= g.sc_T) break;   // uniform
-                    for (int j = 0; j < min(64, g.sc_k - j0); ++j) {
-                        const int p = __builtin_amdgcn_readlane(pos[i], j);
-                        if (p >= 0 && p < n && store) nt_store16(v[i], &xp[(int64_t)p * vecs + c]);
-                    }
+            for (int i = 0; i < MOVE_AHEAD; ++i) {
+                if (p0 + i * waves >= pieces) break;   // uniform
+                for (int j = 0; j < min(64, g.sc_k - j0); ++j) {
+                    const int p = __builtin_amdgcn_readlane(pos[i], j);
+                    if (p >= 0 && p < n && c[i] < vecs) nt_store16(v[i], &xp[(int64_t)p * vecs + c[i]]);
                 }
             }
-    }
+        }
 }
 
 // Workgroup number b of `grid` does its tiles.

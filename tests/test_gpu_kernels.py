@@ -902,3 +902,59 @@ def test_joined_dispatch_with_logits_that_are_no_numbers(T, E, k, d, f, dtype):
     want_out = (want[pos] * route[1][..., None]).sum(1)
     assert torch.isfinite(out[plain].float()).all()
     assert float((out.float() - want_out)[plain].abs().max()) <= bound * float(want_out[plain].abs().max())
+
+
+@pytest.mark.parametrize("T,k,d,n_shared", [(97, 3, 8, 2), (300, 4, 264, 0), (130, 2, 512, 1), (700, 5, 520, 2), (260, 64, 1032, 0), (3000, 2, 64, 1), (97, 3, 4104, 2)])
+def test_rows_of_any_width_moved_beside_the_tiles(T, k, d, n_shared):
+    """Pieces of a row: one of few lanes, whole ones, a last one of one lane; more pieces than wavefronts; positions outside the buffer."""
+    S, E, f, bf = 2, 2 * k, 64, torch.bfloat16
+    table = grace.GraceTable(E, 2, 1, [0, 0], [1, 1], list(range(E + 1)), [e >= S for e in range(E)])
+    assert grace.grace_ffn_joins_shared(True, T, d, f, n_shared, k=k, S=S, I=E)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s: (torch.randn(s, generator=gen, device="cuda") * 0.1).to(bf)
+    x, w, sh = normal(T, d), (normal(S, f, d), normal(S, f, d)), (normal(n_shared, f, d), normal(n_shared, f, d))
+    _, (pos, src, ioff, _, _, _) = grace.grace_route_permute(table, 0, torch.randn((T, E), generator=gen, device="cuda"), k, None)
+    dropped = pos.clone()
+    dropped[::11], dropped[5::13] = -1, T * k
+    xp, want = (torch.full((T * k + 4, d), 7.0, dtype=bf, device="cuda") for _ in range(2))
+    grace.grace_permute_rows(x, dropped, k, want)
+    ws, state = torch.empty(grace.grace_workspace_bytes(T, E, k, E, d, f), dtype=torch.uint8, device="cuda"), torch.zeros(8, dtype=torch.int32, device="cuda")
+    if n_shared:
+        ws2 = torch.empty(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared), dtype=torch.uint8, device="cuda")
+        grace.grace_expert_shared_ffn_up_scatter(table, 0, x, dropped, src, xp, ioff, k, *w, *sh, state, ws, ws2)
+    else:
+        grace.grace_expert_ffn_up_share_scatter(table, 0, x, dropped, src, xp, ioff, k, *w, state, ws)
+    assert torch.equal(xp, want)
+
+
+@pytest.mark.parametrize("d,n_shared", [(256, 0), (512, 0), (256, 2), (512, 2)])
+def test_narrow_rows_do_not_hold_up_the_launch_that_moves_them(d, n_shared):
+    """A step with the rows moved beside the tiles against one with a launch for them: no slower.  (Twice as slow when a workgroup took a token at a
+    time; the bound leaves room for noise.)"""
+    T, k, E, f, bf = 1000, 2, 16, 352, torch.bfloat16
+    table = grace.GraceTable(E, 4, 1, [0] * 4, [1] * 4, list(range(E + 1)), [e // 4 for e in range(E)])
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    normal = lambda *s: (torch.randn(s, generator=gen, device="cuda") * 0.1).to(bf)
+    shared = (normal(n_shared, f, d), normal(n_shared, f, d), normal(n_shared, d, f)) if n_shared else None
+    layer = grace.GraceMoELayer(table, 0, T, k, d, f, bf, normal(4, f, d), normal(4, f, d), normal(4, d, f), shared=shared)
+    logits, x = torch.randn((T, E), generator=gen, device="cuda"), normal(T, d)
+    assert layer.join_shared[True] if n_shared else layer.gather_rows
+    times = []
+    for joint in (True, False):
+        if not joint:
+            layer.gather_rows, layer.join_shared, layer._key = False, [False, False], None
+        layer.forward(logits, x)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                layer.forward(logits, x)
+        layer._key = None
+        best = float("inf")
+        for _ in range(10):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record(); graph.replay(); b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    assert times[0] <= 1.3 * times[1], times
