@@ -451,9 +451,60 @@ static Rows expert_rows(int S, int I, int32_t T, int32_t k) {
 }
 static Rows shared_rows(int32_t T) { return {T, T, 1, true, T, T}; }
 
+// Whether the joined gate+up projection is dealt out in units of 4 columns (ffn_tiny_cols.hip) rather than a workgroup per slot and strip (ffn_tiny.hip):
+// up to 8 tokens, K in whole 128-byte lines.  Every workgroup waits for the whole gate then, which pays where slots without rows would leave
+// workgroups idle: not for one or two slots (d = 4096, f = 3584, 1 to 8 tokens 0.91 to 1.04 times as fast), for more than 4 tokens not where a
+// slot has fewer units than half the compute units (f = 192 and 256, 5 and 8 tokens 0.97 to 1.06), and not with shared experts, whose tiles
+// need not wait (2 and 4 of f = 352 and 1408 0.88 to 1.05).  Where it is taken, steps of 1 to 8 tokens, 8 to 19 slots: f = 704 to 2816 1.01 to
+// 1.21, in the mean 1.08; f = 192 and 256, up to 4 tokens 1.05 to 1.22.
+static bool deals_columns(int S, int32_t T, int32_t d, int32_t f, grace_dtype dt, int n_cu) {
+    return S > 2 && T <= TINY_COLS_T && (T <= 4 || f >= 2 * n_cu) && (int64_t)d * (dt == GRACE_F32 ? 4 : 2) % 128 == 0;
+}
+
+// One launch for the down projections and the combine of a joined step (ffn_tiny_down.hip): its operands fit 32-bit offsets and its partial
+// sums the LDS.  A workgroup has 8 or 16 columns of everything to do, so narrow tokens leave compute units idle: with fewer
+// workgroups than 5 for 8 of them it has to be little work each, and more of it where shared experts' own launch goes too.
+// Whole steps, two or three launches -> one, bf16 | fp32, 2 to 16 tokens, rank with half the experts: d >= 1536 1.01 to 1.46 | 0.98 to 1.40 times
+// as fast (f = 1024 to 4096; with 2 shared experts 1.01 to 1.35 | 1.00 to 1.31); d = 1024 with 4 parts 1.09 to 1.24 | 1.08 to 1.25, with 8 to 32
+// 0.90 to 1.07 | 0.87 to 1.08; d = 512 with 4 1.12 to 1.20 | 1.14 to 1.25, with 8 to 32 0.77 to 0.97 | 0.75 to 0.92; with 2 shared
+// experts and 10 to 18 parts d = 1024 1.13 to 1.38 | 1.09 to 1.34, d = 512 1.02 to 1.36 | 0.95 to 1.29.
+static bool joins_combine(int32_t T, int32_t k, int32_t d, int32_t f, int n_shared, int S, grace_dtype dt, int n_cu) {
+    const int64_t row = (int64_t)f * (dt == GRACE_F32 ? 4 : 2);
+    if (T > TINY_DOWN_T || k > GRACE_MAX_TOPK || row % 16 != 0 || 16 * row >= (int64_t)NO_DATA || std::max(n_shared, 1) * T * row >= (int64_t)NO_DATA) return false;
+    if (tiny_down_lds(T, k, S, n_shared, d, n_cu) > pers::LDS_BYTES) return false;
+    const int blocks = tiny_down_blocks(d, n_cu), parts = std::min(S, T * k) + n_shared;
+    return 8 * blocks >= 5 * n_cu || parts <= (n_shared ? std::max(16, blocks / 4) : 4);
+}
+
+// Whether tiny_up_kernel is faster than the two launches with `tiles` workgroups for the projection.  Every one of them looks for its rows (1.5 us), those
+// of slots without rows too, which the projection's own launch leaves at once.  Layer steps, two launches -> joined, 700 drawn ones (d = 64 to 4096, f = 64 to
+// 3584, 1 to 128 slots), by workgroups per compute unit, mean (least) times as fast: 9 to 32 tokens, bf16, up to 4 1.3 (1.02), 8 1.2 (1.03), 12 1.15 (1.01), 16
+// 1.03 (0.91), 32 0.95 (0.82), 112 0.66 (118 instead of 74 us); fp32 up to 4 1.2 (1.04), 6 1.15 (0.95), 8 1.03 (0.91), 24 0.93 (0.82); up to 8 tokens with
+// shared experts up to 24 1.3 (1.03), 64 0.94 (0.77), where the combine is joined too up to 44 1.4 (1.04), 64 1.0 (0.91).
+// Pieces of 64 rows (fp32), more than 16 experts: the dispatch's workgroups have little less to do than a launch of their own, so it pays where all are resident at
+// once (joined_waves: two per compute unit), 0.96 to 1.24, beyond 0.67 to 0.95.  Narrow rows and many choices of many experts likewise: beyond 0.89 to 0.98.
+static bool tiny_up_pays(int64_t tiles, bool pieces, int32_t T, int32_t k, int32_t d, int32_t f, int E, int S, int n_shared, grace_dtype dt, int n_cu) {
+    const int64_t most = pieces ? 2 : T > 32 ? 4 : T > 8 ? (dt == GRACE_BF16 ? 12 : 6) : joins_combine(T, k, d, f, n_shared, S, dt, n_cu) ? 56 : 24;
+    if (tiles > most * n_cu) return false;
+    const int64_t row_bytes = (int64_t)d * (dt == GRACE_F32 ? 4 : 2);
+    if ((pieces && E > TINY_LANE_E) || (row_bytes <= 512 && E > 64 && T * k > 120)) return T + tiles <= 2 * (int64_t)n_cu;
+    return true;
+}
+
+// Wavefronts per workgroup of tiny_up_kernel, `waves` by the tiles alone: where these are few and short, the dispatch's workgroups, which have as
+// many, are the launch's end.  As many more as all workgroups can be resident with (16 wavefronts per compute unit).  Layer steps with `waves` = 4 -> 8 or 16,
+// us: 128 experts, k = 8, d = 64, f = 352, 30 tokens 22.0 -> 16.1 (two launches 18.1), 64, d = 256, f = 512, 63 tokens 22.7 -> 18.4 (21.0); fp32, 64, k = 6, f = 512,
+// 77 tokens 25.8 -> 21.4 (24.2).  Rows of more than 1 KB 0.97 to 1.09.
+static int joined_waves(int waves, int64_t tiles, bool pieces, int32_t T, int32_t k, int32_t d, int E, grace_dtype dt, int n_cu) {
+    if (E <= TINY_LANE_E || (!pieces && (int64_t)d * (dt == GRACE_F32 ? 4 : 2) > 1024)) return waves;
+    const int most = T > 32 ? 8 : strm::MAX_WAVES, at_once = E <= 64 ? 4 : 1;   // tokens of the gate per wavefront
+    while (waves < most && (waves * at_once < T || waves * 64 < T * k) && (T + tiles) * waves * 2 <= (int64_t)n_cu * 16) waves *= 2;
+    return waves;
+}
+
 // Smallest batches: one launch for the dispatch and the experts' gate+up projection (ffn_tiny.hip), whose hidden activation the down
 // projection then finds slot by slot.
-static bool joins_dispatch(const grace_table *table, int32_t rank, int32_t T, int32_t k, int32_t d, int32_t f, grace_dtype dt, int n_cu) {
+static bool joins_dispatch(const grace_table *table, int32_t rank, int32_t T, int32_t k, int32_t d, int32_t f, int n_shared, grace_dtype dt, int n_cu) {
     const int S = table->rank_ptr[rank + 1] - table->rank_ptr[rank], el = dt == GRACE_F32 ? 4 : 2;
     if (S < 1 || !tiny_batch(T, k, table->E, table->I)) return false;
     if (S > k && (size_t)T * S * f * el > SLOT_ROWS_MOST) return false;
@@ -466,16 +517,20 @@ static bool joins_dispatch(const grace_table *table, int32_t rank, int32_t T, in
     Grid l = grid_of<true>(u, up, dt, rows, n_cu);
     if (u == Route::MID && dt == GRACE_BF16) {
         if (T > mid::BM) return false;   // one piece per slot
+        // (four wavefronts' dispatch is longer than the tiles: d = 256, 89 tokens of 60 experts, k = 6 24.8 -> 27.7 us a step, of 64, k = 8 37.1 -> 40.7)
+        if ((int64_t)d * el <= 512 && table->E > TINY_LANE_E && T * k > 256) return false;
         l.groups = tiny_up_mid_blocks(S, up.K, (up.N + mid::Shape<true>::BN - 1) / mid::Shape<true>::BN, n_cu);
         if (l.groups == 0) return false;
     } else if (u == Route::STREAM) {
-        const int64_t pieces = stream_pieces<4>(rows) && dt == GRACE_F32 ? (T + strm::MAX_ROWS - 1) / strm::MAX_ROWS : 1;
-        l.groups = (int64_t)S * ((up.N + strm::Shape<true>::COLS - 1) / strm::Shape<true>::COLS) * pieces;
-        if (T > 32 && l.groups > (pieces > 1 ? 2 : 4) * (int64_t)n_cu) return false;
+        const bool pieces = stream_pieces<4>(rows) && dt == GRACE_F32;
+        l.groups = (int64_t)S * ((up.N + strm::Shape<true>::COLS - 1) / strm::Shape<true>::COLS) * (pieces ? (T + strm::MAX_ROWS - 1) / strm::MAX_ROWS : 1);
+        const bool dealt = n_shared == 0 && deals_columns(S, T, d, f, dt, n_cu);
+        if (!dealt && !tiny_up_pays(l.groups, pieces, T, k, d, f, table->E, S, n_shared, dt, n_cu)) return false;
     } else {
         return false;
     }
     l.groups += T + 8;
+    l.threads = 64 * strm::MAX_WAVES;
     return launchable(l);
 }
 
@@ -571,16 +626,6 @@ static int expert_ffn_up(const char *who, const grace_table *table, int32_t rank
     return launch_gemm<true, pers::EXPERTS>(up, dt, rows, (hipStream_t)stream, who);
 }
 
-// Whether the joined gate+up projection is dealt out in units of 4 columns (ffn_tiny_cols.hip) rather than a workgroup per slot and strip (ffn_tiny.hip):
-// up to 8 tokens, K in whole 128-byte lines.  Every workgroup waits for the whole gate then, which pays where slots without rows would leave
-// workgroups idle: not for one or two slots (d = 4096, f = 3584, 1 to 8 tokens 0.91 to 1.04 times as fast), for more than 4 tokens not where a
-// slot has fewer units than half the compute units (f = 192 and 256, 5 and 8 tokens 0.97 to 1.06), and not with shared experts, whose tiles
-// need not wait (2 and 4 of f = 352 and 1408 0.88 to 1.05).  Where it is taken, steps of 1 to 8 tokens, 8 to 19 slots: f = 704 to 2816 1.01 to
-// 1.21, in the mean 1.08; f = 192 and 256, up to 4 tokens 1.05 to 1.22.
-static bool deals_columns(int S, int32_t T, int32_t d, int32_t f, grace_dtype dt, int n_cu) {
-    return S > 2 && T <= TINY_COLS_T && (T <= 4 || f >= 2 * n_cu) && (int64_t)d * (dt == GRACE_F32 ? 4 : 2) % 128 == 0;
-}
-
 extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T,
                                            int32_t E, int32_t k, int32_t renorm, const uint32_t *rr_in, uint32_t *rr_out,
                                            int32_t *topk_expert, float *topk_weight, int32_t *topk_inst, int32_t *expert_count,
@@ -602,7 +647,7 @@ extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t loc
     const int n_cu = compute_units();
     if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", who);
     auto shared_alone = [&] { return n_shared ? grace_shared_ffn_up(x, T, d, f, n_shared, dt, shared_gate, shared_up, ws_shared, stream) : GRACE_OK; };
-    if (T == 0 || !joins_dispatch(table, local_rank, T, k, d, f, dt, n_cu)) {
+    if (T == 0 || !joins_dispatch(table, local_rank, T, k, d, f, n_shared, dt, n_cu)) {
         rc = grace_route_permute(table, local_rank, policy, logits, T, E, k, renorm, rr_in, rr_out, topk_expert, topk_weight, topk_inst,
                                  expert_count, x, d, dt, perm_pos, perm_src, inst_off, rank_off, node_off, xp, ws, stream);
         if (rc != GRACE_OK) return rc;
@@ -640,7 +685,8 @@ extern "C" int grace_dispatch_ffn_up_share(const grace_table *table, int32_t loc
         launch_tiny_up_mid(a, n_cu, (hipStream_t)stream);
     } else {
         const Grid l = dt == GRACE_BF16 ? stream_grid<true, 2>(shape, rows, n_cu, a.shared_strips) : stream_grid<true, 4>(shape, rows, n_cu, a.shared_strips);
-        const int waves = l.threads / 64;   // (stream_grid's, whose partial sums alone may take 64 KB)
+        const int64_t tiles = (int64_t)S * a.n_strips * (pieces ? (T + strm::MAX_ROWS - 1) / strm::MAX_ROWS : 1) + a.shared_strips;
+        const int waves = joined_waves(l.threads / 64, tiles, pieces, T, k, d, E, dt, n_cu);   // (stream_grid's partial sums alone may take 64 KB)
         if (tiny_up_lds(T, waves, pieces) > LDS_WITHOUT_ASKING && !allow_full_lds(tiny_up_kernel_of(dt, T, E, pieces), who)) return GRACE_EHIP;
         launch_tiny_up(a, dt, waves, pieces, n_cu, (hipStream_t)stream);
     }
@@ -676,7 +722,7 @@ static_assert(SHARE_STATE_INTS == GRACE_SHARE_STATE_INTS, "header and kernels mu
 
 static int expert_ffn_down(const char *who, const grace_table *table, int32_t rank, const int32_t *inst_off, int32_t T,
                            int32_t k, int32_t d, int32_t f, grace_dtype dt, const void *w_down, void *y, int32_t *state,
-                           bool clear_others, void *ws, void *stream, bool joined = false) {
+                           bool clear_others, void *ws, void *stream, int joined_shared = -1 /* of a joined step: shared experts */) {
     int g0, S;
     int rc = expert_ffn_common(who, table, rank, T, k, d, f, dt, g0, S);
     if (rc != GRACE_OK) return rc;
@@ -696,10 +742,10 @@ static int expert_ffn_down(const char *who, const grace_table *table, int32_t ra
     GemmArgs dn = expert_shape(false, S, d, f);
     dn.A = ws; dn.B0 = w_down; dn.out = y;
     dn.seg_off = inst_off + g0;
-    if (joined) {
+    if (joined_shared >= 0) {
         const int n_cu = compute_units();
         if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", who);
-        if (joins_dispatch(table, rank, T, k, d, f, dt, n_cu)) dn.a_slot_rows = T;
+        if (joins_dispatch(table, rank, T, k, d, f, joined_shared, dt, n_cu)) dn.a_slot_rows = T;
     }
     dn.share_state = state; dn.stale = state ? 1 : clear_others ? 2 : 0; dn.share_rows = (int64_t)T * k; dn.share_row_vec = (int)((size_t)d * el / 16);
     return launch_gemm<false, pers::EXPERTS>(dn, dt, expert_rows(S, table->I, T, k), (hipStream_t)stream, who);
@@ -724,21 +770,6 @@ extern "C" int grace_expert_ffn_down_share(const grace_table *table, int32_t ran
     return expert_ffn_down("expert_ffn_down_share", table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream);
 }
 
-// One launch for the down projections and the combine of a joined step (ffn_tiny_down.hip): its operands fit 32-bit offsets and its partial
-// sums the LDS.  A workgroup has 8 or 16 columns of everything to do, so narrow tokens leave compute units idle: with fewer
-// workgroups than 5 for 8 of them it has to be little work each, and more of it where shared experts' own launch goes too.
-// Whole steps, two or three launches -> one, bf16 | fp32, 2 to 16 tokens, rank with half the experts: d >= 1536 1.01 to 1.46 | 0.98 to 1.40 times
-// as fast (f = 1024 to 4096; with 2 shared experts 1.01 to 1.35 | 1.00 to 1.31); d = 1024 with 4 parts 1.09 to 1.24 | 1.08 to 1.25, with 8 to 32
-// 0.90 to 1.07 | 0.87 to 1.08; d = 512 with 4 1.12 to 1.20 | 1.14 to 1.25, with 8 to 32 0.77 to 0.97 | 0.75 to 0.92; with 2 shared
-// experts and 10 to 18 parts d = 1024 1.13 to 1.38 | 1.09 to 1.34, d = 512 1.02 to 1.36 | 0.95 to 1.29.
-static bool joins_combine(int32_t T, int32_t k, int32_t d, int32_t f, int n_shared, int S, grace_dtype dt, int n_cu) {
-    const int64_t row = (int64_t)f * (dt == GRACE_F32 ? 4 : 2);
-    if (T > TINY_DOWN_T || k > GRACE_MAX_TOPK || row % 16 != 0 || 16 * row >= (int64_t)NO_DATA || std::max(n_shared, 1) * T * row >= (int64_t)NO_DATA) return false;
-    if (tiny_down_lds(T, k, S, n_shared, d, n_cu) > pers::LDS_BYTES) return false;
-    const int blocks = tiny_down_blocks(d, n_cu), parts = std::min(S, T * k) + n_shared;
-    return 8 * blocks >= 5 * n_cu || parts <= (n_shared ? std::max(16, blocks / 4) : 4);
-}
-
 extern "C" int grace_dispatch_ffn_down_share(const grace_table *table, int32_t rank, const int32_t *inst_off, const int32_t *perm_pos,
                                              const float *topk_weight, int32_t T, int32_t k, int32_t d, int32_t f, int32_t n_shared,
                                              grace_dtype dt, const void *w_down, const void *shared_down, void *y, void *y_shared,
@@ -751,8 +782,8 @@ extern "C" int grace_dispatch_ffn_down_share(const grace_table *table, int32_t r
     if (rc != GRACE_OK) return rc;
     const int n_cu = compute_units();
     if (n_cu <= 0) return fail(GRACE_EHIP, "%s: cannot query the device", who);
-    if (T == 0 || !out || !joins_dispatch(table, rank, T, k, d, f, dt, n_cu) || !joins_combine(T, k, d, f, n_shared, S, dt, n_cu)) {
-        rc = expert_ffn_down(who, table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream, true);
+    if (T == 0 || !out || !joins_dispatch(table, rank, T, k, d, f, n_shared, dt, n_cu) || !joins_combine(T, k, d, f, n_shared, S, dt, n_cu)) {
+        rc = expert_ffn_down(who, table, rank, inst_off, T, k, d, f, dt, w_down, y, state, false, ws, stream, n_shared);
         if (rc == GRACE_OK && n_shared) rc = grace_shared_ffn_down(T, d, f, n_shared, dt, shared_down, y_shared, ws_shared, stream);
         if (rc != GRACE_OK || !out) return rc;
         const void *ys = n_shared ? y_shared : nullptr;
@@ -791,7 +822,7 @@ extern "C" int grace_dispatch_joins_ffn(const grace_table *table, int32_t local_
     if (rc != GRACE_OK) return rc;
     if (n_cu == 0) n_cu = compute_units();
     if (n_cu <= 0) return fail(GRACE_EHIP, "dispatch_joins_ffn: cannot query the device");
-    *joined = T == 0 || !joins_dispatch(table, local_rank, T, k, d, f, dt, n_cu) ? 0 : joins_combine(T, k, d, f, n_shared, S, dt, n_cu) ? 2 : 1;
+    *joined = T == 0 || !joins_dispatch(table, local_rank, T, k, d, f, n_shared, dt, n_cu) ? 0 : joins_combine(T, k, d, f, n_shared, S, dt, n_cu) ? 2 : 1;
     return GRACE_OK;
 }
 
