@@ -12,6 +12,11 @@ from .binding import SHARE_STATE_INTS, GraceTable, _check, _dtype_code, _stream,
 STAGES = ("route", "permute", "route_permute", "dispatch_ffn_up", "ffn_up", "ffn_down", "shared_up", "shared_down", "ffn_shared_up", "ffn_shared_down", "ffn_down_combine", "combine")
 
 
+def dispatch_is_one_launch(T: int, k: int, E: int, I: int) -> bool:
+    """Whether grace_route_permute takes one launch, with the rows (its smallest batches, see grace_moe.h)."""
+    return max(E, I) <= 256 and T * k <= 1024 and 1 <= T <= (32 if E > 64 else 96 if k > 2 else 256)
+
+
 class GraceMoELayer:
     """route -> permute -> grouped expert FFN (local share) [-> shared FFN] -> combine.
 
@@ -72,9 +77,11 @@ class GraceMoELayer:
         # ahead of it otherwise), which then runs ahead of the expert FFN; False: the scatter is part of the dispatch call
         self.fuse_scatter = self.n_shared > 0
         # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows;
-        # elsewhere the dispatch call moves them (small batches in its one launch)
+        # elsewhere the dispatch call moves them.  So does a dispatch of one launch, which is no shorter without them: 99 steps of the 96-row kernel with
+        # the rows in the projection 0.96 to 1.01 times as fast, in the mean 0.99 (33 to 96 tokens of more than 64 experts, three launches, 1.03)
         self.gather_rows = not self.n_shared and S > 0 and T > 0 and (
-            grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I) or grace_ffn_joins_shared(True, T, d, f, 0, self.dt, k=k, S=S, I=table.I))
+            grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I) or
+            not dispatch_is_one_launch(T, k, table.E, table.I) and grace_ffn_joins_shared(True, T, d, f, 0, self.dt, k=k, S=S, I=table.I))
         # with shared experts: their projections in one launch with the experts' (grace_expert_shared_ffn_up_scatter, _down) where the library
         # does that; False: a call each
         self.join_shared = [self.n_shared > 0 and S > 0 and T > 0 and

@@ -6,6 +6,7 @@ import sys
 import pytest
 
 import paper_2509_25041_amd as grace
+from paper_2509_25041_amd.layer import dispatch_is_one_launch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -98,3 +99,28 @@ def test_smallest_batches_are_joined_where_that_is_faster(tmp_path, E, R, T, k, 
     assert (launches == 1) == (said > 0)
     if waves:
         assert first == waves
+
+
+DISPATCH = PRELUDE + r"""
+for E in (3, 64, 65, 200):
+    for k in (1, 2, 3, 11):
+        for T in (1, 32, 33, 85, 94, 96, 97, 256, 257) if k <= E else ():
+            for I in (E, 300):
+                h, ints = C.c_void_p(), lambda v: (i32 * len(v))(*v)
+                n = [I - E + 1] + [1] * (E - 1)
+                R = max(n)
+                assert lib.grace_table_create(C.byref(h), E, R, 1, ints([0] * R), ints([1] * R), ints([sum(n[:e]) for e in range(E + 1)]), ints(list(range(n[0])) + [0] * (E - 1)),
+                                              None) == 0, lib.grace_last_error()
+                C.c_int.in_dll(recorder, "n_recorded").value = 0
+                assert lib.grace_route_permute(h, 0, 0, at, T, E, k, 1, None, None, at, at, at, at, at, 64, 1, at, at, at, at, at, at, at, None) == 0, lib.grace_last_error()
+                print(T, k, E, I, C.c_int.in_dll(recorder, "n_recorded").value)
+                lib.grace_table_destroy(h)
+"""
+
+
+def test_layer_knows_where_the_dispatch_is_one_launch(tmp_path):
+    """The layer leaves the rows to such a dispatch, whose launch is no shorter without them."""
+    lines = [tuple(map(int, line.split())) for line in run(tmp_path, DISPATCH).splitlines()]
+    assert len(lines) > 200 and {n == 1 for *_, n in lines} == {True, False}
+    for *sizes, launches in lines:
+        assert dispatch_is_one_launch(*sizes) == (launches == 1), (sizes, launches)
