@@ -958,3 +958,41 @@ def test_narrow_rows_do_not_hold_up_the_launch_that_moves_them(d, n_shared):
             best = min(best, a.elapsed_time(b))
         times.append(best)
     assert times[0] <= 1.3 * times[1], times
+
+
+@pytest.mark.parametrize("T,k,R,n_shared,d,f,dtype", [
+    (16, 5, 3, 0, 256, 64, "bf16"), (5, 3, 3, 2, 512, 96, "bf16"), (8, 7, 2, 1, 132, 68, "f32"), (16, 5, 1, 1, 256, 64, "f32"), (3, 3, 1, 0, 2048, 64, "bf16"),
+])
+def test_joined_combine_of_weights_that_are_no_numbers(T, k, R, n_shared, d, f, dtype):
+    """Gate weights that are not finite, of this rank's rows and of others', and dropped positions: the one launch for the down projections and the
+    combine makes of its y what the combine makes of it, bit for bit."""
+    E, (tdt, dt) = 9, (torch.bfloat16, grace.GRACE_BF16) if dtype == "bf16" else (torch.float32, grace.GRACE_F32)
+    table = grace.GraceTable(E, R, 1, [0] * R, [1] * R, list(range(E + 1)), [e % R for e in range(E)])
+    assert grace.grace_dispatch_joins_ffn(table, 0, T, k, d, f, dt, n_shared=n_shared) == 2
+    S = len(table.local_experts(0))
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s: (torch.randn(s, generator=gen, device="cuda") * 0.1).to(tdt)
+    w, sh = [normal(S, f, d), normal(S, f, d), normal(S, d, f)], [normal(n_shared, f, d), normal(n_shared, f, d), normal(n_shared, d, f)] if n_shared else None
+    y, ys, state = normal(T * k, d).zero_(), normal(T, d) if n_shared else None, torch.zeros(8, dtype=torch.int32, device="cuda")
+    ws = torch.empty(grace.grace_workspace_bytes(T, E, k, E, d, f, 0, dt), dtype=torch.uint8, device="cuda")
+    ws2 = torch.empty(grace.grace_workspace_bytes(T, 1, 1, 1, d, f, n_shared, dt), dtype=torch.uint8, device="cuda")
+    route, perm = grace.grace_dispatch_ffn_up_share(table, 0, torch.randn((T, E), generator=gen, device="cuda"), k, normal(T, d), w[0], w[1], state, ws,
+                                                    shared=sh and sh[:2], ws_shared=ws2)
+    pos, weight = perm[0].view(T, k).clone(), route[1].clone()
+    here = pos < int(perm[2][S])     # (rank 0's rows are the first ones)
+    spoilt = torch.zeros(T, dtype=torch.bool, device="cuda")
+    for n, t in enumerate(range(0, T, 2)):
+        of = torch.nonzero(here[t] if n % 3 == 0 or R == 1 else ~here[t]).view(-1).tolist()
+        if not of:
+            continue
+        weight[t, of[-1]] = [float("nan"), float("inf"), -float("inf")][n % 3]
+        if n % 4 == 3:
+            pos[t, of[-1]] = T * k   # no row at all: its weight does not matter
+        else:
+            spoilt[t] = True
+    pos[1::4, 0] = -1
+    out = grace.grace_dispatch_ffn_down_share(table, 0, perm[2], pos.view(-1), weight, w[2], y, state, ws, sh and sh[2], ys, ws2)
+    want = grace.grace_combine(y, pos.view(-1), weight, ys) if R == 1 else grace.grace_combine_share(y, pos.view(-1), weight, state, ys)
+    torch.cuda.synchronize()
+    assert spoilt.any() and torch.equal(torch.isfinite(out.float()).all(1), ~spoilt)
+    assert torch.equal(out.isnan(), want.isnan()) and torch.equal(out.nan_to_num(), want.nan_to_num())
