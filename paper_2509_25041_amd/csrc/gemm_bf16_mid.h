@@ -263,37 +263,43 @@ inline int64_t grid_blocks(int64_t tiles, int n_cu, bool exact) {
 // of d = 4096, f = 14336, down 114 -> 60 us).  More halves than units are slower again (308 of 32 rows 16.0 us, 220 of 48 rows 15.0 us).
 // With fewer than four steps along K there is too little to cut: K = 128, 64 tiles of 4 to 16 segments whole 5.5, halved 6.7 us (K = 256, 48
 // tiles 7.0 -> 5.9 us).
-// Rows to their positions: a piece of 64 16-byte vectors of a token's row is read once and written k times, by one wavefront, AHEAD pieces at a time.  A
-// token's positions wait in the lanes (64 at a time), so that no store waits for a load of its own.  (By pieces, not with a workgroup per token:
-// narrow rows would leave its wavefronts idle.  Layer steps of 97 tokens, k = 2, f = 352, d = 256, 512, 1024 45.0, 45.7, 32.8 -> 20.4, 21.6, 24.6 us.)
+// Rows to their positions: a row is read once and written k times, by one, two or four wavefronts (narrow rows by as many as have a piece of 64
+// 16-byte vectors to move), AHEAD tokens at a time.  A token's positions wait in the lanes (64 at a time), so that no store waits for a load of its own.
+// (With the workgroup per token narrow rows leave its wavefronts idle: layer steps of 97 tokens, k = 2, f = 352, d = 256, 512, 1024 45.0, 45.7, 32.8 -> 20.4,
+// 21.6, 24.6 us.  Pieces dealt one by one are faster beside tiles whose weights come from HBM, 3001 tokens of d = 2048, f = 352, gate+up 56.9 -> 56.0 us, and
+// slower beside weights in the last-level cache, 47.2 -> 50.0.)
 constexpr int MOVE_AHEAD = 4;
 __host__ __device__ inline int move_pieces(int row_bytes) { return (row_bytes + 1023) >> 10; }   // of a row
 __device__ __forceinline__ void move_rows(const GemmArgs &g, int b, int movers) {
     const int vecs = g.sc_row_bytes >> 4, per_row = move_pieces(g.sc_row_bytes), n = g.sc_T * g.sc_k, lane = (int)threadIdx.x & 63;   // (n below 2^31)
-    const int wave = __builtin_amdgcn_readfirstlane(b * (THREADS / 64) + ((int)threadIdx.x >> 6)), waves = movers * (THREADS / 64);
-    const int64_t pieces = (int64_t)g.sc_T * per_row;   // (below 2^31, as the tokens' bytes are)
+    const int each_log = per_row >= 4 ? 2 : per_row == 2 ? 1 : 0;   // wavefronts of a token (three pieces: one after the other)
+    const int first = (b << (2 - each_log)) + (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) >> each_log), step = movers << (2 - each_log);
+    static_assert(THREADS == 256, "four wavefronts");
     const uint4 *const x = (const uint4 *)g.sc_x;
     uint4 *const xp = (uint4 *)g.sc_xp;
-    for (int64_t p0 = wave; p0 < pieces; p0 += MOVE_AHEAD * waves)
-        for (int j0 = 0; j0 < g.sc_k; j0 += 64) {
-            uint4 v[MOVE_AHEAD];
-            int pos[MOVE_AHEAD], c[MOVE_AHEAD];
+    for (int c0 = (int)threadIdx.x & ((64 << each_log) - 64); c0 < vecs; c0 += 64 << each_log) {   // whole wavefronts stay
+        const int c = min(c0 + lane, vecs - 1);
+        const bool store = c0 + lane < vecs;
+        for (int t0 = first; t0 < g.sc_T; t0 += MOVE_AHEAD * step)
+            for (int j0 = 0; j0 < g.sc_k; j0 += 64) {
+                uint4 v[MOVE_AHEAD];
+                int pos[MOVE_AHEAD];
 #pragma unroll
-            for (int i = 0; i < MOVE_AHEAD; ++i) {
-                const uint32_t piece = (uint32_t)min(p0 + i * waves, pieces - 1), t = piece / (uint32_t)per_row;
-                c[i] = (int)(piece - t * (uint32_t)per_row) * 64 + lane;
-                v[i] = x[(int64_t)t * vecs + min(c[i], vecs - 1)];
-                pos[i] = g.sc_pos[(int64_t)t * g.sc_k + min(j0 + lane, g.sc_k - 1)];
-            }
+                for (int i = 0; i < MOVE_AHEAD; ++i) {
+                    const int64_t t = min(t0 + i * step, g.sc_T - 1);
+                    v[i] = x[t * vecs + c];
+                    pos[i] = g.sc_pos[t * g.sc_k + min(j0 + lane, g.sc_k - 1)];
+                }
 #pragma unroll
-            for (int i = 0; i < MOVE_AHEAD; ++i) {
-                if (p0 + i * waves >= pieces) break;   // uniform
-                for (int j = 0; j < min(64, g.sc_k - j0); ++j) {
-                    const int p = __builtin_amdgcn_readlane(pos[i], j);
-                    if (p >= 0 && p < n && c[i] < vecs) nt_store16(v[i], &xp[(int64_t)p * vecs + c[i]]);
+                for (int i = 0; i < MOVE_AHEAD; ++i) {
+                    if (t0 + i * step >= g.sc_T) break;   // uniform
+                    for (int j = 0; j < min(64, g.sc_k - j0); ++j) {
+                        const int p = __builtin_amdgcn_readlane(pos[i], j);
+                        if (p >= 0 && p < n && store) nt_store16(v[i], &xp[(int64_t)p * vecs + c]);
+                    }
                 }
             }
-        }
+    }
 }
 
 // Workgroup number b of `grid` does its tiles.
