@@ -482,11 +482,12 @@ static bool joins_combine(int32_t T, int32_t k, int32_t d, int32_t f, int n_shar
 // 1.03 (0.91), 32 0.95 (0.82), 112 0.66 (118 instead of 74 us); fp32 up to 4 1.2 (1.04), 6 1.15 (0.95), 8 1.03 (0.91), 24 0.93 (0.82); up to 8 tokens with
 // shared experts up to 24 1.3 (1.03), 64 0.94 (0.77), where the combine is joined too up to 44 1.4 (1.04), 64 1.0 (0.91).
 // Pieces of 64 rows (fp32), more than 16 experts: the dispatch's workgroups have little less to do than a launch of their own, so it pays where all are resident at
-// once (joined_waves: two per compute unit), 0.96 to 1.24, beyond 0.67 to 0.95.  Narrow rows and many choices of many experts likewise: beyond 0.89 to 0.98.
+// once (joined_waves: two per compute unit), 0.96 to 1.24, beyond 0.67 to 0.95; rows of 4 KB and more up to one per compute unit, which the launcher still cuts
+// lower, 0.98 to 1.30 (219 tokens of 16 experts, d = 1536, f = 704, 352 pieces 43 -> 52 us).  Narrow rows and many choices of many experts likewise: beyond 0.89 to 0.98.
 static bool tiny_up_pays(int64_t tiles, bool pieces, int32_t T, int32_t k, int32_t d, int32_t f, int E, int S, int n_shared, grace_dtype dt, int n_cu) {
-    const int64_t most = pieces ? 2 : T > 32 ? 4 : T > 8 ? (dt == GRACE_BF16 ? 12 : 6) : joins_combine(T, k, d, f, n_shared, S, dt, n_cu) ? 56 : 24;
-    if (tiles > most * n_cu) return false;
     const int64_t row_bytes = (int64_t)d * (dt == GRACE_F32 ? 4 : 2);
+    const int64_t most = pieces ? (row_bytes >= 4096 ? 1 : 2) : T > 32 ? 4 : T > 8 ? (dt == GRACE_BF16 ? 12 : 6) : joins_combine(T, k, d, f, n_shared, S, dt, n_cu) ? 56 : 24;
+    if (tiles > most * n_cu) return false;
     if ((pieces && E > TINY_LANE_E) || (row_bytes <= 512 && E > 64 && T * k > 120)) return T + tiles <= 2 * (int64_t)n_cu;
     return true;
 }

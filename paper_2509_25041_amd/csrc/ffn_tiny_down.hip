@@ -6,7 +6,7 @@
 // added there in order, rounded as y is, written to y and combined.
 //
 // Bound by latency, then by the weights: 8 weight rows x 128 bytes per load (whole lines; tiny_parts.h).  d = 2048, f = 1024, k = 8: one token, rank with 16 of 64 experts, down and combine 5.4 + 1.9 us in two
-// launches -> 7.8 in one, and the launch between them; 16 tokens of 128 experts, f = 768, 8.4 + 3.4 -> 8.6.  Whole steps of one token 16.7 -> 15.4.
+// launches -> 7.5 in one, and the launch between them; 16 tokens of 128 experts, f = 768, 8.4 + 3.4 -> 8.6.  Whole steps of one token 16.7 -> 15.4.
 // Two shared experts are 2 more segments, not a launch of 5 to 9 us (steps of 2 to 16 tokens 1.15 to 1.35 times as fast).  Where it is the slower one: joins_combine.
 #include "ffn_tiny.h"
 #include "gemm_stream.h"

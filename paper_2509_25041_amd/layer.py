@@ -77,7 +77,7 @@ class GraceMoELayer:
         # ahead of it otherwise), which then runs ahead of the expert FFN; False: the scatter is part of the dispatch call
         self.fuse_scatter = self.n_shared > 0
         # without: the same with the experts' gate+up projection (grace_expert_ffn_up_share_scatter) where its launch carries the rows;
-        # elsewhere the dispatch call moves them.  So does a dispatch of one launch, which is no shorter without them: 99 steps of the 96-row kernel with
+        # elsewhere the dispatch call moves them.  So does a dispatch of one launch, which is no shorter without them: 116 steps of the 96-row kernel with
         # the rows in the projection 0.96 to 1.01 times as fast, in the mean 0.99 (33 to 96 tokens of more than 64 experts, three launches, 1.03)
         self.gather_rows = not self.n_shared and S > 0 and T > 0 and (
             grace_ffn_carries_rows(T, d, f, self.dt, k=k, S=S, I=table.I) or
@@ -184,7 +184,13 @@ class GraceMoELayer:
         """One layer step on torch's current stream.  With `events` (a list to
         append to), a pair of HIP events is recorded around every library call,
         or only around the calls named in `timed_stages`; `event_pool` supplies
-        pre-created timing events (popped two per timed call)."""
+        pre-created timing events (popped two per timed call).
+
+        The calls of a step, in order, and so the names that record something: one of the smallest batches (join_dispatch)
+        "dispatch_ffn_up" and "ffn_down_combine" (join_combine), or "ffn_down", which takes the shared experts along, and "combine";
+        fuse_scatter, gather_rows and join_shared do not act on it.  Any other step "route_permute" (or "route" and "permute"),
+        "shared_up" and "ffn_up" or both as "ffn_shared_up" (join_shared), "ffn_down" and "shared_down" or both as
+        "ffn_shared_down", "combine"."""
         stream = _stream()
         key = (logits.data_ptr(), x.data_ptr(), None if rr_in is None else rr_in.data_ptr(),
                None if rr_out is None else rr_out.data_ptr(), stream)

@@ -85,7 +85,7 @@ F32, BF16 = grace.GRACE_F32, grace.GRACE_BF16
     (128, 2, 16, 4, 1024, 512, 0, BF16, 1, 4), (16, 1, 14, 6, 1536, 2048, 0, F32, 0, None), (128, 1, 2, 4, 256, 3584, 0, BF16, 1, 8),
     # pieces of 64 rows: resident at once or not (the first one 34 and 51 us)
     (60, 16, 195, 2, 1024, 352, 0, F32, 0, None), (64, 16, 104, 1, 512, 1024, 0, F32, 0, None), (64, 16, 79, 6, 512, 352, 0, F32, 1, 8),
-    (8, 4, 256, 2, 128, 256, 0, F32, 1, 4),
+    (8, 4, 256, 2, 128, 256, 0, F32, 1, 4), (16, 8, 219, 1, 1536, 704, 0, F32, 0, None), (16, 8, 219, 1, 1536, 512, 0, F32, 1, 4),
     # narrow rows, many choices of many experts (the first one 18 us, 22 in one launch of 4 wavefronts, 16 of 16)
     (128, 16, 30, 8, 64, 352, 0, BF16, 1, 16), (64, 8, 63, 8, 256, 512, 0, BF16, 1, 8), (128, 8, 30, 6, 128, 704, 0, BF16, 0, None),
     (128, 8, 16, 8, 2048, 768, 0, BF16, 2, 4),
