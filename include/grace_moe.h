@@ -319,7 +319,7 @@ int grace_expert_ffn_down_share(const grace_table *table, int32_t rank, const in
  * the dispatch and the projection are one launch that lays the hidden activation out in ws by slots (row j of slot s at row s * T + j of
  * [S * T, f]), which _down_share then expects, and which takes the shared experts' projection along if that is streamed as well; up to 16
  * tokens the down projections and the combine can be one launch.  Elsewhere it is the calls one after the other; with out == NULL the combine is left
- * to the caller.  The same sizes, table
+ * to the caller.  The same sizes (n_shared among them), table
  * and rank in both calls.  Same results as the calls', those behind the gate+up projections up to the order of their sums.
  * DEVICE: as for these; x is not NULL (unless T == 0); shared pointers and y_shared are not used if n_shared == 0. */
 int grace_dispatch_ffn_up_share(const grace_table *table, int32_t local_rank, grace_policy policy, const float *logits, int32_t T, int32_t E,
